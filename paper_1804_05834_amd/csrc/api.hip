@@ -1405,7 +1405,24 @@ int32_t dqn_preprocess(const uint8_t *raw, int64_t n, int32_t height, int32_t wi
     if (n < 1 || n > 65535 || height < 1 || width < 1 || height > 4096 || width > 4096)
         return fail(nullptr, DQN_ERR_INVALID_ARG, "dqn_preprocess: n must be in 1..65535, height and width in 1..4096");
     hipStream_t st = (hipStream_t)stream;
-    misc::k_preprocess<<<dim3((net::FRAME + 255) / 256, (unsigned)n), 256, 0, st>>>(raw, height, width, grey_lut, frames);
+    // frames of at most four source rows per output row go through LDS, in bands of output rows: as few bands
+    // as keep a band's source rows within 12 KB (so that several workgroups share a CU) and, for few frames, as many
+    // as give every CU a workgroup
+    int bands = 1;
+    auto band_bytes = [&](int b) { return ((84 / b) * height / 84 + 3) * width + 32; };
+    static const int divisors[] = {1, 2, 3, 4, 6, 7, 12, 14, 21, 28, 42, 84};
+    for (int d : divisors) {
+        bands = d;
+        if (band_bytes(d) <= 12288 && (d >= 28 || n * d >= 256)) break;
+    }
+    if (height <= 4 * 84 && band_bytes(bands) <= 49152 && aligned(frames, 4)) {
+        const dim3 grid((unsigned)bands, (unsigned)n);
+        const long total = (long)n * height * width;
+        if (grey_lut) misc::k_preprocess_staged<true><<<grid, 256, band_bytes(bands), st>>>(raw, total, height, width, grey_lut, frames, 84 / bands);
+        else misc::k_preprocess_staged<false><<<grid, 256, band_bytes(bands), st>>>(raw, total, height, width, grey_lut, frames, 84 / bands);
+    } else {
+        misc::k_preprocess<<<dim3((net::FRAME + 255) / 256, (unsigned)n), 256, 0, st>>>(raw, height, width, grey_lut, frames);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(nullptr, DQN_ERR_HIP, std::string("dqn_preprocess: ") + hipGetErrorString(e));
     return DQN_OK;
