@@ -1531,21 +1531,21 @@ int32_t dqn_act_static(dqn_ctx *c, const uint8_t *obs, int32_t E, float epsilon,
 }
 
 // ------------------------------------------------------------ training
-static misc::SampleArgs sample_args(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed)
+static misc::SampleArgs sample_args(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed, int32_t *idx_out)
 {
     const Workspace &w = c->ws;
     // raw importance weights; the head kernel divides by their maximum
     return misc::SampleArgs{c->tree, c->L, c->levels, c->stored, B, beta, draw_seed, c->cfg.per_stratified,
                             w.b_idx, w.b_w,
                             misc::MetaGather{c->meta_a, c->meta_r, c->meta_done, w.b_a, w.b_r, w.b_done}, uniform_replay(c),
-                            c->slot_limit};
+                            c->slot_limit, idx_out};
 }
 
 // The sampling kernel of a replay-mode step.  The fp32 path copies the drawn frame stacks next
 // (its conv1 reads a materialised stack): there the two are one launch.
-static void enqueue_sample(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed, hipStream_t st)
+static void enqueue_sample(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed, int32_t *idx_out, hipStream_t st)
 {
-    const misc::SampleArgs S = sample_args(c, B, beta, draw_seed);
+    const misc::SampleArgs S = sample_args(c, B, beta, draw_seed, idx_out);
     if (c->cfg.precision == 0) {
         misc::GatherArgs G{(const uint8_t *)c->buf.replay_frames, c->meta_a, c->meta_r, c->meta_done,
                            (long)c->cfg.replay_capacity, c->ws.b_idx, c->ws.stack5, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -1603,9 +1603,6 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     long ss;
     int32_t rc = forward_trunk(c, w, passes, 3, &ns, &ss, st, draw);
     if (rc) return rc;
-    // the drawn indices exist once the sampling kernel, or the first forward kernel, has run
-    if (!batch && O.idx && hipMemcpyAsync(O.idx, w.b_idx, (size_t)B * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return fail(c, DQN_ERR_HIP, "dqn_train_step: copy failed");
 
     misc::HeadArgs H{};
     H.part = w.f1part; H.nsplit = ns; H.split_stride = ss;
@@ -1709,17 +1706,18 @@ int32_t dqn_train_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, float beta
     if (c->cfg.replay_capacity <= 0 || c->stored <= 0) return fail(c, DQN_ERR_STATE, "dqn_train_step: replay is empty");
     if (!(beta >= 0.f)) return fail(c, DQN_ERR_INVALID_ARG, "dqn_train_step: beta must be >= 0");
     const bool graphs = !c->prof && !c->graph_off && c->cap && c->side;
+    int32_t *idx_out = out ? out->idx : nullptr;   // written by whichever kernel draws
     if (!graphs && !in_kernel_draw_fits(c, B)) {
-        enqueue_sample(c, B, beta, draw_seed, st);
+        enqueue_sample(c, B, beta, draw_seed, idx_out, st);
         return enqueue_step(c, B, nullptr, out, st);
     }
     if (!graphs) {
         // the first forward kernel draws the transitions (and, in fp32, gathers their frames for the
         // weight gradient): one launch less on the critical path
-        const misc::SampleArgs S = sample_args(c, B, beta, draw_seed);
+        const misc::SampleArgs S = sample_args(c, B, beta, draw_seed, idx_out);
         return enqueue_step(c, B, nullptr, out, st, &S);
     }
-    enqueue_sample(c, B, beta, draw_seed, st);
+    enqueue_sample(c, B, beta, draw_seed, idx_out, st);
 
     dqn_ctx::StepGraph *g = nullptr;
     if (graphs) {
@@ -1752,7 +1750,6 @@ int32_t dqn_train_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, float beta
         add(out->y, w.o_y, B);
         add(out->td, w.o_td, B);
         add(out->a_star, w.o_astar, B);
-        add(out->idx, w.b_idx, B);
         add(out->is_w, w.o_isw, B);
         add(out->td_abs_mean, w.o_loss + 1, 1);
         add(out->q_max_mean, w.o_loss + 2, 1);

@@ -61,6 +61,7 @@ struct SampleArgs {
     int uniform;   // 1: every stored slot has leaf 1 (priority exponent 0, tree built by a bulk fill): no tree reads
     long limit;    // slots that may hold a transition are [0, limit): `size` for one stream; with many
                    // environment streams the stored transitions are not the first `size` slots
+    int32_t *idx_out;   // the caller's copy of the drawn slots, or nullptr
 };
 
 // The mass the draws are scaled by: the root of the tree; in uniform mode the number of stored slots
@@ -201,9 +202,9 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
 __device__ __forceinline__ void per_sample_emit(const SampleArgs &A, int j, long slot, float total, float leaf)
 {
     A.idx[j] = (int32_t)slot;
-    if (A.uniform) {
-        A.is_w[j] = 1.f;   // (N * 1/N)^-beta
-    } else {
+    if (A.idx_out) A.idx_out[j] = (int32_t)slot;
+    float w = 1.f;   // uniform: (N * 1/N)^-beta
+    if (!A.uniform) {
         const double P = (double)leaf / (double)total;
         // a tree without mass (every stored transition has priority zero) has nothing to draw: weight 0
         A.is_w[j] = total > 0.f ? (float)pow((double)A.size * P, -(double)A.beta) : 0.f;
