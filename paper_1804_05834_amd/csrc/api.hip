@@ -1341,14 +1341,10 @@ int32_t dqn_replay_store(dqn_ctx *c, int64_t n, const uint8_t *frames, const int
         return fail(c, DQN_ERR_INVALID_ARG, "dqn_replay_store: NULL argument or frames not 16-byte aligned");
     hipStream_t st = (hipStream_t)stream;
     const int64_t h0 = c->cursor;
-    launch(c, "replay_write", st, [&] {
-        misc::k_replay_write<<<dim3((unsigned)n), 256, 0, st>>>((uint8_t *)c->buf.replay_frames, c->meta_a, c->meta_r,
-                                                                c->meta_done, cap, h0, frames, a, r, done);
-    });
-    launch(c, "store_priorities", st, [&] {
-        misc::k_store_priorities<<<1, (int)((n + 4 + 63) / 64 * 64), 0, st>>>(c->tree, c->L, c->levels, cap, h0, c->seq,
-                                                                             (int)n, c->meta_done, c->cfg.per_alpha);
-    });
+    const misc::StoreArgs A{(uint8_t *)c->buf.replay_frames, c->meta_a, c->meta_r, c->meta_done, cap, h0, c->seq, (int)n,
+                            frames, a, r, done, c->tree, c->L, c->levels, c->cfg.per_alpha};
+    const unsigned block = std::max(256u, (unsigned)(n + 4 + 63) / 64 * 64);
+    launch(c, "replay_store", st, [&] { misc::k_replay_store<<<dim3((unsigned)n + 1), block, 0, st>>>(A); });
     c->leaves_all_one = false;
     c->cursor = (h0 + n) % cap;
     c->seq += n;
@@ -1372,13 +1368,11 @@ int32_t dqn_replay_store_envs(dqn_ctx *c, int32_t E, const uint8_t *frames, cons
     hipStream_t st = (hipStream_t)stream;
     const long C = (long)(cap / E);
     const long t = (long)c->seq, l = t % C;
-    // two launches: the time steps with the leaves they settle, then the tree above the leaves
-    launch(c, "replay_write", st, [&] {
-        misc::k_replay_write_envs<<<dim3((unsigned)E), 256, 0, st>>>((uint8_t *)c->buf.replay_frames, c->meta_a, c->meta_r,
-                                                                     c->meta_done, C, l, frames, a, r, done, c->tree, c->L,
-                                                                     t, c->cfg.per_alpha);
-    });
-    rebuild_tree(c, st);
+    const int BL = tree_block_leaves(c), nblk = (int)(c->L / BL);
+    const misc::StoreEnvsArgs A{(uint8_t *)c->buf.replay_frames, c->meta_a, c->meta_r, c->meta_done, E, (int)C, (int)l, t,
+                                frames, a, r, done, c->tree, c->L, BL, nblk, c->cfg.per_alpha, tree_counter(c, 1)};
+    launch(c, "store_envs", st, [&] { misc::k_store_envs<<<dim3((unsigned)(nblk + E)), 256, 0, st>>>(A); });
+    finish_tree(c, st);
     c->envs = E;
     c->sub = C;
     c->slot_limit = (long)E * C;

@@ -929,36 +929,118 @@ __global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A)
     per_update_body<1>(A, lds);
 }
 
-// Store path (Alg.2 "store transition with maximal priority"): n time steps have just been
-// written to ring slots h0 .. h0+n-1 (stream positions seq0 .. seq0+n-1).  Thread j settles
-// the leaf of slot h0-1+j: for j < n that transition has just become complete (its s' ends in a
-// new frame) and enters with leaf = fp32(max_p^alpha), unless its state stack would reach back
-// before the start of the stream or across an episode end (done at one of the three slots
-// before it), in which case it is never sampled (leaf 0); the last written slot (not complete
-// yet) and the three after it, whose windows mix the newest frames with the oldest (j = n ..
-// n+3), get leaf 0.
-// One workgroup, n + 4 <= 1024 distinct slots, then the same level-by-level walk as above.
-__global__ __launch_bounds__(1024) void k_store_priorities(float *tree, long L, int levels, long cap,
-                                                           long h0, long seq0, int n,
-                                                           const uint8_t *done, float alpha)
+// Repair of the tree above `cnt` CONSECUTIVE leaves first .. first + cnt - 1 (heap indexes), whose new values
+// stand in val[0 .. cnt) (LDS, at least cnt + 1 floats): at every level the touched nodes are one run, and the
+// only other nodes a level needs are the sibling left of the run and the one right of it, which no leaf of the
+// run lies under.  So all of them are requested at once (sib[0 .. 2 * levels), the caller's sibling_load) and
+// the walk to the root is one round trip to memory instead of one per level; node = left + right in fp32 as
+// everywhere, so the bits are those of any other order of repair.  While a run is wider than two nodes the
+// workgroup halves it in LDS, from there on wave 0 carries it in registers.  Every thread must call this.
+// Measured (one time step, 1M-slot ring): 3.3 us for the whole store as one launch, against 3.3 + 5.7 us and
+// a second launch for the frame copy and the level-by-level walk.
+__device__ __forceinline__ float sibling_load(const float *tree, int first, int cnt, int levels, int t)
 {
-    const int j = threadIdx.x;
-    const bool walk = j < n + 4;
-    long slot = (h0 - 1 + j) % cap;
-    if (slot < 0) slot += cap;
+    // t < levels: left sibling of level t's run; t in [64, 64 + levels): right sibling (levels <= 30)
+    const int l = t & 63;
+    if (t >= 128 || l >= levels) return 0.f;
+    const int lo = first >> l, hi = (first + cnt - 1) >> l;
+    const bool want = t < 64 ? (lo & 1) : !(hi & 1);
+    return want ? tree[t < 64 ? lo - 1 : hi + 1] : 0.f;
+}
+__device__ __forceinline__ void tree_repair_run(float *tree, int first, int cnt, int levels, float *val, const float *sib)
+{
+    const int tid = threadIdx.x, nt = blockDim.x;
+    int lo = first, hi = first + cnt - 1, l = 0;
+    __syncthreads();
+    while (hi - lo > 1) {   // uniform
+        const int plo = lo >> 1, phi = hi >> 1;
+        for (int i = tid; i <= hi - lo; i += nt) tree[lo + i] = val[i];
+        float pv = 0.f;      // a parent run is at most half as long plus one: one parent per thread
+        const int p = plo + tid;
+        if (p <= phi)
+            pv = (2 * p < lo ? sib[l] : val[2 * p - lo]) + (2 * p + 1 > hi ? sib[64 + l] : val[2 * p + 1 - lo]);
+        __syncthreads();
+        if (p <= phi) val[tid] = pv;
+        __syncthreads();
+        lo = plo; hi = phi; ++l;
+    }
+    if (tid >= 64) return;
+    float x0 = val[0], x1 = val[hi - lo];
+    for (;; ++l) {
+        if (tid == 0) tree[lo] = x0;
+        if (tid == 1 && hi != lo) tree[hi] = x1;
+        if (l >= levels) break;
+        const float sl = sib[l], sr = sib[64 + l];
+        if (hi == lo) x0 = x1 = (lo & 1) ? sl + x0 : x0 + sr;
+        else if (lo & 1) { x0 = sl + x0; x1 = x1 + sr; }
+        else x0 = x1 = x0 + x1;
+        lo >>= 1; hi >>= 1;
+    }
+}
+
+// Store path (Alg.1 "store transition", Alg.2 "with maximal priority"): n time steps go to ring slots
+// h0 .. h0+n-1 (stream positions seq0 .. seq0+n-1).  Workgroups 1 .. n copy a time step each; workgroup 0
+// settles the leaves and the tree, which depend on earlier time steps and on the flags in `done` only, so
+// both run in one launch.  Thread j of workgroup 0 settles the leaf of slot h0-1+j: for j < n that transition
+// becomes complete (its s' ends in a new frame) and enters with leaf = fp32(max_p^alpha), unless its state
+// stack would reach back before the start of the stream or across an episode end (done at one of the three
+// slots before it), in which case it is never sampled (leaf 0); the last written slot (not complete
+// yet) and the three after it, whose windows mix the newest frames with the oldest (j = n ..
+// n+3), get leaf 0.  n + 4 <= 1024 distinct slots; blockDim.x >= n + 4.
+struct StoreArgs {
+    uint8_t *frames;
+    int32_t *meta_a;
+    float *meta_r;
+    uint8_t *meta_done;
+    long cap, h0, seq0;
+    int n;
+    const uint8_t *src;
+    const int32_t *a;
+    const float *r;
+    const uint8_t *done;
+    float *tree;
+    long L;
+    int levels;
+    float alpha;
+};
+__global__ __launch_bounds__(1024) void k_replay_store(StoreArgs A)
+{
+    if (blockIdx.x > 0) {
+        const long j = (long)blockIdx.x - 1;
+        const long slot = (A.h0 + j) % A.cap;
+        const uint4 *s = reinterpret_cast<const uint4 *>(A.src + j * net::FRAME);
+        uint4 *d = reinterpret_cast<uint4 *>(A.frames + slot * net::FRAME);
+        for (int t = threadIdx.x; t < net::FRAME / 16; t += blockDim.x) d[t] = s[t];
+        if (threadIdx.x == 0) {
+            A.meta_a[slot] = A.a[j];
+            A.meta_r[slot] = A.r[j];
+            A.meta_done[slot] = A.done[j];
+        }
+        return;
+    }
+    __shared__ float val[1026], sib[128];
+    const int j = threadIdx.x, n = A.n, cnt = n + 4;
+    long slot = (A.h0 - 1 + j) % A.cap;
+    if (slot < 0) slot += A.cap;
+    const bool run = A.h0 >= 1 && A.h0 - 1 + cnt <= A.cap;   // the slots do not wrap around the ring's end
+    const int first = (int)(A.L + A.h0 - 1);
+    const float mp = A.tree[2 * A.L];
+    const float sv = run && j < 128 ? sibling_load(A.tree, first, cnt, A.levels, j) : 0.f;
     float v = 0.f;
     if (j < n) {
-        const long q = seq0 - 1 + j;  // stream position of the transition's own frame
-        bool valid = q >= 3;
+        bool valid = A.seq0 - 1 + j >= 3;   // stream position of the transition's own frame
 #pragma unroll
         for (int k = 1; k <= 3; ++k) {
             long sk = slot - k;
-            if (sk < 0) sk += cap;
-            if (done[sk]) valid = false;
+            if (sk < 0) sk += A.cap;
+            if (q >= 0 ? A.done[q] : A.meta_done[sk]) valid = false;
         }
-        if (valid) v = (float)pow((double)tree[2 * L], (double)alpha);
+        if (valid) v = (float)pow((double)mp, (double)A.alpha);
     }
-    tree_walk(tree, (int)(L + slot), v, walk, levels);
+    if (!run) return tree_walk(A.tree, (int)(A.L + slot), v, j < cnt, A.levels);   // uniform for the workgroup
+    if (j < cnt) val[j] = v;
+    if (j < 128) sib[j] = sv;
+    tree_repair_run(A.tree, first, cnt, A.levels, val, sib);
 }
 
 // Frame preprocessing (Sec.3: palette frame -> grey-scale -> linear interpolation to 84 x 84).
@@ -1118,6 +1200,8 @@ __global__ __launch_bounds__(256) void k_replay_write(uint8_t *frames, int32_t *
 // wide loads and the fetches go to LDS.  252 threads: thread t keeps column t % 84 (its source columns and
 // weight stay in registers) and walks down every third row; four neighbouring lanes put their bytes into one
 // 4-byte store (84 is a multiple of 4, so such a quad lies in one row).  Same arithmetic, same bytes.
+            // a flag of this call is read from the caller's array: its slot is being written meanwhile
+            const int q = j - 1 - k;
 // Dynamic LDS: the staged rows.
 template <bool LUT>
 __global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, long total, int H, int W, const float *lut,
@@ -1153,6 +1237,78 @@ __global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, l
     }
     if (LUT) grey_tab[tid] = lut[tid];
     if (tid < rows) {
+// The same for frames of ordinary size (at most four source rows per output row): a workgroup owns `rows` output rows
+// of one frame, copies the source rows under them into LDS with 16-byte loads and blends out of LDS, the grey table
+// in LDS as well.  The one-thread-per-pixel kernel above is bound by its eight scattered one-byte and table
+// fetches per pixel (77.5 us for 2048 frames of 210 x 160, 83 MB: 1.07 TB/s); here memory sees each byte once in
+// wide loads and the fetches go to LDS.  252 threads: thread t keeps column t % 84 (its source columns and
+// weight stay in registers) and walks down every third row; four neighbouring lanes put their bytes into one
+// 4-byte store (84 is a multiple of 4, so such a quad lies in one row).  Same arithmetic, same bytes.
+// Dynamic LDS: the staged rows.
+template <bool LUT>
+__global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, long total, int H, int W, const float *lut,
+                                                           uint8_t *out, int rows)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t px_dyn[];
+    __shared__ float grey_tab[256];
+    __shared__ int row_at[84];
+    __shared__ float row_f[84];
+    const int tid = threadIdx.x, i0 = blockIdx.x * rows;
+    auto source = [](int o, int N, int &at, float &f) {   // exact source coordinate of output line o, clamped
+        const int q = min(max((2 * o + 1) * N - 84, 0), 168 * (N - 1));
+        at = q / 168;
+        f = (float)(q % 168) / 168.f;
+    };
+    int ya, yb;
+    float f;
+    source(i0, H, ya, f);
+    source(i0 + rows - 1, H, yb, f);
+    const int yend = min(yb + 1, H - 1);
+    const long beg = ((long)blockIdx.y * H + ya) * W;        // bytes of `raw`
+    const int len = (yend - ya + 1) * W;
+    const int mis = (int)((uintptr_t)(raw + beg) & 15);
+    const uint8_t *al = raw + beg - mis;                       // 16-byte aligned
+    for (int g = tid; 16 * g < mis + len; g += 256) {
+        const long first = beg - mis + 16L * g;
+        if (first >= 0 && first + 16 <= total) {
+            *reinterpret_cast<uint4 *>(px_dyn + 16 * g) = *reinterpret_cast<const uint4 *>(al + 16 * g);
+        } else {   // the first and the last bytes of the whole array
+            for (int b = 0; b < 16; ++b)
+                if (first + b >= 0 && first + b < total) px_dyn[16 * g + b] = al[16 * g + b];
+        }
+    }
+    if (LUT) grey_tab[tid] = lut[tid];
+    if (tid < rows) {
+        int at;
+        source(i0 + tid, H, at, row_f[tid]);
+        row_at[tid] = mis + (at - ya) * W;
+    }
+    __syncthreads();
+    if (tid >= 252) return;
+    const int j = tid % 84, rg = tid / 84;
+    int x0;
+    float fx;
+    source(j, W, x0, fx);
+    const int x1 = min(x0 + 1, W - 1);
+    uint8_t *dst = out + (long)blockIdx.y * net::FRAME + (long)i0 * 84 + (j & ~3);
+    for (int i = rg; i < rows; i += 3) {
+        const int at = row_at[i];
+        const float fy = row_f[i];
+        const int below = at + W < mis + len ? at + W : at;   // the last source row has no row below it
+        auto grey = [&](int q) {
+            const uint8_t b = px_dyn[q];
+            return LUT ? grey_tab[b] : (float)b;
+        };
+        const float top = grey(at + x0) * (1.f - fx) + grey(at + x1) * fx;
+        const float bot = grey(below + x0) * (1.f - fx) + grey(below + x1) * fx;
+        const float v = top * (1.f - fy) + bot * fy;
+        uint32_t b = (uint32_t)(uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f) << (8 * (j & 3));
+        b |= __shfl_xor(b, 1, 64);
+        b |= __shfl_xor(b, 2, 64);
+        if ((j & 3) == 0) *reinterpret_cast<uint32_t *>(dst + 84 * i) = b;
+    }
+}
+
         int at;
         source(i0 + tid, H, at, row_f[tid]);
         row_at[tid] = mis + (at - ya) * W;
