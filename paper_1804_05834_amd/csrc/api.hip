@@ -264,10 +264,16 @@ void launch(dqn_ctx *c, const char *name, hipStream_t st, F &&f)
     f();
 }
 
-// Every internal node of the sum-tree from its leaves, twelve levels per launch.
-void rebuild_tree(dqn_ctx *c, hipStream_t st)
+// Launch shape of a kernel that builds the whole sum-tree from its leaves: blocks of BL leaves.  The state area
+// behind the heap holds the maximal priority (word 0) and the arrival counters of the launches whose last
+// workgroup finishes the work (words 1 and 2; 0 between launches).
+int tree_block_leaves(const dqn_ctx *c) { return (int)std::min<long>(c->L, 4096); }
+unsigned *tree_counter(dqn_ctx *c, int k) { return reinterpret_cast<unsigned *>(c->tree + 2 * c->L + k); }
+// What such a launch leaves to do: the levels above the blocks' roots of a tree of more than 4096 x 4096 leaves
+void finish_tree(dqn_ctx *c, hipStream_t st)
 {
-    for (long Lcur = c->L; Lcur >= 2; Lcur >>= 12) {
+    if (c->L >> 12 <= 4096) return;   // built by the launch's last workgroup
+    for (long Lcur = c->L >> 12; Lcur >= 2; Lcur >>= 12) {
         const int BL = (int)std::min<long>(Lcur, 4096);
         launch(c, "tree_rebuild", st, [&] { misc::k_tree_rebuild<<<dim3((unsigned)(Lcur / BL)), 256, 0, st>>>(c->tree, Lcur, BL); });
         if (Lcur <= 4096) break;
@@ -1267,10 +1273,11 @@ int32_t per_fill(dqn_ctx *c, const float *priorities, int64_t n, void *stream)
     if (n > 0 && (!priorities || !aligned(priorities, 16))) return fail(c, DQN_ERR_INVALID_ARG, "per_fill: priorities NULL or misaligned");
     hipStream_t st = (hipStream_t)stream;
     const long L = c->L;
-    launch(c, "tree_leaves", st, [&] {
-        misc::k_tree_leaves<<<grid1(L, 256), 256, 0, st>>>(c->tree, L, priorities, n, c->cfg.per_alpha);
+    const int BL = tree_block_leaves(c);
+    launch(c, "tree_fill", st, [&] {
+        misc::k_tree_fill<<<dim3((unsigned)(L / BL)), 256, 0, st>>>(c->tree, L, BL, priorities, n, c->cfg.per_alpha, tree_counter(c, 1));
     });
-    rebuild_tree(c, st);
+    finish_tree(c, st);
     c->envs = 0;
     c->sub = (long)c->cfg.replay_capacity;
     c->slot_limit = n;
@@ -1292,9 +1299,8 @@ int32_t per_sample(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed, int32_
     launch(c, "per_sample", st, [&] {
         misc::k_per_sample<<<(B + 3) / 4, 256, 0, st>>>(misc::SampleArgs{
             c->tree, c->L, c->levels, c->stored, B, beta, draw_seed, c->cfg.per_stratified, idx, is_w, misc::MetaGather{},
-            uniform_replay(c), c->slot_limit});
+            uniform_replay(c), c->slot_limit, nullptr}, tree_counter(c, 2));
     });
-    launch(c, "per_normalise", st, [&] { misc::k_per_normalise<<<1, 1024, 0, st>>>(is_w, B); });
     return hip_status(c, "per_sample");
 }
 
@@ -1547,7 +1553,7 @@ static void enqueue_sample(dqn_ctx *c, int32_t B, float beta, uint64_t draw_seed
         launch(c, "sample_gather", st, [&] { misc::k_sample_gather<<<dim3(B, 5), 256, 0, st>>>(S, G); });
         return;
     }
-    launch(c, "per_sample", st, [&] { misc::k_per_sample<<<(B + 3) / 4, 256, 0, st>>>(S); });
+    launch(c, "per_sample", st, [&] { misc::k_per_sample<<<(B + 3) / 4, 256, 0, st>>>(S, nullptr); });
 }
 
 // Enqueues every kernel of one training step on st (and on the side streams, which fork from

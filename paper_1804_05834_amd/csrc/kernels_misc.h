@@ -629,105 +629,271 @@ __global__ void k_fill(float *p, float v, long n)
 // ------------------------------------------------------------- sum-tree
 // Heap layout: tree[1] root, children of i at 2i and 2i+1, leaves at
 // tree[L..2L); tree[2L] holds the running maximum priority.
-__global__ void k_tree_leaves(float *tree, long L, const float *p, long n, float alpha)
+// Internal nodes from the leaves, twelve levels per pass.  The tree over Lcur leaves (leaves at
+// tree[Lcur, 2 Lcur)) is cut into blocks of BL = min(Lcur, 4096) leaves, sixteen leaves per thread: a thread
+// forms the four levels above its own leaves in registers, a wave the next six by lane exchange, wave 0 the
+// last two from the waves' sums in LDS, so the block waits at ONE barrier (a barrier per level and an LDS
+// copy of the block took 6.9 us per launch at a million leaves, this 4).  Node = left + right in fp32, so every
+// node has the bits that any other order of repair gives.
+// v: the thread's sixteen leaves (threads at or past BL / 16 do not count); 16 <= BL <= 4096; b: number of the
+// block.  Returns the block's root in every thread of wave 0.  sh: 4 floats of LDS.
+__device__ __forceinline__ float tree_block16(float *tree, long Lcur, int BL, long b, const float (&v)[16], float *sh)
 {
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= L) return;
-    tree[L + i] = i < n ? (float)pow((double)p[i], (double)alpha) : 0.f;
-    if (i == 0) tree[0] = 0.f;
-}
-__global__ void k_tree_level(float *tree, long first, long count)
-{
-    long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    long node = first + i;
-    tree[node] = tree[2 * node] + tree[2 * node + 1];
-}
-
-// Rebuild of the internal nodes from the leaves, 12 levels per launch: the tree over Lcur leaves
-// (leaves at tree[Lcur, 2 Lcur)) is cut into blocks of BL = min(Lcur, 4096) leaves; a workgroup loads
-// its block's leaves, forms the block's sub-tree in LDS level by level (node = left + right in fp32,
-// so every node has the bits any other order of repair gives) and writes its BL - 1 internal
-// nodes.  The block roots are the leaves of the tree one launch up: Lcur >> 12 of them.
-// The block of BL leaves number b of the tree over Lcur leaves; t: 2 * 4096 floats of LDS
-__device__ __forceinline__ void tree_block(float *tree, long Lcur, int BL, long b, float *t)
-{
-    const long root = Lcur / BL + b;          // heap index of the block root
-    for (int i = threadIdx.x; i < BL; i += 256) t[BL + i] = tree[Lcur + b * BL + i];
-    for (int first = BL >> 1; first >= 1; first >>= 1) {
+    const int tid = threadIdx.x, nthr = BL / 16;
+    const bool on = tid < nthr;
+    long at = (Lcur + b * BL) / 2 + 8L * tid;   // heap index of the thread's first node, one level up
+    float w8[8], w4[4], w2[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w8[i] = v[2 * i] + v[2 * i + 1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w4[i] = w8[2 * i] + w8[2 * i + 1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w2[i] = w4[2 * i] + w4[2 * i + 1];
+    float s = w2[0] + w2[1];
+    if (on) {
+        // (a run of eight nodes starts at a multiple of eight; the heap itself is 256-byte aligned)
+        *reinterpret_cast<float4 *>(tree + at) = float4{w8[0], w8[1], w8[2], w8[3]};
+        *reinterpret_cast<float4 *>(tree + at + 4) = float4{w8[4], w8[5], w8[6], w8[7]};
+        *reinterpret_cast<float4 *>(tree + at / 2) = float4{w4[0], w4[1], w4[2], w4[3]};
+        *reinterpret_cast<float2 *>(tree + at / 4) = float2{w2[0], w2[1]};
+        tree[at / 8] = s;
+    }
+    at /= 8;
+#pragma unroll
+    for (int k = 1; k <= 6; ++k) {
+        s += __shfl_xor(s, 1 << (k - 1), 64);
+        if (on && (nthr >> k) >= 1 && (tid & ((1 << k) - 1)) == 0) tree[at >> k] = s;
+    }
+    if (nthr > 64) {   // uniform
+        if ((tid & 63) == 0) sh[tid >> 6] = s;
         __syncthreads();
-        for (int i = threadIdx.x; i < first; i += 256) t[first + i] = t[2 * (first + i)] + t[2 * (first + i) + 1];
+        if (tid < 64) {
+            const int nw = nthr / 64;   // 2 or 4 waves
+            const long top = (Lcur + b * BL) / 1024;
+            float a0 = sh[0] + sh[1], a1 = 0.f;
+            if (nw == 4) a1 = sh[2] + sh[3];
+            if (tid == 0) {
+                tree[top / 2] = a0;
+                if (nw == 4) {
+                    tree[top / 2 + 1] = a1;
+                    tree[top / 4] = a0 + a1;
+                }
+            }
+            s = nw == 4 ? a0 + a1 : a0;
+        }
     }
-    __syncthreads();
-    // local node p at depth d (p in [2^d, 2^(d+1))) is heap node (root << d) + (p - 2^d)
-    for (int p = 1 + threadIdx.x; p < BL; p += 256) {
-        const int d = 31 - __clz(p);
-        tree[(root << d) + (p - (1 << d))] = t[p];
+    return s;
+}
+__device__ __forceinline__ void tree_load16(const float *tree, long Lcur, int BL, long b, float (&v)[16])
+{
+    const float4 *p = reinterpret_cast<const float4 *>(tree + Lcur + b * BL + 16L * ((int)threadIdx.x < BL / 16 ? threadIdx.x : 0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 q = p[i];
+        v[4 * i] = q.x; v[4 * i + 1] = q.y; v[4 * i + 2] = q.z; v[4 * i + 3] = q.w;
     }
 }
+// a block of any launch above the leaves' own (trees of more than 4096 x 4096 leaves only)
 __global__ __launch_bounds__(256) void k_tree_rebuild(float *tree, long Lcur, int BL)
 {
-    __shared__ float t[2 * 4096];             // local heap: t[1] block root, leaves at t[BL, 2 BL)
-    tree_block(tree, Lcur, BL, blockIdx.x, t);
-}
-// One thread per stream: the leaves the new time step settles, by the rules of the one-stream store
-// path applied to the stream's own sub-ring (see k_store_priorities): the transition at local slot
-// l - 1 has just become complete and enters with leaf = fp32(max_p^alpha) unless its state stack
-// would reach back before the stream's start (t - 1 < 3) or across an episode end; the slot just
-// written and the three after it get leaf 0.  Reads only transition data of earlier time steps.
-// The internal nodes are rebuilt afterwards.
-__device__ __forceinline__ void store_leaves_env(float *tree, long L, long C, long l, long t, long e,
-                                                 const uint8_t *done, float alpha)
-{
-    const long base = e * C;
-    auto at = [&](long k) { long q = (l + k) % C; if (q < 0) q += C; return base + q; };
-    if (t >= 1) {
-        bool valid = t - 1 >= 3;
-        for (int k = 2; k <= 4; ++k)
-            if (done[at(-k)]) valid = false;
-        tree[L + at(-1)] = valid ? (float)pow((double)tree[2 * L], (double)alpha) : 0.f;
+    __shared__ float sh[4];
+    if (BL < 16) {
+        if (threadIdx.x == 0)
+            for (long i = Lcur - 1; i >= 1; --i) tree[i] = tree[2 * i] + tree[2 * i + 1];
+        return;
     }
-    for (int k = 0; k < 4; ++k) tree[L + at(k)] = 0.f;
+    float v[16];
+    tree_load16(tree, Lcur, BL, blockIdx.x, v);
+    (void)tree_block16(tree, Lcur, BL, blockIdx.x, v, sh);
 }
-// grid (E): frame and transition data of stream e (waves 0..3), and its leaves (one thread of the last wave)
-__global__ __launch_bounds__(256) void k_replay_write_envs(uint8_t *frames, int32_t *meta_a, float *meta_r,
-                                                           uint8_t *meta_done, long C, long l,
-                                                           const uint8_t *src, const int32_t *a,
-                                                           const float *r, const uint8_t *done,
-                                                           float *tree, long L, long t, float alpha)
+
+// ---- work that the last workgroup of a launch to arrive does for all of them
+// A workgroup hands over its few words with device-scope stores, waits until they are acknowledged and draws
+// a number; the one that draws the last reads all words with device-scope loads.  Only those words are made
+// visible beyond the die's L2: a device-wide fence here would write the whole L2 back, a thousand times a
+// launch.  No workgroup waits for another.  The counter is 0 before the launch and the last one puts it back.
+__device__ __forceinline__ void publish_word(float *p, float v)
 {
-    const long e = blockIdx.x, slot = e * C + l;
-    if (threadIdx.x == 192) store_leaves_env(tree, L, C, l, t, e, meta_done, alpha);
-    const uint4 *s = reinterpret_cast<const uint4 *>(src + e * net::FRAME);
-    uint4 *d = reinterpret_cast<uint4 *>(frames + slot * net::FRAME);
-    for (int t4 = threadIdx.x; t4 < net::FRAME / 16; t4 += 256) d[t4] = s[t4];
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float read_word(const float *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// called by one thread, after the barrier behind which all of the workgroup's words have been stored and
+// acknowledged (words_acknowledged() by the threads that stored them)
+__device__ __forceinline__ void words_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ bool arrived_last(unsigned *count, unsigned of)
+{
+    const unsigned k = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (k != of - 1) return false;
+    __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+// Whole tree in one launch: every workgroup builds the block of leaves it holds in registers, and the one that
+// arrives last builds the levels above the nblk block roots (nblk <= 4096; more: k_tree_rebuild goes on).
+// Must be called by all 256 threads.  count: one word of the tree's state area.
+__device__ __forceinline__ void tree_build_leaves(float *tree, long L, int BL, long b, int nblk, const float (&v)[16],
+                                                  unsigned *count, float *sh /*8*/)
+{
+    const float root = tree_block16(tree, L, BL, b, v, sh);
+    if (nblk == 1 || nblk > 4096) return;
     if (threadIdx.x == 0) {
-        meta_a[slot] = a[e];
-        meta_r[slot] = r[e];
-        meta_done[slot] = done[e];
+        publish_word(tree + nblk + b, root);
+        words_acknowledged();
+        sh[4] = arrived_last(count, (unsigned)nblk) ? 1.f : 0.f;
     }
+    __syncthreads();
+    if (sh[4] == 0.f) return;
+    if (nblk < 16) {   // 2, 4 or 8
+        if (threadIdx.x == 0)
+            for (int i = nblk - 1; i >= 1; --i)
+                tree[i] = 2 * i >= nblk ? read_word(tree + 2 * i) + read_word(tree + 2 * i + 1) : tree[2 * i] + tree[2 * i + 1];
+        return;
+    }
+    float r[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) r[i] = read_word(tree + nblk + ((int)threadIdx.x < nblk / 16 ? 16 * threadIdx.x + i : i));
+    (void)tree_block16(tree, nblk, nblk, 0, r, sh);
 }
 
-__global__ __launch_bounds__(256) void k_per_sample(SampleArgs A)
+// Bulk fill: leaf i = fp32(p_i^alpha) for i < n, 0 beyond, and the tree above; grid (L / BL)
+__global__ __launch_bounds__(256) void k_tree_fill(float *tree, long L, int BL, const float *p, long n, float alpha,
+                                                   unsigned *count)
 {
-    const int lane = threadIdx.x & 63;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= A.B) return;
-    const int jj[1] = {j};
-    long slot[1];
-    float leaf[1];
-    const float total = per_sample_walk<1>(A, jj, lane, slot, leaf);
-    if (lane == 0) per_sample_emit(A, j, slot[0], total, leaf[0]);
+    __shared__ float sh[8];
+    if (BL < 16) {   // a tree of eight leaves
+        if (threadIdx.x == 0) {
+            for (long i = 0; i < L; ++i) tree[L + i] = i < n ? (float)pow((double)p[i], (double)alpha) : 0.f;
+            for (long i = L - 1; i >= 1; --i) tree[i] = tree[2 * i] + tree[2 * i + 1];
+            tree[0] = 0.f;
+        }
+        return;
+    }
+    const long i0 = (long)blockIdx.x * BL + 16L * threadIdx.x;
+    const bool on = (int)threadIdx.x < BL / 16;
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = on && i0 + i < n ? p[i0 + i] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = on && i0 + i < n ? (float)pow((double)v[i], (double)alpha) : 0.f;
+    if (on) {
+        float4 *d = reinterpret_cast<float4 *>(tree + L + i0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i] = float4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) tree[0] = 0.f;
+    tree_build_leaves(tree, L, BL, blockIdx.x, gridDim.x, v, count, sh);
 }
 
-// w_j <- w_j / max_j w_j over the minibatch (single workgroup)
-__global__ __launch_bounds__(1024) void k_per_normalise(float *is_w, int B)
+// Store path of many environment streams: one time step for each of E streams of C slots (C >= 16), at local
+// slot l (t steps stored per stream before), in ONE launch.  The first nblk workgroups rebuild the tree over
+// the whole ring, forming the leaves the new time step settles as they go; the other E copy a stream's
+// frame and transition data.  The leaves follow the rules of the one-stream store path in the stream's
+// own sub-ring (see k_replay_store): the transition at local slot l - 1 has just become complete and enters with
+// leaf = fp32(max_p^alpha) unless its state stack would reach back before the stream's start (t - 1 < 3) or across
+// an episode end; the slot just written and the three after it get leaf 0.  They depend on transition data of
+// earlier time steps only, which this launch does not write.
+// (A write launch and two rebuild launches took 9.3 + 2 x 6.9 us for 2048 streams over a million slots.)
+struct StoreEnvsArgs {
+    uint8_t *frames;
+    int32_t *meta_a;
+    float *meta_r;
+    uint8_t *meta_done;
+    int E;
+    int C, l;
+    long t;
+    const uint8_t *src;
+    const int32_t *a;
+    const float *r;
+    const uint8_t *done;
+    float *tree;
+    long L;
+    int BL, nblk;
+    float alpha;
+    unsigned *count;
+};
+__global__ __launch_bounds__(256) void k_store_envs(StoreEnvsArgs A)
+{
+    __shared__ float sh[8];
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= A.nblk) {
+        const long e = (long)blockIdx.x - A.nblk, slot = e * A.C + A.l;
+        const uint4 *s = reinterpret_cast<const uint4 *>(A.src + e * net::FRAME);
+        uint4 *d = reinterpret_cast<uint4 *>(A.frames + slot * net::FRAME);
+        for (int q = tid; q < net::FRAME / 16; q += 256) d[q] = s[q];
+        if (tid == 0) {
+            A.meta_a[slot] = A.a[e];
+            A.meta_r[slot] = A.r[e];
+            A.meta_done[slot] = A.done[e];
+        }
+        return;
+    }
+    float v[16];
+    tree_load16(A.tree, A.L, A.BL, blockIdx.x, v);
+    const float mp = A.tree[2 * A.L];
+    const long slot0 = (long)blockIdx.x * A.BL + 16L * tid;
+    int e = (int)(slot0 / A.C), off = (int)(slot0 - (long)e * A.C);
+    bool dirty = false;
+    if (tid < A.BL / 16) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            int d = off - (A.l - 1);   // distance of this slot behind local slot l - 1, cyclic
+            if (d < 0) d += A.C;
+            if (d >= A.C) d -= A.C;    // (l = 0: slot l - 1 is the sub-ring's last)
+            if (d < 5 && e < A.E && (d > 0 || A.t >= 1)) {
+                float leaf = 0.f;
+                if (d == 0 && A.t - 1 >= 3) {
+                    bool valid = true;
+                    for (int k = 1; k <= 3; ++k) {
+                        const int q = off - k < 0 ? off - k + A.C : off - k;
+                        if (A.meta_done[(long)e * A.C + q]) valid = false;
+                    }
+                    if (valid) leaf = (float)pow((double)mp, (double)A.alpha);
+                }
+                v[i] = leaf;
+                dirty = true;
+            }
+            if (++off == A.C) { off = 0; ++e; }
+        }
+        if (dirty) {
+            float4 *p = reinterpret_cast<float4 *>(A.tree + A.L + slot0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) p[i] = float4{v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]};
+        }
+    }
+    tree_build_leaves(A.tree, A.L, A.BL, blockIdx.x, A.nblk, v, A.count, sh);
+}
+
+// The sampling kernel.  With `count` (per_sample) the workgroup that arrives last also divides the raw weights
+// by their maximum over the minibatch; without it the consumer does.
+__global__ __launch_bounds__(256) void k_per_sample(SampleArgs A, unsigned *count)
 {
     __shared__ float sh[16];
-    const int j = threadIdx.x;
-    const float w = j < B ? is_w[j] : 0.f;
-    const float wmax = block_max_1024(w, sh);
-    if (j < B) is_w[j] = wmax > 0.f ? w / wmax : 0.f;
+    __shared__ int last;
+    const int lane = threadIdx.x & 63;
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j < A.B) {
+        const int jj[1] = {j};
+        long slot[1];
+        float leaf[1];
+        const float total = per_sample_walk<1>(A, jj, lane, slot, leaf);
+        if (lane == 0) per_sample_emit(A, j, slot[0], total, leaf[0], count != nullptr);
+    }
+    if (!count) return;
+    words_acknowledged();
+    __syncthreads();
+    if (threadIdx.x == 0) last = arrived_last(count, gridDim.x);
+    __syncthreads();
+    if (!last) return;
+    float w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = read_word(A.is_w + min((int)threadIdx.x + 256 * k, A.B - 1));
+    const float wmax = block_max_1024(fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3])), sh);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if ((int)threadIdx.x + 256 * k < A.B) A.is_w[threadIdx.x + 256 * k] = wmax > 0.f ? w[k] / wmax : 0.f;
 }
 
 // Leaf-to-root repair by the threads of ONE workgroup, each starting from its own distinct leaf
@@ -1031,6 +1197,8 @@ __global__ __launch_bounds__(1024) void k_replay_store(StoreArgs A)
         bool valid = A.seq0 - 1 + j >= 3;   // stream position of the transition's own frame
 #pragma unroll
         for (int k = 1; k <= 3; ++k) {
+            // a flag of this call is read from the caller's array: its slot is being written meanwhile
+            const int q = j - 1 - k;
             long sk = slot - k;
             if (sk < 0) sk += A.cap;
             if (q >= 0 ? A.done[q] : A.meta_done[sk]) valid = false;
@@ -1067,6 +1235,78 @@ __global__ __launch_bounds__(256) void k_preprocess(const uint8_t *raw, int H, i
     const float bot = grey(y1, x0) * (1.f - fx) + grey(y1, x1) * fx;
     const float v = top * (1.f - fy) + bot * fy;
     out[(long)blockIdx.y * net::FRAME + o] = (uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f);
+}
+
+// The same for frames of ordinary size (at most four source rows per output row): a workgroup owns `rows` output rows
+// of one frame, copies the source rows under them into LDS with 16-byte loads and blends out of LDS, the grey table
+// in LDS as well.  The one-thread-per-pixel kernel above is bound by its eight scattered one-byte and table
+// fetches per pixel (77.5 us for 2048 frames of 210 x 160, 83 MB: 1.07 TB/s); here memory sees each byte once in
+// wide loads and the fetches go to LDS.  252 threads: thread t keeps column t % 84 (its source columns and
+// weight stay in registers) and walks down every third row; four neighbouring lanes put their bytes into one
+// 4-byte store (84 is a multiple of 4, so such a quad lies in one row).  Same arithmetic, same bytes.
+// Dynamic LDS: the staged rows.
+template <bool LUT>
+__global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, long total, int H, int W, const float *lut,
+                                                           uint8_t *out, int rows)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t px_dyn[];
+    __shared__ float grey_tab[256];
+    __shared__ int row_at[84];
+    __shared__ float row_f[84];
+    const int tid = threadIdx.x, i0 = blockIdx.x * rows;
+    auto source = [](int o, int N, int &at, float &f) {   // exact source coordinate of output line o, clamped
+        const int q = min(max((2 * o + 1) * N - 84, 0), 168 * (N - 1));
+        at = q / 168;
+        f = (float)(q % 168) / 168.f;
+    };
+    int ya, yb;
+    float f;
+    source(i0, H, ya, f);
+    source(i0 + rows - 1, H, yb, f);
+    const int yend = min(yb + 1, H - 1);
+    const long beg = ((long)blockIdx.y * H + ya) * W;        // bytes of `raw`
+    const int len = (yend - ya + 1) * W;
+    const int mis = (int)((uintptr_t)(raw + beg) & 15);
+    const uint8_t *al = raw + beg - mis;                       // 16-byte aligned
+    for (int g = tid; 16 * g < mis + len; g += 256) {
+        const long first = beg - mis + 16L * g;
+        if (first >= 0 && first + 16 <= total) {
+            *reinterpret_cast<uint4 *>(px_dyn + 16 * g) = *reinterpret_cast<const uint4 *>(al + 16 * g);
+        } else {   // the first and the last bytes of the whole array
+            for (int b = 0; b < 16; ++b)
+                if (first + b >= 0 && first + b < total) px_dyn[16 * g + b] = al[16 * g + b];
+        }
+    }
+    if (LUT) grey_tab[tid] = lut[tid];
+    if (tid < rows) {
+        int at;
+        source(i0 + tid, H, at, row_f[tid]);
+        row_at[tid] = mis + (at - ya) * W;
+    }
+    __syncthreads();
+    if (tid >= 252) return;
+    const int j = tid % 84, rg = tid / 84;
+    int x0;
+    float fx;
+    source(j, W, x0, fx);
+    const int x1 = min(x0 + 1, W - 1);
+    uint8_t *dst = out + (long)blockIdx.y * net::FRAME + (long)i0 * 84 + (j & ~3);
+    for (int i = rg; i < rows; i += 3) {
+        const int at = row_at[i];
+        const float fy = row_f[i];
+        const int below = at + W < mis + len ? at + W : at;   // the last source row has no row below it
+        auto grey = [&](int q) {
+            const uint8_t b = px_dyn[q];
+            return LUT ? grey_tab[b] : (float)b;
+        };
+        const float top = grey(at + x0) * (1.f - fx) + grey(at + x1) * fx;
+        const float bot = grey(below + x0) * (1.f - fx) + grey(below + x1) * fx;
+        const float v = top * (1.f - fy) + bot * fy;
+        uint32_t b = (uint32_t)(uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f) << (8 * (j & 3));
+        b |= __shfl_xor(b, 1, 64);
+        b |= __shfl_xor(b, 2, 64);
+        if ((j & 3) == 0) *reinterpret_cast<uint32_t *>(dst + 84 * i) = b;
+    }
 }
 
 // Stored layer outputs back in the canonical order: src [n][P][C] (channel-last, fp32 or bf16) ->
@@ -1193,149 +1433,3 @@ __global__ __launch_bounds__(256) void k_replay_write(uint8_t *frames, int32_t *
 }
 
 }  // namespace misc
-// The same for frames of ordinary size (at most four source rows per output row): a workgroup owns `rows` output rows
-// of one frame, copies the source rows under them into LDS with 16-byte loads and blends out of LDS, the grey table
-// in LDS as well.  The one-thread-per-pixel kernel above is bound by its eight scattered one-byte and table
-// fetches per pixel (77.5 us for 2048 frames of 210 x 160, 83 MB: 1.07 TB/s); here memory sees each byte once in
-// wide loads and the fetches go to LDS.  252 threads: thread t keeps column t % 84 (its source columns and
-// weight stay in registers) and walks down every third row; four neighbouring lanes put their bytes into one
-// 4-byte store (84 is a multiple of 4, so such a quad lies in one row).  Same arithmetic, same bytes.
-            // a flag of this call is read from the caller's array: its slot is being written meanwhile
-            const int q = j - 1 - k;
-// Dynamic LDS: the staged rows.
-template <bool LUT>
-__global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, long total, int H, int W, const float *lut,
-                                                           uint8_t *out, int rows)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t px_dyn[];
-    __shared__ float grey_tab[256];
-    __shared__ int row_at[84];
-    __shared__ float row_f[84];
-    const int tid = threadIdx.x, i0 = blockIdx.x * rows;
-    auto source = [](int o, int N, int &at, float &f) {   // exact source coordinate of output line o, clamped
-        const int q = min(max((2 * o + 1) * N - 84, 0), 168 * (N - 1));
-        at = q / 168;
-        f = (float)(q % 168) / 168.f;
-    };
-    int ya, yb;
-    float f;
-    source(i0, H, ya, f);
-    source(i0 + rows - 1, H, yb, f);
-    const int yend = min(yb + 1, H - 1);
-    const long beg = ((long)blockIdx.y * H + ya) * W;        // bytes of `raw`
-    const int len = (yend - ya + 1) * W;
-    const int mis = (int)((uintptr_t)(raw + beg) & 15);
-    const uint8_t *al = raw + beg - mis;                       // 16-byte aligned
-    for (int g = tid; 16 * g < mis + len; g += 256) {
-        const long first = beg - mis + 16L * g;
-        if (first >= 0 && first + 16 <= total) {
-            *reinterpret_cast<uint4 *>(px_dyn + 16 * g) = *reinterpret_cast<const uint4 *>(al + 16 * g);
-        } else {   // the first and the last bytes of the whole array
-            for (int b = 0; b < 16; ++b)
-                if (first + b >= 0 && first + b < total) px_dyn[16 * g + b] = al[16 * g + b];
-        }
-    }
-    if (LUT) grey_tab[tid] = lut[tid];
-    if (tid < rows) {
-// The same for frames of ordinary size (at most four source rows per output row): a workgroup owns `rows` output rows
-// of one frame, copies the source rows under them into LDS with 16-byte loads and blends out of LDS, the grey table
-// in LDS as well.  The one-thread-per-pixel kernel above is bound by its eight scattered one-byte and table
-// fetches per pixel (77.5 us for 2048 frames of 210 x 160, 83 MB: 1.07 TB/s); here memory sees each byte once in
-// wide loads and the fetches go to LDS.  252 threads: thread t keeps column t % 84 (its source columns and
-// weight stay in registers) and walks down every third row; four neighbouring lanes put their bytes into one
-// 4-byte store (84 is a multiple of 4, so such a quad lies in one row).  Same arithmetic, same bytes.
-// Dynamic LDS: the staged rows.
-template <bool LUT>
-__global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, long total, int H, int W, const float *lut,
-                                                           uint8_t *out, int rows)
-{
-    extern __shared__ __attribute__((aligned(16))) uint8_t px_dyn[];
-    __shared__ float grey_tab[256];
-    __shared__ int row_at[84];
-    __shared__ float row_f[84];
-    const int tid = threadIdx.x, i0 = blockIdx.x * rows;
-    auto source = [](int o, int N, int &at, float &f) {   // exact source coordinate of output line o, clamped
-        const int q = min(max((2 * o + 1) * N - 84, 0), 168 * (N - 1));
-        at = q / 168;
-        f = (float)(q % 168) / 168.f;
-    };
-    int ya, yb;
-    float f;
-    source(i0, H, ya, f);
-    source(i0 + rows - 1, H, yb, f);
-    const int yend = min(yb + 1, H - 1);
-    const long beg = ((long)blockIdx.y * H + ya) * W;        // bytes of `raw`
-    const int len = (yend - ya + 1) * W;
-    const int mis = (int)((uintptr_t)(raw + beg) & 15);
-    const uint8_t *al = raw + beg - mis;                       // 16-byte aligned
-    for (int g = tid; 16 * g < mis + len; g += 256) {
-        const long first = beg - mis + 16L * g;
-        if (first >= 0 && first + 16 <= total) {
-            *reinterpret_cast<uint4 *>(px_dyn + 16 * g) = *reinterpret_cast<const uint4 *>(al + 16 * g);
-        } else {   // the first and the last bytes of the whole array
-            for (int b = 0; b < 16; ++b)
-                if (first + b >= 0 && first + b < total) px_dyn[16 * g + b] = al[16 * g + b];
-        }
-    }
-    if (LUT) grey_tab[tid] = lut[tid];
-    if (tid < rows) {
-        int at;
-        source(i0 + tid, H, at, row_f[tid]);
-        row_at[tid] = mis + (at - ya) * W;
-    }
-    __syncthreads();
-    if (tid >= 252) return;
-    const int j = tid % 84, rg = tid / 84;
-    int x0;
-    float fx;
-    source(j, W, x0, fx);
-    const int x1 = min(x0 + 1, W - 1);
-    uint8_t *dst = out + (long)blockIdx.y * net::FRAME + (long)i0 * 84 + (j & ~3);
-    for (int i = rg; i < rows; i += 3) {
-        const int at = row_at[i];
-        const float fy = row_f[i];
-        const int below = at + W < mis + len ? at + W : at;   // the last source row has no row below it
-        auto grey = [&](int q) {
-            const uint8_t b = px_dyn[q];
-            return LUT ? grey_tab[b] : (float)b;
-        };
-        const float top = grey(at + x0) * (1.f - fx) + grey(at + x1) * fx;
-        const float bot = grey(below + x0) * (1.f - fx) + grey(below + x1) * fx;
-        const float v = top * (1.f - fy) + bot * fy;
-        uint32_t b = (uint32_t)(uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f) << (8 * (j & 3));
-        b |= __shfl_xor(b, 1, 64);
-        b |= __shfl_xor(b, 2, 64);
-        if ((j & 3) == 0) *reinterpret_cast<uint32_t *>(dst + 84 * i) = b;
-    }
-}
-
-        int at;
-        source(i0 + tid, H, at, row_f[tid]);
-        row_at[tid] = mis + (at - ya) * W;
-    }
-    __syncthreads();
-    if (tid >= 252) return;
-    const int j = tid % 84, rg = tid / 84;
-    int x0;
-    float fx;
-    source(j, W, x0, fx);
-    const int x1 = min(x0 + 1, W - 1);
-    uint8_t *dst = out + (long)blockIdx.y * net::FRAME + (long)i0 * 84 + (j & ~3);
-    for (int i = rg; i < rows; i += 3) {
-        const int at = row_at[i];
-        const float fy = row_f[i];
-        const int below = at + W < mis + len ? at + W : at;   // the last source row has no row below it
-        auto grey = [&](int q) {
-            const uint8_t b = px_dyn[q];
-            return LUT ? grey_tab[b] : (float)b;
-        };
-        const float top = grey(at + x0) * (1.f - fx) + grey(at + x1) * fx;
-        const float bot = grey(below + x0) * (1.f - fx) + grey(below + x1) * fx;
-        const float v = top * (1.f - fy) + bot * fy;
-        uint32_t b = (uint32_t)(uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f) << (8 * (j & 3));
-        b |= __shfl_xor(b, 1, 64);
-        b |= __shfl_xor(b, 2, 64);
-        if ((j & 3) == 0) *reinterpret_cast<uint32_t *>(dst + 84 * i) = b;
-    }
-}
-

@@ -44,7 +44,7 @@ struct MetaGather {
 // shuffles.  20 levels cost 3 dependent round trips instead of 20 (the round at the
 // root is wider where that saves one, see first_round_levels), and every fetch is a
 // contiguous run of the heap array.
-// is_w receives the RAW weight (N P(j))^-beta; k_per_normalise (or the consumer)
+// is_w receives the RAW weight (N P(j))^-beta; the sampling kernel's last workgroup (or the consumer)
 // divides by the minibatch maximum.
 struct SampleArgs {
     const float *tree;
@@ -198,8 +198,8 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
 }
 
 // What one lane writes for draw j once the walk has ended: index, raw weight (from the leaf's value and
-// the total the walk returned), transition data.
-__device__ __forceinline__ void per_sample_emit(const SampleArgs &A, int j, long slot, float total, float leaf)
+// the total the walk returned), transition data.  publish: the weight is read by another workgroup of the launch.
+__device__ __forceinline__ void per_sample_emit(const SampleArgs &A, int j, long slot, float total, float leaf, bool publish = false)
 {
     A.idx[j] = (int32_t)slot;
     if (A.idx_out) A.idx_out[j] = (int32_t)slot;
@@ -207,8 +207,10 @@ __device__ __forceinline__ void per_sample_emit(const SampleArgs &A, int j, long
     if (!A.uniform) {
         const double P = (double)leaf / (double)total;
         // a tree without mass (every stored transition has priority zero) has nothing to draw: weight 0
-        A.is_w[j] = total > 0.f ? (float)pow((double)A.size * P, -(double)A.beta) : 0.f;
+        w = total > 0.f ? (float)pow((double)A.size * P, -(double)A.beta) : 0.f;
     }
+    if (publish) __hip_atomic_store(A.is_w + j, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else A.is_w[j] = w;
     if (A.G.a) {   // the three loads first: behind a store the compiler would hold a load back
         const int32_t a = A.G.meta_a[slot];
         const float r = A.G.meta_r[slot];
