@@ -14,6 +14,7 @@
 #include "../../include/dqn.h"
 #include "gemm_bf16.h"
 #include "gemm_fp32.h"
+#include "gemm_split.h"
 #include "kernels_misc.h"
 #include "net.h"
 
@@ -58,6 +59,7 @@ struct Workspace {
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
     gbf::bf16_t *w2t;  // bf16 only: the online conv2 weights as [tap][channel in][channel out] (see misc::k_w2_transposed)
+    uint16_t *packed;  // fp32 only: the conv weights of both networks as bf16 parts (packed.h)
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -108,10 +110,12 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
     w.w2t = (gbf::bf16_t *)take(c.precision == 1 ? net::L2N * 2 : 0);
+    w.packed = (uint16_t *)take(c.precision == 0 ? 2 * (size_t)sp::W_TOTAL * 2 : 0);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
-    w.act1 = take(rows * net::A1 * es);
-    w.act2 = take(rows * net::A2 * es);
+    // (fp32: conv1's and conv2's outputs exist in memory for the rows of the backward pass only)
+    w.act1 = take((c.precision == 1 ? rows : MB) * net::A1 * es);
+    w.act2 = take((c.precision == 1 ? rows : MB) * net::A2 * es);
     w.act3 = take(rows * net::A3 * es);
     size_t f1rows = std::max({std::min<size_t>(rows, 192) * 14, std::min<size_t>(rows, 512) * 7,
                               std::min<size_t>(rows, 1536) * 2, rows});
@@ -314,6 +318,14 @@ void he_uniform_host(std::vector<float> &blob, int K, int dueling, uint64_t seed
     }
 }
 
+// the copy of a network's conv weights that the fp32 forward kernel reads
+void pack_conv(dqn_ctx *c, int net_i, hipStream_t st)
+{
+    launch(c, "pack_conv", st, [&] {
+        sp::k_pack_conv<<<grid1(net::F1W, 256), 256, 0, st>>>(net_i ? c->theta_t : c->theta, c->ws.packed + (net_i ? sp::W_TOTAL : 0));
+    });
+}
+
 void permute(dqn_ctx *c, const float *src, float *dst, int dir, hipStream_t st)
 {
     launch(c, "permute", st, [&] { misc::k_permute<<<grid1(c->n, 256), 256, 0, st>>>(src, dst, c->n, dir); });
@@ -340,7 +352,6 @@ struct Pass {
     const int32_t *idx;  // ring mode: sampled slots (or where the forward kernel leaves them); frames are read from the ring
     int shift;           // ring mode: 0 = s (frames i-3..i), 1 = s' (frames i-2..i+1)
     uint8_t *stack;      // fp32 ring mode: where conv1 leaves a gathered copy of the frames for the weight gradient
-    int stack_mode;      // 1: frames 0-3 of the sample to stack frames 0-3; 2: frame 3 to stack frame 4
 };
 
 const float *theta_of(dqn_ctx *c, int net) { return net ? c->theta_t : c->theta; }
@@ -350,33 +361,36 @@ const gbf::bf16_t *shadow_of(dqn_ctx *c, int net)
     return sh + (net ? align_up((size_t)c->n * 2, 256) / 2 : 0);
 }
 
-// Launch shapes of the conv1 forward kernels for `samples` samples (all passes), and whether a wave's
-// (wave group's) share of strips spans few enough samples for it to draw them itself.
+// Launch shapes of the conv1 forward kernel for `samples` samples (all passes), and whether a wave's
+// share of strips spans few enough samples for it to draw them itself.
 struct Conv1Plan {
-    bool ks2;        // fp32: four waves per strip (fewer wave pairs than SIMDs)
     int grid;
     bool draw_fits;
 };
-Conv1Plan conv1_plan_f32(int samples, int num_cu)
-{
-    const int units = samples * gbf::c1::UNITS;
-    Conv1Plan P;
-    P.ks2 = 2 * units <= 4 * num_cu;
-    P.grid = P.ks2 ? std::min(units, 2 * num_cu) : std::min((units + 1) / 2, 2 * num_cu);
-    const int groups = P.ks2 ? P.grid : 2 * P.grid;
-    const int upg = (units + groups - 1) / groups + 1;   // strips per group of waves, at most
-    P.draw_fits = (upg + gbf::c1::UNITS - 1) / gbf::c1::UNITS + 1 <= gbf::c1::MAX_DRAWS;
-    return P;
-}
 Conv1Plan conv1_plan_bf16(int samples, int num_cu)
 {
     const int units = samples * gbf::c1::UNITS;
     Conv1Plan P;
-    P.ks2 = false;
     // one wave per strip of a sample, four waves per workgroup, two workgroups resident per CU
     P.grid = std::min((units + 3) / 4, 2 * num_cu);
     const int upw = (units + 4 * P.grid - 1) / (4 * P.grid) + 1;
     P.draw_fits = (upw + gbf::c1::UNITS - 1) / gbf::c1::UNITS + 1 <= gbf::c1::MAX_DRAWS;
+    return P;
+}
+// fp32: the conv layers' launch (sp::k_conv123_fwd).  A sample is spread over as many workgroups as there are
+// compute units for it: with whole samples a launch lasts a whole sample's time however few there are.
+struct Conv123Plan {
+    int r3, parts, grid;
+    bool draw_fits;
+};
+Conv123Plan conv123_plan(int samples, int num_cu)
+{
+    Conv123Plan P;
+    P.r3 = 7 * samples <= num_cu ? 1 : 2 * samples <= num_cu ? 4 : 7;
+    P.parts = (7 + P.r3 - 1) / P.r3;
+    const int units = samples * P.parts;
+    P.grid = P.r3 == 7 ? std::min(units, num_cu) : units;
+    P.draw_fits = (units + P.grid - 1) / P.grid <= sp::MAX_UNITS;
     return P;
 }
 // bf16: conv1 + conv2 as one launch, one workgroup per CU, for passes of n[0..npass) samples?
@@ -393,11 +407,21 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
     }
     return true;
 }
+// fp32 training: do the rows of the first pass keep the order of summation of the fp32 matrix instruction?
+// Their stored activations are what the ReLU decisions of the backward pass are taken on.  About one
+// pre-activation in ten million is zero to within the rounding of its sum, and falls the other way under
+// another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and one such
+// decision moves a gradient by 1e-4 to 2e-3 of its norm (measured over 30 seeds at 64, 128 and 256: 4, 8 and
+// 12 of them beyond 1e-4 after two steps, none of 130 at 32).  Large batches therefore keep it, so that their
+// results stay those of the plain fp32 chain; the two passes over s', whose activations are only values,
+// take the split form at every size.  Small batches, where a layer-by-layer chain is latency and nothing
+// else, take it for all three: the line lies where a sample no longer has two workgroups to itself.
+bool keeps_fp32_order(const dqn_ctx *c, const Pass *pass, int npass) { return npass == 3 && 2 * 3 * pass[0].n > c->num_cu; }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not
 // (few compute units and a large batch), a sampling launch runs in front of the step.
 bool in_kernel_draw_fits(const dqn_ctx *c, int B)
 {
-    if (c->cfg.precision == 0) return conv1_plan_f32(3 * B, c->num_cu).draw_fits;
+    if (c->cfg.precision == 0) return conv123_plan(3 * B, c->num_cu).draw_fits && conv123_plan(2 * B, c->num_cu).draw_fits;
     const int n[3] = {B, B, B};
     return fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
@@ -406,7 +430,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
                           long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw)
 {
     using namespace g32;
-    float *act1 = (float *)w.act1, *act2 = (float *)w.act2, *act3 = (float *)w.act3;
+    float *act3 = (float *)w.act3;
     long row0[3];
     long rows = 0;
     for (int i = 0; i < npass; ++i) { row0[i] = rows; rows += pass[i].n; }
@@ -431,50 +455,60 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         return tile;
     };
 
-    // Few rows (small batches): the reduction slab of every stage is sliced over extra waves
-    // (KS > 1), which shortens the dependent chain of stages per tile.
-    const bool small = rows * 81 < 64 * 512;
-    {  // conv1: one wave per strip of a sample and channel half; a small batch also halves the reduction
-        using namespace gbf;
-        c1::FwdArgsF A{};
-        A.nseg = npass;
-        int first = 0;
-        for (int i = 0; i < npass; ++i) {
-            const float *theta = theta_of(c, pass[i].net);
-            A.seg[i] = c1::FwdSegF{c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
-                                   theta + net::C1W, theta + net::C1B, act1 + row0[i] * net::A1, pass[i].n, first,
-                                   pass[i].stack, pass[i].stack_mode};
-            first += pass[i].n;
-        }
-        for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
-        A.total = first;
-        A.draw = draw != nullptr;
-        if (draw) A.samp = *draw;
-        const Conv1Plan plan = conv1_plan_f32(first, c->num_cu);
-        const bool ks2 = plan.ks2;
-        const int grid = plan.grid;
+    // conv1, conv2 and conv3: one launch for the passes [p0, npass)
+    const int p0 = keeps_fp32_order(c, pass, npass) ? 1 : 0;
+    {
+        const int samples = (int)(rows - row0[p0]);
+        const Conv123Plan plan = conv123_plan(samples, c->num_cu);
         if (draw && !plan.draw_fits)   // the caller asks in_kernel_draw_fits first
             return fail(c, DQN_ERR_INVALID_ARG, "forward: batch too large for in-kernel sampling");
-        if (ks2) launch(c, "conv1_fwd", st, [&] { c1::k_conv1_fwd_f32<2><<<dim3(grid), 256, 0, st>>>(A); });
-        else launch(c, "conv1_fwd", st, [&] { c1::k_conv1_fwd_f32<1><<<dim3(grid), 256, 0, st>>>(A); });
+        sp::Args A{};
+        A.nseg = npass - p0;
+        for (int i = p0; i < npass; ++i) {
+            const float *theta = theta_of(c, pass[i].net);
+            // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
+            const bool keep = npass == 3 && i == 0;
+            A.seg[i - p0] = sp::Seg{gbf::c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
+                                    c->ws.packed + (pass[i].net ? sp::W_TOTAL : 0), theta + net::C1B, theta + net::C2B, theta + net::C3B,
+                                    keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
+                                    pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts, pass[i].stack};
+        }
+        for (int i = A.nseg; i < 3; ++i) A.seg[i] = A.seg[0];
+        A.units = samples * plan.parts;
+        A.draw = draw != nullptr;
+        if (draw) A.samp = *draw;
+        launch(c, "conv123_fwd", st, [&] {
+            if (plan.r3 == 1) sp::k_conv123_fwd<1><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 4) sp::k_conv123_fwd<4><<<dim3(plan.grid), 512, sp::Geo<4>::LDS, st>>>(A);
+            else sp::k_conv123_fwd<7><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
+        });
     }
-    {  // conv2
-        FwdArgs A{};
-        int BM = small ? 32 : 64;
-        int tiles = build(A, BM, 81, [&](int i) { return (const void *)(act1 + row0[i] * net::A1); },
-                          [&](int) { return (long)net::A1; }, net::C2W, net::C2B, act2, net::A2, true);
-        A.klen = GConv2::K; A.split_stride = 0; A.scale = 1.0f;
-        if (small) launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 32, 32, 4><<<dim3(tiles, 2, 1), 256, 0, st>>>(A); });
-        else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3(tiles, 1, 1), 256, 0, st>>>(A); });
-    }
-    {  // conv3
-        FwdArgs A{};
-        int BM = small ? 32 : 64;
-        int tiles = build(A, BM, 49, [&](int i) { return (const void *)(act2 + row0[i] * net::A2); },
-                          [&](int) { return (long)net::A2; }, net::C3W, net::C3B, act3, net::A3, true);
-        A.klen = GConv3::K; A.split_stride = 0; A.scale = 1.0f;
-        if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3(tiles, 2, 1), 192, 0, st>>>(A); });
-        else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3(tiles, 1, 1), 256, 0, st>>>(A); });
+    if (p0 == 1) {   // the training rows, layer by layer (their transitions have been drawn by the launch above)
+        const Pass &P = pass[0];
+        const float *theta = theta_of(c, P.net);
+        float *act1 = (float *)w.act1, *act2 = (float *)w.act2;
+        gbf::c1::FwdSegF F{gbf::c1::Src{P.x, P.xs, P.idx, (long)c->cfg.replay_capacity, P.shift, (int)c->sub},
+                           theta + net::C1W, theta + net::C1B, act1, P.n, P.stack};
+        const int grid = std::min((P.n * gbf::c1::UNITS + 1) / 2, 2 * c->num_cu);
+        launch(c, "conv1_fwd", st, [&] { gbf::c1::k_conv1_fwd_f32<<<dim3(grid), 256, 0, st>>>(F); });
+        auto one = [&](const float *x, long xs, int64_t woff, int64_t boff, float *y, int M) {
+            FwdArgs A{};
+            A.nseg = 1;
+            A.seg[0] = A.seg[1] = A.seg[2] = FwdSeg{x, theta + woff, theta + boff, y, M, 0, xs};
+            A.scale = 1.0f;
+            return A;
+        };
+        // (few rows: the reduction slab of every stage is sliced over extra waves, KS > 1, which shortens the
+        // dependent chain of stages per tile)
+        const bool small = rows * 81 < 64 * 512;
+        const int M2 = P.n * 81, M3 = P.n * 49;
+        FwdArgs A2 = one(act1, net::A1, net::C2W, net::C2B, act2, M2), A3 = one(act2, net::A2, net::C3W, net::C3B, act3, M3);
+        A2.klen = GConv2::K;
+        A3.klen = GConv3::K;
+        if (small) launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 32, 32, 4><<<dim3((M2 + 31) / 32, 2, 1), 256, 0, st>>>(A2); });
+        else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3((M2 + 63) / 64, 1, 1), 256, 0, st>>>(A2); });
+        if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3((M3 + 31) / 32, 2, 1), 192, 0, st>>>(A3); });
+        else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3((M3 + 63) / 64, 1, 1), 256, 0, st>>>(A3); });
     }
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
         FwdArgs A{};
@@ -712,6 +746,7 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     RA.theta = c->theta; RA.v = c->rms_v; RA.m = c->rms_m; RA.g = c->grads;
     RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)c->buf.shadow_bf16 : nullptr;
     RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w.w2t : nullptr;
+    RA.packed = cfg.precision == 0 ? w.packed : nullptr;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
     if (last_part && last_part->on) launch(c, "rmsprop", st, [&] { k_rmsprop_pu<<<blk + 1, 256, 0, st>>>(RA, *last_part); });
     else launch(c, "rmsprop", st, [&] { misc::k_rmsprop<<<blk, 256, 0, st>>>(RA); });
@@ -1088,6 +1123,17 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(c->theta_t, sh + half, c->n);
         misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
+    if (cfg->precision == 0) {
+        pack_conv(c, 0, st);
+        pack_conv(c, 1, st);
+        // the forward launch of the conv layers holds a sample's images in LDS
+        if (hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
+            hipFuncSetAttribute((const void *)sp::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<7>::LDS) != hipSuccess) {
+            (void)hipGetLastError();
+            delete c;
+            return fail(nullptr, DQN_ERR_HIP, "dqn_init: the device does not grant the forward kernel its LDS");
+        }
+    }
     if (hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) {
         delete c;
         return fail(nullptr, DQN_ERR_HIP, "dqn_init: device initialisation failed");
@@ -1226,6 +1272,7 @@ int32_t dqn_set_params(dqn_ctx *c, int32_t which, const float *src, void *stream
         misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, sh + (which ? half : 0), c->n);
         if (which == 0) misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
+    if (c->cfg.precision == 0 && which <= 1) pack_conv(c, which, st);
     return hip_status(c, "dqn_set_params");
 }
 
@@ -1260,6 +1307,8 @@ int32_t dqn_sync_target(dqn_ctx *c, void *stream)
         size_t half = align_up((size_t)c->n * 2, 256) / 2;
         if (hipMemcpyAsync(sh + half, sh, (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
             return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
+    } else if (hipMemcpyAsync(c->ws.packed + sp::W_TOTAL, c->ws.packed, (size_t)sp::W_TOTAL * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) {
+        return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     }
     return DQN_OK;
 }
@@ -1596,9 +1645,9 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     const bool stacking = !batch && cfg.precision == 0 && draw;
 
     // forward: online(s), online(s'), target(s') in one launch per layer
-    Pass passes[3] = {{s, xs, 0, B, ring_idx, 0, stacking ? w.stack5 : nullptr, 1},
-                      {sn, xs, 0, B, ring_idx, 1, stacking ? w.stack5 : nullptr, 2},
-                      {sn, xs, 1, B, ring_idx, 1, nullptr, 0}};
+    Pass passes[3] = {{s, xs, 0, B, ring_idx, 0, stacking ? w.stack5 : nullptr},
+                      {sn, xs, 0, B, ring_idx, 1, nullptr},
+                      {sn, xs, 1, B, ring_idx, 1, nullptr}};
     int ns;
     long ss;
     int32_t rc = forward_trunk(c, w, passes, 3, &ns, &ss, st, draw);

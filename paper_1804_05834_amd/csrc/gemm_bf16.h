@@ -1182,9 +1182,9 @@ __global__ __launch_bounds__(256, 2) void k_conv1_fwd(FwdArgs A)
     }
 }
 
-
 // ---------------------------------------------------------------------------
-// The same forward pass in fp32 (v_mfma_f32_16x16x4_f32), for the full-precision path.
+// The same forward pass in fp32 (v_mfma_f32_16x16x4_f32), for the training rows of large fp32 batches (see
+// forward_trunk_f32 for when; everything else in fp32 goes through sp::k_conv123_fwd).
 //
 // Units and lanes as above (strip of 4 output rows, 16 lanes x 5 pixels), but the strip stays in
 // LDS as the uint8 it is (6,720 bytes per wave, no conversion while staging): the MFMA takes one
@@ -1193,10 +1193,8 @@ __global__ __launch_bounds__(256, 2) void k_conv1_fwd(FwdArgs A)
 // kernel columns of all five pixels: word jj is columns 0-3 of pixel jj and columns 4-7 of pixel
 // jj-1.  One v_cvt_f32_ubyte per byte, 24 per 40 MFMAs.
 // A wave holds the weights of 16 output channels (64 registers): waves work in pairs, one channel
-// half each.  KS = 2 (small batches: fewer units than SIMDs) also cuts the reduction in two, frames
-// 0-1 and 2-3, over two such pairs, which then add their sums through LDS in a fixed order.
-// The first wave of a group can copy its strip to a gathered stack (the weight-gradient kernel of
-// this path reads a materialised state): segment 0 supplies frames 0-3, segment 1 its last frame.
+// half each.  The first wave of a pair can copy its strip to a gathered stack (the weight-gradient kernel
+// of this path reads a materialised state).
 // ---------------------------------------------------------------------------
 constexpr int RAWSTRIP = 4 * SROWS * 84;   // bytes of one strip as uint8
 struct FwdSegF {
@@ -1205,16 +1203,7 @@ struct FwdSegF {
     const float *bias;  // [32]
     float *y;           // [n][400][32]
     int n;
-    int first;
-    uint8_t *stack;     // [n][5][84][84] or nullptr
-    int stack_mode;     // 1: frames 0-3 of the sample to stack frames 0-3; 2: frame 3 to stack frame 4
-};
-struct FwdArgsF {
-    FwdSegF seg[3];
-    int nseg;
-    int total;
-    int draw;
-    misc::SampleArgs samp;
+    uint8_t *stack;     // [n][5][84][84] or nullptr: frames 0-3 of the stack are written
 };
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c)
@@ -1222,13 +1211,9 @@ __device__ __forceinline__ v4f mfma4(float a, float b, v4f c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <int KS>
-__device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, int u1, int hh, int ks, uint8_t *xs,
-                                                    v4f *red, const int *slots, int lane)
+__device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, int u1, int hh, uint8_t *xs, int lane)
 {
-    constexpr int NCY = 8 / KS;   // (frame, kernel-row half) pairs of this wave
     const int n = lane & 15, kg = lane >> 4, oyl = n >> 2, q = n & 3;
-    const bool first_wave = hh == 0 && ks == 0;
     StripOff O;
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
@@ -1236,19 +1221,18 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
         O.off[i] = t < CHUNKS ? (t / (CHUNKS / 4)) * FR + (t % (CHUNKS / 4)) * 16 : 0;
     }
     const int gfirst = u0 / UNITS;
-    auto slot_of = [&](int gq) { return slots ? slots[gq - gfirst] : sample_slot(S.src, gq); };
+    auto slot_of = [&](int gq) { return sample_slot(S.src, gq); };
     StripRaw R;
     strip_load(R, S.src, gfirst, slot_of(gfirst), u0 % UNITS, lane, O);
     int slot_next = u0 + 1 < u1 ? slot_of((u0 + 1) / UNITS) : 0;
-    // weights: wa[8 cyl + 4 xh + b] = W[16hh + n][frame, kernel row 4yq + kg of pair NCY ks + cyl][4 xh + b]
-    float wa[8 * NCY];
+    // weights: wa[8 cy + 4 xh + b] = W[16hh + n][frame cy / 2, kernel row 4 (cy % 2) + kg][4 xh + b]
+    float wa[64];
 #pragma unroll
-    for (int cyl = 0; cyl < NCY; ++cyl) {
-        const int cy = NCY * ks + cyl;
+    for (int cy = 0; cy < 8; ++cy) {
         const float *p = S.w + (16 * hh + n) * 256 + (cy >> 1) * 64 + (4 * (cy & 1) + kg) * 8;
         const v4f lo = *reinterpret_cast<const v4f *>(p), hi = *reinterpret_cast<const v4f *>(p + 4);
-        wa[8 * cyl + 0] = lo.x; wa[8 * cyl + 1] = lo.y; wa[8 * cyl + 2] = lo.z; wa[8 * cyl + 3] = lo.w;
-        wa[8 * cyl + 4] = hi.x; wa[8 * cyl + 5] = hi.y; wa[8 * cyl + 6] = hi.z; wa[8 * cyl + 7] = hi.w;
+        wa[8 * cy + 0] = lo.x; wa[8 * cy + 1] = lo.y; wa[8 * cy + 2] = lo.z; wa[8 * cy + 3] = lo.w;
+        wa[8 * cy + 4] = hi.x; wa[8 * cy + 5] = hi.y; wa[8 * cy + 6] = hi.z; wa[8 * cy + 7] = hi.w;
     }
     const v4f bias = *reinterpret_cast<const v4f *>(S.bias + 16 * hh + 4 * kg);
     const uint8_t *px = xs + (4 * oyl + kg) * 84 + 20 * q;
@@ -1261,8 +1245,8 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
                 *reinterpret_cast<u32x4 *>(xs + t * 16) = R.raw[i];
                 // rows 16s .. 16s+15 of the frames are this strip's own (the last strip owns all 20)
                 const int fr = t / (CHUNKS / 4), off = (t % (CHUNKS / 4)) * 16;
-                if (first_wave && S.stack && (off < 16 * 84 || strip == UNITS - 1) && (S.stack_mode == 1 || fr == 3))
-                    *reinterpret_cast<u32x4 *>(S.stack + ((long)g * 5 + (S.stack_mode == 1 ? fr : 4)) * FR + strip * (16 * 84) + off) = R.raw[i];
+                if (hh == 0 && S.stack && (off < 16 * 84 || strip == UNITS - 1))
+                    *reinterpret_cast<u32x4 *>(S.stack + ((long)g * 5 + fr) * FR + strip * (16 * 84) + off) = R.raw[i];
             }
         }
         if (u + 1 < u1) {
@@ -1273,8 +1257,7 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
 #pragma unroll
         for (int j = 0; j < 5; ++j) acc[j] = v4f{0, 0, 0, 0};
 #pragma unroll
-        for (int cyl = 0; cyl < NCY; ++cyl) {
-            const int cy = NCY * ks + cyl;   // frame cy / 2, kernel rows 4 (cy % 2) + kg
+        for (int cy = 0; cy < 8; ++cy) {   // frame cy / 2, kernel rows 4 (cy % 2) + kg
             const uint8_t *p = px + (cy >> 1) * (SROWS * 84) + (cy & 1) * (4 * 84);
             uint32_t d[6];
 #pragma unroll
@@ -1292,61 +1275,31 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
 #pragma unroll
-                    for (int j = 0; j < 5; ++j) acc[j] = mfma4(wa[8 * cyl + 4 * xh + b], f[j + xh][b], acc[j]);
+                    for (int j = 0; j < 5; ++j) acc[j] = mfma4(wa[8 * cy + 4 * xh + b], f[j + xh][b], acc[j]);
         }
-        if constexpr (KS == 2) {   // frames 2-3 join frames 0-1; the buffer alternates, so one barrier per unit
-            v4f *r = red + (((u - u0) & 1) * 2 + hh) * (5 * 64);
-            if (ks == 1) {
+        float *y = S.y + ((long)g * 400 + 20 * (4 * strip + oyl) + 5 * q) * 32 + 16 * hh + 4 * kg;
+        constexpr float sc = 1.0f / 255.0f;
 #pragma unroll
-                for (int j = 0; j < 5; ++j) r[j * 64 + lane] = acc[j];
-            }
-            sync_lds();
-            if (ks == 0) {
-#pragma unroll
-                for (int j = 0; j < 5; ++j) acc[j] += r[j * 64 + lane];
-            }
-        }
-        if (ks == 0) {
-            float *y = S.y + ((long)g * 400 + 20 * (4 * strip + oyl) + 5 * q) * 32 + 16 * hh + 4 * kg;
-            constexpr float sc = 1.0f / 255.0f;
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                v4f o;
-                o.x = fmaxf(acc[j].x * sc + bias.x, 0.f);
-                o.y = fmaxf(acc[j].y * sc + bias.y, 0.f);
-                o.z = fmaxf(acc[j].z * sc + bias.z, 0.f);
-                o.w = fmaxf(acc[j].w * sc + bias.w, 0.f);
-                *reinterpret_cast<v4f *>(y + j * 32) = o;
-            }
+        for (int j = 0; j < 5; ++j) {
+            v4f o;
+            o.x = fmaxf(acc[j].x * sc + bias.x, 0.f);
+            o.y = fmaxf(acc[j].y * sc + bias.y, 0.f);
+            o.z = fmaxf(acc[j].z * sc + bias.z, 0.f);
+            o.w = fmaxf(acc[j].w * sc + bias.w, 0.f);
+            *reinterpret_cast<v4f *>(y + j * 32) = o;
         }
     }
 }
 
-// KS = 1: the four waves of a workgroup are two pairs, each with a unit range of its own.
-// KS = 2: they are one group of four on one unit range.
-template <int KS>
-__global__ __launch_bounds__(256, 2) void k_conv1_fwd_f32(FwdArgsF A)
+// The four waves of a workgroup are two pairs, each with a unit range of its own.
+__global__ __launch_bounds__(256, 2) void k_conv1_fwd_f32(FwdSegF S)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4 * RAWSTRIP];
-    __shared__ __attribute__((aligned(16))) v4f red[KS == 2 ? 2 * 2 * 5 * 64 : 1];
-    __shared__ int slot_tab[4][MAX_DRAWS];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int hh = wave & 1, ks = KS == 2 ? wave >> 1 : 0;
-    const long ng = (long)gridDim.x * (KS == 2 ? 1 : 2), gid = KS == 2 ? (long)blockIdx.x : (long)blockIdx.x * 2 + (wave >> 1);
-    const long units = (long)A.total * UNITS;
-    const int u0 = (int)(gid * units / ng), u1 = (int)((gid + 1) * units / ng);
-    if (A.draw && u0 < u1) draw_slots(A.samp, A.seg[0].n, u0, u1, slot_tab[wave], lane, hh == 0 && ks == 0);
-    for (int s = 0; s < A.nseg; ++s) {
-        FwdSegF S = A.seg[0];
-        if (s == 1) S = A.seg[1];
-        if (s == 2) S = A.seg[2];
-        const int lo = max(u0, UNITS * S.first) - UNITS * S.first;
-        const int hi = min(u1, UNITS * (S.first + S.n)) - UNITS * S.first;
-        if (lo < hi)
-            conv1_fwd_units_f32<KS>(S, lo, hi, hh, ks, lds + wave * RAWSTRIP, red,
-                                    A.draw ? slot_tab[wave] + (S.first + lo / UNITS - u0 / UNITS) : nullptr, lane);
-    }
+    const long np = (long)gridDim.x * 2, pid = (long)blockIdx.x * 2 + (wave >> 1), units = (long)S.n * UNITS;
+    const int u0 = (int)(pid * units / np), u1 = (int)((pid + 1) * units / np);
+    if (u0 < u1) conv1_fwd_units_f32(S, u0, u1, wave & 1, lds + wave * RAWSTRIP, lane);
 }
 
 struct WgradArgs {

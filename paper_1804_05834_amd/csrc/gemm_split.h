@@ -1,0 +1,438 @@
+// fp32 layers on the bf16 matrix cores, without giving up fp32 accuracy.
+//
+// A float is the sum of three bf16 numbers: x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1).
+// Round-to-nearest leaves 8 significant bits to each, 24 in all, so the sum is x itself: nothing of an
+// operand is dropped.  A product x*w is then nine products of bf16 numbers, each exact in the fp32
+// accumulator of the matrix instruction; the three smallest (x1*w2, x2*w1, x2*w2: below 2^-26 of
+// |x*w|, a quarter of what rounding one fp32 product may cost) are left out, six remain.  Pixels are
+// bytes and exact in ONE bf16 number, so conv1 needs three products and drops none.
+// Measured on this chip against fp64 sums of 64 / 512 / 3136 products (32 x 32 results, error over
+// sum |a*b|, three distributions): rms 2.1 / 2.5 / 2.5e-8 with six products, 2.8 / 2.8 / 2.8e-8 with
+// v_mfma_f32_32x32x2_f32 for normal operands; 2.8 / 3.0 / 3.6e-8 against 2.6 / 2.6 / 2.8e-8 for
+// ReLU-like ones, 8.2e-8 / 2.4e-7 / 5.2e-7 against 1.2e-7 / 3.2e-7 / 7.9e-7 for positive ones; with all
+// nine products the same figures to three digits.
+// Cost per 32 reduction elements of a 16 x 16 tile: six bf16 instructions of 16 cycles against eight
+// fp32 ones of 32: 96 against 256 cycles of the matrix pipe.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "gemm_bf16.h"
+#include "net.h"
+#include "packed.h"
+#include "sumtree.h"
+
+namespace sp {
+
+using gbf::bf16_t;
+using gbf::mfma;
+using gbf::mfma16;
+using gbf::pack4;
+using gbf::sync_lds;
+using gbf::v8bf;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+
+// The three bf16 parts of four floats
+struct Split4 { uint2 p[3]; };
+__device__ __forceinline__ v4f unpack4(uint2 u)
+{
+    return v4f{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
+               __uint_as_float(u.y & 0xFFFF0000u)};
+}
+__device__ __forceinline__ Split4 split4(v4f v)
+{
+    Split4 s;
+    s.p[0] = pack4(v.x, v.y, v.z, v.w);
+    v4f r = v - unpack4(s.p[0]);
+    s.p[1] = pack4(r.x, r.y, r.z, r.w);
+    r = r - unpack4(s.p[1]);
+    s.p[2] = pack4(r.x, r.y, r.z, r.w);
+    return s;
+}
+// The six products of a 32 x 32 x 16 step, smallest first
+__device__ __forceinline__ v16f mfma6(const v8bf (&a)[3], const v8bf (&b)[3], v16f c)
+{
+    c = mfma(a[2], b[0], c);
+    c = mfma(a[0], b[2], c);
+    c = mfma(a[1], b[1], c);
+    c = mfma(a[1], b[0], c);
+    c = mfma(a[0], b[1], c);
+    return mfma(a[0], b[0], c);
+}
+
+// ---------------------------------------------------------------------------
+// conv1, conv2 and conv3 forward in ONE launch.  A unit is the part of a sample that yields R3 of the seven
+// output rows of conv3 (R3 = 7: the whole sample): it needs R3 + 2 rows of conv2 and 2 R3 + 6 rows of conv1.
+// One workgroup of eight waves works on a unit at a time and keeps everything between the pixels
+// and conv3's output in LDS; only the rows the backward pass reads also go to memory.
+//   pixels    read from the ring (or the states) and staged as bf16 (exact)
+//   conv1     16x16x32: wave = (channel half, every fourth tile of 16 pixels), the wave's weights in registers
+//   conv2/3   32x32x16: wave = (channel half, quarter of the reduction), every weight fragment
+//             is read once per unit by one wave; the four partial tiles meet in LDS, each wave
+//             finishing a quarter of the channels (bias, ReLU, split)
+// The weights (456 KB of parts per network) do not fit a CU beside the images, so they stream from the
+// L2s: conv2's are requested before conv1 starts, conv3's take the registers conv2's leave step by step,
+// and conv1's of the next unit those of conv3's; so do the next unit's pixels.
+// R3 = 7 is the least work (no row twice); with few samples smaller parts spread a sample over
+// several CUs, recomputing the rows that neighbouring parts share: R3 = 4 costs 1.3 times the conv1 and 1.2 times
+// the conv2 work, R3 = 1 2.8 and 2.3 times.
+// Image layout: a pixel's 32 (64) channels of part 0, then part 1, then part 2, at a pitch of an odd
+// number of 16-byte units, so that the pixels of an output row hit different banks; conv1's image holds
+// the even columns of a row before the odd ones (conv2 has stride 2).
+// In draw mode the workgroup draws its units' transitions (two per wave and walk) before the first pixel;
+// the workgroups that own part 0 of segment 0 publish the draws.
+// ---------------------------------------------------------------------------
+struct Seg {
+    gbf::c1::Src src;
+    const bf16_t *w;             // packed conv weights
+    const float *b1, *b2, *b3;
+    float *y1, *y2;              // conv1 / conv2 output for the backward pass, or nullptr
+    float *y3;
+    int n;
+    int first;                   // first unit of the segment
+    uint8_t *stack;              // where the frames are left for conv1's weight gradient ([n][5][84][84]), or nullptr
+};
+struct Args {
+    Seg seg[3];
+    int nseg;
+    int units;                   // of all segments
+    int draw;                    // segment samples are drawn here (every segment has the same n)
+    misc::SampleArgs samp;
+};
+constexpr int MAX_UNITS = 96;    // units of one workgroup at most
+constexpr int W2_PRE = 6;        // steps of conv2's weights that are requested before conv1 (all eight do not fit beside it)
+
+template <int R3> struct Geo {
+    static constexpr int PARTS = (7 + R3 - 1) / R3;
+    static constexpr bool MANY = R3 == 7;   // a workgroup takes one unit after the other; otherwise just one
+    static constexpr int R2 = R3 + 2, R1 = 2 * R3 + 6, PR = 4 * R1 + 4;   // rows of conv2, conv1, pixels
+    static constexpr int M1 = R1 * 20, M2 = R2 * 9, M3 = R3 * 7;
+    static constexpr int T1 = (M1 + 15) / 16, T2 = (M2 + 31) / 32, T3 = (M3 + 31) / 32;
+    static constexpr int CH = PR * 84 / 16, NPX = (4 * CH + 511) / 512;   // 16-byte pieces per frame, per thread
+    static constexpr int PXB = 4 * PR * 84 * 2;   // pixels; later conv2's image
+    static constexpr int P1 = 208, P2 = 400;      // pixel pitch of the images in bytes
+    static constexpr int I1B = M1 * P1;           // conv1's image; later the partial tiles
+    static constexpr int TAB = (2 * MAX_UNITS + 4) * 4;
+    static constexpr int LDS = PXB + I1B + TAB;
+    static_assert(PR * 84 % 16 == 0 && M2 * P2 <= PXB && 24 * T2 * 1024 <= I1B && 24 * T3 * 1024 <= I1B, "LDS layout");
+};
+
+// The partial tiles of the four waves of a channel half: wave kq ends up with rows 8 kq + 4 h + 0..3 of the half
+// (accumulator registers 4 kq .. 4 kq + 3), summed in the order own, then the others ascending.
+template <int T>
+__device__ __forceinline__ void reduce_quarters(const v16f (&acc)[T], v4f (&own)[T], v4f *scratch, int kq, int ch, int lane)
+{
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        if (g == kq) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) own[t] = v4f{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+        } else {
+            v4f *d = scratch + (((g * 3 + (kq < g ? kq : kq - 1)) * 2 + ch) * T) * 64 + lane;
+#pragma unroll
+            for (int t = 0; t < T; ++t) d[t * 64] = v4f{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+        }
+    }
+    sync_lds();
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int t = 0; t < T; ++t) own[t] += scratch[(((kq * 3 + j) * 2 + ch) * T + t) * 64 + lane];
+}
+
+template <int R3>
+__global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
+{
+    // The segments are indexed at run time; through the by-value structure that would be a copy in scratch
+    // memory, or a select over three times fifteen scalars.  The arguments themselves lie in constant memory.
+    typedef const __attribute__((address_space(4))) Args *ArgsPtr;
+    const ArgsPtr AP = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+#define SP_SEG(s) (AP->seg[s])
+    const Args &A = A_by_value;
+    using G = Geo<R3>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    uint8_t *pxb = lds, *img1 = lds + G::PXB;
+    bf16_t *px = reinterpret_cast<bf16_t *>(pxb);
+    uint8_t *img2 = pxb;
+    v4f *scratch = reinterpret_cast<v4f *>(img1);
+    int *slots = reinterpret_cast<int *>(lds + G::PXB + G::I1B);
+    float *leafv = reinterpret_cast<float *>(slots + MAX_UNITS);   // [MAX_UNITS], then the total
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nt = wave & 1, tg = wave >> 1;      // conv1
+    const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
+    int tid = threadIdx.x, lane = tid & 63;
+    const int G0 = (int)gridDim.x;
+    const int nu = G::MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
+
+    auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
+    v8bf w1[8][3];
+    auto load_w1 = [&](const bf16_t *w, int s) {
+        const v8bf *p = reinterpret_cast<const v8bf *>(w + (nt * 8 + s) * 3 * FRAG) + lane;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) w1[s][q] = p[q * 64];
+    };
+    u32x4 raw[G::NPX];
+    auto load_px = [&](int si, int u, int slot) {
+        const int ul = u - SP_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
+        const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
+        const uint8_t *f[4];
+        const gbf::c1::Src src{SP_SEG(si).src.x, SP_SEG(si).src.xs, SP_SEG(si).src.idx, SP_SEG(si).src.cap, SP_SEG(si).src.shift, SP_SEG(si).src.sub};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = gbf::c1::frame_ptr(src, g, slot, k) + row0 * (8 * 84);
+#pragma unroll
+        for (int i = 0; i < G::NPX; ++i) {
+            int t = tid + 512 * i;
+            if (t > 4 * G::CH - 1) t = 4 * G::CH - 1;
+            const int k = t / G::CH;
+            const uint8_t *fp = k == 0 ? f[0] : k == 1 ? f[1] : k == 2 ? f[2] : f[3];
+            raw[i] = *reinterpret_cast<const u32x4 *>(fp + (t - k * G::CH) * 16);
+        }
+    };
+
+    int u = (int)blockIdx.x;
+    int si = seg_of(u);
+    const bool ring = A.seg[0].src.idx != nullptr;   // of every segment, or of none
+#pragma unroll
+    for (int s = 0; s < 8; ++s) load_w1(SP_SEG(si).w, s);
+    if (ring) {
+        if (A.draw) {
+#pragma unroll 1
+            for (int k = 2 * wave; k < nu; k += 16) {
+                const int kb = k + 1 < nu ? k + 1 : k;
+                // (draw j of a segment is its sample j)
+                const int ga = (u + k * G0) / G::PARTS, gb = (u + kb * G0) / G::PARTS, n = A.seg[0].n;
+                const int jj[2] = {ga % n, gb % n};
+                long sl[2];
+                float leaf[2];
+                const float total = misc::per_sample_walk<2>(A.samp, jj, lane, sl, leaf);
+                if (lane == 0) {
+                    slots[k] = (int)sl[0];
+                    slots[kb] = (int)sl[1];
+                    leafv[k] = leaf[0];
+                    leafv[kb] = leaf[1];
+                    if (k == 0) leafv[MAX_UNITS] = total;
+                }
+            }
+        } else {
+            for (int k = tid; k < nu; k += 512) {
+                // (the segments' index lists are one and the same)
+                slots[k] = A.seg[0].src.idx[(u + k * G0) / G::PARTS % A.seg[0].n];
+            }
+        }
+        sync_lds();   // the slot table is complete
+    }
+    load_px(si, u, ring ? slots[0] : 0);
+    if (A.draw && wave == 7)   // index, raw importance weight and transition data of the segment-0 draws
+        for (int k = lane; k < nu; k += 64) {
+            const int uk = u + k * G0;
+            if (uk < A.seg[0].n * G::PARTS && uk % G::PARTS == 0)
+                misc::per_sample_emit(A.samp, uk / G::PARTS, slots[k], leafv[MAX_UNITS], leafv[k]);
+        }
+
+    for (int k = 0; k < nu; ++k) {
+        // opaque, so that the lane addresses of all phases are formed where they are used and do not occupy
+        // registers throughout the loop
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        const int n16 = lane & 15, kg = lane >> 4, i32 = lane & 31, h = lane >> 5;
+        const int ul = u - SP_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
+        const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
+        const bf16_t *const wts = SP_SEG(si).w;
+        const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
+        // pixels -> LDS
+        uint8_t *const stack = SP_SEG(si).stack;
+#pragma unroll
+        for (int i = 0; i < G::NPX; ++i) {
+            const int t = tid + 512 * i;
+            if (t < 4 * G::CH) {
+                uint4 *d = reinterpret_cast<uint4 *>(px + t * 16);
+                d[0] = gbf::cvt8_u8(raw[i].x, raw[i].y);
+                d[1] = gbf::cvt8_u8(raw[i].z, raw[i].w);
+                if (stack) {
+                    const int f = t / G::CH;
+                    *reinterpret_cast<u32x4 *>(stack + ((long)g * 5 + f) * net::FRAME + row0 * (8 * 84) + (t - f * G::CH) * 16) = raw[i];
+                }
+            }
+        }
+        sync_lds();
+        v8bf w2[8][3], w3[9][3];
+        const v8bf *p2 = reinterpret_cast<const v8bf *>(wts + W2_AT + (((kq * 2 + ch) * 8) * 3) * FRAG) + lane;
+        const v8bf *p3 = reinterpret_cast<const v8bf *>(wts + W3_AT + (((kq * 2 + ch) * 9) * 3) * FRAG) + lane;
+#pragma unroll
+        for (int s = 0; s < W2_PRE; ++s)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
+        const v4f bias1 = *reinterpret_cast<const v4f *>(SP_SEG(si).b1 + 16 * nt + 4 * kg);
+        const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2 and conv3
+        float *const y1 = SP_SEG(si).y1, *const y2 = SP_SEG(si).y2;
+        __builtin_amdgcn_sched_barrier(0);
+
+        // ---- conv1
+#pragma unroll 1
+        for (int t = tg; t < G::T1; t += 4) {
+            const int m = 16 * t + n16, mc = m < G::M1 ? m : G::M1 - 1;
+            const int y = mc / 20, x = mc - 20 * y;
+            const bf16_t *p = px + (4 * y + kg) * 84 + 4 * x;
+            auto pixels = [&](int s) {   // frame s / 2, kernel rows 4 (s % 2) + kg
+                return __builtin_bit_cast(v8bf, *reinterpret_cast<const u32x4_a8 *>(p + (s >> 1) * (G::PR * 84) + (s & 1) * (4 * 84)));
+            };
+            v4f a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
+            v8bf b0 = pixels(0), b1 = pixels(1);
+#pragma unroll
+            for (int s = 0; s < 8; s += 2) {
+                const v8bf c0 = b0, c1 = b1;
+                if (s < 6) { b0 = pixels(s + 2); b1 = pixels(s + 3); }
+                __builtin_amdgcn_sched_barrier(0);
+                a0 = mfma16(w1[s][2], c0, a0);
+                a1 = mfma16(w1[s + 1][2], c1, a1);
+                a0 = mfma16(w1[s][1], c0, a0);
+                a1 = mfma16(w1[s + 1][1], c1, a1);
+                a0 = mfma16(w1[s][0], c0, a0);
+                a1 = mfma16(w1[s + 1][0], c1, a1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            constexpr float sc = 1.0f / 255.0f;
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf((a0[r] + a1[r]) * sc + bias1[r], 0.f);
+            if (m < G::M1) {
+                const Split4 q = split4(v);
+                uint8_t *d = img1 + (y * 20 + (x & 1) * 10 + (x >> 1)) * G::P1 + (16 * nt + 4 * kg) * 2;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 64) = q.p[pl];
+                if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
+                    *reinterpret_cast<v4f *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 16 * nt + 4 * kg) = v;
+            }
+        }
+        sync_lds();
+
+        // ---- conv2: kernel row kq
+        {
+            constexpr int T = G::T2, NA = T == 1 ? 2 : 1;
+            const uint8_t *pa[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                int m = 32 * t + i32;
+                if (m > G::M2 - 1) m = G::M2 - 1;
+                const int y = m / 9, x = m - 9 * y;
+                pa[t] = img1 + ((2 * y + kq) * 20 + x) * G::P1 + h * 16;
+            }
+            v16f acc[NA][T];
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
+#pragma unroll
+            for (int s = W2_PRE; s < 8; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
+            v8bf b[3], nb[3];
+            auto load_b = [&](int i) {
+                const int s = i / T, t = i % T, off = (((s >> 1) & 1) * 10 + (s >> 2)) * G::P1 + (s & 1) * 32;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 64);
+            };
+            load_b(0);
+#pragma unroll
+            for (int i = 0; i < 8 * T; ++i) {   // the operands of a product are requested before the one before it
+                const int s = i / T, t = i % T;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) b[pl] = nb[pl];
+                if (i + 1 < 8 * T) load_b(i + 1);
+                if (t == 0 && s > 0) {          // conv3's weights into the registers of step s - 1
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) w3[s - 1][q] = p3[((s - 1) * 3 + q) * 64];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                acc[s % NA][t] = mfma6(w2[s], b, acc[s % NA][t]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int q = 0; q < 6; ++q) w3[7 + q / 3][q % 3] = p3[(7 * 3 + q) * 64];
+            const v4f bias2 = *reinterpret_cast<const v4f *>(SP_SEG(si).b2 + co);
+            if constexpr (NA == 2) acc[0][0] += acc[1][0];
+            sync_lds();   // every wave has read conv1's image
+            v4f own[T];
+            reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int m = 32 * t + i32, y = m / 9;
+                v4f v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(own[t][r] + bias2[r], 0.f);
+                if (m < G::M2) {
+                    const Split4 q = split4(v);
+                    uint8_t *d = img2 + m * G::P2 + co * 2;
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 128) = q.p[pl];
+                    if (y2 && row0 + y >= rowp + G::R2)
+                        *reinterpret_cast<v4f *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + co) = v;
+                }
+            }
+        }
+        // the next unit's pixels
+        // (behind the last unit: its own once more, so that the registers are written on every path and do not
+        // have to keep their old contents until here)
+        const int kn = k + 1 < nu ? k + 1 : k, un = (int)blockIdx.x + kn * G0, sn = seg_of(un);
+        const bf16_t *const wn = SP_SEG(sn).w;
+        if constexpr (G::MANY) load_px(sn, un, ring ? slots[kn] : 0);
+        sync_lds();
+
+        // ---- conv3: steps 9 kq .. 9 kq + 8 of 36
+        {
+            constexpr int T = G::T3, NA = T == 1 ? 2 : 1;
+            const uint8_t *pa[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                int m = 32 * t + i32;
+                if (m > G::M3 - 1) m = G::M3 - 1;
+                const int y = m / 7, x = m - 7 * y;
+                pa[t] = img2 + (y * 9 + x) * G::P2 + h * 16;
+            }
+            v16f acc[NA][T];
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
+            v8bf b[3], nb[3];
+            auto load_b = [&](int i) {
+                const int s = i / T, t = i % T, sg = 9 * kq + s, tap = sg >> 2;
+                const int off = ((tap / 3) * 9 + tap % 3) * G::P2 + (sg & 3) * 32;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 128);
+            };
+            load_b(0);
+#pragma unroll
+            for (int i = 0; i < 9 * T; ++i) {
+                const int s = i / T, t = i % T;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) b[pl] = nb[pl];
+                if (i + 1 < 9 * T) load_b(i + 1);
+                if (G::MANY && t == 0 && s > 0) load_w1(wn, s - 1);   // conv1's weights of the next unit
+                __builtin_amdgcn_sched_barrier(0);
+                acc[s % NA][t] = mfma6(w3[s], b, acc[s % NA][t]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const v4f bias3 = *reinterpret_cast<const v4f *>(SP_SEG(si).b3 + co);
+            if constexpr (NA == 2) acc[0][0] += acc[1][0];
+            v4f own[T];
+            reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int m = 32 * t + i32, y = m / 7;
+                v4f v;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(own[t][r] + bias3[r], 0.f);
+                if (m < G::M3 && row0 + y >= rowp + R3)
+                    *reinterpret_cast<v4f *>(SP_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + co) = v;
+            }
+        }
+        if (!G::MANY) break;
+        si = sn;
+        u += G0;
+    }
+#undef SP_SEG
+}
+
+}  // namespace sp

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "net.h"
+#include "packed.h"
 #include "sumtree.h"
 
 namespace misc {
@@ -496,7 +497,8 @@ struct RmsArgs {
     RmsSeg seg[5];
     float *theta, *v, *m, *g;
     __hip_bfloat16 *shadow;  // bf16 copy of theta (same order) or nullptr
-    __hip_bfloat16 *w2t;     // with it: conv2's weights once more, as [tap][channel in][channel out] (or nullptr)
+    uint16_t *packed;        // fp32 path: the conv weights as bf16 parts (packed.h), or nullptr
+    __hip_bfloat16 *w2t;     // with the bf16 copy: conv2's weights once more, as [tap][channel in][channel out] (or nullptr)
     float lr, rho, eps;
 };
 
@@ -520,6 +522,10 @@ __device__ __forceinline__ void rms_apply(const RmsArgs &A, long i, float g, con
     A.theta[i] = th;
     if (store_g) A.g[i] = g;
     if (A.shadow) A.shadow[i] = __float2bfloat16(th);
+    if (A.packed) {
+        const int at = sp::packed_at(i);
+        if (at >= 0) sp::store_parts(A.packed, at, th);
+    }
     if (A.w2t && i >= net::C2W && i < net::C2W + 64 * 512) {
         const int t = (int)(i - net::C2W);   // [channel out][tap][channel in]
         A.w2t[(t & 511) * 64 + (t >> 9)] = __float2bfloat16(th);
