@@ -416,7 +416,7 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 // results stay those of the plain fp32 chain; the two passes over s', whose activations are only values,
 // take the split form at every size.  Small batches, where a layer-by-layer chain is latency and nothing
 // else, take it for all three: the line lies where a sample no longer has two workgroups to itself.
-bool keeps_fp32_order(const dqn_ctx *c, const Pass *pass, int npass) { return npass == 3 && 2 * 3 * pass[0].n > c->num_cu; }
+bool keeps_fp32_order(const dqn_ctx *c, int B) { return 2 * 3 * B > c->num_cu; }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not
 // (few compute units and a large batch), a sampling launch runs in front of the step.
 bool in_kernel_draw_fits(const dqn_ctx *c, int B)
@@ -456,7 +456,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
     };
 
     // conv1, conv2 and conv3: one launch for the passes [p0, npass)
-    const int p0 = keeps_fp32_order(c, pass, npass) ? 1 : 0;
+    const int p0 = npass == 3 && keeps_fp32_order(c, pass[0].n) ? 1 : 0;
     {
         const int samples = (int)(rows - row0[p0]);
         const Conv123Plan plan = conv123_plan(samples, c->num_cu);
@@ -471,7 +471,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
             A.seg[i - p0] = sp::Seg{gbf::c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
                                     c->ws.packed + (pass[i].net ? sp::W_TOTAL : 0), theta + net::C1B, theta + net::C2B, theta + net::C3B,
                                     keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
-                                    pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts, pass[i].stack};
+                                    pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts};
         }
         for (int i = A.nseg; i < 3; ++i) A.seg[i] = A.seg[0];
         A.units = samples * plan.parts;
@@ -796,12 +796,26 @@ __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::Wg
     }
 }
 
+// conv2's two gradients and conv1's weight gradient in split form (sp::conv2_dgrad_conv1_wgrad_body): nps workgroups
+// take fifths of samples, the others are 64 x 256 tiles of conv2's weight gradient.
+constexpr int BACK_PARTS = 5;
+constexpr int CONV21_LDS = std::max({(int)sp::BackGeo<BACK_PARTS>::LDS, 2 * sp::wgrad_lds<64, 256>(), 4 * misc::PU_LDS_WORDS});
+__global__ __launch_bounds__(512, 1) void k_conv21_bwd_sp(sp::BackArgs PA, g32::WgradArgs WA, int nps, SplitUpdate U)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_dyn[];
+    if (U.on && blockIdx.x == 0) return update_part(U, 3, reinterpret_cast<int *>(lds_dyn));
+    const int id = (int)blockIdx.x - U.on;
+    if (id < nps) sp::conv2_dgrad_conv1_wgrad_body<BACK_PARTS>(PA, id, nps, lds_dyn);
+    else sp::wgrad_tile<g32::GConv2, 64, 256, 2, 1>(WA, (id - nps) & 1, 0, (id - nps) >> 1, reinterpret_cast<gbf::bf16_t *>(lds_dyn));
+}
+
 // ----- backward through fc1, conv3, conv2, conv1 (no input gradient for conv1) -----
 // The input-gradient chain and conv1's weight gradient run on st; the weight gradients of fc1,
 // conv3 and conv2 run on sd behind the events the chain records.  All of st's kernels are
 // enqueued before any of sd's: handing the host from one stream to another costs more than a
 // launch, and the device does not care in which order the host filled the two queues.
-void backward_f32(dqn_ctx *c, int B, const uint8_t *s, long xs, int *ns1, int *ns2, int *ns3, hipStream_t st,
+// ps: the pass on s; s, xs: its frames as contiguous states (small batches: not used).
+void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, int *ns1, int *ns2, int *ns3, hipStream_t st,
                   hipStream_t sd, const SmallTail *tail)
 {
     using namespace g32;
@@ -853,6 +867,21 @@ void backward_f32(dqn_ctx *c, int B, const uint8_t *s, long xs, int *ns1, int *n
                     k_layer_bwd_f32<DConv3, 64, 64, 1, GConv3, 256, false, 1><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G3, P, HW, U);
                 });
             }
+        }
+        if (!keeps_fp32_order(c, B)) {
+            // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample
+            // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient
+            const int nps = std::min({BACK_PARTS * B, std::max(1, c->num_cu * 5 / 8), MAX_WSPLIT1});
+            const int splits = std::max(1, std::min<int>(MAX_WSPLIT, (c->num_cu - nps - U.on) / 2));
+            const long rows = (long)B * 81;
+            const int rps = (int)((std::max<long>((rows + splits - 1) / splits, 64) + 31) / 32 * 32);
+            *ns2 = (int)((rows + rps - 1) / rps);
+            *ns1 = nps;
+            const sp::BackArgs PA{d2, w.packed, act1,
+                                  gbf::c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, B};
+            const WgradArgs G{d2, act1, w.gp2, B, rps, net::A1, net::L2N, 1.0f};
+            launch(c, "conv21_bwd", st, [&] { k_conv21_bwd_sp<<<nps + 2 * *ns2 + U.on, 512, CONV21_LDS, st>>>(PA, G, nps, U); });
+            return;
         }
         {
             DgradArgs D{d2, c->theta + net::C2W, act1, d1, B};
@@ -1126,8 +1155,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
     if (cfg->precision == 0) {
         pack_conv(c, 0, st);
         pack_conv(c, 1, st);
-        // the forward launch of the conv layers holds a sample's images in LDS
-        if (hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
+        // the launches of the conv layers hold images in LDS
+        if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
+            hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
             hipFuncSetAttribute((const void *)sp::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<7>::LDS) != hipSuccess) {
             (void)hipGetLastError();
             delete c;
@@ -1708,7 +1738,7 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     // (of 20 levels: 2, 5, 7 and 6; the RMSProp launch is the one its part can outlast, fc1's the shortest)
     const SplitUpdate U{PU, w.pu_state, {lv / 10, 7 * lv / 20, 7 * lv / 10}, batch ? 0 : 1};
     if (cfg.precision == 1) backward_bf16(c, B, passes[0], &ns1, &ns2, &ns3, st, HW, U);
-    else backward_f32(c, B, stacking ? w.stack5 : s, stacking ? 5L * net::FRAME : xs, &ns1, &ns2, &ns3, st, sd,
+    else backward_f32(c, B, passes[0], stacking ? w.stack5 : s, stacking ? 5L * net::FRAME : xs, &ns1, &ns2, &ns3, st, sd,
                       fuse_tail ? &tail : nullptr);
     ev_record(c->ev_join, sd, st);
     ev_wait(st, c->ev_join, sd);

@@ -18,6 +18,7 @@
 #include <stdint.h>
 
 #include "gemm_bf16.h"
+#include "gemm_fp32.h"
 #include "net.h"
 #include "packed.h"
 #include "sumtree.h"
@@ -91,7 +92,6 @@ struct Seg {
     float *y3;
     int n;
     int first;                   // first unit of the segment
-    uint8_t *stack;              // where the frames are left for conv1's weight gradient ([n][5][84][84]), or nullptr
 };
 struct Args {
     Seg seg[3];
@@ -241,7 +241,6 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         const bf16_t *const wts = SP_SEG(si).w;
         const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
         // pixels -> LDS
-        uint8_t *const stack = SP_SEG(si).stack;
 #pragma unroll
         for (int i = 0; i < G::NPX; ++i) {
             const int t = tid + 512 * i;
@@ -249,10 +248,6 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 uint4 *d = reinterpret_cast<uint4 *>(px + t * 16);
                 d[0] = gbf::cvt8_u8(raw[i].x, raw[i].y);
                 d[1] = gbf::cvt8_u8(raw[i].z, raw[i].w);
-                if (stack) {
-                    const int f = t / G::CH;
-                    *reinterpret_cast<u32x4 *>(stack + ((long)g * 5 + f) * net::FRAME + row0 * (8 * 84) + (t - f * G::CH) * 16) = raw[i];
-                }
             }
         }
         sync_lds();
@@ -433,6 +428,359 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         u += G0;
     }
 #undef SP_SEG
+}
+
+// ---------------------------------------------------------------------------
+// The backward pass.  Operands are fp32 in memory; a thread splits what it has loaded on the way into LDS (22
+// vector instructions per four values), where an operand tile lies three times, once per part.  A 16-deep
+// step of a 32 x 32 block reads six fragments for six products, half the LDS bytes per product of a plain
+// bf16 tile.
+// ---------------------------------------------------------------------------
+constexpr int BK = 32;           // reduction elements per stage of a weight-gradient tile
+
+// four values into the three part tiles (PS elements apart)
+template <int PS> __device__ __forceinline__ void put4(bf16_t *p, v4f v)
+{
+    const Split4 s = split4(v);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2 *>(p + q * PS) = s.p[q];
+}
+template <int PS> __device__ __forceinline__ void get_tr(v8bf (&f)[3], const bf16_t *p, int ld)
+{
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[q] = gbf::frag_tr(p + q * PS, ld);
+}
+
+// Weight gradient (see g32::wgrad_tile): output channels [by*BMO, +BMO) x im2col columns [bx*BNK, +BNK) over the rows
+// of split bz.  Both operands have the reduction as their slow dimension: LDS transpose loads.
+template <int BMO, int BNK> constexpr int wgrad_lds() { return 3 * BK * (BMO + 8 + BNK + 8); }   // elements
+template <class G, int BMO, int BNK, int WM, int WN>
+__device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int by, int bz, bf16_t *lds)
+{
+    constexpr int WAVES_M = BMO / (32 * WM), WAVES_N = BNK / (32 * WN), T = WAVES_M * WAVES_N * 64;
+    constexpr int LDY = BMO + 8, LDX = BNK + 8, PY = BK * LDY, PX = BK * LDX;
+    constexpr int YR = T / (BMO / 4), XR = T / (BNK / 4), NY = BK / YR, NX = BK / XR;
+    static_assert(NY * YR == BK && NX * XR == BK, "tile/threads mismatch");
+    bf16_t *Ys = lds, *Xs = lds + 3 * PY;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kc0 = bx * BNK, o0 = by * BMO;
+    const int mbeg = bz * A.rps, mend = min(mbeg + A.rps, A.B * G::P);
+    const float *x = static_cast<const float *>(A.x);
+    const int yr = tid / (BMO / 4), yc = (tid % (BMO / 4)) * 4;
+    const int xr = tid / (BNK / 4), xc = (tid % (BNK / 4)) * 4;
+    const int xko = G::k_off(kc0 + xc);
+    v4f ry[NY], rx[NX];
+    int left = 0;   // rows of the loaded stage that exist
+    auto gload = [&](int mb) {
+        left = mend - mb;
+#pragma unroll
+        for (int i = 0; i < NY; ++i) ry[i] = *reinterpret_cast<const v4f *>(A.dy + (long)min(mb + yr + i * YR, mend - 1) * G::N + o0 + yc);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) rx[i] = *reinterpret_cast<const v4f *>(x + G::row_off(min(mb + xr + i * XR, mend - 1), A.xs) + xko);
+    };
+    auto sstore = [&]() {
+        // (rows past the end: dY as zeros is enough)
+#pragma unroll
+        for (int i = 0; i < NY; ++i) put4<PY>(&Ys[(yr + i * YR) * LDY + yc], yr + i * YR < left ? ry[i] : v4f{0, 0, 0, 0});
+#pragma unroll
+        for (int i = 0; i < NX; ++i) put4<PX>(&Xs[(xr + i * XR) * LDX + xc], rx[i]);
+    };
+    const int wo = wave % WAVES_M, wk = wave / WAVES_M;
+    const int li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
+    const int trow = 8 * h + (s16 >> 2), tcol = 16 * half + 4 * (s16 & 3);
+    const bf16_t *yp = Ys + trow * LDY + wo * 32 * WM + tcol, *xp = Xs + trow * LDX + wk * 32 * WN + tcol;
+    const bool do_bias = bx == 0 && wk == 0;
+    v16f acc[WM][WN], accb[WM];
+#pragma unroll
+    for (int a = 0; a < WM; ++a) {
+        accb[a] = v16f{0};
+#pragma unroll
+        for (int b = 0; b < WN; ++b) acc[a][b] = v16f{0};
+    }
+    v8bf ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    if (mbeg < mend) gload(mbeg);
+    for (int mb = mbeg; mb < mend; mb += BK) {
+        if (mb != mbeg) sync_lds();
+        sstore();
+        if (mb + BK < mend) gload(mb + BK);
+        sync_lds();
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 16) {
+            v8bf fa[WM][3], fb[WN][3];
+#pragma unroll
+            for (int a = 0; a < WM; ++a) get_tr<PY>(fa[a], yp + kk * LDY + a * 32, LDY);
+#pragma unroll
+            for (int b = 0; b < WN; ++b) get_tr<PX>(fb[b], xp + kk * LDX + b * 32, LDX);
+#pragma unroll
+            for (int a = 0; a < WM; ++a) {
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = mfma6(fa[a], fb[b], acc[a][b]);
+                if (do_bias) {
+                    accb[a] = mfma(fa[a][2], ones, accb[a]);
+                    accb[a] = mfma(fa[a][1], ones, accb[a]);
+                    accb[a] = mfma(fa[a][0], ones, accb[a]);
+                }
+            }
+        }
+    }
+    float *part = A.part + (long)bz * A.part_stride;
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int o = o0 + (wo * WM + a) * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+#pragma unroll
+            for (int b = 0; b < WN; ++b) part[(long)o * G::K + kc0 + (wk * WN + b) * 32 + li] = acc[a][b][r];
+            if (do_bias && li == 0) part[(long)G::N * G::K + o] = accb[a][r];
+        }
+}
+
+// ---------------------------------------------------------------------------
+// conv2's input gradient AND conv1's weight gradient of a part of a sample in one workgroup of eight waves:
+// conv1's dY is needed by nothing but conv1's weight gradient, position by position, so it goes into LDS, in the
+// layout the weight gradient reads, and never to memory.  A unit is 1/P of a sample: 20 / P rows of conv1's
+// output, which take the (10 / P) + 1 rows of conv2's dY around them (no work twice).
+//   input gradient   32x32x16; wave = (stride parity class, kernel rows py or py + 2): a pixel of a class meets four
+//                    taps, a wave two of them: 96 registers of weights, fetched once per workgroup.  The two
+//                    halves of the sum meet in LDS, each wave finishing 16 of the 32 channels
+//   weight gradient  32x32x16, three products (pixels are exact); wave = (64 of the 256 columns, every other step of 16
+//                    positions); the two halves meet once, at the end
+// Workgroup b takes units b, b + nblocks, ... and writes one partial of conv1's weight gradient.
+// ---------------------------------------------------------------------------
+struct BackArgs {
+    const float *dy;      // [B][81][64]: gradient w.r.t. conv2's pre-activation
+    const uint16_t *w;    // packed conv weights
+    const float *xact;    // [B][400][32]: conv1's output
+    gbf::c1::Src src;     // where the frames of sample n come from
+    float *part1;         // [nblocks][32*256 + 32]
+    int B;
+};
+template <int P> struct BackGeo {
+    static constexpr int RA = 10 / P, RD = 2 * RA, NPOS = RD * 20, NKS = (NPOS + 15) / 16;
+    static constexpr int T = (RA * 10 + 31) / 32;              // tiles of 32 positions of a class
+    static constexpr int FRW = 4 * RD + 4, CH = FRW * 84 / 16, NPX = (4 * CH + 511) / 512;
+    static constexpr int NDY = ((RA + 1) * 9 * 16 + 511) / 512; // 16-byte pieces of dY per thread
+    static constexpr int LDY = 40;                              // row stride (elements) of conv1's dY
+    static constexpr int PD = NKS * 16 * LDY;                   // elements of one part of it
+    static constexpr int DYS = 3 * PD * 2, IMG = (RA + 1) * 11 * 400, XIN = 4 * FRW * 84 * 2, SCR = 16 * T * 1024;
+    static constexpr int SCRB = SCR > 32768 ? SCR : 32768;      // (the final exchange of the weight gradient needs 32 KB)
+    static constexpr int LDS = DYS + IMG + XIN + SCRB;
+    static_assert(DYS % 16 == 0 && IMG % 16 == 0 && XIN % 16 == 0 && FRW * 84 % 16 == 0 && RD * 4 * 84 % 16 == 0, "LDS layout");
+};
+
+template <int P>
+__device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, int bid, int nblocks, uint8_t *lds)
+{
+    using G = BackGeo<P>;
+    bf16_t *dys = reinterpret_cast<bf16_t *>(lds), *xin = reinterpret_cast<bf16_t *>(lds + G::DYS + G::IMG);
+    uint8_t *img = lds + G::DYS;
+    v4f *scr = reinterpret_cast<v4f *>(lds + G::DYS + G::IMG + G::XIN);
+    int tid = threadIdx.x, lane = tid & 63, i32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int py = (wave >> 1) & 1, px = wave & 1, kh = wave >> 2, cls = wave & 3;
+    const int units = A.B * P;
+    if (bid >= units) return;
+
+    v4f rdy[G::NDY];
+    u32x4 raw[G::NPX];
+    auto load_unit = [&](int u, int slot) {
+        const int g = u / P, part = u % P;
+        const float *d = A.dy + (long)g * net::A2;
+#pragma unroll
+        for (int i = 0; i < G::NDY; ++i) {   // piece e: row e / 144, column and channels e % 144
+            const int e = tid + 512 * i, r = part * G::RA - 1 + e / 144;
+            const bool in = e < (G::RA + 1) * 144 && r >= 0 && r < 9;
+            rdy[i] = *reinterpret_cast<const v4f *>(d + (in ? r * 576 + (e % 144) * 4 : 0));
+        }
+        const uint8_t *f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = gbf::c1::frame_ptr(A.src, g, slot, k) + part * (G::RD * 4 * 84);
+#pragma unroll
+        for (int i = 0; i < G::NPX; ++i) {
+            int t = tid + 512 * i;
+            if (t > 4 * G::CH - 1) t = 4 * G::CH - 1;
+            const int k = t / G::CH;
+            const uint8_t *fp = k == 0 ? f[0] : k == 1 ? f[1] : k == 2 ? f[2] : f[3];
+            raw[i] = *reinterpret_cast<const u32x4 *>(fp + (t - k * G::CH) * 16);
+        }
+    };
+    const int slot0 = gbf::c1::sample_slot(A.src, bid / P);
+    v8bf wa[8][3];   // step s: kernel column px + 2 (s / 4), output channels 16 (s % 4) ..
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int tap = (py + 2 * kh) * 4 + px + 2 * (s >> 2);
+        const v8bf *p = reinterpret_cast<const v8bf *>(A.w + W2B_AT + ((tap * 4 + (s & 3)) * 3) * FRAG) + lane;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) wa[s][q] = p[q * 64];
+    }
+    load_unit(bid, slot0);
+    int slot_next = bid + nblocks < units ? gbf::c1::sample_slot(A.src, (bid + nblocks) / P) : 0;
+    // zeros once: the image's border columns, and the rows of conv1's dY past the last position
+    for (int i = tid; i < G::IMG / 16; i += 512) *reinterpret_cast<u32x4 *>(img + i * 16) = u32x4{0, 0, 0, 0};
+    for (int i = tid; i < 3 * (G::NKS * 16 - G::NPOS) * G::LDY / 2; i += 512) {
+        constexpr int W = (G::NKS * 16 - G::NPOS) * G::LDY / 2;   // words per part
+        reinterpret_cast<uint32_t *>(dys)[(W ? i / (W ? W : 1) : 0) * (G::PD / 2) + G::NPOS * G::LDY / 2 + (W ? i % (W ? W : 1) : 0)] = 0;
+    }
+
+    v16f wacc[2] = {v16f{0}, v16f{0}}, accb = {0};
+    v8bf ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    const int cp = wave & 3;   // weight gradient: columns 64 cp .. (frame cp)
+    const bool do_bias = cp == 0;
+
+    for (int u = bid; u < units; u += nblocks) {
+        asm volatile("" : "+v"(tid));   // opaque: see k_conv123_fwd
+        lane = tid & 63; i32 = lane & 31; h = lane >> 5;
+        const int g = u / P, part = u % P;
+        sync_lds();   // the unit before has been read (the first time: the zeros are there)
+#pragma unroll
+        for (int i = 0; i < G::NDY; ++i) {
+            const int e = tid + 512 * i, lr = e / 144, r = part * G::RA - 1 + lr, c = (e % 144) >> 4, ch = (e & 15) * 4;
+            if (e < (G::RA + 1) * 144) {
+                const Split4 q = split4(r >= 0 && r < 9 ? rdy[i] : v4f{0, 0, 0, 0});
+                uint8_t *d = img + (lr * 11 + c + 1) * 400 + ch * 2;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 128) = q.p[pl];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < G::NPX; ++i) {
+            const int t = tid + 512 * i;
+            if (t < 4 * G::CH) {
+                uint4 *d = reinterpret_cast<uint4 *>(xin + t * 16);
+                d[0] = gbf::cvt8_u8(raw[i].x, raw[i].y);
+                d[1] = gbf::cvt8_u8(raw[i].z, raw[i].w);
+            }
+        }
+        const int un = u + nblocks < units ? u + nblocks : u;   // (the last unit once more: the registers are written on every path)
+        load_unit(un, slot_next);
+        slot_next = u + 2 * nblocks < units ? gbf::c1::sample_slot(A.src, (u + 2 * nblocks) / P) : 0;
+        // conv1's activations (the ReLU mask) of the 16 channels this wave finishes
+        v4f xm[G::T][2];
+        int pos[G::T];
+#pragma unroll
+        for (int t = 0; t < G::T; ++t) {
+            const int m = 32 * t + i32, mc = m < G::RA * 10 ? m : G::RA * 10 - 1, a = mc / 10, b = mc - 10 * a;
+            pos[t] = (2 * a + py) * 20 + 2 * b + px;
+            const float *p = A.xact + (long)g * net::A1 + (part * G::NPOS + pos[t]) * 32 + 16 * kh + 4 * h;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) xm[t][j] = *reinterpret_cast<const v4f *>(p + 8 * j);
+        }
+        sync_lds();   // image and frames are complete
+
+        // ---- conv2's input gradient
+        v16f acc[G::T];
+        const uint8_t *pa[G::T];
+#pragma unroll
+        for (int t = 0; t < G::T; ++t) {
+            acc[t] = v16f{0};
+            const int m = 32 * t + i32, mc = m < G::RA * 10 ? m : G::RA * 10 - 1, a = mc / 10, b = mc - 10 * a;
+            pa[t] = img + ((a + 1 - kh) * 11 + b + 1) * 400 + h * 16;   // position (a - kh, b) of dY
+        }
+        v8bf b3[3], nb[3];
+        auto load_b = [&](int i) {
+            const int s = i / G::T, t = i % G::T, off = -(s >> 2) * 400 + (s & 3) * 32;
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 128);
+        };
+        load_b(0);
+#pragma unroll
+        for (int i = 0; i < 8 * G::T; ++i) {
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) b3[pl] = nb[pl];
+            if (i + 1 < 8 * G::T) load_b(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            acc[i % G::T] = mfma6(wa[i / G::T], b3, acc[i % G::T]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // accumulator register 4g + r = channel 8g + 4h + r; the wave keeps g = 2 kh, 2 kh + 1 and hands over the others
+        v4f own[G::T][2];
+#pragma unroll
+        for (int t = 0; t < G::T; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const v4f lo = {acc[t][4 * j], acc[t][4 * j + 1], acc[t][4 * j + 2], acc[t][4 * j + 3]};
+                const v4f hi = {acc[t][4 * j + 8], acc[t][4 * j + 9], acc[t][4 * j + 10], acc[t][4 * j + 11]};
+                own[t][j] = kh ? hi : lo;
+                scr[(((cls * 2 + (kh ^ 1)) * G::T + t) * 2 + j) * 64 + lane] = kh ? lo : hi;
+            }
+        sync_lds();
+#pragma unroll
+        for (int t = 0; t < G::T; ++t)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                v4f v = own[t][j] + scr[(((cls * 2 + kh) * G::T + t) * 2 + j) * 64 + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = xm[t][j][r] > 0.f ? v[r] : 0.f;
+                if (32 * t + i32 < G::RA * 10) put4<G::PD>(dys + pos[t] * G::LDY + 16 * kh + 8 * j + 4 * h, v);
+            }
+        sync_lds();   // conv1's dY is complete
+
+        // ---- conv1's weight gradient: frame cp, kernel rows 0 - 3 and 4 - 7, steps kh, kh + 2, ...
+        const int s16 = lane & 15, half = (lane >> 4) & 1, rsub = 8 * h + (s16 >> 2);
+        const int kc = 16 * half + 4 * (s16 & 3);
+        const bf16_t *yp = dys + rsub * G::LDY + 16 * half + 4 * (s16 & 3);
+        const bf16_t *xw = xin + cp * (G::FRW * 84) + (kc >> 3) * 84 + (kc & 7);
+        typedef __attribute__((address_space(3))) gbf::v4s *lds_v4s;
+        auto pixel = [&](int p) {   // window of position p (clamped: past the last one dY is zero)
+            if (G::NPOS % 16 != 0) p = p < G::NPOS ? p : G::NPOS - 1;
+            const int y = p / 20;
+            return 336 * y + 4 * (p - 20 * y);
+        };
+#pragma unroll
+        for (int t2 = 0; t2 < (G::NKS + 1) / 2; ++t2) {
+            const int t = 2 * t2 + kh;
+            if (t >= G::NKS) break;   // uniform for the wave
+            v8bf fa[3], fb[2];
+            get_tr<G::PD>(fa, yp + 16 * t * G::LDY, G::LDY);
+            const bf16_t *x0 = xw + pixel(16 * t + rsub), *x1 = xw + pixel(16 * t + rsub + 4);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {   // 32 columns = four kernel rows
+                const gbf::v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(x0 + b * 336));
+                const gbf::v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(x1 + b * 336));
+                typedef short v8s __attribute__((ext_vector_type(8)));
+                const v8s xb = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                fb[b] = __builtin_bit_cast(v8bf, xb);
+            }
+#pragma unroll
+            for (int pl = 2; pl >= 0; --pl) {
+                wacc[0] = mfma(fa[pl], fb[0], wacc[0]);
+                wacc[1] = mfma(fa[pl], fb[1], wacc[1]);
+                if (do_bias) accb = mfma(fa[pl], ones, accb);
+            }
+        }
+    }
+    // the odd steps join the even ones
+    float *sf = reinterpret_cast<float *>(scr);
+    float *part = A.part1 + (long)bid * (32 * 256 + 32);
+    if (kh == 1) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sf[((cp * 2 + b) * 16 + r) * 64 + lane] = wacc[b][r];
+        if (do_bias && i32 == 0) {
+            // (column 0 of the product with ones; conv1's dY is no longer read)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) reinterpret_cast<float *>(img)[16 * h + r] = accb[r];
+        }
+    }
+    sync_lds();
+    if (kh == 0) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = 8 * (r / 4) + 4 * h + (r % 4);
+                part[o * 256 + 64 * cp + 32 * b + i32] = (wacc[b][r] + sf[((cp * 2 + b) * 16 + r) * 64 + lane]) * (1.0f / 255.0f);
+            }
+        if (do_bias && i32 == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[32 * 256 + 8 * (r / 4) + 4 * h + (r % 4)] = accb[r] + reinterpret_cast<float *>(img)[16 * h + r];
+        }
+    }
 }
 
 }  // namespace sp

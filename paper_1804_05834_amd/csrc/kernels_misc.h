@@ -522,10 +522,7 @@ __device__ __forceinline__ void rms_apply(const RmsArgs &A, long i, float g, con
     A.theta[i] = th;
     if (store_g) A.g[i] = g;
     if (A.shadow) A.shadow[i] = __float2bfloat16(th);
-    if (A.packed) {
-        const int at = sp::packed_at(i);
-        if (at >= 0) sp::store_parts(A.packed, at, th);
-    }
+    if (A.packed && i < net::F1W) sp::store_packed(A.packed, i, th);
     if (A.w2t && i >= net::C2W && i < net::C2W + 64 * 512) {
         const int t = (int)(i - net::C2W);   // [channel out][tap][channel in]
         A.w2t[(t & 511) * 64 + (t >> 9)] = __float2bfloat16(th);

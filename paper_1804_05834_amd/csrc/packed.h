@@ -18,10 +18,13 @@ __device__ __forceinline__ float bf16_value(uint16_t b) { return __uint_as_float
 //   conv1: [channel half 16][step of 32][part]          16x16x32 operand: lane = channel + 16 * (k / 8)
 //   conv2: [kernel row][channel half 32][step of 16][part]  32x32x16 operand: lane = channel + 32 * (k / 8)
 //   conv3: [quarter of 9 steps][channel half 32][step of 16][part]
+// and once more for conv2's input gradient, whose reduction runs over the output channels:
+//   conv2: [tap][step of 16 output channels][part]          32x32x16 operand: lane = channel in + 32 * (channel out / 8)
 // ---------------------------------------------------------------------------
 constexpr int FRAG = 512;                       // elements of a fragment
 constexpr int W1_FR = 2 * 8 * 3, W2_FR = 4 * 2 * 8 * 3, W3_FR = 4 * 2 * 9 * 3;
-constexpr int W2_AT = W1_FR * FRAG, W3_AT = (W1_FR + W2_FR) * FRAG, W_TOTAL = (W1_FR + W2_FR + W3_FR) * FRAG;
+constexpr int W2_AT = W1_FR * FRAG, W3_AT = (W1_FR + W2_FR) * FRAG;
+constexpr int W2B_FR = 16 * 4 * 3, W2B_AT = W3_AT + W3_FR * FRAG, W_TOTAL = W2B_AT + W2B_FR * FRAG;
 
 // Where part 0 of conv parameter i of the blob (internal order) goes; part p is p * FRAG further.
 // -1: a bias or not a conv parameter.
@@ -42,6 +45,13 @@ __host__ __device__ __forceinline__ int packed_at(long i)
     }
     return -1;
 }
+// The second place of a conv2 weight (the input gradient's); -1: no conv2 weight
+__host__ __device__ __forceinline__ int packed_back_at(long i)
+{
+    if (i < net::C2W || i >= net::C2B) return -1;
+    const int t = (int)(i - net::C2W), o = t >> 9, tap = (t & 511) >> 5, ci = t & 31;
+    return W2B_AT + ((tap * 4 + (o >> 4)) * 3) * FRAG + (ci + 32 * ((o >> 3) & 1)) * 8 + (o & 7);
+}
 __device__ __forceinline__ void store_parts(uint16_t *packed, int at, float x)
 {
     const uint16_t a = bf16_bits(x);
@@ -52,13 +62,19 @@ __device__ __forceinline__ void store_parts(uint16_t *packed, int at, float x)
     packed[at + FRAG] = b;
     packed[at + 2 * FRAG] = bf16_bits(r);
 }
+// parameter i of the blob into its place or places (nothing for a bias or a parameter beyond the conv layers)
+__device__ __forceinline__ void store_packed(uint16_t *packed, long i, float x)
+{
+    const int at = packed_at(i), back = packed_back_at(i);
+    if (at >= 0) store_parts(packed, at, x);
+    if (back >= 0) store_parts(packed, back, x);
+}
 // conv weights of one network -> packed parts; one thread per parameter below fc1
 __global__ __launch_bounds__(256) void k_pack_conv(const float *theta, uint16_t *packed)
 {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= net::F1W) return;
-    const int at = packed_at(i);
-    if (at >= 0) store_parts(packed, at, theta[i]);
+    store_packed(packed, i, theta[i]);
 }
 
 }  // namespace sp
