@@ -59,7 +59,7 @@ struct Workspace {
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
     gbf::bf16_t *w2t;  // bf16 only: the online conv2 weights as [tap][channel in][channel out] (see misc::k_w2_transposed)
-    uint16_t *packed;  // fp32 only: the conv weights of both networks as bf16 parts (packed.h)
+    uint16_t *packed;  // the conv weights of both networks in the forward launches' order (packed.h)
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -110,7 +110,7 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
     w.w2t = (gbf::bf16_t *)take(c.precision == 1 ? net::L2N * 2 : 0);
-    w.packed = (uint16_t *)take(c.precision == 0 ? 2 * (size_t)sp::W_TOTAL * 2 : 0);
+    w.packed = (uint16_t *)take(2 * (size_t)(c.precision == 0 ? sp::W_TOTAL : sp::B_TOTAL) * 2);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
     // (fp32: conv1's and conv2's outputs exist in memory for the rows of the backward pass only)
@@ -169,6 +169,7 @@ struct dqn_ctx {
     // bf16: conv1 + conv2 forward run as one launch (gbf::c12) from this many samples per launch on;
     // INT_MAX: never (the launch needs 140 KB of LDS per workgroup, granted at initialisation)
     int conv12_min = INT32_MAX;
+    bool conv123 = false;   // bf16: conv1 to conv3 as one launch for few samples (gbf::c123)
     // bf16: fc1 forward as 128 x 128 tiles (gbf::f1) from this many rows per launch on; needs 72 KB of LDS
     float *gp4 = nullptr, *gp5 = nullptr;   // where fc1's and the head's weight gradients are written: inside `grads`
     bool fused_bwd = false;   // conv2's input gradient and conv1's weight gradient in one workgroup per sample
@@ -318,11 +319,15 @@ void he_uniform_host(std::vector<float> &blob, int K, int dueling, uint64_t seed
     }
 }
 
-// the copy of a network's conv weights that the fp32 forward kernel reads
+// the copy of a network's conv weights that the fused forward launches read
+long packed_count(const dqn_ctx *c) { return c->cfg.precision == 0 ? sp::W_TOTAL : sp::B_TOTAL; }
+uint16_t *packed_of(dqn_ctx *c, int net_i) { return c->ws.packed + (net_i ? packed_count(c) : 0); }
 void pack_conv(dqn_ctx *c, int net_i, hipStream_t st)
 {
+    const float *theta = net_i ? c->theta_t : c->theta;
     launch(c, "pack_conv", st, [&] {
-        sp::k_pack_conv<<<grid1(net::F1W, 256), 256, 0, st>>>(net_i ? c->theta_t : c->theta, c->ws.packed + (net_i ? sp::W_TOTAL : 0));
+        if (c->cfg.precision == 0) sp::k_pack_conv<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i));
+        else sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i));
     });
 }
 
@@ -393,6 +398,11 @@ Conv123Plan conv123_plan(int samples, int num_cu)
     P.draw_fits = (units + P.grid - 1) / P.grid <= sp::MAX_UNITS;
     return P;
 }
+// bf16: all three conv layers as one launch (gbf::c123), or conv1 + conv2 and conv3 (gbf::c12, gbf::ps)?
+// One unit per workgroup and a launch less: ahead while the samples of a training launch have a CU each (batch 77: 81.4
+// against 84.2 us per step, 32: 70.3 against 78.9, 128: 94.2 against 90.5), acting, which draws nothing, up to two
+// (512 observations: 34.8 against 38.6 us, 1024: 49.3 against 47.8, 1: 19.1 against 27.6).
+bool fused123(const dqn_ctx *c, long samples, int npass) { return c->conv123 && samples <= (npass == 1 ? 2 : 1) * c->num_cu; }
 // bf16: conv1 + conv2 as one launch, one workgroup per CU, for passes of n[0..npass) samples?
 bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 {
@@ -423,7 +433,7 @@ bool in_kernel_draw_fits(const dqn_ctx *c, int B)
 {
     if (c->cfg.precision == 0) return conv123_plan(3 * B, c->num_cu).draw_fits && conv123_plan(2 * B, c->num_cu).draw_fits;
     const int n[3] = {B, B, B};
-    return fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
+    return fused123(c, 3l * B, 3) || fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
 
 int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *nsplit_out,
@@ -469,7 +479,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
             // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
             const bool keep = npass == 3 && i == 0;
             A.seg[i - p0] = sp::Seg{gbf::c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
-                                    c->ws.packed + (pass[i].net ? sp::W_TOTAL : 0), theta + net::C1B, theta + net::C2B, theta + net::C3B,
+                                    packed_of(c, pass[i].net), theta + net::C1B, theta + net::C2B, theta + net::C3B,
                                     keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
                                     pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts};
         }
@@ -554,9 +564,33 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         return tile;
     };
 
+    const bool fused3 = fused123(c, rows, npass);
+    if (fused3) {
+        const Conv123Plan plan = conv123_plan((int)rows, c->num_cu);
+        c123::Args A{};
+        A.nseg = npass;
+        for (int i = 0; i < npass; ++i) {
+            const float *theta = theta_of(c, pass[i].net);
+            // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
+            const bool keep = npass == 3 && i == 0;
+            A.seg[i] = c123::Seg{c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
+                                 packed_of(c, pass[i].net), theta + net::C1B, theta + net::C2B, theta + net::C3B,
+                                 keep ? act1 : nullptr, keep ? act2 : nullptr, act3 + row0[i] * net::A3, pass[i].n,
+                                 (int)row0[i] * plan.parts};
+        }
+        for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
+        A.units = (int)rows * plan.parts;
+        A.draw = draw != nullptr;
+        if (draw) A.samp = *draw;
+        launch(c, "conv123_fwd", st, [&] {
+            if (plan.r3 == 1) c123::k_conv123_fwd<1><<<dim3(plan.grid), 512, c123::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 4) c123::k_conv123_fwd<4><<<dim3(plan.grid), 512, c123::Geo<4>::LDS, st>>>(A);
+            else c123::k_conv123_fwd<7><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
+        });
+    }
     // conv1 + conv2 as one launch, one workgroup per CU (faster from a handful of samples on)
     const int pass_n[3] = {pass[0].n, npass > 1 ? pass[1].n : 0, npass > 2 ? pass[2].n : 0};
-    const bool fused12 = fused12_fits(c, pass_n, npass, draw != nullptr);
+    const bool fused12 = !fused3 && fused12_fits(c, pass_n, npass, draw != nullptr);
     const int grid12 = (int)std::min<long>(rows, c->num_cu);
     if (fused12) {
         c12::Args A{};
@@ -577,7 +611,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
         launch(c, "conv12_fwd", st, [&] { c12::k_conv12_fwd<<<dim3(grid12), 512, c12::LDS_BYTES, st>>>(A); });
-    } else
+    } else if (!fused3)
     {  // conv1: persistent waves, strips of the frames staged in LDS (read from the ring in ring mode)
         c1::FwdArgs A{};
         A.nseg = npass;
@@ -616,12 +650,12 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.total = first;
         return std::min(first, 2 * c->num_cu);
     };
-    if (!fused12) {
+    if (!fused12 && !fused3) {
         ps::Args A{};
         const int grid = per_sample(A, act1, net::A1, net::C2W, net::C2B, act2, net::A2);
         launch(c, "conv2_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G2><<<dim3(grid), 256, 0, st>>>(A); });
     }
-    {
+    if (!fused3) {
         ps::Args A{};
         const int grid = per_sample(A, act2, net::A2, net::C3W, net::C3B, act3, net::A3);
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
@@ -746,7 +780,7 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     RA.theta = c->theta; RA.v = c->rms_v; RA.m = c->rms_m; RA.g = c->grads;
     RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)c->buf.shadow_bf16 : nullptr;
     RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w.w2t : nullptr;
-    RA.packed = cfg.precision == 0 ? w.packed : nullptr;
+    RA.packed = w.packed;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
     if (last_part && last_part->on) launch(c, "rmsprop", st, [&] { k_rmsprop_pu<<<blk + 1, 256, 0, st>>>(RA, *last_part); });
     else launch(c, "rmsprop", st, [&] { misc::k_rmsprop<<<blk, 256, 0, st>>>(RA); });
@@ -1152,9 +1186,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(c->theta_t, sh + half, c->n);
         misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
+    pack_conv(c, 0, st);
+    pack_conv(c, 1, st);
     if (cfg->precision == 0) {
-        pack_conv(c, 0, st);
-        pack_conv(c, 1, st);
         // the launches of the conv layers hold images in LDS
         if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
             hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
@@ -1182,6 +1216,15 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
                             gbf::c12::LDS_BYTES) == hipSuccess) {
         const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");
         c->conv12_min = m && m[0] ? std::atoi(m) : 8;
+    } else {
+        (void)hipGetLastError();
+    }
+    if (cfg->precision == 1 &&
+        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<1>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<1>::LDS) == hipSuccess &&
+        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<4>::LDS) == hipSuccess &&
+        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<7>::LDS) == hipSuccess) {
+        const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");   // asks for the two-launch form at every size
+        c->conv123 = !(m && m[0]);
     } else {
         (void)hipGetLastError();
     }
@@ -1302,7 +1345,7 @@ int32_t dqn_set_params(dqn_ctx *c, int32_t which, const float *src, void *stream
         misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, sh + (which ? half : 0), c->n);
         if (which == 0) misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
-    if (c->cfg.precision == 0 && which <= 1) pack_conv(c, which, st);
+    if (which <= 1) pack_conv(c, which, st);
     return hip_status(c, "dqn_set_params");
 }
 
@@ -1337,9 +1380,9 @@ int32_t dqn_sync_target(dqn_ctx *c, void *stream)
         size_t half = align_up((size_t)c->n * 2, 256) / 2;
         if (hipMemcpyAsync(sh + half, sh, (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
             return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
-    } else if (hipMemcpyAsync(c->ws.packed + sp::W_TOTAL, c->ws.packed, (size_t)sp::W_TOTAL * 2, hipMemcpyDeviceToDevice, st) != hipSuccess) {
-        return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     }
+    if (hipMemcpyAsync(packed_of(c, 1), packed_of(c, 0), (size_t)packed_count(c) * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
+        return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     return DQN_OK;
 }
 

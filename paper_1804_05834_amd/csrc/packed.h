@@ -1,5 +1,6 @@
-// The fp32 network's conv weights as sums of three bf16 numbers (see gemm_split.h for the arithmetic), laid
-// out for the forward kernel.  RMSProp keeps the copy of the online network up to date.
+// The conv weights in the order in which the matrix instructions of the fused forward launches take them: as
+// sums of three bf16 numbers for the fp32 network (see gemm_split.h for the arithmetic), as they are for the
+// bf16 network.  RMSProp keeps the copy of the online network up to date.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -75,6 +76,44 @@ __global__ __launch_bounds__(256) void k_pack_conv(const float *theta, uint16_t 
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= net::F1W) return;
     store_packed(packed, i, theta[i]);
+}
+
+// ---------------------------------------------------------------------------
+// The bf16 network's conv weights for gbf::c123::k_conv123_fwd: fragments of v_mfma_f32_16x16x32_bf16
+// (lane = row + 16 * (k / 8)), [conv1: half][step of 32], [conv2: 16 channels][step], [conv3: 16 channels][step].
+// A step of conv1 is four columns of two kernel rows per lane group: [frame][column half], rows 2g and 2g + 1.
+// Row i of half hh of conv1 is channel 8 (i / 4) + 4 hh + i % 4, so that a lane that holds rows 4g .. 4g+3 of both
+// halves holds eight consecutive channels.
+// ---------------------------------------------------------------------------
+constexpr int B_W2 = 2 * 8 * FRAG, B_W3 = B_W2 + 4 * 16 * FRAG, B_TOTAL = B_W3 + 4 * 18 * FRAG;
+__host__ __device__ __forceinline__ int packed_bf16_at(long i)
+{
+    if (i >= net::C3B || i < 0) return -1;
+    if (i >= net::C3W) {
+        const int t = (int)(i - net::C3W), o = t / 576, k = t % 576;
+        return B_W3 + ((o >> 4) * 18 + (k >> 5)) * FRAG + ((o & 15) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+    }
+    if (i >= net::C2W && i < net::C2B) {
+        const int t = (int)(i - net::C2W), o = t >> 9, k = t & 511;
+        return B_W2 + ((o >> 4) * 16 + (k >> 5)) * FRAG + ((o & 15) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+    }
+    if (i < net::C1B) {
+        const int t = (int)i, o = t >> 8, k = t & 255;
+        // frame k / 64, kernel row (k / 8) % 8, column k % 8
+        const int step = 2 * (k >> 6) + ((k >> 2) & 1), kg = (k >> 4) & 3, j = 4 * ((k >> 3) & 1) + (k & 3);
+        return (((o >> 2) & 1) * 8 + step) * FRAG + (4 * (o >> 3) + (o & 3) + 16 * kg) * 8 + j;
+    }
+    return -1;
+}
+__device__ __forceinline__ void store_packed_bf16(uint16_t *packed, long i, float x)
+{
+    const int at = packed_bf16_at(i);
+    if (at >= 0) packed[at] = bf16_bits(x);
+}
+__global__ __launch_bounds__(256) void k_pack_conv_bf16(const float *theta, uint16_t *packed)
+{
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i < net::F1W) store_packed_bf16(packed, i, theta[i]);
 }
 
 }  // namespace sp
