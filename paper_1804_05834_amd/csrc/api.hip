@@ -113,9 +113,8 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.packed = (uint16_t *)take(2 * (size_t)(c.precision == 0 ? sp::W_TOTAL : sp::B_TOTAL) * 2);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
-    // (fp32: conv1's and conv2's outputs exist in memory for the rows of the backward pass only)
-    w.act1 = take((c.precision == 1 ? rows : MB) * net::A1 * es);
-    w.act2 = take((c.precision == 1 ? rows : MB) * net::A2 * es);
+    w.act1 = take(rows * net::A1 * es);
+    w.act2 = take(rows * net::A2 * es);
     w.act3 = take(rows * net::A3 * es);
     size_t f1rows = std::max({std::min<size_t>(rows, 192) * 14, std::min<size_t>(rows, 512) * 7,
                               std::min<size_t>(rows, 1536) * 2, rows});
@@ -372,6 +371,15 @@ struct Conv1Plan {
     int grid;
     bool draw_fits;
 };
+Conv1Plan conv1_plan_f32(int samples, int num_cu)
+{
+    const int units = samples * gbf::c1::UNITS;
+    Conv1Plan P;
+    P.grid = std::min((units + 1) / 2, 2 * num_cu);
+    const int upp = (units + 2 * P.grid - 1) / (2 * P.grid) + 1;   // strips per pair of waves, at most
+    P.draw_fits = (upp + gbf::c1::UNITS - 1) / gbf::c1::UNITS + 1 <= gbf::c1::MAX_DRAWS;
+    return P;
+}
 Conv1Plan conv1_plan_bf16(int samples, int num_cu)
 {
     const int units = samples * gbf::c1::UNITS;
@@ -417,21 +425,26 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
     }
     return true;
 }
-// fp32 training: do the rows of the first pass keep the order of summation of the fp32 matrix instruction?
-// Their stored activations are what the ReLU decisions of the backward pass are taken on.  About one
-// pre-activation in ten million is zero to within the rounding of its sum, and falls the other way under
-// another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and one such
-// decision moves a gradient by 1e-4 to 2e-3 of its norm (measured over 30 seeds at 64, 128 and 256: 4, 8 and
-// 12 of them beyond 1e-4 after two steps, none of 130 at 32).  Large batches therefore keep it, so that their
-// results stay those of the plain fp32 chain; the two passes over s', whose activations are only values,
-// take the split form at every size.  Small batches, where a layer-by-layer chain is latency and nothing
-// else, take it for all three: the line lies where a sample no longer has two workgroups to itself.
-bool keeps_fp32_order(const dqn_ctx *c, int B) { return 2 * 3 * B > c->num_cu; }
+// fp32 training: how many of the step's passes keep the order of summation of the fp32 matrix instruction, layer by
+// layer, instead of the split form (gemm_split.h)?
+// The stored activations of the first pass (on s) are what the ReLU decisions of the backward pass are taken on.
+// About one pre-activation in ten million is zero to within the rounding of its sum, and falls the other
+// way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
+// one such decision moves a gradient by 1e-4 to 2e-3 of its norm (measured over 30 seeds at 64, 128 and 256: 4, 8
+// and 12 of them beyond 1e-4 after two steps, none of 300 at 32).  Larger batches therefore keep it for the first
+// pass, so that their results stay those of the plain fp32 chain; the passes over s', whose activations are
+// only values, take the split form.  At larger ones the last bits of those values reach a decision, or a draw, through
+// the updated parameters and priorities too (one of 30 seeds at 256, two of 20 at 1000): there every pass keeps it.
+// The first line lies where a sample no longer has two workgroups to itself.
+int native_passes(const dqn_ctx *c, int B) { return 2 * 3 * B <= c->num_cu ? 0 : B <= 128 ? 1 : 3; }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not
 // (few compute units and a large batch), a sampling launch runs in front of the step.
 bool in_kernel_draw_fits(const dqn_ctx *c, int B)
 {
-    if (c->cfg.precision == 0) return conv123_plan(3 * B, c->num_cu).draw_fits && conv123_plan(2 * B, c->num_cu).draw_fits;
+    if (c->cfg.precision == 0) {
+        const int np = native_passes(c, B);
+        return np == 3 ? conv1_plan_f32(3 * B, c->num_cu).draw_fits : conv123_plan((3 - np) * B, c->num_cu).draw_fits;
+    }
     const int n[3] = {B, B, B};
     return fused123(c, 3l * B, 3) || fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
@@ -445,15 +458,17 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
     long rows = 0;
     for (int i = 0; i < npass; ++i) { row0[i] = rows; rows += pass[i].n; }
 
-    auto build = [&](FwdArgs &A, int BM, int P, auto xptr, auto xstride, int64_t woff, int64_t boff,
+    // the first np passes as segments of a tiled launch; returns the number of row tiles
+    auto build = [&](FwdArgs &A, int np, int BM, int P, auto xptr, long xs, int64_t woff, int64_t boff,
                      float *ybase, long ystride, bool with_bias) {
         int tile = 0;
-        A.nseg = npass;
-        for (int i = 0; i < npass; ++i) {
+        A.nseg = np;
+        A.scale = 1.0f;
+        for (int i = 0; i < np; ++i) {
             FwdSeg &S = A.seg[i];
             const float *theta = theta_of(c, pass[i].net);
             S.x = xptr(i);
-            S.xs = xstride(i);
+            S.xs = xs;
             S.w = theta + woff;
             S.bias = with_bias ? theta + boff : nullptr;
             S.y = ybase + row0[i] * ystride;
@@ -461,13 +476,13 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
             S.tile_begin = tile;
             tile += (S.M + BM - 1) / BM;
         }
-        for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
+        for (int i = np; i < 3; ++i) A.seg[i] = A.seg[0];
         return tile;
     };
 
     // conv1, conv2 and conv3: one launch for the passes [p0, npass)
-    const int p0 = npass == 3 && keeps_fp32_order(c, pass[0].n) ? 1 : 0;
-    {
+    const int p0 = npass == 3 ? native_passes(c, pass[0].n) : 0;
+    if (p0 < npass) {
         const int samples = (int)(rows - row0[p0]);
         const Conv123Plan plan = conv123_plan(samples, c->num_cu);
         if (draw && !plan.draw_fits)   // the caller asks in_kernel_draw_fits first
@@ -493,38 +508,44 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
             else sp::k_conv123_fwd<7><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
         });
     }
-    if (p0 == 1) {   // the training rows, layer by layer (their transitions have been drawn by the launch above)
-        const Pass &P = pass[0];
-        const float *theta = theta_of(c, P.net);
+    if (p0 > 0) {   // the passes [0, p0), layer by layer
+        const long n0 = row0[p0 - 1] + pass[p0 - 1].n;   // their samples
         float *act1 = (float *)w.act1, *act2 = (float *)w.act2;
-        gbf::c1::FwdSegF F{gbf::c1::Src{P.x, P.xs, P.idx, (long)c->cfg.replay_capacity, P.shift, (int)c->sub},
-                           theta + net::C1W, theta + net::C1B, act1, P.n, P.stack};
-        const int grid = std::min((P.n * gbf::c1::UNITS + 1) / 2, 2 * c->num_cu);
-        launch(c, "conv1_fwd", st, [&] { gbf::c1::k_conv1_fwd_f32<<<dim3(grid), 256, 0, st>>>(F); });
-        auto one = [&](const float *x, long xs, int64_t woff, int64_t boff, float *y, int M) {
-            FwdArgs A{};
-            A.nseg = 1;
-            A.seg[0] = A.seg[1] = A.seg[2] = FwdSeg{x, theta + woff, theta + boff, y, M, 0, xs};
-            A.scale = 1.0f;
-            return A;
-        };
+        gbf::c1::FwdArgsF F{};
+        F.nseg = p0;
+        for (int i = 0; i < 3; ++i) {
+            const int q = i < p0 ? i : 0;
+            const float *theta = theta_of(c, pass[q].net);
+            F.seg[i] = gbf::c1::FwdSegF{gbf::c1::Src{pass[q].x, pass[q].xs, pass[q].idx, (long)c->cfg.replay_capacity, pass[q].shift, (int)c->sub},
+                                        theta + net::C1W, theta + net::C1B, act1 + row0[q] * net::A1, pass[q].n, (int)row0[q], pass[q].stack};
+        }
+        F.total = (int)n0;
+        F.draw = draw && p0 == npass;   // (otherwise the launch above has drawn)
+        if (F.draw) F.samp = *draw;
+        const Conv1Plan plan = conv1_plan_f32((int)n0, c->num_cu);
+        if (F.draw && !plan.draw_fits) return fail(c, DQN_ERR_INVALID_ARG, "forward: batch too large for in-kernel sampling");
+        launch(c, "conv1_fwd", st, [&] { gbf::c1::k_conv1_fwd_f32<<<dim3(plan.grid), 256, 0, st>>>(F); });
         // (few rows: the reduction slab of every stage is sliced over extra waves, KS > 1, which shortens the
         // dependent chain of stages per tile)
         const bool small = rows * 81 < 64 * 512;
-        const int M2 = P.n * 81, M3 = P.n * 49;
-        FwdArgs A2 = one(act1, net::A1, net::C2W, net::C2B, act2, M2), A3 = one(act2, net::A2, net::C3W, net::C3B, act3, M3);
+        const int BM = small ? 32 : 64;
+        FwdArgs A2{}, A3{};
+        const int t2 = build(A2, p0, BM, 81, [&](int i) { return (const void *)(act1 + row0[i] * net::A1); }, net::A1, net::C2W,
+                             net::C2B, act2, net::A2, true);
+        const int t3 = build(A3, p0, BM, 49, [&](int i) { return (const void *)(act2 + row0[i] * net::A2); }, net::A2, net::C3W,
+                             net::C3B, act3, net::A3, true);
         A2.klen = GConv2::K;
         A3.klen = GConv3::K;
-        if (small) launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 32, 32, 4><<<dim3((M2 + 31) / 32, 2, 1), 256, 0, st>>>(A2); });
-        else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3((M2 + 63) / 64, 1, 1), 256, 0, st>>>(A2); });
-        if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3((M3 + 31) / 32, 2, 1), 192, 0, st>>>(A3); });
-        else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3((M3 + 63) / 64, 1, 1), 256, 0, st>>>(A3); });
+        if (small) launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 32, 32, 4><<<dim3(t2, 2, 1), 256, 0, st>>>(A2); });
+        else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3(t2, 1, 1), 256, 0, st>>>(A2); });
+        if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3(t3, 2, 1), 192, 0, st>>>(A3); });
+        else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3(t3, 1, 1), 256, 0, st>>>(A3); });
     }
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
         FwdArgs A{};
         const int ns = fc1_splits(rows, 0);
-        int tiles = build(A, 32, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); },
-                          [&](int) { return (long)net::A3; }, net::F1W, net::F1B, w.f1part, net::HID, false);
+        int tiles = build(A, npass, 32, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
+                          net::F1B, w.f1part, net::HID, false);
         A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
         // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well
         if (rows <= 192) launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); });
@@ -902,7 +923,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 });
             }
         }
-        if (!keeps_fp32_order(c, B)) {
+        if (native_passes(c, B) == 0) {
             // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample
             // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient
             const int nps = std::min({BACK_PARTS * B, std::max(1, c->num_cu * 5 / 8), MAX_WSPLIT1});

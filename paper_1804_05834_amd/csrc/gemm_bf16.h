@@ -1204,7 +1204,15 @@ struct FwdSegF {
     const float *bias;  // [32]
     float *y;           // [n][400][32]
     int n;
+    int first;
     uint8_t *stack;     // [n][5][84][84] or nullptr: frames 0-3 of the stack are written
+};
+struct FwdArgsF {
+    FwdSegF seg[3];
+    int nseg;
+    int total;
+    int draw;
+    misc::SampleArgs samp;
 };
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c)
@@ -1212,7 +1220,7 @@ __device__ __forceinline__ v4f mfma4(float a, float b, v4f c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, int u1, int hh, uint8_t *xs, int lane)
+__device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, int u1, int hh, uint8_t *xs, const int *slots, int lane)
 {
     const int n = lane & 15, kg = lane >> 4, oyl = n >> 2, q = n & 3;
     StripOff O;
@@ -1222,7 +1230,7 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
         O.off[i] = t < CHUNKS ? (t / (CHUNKS / 4)) * FR + (t % (CHUNKS / 4)) * 16 : 0;
     }
     const int gfirst = u0 / UNITS;
-    auto slot_of = [&](int gq) { return sample_slot(S.src, gq); };
+    auto slot_of = [&](int gq) { return slots ? slots[gq - gfirst] : sample_slot(S.src, gq); };
     StripRaw R;
     strip_load(R, S.src, gfirst, slot_of(gfirst), u0 % UNITS, lane, O);
     int slot_next = u0 + 1 < u1 ? slot_of((u0 + 1) / UNITS) : 0;
@@ -1293,14 +1301,25 @@ __device__ __forceinline__ void conv1_fwd_units_f32(const FwdSegF &S, int u0, in
 }
 
 // The four waves of a workgroup are two pairs, each with a unit range of its own.
-__global__ __launch_bounds__(256, 2) void k_conv1_fwd_f32(FwdSegF S)
+__global__ __launch_bounds__(256, 2) void k_conv1_fwd_f32(FwdArgsF A)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4 * RAWSTRIP];
+    __shared__ int slot_tab[4][MAX_DRAWS];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long np = (long)gridDim.x * 2, pid = (long)blockIdx.x * 2 + (wave >> 1), units = (long)S.n * UNITS;
+    const long np = (long)gridDim.x * 2, pid = (long)blockIdx.x * 2 + (wave >> 1), units = (long)A.total * UNITS;
     const int u0 = (int)(pid * units / np), u1 = (int)((pid + 1) * units / np);
-    if (u0 < u1) conv1_fwd_units_f32(S, u0, u1, wave & 1, lds + wave * RAWSTRIP, lane);
+    if (A.draw && u0 < u1) draw_slots(A.samp, A.seg[0].n, u0, u1, slot_tab[wave], lane, (wave & 1) == 0);
+    for (int s = 0; s < A.nseg; ++s) {
+        FwdSegF S = A.seg[0];
+        if (s == 1) S = A.seg[1];
+        if (s == 2) S = A.seg[2];
+        const int lo = max(u0, UNITS * S.first) - UNITS * S.first;
+        const int hi = min(u1, UNITS * (S.first + S.n)) - UNITS * S.first;
+        if (lo < hi)
+            conv1_fwd_units_f32(S, lo, hi, wave & 1, lds + wave * RAWSTRIP,
+                                A.draw ? slot_tab[wave] + (S.first + lo / UNITS - u0 / UNITS) : nullptr, lane);
+    }
 }
 
 struct WgradArgs {
