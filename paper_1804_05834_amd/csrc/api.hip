@@ -80,12 +80,8 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr size_t MAX_STEP_GRAPHS = 16;  // recorded steps kept per context (one per batch size)
 
-// reduction splits of the fc1 forward GEMM (3136 = 98*32 = 49*64 reduction elements)
-int fc1_splits(long M, int precision)
-{
-    if (precision == 1) return M <= 2048 ? 7 : 1;
-    return M <= 512 ? 7 : M <= 1536 ? 2 : 1;
-}
+// reduction splits of the fp32 fc1 forward GEMM (3136 = 98*32 reduction elements)
+int fc1_splits(long M) { return M <= 512 ? 7 : M <= 1536 ? 2 : 1; }
 
 Workspace carve(const dqn_config &c, uint8_t *base)
 {
@@ -543,7 +539,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
     }
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
         FwdArgs A{};
-        const int ns = fc1_splits(rows, 0);
+        const int ns = fc1_splits(rows);
         int tiles = build(A, npass, 32, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
                           net::F1B, w.f1part, net::HID, false);
         A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
@@ -565,25 +561,6 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
     long row0[3];
     long rows = 0;
     for (int i = 0; i < npass; ++i) { row0[i] = rows; rows += pass[i].n; }
-
-    auto build = [&](FwdArgs &A, int BM, int P, auto xptr, auto xstride, int64_t woff, int64_t boff,
-                     auto yptr, bool with_bias) {
-        int tile = 0;
-        A.nseg = npass;
-        for (int i = 0; i < npass; ++i) {
-            FwdSeg &S = A.seg[i];
-            S.x = xptr(i);
-            S.xs = xstride(i);
-            S.w = shadow_of(c, pass[i].net) + woff;
-            S.bias = with_bias ? theta_of(c, pass[i].net) + boff : nullptr;
-            S.y = yptr(i);
-            S.M = pass[i].n * P;
-            S.tile_begin = tile;
-            tile += (S.M + BM - 1) / BM;
-        }
-        for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
-        return tile;
-    };
 
     const bool fused3 = fused123(c, rows, npass);
     if (fused3) {
@@ -681,7 +658,8 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         const int grid = per_sample(A, act2, net::A2, net::C3W, net::C3B, act3, net::A3);
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
     }
-    if (c->fc1_big && rows >= c->fc1_big_rows) {
+    const bool few_fit = (size_t)rows * FC1_SPLITS <= w.f1rows;
+    if (c->fc1_big && (rows >= c->fc1_big_rows || !few_fit)) {
         // many rows: 128 x 128 tiles, double-buffered stages, few reduction splits
         f1::Args A{};
         A.nseg = npass;
@@ -704,14 +682,21 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         *nsplit_out = ns;
         *split_stride_out = rows * net::HID;
     } else {
+        if (!few_fit) return fail(c, DQN_ERR_STATE, "forward: no fc1 kernel for this many rows");
         FwdArgs A{};
-        const int ns = fc1_splits(rows, 1);
-        int tiles = build(A, 64, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); },
-                          [&](int) { return (long)net::A3; }, net::F1W, net::F1B,
-                          [&](int i) { return (void *)(w.f1part + row0[i] * net::HID); }, false);
-        A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
-        launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 64, 128, 1, 2, true><<<dim3(tiles, 4, ns), 256, 0, st>>>(A); });
-        *nsplit_out = ns;
+        int tile = 0;
+        A.nseg = npass;
+        for (int i = 0; i < npass; ++i) {
+            A.seg[i] = FwdSeg{act3 + row0[i] * net::A3, shadow_of(c, pass[i].net) + net::F1W, nullptr,
+                              w.f1part + row0[i] * net::HID, pass[i].n, tile, (long)net::A3};
+            tile += (pass[i].n + 31) / 32;
+        }
+        for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
+        A.split_stride = rows * net::HID;
+        // half as wide where that still leaves no more than a workgroup per CU
+        if (tile * 8 * FC1_SPLITS <= c->num_cu) launch(c, "fc1_fwd", st, [&] { k_fc1_fwd_few<64><<<dim3(tile, 8, FC1_SPLITS), 128, 0, st>>>(A); });
+        else launch(c, "fc1_fwd", st, [&] { k_fc1_fwd_few<128><<<dim3(tile, 4, FC1_SPLITS), 256, 0, st>>>(A); });
+        *nsplit_out = FC1_SPLITS;
         *split_stride_out = rows * net::HID;
     }
     return hip_status(c, "forward");

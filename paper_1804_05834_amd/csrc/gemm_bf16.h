@@ -131,7 +131,7 @@ struct FwdSeg {
     const void *x;      // uint8 (conv1) or bf16 activations
     const bf16_t *w;    // [N][K] bf16 copy of the weights
     const float *bias;  // [N] fp32 (master copy) or nullptr
-    void *y;            // bf16 [M][N], or fp32 raw partial sums when RAW
+    void *y;            // fp32 raw partial sums [M][N]
     int M;
     int tile_begin;
     long xs;
@@ -139,22 +139,21 @@ struct FwdSeg {
 struct FwdArgs {
     FwdSeg seg[3];
     int nseg;
-    int klen;
     long split_stride;
-    float scale;
 };
 
-// Workgroup tile BM x BN; each wave owns WM x WN MFMA blocks of 32x32.
-template <class G, int BM, int BN, int WM, int WN, bool RAW>
-__global__ __launch_bounds__((BM / (32 * WM)) * (BN / (32 * WN)) * 64) void k_fwd(FwdArgs A)
+// fc1 for few rows: raw fp32 partial sums of FC1_SPLITS reduction splits (the head kernels add them), 32 rows x BN
+// columns per workgroup, one wave per 32 columns.  A split is seven stages of 64, and with few rows there is about
+// one workgroup per CU, so nothing hides a stage's way from memory but the other stages: all seven are
+// requested at once (140 registers) and the launch is one round trip, then seven short stages out of two LDS
+// buffers.  With one stage in flight ahead of the one in work it was a chain of seven trips: 11.4 us at 231 rows.
+constexpr int FC1_SPLITS = 7;
+template <int BN>
+__global__ __launch_bounds__(2 * BN) void k_fc1_fwd_few(FwdArgs A)
 {
-    constexpr int WAVES_M = BM / (32 * WM), WAVES_N = BN / (32 * WN), T = WAVES_M * WAVES_N * 64;
-    constexpr int NA = BM * 8 / T, NB = (BN * 8 + T - 1) / T;
-    static_assert(NA * T == BM * 8, "tile/threads mismatch");
-    using in_t = typename in_type<G>::t;
-    __shared__ __attribute__((aligned(16))) bf16_t As[BM * LDK];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[BN * LDK];
-
+    constexpr int BM = 32, T = 2 * BN, NST = GFc1::K / FC1_SPLITS / BK, NA = BM * 8 / T, NB = BN * 8 / T;
+    static_assert(NST * FC1_SPLITS * BK == GFc1::K && NA * T == BM * 8 && NB * T == BN * 8, "tile/threads mismatch");
+    __shared__ __attribute__((aligned(16))) bf16_t As[2][BM * LDK], Bs[2][BN * LDK];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // tile order: column tiles of one row tile together, reduction splits apart
     const int t = net::tile_of_workgroup();
@@ -162,127 +161,53 @@ __global__ __launch_bounds__((BM / (32 * WM)) * (BN / (32 * WN)) * 64) void k_fw
     FwdSeg S = A.seg[0];
     if (A.nseg > 1 && bx >= A.seg[1].tile_begin) S = A.seg[1];
     if (A.nseg > 2 && bx >= A.seg[2].tile_begin) S = A.seg[2];
-    const int m0 = (bx - S.tile_begin) * BM, n0 = by * BN;
-    const int kbeg = bz * A.klen, kend = kbeg + A.klen;
-    const in_t *x = static_cast<const in_t *>(S.x);
-
+    const int m0 = (bx - S.tile_begin) * BM, n0 = by * BN, k0 = bz * (NST * BK);
+    const bf16_t *x = static_cast<const bf16_t *>(S.x);
     const int lr = tid >> 3, kq = (tid & 7) * 8;
-    long aoff[NA];
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a native vector: stays in registers
+    u32x4 ra[NST][NA], rb[NST][NB];
+    const bf16_t *pa[NA], *pb[NB];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
         int m = m0 + lr + i * (T / 8);
-        aoff[i] = m < S.M ? G::row_off(m, S.xs) : -1;
+        if (m > S.M - 1) m = S.M - 1;             // rows past the end repeat the last row; they are never stored
+        pa[i] = x + (long)m * S.xs + k0 + kq;
     }
-    uint4 ra[NA], rb[NB];
-    auto gload = [&](int k0) {
-        const int ko = G::k_off(k0 + kq);
 #pragma unroll
-        for (int i = 0; i < NA; ++i) ra[i] = aoff[i] >= 0 ? ld8(x + aoff[i] + ko) : uint4{0, 0, 0, 0};
+    for (int i = 0; i < NB; ++i) pb[i] = S.w + (long)(n0 + lr + i * (T / 8)) * GFc1::K + k0 + kq;
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            int r = lr + i * (T / 8);
-            if (r < BN) rb[i] = ld8(S.w + (long)(n0 + r) * G::K + k0 + kq);
-        }
-    };
-    auto sstore = [&]() {
+    for (int st = 0; st < NST; ++st) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) *reinterpret_cast<uint4 *>(&As[(lr + i * (T / 8)) * LDK + kq]) = ra[i];
+        for (int i = 0; i < NA; ++i) ra[st][i] = *reinterpret_cast<const u32x4 *>(pa[i] + st * BK);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            int r = lr + i * (T / 8);
-            if (r < BN) *reinterpret_cast<uint4 *>(&Bs[r * LDK + kq]) = rb[i];
-        }
-    };
-
-    const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+        for (int i = 0; i < NB; ++i) rb[st][i] = *reinterpret_cast<const u32x4 *>(pb[i] + st * BK);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const int li = lane & 31, h = lane >> 5;
-    const bf16_t *ap = &As[(wm * 32 * WM + li) * LDK + 8 * h];
-    const bf16_t *bp = &Bs[(wn * 32 * WN + li) * LDK + 8 * h];
-    v16f acc[WM][WN];
+    v16f acc = {0};
 #pragma unroll
-    for (int a = 0; a < WM; ++a)
+    for (int st = 0; st < NST; ++st) {
+        bf16_t *as = As[st & 1], *bs = Bs[st & 1];
 #pragma unroll
-        for (int b = 0; b < WN; ++b) acc[a][b] = v16f{0};
-
-    // bias of this lane's channels, requested before the loop so the epilogue does not wait for it
-    v4f bias_r[WN][4];
-    if (!RAW) {
+        for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4 *>(&as[(lr + i * (T / 8)) * LDK + kq]) = ra[st][i];
 #pragma unroll
-        for (int b = 0; b < WN; ++b)
+        for (int i = 0; i < NB; ++i) *reinterpret_cast<u32x4 *>(&bs[(lr + i * (T / 8)) * LDK + kq]) = rb[st][i];
+        sync_lds();   // the buffer is complete; every wave is past the stage before, which read the other one
+        v8bf fa[4], fb[4];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                bias_r[b][g] = *reinterpret_cast<const v4f *>(S.bias + n0 + (wn * WN + b) * 32 + 8 * g + 4 * h);
+        for (int k = 0; k < 4; ++k) {
+            fa[k] = frag_k(as + li * LDK + 8 * h + 16 * k);
+            fb[k] = frag_k(bs + (wave * 32 + li) * LDK + 8 * h + 16 * k);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc = mfma(fb[k], fa[k], acc);   // transposed tile
     }
-
-    gload(kbeg);
-    sstore();
-    __syncthreads();
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-        const bool more = k0 + BK < kend;
-        if (more) gload(k0 + BK);
+    // acc[4g + j] = Y[row m = lane li][channel = 8g + 4h + j]
+    const int m = m0 + li;
+    if (m >= S.M) return;
+    float *y = static_cast<float *>(S.y) + (long)bz * A.split_stride + (long)m * GFc1::N + n0 + wave * 32 + 4 * h;
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 16) {
-            v8bf fa[WM], fb[WN];
-#pragma unroll
-            for (int a = 0; a < WM; ++a) fa[a] = frag_k(ap + a * 32 * LDK + kk);
-#pragma unroll
-            for (int b = 0; b < WN; ++b) fb[b] = frag_k(bp + b * 32 * LDK + kk);
-#pragma unroll
-            for (int a = 0; a < WM; ++a)
-#pragma unroll
-                for (int b = 0; b < WN; ++b) acc[a][b] = mfma(fb[b], fa[a], acc[a][b]);  // transposed tile
-        }
-        __syncthreads();
-        if (more) {
-            sstore();
-            __syncthreads();
-        }
-    }
-
-    // acc[a][b][4g + j] = Y[row m = block a, lane li][channel = block b, 8g + 4h + j]
-    if constexpr (RAW) {
-#pragma unroll
-        for (int a = 0; a < WM; ++a) {
-            const int m = m0 + (wm * WM + a) * 32 + li;
-            if (m >= S.M) continue;
-            float *y = static_cast<float *>(S.y) + (long)bz * A.split_stride;
-#pragma unroll
-            for (int b = 0; b < WN; ++b)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int col = n0 + (wn * WN + b) * 32 + 8 * g + 4 * h;
-                    *reinterpret_cast<v4f *>(y + (long)m * G::N + col) =
-                        v4f{acc[a][b][4 * g] * A.scale, acc[a][b][4 * g + 1] * A.scale,
-                            acc[a][b][4 * g + 2] * A.scale, acc[a][b][4 * g + 3] * A.scale};
-                }
-        }
-    } else {
-        // bias + ReLU, the bf16 tile goes through LDS (the operand tiles are no longer read: the
-        // loop ends on a barrier) and leaves as whole rows, 16 bytes per lane
-        static_assert(RAW || BN <= BK, "the output tile is staged in the A tile's LDS");
-#pragma unroll
-        for (int a = 0; a < WM; ++a)
-#pragma unroll
-            for (int b = 0; b < WN; ++b)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int col = (wn * WN + b) * 32 + 8 * g + 4 * h;
-                    const v4f bv = bias_r[b][g];
-                    *reinterpret_cast<uint2 *>(&As[((wm * WM + a) * 32 + li) * LDK + col]) =
-                        pack4(fmaxf(acc[a][b][4 * g] * A.scale + bv.x, 0.f), fmaxf(acc[a][b][4 * g + 1] * A.scale + bv.y, 0.f),
-                              fmaxf(acc[a][b][4 * g + 2] * A.scale + bv.z, 0.f), fmaxf(acc[a][b][4 * g + 3] * A.scale + bv.w, 0.f));
-                }
-        __syncthreads();
-        constexpr int CH = BN / 8;
-        static_assert((BM * CH) % T == 0, "tile/threads mismatch");
-#pragma unroll
-        for (int i = 0; i < BM * CH / T; ++i) {
-            const int c = tid + i * T, row = c / CH, ch = c % CH;
-            if (m0 + row < S.M)
-                *reinterpret_cast<uint4 *>(static_cast<bf16_t *>(S.y) + (long)(m0 + row) * G::N + n0 + ch * 8) =
-                    *reinterpret_cast<const uint4 *>(&As[row * LDK + ch * 8]);
-        }
-    }
+    for (int g = 0; g < 4; ++g) *reinterpret_cast<v4f *>(y + 8 * g) = v4f{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
 }
 
 // Dispatch-order number u of `total` workgroups -> tile number, die-aware as net::tile_of_workgroup
