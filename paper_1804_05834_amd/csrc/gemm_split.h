@@ -112,8 +112,9 @@ template <int R3> struct Geo {
     static constexpr int CH = PR * 84 / 16, NPX = (4 * CH + 511) / 512;   // 16-byte pieces per frame, per thread
     static constexpr int PXB = 4 * PR * 84 * 2;   // pixels; later conv2's image
     static constexpr int P1 = 208, P2 = 400;      // pixel pitch of the images in bytes
-    static constexpr int I1B = M1 * P1;           // conv1's image; later the partial tiles
-    static constexpr int TAB = (2 * MAX_UNITS + 4) * 4;
+    static constexpr int W1B = W1_FR * FRAG * 2;  // conv1's weights, in the image's place until conv1 begins (one unit only)
+    static constexpr int I1B = MANY || M1 * P1 > W1B ? M1 * P1 : W1B;   // conv1's image; later the partial tiles
+    static constexpr int TAB = (2 * MAX_UNITS + 4 + 160) * 4;   // slots, leaf values, total; biases
     static constexpr int LDS = PXB + I1B + TAB;
     static_assert(PR * 84 % 16 == 0 && M2 * P2 <= PXB && 24 * T2 * 1024 <= I1B && 24 * T3 * 1024 <= I1B, "LDS layout");
 };
@@ -158,6 +159,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
     v4f *scratch = reinterpret_cast<v4f *>(img1);
     int *slots = reinterpret_cast<int *>(lds + G::PXB + G::I1B);
     float *leafv = reinterpret_cast<float *>(slots + MAX_UNITS);   // [MAX_UNITS], then the total
+    float *bias = leafv + MAX_UNITS + 4;                           // conv1 [32], conv2 [64], conv3 [64]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nt = wave & 1, tg = wave >> 1;      // conv1
     const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
@@ -173,11 +175,12 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         for (int q = 0; q < 3; ++q) w1[s][q] = p[q * 64];
     };
     u32x4 raw[G::NPX];
-    auto load_px = [&](int si, int u, int slot) {
-        const int ul = u - SP_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
+    auto load_px = [&](const uint8_t *x, long xs, int shift, int first, int u, int slot) {
+        const int ul = u - first, g = ul / G::PARTS, part = ul % G::PARTS;
         const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
         const uint8_t *f[4];
-        const gbf::c1::Src src{SP_SEG(si).src.x, SP_SEG(si).src.xs, SP_SEG(si).src.idx, SP_SEG(si).src.cap, SP_SEG(si).src.shift, SP_SEG(si).src.sub};
+        // (the segments' slot lists, ring and sub-rings are one and the same)
+        const gbf::c1::Src src{x, xs, A.seg[0].src.idx, A.seg[0].src.cap, shift, A.seg[0].src.sub};
 #pragma unroll
         for (int k = 0; k < 4; ++k) f[k] = gbf::c1::frame_ptr(src, g, slot, k) + row0 * (8 * 84);
 #pragma unroll
@@ -193,8 +196,44 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
     int u = (int)blockIdx.x;
     int si = seg_of(u);
     const bool ring = A.seg[0].src.idx != nullptr;   // of every segment, or of none
+    // What the first loads need of the segment, picked from the arguments without a second, dependent trip to
+    // constant memory
+    const uint8_t *x0 = A.seg[0].src.x;
+    const bf16_t *wf = A.seg[0].w;
+    long xs0 = A.seg[0].src.xs;
+    int shift0 = A.seg[0].src.shift, first0 = A.seg[0].first;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) load_w1(SP_SEG(si).w, s);
+    for (int q = 1; q < 3; ++q)
+        if (si == q) { x0 = A.seg[q].src.x; wf = A.seg[q].w; xs0 = A.seg[q].src.xs; shift0 = A.seg[q].src.shift; first0 = A.seg[q].first; }
+    // The first pixels before the weights, which are twenty times as many bytes, where their slot is known; drawing
+    // comes first otherwise, with the weights on their way
+    if (!ring) load_px(x0, xs0, shift0, first0, u, 0);
+    v8bf w1s[G::MANY ? 1 : 6];   // one unit only: this wave's eighth of conv1's weights, on their way to LDS
+    if constexpr (G::MANY) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) load_w1(wf, s);
+    } else {
+        const v8bf *p = reinterpret_cast<const v8bf *>(wf + wave * 6 * FRAG) + lane;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) w1s[q] = p[q * 64];
+    }
+    // four waves want the same half of conv1's weights: through LDS they are fetched once per workgroup
+    auto store_w1 = [&] {
+        if constexpr (!G::MANY) {
+            v8bf *d = reinterpret_cast<v8bf *>(img1) + wave * 6 * 64 + lane;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) d[q * 64] = w1s[q];
+        }
+    };
+    auto read_w1 = [&] {
+        if constexpr (!G::MANY) {
+            const v8bf *p = reinterpret_cast<const v8bf *>(img1) + nt * 24 * 64 + lane;
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) w1[s][q] = p[(s * 3 + q) * 64];
+        }
+    };
     if (ring) {
         if (A.draw) {
 #pragma unroll 1
@@ -220,9 +259,11 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 slots[k] = A.seg[0].src.idx[(u + k * G0) / G::PARTS % A.seg[0].n];
             }
         }
-        sync_lds();   // the slot table is complete
+        store_w1();
+        sync_lds();   // the slot table is complete, and the weights
+        load_px(x0, xs0, shift0, first0, u, slots[0]);
+        read_w1();
     }
-    load_px(si, u, ring ? slots[0] : 0);
     if (A.draw && wave == 7)   // index, raw importance weight and transition data of the segment-0 draws
         for (int k = lane; k < nu; k += 64) {
             const int uk = u + k * G0;
@@ -240,6 +281,8 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
         const bf16_t *const wts = SP_SEG(si).w;
         const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
+        // (the biases are read behind the next barrier, and the unit before has left its last phase that reads them)
+        if (tid < 160) bias[tid] = tid < 32 ? SP_SEG(si).b1[tid] : tid < 96 ? SP_SEG(si).b2[tid - 32] : SP_SEG(si).b3[tid - 96];
         // pixels -> LDS
 #pragma unroll
         for (int i = 0; i < G::NPX; ++i) {
@@ -250,22 +293,23 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 d[1] = gbf::cvt8_u8(raw[i].z, raw[i].w);
             }
         }
-        sync_lds();
+        if (G::MANY || ring) {
+            sync_lds();
+        } else {
+            store_w1();
+            sync_lds();
+            read_w1();
+            sync_lds();
+        }
         v8bf w2[8][3], w3[9][3];
         const v8bf *p2 = reinterpret_cast<const v8bf *>(wts + W2_AT + (((kq * 2 + ch) * 8) * 3) * FRAG) + lane;
         const v8bf *p3 = reinterpret_cast<const v8bf *>(wts + W3_AT + (((kq * 2 + ch) * 9) * 3) * FRAG) + lane;
-#pragma unroll
-        for (int s = 0; s < W2_PRE; ++s)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
-        const v4f bias1 = *reinterpret_cast<const v4f *>(SP_SEG(si).b1 + 16 * nt + 4 * kg);
         const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2 and conv3
         float *const y1 = SP_SEG(si).y1, *const y2 = SP_SEG(si).y2;
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- conv1
-#pragma unroll 1
-        for (int t = tg; t < G::T1; t += 4) {
+        auto conv1_tile = [&](int t) {
             const int m = 16 * t + n16, mc = m < G::M1 ? m : G::M1 - 1;
             const int y = mc / 20, x = mc - 20 * y;
             const bf16_t *p = px + (4 * y + kg) * 84 + 4 * x;
@@ -288,6 +332,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 __builtin_amdgcn_sched_barrier(0);
             }
             constexpr float sc = 1.0f / 255.0f;
+            const v4f bias1 = *reinterpret_cast<const v4f *>(bias + 16 * nt + 4 * kg);
             v4f v;
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = fmaxf((a0[r] + a1[r]) * sc + bias1[r], 0.f);
@@ -299,7 +344,22 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
                     *reinterpret_cast<v4f *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 16 * nt + 4 * kg) = v;
             }
-        }
+        };
+        auto load_w2 = [&] {
+#pragma unroll
+            for (int s = 0; s < W2_PRE; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
+        };
+        // conv2's first weights: behind the first tile where in front of it they would hold up conv1's own
+        if constexpr (G::MANY) load_w2();
+        __builtin_amdgcn_sched_barrier(0);
+        conv1_tile(tg);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (!G::MANY) load_w2();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+        for (int t = tg + 4; t < G::T1; t += 4) conv1_tile(t);
         sync_lds();
 
         // ---- conv2: kernel row kq
@@ -345,11 +405,11 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
             }
 #pragma unroll
             for (int q = 0; q < 6; ++q) w3[7 + q / 3][q % 3] = p3[(7 * 3 + q) * 64];
-            const v4f bias2 = *reinterpret_cast<const v4f *>(SP_SEG(si).b2 + co);
             if constexpr (NA == 2) acc[0][0] += acc[1][0];
             sync_lds();   // every wave has read conv1's image
             v4f own[T];
             reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+            const v4f bias2 = *reinterpret_cast<const v4f *>(bias + 32 + co);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const int m = 32 * t + i32, y = m / 9;
@@ -371,7 +431,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         // have to keep their old contents until here)
         const int kn = k + 1 < nu ? k + 1 : k, un = (int)blockIdx.x + kn * G0, sn = seg_of(un);
         const bf16_t *const wn = SP_SEG(sn).w;
-        if constexpr (G::MANY) load_px(sn, un, ring ? slots[kn] : 0);
+        if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, ring ? slots[kn] : 0);
         sync_lds();
 
         // ---- conv3: steps 9 kq .. 9 kq + 8 of 36
@@ -409,10 +469,10 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
                 acc[s % NA][t] = mfma6(w3[s], b, acc[s % NA][t]);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const v4f bias3 = *reinterpret_cast<const v4f *>(SP_SEG(si).b3 + co);
             if constexpr (NA == 2) acc[0][0] += acc[1][0];
             v4f own[T];
             reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+            const v4f bias3 = *reinterpret_cast<const v4f *>(bias + 96 + co);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const int m = 32 * t + i32, y = m / 7;
