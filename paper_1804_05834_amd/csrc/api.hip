@@ -355,11 +355,12 @@ struct Pass {
 };
 
 const float *theta_of(dqn_ctx *c, int net) { return net ? c->theta_t : c->theta; }
-const gbf::bf16_t *shadow_of(dqn_ctx *c, int net)
-{
-    const gbf::bf16_t *sh = (const gbf::bf16_t *)c->buf.shadow_bf16;
-    return sh + (net ? align_up((size_t)c->n * 2, 256) / 2 : 0);
-}
+// The bf16 copy of a network begins half a cache line into its buffer: the weights of fc1, conv2 and conv3 sit half a
+// line off in the blob, and a row's 128 bytes per reduction stage are one line this way, not the halves of two.
+constexpr size_t SHADOW_AT = 32;   // elements
+size_t shadow_bytes(int64_t n) { return align_up((size_t)n * 2 + SHADOW_AT * 2, 256); }
+static_assert((net::F1W + SHADOW_AT) % 64 == 0 && (net::C2W + SHADOW_AT) % 64 == 0 && (net::C3W + SHADOW_AT) % 64 == 0, "line-aligned weights");
+gbf::bf16_t *shadow_of(dqn_ctx *c, int net) { return (gbf::bf16_t *)c->buf.shadow_bf16 + (net ? shadow_bytes(c->n) / 2 : 0) + SHADOW_AT; }
 
 // Launch shapes of the conv1 forward kernel for `samples` samples (all passes), and whether a wave's
 // share of strips spans few enough samples for it to draw them itself.
@@ -660,7 +661,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
     }
     const bool few_fit = (size_t)rows * FC1_SPLITS <= w.f1rows;
     if (c->fc1_big && (rows >= c->fc1_big_rows || !few_fit)) {
-        // many rows: 128 x 128 tiles, double-buffered stages, few reduction splits
+        // many rows: 128 x 128 tiles, four stages in LDS, few reduction splits
         f1::Args A{};
         A.nseg = npass;
         int tile = 0;
@@ -784,7 +785,7 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     }
     for (; k < 5; ++k) RA.seg[k].block_begin = 0x7fffffff;  // never selected
     RA.theta = c->theta; RA.v = c->rms_v; RA.m = c->rms_m; RA.g = c->grads;
-    RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)c->buf.shadow_bf16 : nullptr;
+    RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)shadow_of(c, 0) : nullptr;
     RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w.w2t : nullptr;
     RA.packed = w.packed;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
@@ -1101,7 +1102,7 @@ int32_t dqn_query_sizes(const dqn_config *cfg, dqn_sizes *out)
     s.param_count = n;
     s.params = align_up((size_t)n * 4, 256);
     s.opt_state = s.params * (cfg->rms_centered ? 2 : 1);
-    s.shadow_bf16 = cfg->precision == 1 ? 2 * align_up((size_t)n * 2, 256) : 0;
+    s.shadow_bf16 = cfg->precision == 1 ? 2 * shadow_bytes(n) : 0;
     s.grads = s.params;
     const int64_t cap = cfg->replay_capacity;
     s.replay_frames = (size_t)cap * net::FRAME;
@@ -1186,10 +1187,8 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         misc::k_fill<<<1, 64, 0, st>>>(c->tree + 2 * c->L, 1.0f, 1);  // maximal priority starts at 1
     }
     if (cfg->precision == 1) {
-        __hip_bfloat16 *sh = (__hip_bfloat16 *)b->shadow_bf16;
-        size_t half = align_up((size_t)c->n * 2, 256) / 2;
-        misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(c->theta, sh, c->n);
-        misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(c->theta_t, sh + half, c->n);
+        for (int i = 0; i < 2; ++i)
+            misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta_of(c, i), (__hip_bfloat16 *)shadow_of(c, i), c->n);
         misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
     pack_conv(c, 0, st);
@@ -1346,9 +1345,7 @@ int32_t dqn_set_params(dqn_ctx *c, int32_t which, const float *src, void *stream
     hipStream_t st = (hipStream_t)stream;
     permute(c, src, dst, 0, st);
     if (c->cfg.precision == 1 && which <= 1) {
-        __hip_bfloat16 *sh = (__hip_bfloat16 *)c->buf.shadow_bf16;
-        size_t half = align_up((size_t)c->n * 2, 256) / 2;
-        misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, sh + (which ? half : 0), c->n);
+        misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, (__hip_bfloat16 *)shadow_of(c, which), c->n);
         if (which == 0) misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
     }
     if (which <= 1) pack_conv(c, which, st);
@@ -1382,9 +1379,7 @@ int32_t dqn_sync_target(dqn_ctx *c, void *stream)
     if (hipMemcpyAsync(c->theta_t, c->theta, (size_t)c->n * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
         return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     if (c->cfg.precision == 1) {
-        __hip_bfloat16 *sh = (__hip_bfloat16 *)c->buf.shadow_bf16;
-        size_t half = align_up((size_t)c->n * 2, 256) / 2;
-        if (hipMemcpyAsync(sh + half, sh, (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
+        if (hipMemcpyAsync(shadow_of(c, 1), shadow_of(c, 0), (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
             return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     }
     if (hipMemcpyAsync(packed_of(c, 1), packed_of(c, 0), (size_t)packed_count(c) * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)

@@ -223,20 +223,28 @@ __device__ __forceinline__ int tile_of(int u, int total)
 // reduction splits, which the head kernel adds up.
 //
 // 128 x 128 output tile per workgroup of four waves, 64 x 64 per wave (2 x 2 MFMA blocks, so every
-// LDS fragment feeds two matrix instructions), reduction stages of 64 elements in LDS tiles that are
-// double-buffered: ONE barrier per stage and sixteen 32x32x16 MFMAs per wave between two barriers.
-// While stage s is multiplied, stage s+1 goes from registers to the other LDS buffer and stage s+3
-// is requested from memory.  The 49 stages of the reduction are dealt out evenly to the splits.
-// Measured per stage and workgroup in the steady state: 16 MFMAs per wave take 250 ns, with the LDS
-// reads beside them 285 ns, with the 32 KB of LDS writes as well 430 ns: the loop is bound by LDS
-// bandwidth (96 KB per stage and compute unit), not by the matrix pipe.
+// LDS fragment feeds two matrix instructions), reduction stages of 64 elements, four of them in LDS.
+// A CU gets one workgroup (8192 rows have 256 tiles, fewer rows are split until there are about as
+// many), so nothing hides a wave's waits but its own depth: stages go from memory straight to LDS,
+// three to four ahead, and from LDS to registers one whole stage ahead, so that a stage's sixteen
+// MFMAs have their operands from the start and the next stage's reads and requests lie between
+// them.  One barrier per stage, none of whose operands are on their way through registers to LDS.
+// A row's 128 bytes of a stage are eight 16-byte pieces; piece c of row r lies in place c ^ (r % 8),
+// which puts the sixteen rows that a read takes in one pass into different banks without padding
+// (a load that goes to LDS cannot pad).  The 49 stages are dealt out evenly to the splits.
+// Rows of both operands have to start on a cache line, or every piece of a stage is two requests:
+// with the weights half a line off, 8192 rows took 43 us however deep the pipeline was.
+// Measured (8192 rows, one split, behind conv3): 43 us with two buffers filled through registers,
+// 35 us now; 24 us of it with nothing fetched, 22 us with nothing multiplied.  1536 rows in four
+// splits: 13.6 -> 12.0 us.  The requests between the MFMAs instead of in front of them: 34 -> 30 us alone.
 // Tile order: the four column tiles of one row tile and split next to each other (they share the
 // activations), row tiles of one split after each other (they share the weights).
 // ---------------------------------------------------------------------------
 namespace f1 {
 constexpr int BM = 128, BN = 128;
-constexpr int TILE = BM * LDK;                   // elements of one operand tile in LDS
-constexpr int LDS_BYTES = 2 * 2 * TILE * 2;      // two operands, two buffers: 73,728 bytes
+constexpr int NBUF = 4;                          // stages in LDS
+constexpr int TILE = BM * BK;                    // elements of one operand tile in LDS
+constexpr int LDS_BYTES = 2 * NBUF * TILE * 2;   // 131,072 bytes: one workgroup per CU
 constexpr int STAGES = GFc1::K / BK;             // 49
 
 struct Args {
@@ -255,10 +263,17 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_s_barrier();
 }
 
-__global__ __launch_bounds__(256, 2) void k_fc1_fwd(Args A)
+// 16 bytes per lane from memory to LDS, lane l's to p + 8 l, past the registers.  In assembly, because the compiler
+// would let every LDS read behind it wait for its arrival; `ready` waits for what a stage needs.
+__device__ __forceinline__ void to_lds(const bf16_t *g, bf16_t *p)
 {
-    extern __shared__ __attribute__((aligned(16))) bf16_t lds[];
-    bf16_t *As = lds, *Bs = lds + 2 * TILE;      // [buffer][row][LDK]
+    const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory");
+}
+
+__global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
+{
+    extern __shared__ __attribute__((aligned(16))) bf16_t lds[];   // [operand][buffer][row][BK], pieces in permuted places
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t = tile_of(blockIdx.x, gridDim.x);
     const int by = t & 3, bx = (t >> 2) % A.tiles_m, bz = (t >> 2) / A.tiles_m;
@@ -269,93 +284,87 @@ __global__ __launch_bounds__(256, 2) void k_fc1_fwd(Args A)
     const int s0 = STAGES * bz / A.nsplit, n = STAGES * (bz + 1) / A.nsplit - s0;
     const bf16_t *x = static_cast<const bf16_t *>(S.x);
 
-    // staging: 16-byte piece c = tid + 256 i of a 128 x 64 tile is row c / 8, elements 8 (c % 8) .. +7
-    const int lr = tid >> 3, kq = (tid & 7) * 8;
+    // Instruction q of a wave fetches rows 8 (4 wave + q) .. + 7 of a tile: lane l row l / 8, and of that row the
+    // 16-byte piece whose place in LDS lane l's is (fetch_piece).
+    const int fr = wave * 32 + (lane >> 3), fk = ((lane & 7) ^ (lane >> 3)) * 8;
     const bf16_t *pa[4], *pb[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int m = m0 + lr + 32 * i;
+    for (int q = 0; q < 4; ++q) {
+        int m = m0 + fr + 8 * q;
         if (m > S.M - 1) m = S.M - 1;             // rows past the end repeat the last row; they are never stored
-        pa[i] = x + (long)m * S.xs + kq;
-        pb[i] = S.w + (long)(n0 + lr + 32 * i) * GFc1::K + kq;
+        pa[q] = x + (long)m * S.xs + fk + s0 * BK;
+        pb[q] = S.w + (long)(n0 + fr + 8 * q) * GFc1::K + fk + s0 * BK;
     }
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a native vector: stays in registers
-    struct Regs { u32x4 a[4], b[4]; };
-    Regs R0, R1;                                  // two stages on their way from memory
-    auto gload = [&](Regs &R, int st) {
-        const int k0 = (s0 + st) * BK;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            R.a[i] = *reinterpret_cast<const u32x4 *>(pa[i] + k0);
-            R.b[i] = *reinterpret_cast<const u32x4 *>(pb[i] + k0);
-        }
-    };
-    auto sstore = [&](const Regs &R, int buf) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<u32x4 *>(&As[buf * TILE + (lr + 32 * i) * LDK + kq]) = R.a[i];
-            *reinterpret_cast<u32x4 *>(&Bs[buf * TILE + (lr + 32 * i) * LDK + kq]) = R.b[i];
-        }
-    };
+    auto fetch_a = [&](int st, int buf, int q) { to_lds(pa[q] + st * BK, lds + buf * TILE + (wave * 4 + q) * 512); };
+    auto fetch_b = [&](int st, int buf, int q) { to_lds(pb[q] + st * BK, lds + (NBUF + buf) * TILE + (wave * 4 + q) * 512); };
     const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 31, h = lane >> 5;
-    const int apo = (wm * 64 + li) * LDK + 8 * h, bpo = (wn * 64 + li) * LDK + 8 * h;
     v16f acc[2][2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = v16f{0};
     struct Frag { v8bf a[2], b[2]; };             // the operands of one 16-deep step of the wave's 64 x 64
-    auto rd = [&](int buf, int kk) {
+    const bf16_t *ap[4], *bp[4];                  // of step s; the piece's place again
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int at = ((2 * s + h) ^ (li & 7)) * 8;
+        ap[s] = lds + (wm * 64 + li) * BK + at;
+        bp[s] = lds + NBUF * TILE + (wn * 64 + li) * BK + at;
+    }
+    auto rd = [&](int buf, int s) {
         Frag F;
-        const bf16_t *ap = As + buf * TILE + apo + kk, *bp = Bs + buf * TILE + bpo + kk;
-        F.a[0] = frag_k(ap); F.a[1] = frag_k(ap + 32 * LDK);
-        F.b[0] = frag_k(bp); F.b[1] = frag_k(bp + 32 * LDK);
+        F.a[0] = frag_k(ap[s] + buf * TILE); F.a[1] = frag_k(ap[s] + buf * TILE + 32 * BK);
+        F.b[0] = frag_k(bp[s] + buf * TILE); F.b[1] = frag_k(bp[s] + buf * TILE + 32 * BK);
         return F;
     };
-    auto mm = [&](const Frag &F) {
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[a][b] = mfma(F.b[b], F.a[a], acc[a][b]);  // transposed tile
+    // everything but the last `later` stages that were requested has arrived in LDS, and every wave is through with
+    // its reads
+    auto ready = [&](int later) {
+        if (later >= 3) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+        else if (later == 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        else if (later == 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        lds_barrier();
     };
 
-    gload(R0, 0);
-    if (n > 1) gload(R1, 1);
-    sstore(R0, 0);
-    if (n > 2) gload(R0, 2);
-    lds_barrier();
-    Frag cur = rd(0, 0);
-    // Stage i out of buffer buf.  NX holds stage i + 1 (requested two stages ago) and is refilled with
-    // stage i + 3.  The operands of a step are requested before the matrix instructions of the step
-    // before it; the barrier sits in front of the stage's last step, whose matrix instructions then
-    // cover the barrier and the first LDS reads of the next stage.  The other buffer was last read
-    // before the previous barrier, so it may be written at any point of this stage.
-    auto stage = [&](int i, int buf, Regs &NX) {
-        Frag f1 = rd(buf, 16);
-        __builtin_amdgcn_sched_barrier(0);
-        mm(cur);
-        __builtin_amdgcn_sched_barrier(0);
-        Frag f2 = rd(buf, 32);
-        if (i + 1 < n) sstore(NX, buf ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-        mm(f1);
-        __builtin_amdgcn_sched_barrier(0);
-        Frag f3 = rd(buf, 48);
-        if (i + 3 < n) gload(NX, i + 3);
-        __builtin_amdgcn_sched_barrier(0);
-        mm(f2);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_barrier();
-        if (i + 1 < n) cur = rd(buf ^ 1, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        mm(f3);
-        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < NBUF; ++st)
+        if (st < n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { fetch_a(st, st, q); fetch_b(st, st, q); }
+    ready((n < NBUF ? n : NBUF) - 1);                              // stage 0
+    Frag F[2][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) F[0][s] = rd(0, s);
+    ready((n < NBUF ? n : NBUF) - 2);                              // stage 1, and buffer 0 is free
+    // Stage i, whose operands are in registers: stage i + 1 goes from LDS to registers meanwhile and stage i + 4 is
+    // requested into the buffer that stage i was read from.
+    auto stage = [&](int i, int buf) {
+        Frag (&C)[4] = F[buf & 1], (&X)[4] = F[(buf & 1) ^ 1];
+        const bool more = i + NBUF < n;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            X[s] = rd((buf + 1) % NBUF, s);
+            __builtin_amdgcn_sched_barrier(0);
+            acc[0][0] = mfma(C[s].b[0], C[s].a[0], acc[0][0]);   // transposed tile
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) fetch_a(i + NBUF, buf, s);
+            __builtin_amdgcn_sched_barrier(0);
+            acc[0][1] = mfma(C[s].b[1], C[s].a[0], acc[0][1]);
+            acc[1][0] = mfma(C[s].b[0], C[s].a[1], acc[1][0]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) fetch_b(i + NBUF, buf, s);
+            __builtin_amdgcn_sched_barrier(0);
+            acc[1][1] = mfma(C[s].b[1], C[s].a[1], acc[1][1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        ready(n - 3 - i < 2 ? n - 3 - i : 2);
     };
-    for (int i = 0; i < n; i += 2) {              // unrolled by two: the register sets alternate statically
-        stage(i, 0, R1);
-        if (i + 1 < n) stage(i + 1, 1, R0);
-    }
+    for (int i = 0; i < n; i += NBUF)
+#pragma unroll
+        for (int j = 0; j < NBUF; ++j)
+            if (i + j < n) stage(i + j, j);
 
     // acc[a][b][4g + j] = Y[row block a, lane li][column block b, 8g + 4h + j].  The tile leaves through LDS
     // (the operand buffers are no longer read: the loop ends on a barrier), so that it is written as whole
