@@ -19,18 +19,55 @@ __device__ __forceinline__ void sync_lds()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-__device__ __forceinline__ float wave_sum(float v)
+// The value of lane `lane ^ O`.  Within sixteen lanes by the operand permutation of a vector instruction, across by the
+// row and half swaps: a few cycles each, where the exchange through LDS that __shfl_xor compiles to is a round trip of
+// about a hundred, and the reductions of the head and of the tree are chains of them.
+template <int O> __device__ __forceinline__ int lane_xor(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    if constexpr (O == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);          // quad_perm 1 0 3 2
+    else if constexpr (O == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);     // quad_perm 2 3 0 1
+    else if constexpr (O == 4)                                                                     // half mirror (7 - l), then 3 - l
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true), 0x1B, 0xF, 0xF, true);
+    else if constexpr (O == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, true);    // rotation by 8 of 16
+    else if constexpr (O == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (int)(threadIdx.x & 16 ? r[0] : r[1]);
+    } else {
+        static_assert(O == 32, "lane_xor: O is a power of two below 64");
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (int)(threadIdx.x & 32 ? r[0] : r[1]);
+    }
+}
+template <int O> __device__ __forceinline__ float lane_xor(float v) { return __int_as_float(lane_xor<O>(__float_as_int(v))); }
+
+template <int O = 32> __device__ __forceinline__ float wave_sum(float v)   // over groups of 2 O lanes
+{
+    v += lane_xor<O>(v);
+    if constexpr (O > 1) return wave_sum<O / 2>(v);
+    else return v;
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, lane_xor<32>(v));
+    v = fmaxf(v, lane_xor<16>(v));
+    v = fmaxf(v, lane_xor<8>(v));
+    v = fmaxf(v, lane_xor<4>(v));
+    v = fmaxf(v, lane_xor<2>(v));
+    return fmaxf(v, lane_xor<1>(v));
+}
+// the largest value of the wave and the lowest index that holds it, in every lane
+template <int O = 32> __device__ __forceinline__ void wave_argmax(float &bv, int &bi)
+{
+    const float ov = lane_xor<O>(bv);
+    const int oi = lane_xor<O>(bi);
+    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    if constexpr (O > 1) wave_argmax<O / 2>(bv, bi);
 }
 
 __device__ __forceinline__ float block_max_1024(float v, float *sh /*16*/)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    v = wave_max(v);
     __syncthreads();
     if (lane == 0) sh[wave] = v;
     __syncthreads();
@@ -92,8 +129,7 @@ __device__ __forceinline__ void head_rows3_dot(const HeadRound &H, const float (
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < net::HID / 16; ++k) acc += H.w[k] * x[l + 16 * k];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    acc = wave_sum<8>(acc);
     if (l == 0) raw[p][r] = acc + H.b;
 }
 
@@ -202,9 +238,7 @@ __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
         head_rows3_dot(H0, hid, K, A.dueling, raw, tid);
     }
     if (norm) {  // per-wave maxima of the raw weights; thread 0 combines them below
-        float wmax = fmaxf(w0, w1);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) wmax = fmaxf(wmax, __shfl_xor(wmax, o, 64));
+        const float wmax = wave_max(fmaxf(w0, w1));
         if ((tid & 63) == 0) shm[tid >> 6] = wmax;
     }
     __syncthreads();
@@ -220,13 +254,8 @@ __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
         // argmax with the lowest index winning ties; lanes past K never win
         float bv = a < K ? qa : -3.4028234663852886e38f;
         int bi = a < K ? a : 64;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(bv, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
-        const float q_aj = __shfl(qa, aj, 64);
+        wave_argmax(bv, bi);
+        const float q_aj = lane_value(qa, aj);
         if (a == 0) {
             res_as[p] = bi;
             if (p == 0) { res_q[0] = q_aj; res_q[1] = bv; }
@@ -401,8 +430,7 @@ __device__ __forceinline__ void head_rows1_dot(const HeadRound &H, const float *
     float acc = 0.f;
 #pragma unroll
     for (int k = 0; k < net::HID / 16; ++k) acc += H.w[k] * hid[l + 16 * k];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+    acc = wave_sum<8>(acc);
     if (l == 0 && H.d >= 0) raw[H.d] = acc + H.b;
 }
 template <int NS>
@@ -447,12 +475,7 @@ __global__ __launch_bounds__(256) void k_head_act(HeadActArgs A)
         // argmax with the lowest index winning ties; lanes past K never win
         float bv = a < K ? qa : -3.4028234663852886e38f;
         int bi = a < K ? a : 64;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(bv, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
+        wave_argmax(bv, bi);
         if (a == 0) {
             int act = bi;
             const float u = draw_u24(A.seed, 2ull * (uint64_t)e);
@@ -665,11 +688,16 @@ __device__ __forceinline__ float tree_block16(float *tree, long Lcur, int BL, lo
         tree[at / 8] = s;
     }
     at /= 8;
-#pragma unroll
-    for (int k = 1; k <= 6; ++k) {
-        s += __shfl_xor(s, 1 << (k - 1), 64);
+    auto level = [&](int k, float other) {
+        s += other;
         if (on && (nthr >> k) >= 1 && (tid & ((1 << k) - 1)) == 0) tree[at >> k] = s;
-    }
+    };
+    level(1, lane_xor<1>(s));
+    level(2, lane_xor<2>(s));
+    level(3, lane_xor<4>(s));
+    level(4, lane_xor<8>(s));
+    level(5, lane_xor<16>(s));
+    level(6, lane_xor<32>(s));
     if (nthr > 64) {   // uniform
         if ((tid & 63) == 0) sh[tid >> 6] = s;
         __syncthreads();
@@ -1309,8 +1337,8 @@ __global__ __launch_bounds__(256) void k_preprocess_staged(const uint8_t *raw, l
         const float bot = grey(below + x0) * (1.f - fx) + grey(below + x1) * fx;
         const float v = top * (1.f - fy) + bot * fy;
         uint32_t b = (uint32_t)(uint8_t)fminf(fmaxf(rintf(v), 0.f), 255.f) << (8 * (j & 3));
-        b |= __shfl_xor(b, 1, 64);
-        b |= __shfl_xor(b, 2, 64);
+        b |= (uint32_t)lane_xor<1>((int)b);
+        b |= (uint32_t)lane_xor<2>((int)b);
         if ((j & 3) == 0) *reinterpret_cast<uint32_t *>(dst + 84 * i) = b;
     }
 }

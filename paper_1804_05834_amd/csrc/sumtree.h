@@ -82,6 +82,9 @@ __device__ __forceinline__ int first_round_levels(int levels)
     return levels > 6 && (m == 1 || m == 2) ? 6 + m : min(6, levels);
 }
 
+// v of lane `l`, the same l in every lane
+__device__ __forceinline__ float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+
 template <int ND>
 __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int (&jj)[ND], int lane, long (&slot)[ND],
                                                  float (&leaf)[ND])
@@ -101,6 +104,15 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
         }
         return total;
     }
+    // One level down: the walk is the same in every lane, so its position is kept in scalar registers and the
+    // children's sums are read from the lanes that hold them; through the exchange in LDS (__shfl) a level was two
+    // round trips of a hundred cycles, and they follow each other.
+    auto step = [](float left, float right, int c, float &zd, float &lf) {
+        const bool down_left = zd < left || right == 0.f;   // nothing on the right: a zero leaf is never drawn
+        lf = down_left ? left : right;
+        zd = down_left ? zd : zd - left;
+        return __builtin_amdgcn_readfirstlane(down_left ? c : c + 1);
+    };
     const float *tree = A.tree;
     float total = 0.f, z[ND];
     long node[ND];
@@ -124,7 +136,7 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
             const int n = 64 * q + lane;
             v[q] = n >= 1 && n < (2 << r0) ? tree[n] : 0.f;
         }
-        total = __shfl(v[0], 1, 64);
+        total = lane_value(v[0], 1);
 #pragma unroll
         for (int d = 0; d < ND; ++d) {
             z[d] = mass(jj[d], total);
@@ -138,15 +150,7 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
                 else if (t == 5) m = v[1];
                 else if (t == 6) m = (c & 64) ? v[3] : v[2];
                 else m = (c & 128) ? ((c & 64) ? v[7] : v[6]) : ((c & 64) ? v[5] : v[4]);
-                const float left = __shfl(m, c & 63, 64), right = __shfl(m, (c & 63) + 1, 64);
-                if (z[d] < left || right == 0.f) {
-                    cur = c;
-                    leaf[d] = left;
-                } else {
-                    z[d] = z[d] - left;
-                    cur = c + 1;
-                    leaf[d] = right;
-                }
+                cur = step(lane_value(m, c & 63), lane_value(m, (c & 63) + 1), c, z[d], leaf[d]);
             }
             node[d] = cur;
         }
@@ -162,7 +166,7 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
             if (r == 6) vb[d] = tree[(node[d] << 6) + lane];
         }
         if (done == 0) {
-            total = __shfl(va[0], 1, 64);
+            total = lane_value(va[0], 1);
 #pragma unroll
             for (int d = 0; d < ND; ++d) z[d] = mass(jj[d], total);
         }
@@ -171,16 +175,8 @@ __device__ __forceinline__ float per_sample_walk(const SampleArgs &A, const int 
             int cur = 1;  // local heap index
             for (int t = 0; t < r; ++t) {
                 const int c = 2 * cur;  // left child
-                const float left = c < 64 ? __shfl(va[d], c, 64) : __shfl(vb[d], c - 64, 64);
-                const float right = c < 64 ? __shfl(va[d], c + 1, 64) : __shfl(vb[d], c - 63, 64);
-                if (z[d] < left || right == 0.f) {   // nothing on the right: a zero leaf is never drawn
-                    cur = c;
-                    leaf[d] = left;
-                } else {
-                    z[d] = z[d] - left;
-                    cur = c + 1;
-                    leaf[d] = right;
-                }
+                const float m = c < 64 ? va[d] : vb[d];
+                cur = step(lane_value(m, c & 63), lane_value(m, (c & 63) + 1), c, z[d], leaf[d]);
             }
             node[d] = (node[d] << r) + (cur - (1 << r));
         }
