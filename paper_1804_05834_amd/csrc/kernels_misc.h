@@ -118,18 +118,32 @@ __device__ __forceinline__ void head_rows3_load(HeadRound &H, int round, const f
     for (int k = 0; k < net::HID / 16; ++k) H.w[k] = w[l + 16 * k];
     H.b = head[head_b_off(r, K, dueling)];
 }
-__device__ __forceinline__ void head_rows3_dot(const HeadRound &H, const float (*hid)[net::HID] /*LDS [3][512]*/,
+// Where hidden unit i lies in LDS: lane l of a group of sixteen takes units l, l + 16, ... in turn, and finds them side
+// by side, eight 16-byte reads instead of 32 of four bytes (the pitch of 36 keeps the sixteen lanes in different banks).
+constexpr int HID_LDS = 16 * 36;
+__device__ __forceinline__ int hid_at(int i) { return (i & 15) * 36 + (i >> 4); }
+// sum over k of w[k] * unit l + 16 k, in the order of k, then over the sixteen lanes
+__device__ __forceinline__ float head_dot(const HeadRound &H, const float *hid, int l)
+{
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < net::HID / 16; k += 4) {
+        const float4 x = *reinterpret_cast<const float4 *>(hid + l * 36 + k);
+        acc += H.w[k] * x.x;
+        acc += H.w[k + 1] * x.y;
+        acc += H.w[k + 2] * x.z;
+        acc += H.w[k + 3] * x.w;
+    }
+    return wave_sum<8>(acc);
+}
+__device__ __forceinline__ void head_rows3_dot(const HeadRound &H, const float (*hid)[HID_LDS] /*LDS [3]*/,
                                                int K, int dueling, float (*raw)[65] /*LDS [3][65]*/, int tid)
 {
     if (H.d < 0) return;  // uniform within the 16-lane group
     const int R = K + (dueling ? 1 : 0);
     const int l = tid & 15;
     const int p = H.d / R, r = H.d - p * R;
-    const float *x = hid[p];
-    float acc = 0.f;
-#pragma unroll
-    for (int k = 0; k < net::HID / 16; ++k) acc += H.w[k] * x[l + 16 * k];
-    acc = wave_sum<8>(acc);
+    const float acc = head_dot(H, hid[p], l);
     if (l == 0) raw[p][r] = acc + H.b;
 }
 
@@ -175,7 +189,7 @@ constexpr int HEAD_MAX_SPLITS = 7;   // most reduction splits of fc1
 template <int NS>
 __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
 {
-    __shared__ float hid[3][net::HID];
+    __shared__ __attribute__((aligned(16))) float hid[3][HID_LDS];
     __shared__ float raw[3][MAXR];
     __shared__ float q[3][64];
     __shared__ float shm[16];
@@ -208,6 +222,7 @@ __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- hidden layer: split sums in split order, bias, ReLU
+    float hs;   // the thread's unit of pass 0
     {
         float acc[3] = {0.f, 0.f, 0.f};
 #pragma unroll
@@ -215,10 +230,10 @@ __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
 #pragma unroll
             for (int sp = 0; sp < NS; ++sp) acc[p] += ps[p][sp];
         }
-        const float hs = fmaxf(acc[0] + b_on, 0.f);
-        hid[0][tid] = hs;
-        hid[1][tid] = fmaxf(acc[1] + b_on, 0.f);
-        hid[2][tid] = fmaxf(acc[2] + b_tg, 0.f);
+        hs = fmaxf(acc[0] + b_on, 0.f);
+        hid[0][hid_at(tid)] = hs;
+        hid[1][hid_at(tid)] = fmaxf(acc[1] + b_on, 0.f);
+        hid[2][hid_at(tid)] = fmaxf(acc[2] + b_tg, 0.f);
         A.h_s[(long)j * net::HID + tid] = hs;
     }
     __syncthreads();
@@ -311,7 +326,7 @@ __global__ __launch_bounds__(512) void k_head_train(HeadArgs A)
             if (r < R) acc += ((A.dueling && r == 0) ? g : (r == hit ? g : 0.f) - gk) * hw[r];
         for (int r = HW_PRE; r < R; ++r)
             acc += ((A.dueling && r == 0) ? g : (r == hit ? g : 0.f) - gk) * A.head_on[head_w_off(r, K, A.dueling) + tid];
-        const float gmask = hid[0][tid] > 0.f ? acc : 0.f;
+        const float gmask = hs > 0.f ? acc : 0.f;
         if (A.dh_bf16) static_cast<__hip_bfloat16 *>(A.dh)[(long)j * net::HID + tid] = __float2bfloat16(gmask);
         else static_cast<float *>(A.dh)[(long)j * net::HID + tid] = gmask;
     }
@@ -405,13 +420,17 @@ struct HeadActArgs {
     float *q_out;  // optional [E][K]
 };
 
-// Acting (Alg.1 action lines): finish fc1, evaluate the head, pick the action.  One workgroup per
-// observation, built like the training head: every global operand (the partial sums of the thread's two
-// hidden units, the biases, the head weights of the first 32 dot products, spread over groups of 16 lanes)
-// is requested before anything is waited for, the dueling combine (Eq.13) and the argmax run on one wave
+// Acting (Alg.1 action lines): finish fc1, evaluate the head, pick the action.  ROWS observations per workgroup at a
+// time, built like the training head: every global operand (the partial sums of the thread's two
+// hidden units per row, the biases, the head weights of the first 32 dot products, spread over groups of 16 lanes)
+// is requested before anything is waited for, the dueling combine (Eq.13) and the argmax run on one wave per row
 // with lane a holding action a, and the arithmetic is that of k_head_train, so Q(s, .) has the same bits
 // here and there.  NS: reduction splits of fc1 (A.nsplit), a template argument so that the loads are
 // unconditional.
+// With a workgroup per observation, 8192 of them fetched the head's weights, 39 KB at 18 actions, 8192 times and took
+// 21 us for 17 MB of partial sums.  So many observations share workgroups that keep the weights in registers and take
+// four rows in turn, the next four's sums on their way: 9.1 us (2048 in three splits: 6.9 -> 5.1).  Fewer have a
+// workgroup each, which has the shorter chain (launch_head_act).
 __device__ __forceinline__ void head_rows1_load(HeadRound &H, int round, const float *head, int K, int dueling, int tid)
 {
     const int R = K + (dueling ? 1 : 0);
@@ -424,81 +443,130 @@ __device__ __forceinline__ void head_rows1_load(HeadRound &H, int round, const f
     for (int k = 0; k < net::HID / 16; ++k) H.w[k] = w[l + 16 * k];
     H.b = head[head_b_off(r, K, dueling)];
 }
-__device__ __forceinline__ void head_rows1_dot(const HeadRound &H, const float *hid /*LDS [512]*/, float *raw /*LDS*/, int tid)
+template <int NS, int ROWS>
+__global__ __launch_bounds__(256, ROWS == 1 ? 1 : 3) void k_head_act(HeadActArgs A)
 {
-    const int l = tid & 15;
-    float acc = 0.f;
-#pragma unroll
-    for (int k = 0; k < net::HID / 16; ++k) acc += H.w[k] * hid[l + 16 * k];
-    acc = wave_sum<8>(acc);
-    if (l == 0 && H.d >= 0) raw[H.d] = acc + H.b;
-}
-template <int NS>
-__global__ __launch_bounds__(256) void k_head_act(HeadActArgs A)
-{
-    __shared__ float hid[net::HID];
-    __shared__ float raw[MAXR];
-    const int e = blockIdx.x, tid = threadIdx.x;
+    __shared__ __attribute__((aligned(16))) float hid[ROWS][HID_LDS];
+    __shared__ float raw[ROWS][MAXR];
+    const int tid = threadIdx.x, wave = tid >> 6, l = tid & 15;
     const int K = A.K, R = K + (A.dueling ? 1 : 0);
-    float ps[2][NS];
+    float ps[ROWS][2][NS];
+    auto load_sums = [&](int e0) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+        for (int r = 0; r < ROWS; ++r) {
+            const int e = min(e0 + r, A.E - 1);   // (rows past the end repeat the last one)
 #pragma unroll
-        for (int sp = 0; sp < NS; ++sp) ps[u][sp] = A.part[sp * A.split_stride + (long)e * net::HID + tid + 256 * u];
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int sp = 0; sp < NS; ++sp) ps[r][u][sp] = A.part[sp * A.split_stride + (long)e * net::HID + tid + 256 * u];
+        }
+    };
+    int e0 = blockIdx.x * ROWS;
+    load_sums(e0);
     const float b0 = A.f1b[tid], b1 = A.f1b[tid + 256];
     HeadRound H0, H1;
     head_rows1_load(H0, 0, A.head, K, A.dueling, tid);
     head_rows1_load(H1, 1, A.head, K, A.dueling, tid);
     __builtin_amdgcn_sched_barrier(0);
-    {
-        float acc[2] = {0.f, 0.f};
+    // (head_dot for the rows side by side: a row's sum is one chain of 32 additions, in that order)
+    auto dots = [&](const HeadRound &H) {
+        float acc[ROWS] = {};
+        float4 x[ROWS], nx[ROWS];
+        auto read = [&](int k) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+            for (int r = 0; r < ROWS; ++r) nx[r] = *reinterpret_cast<const float4 *>(&hid[r][l * 36 + k]);
+        };
+        read(0);
 #pragma unroll
-            for (int sp = 0; sp < NS; ++sp) acc[u] += ps[u][sp];
-        hid[tid] = fmaxf(acc[0] + b0, 0.f);
-        hid[tid + 256] = fmaxf(acc[1] + b1, 0.f);
-    }
-    __syncthreads();
-    head_rows1_dot(H0, hid, raw, tid);
-    head_rows1_dot(H1, hid, raw, tid);
-    for (int round = 2; 16 * round < R; ++round) {   // more than 32 dot products: K > 31
-        head_rows1_load(H0, round, A.head, K, A.dueling, tid);
-        head_rows1_dot(H0, hid, raw, tid);
-    }
-    __syncthreads();
-    if (tid < 64) {
-        const int a = tid;
-        const float v = a < K ? raw[A.dueling ? 1 + a : a] : 0.f;
-        float qa = v;
-        if (A.dueling) qa = raw[0] + (v - wave_sum(v) / (float)K);
-        // argmax with the lowest index winning ties; lanes past K never win
-        float bv = a < K ? qa : -3.4028234663852886e38f;
-        int bi = a < K ? a : 64;
-        wave_argmax(bv, bi);
-        if (a == 0) {
-            int act = bi;
-            const float u = draw_u24(A.seed, 2ull * (uint64_t)e);
-            if (u < A.epsilon) {
-                const float u2 = draw_u24(A.seed, 2ull * (uint64_t)e + 1ull);
-                act = min((int)floorf(u2 * (float)K), K - 1);
-            }
-            A.actions[e] = act;
+        for (int k = 0; k < net::HID / 16; k += 4) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) x[r] = nx[r];
+            if (k + 4 < net::HID / 16) read(k + 4);
+            if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);   // all reads at once would take the registers of three workgroups
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k] * x[r].x;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 1] * x[r].y;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 2] * x[r].z;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 3] * x[r].w;
+            if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);
         }
-        if (A.q_out && a < K) A.q_out[(long)e * K + a] = qa;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum<8>(acc[r]);
+        if (l == 0 && H.d >= 0)
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) raw[r][H.d] = acc[r] + H.b;
+    };
+    for (;;) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            float acc[2] = {0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int sp = 0; sp < NS; ++sp) acc[u] += ps[r][u][sp];
+            hid[r][hid_at(tid)] = fmaxf(acc[0] + b0, 0.f);
+            hid[r][hid_at(tid + 256)] = fmaxf(acc[1] + b1, 0.f);
+        }
+        const int next = e0 + (int)gridDim.x * ROWS;
+        if (ROWS > 1 && next < A.E) load_sums(next);
+        sync_lds();
+        dots(H0);
+        if (16 + 4 * wave < R) dots(H1);
+        if constexpr (ROWS == 1)
+            for (int round = 2; 16 * round < R; ++round) {   // more than 32 dot products: K > 31
+                head_rows1_load(H0, round, A.head, K, A.dueling, tid);
+                dots(H0);
+            }
+        sync_lds();
+        const int e = e0 + wave;
+        if (wave < ROWS && e < A.E) {
+            const int a = tid & 63;
+            const float *rw = raw[ROWS == 1 ? 0 : wave];
+            const float v = a < K ? rw[A.dueling ? 1 + a : a] : 0.f;
+            float qa = v;
+            if (A.dueling) qa = rw[0] + (v - wave_sum(v) / (float)K);
+            // argmax with the lowest index winning ties; lanes past K never win
+            float bv = a < K ? qa : -3.4028234663852886e38f;
+            int bi = a < K ? a : 64;
+            wave_argmax(bv, bi);
+            if (a == 0) {
+                int act = bi;
+                const float u = draw_u24(A.seed, 2ull * (uint64_t)e);
+                if (u < A.epsilon) {
+                    const float u2 = draw_u24(A.seed, 2ull * (uint64_t)e + 1ull);
+                    act = min((int)floorf(u2 * (float)K), K - 1);
+                }
+                A.actions[e] = act;
+            }
+            if (A.q_out && a < K) A.q_out[(long)e * K + a] = qa;
+        }
+        if (ROWS == 1 || next >= A.E) break;
+        // (the next round writes hid, which every wave has read, before the barrier behind which raw is written again)
+        e0 = next;
     }
 }
+// Four rows per workgroup from four observations per CU on, where a workgroup each no longer fits the chip at once
+// (1024 in six splits: 4.5 against 5.0 us, 600 in seven: 5.1 against 4.5), and for heads of at most 32 rows, whose
+// weights fit in registers.  Three workgroups fit a CU.
+template <int NS> void launch_head_act_ns(const HeadActArgs &H, int num_cu, hipStream_t st)
+{
+    if (H.E >= 4 * num_cu && H.K + (H.dueling ? 1 : 0) <= 32) k_head_act<NS, 4><<<min((H.E + 3) / 4, 3 * num_cu), 256, 0, st>>>(H);
+    else k_head_act<NS, 1><<<H.E, 256, 0, st>>>(H);
+}
 // the launch for a run-time number of splits
-inline void launch_head_act(const HeadActArgs &H, hipStream_t st)
+inline void launch_head_act(const HeadActArgs &H, int num_cu, hipStream_t st)
 {
     switch (H.nsplit) {
-    case 1: k_head_act<1><<<H.E, 256, 0, st>>>(H); break;
-    case 2: k_head_act<2><<<H.E, 256, 0, st>>>(H); break;
-    case 3: k_head_act<3><<<H.E, 256, 0, st>>>(H); break;
-    case 4: k_head_act<4><<<H.E, 256, 0, st>>>(H); break;
-    case 5: k_head_act<5><<<H.E, 256, 0, st>>>(H); break;
-    case 6: k_head_act<6><<<H.E, 256, 0, st>>>(H); break;
-    default: k_head_act<7><<<H.E, 256, 0, st>>>(H); break;
+    case 1: launch_head_act_ns<1>(H, num_cu, st); break;
+    case 2: launch_head_act_ns<2>(H, num_cu, st); break;
+    case 3: launch_head_act_ns<3>(H, num_cu, st); break;
+    case 4: launch_head_act_ns<4>(H, num_cu, st); break;
+    case 5: launch_head_act_ns<5>(H, num_cu, st); break;
+    case 6: launch_head_act_ns<6>(H, num_cu, st); break;
+    default: launch_head_act_ns<7>(H, num_cu, st); break;
     }
 }
 
