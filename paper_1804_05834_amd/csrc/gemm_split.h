@@ -61,6 +61,45 @@ __device__ __forceinline__ v16f mfma6(const v8bf (&a)[3], const v8bf (&b)[3], v1
     c = mfma(a[0], b[1], c);
     return mfma(a[0], b[0], c);
 }
+// The same with the leading products in a sum of their own, to which the caller adds the rest once at the end.  The
+// matrix instruction's additions do not round to nearest: each leaves an error of the same sign, up to a unit in the
+// last place of the sum.  In a gradient, which is a sum of tens of thousands of such results that cancel, these errors
+// would add up (conv1's weight gradient at a batch of 42 with everything in one sum: 8.2e-7 of its norm off fp64, in the
+// plain fp32 chain 3.8e-7).  The other five products are below 2^-8 of the leading one, and so are their sum's errors.
+struct Acc2 { v16f hi, lo; };
+__device__ __forceinline__ void mfma6(const v8bf (&a)[3], const v8bf (&b)[3], Acc2 &c)
+{
+    c.lo = mfma(a[2], b[0], c.lo);
+    c.hi = mfma(a[0], b[0], c.hi);
+    c.lo = mfma(a[0], b[2], c.lo);
+    c.lo = mfma(a[1], b[1], c.lo);
+    c.lo = mfma(a[1], b[0], c.lo);
+    c.lo = mfma(a[0], b[1], c.lo);
+}
+// ... where b is exact in one part
+__device__ __forceinline__ void mfma3(const v8bf (&a)[3], v8bf b, v16f &hi, v16f &lo)
+{
+    lo = mfma(a[2], b, lo);
+    hi = mfma(a[0], b, hi);
+    lo = mfma(a[1], b, lo);
+}
+// Sums of a's rows (bias gradients): the leading parts in column 0 of one accumulator, the others in column 1
+struct RowSum {
+    v8bf e0, e1;
+    v16f acc;
+    __device__ __forceinline__ explicit RowSum(int col) : acc{0}
+    {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { e0[e] = (__bf16)(col == 0 ? 1.0f : 0.0f); e1[e] = (__bf16)(col == 1 ? 1.0f : 0.0f); }
+    }
+    __device__ __forceinline__ void add(const v8bf (&a)[3])
+    {
+        acc = mfma(a[2], e1, acc);
+        acc = mfma(a[1], e1, acc);
+        acc = mfma(a[0], e0, acc);
+    }
+    __device__ __forceinline__ float row(int r) const { return acc[r] + __shfl_xor(acc[r], 1); }   // in columns 0 and 1, by all lanes
+};
 
 // ---------------------------------------------------------------------------
 // conv1, conv2 and conv3 forward in ONE launch.  A unit is the part of a sample that yields R3 of the seven
@@ -550,16 +589,14 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
     const int trow = 8 * h + (s16 >> 2), tcol = 16 * half + 4 * (s16 & 3);
     const bf16_t *yp = Ys + trow * LDY + wo * 32 * WM + tcol, *xp = Xs + trow * LDX + wk * 32 * WN + tcol;
     const bool do_bias = bx == 0 && wk == 0;
-    v16f acc[WM][WN], accb[WM];
+    Acc2 acc[WM][WN];
+    RowSum accb[WM] = {RowSum(li), RowSum(li)};
+    static_assert(WM == 2, "accb");
 #pragma unroll
     for (int a = 0; a < WM; ++a) {
-        accb[a] = v16f{0};
 #pragma unroll
-        for (int b = 0; b < WN; ++b) acc[a][b] = v16f{0};
+        for (int b = 0; b < WN; ++b) acc[a][b] = Acc2{v16f{0}, v16f{0}};
     }
-    v8bf ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
     if (mbeg < mend) gload(mbeg);
     for (int mb = mbeg; mb < mend; mb += BK) {
         if (mb != mbeg) sync_lds();
@@ -576,12 +613,8 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
 #pragma unroll
             for (int a = 0; a < WM; ++a) {
 #pragma unroll
-                for (int b = 0; b < WN; ++b) acc[a][b] = mfma6(fa[a], fb[b], acc[a][b]);
-                if (do_bias) {
-                    accb[a] = mfma(fa[a][2], ones, accb[a]);
-                    accb[a] = mfma(fa[a][1], ones, accb[a]);
-                    accb[a] = mfma(fa[a][0], ones, accb[a]);
-                }
+                for (int b = 0; b < WN; ++b) mfma6(fa[a], fb[b], acc[a][b]);
+                if (do_bias) accb[a].add(fa[a]);
             }
         }
     }
@@ -592,8 +625,11 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
         for (int r = 0; r < 16; ++r) {
             const int o = o0 + (wo * WM + a) * 32 + 8 * (r / 4) + 4 * h + (r % 4);
 #pragma unroll
-            for (int b = 0; b < WN; ++b) part[(long)o * G::K + kc0 + (wk * WN + b) * 32 + li] = acc[a][b][r];
-            if (do_bias && li == 0) part[(long)G::N * G::K + o] = accb[a][r];
+            for (int b = 0; b < WN; ++b) part[(long)o * G::K + kc0 + (wk * WN + b) * 32 + li] = acc[a][b].hi[r] + acc[a][b].lo[r];
+            if (do_bias) {   // uniform for the wave
+                const float v = accb[a].row(r);
+                if (li == 0) part[(long)G::N * G::K + o] = v;
+            }
         }
 }
 
@@ -684,10 +720,8 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
         reinterpret_cast<uint32_t *>(dys)[(W ? i / (W ? W : 1) : 0) * (G::PD / 2) + G::NPOS * G::LDY / 2 + (W ? i % (W ? W : 1) : 0)] = 0;
     }
 
-    v16f wacc[2] = {v16f{0}, v16f{0}}, accb = {0};
-    v8bf ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    v16f wacc[2] = {v16f{0}, v16f{0}};
+    RowSum accb(i32);
     const int cp = wave & 3;   // weight gradient: columns 64 cp .. (frame cp)
     const bool do_bias = cp == 0;
 
@@ -732,11 +766,11 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
         sync_lds();   // image and frames are complete
 
         // ---- conv2's input gradient
-        v16f acc[G::T];
+        Acc2 acc[G::T];
         const uint8_t *pa[G::T];
 #pragma unroll
         for (int t = 0; t < G::T; ++t) {
-            acc[t] = v16f{0};
+            acc[t] = Acc2{v16f{0}, v16f{0}};
             const int m = 32 * t + i32, mc = m < G::RA * 10 ? m : G::RA * 10 - 1, a = mc / 10, b = mc - 10 * a;
             pa[t] = img + ((a + 1 - kh) * 11 + b + 1) * 400 + h * 16;   // position (a - kh, b) of dY
         }
@@ -753,7 +787,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
             for (int pl = 0; pl < 3; ++pl) b3[pl] = nb[pl];
             if (i + 1 < 8 * G::T) load_b(i + 1);
             __builtin_amdgcn_sched_barrier(0);
-            acc[i % G::T] = mfma6(wa[i / G::T], b3, acc[i % G::T]);
+            mfma6(wa[i / G::T], b3, acc[i % G::T]);
             __builtin_amdgcn_sched_barrier(0);
         }
         // accumulator register 4g + r = channel 8g + 4h + r; the wave keeps g = 2 kh, 2 kh + 1 and hands over the others
@@ -762,8 +796,9 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
         for (int t = 0; t < G::T; ++t)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const v4f lo = {acc[t][4 * j], acc[t][4 * j + 1], acc[t][4 * j + 2], acc[t][4 * j + 3]};
-                const v4f hi = {acc[t][4 * j + 8], acc[t][4 * j + 9], acc[t][4 * j + 10], acc[t][4 * j + 11]};
+                const v16f s = acc[t].hi + acc[t].lo;
+                const v4f lo = {s[4 * j], s[4 * j + 1], s[4 * j + 2], s[4 * j + 3]};
+                const v4f hi = {s[4 * j + 8], s[4 * j + 9], s[4 * j + 10], s[4 * j + 11]};
                 own[t][j] = kh ? hi : lo;
                 scr[(((cls * 2 + (kh ^ 1)) * G::T + t) * 2 + j) * 64 + lane] = kh ? lo : hi;
             }
@@ -790,6 +825,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
             const int y = p / 20;
             return 336 * y + 4 * (p - 20 * y);
         };
+        v16f lo2[2] = {v16f{0}, v16f{0}};   // of this unit: see Acc2
 #pragma unroll
         for (int t2 = 0; t2 < (G::NKS + 1) / 2; ++t2) {
             const int t = 2 * t2 + kh;
@@ -805,14 +841,17 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
                 const v8s xb = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 fb[b] = __builtin_bit_cast(v8bf, xb);
             }
-#pragma unroll
-            for (int pl = 2; pl >= 0; --pl) {
-                wacc[0] = mfma(fa[pl], fb[0], wacc[0]);
-                wacc[1] = mfma(fa[pl], fb[1], wacc[1]);
-                if (do_bias) accb = mfma(fa[pl], ones, accb);
-            }
+            mfma3(fa, fb[0], wacc[0], lo2[0]);
+            mfma3(fa, fb[1], wacc[1], lo2[1]);
+            if (do_bias) accb.add(fa);
         }
+        wacc[0] += lo2[0];
+        wacc[1] += lo2[1];
     }
+    float bsum[16];
+    if (do_bias)   // uniform for the wave
+#pragma unroll
+        for (int r = 0; r < 16; ++r) bsum[r] = accb.row(r);
     // the odd steps join the even ones
     float *sf = reinterpret_cast<float *>(scr);
     float *part = A.part1 + (long)bid * (32 * 256 + 32);
@@ -824,7 +863,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
         if (do_bias && i32 == 0) {
             // (column 0 of the product with ones; conv1's dY is no longer read)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) reinterpret_cast<float *>(img)[16 * h + r] = accb[r];
+            for (int r = 0; r < 16; ++r) reinterpret_cast<float *>(img)[16 * h + r] = bsum[r];
         }
     }
     sync_lds();
@@ -838,7 +877,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
             }
         if (do_bias && i32 == 0) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) part[32 * 256 + 8 * (r / 4) + 4 * h + (r % 4)] = accb[r] + reinterpret_cast<float *>(img)[16 * h + r];
+            for (int r = 0; r < 16; ++r) part[32 * 256 + 8 * (r / 4) + 4 * h + (r % 4)] = bsum[r] + reinterpret_cast<float *>(img)[16 * h + r];
         }
     }
 }
