@@ -422,23 +422,31 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
     }
     return true;
 }
-// fp32 training: how many of the step's passes keep the order of summation of the fp32 matrix instruction, layer by
-// layer, instead of the split form (gemm_split.h)?
+// fp32 training: how many of the step's passes keep the order of summation of the fp32 matrix instruction instead
+// of the split form (gemm_split.h)?
 // The stored activations of the first pass (on s) are what the ReLU decisions of the backward pass are taken on.
 // About one pre-activation in ten million is zero to within the rounding of its sum, and falls the other
 // way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
-// one such decision moves a gradient by 1e-4 to 2e-3 of its norm (measured over 30 seeds at 64, 128 and 256: 4, 8
-// and 12 of them beyond 1e-4 after two steps, none of 300 at 32).  Larger batches therefore keep it for the first
-// pass, so that their results stay those of the plain fp32 chain; the passes over s', whose activations are
-// only values, take the split form.  At larger ones the last bits of those values reach a decision, or a draw, through
-// the updated parameters and priorities too (one of 30 seeds at 256, two of 20 at 1000): there every pass keeps it.
-// The first line lies where a sample no longer has two workgroups to itself.
-int native_passes(const dqn_ctx *c, int B) { return 2 * 3 * B <= c->num_cu ? 0 : B <= 128 ? 1 : 3; }
+// one such decision moves a gradient by 1e-4 to 7e-2 of its norm (batches of 32 and 42, 150 seeds each, first step with
+// the split form in every pass: 9 and 6 of them beyond 1e-4; with the first pass in this order 0, and 3 of 450 after
+// three steps).  Every batch therefore keeps it for the first pass, so that its results stay those of the plain fp32
+// chain; the passes over s', whose activations are only values, take the split form.  At larger ones the last bits of
+// those values reach a decision, or a draw, through the updated parameters and priorities too (one of 30 seeds at 256,
+// two of 20 at 1000): there every pass keeps it.
+int native_passes(const dqn_ctx *c, int B) { return B <= 128 ? 1 : 3; }
+// Small batches: the first pass's layers and the split form of the others as units of one launch
+// (sp::k_conv123_step), one workgroup per CU and one round: the others take at least two workgroups per sample, the first
+// pass four (27 us at a batch of 32, the step 85.2), or two where four no longer fit beside them (33 us at 42).  With the
+// first pass as three launches of its own the step took 107.8 us at 32.
+bool step_launch(const dqn_ctx *c, int B) { return 2 * 3 * B <= c->num_cu; }
+int step_native_rows(const dqn_ctx *c, int B) { return 8 * B <= c->num_cu ? 2 : 4; }   // rows of conv3 per unit
+int step_native_blocks(const dqn_ctx *c, int B) { return B * (step_native_rows(c, B) == 2 ? 4 : 2); }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not
 // (few compute units and a large batch), a sampling launch runs in front of the step.
 bool in_kernel_draw_fits(const dqn_ctx *c, int B)
 {
     if (c->cfg.precision == 0) {
+        if (step_launch(c, B)) return true;   // one unit per workgroup
         const int np = native_passes(c, B);
         return np == 3 ? conv1_plan_f32(3 * B, c->num_cu).draw_fits : conv123_plan((3 - np) * B, c->num_cu).draw_fits;
     }
@@ -479,9 +487,11 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
 
     // conv1, conv2 and conv3: one launch for the passes [p0, npass)
     const int p0 = npass == 3 ? native_passes(c, pass[0].n) : 0;
+    const bool step = npass == 3 && step_launch(c, pass[0].n);   // the first pass in the same launch
     if (p0 < npass) {
         const int samples = (int)(rows - row0[p0]);
-        const Conv123Plan plan = conv123_plan(samples, c->num_cu);
+        const int nat = step ? step_native_blocks(c, pass[0].n) : 0;
+        const Conv123Plan plan = conv123_plan(samples, c->num_cu - nat);
         if (draw && !plan.draw_fits)   // the caller asks in_kernel_draw_fits first
             return fail(c, DQN_ERR_INVALID_ARG, "forward: batch too large for in-kernel sampling");
         sp::Args A{};
@@ -499,13 +509,27 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         A.units = samples * plan.parts;
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
-        launch(c, "conv123_fwd", st, [&] {
+        if (step) {
+            const float *theta = theta_of(c, pass[0].net);
+            sp::StepArgs S{};
+            S.split = A;
+            S.nat = sp::NatArgs{gbf::c1::Src{pass[0].x, pass[0].xs, pass[0].idx, (long)c->cfg.replay_capacity, pass[0].shift, (int)c->sub},
+                                theta + net::C1W, theta + net::C1B, theta + net::C2W, theta + net::C2B, theta + net::C3W, theta + net::C3B,
+                                (float *)w.act1, (float *)w.act2, act3, 2 * (int)rows * gbf::c1::UNITS <= 4 * c->num_cu};
+            S.nat_blocks = nat;
+            const bool few = step_native_rows(c, pass[0].n) == 2;
+            launch(c, "conv123_fwd", st, [&] {
+                if (plan.r3 == 1) sp::k_conv123_step<1, 2><<<dim3(nat + plan.grid), 512, sp::step_lds<1, 2>(), st>>>(S);
+                else if (few) sp::k_conv123_step<4, 2><<<dim3(nat + plan.grid), 512, sp::step_lds<4, 2>(), st>>>(S);
+                else sp::k_conv123_step<4, 4><<<dim3(nat + plan.grid), 512, sp::step_lds<4, 4>(), st>>>(S);
+            });
+        } else launch(c, "conv123_fwd", st, [&] {
             if (plan.r3 == 1) sp::k_conv123_fwd<1><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
             else if (plan.r3 == 4) sp::k_conv123_fwd<4><<<dim3(plan.grid), 512, sp::Geo<4>::LDS, st>>>(A);
             else sp::k_conv123_fwd<7><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
         });
     }
-    if (p0 > 0) {   // the passes [0, p0), layer by layer
+    if (p0 > 0 && !step) {   // the passes [0, p0), layer by layer
         const long n0 = row0[p0 - 1] + pass[p0 - 1].n;   // their samples
         float *act1 = (float *)w.act1, *act2 = (float *)w.act2;
         gbf::c1::FwdArgsF F{};
@@ -909,7 +933,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 });
             }
         }
-        if (native_passes(c, B) == 0) {
+        if (step_launch(c, B)) {
             // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample
             // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient
             const int nps = std::min({BACK_PARTS * B, std::max(1, c->num_cu * 5 / 8), MAX_WSPLIT1});
@@ -1197,6 +1221,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         // the launches of the conv layers hold images in LDS
         if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
             hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
+            hipFuncSetAttribute((const void *)sp::k_conv123_step<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<1, 2>()) != hipSuccess ||
+            hipFuncSetAttribute((const void *)sp::k_conv123_step<4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<4, 2>()) != hipSuccess ||
+            hipFuncSetAttribute((const void *)sp::k_conv123_step<4, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<4, 4>()) != hipSuccess ||
             hipFuncSetAttribute((const void *)sp::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<7>::LDS) != hipSuccess) {
             (void)hipGetLastError();
             delete c;

@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gemm_bf16.h"
 #include "gemm_fp32.h"
 #include "net.h"
@@ -181,17 +183,16 @@ __device__ __forceinline__ void reduce_quarters(const v16f (&acc)[T], v4f (&own)
         for (int t = 0; t < T; ++t) own[t] += scratch[(((kq * 3 + j) * 2 + ch) * T + t) * 64 + lane];
 }
 
+// Workgroup bid of G0; the kernel's arguments begin with A.
 template <int R3>
-__global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
+__device__ __forceinline__ void conv123_body(const Args &A, const int bid, const int G0, uint8_t *lds)
 {
     // The segments are indexed at run time; through the by-value structure that would be a copy in scratch
     // memory, or a select over three times fifteen scalars.  The arguments themselves lie in constant memory.
     typedef const __attribute__((address_space(4))) Args *ArgsPtr;
     const ArgsPtr AP = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
 #define SP_SEG(s) (AP->seg[s])
-    const Args &A = A_by_value;
     using G = Geo<R3>;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     uint8_t *pxb = lds, *img1 = lds + G::PXB;
     bf16_t *px = reinterpret_cast<bf16_t *>(pxb);
     uint8_t *img2 = pxb;
@@ -203,8 +204,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
     const int nt = wave & 1, tg = wave >> 1;      // conv1
     const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
     int tid = threadIdx.x, lane = tid & 63;
-    const int G0 = (int)gridDim.x;
-    const int nu = G::MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
+    const int nu = G::MANY ? (A.units - bid + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
 
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
     v8bf w1[8][3];
@@ -232,18 +232,14 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         }
     };
 
-    int u = (int)blockIdx.x;
+    int u = bid;
     int si = seg_of(u);
     const bool ring = A.seg[0].src.idx != nullptr;   // of every segment, or of none
-    // What the first loads need of the segment, picked from the arguments without a second, dependent trip to
-    // constant memory
-    const uint8_t *x0 = A.seg[0].src.x;
-    const bf16_t *wf = A.seg[0].w;
-    long xs0 = A.seg[0].src.xs;
-    int shift0 = A.seg[0].src.shift, first0 = A.seg[0].first;
-#pragma unroll
-    for (int q = 1; q < 3; ++q)
-        if (si == q) { x0 = A.seg[q].src.x; wf = A.seg[q].w; xs0 = A.seg[q].src.xs; shift0 = A.seg[q].src.shift; first0 = A.seg[q].first; }
+    // (scalar loads: a select over the three segments' arguments became a table in scratch memory)
+    const uint8_t *x0 = SP_SEG(si).src.x;
+    const bf16_t *wf = SP_SEG(si).w;
+    const long xs0 = SP_SEG(si).src.xs;
+    const int shift0 = SP_SEG(si).src.shift, first0 = SP_SEG(si).first;
     // The first pixels before the weights, which are twenty times as many bytes, where their slot is known; drawing
     // comes first otherwise, with the weights on their way
     if (!ring) load_px(x0, xs0, shift0, first0, u, 0);
@@ -468,7 +464,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         // the next unit's pixels
         // (behind the last unit: its own once more, so that the registers are written on every path and do not
         // have to keep their old contents until here)
-        const int kn = k + 1 < nu ? k + 1 : k, un = (int)blockIdx.x + kn * G0, sn = seg_of(un);
+        const int kn = k + 1 < nu ? k + 1 : k, un = bid + kn * G0, sn = seg_of(un);
         const bf16_t *const wn = SP_SEG(sn).w;
         if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, ring ? slots[kn] : 0);
         sync_lds();
@@ -527,6 +523,344 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A_by_value)
         u += G0;
     }
 #undef SP_SEG
+}
+
+template <int R3>
+__global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    conv123_body<R3>(A, (int)blockIdx.x, (int)gridDim.x, lds);
+}
+
+// ---------------------------------------------------------------------------
+// The same three layers of the pass on s of a training step, in the order of summation that the layers' own launches
+// have (gbf::c1::k_conv1_fwd_f32, g32::k_fwd): its stored activations are what the backward pass takes its ReLU
+// decisions on, and a decision on a pre-activation that is zero to within the rounding of its sum falls by the
+// order of that sum.  In the split form one batch of 32 in thirty had a decision fall the other way and its gradient
+// 1e-4 to 7e-2 of its norm off; in this order the activations are those launches' bit for bit.
+// Beside the passes over s' (conv123_body) in one launch: a unit, R3 rows of conv3's output, has a compute unit to itself,
+// and with R3 = 2 it takes about as long as theirs: 24 us alone, 27 beside 64 samples of s' (20 us).  Bound by the fp32
+// matrix pipe (16x16x4: 32 cycles for 1024 products, 31,200 cycles for R3 = 2) and the round trips between the layers.  Of
+// the first form's 32 us, 5 were weights that all waves asked for at once: conv1's now go through LDS, conv2's are
+// requested behind the first tile, conv3's three at a time beside conv2's steps.  16-wide tiles waste a quarter of conv2's
+// and an eighth of conv3's work where 32-wide ones waste almost half.
+//   conv1   wave = (channel half, every fourth tile of 16 positions); the pixels lie in LDS as floats
+//   conv2   wave = (channel half, kernel column), rows in order; then the four columns' sums in order
+//   conv3   twelve tiles (16 channels, every third 32 of the reduction) over eight waves, three sums in order
+// A 32x32x2 instruction of those launches adds products k and k + 4 of eight; the four of a 16x16x4 one are therefore
+// k = 0, 4, 1, 5, then 2, 6, 3, 7: the images hold sixteen channels in that order (a lane's share is 16 bytes), the
+// weights, sixteen natural bytes per lane, are brought into it by exchanging halves of registers.
+// ---------------------------------------------------------------------------
+struct NatArgs {
+    gbf::c1::Src src;
+    const float *w1, *b1, *w2, *b2, *w3, *b3;
+    float *y1, *y2, *y3;
+    int halves;   // conv1 sums frames 0-1 and 2-3 apart
+};
+struct StepArgs {
+    Args split;   // the passes over s'
+    NatArgs nat;
+    int nat_blocks;
+};
+template <int R3> struct NatGeo {
+    static constexpr int PARTS = (7 + R3 - 1) / R3;
+    static constexpr int R2 = R3 + 2, R1 = 2 * R3 + 6, PR = 4 * R1 + 4;   // rows of conv2, conv1, pixels
+    static constexpr int M1 = R1 * 20, M2 = R2 * 9, M3 = R3 * 7;
+    static constexpr int T1 = (M1 + 15) / 16, T2 = (M2 + 15) / 16, T3 = (M3 + 15) / 16;
+    static constexpr int CH = PR * 84 / 16, NPX = (4 * CH + 511) / 512;
+    static constexpr int P1 = 36, P2 = 68;                                // pixel pitch of the images in floats
+    static constexpr int PXB = 4 * PR * 84 * 4, I1B = M1 * P1 * 4, I2B = M2 * P2 * 4, LDS = PXB + I1B + I2B + 16;
+    static_assert(PR * 84 % 16 == 0 && 16 * T2 * 1024 <= PXB && 12 * T3 * 1024 <= PXB, "LDS layout");
+    static_assert(I1B + I2B >= 32 * 1024, "conv1's weights");
+    static_assert(4 * T3 <= 8, "one finishing tile of conv3 per wave");
+};
+
+using gbf::c1::mfma4;
+// channels 4 kg .. 4 kg + 3 of sixteen -> this lane's share in the order above
+__device__ __forceinline__ v4f lane_share(v4f w)
+{
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.x), __float_as_uint(w.y), false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.z), __float_as_uint(w.w), false, false);
+    return v4f{__uint_as_float(p[0]), __uint_as_float(q[0]), __uint_as_float(p[1]), __uint_as_float(q[1])};
+}
+// channels 4 kg .. + 3 of a position -> the image's sixteen
+__device__ __forceinline__ void put_share(float *d, int kg, v4f v)
+{
+    float *e = d + (kg & 1) * 4 + (kg >> 1) * 2;
+    *reinterpret_cast<float2 *>(e) = float2{v.x, v.z};
+    *reinterpret_cast<float2 *>(e + 8) = float2{v.y, v.w};
+}
+
+template <int R3>
+__device__ __forceinline__ void conv123_native_body(const NatArgs &A, const bool draw, const misc::SampleArgs &samp, const int bid, uint8_t *lds)
+{
+    using G = NatGeo<R3>;
+    float *px = reinterpret_cast<float *>(lds), *img1 = reinterpret_cast<float *>(lds + G::PXB);
+    float *img2 = reinterpret_cast<float *>(lds + G::PXB + G::I1B);
+    int *slot_tab = reinterpret_cast<int *>(lds + G::PXB + G::I1B + G::I2B);
+    v4f *scratch = reinterpret_cast<v4f *>(lds);   // the pixels' place, behind conv1
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = bid / G::PARTS, part = bid % G::PARTS;
+    const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
+    const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
+
+    u32x4 raw[G::NPX];
+    auto load_px = [&](int slot) {
+        const uint8_t *f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = gbf::c1::frame_ptr(A.src, g, slot, k) + row0 * (8 * 84);
+#pragma unroll
+        for (int i = 0; i < G::NPX; ++i) {
+            int t = tid + 512 * i;
+            if (t > 4 * G::CH - 1) t = 4 * G::CH - 1;
+            const int k = t / G::CH;
+            const uint8_t *fp = k == 0 ? f[0] : k == 1 ? f[1] : k == 2 ? f[2] : f[3];
+            raw[i] = *reinterpret_cast<const u32x4 *>(fp + (t - k * G::CH) * 16);
+        }
+    };
+    const bool ring = A.src.idx != nullptr;
+    if (!ring) load_px(0);
+    const int nt = wave & 1, tg = wave >> 1;
+    // conv1's weights, an eighth per wave: fragment f = channel half f / 16; frame and kernel rows of pair f % 16 / 2,
+    // columns 4 (f % 2) ..; through LDS to the four waves that want them
+    v4f w1s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int f = 4 * wave + q, s = (f >> 1) & 7;
+        w1s[q] = *reinterpret_cast<const v4f *>(A.w1 + (16 * (f >> 4) + n) * 256 + (s >> 1) * 64 + (4 * (s & 1) + kg) * 8 + 4 * (f & 1));
+    }
+    const v4f bias1 = *reinterpret_cast<const v4f *>(A.b1 + 16 * nt + 4 * kg);
+    const v4f bias2 = *reinterpret_cast<const v4f *>(A.b2 + 16 * (wave & 3) + 4 * kg);
+    const v4f bias3 = *reinterpret_cast<const v4f *>(A.b3 + 16 * (wave & 3) + 4 * kg);
+    if (ring) {
+        if (draw) {
+            if (wave == 0) {
+                const int jj[2] = {g, g};
+                long sl[2];
+                float leaf[2];
+                misc::per_sample_walk<2>(samp, jj, lane, sl, leaf);
+                if (lane == 0) slot_tab[0] = (int)sl[0];
+            }
+            sync_lds();
+            load_px(slot_tab[0]);
+        } else {
+            load_px(A.src.idx[g]);
+        }
+    }
+    const int ch = wave & 1, kq = wave >> 1;
+    v4f *wl = reinterpret_cast<v4f *>(img1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wl[(4 * wave + q) * 64 + lane] = w1s[q];
+#pragma unroll
+    for (int i = 0; i < G::NPX; ++i) {
+        const int t = tid + 512 * i;
+        if (t < 4 * G::CH) {
+            v4f *d = reinterpret_cast<v4f *>(px + t * 16);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = g32::cvt4((uint32_t)raw[i][j]);
+        }
+    }
+    sync_lds();
+    v4f w1[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) w1[q] = wl[(16 * nt + q) * 64 + lane];
+    sync_lds();   // the weights' place is conv1's image from here on
+
+    // ---- conv1
+    auto conv1_tile = [&](int t) {
+        const int m = 16 * t + n, mc = m < G::M1 ? m : G::M1 - 1, y = mc / 20, x = mc - 20 * y;
+        const float *p = px + (4 * y + kg) * 84 + 4 * x;
+        v4f acc = {0, 0, 0, 0}, first = {0, 0, 0, 0}, b[2], nb[2];
+        auto load_b = [&](int s) {
+            const float *q = p + (s >> 1) * (G::PR * 84) + (s & 1) * (4 * 84);
+            nb[0] = *reinterpret_cast<const v4f *>(q);
+            nb[1] = *reinterpret_cast<const v4f *>(q + 4);
+        };
+        load_b(0);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            b[0] = nb[0];
+            b[1] = nb[1];
+            if (s < 7) load_b(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s == 4 && A.halves) {
+                first = acc;
+                acc = v4f{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc = mfma4(w1[2 * s + (e >> 2)][e & 3], b[e >> 2][e & 3], acc);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (A.halves) acc = first + acc;
+        constexpr float sc = 1.0f / 255.0f;
+        v4f v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[r] * sc + bias1[r], 0.f);
+        if (m < G::M1) {
+            put_share(img1 + m * G::P1 + 16 * nt, kg, v);
+            if (2 * row0 + y >= 2 * rowp + G::R1)
+                *reinterpret_cast<v4f *>(A.y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 16 * nt + 4 * kg) = v;
+        }
+    };
+    conv1_tile(tg);
+    __builtin_amdgcn_sched_barrier(0);
+    v4f w2[8][2];   // step s: kernel row s / 2, channels 16 (s % 2) ..
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+            w2[s][c] = *reinterpret_cast<const v4f *>(A.w2 + (32 * ch + 16 * c + n) * 512 + (s >> 1) * 128 + kq * 32 + 16 * (s & 1) + 4 * kg);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+    for (int t = tg + 4; t < G::T1; t += 4) conv1_tile(t);
+    sync_lds();
+
+    // ---- conv2: kernel column kq
+    // conv3's: [c][s] = slice c ? 2 : wave / 4, step s: products 32 (3 (s / 2) + slice) + 16 (s % 2) .. of channels
+    // 16 (wave % 4) ..; requested three at a time beside conv2's steps
+    v4f w3[2][12];
+    const float *p3 = A.w3 + (16 * (wave & 3) + n) * 576 + 4 * kg;
+    auto load_w3 = [&](int c, int s) { w3[c][s] = *reinterpret_cast<const v4f *>(p3 + 32 * (c ? 2 : wave >> 2) + 96 * (s >> 1) + 16 * (s & 1)); };
+    {
+        constexpr int T = G::T2;
+        const float *pa[T];
+        v4f acc[T][2];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            int m = 16 * t + n;
+            if (m > G::M2 - 1) m = G::M2 - 1;
+            const int y = m / 9, x = m - 9 * y;
+            pa[t] = img1 + (40 * y + 2 * x + kq) * G::P1 + 4 * kg;
+            acc[t][0] = acc[t][1] = v4f{0, 0, 0, 0};
+        }
+        v4f b[T], nb[T];
+        auto load_b = [&](int s) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) nb[t] = *reinterpret_cast<const v4f *>(pa[t] + (s >> 1) * (20 * G::P1) + 16 * (s & 1));
+        };
+        load_b(0);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) b[t] = nb[t];
+            if (s < 7) load_b(s + 1);
+#pragma unroll
+            for (int q = 3 * s; q < 3 * s + 3; ++q) load_w3(q / 12, q % 12);
+            const v4f wa = lane_share(w2[s][0]), wb = lane_share(w2[s][1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    acc[t][0] = mfma4(wa[e], b[t][e], acc[t][0]);
+                    acc[t][1] = mfma4(wb[e], b[t][e], acc[t][1]);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) scratch[((kq * 4 + 2 * ch + c) * T + t) * 64 + lane] = acc[t][c];
+        sync_lds();
+#pragma unroll
+        for (int t = wave >> 2; t < T; t += 2) {   // channels 16 (wave % 4) .., every other tile
+            v4f sum = scratch[((wave & 3) * T + t) * 64 + lane];
+#pragma unroll
+            for (int k = 1; k < 4; ++k) sum += scratch[((k * 4 + (wave & 3)) * T + t) * 64 + lane];
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(sum[r] + bias2[r], 0.f);
+            const int m = 16 * t + n;
+            if (m < G::M2) {
+                put_share(img2 + m * G::P2 + 16 * (wave & 3), kg, v);
+                if (row0 + m / 9 >= rowp + G::R2)
+                    *reinterpret_cast<v4f *>(A.y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + 16 * (wave & 3) + 4 * kg) = v;
+            }
+        }
+    }
+    sync_lds();
+
+    // ---- conv3: a slice is 32 products of every 96
+    {
+        constexpr int T = G::T3;
+        const float *pa[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            int m = 16 * t + n;
+            if (m > G::M3 - 1) m = G::M3 - 1;
+            const int y = m / 7, x = m - 7 * y;
+            pa[t] = img2 + (9 * y + x) * G::P2 + 4 * kg;
+        }
+        auto slices = [&](auto count) {
+            constexpr int C = decltype(count)::value;
+            v4f acc[C][T], b[C][T], nb[C][T];
+            auto load_b = [&](int s) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int j = 3 * (s >> 1) + (c ? 2 : wave >> 2), tap = j >> 1;
+                    const int off = ((tap / 3) * 9 + tap % 3) * G::P2 + 32 * (j & 1) + 16 * (s & 1);
+#pragma unroll
+                    for (int t = 0; t < T; ++t) nb[c][t] = *reinterpret_cast<const v4f *>(pa[t] + off);
+                }
+            };
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[c][t] = v4f{0, 0, 0, 0};
+            load_b(0);
+#pragma unroll
+            for (int s = 0; s < 12; ++s) {
+                v4f wa[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+#pragma unroll
+                    for (int t = 0; t < T; ++t) b[c][t] = nb[c][t];
+                    wa[c] = lane_share(w3[c][s]);
+                }
+                if (s < 11) load_b(s + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+#pragma unroll
+                        for (int t = 0; t < T; ++t) acc[c][t] = mfma4(wa[c][e], b[c][t][e], acc[c][t]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int t = 0; t < T; ++t) scratch[(((c ? 2 : wave >> 2) * 4 + (wave & 3)) * T + t) * 64 + lane] = acc[c][t];
+        };
+        // waves 0-3: slices 0 and 2, waves 4-7: slice 1, so that every SIMD has three of the twelve
+        if (wave < 4) slices(std::integral_constant<int, 2>{});
+        else slices(std::integral_constant<int, 1>{});
+        sync_lds();
+        const int t = wave >> 2;
+        if (t < T) {
+            v4f sum = scratch[((wave & 3) * T + t) * 64 + lane];
+#pragma unroll
+            for (int k = 1; k < 3; ++k) sum += scratch[((k * 4 + (wave & 3)) * T + t) * 64 + lane];
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(sum[r] + bias3[r], 0.f);
+            const int m = 16 * t + n;
+            if (m < G::M3 && row0 + m / 7 >= rowp + R3)
+                *reinterpret_cast<v4f *>(A.y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + 16 * (wave & 3) + 4 * kg) = v;
+        }
+    }
+}
+
+// The forward conv layers of a training step's three passes: workgroups [0, nat_blocks) take parts of s, the others of s'.
+template <int R3, int RN> constexpr int step_lds() { return Geo<R3>::LDS > NatGeo<RN>::LDS ? Geo<R3>::LDS : NatGeo<RN>::LDS; }
+template <int R3, int RN>
+__global__ __launch_bounds__(512, 1) void k_conv123_step(StepArgs A)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int bid = (int)blockIdx.x;
+    if (bid < A.nat_blocks) conv123_native_body<RN>(A.nat, A.split.draw, A.split.samp, bid, lds);
+    else conv123_body<R3>(A.split, bid - A.nat_blocks, (int)gridDim.x - A.nat_blocks, lds);
 }
 
 // ---------------------------------------------------------------------------
