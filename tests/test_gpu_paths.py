@@ -1,0 +1,116 @@
+"""The launches chosen by size (rows per compute unit, parts of a sample, bands of a frame), at the sizes where a rule
+turns or a tile ends: against the oracle, or bit for bit against another path that must give the same.  Helpers and
+tolerances are those of test_gpu_parity.py.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_1804_05834_amd import synth
+from test_gpu_parity import (CONFIGS, TOL, TOL_BF16, _check_indices, _replay_step_case, check_argmax, dev, dq, relerr)  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+# fp32: parts of 1, 4 and 7 rows per workgroup up to 36, 128 and any number of samples; several samples per workgroup
+# above 256.  bf16: one launch for three layers up to 512; fc1 for few rows in 32-row tiles, 64 wide up to 128 rows;
+# the head shared by four rows per workgroup from 1024 rows on
+@pytest.mark.parametrize("E,K,prec", [(36, 6, 0), (37, 6, 0), (128, 18, 0), (129, 18, 0), (257, 3, 0),
+                                      (36, 6, 1), (37, 33, 1), (128, 18, 1), (129, 18, 1), (256, 4, 1), (257, 4, 1),
+                                      (512, 18, 1), (513, 18, 1), (1023, 18, 1), (1024, 33, 1), (1027, 1, 1)])
+def test_act_where_the_launches_change(dq, orc, E, K, prec):
+    print("case act", E, K, prec, flush=True)
+    tol = TOL_BF16 if prec else TOL
+    m = dq.Dqn(dq.make_config(num_actions=K, dueling=1, max_act_batch=E, precision=prec))
+    p = synth.he_uniform_params(3 + K, K, 1, bias_scale=0.05)
+    m.set_params(0, torch.from_numpy(p))
+    obs = synth.states(31, E)
+    a, q = m.act(dev(obs), 0.0, 99, want_q=True)
+    q, ref = q.cpu().numpy(), orc.forward(p, K, 1, obs.numpy(), quant=prec)
+    # row by row, so that none hides behind the largest; with one action a row has a single value, which may lie
+    # near zero while the sums behind it do not: the scale of such a row is that of all values (their rms)
+    scale = np.maximum(np.abs(ref).max(axis=1), np.sqrt(np.mean(ref ** 2)))
+    assert np.all(np.abs(q - ref).max(axis=1) <= tol * scale)
+    check_argmax(a.cpu().numpy(), ref, tol)
+    m.close()
+
+
+# fp32 steps: parts of the samples of s' are 1 row up to 14, 4 rows above; those of s are 2 rows up to 32, 4 rows above;
+# conv1 sums its frames in two halves up to 34; one launch for the conv layers up to 42, layers of s apart up to 128
+@pytest.mark.parametrize("B", [14, 15, 34, 35, 42, 43, 128, 129])
+def test_fp32_step_where_the_launches_change(dq, orc, B):
+    print("case fp32 step", B, flush=True)
+    _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41)
+
+
+@pytest.mark.parametrize("prec,B", [(1, 31), (1, 85), (1, 86), (1, 170), (1, 171)])
+def test_bf16_step_where_the_launches_change(dq, orc, prec, B):
+    """bf16: one launch for the conv layers up to 85 (256 samples of three passes), the large fc1 tiles from 512 rows on."""
+    print("case bf16 step", B, flush=True)
+    _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41, tol=TOL_BF16, prec=1)
+
+
+@pytest.mark.parametrize("n", [35, 42])
+def test_fp32_step_activations_are_those_of_the_separate_launches(dq, n):
+    """A batch of 43 runs the layers of s as launches of their own, its first n rows alone as units of one launch: the
+    stored activations, which the ReLU decisions are taken on, must have the same bits."""
+    print("case activations", n, flush=True)
+    K = 18
+    batch = tuple(dev(t) for t in synth.batch(11, 43, K))
+    acts = []
+    for B in (43, n):
+        m = dq.Dqn(dq.make_config(max_batch=B, seed=7, **CONFIGS["dueling_ddqn"]))
+        m.train_step(B, tuple(t[:B].contiguous() for t in batch))
+        acts.append([m.get_activations(layer, n) for layer in (1, 2, 3)])
+        m.close()
+    for layer, (x, y) in enumerate(zip(*acts)):
+        assert torch.equal(x, y), layer + 1
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 8193])
+def test_tree_build_at_block_edges(dq, orc, n):
+    print("case tree build", n, flush=True)
+    m = dq.Dqn(dq.make_config(replay_capacity=9000))
+    p = synth.exp_priorities(9, n)
+    for _ in range(2):   # the second build finds the arrival counter as the first left it
+        m.per_fill(dev(p))
+        ref = orc.tree_build(p.numpy(), m.L, float(np.float32(0.6)))
+        assert np.array_equal(m.tree.cpu().numpy()[1:], ref[1:])
+    for B in (1, 5, 1023):
+        idx, w = m.per_sample(B, 0.4, 4242)
+        idx_ref, w_ref = _check_indices(orc, idx.cpu().numpy(), ref, n, B, 0.4, 4242)
+        same = idx.cpu().numpy() == idx_ref
+        assert same.mean() > 0.99 and relerr(w.cpu().numpy()[same], w_ref[same]) <= TOL
+    m.close()
+
+
+@pytest.mark.parametrize("cap", [16, 31, 1028])
+def test_store_at_the_edges_of_the_ring(dq, orc, cap):
+    """Rings that a call nearly fills, and runs that end, begin and wrap at the ring's last slot."""
+    print("case store", cap, flush=True)
+    m = dq.Dqn(dq.make_config(replay_capacity=cap))
+    ref = orc.ReplayState(cap, float(np.float32(0.6)))
+    pos, most = 0, min(1020, cap - 8)
+    for n in (1, most, 1, 7, most, most, 2, cap % 7 + 1, most):
+        fr = synth.frames(21, torch.arange(pos, pos + n, device="cuda"), device="cuda")
+        d = synth.dones(42, n, 0.05, "cuda", first=pos)
+        m.replay_store(fr, synth.actions(40, n, 18, "cuda", first=pos), synth.rewards(41, n, "cuda", first=pos), d)
+        ref.store(d.cpu().numpy())
+        pos += n
+        assert np.array_equal(m.tree.cpu().numpy()[1:], ref.tree[1:]), pos
+        assert m.replay_state() == (pos % cap, min(pos, cap), pos)
+    m.close()
+
+
+# bands of a frame; widths that leave every row at another alignment; a frame too tall for LDS; the smallest
+@pytest.mark.parametrize("n,H,W", [(1, 210, 160), (3, 210, 161), (300, 97, 37), (2, 336, 640), (2, 337, 100), (5, 1, 1), (2, 83, 1)])
+def test_preprocess_shapes(dq, orc, n, H, W):
+    print("case preprocess", n, H, W, flush=True)
+    raw = (synth.u24(61, torch.arange(n * H * W)) * 256).floor().clamp(max=255).to(torch.uint8).reshape(n, H, W)
+    lut = (255.0 * synth.u24(62, torch.arange(256))).float()
+    for table in (lut, None):
+        out = dq.preprocess(raw.cuda(), None if table is None else table.cuda()).cpu().numpy()
+        ref, val = orc.preprocess(raw.numpy(), None if table is None else table.numpy())
+        diff = out.astype(np.int32) - ref.astype(np.int32)
+        near = np.abs(val - np.floor(val) - 0.5) <= 1e-3   # (as in test_preprocess_parity)
+        assert np.all(diff[~near] == 0) and np.all(np.abs(diff) <= 1)
