@@ -427,9 +427,8 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 // The stored activations of the first pass (on s) are what the ReLU decisions of the backward pass are taken on.
 // About one pre-activation in ten million is zero to within the rounding of its sum, and falls the other
 // way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
-// one such decision moves a gradient by 1e-4 to 7e-2 of its norm (batches of 32 and 42, 150 seeds each, first step with
-// the split form in every pass: 9 and 6 of them beyond 1e-4; with the first pass in this order 0, and 3 of 450 after
-// three steps).  Every batch therefore keeps it for the first pass, so that its results stay those of the plain fp32
+// one such decision moves a gradient by 1e-4 to 7e-2 of its norm (first steps with the split form in every pass: 9 of 300
+// at 32 and 6 of 150 at 42 beyond 1e-4; with the first pass in this order 0 of them, and 2 after three steps).  Every batch therefore keeps it for the first pass, so that its results stay those of the plain fp32
 // chain; the passes over s', whose activations are only values, take the split form.  At larger ones the last bits of
 // those values reach a decision, or a draw, through the updated parameters and priorities too (one of 30 seeds at 256,
 // two of 20 at 1000): there every pass keeps it.
@@ -565,12 +564,13 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
         FwdArgs A{};
         const int ns = fc1_splits(rows);
-        int tiles = build(A, npass, 32, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
+        const bool few = rows <= 192;
+        int tiles = build(A, npass, few ? 32 : 64, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
                           net::F1B, w.f1part, net::HID, false);
         A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
         // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well
-        if (rows <= 192) launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); });
-        else launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 64><<<dim3(tiles, 8, ns), 128, 0, st>>>(A); });
+        if (few) launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); });
+        else launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 64, 64><<<dim3(tiles, 8, ns), 256, 0, st>>>(A); });
         *nsplit_out = ns;
         *split_stride_out = rows * net::HID;
     }

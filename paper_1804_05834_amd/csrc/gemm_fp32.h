@@ -34,6 +34,13 @@ __device__ __forceinline__ v16f mfma(float a, float b, v16f c)
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
+// A barrier that waits for the wave's LDS operations only: the loads of the stages ahead stay in flight
+__device__ __forceinline__ void sync_lds()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+}
+
 __device__ __forceinline__ v4f ld4(const float *p) { return *reinterpret_cast<const v4f *>(p); }
 // Four input elements as they lie in memory, and their conversion: a staging register holds the raw form,
 // so that nothing waits for a load before the tile of the stage before has been multiplied
@@ -156,8 +163,10 @@ __global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_fwd(FwdArgs
     constexpr int NA = BM * CPR / T, NB = BN * CPR / T;
     static_assert(NA * T == BM * CPR && NB * T == BN * CPR && G::K % BKS == 0, "tile/threads mismatch");
     static_assert((BM + BN) * LD >= (KS - 1) * NWT * 1024, "reduction scratch does not fit the tiles");
+    // Without slices: two buffers and one barrier per stage, the loads two stages ahead (see wgrad_tile)
+    constexpr int NBUF = KS == 1 ? 2 : 1, STAGE = (BM + BN) * LD;
     using in_t = typename G::in_t;
-    __shared__ __attribute__((aligned(16))) float smem[(BM + BN) * LD];
+    __shared__ __attribute__((aligned(16))) float smem[NBUF * (BM + BN) * LD];
     float *As = smem, *Bs = smem + BM * LD;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -175,23 +184,23 @@ __global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_fwd(FwdArgs
     long aoff[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        int m = m0 + lr + i * RPP;
-        aoff[i] = m < S.M ? G::row_off(m, S.xs) : -1;
+        const int m = m0 + lr + i * RPP;
+        aoff[i] = G::row_off(m < S.M ? m : S.M - 1, S.xs);   // (rows past the last one are not stored)
     }
     v4f ra[NA], rb[NB];
     auto gload = [&](int k0) {
         const int ko = G::k_off(k0 + kq);
 #pragma unroll
-        for (int i = 0; i < NA; ++i) ra[i] = aoff[i] >= 0 ? ld4(x + aoff[i] + ko) : v4f{0, 0, 0, 0};
+        for (int i = 0; i < NA; ++i) ra[i] = ld4(x + aoff[i] + ko);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             rb[i] = ld4(S.w + (long)(n0 + lr + i * RPP) * G::K + k0 + kq);
     };
-    auto sstore = [&]() {
+    auto sstore = [&](int at) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) *reinterpret_cast<v4f *>(&As[(lr + i * RPP) * LD + kq]) = ra[i];
+        for (int i = 0; i < NA; ++i) *reinterpret_cast<v4f *>(&As[at + (lr + i * RPP) * LD + kq]) = ra[i];
 #pragma unroll
-        for (int i = 0; i < NB; ++i) *reinterpret_cast<v4f *>(&Bs[(lr + i * RPP) * LD + kq]) = rb[i];
+        for (int i = 0; i < NB; ++i) *reinterpret_cast<v4f *>(&Bs[at + (lr + i * RPP) * LD + kq]) = rb[i];
     };
 
     const int ks = wave / NWT, w2 = wave % NWT;
@@ -203,24 +212,42 @@ __global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_fwd(FwdArgs
     const int col = n0 + wn * 32 + li;
     const float bias = S.bias ? S.bias[col] : 0.f;   // requested here, used in the epilogue
 
-    gload(kbeg);
-    sstore();
-    __syncthreads();
-    for (int k0 = kbeg; k0 < kend; k0 += BKS) {
-        const bool more = k0 + BKS < kend;
-        if (more) gload(k0 + BKS);
+    auto compute = [&](int at) {
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 8) {
-            v4f a = ld4(ap + kk), b = ld4(bp + kk);
+            v4f a = ld4(ap + at + kk), b = ld4(bp + at + kk);
             acc = mfma(a.x, b.x, acc);
             acc = mfma(a.y, b.y, acc);
             acc = mfma(a.z, b.z, acc);
             acc = mfma(a.w, b.w, acc);
         }
+    };
+    gload(kbeg);
+    sstore(0);
+    if constexpr (NBUF == 2) {
+        if (kbeg + BKS < kend) gload(kbeg + BKS);
+        sync_lds();
+        int at = 0;
+        for (int k0 = kbeg; k0 < kend; k0 += BKS) {
+            if (k0 + BKS < kend) {
+                sstore(STAGE - at);
+                if (k0 + 2 * BKS < kend) gload(k0 + 2 * BKS);
+            }
+            compute(at);
+            sync_lds();
+            at = STAGE - at;
+        }
+    } else {
         __syncthreads();
-        if (more) {
-            sstore();
+        for (int k0 = kbeg; k0 < kend; k0 += BKS) {
+            const bool more = k0 + BKS < kend;
+            if (more) gload(k0 + BKS);
+            compute(0);
             __syncthreads();
+            if (more) {
+                sstore(0);
+                __syncthreads();
+            }
         }
     }
     reduce_slices<NWT, KS>(acc, smem, ks, w2, lane);
@@ -273,7 +300,7 @@ struct DgradArgs {
 };
 
 // LDS floats of an input-gradient tile
-template <int BM, int BN, int KS> constexpr int dgrad_lds() { return BM * (BK * KS + 4) + BK * KS * (BN + 4); }
+template <int BM, int BN, int KS> constexpr int dgrad_lds() { return (KS == 1 ? 2 : 1) * (BM * (BK * KS + 4) + BK * KS * (BN + 4)); }
 
 // Tile number t of a grid of (gx, gy, gz) tiles, computed by the first (BM/32)(BN/32) KS waves of
 // the workgroup (a launch may hold wider workgroups: the waves beyond leave at once; a barrier
@@ -340,11 +367,11 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
             qb[i] = ld4(A.w + ((long)(o * D::KH + p) * D::KW + q) * D::CI + n0 + bc);
         }
     };
-    auto sstore = [&](const v4f (&qa)[NA], const v4f (&qb)[NBL]) {
+    auto sstore = [&](const v4f (&qa)[NA], const v4f (&qb)[NBL], int at = 0) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) *reinterpret_cast<v4f *>(&As[(lr + i * RPP) * LD + kq]) = qa[i];
+        for (int i = 0; i < NA; ++i) *reinterpret_cast<v4f *>(&As[at + (lr + i * RPP) * LD + kq]) = qa[i];
 #pragma unroll
-        for (int i = 0; i < NBL; ++i) *reinterpret_cast<v4f *>(&Bs[(br + i * BROWS) * LDB + bc]) = qb[i];
+        for (int i = 0; i < NBL; ++i) *reinterpret_cast<v4f *>(&Bs[at + (br + i * BROWS) * LDB + bc]) = qb[i];
     };
 
     const int ks = wave / NWT, w2 = wave % NWT;
@@ -353,14 +380,14 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     const float *ap = &As[(wm * 32 + li) * LD + ks * BK + 4 * h];
     const float *bp = &Bs[(ks * BK + 4 * h) * LDB + wn * 32 + li];
     v16f acc = {0};
-    auto compute = [&]() {
+    auto compute = [&](int at = 0) {
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 8) {
-            v4f a = ld4(ap + kk);
-            acc = mfma(a.x, bp[(kk + 0) * LDB], acc);
-            acc = mfma(a.y, bp[(kk + 1) * LDB], acc);
-            acc = mfma(a.z, bp[(kk + 2) * LDB], acc);
-            acc = mfma(a.w, bp[(kk + 3) * LDB], acc);
+            v4f a = ld4(ap + at + kk);
+            acc = mfma(a.x, bp[at + (kk + 0) * LDB], acc);
+            acc = mfma(a.y, bp[at + (kk + 1) * LDB], acc);
+            acc = mfma(a.z, bp[at + (kk + 2) * LDB], acc);
+            acc = mfma(a.w, bp[at + (kk + 3) * LDB], acc);
         }
     };
     // where this lane's results go (-1: no such row), and the stored activations there
@@ -401,6 +428,23 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
             sstore(ra[st], rb[st]);
             __syncthreads();
             compute();
+        }
+    } else if constexpr (KS == 1) {   // two buffers: see wgrad_tile
+        constexpr int STAGE = BM * LD + BKS * LDB;
+        gload(0, ra[0], rb[0]);
+        sstore(ra[0], rb[0]);
+        gload(BKS, ra[0], rb[0]);
+        epilogue_loads();
+        sync_lds();
+        int at = 0;
+        for (int k0 = 0; k0 < D::K; k0 += BKS) {
+            if (k0 + BKS < D::K) {
+                sstore(ra[0], rb[0], STAGE - at);
+                if (k0 + 2 * BKS < D::K) gload(k0 + 2 * BKS, ra[0], rb[0]);
+            }
+            compute(at);
+            sync_lds();
+            at = STAGE - at;
         }
     } else {
         gload(0, ra[0], rb[0]);
@@ -450,8 +494,8 @@ struct WgradArgs {
     float scale;       // multiplies dW (1/255 for conv1)
 };
 
-// LDS of one weight-gradient tile pair, in floats
-template <int BMO, int BNK> constexpr int wgrad_lds() { return BK * (BMO + 4) + BK * (BNK + 4); }
+// LDS of a weight-gradient tile, two buffers of both operands, in floats
+template <int BMO, int BNK> constexpr int wgrad_lds() { return 2 * BK * (BMO + 4 + BNK + 4); }
 
 // One weight-gradient tile: output channels [by*BMO, +BMO) x im2col columns [bx*BNK, +BNK) over the
 // rows of split bz, computed by the first T threads of the workgroup; Ys/Xs are the workgroup's LDS.
@@ -464,6 +508,7 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int bx, int by, i
     constexpr int NY = (BK + YR - 1) / YR, NX = (BK + XR - 1) / XR;
     using in_t = typename G::in_t;
     if ((int)threadIdx.x >= T) return;   // a wider workgroup: the waves beyond the tile's leave at once
+    constexpr int STAGE = BK * (LDY + LDX);   // floats of a buffer
     float *Ys = lds, *Xs = lds + BK * LDY;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -478,28 +523,25 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int bx, int by, i
     using raw_t = decltype(ld4raw(x));
     v4f ry[NY];
     raw_t rx[NX];
+    int left = 0;   // rows of the loaded stage that exist
     auto gload = [&](int mb) {
+        left = mend - mb;
 #pragma unroll
-        for (int i = 0; i < NY; ++i) {
-            int r = yr + i * YR, m = mb + r;
-            ry[i] = (r < BK && m < mend) ? ld4(A.dy + (long)m * G::N + o0 + yc) : v4f{0, 0, 0, 0};
-        }
+        for (int i = 0; i < NY; ++i) ry[i] = ld4(A.dy + (long)min(mb + yr + i * YR, mend - 1) * G::N + o0 + yc);
 #pragma unroll
-        for (int i = 0; i < NX; ++i) {
-            int r = xr + i * XR, m = mb + r;
-            rx[i] = (r < BK && m < mend) ? ld4raw(x + G::row_off(m, A.xs) + xko) : raw_t{};
-        }
+        for (int i = 0; i < NX; ++i) rx[i] = ld4raw(x + G::row_off(min(mb + xr + i * XR, mend - 1), A.xs) + xko);
     };
-    auto sstore = [&]() {
+    // (rows past the end: dY as zeros is enough, the input there is that of the last row)
+    auto sstore = [&](int at) {
 #pragma unroll
         for (int i = 0; i < NY; ++i) {
-            int r = yr + i * YR;
-            if (r < BK) *reinterpret_cast<v4f *>(&Ys[r * LDY + yc]) = ry[i];
+            const int r = yr + i * YR;
+            if (r < BK) *reinterpret_cast<v4f *>(&Ys[at + r * LDY + yc]) = r < left ? ry[i] : v4f{0, 0, 0, 0};
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-            int r = xr + i * XR;
-            if (r < BK) *reinterpret_cast<v4f *>(&Xs[r * LDX + xc]) = cvt4(rx[i]);
+            const int r = xr + i * XR;
+            if (r < BK) *reinterpret_cast<v4f *>(&Xs[at + r * LDX + xc]) = cvt4(rx[i]);
         }
     };
 
@@ -510,28 +552,31 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int bx, int by, i
     const bool do_bias = bx == 0 && wk == 0;
     v16f acc = {0}, accb = {0};
 
+    // Two buffers, one barrier per stage: while a stage is multiplied the next one is stored and the one after it is on its
+    // way.  With one buffer and two barriers every stage was a round trip to memory.
     if (mbeg < mend) {
         gload(mbeg);
-        sstore();
+        sstore(0);
+        if (mbeg + BK < mend) gload(mbeg + BK);
     }
-    __syncthreads();
+    sync_lds();
+    int at = 0;
     for (int mb = mbeg; mb < mend; mb += BK) {
-        const bool more = mb + BK < mend;
-        if (more) gload(mb + BK);
+        if (mb + BK < mend) {
+            sstore(STAGE - at);
+            if (mb + 2 * BK < mend) gload(mb + 2 * BK);
+        }
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 8) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                float a = yp[(kk + t) * LDY], b = xp[(kk + t) * LDX];
+                float a = yp[at + (kk + t) * LDY], b = xp[at + (kk + t) * LDX];
                 acc = mfma(a, b, acc);
                 if (do_bias) accb = mfma(a, 1.0f, accb);
             }
         }
-        __syncthreads();
-        if (more) {
-            sstore();
-            __syncthreads();
-        }
+        sync_lds();
+        at = STAGE - at;
     }
 
     float *part = A.part + (long)bz * A.part_stride;
