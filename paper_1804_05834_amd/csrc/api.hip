@@ -568,7 +568,8 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         int tiles = build(A, npass, few ? 32 : 64, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
                           net::F1B, w.f1part, net::HID, false);
         A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
-        // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well
+        // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well.  Many: 64 x 64
+        // (against 32 x 64, two waves: 36.7 / 57.6 us at 768 rows, 71 / 113 at 2048, 118 / 123 at 3000, 15.7 / 21.5 at 200)
         if (few) launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); });
         else launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 64, 64><<<dim3(tiles, 8, ns), 256, 0, st>>>(A); });
         *nsplit_out = ns;
@@ -835,7 +836,7 @@ struct PairF32 {
     int nd, dgx, dgz;        // input gradient: tiles, grid x and z
     int nw, wgx, wgy, wgz;   // weight gradient: tiles, grid
 };
-template <class D, int BM, int BN, int KS, class G, int TH, bool HEAD, int PART>
+template <class D, int BM, int BN, int KS, class G, int TH, bool HEAD, int PART, int KA = 1>
 __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::WgradArgs WA, PairF32 P,
                                                       misc::HeadWgradArgs H, SplitUpdate U)
 {
@@ -849,7 +850,7 @@ __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::Wg
     if (id < P.nd) {
         // dispatch order -> tile number, die-aware within the group
         const int die = id & 7, slot = id >> 3, q = P.nd >> 3, r = P.nd & 7;
-        dgrad_tile<D, BM, BN, KS>(DA, die * q + (die < r ? die : r) + slot, P.dgx, P.dgz, lds);
+        dgrad_tile<D, BM, BN, KS, KA>(DA, die * q + (die < r ? die : r) + slot, P.dgx, P.dgz, lds);
     } else if (id < P.nd + P.nw) {
         int bx, by, bz;
         wgrad_tile_of(id - P.nd, P.wgx, P.wgy, P.wgz, bx, by, bz);
@@ -950,10 +951,12 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
         }
         {
             DgradArgs D{d2, c->theta + net::C2W, act1, d1, B};
-            const int gx = (int)(((long)B * 100 + 63) / 64);
+            // 128 rows, the four slices of the reduction in the same waves (as waves of a 64-row tile: 63.8 against 49.9 us
+            // at a batch of 256, 101.6 against 83.6 at 448, 18.5 against 17.6 at 48)
+            const int gx = (int)(((long)B * 100 + 127) / 128);
             PairF32 P{gx * 4, gx, 4, 8 * *ns2, 8, 1, *ns2};
             launch(c, "conv2_bwd", st, [&] {
-                k_layer_bwd_f32<DConv2, 64, 32, 4, GConv2, 512, false, 3><<<P.nd + P.nw + U.on, 512, 0, st>>>(D, G2, P, HW, U);
+                k_layer_bwd_f32<DConv2, 128, 32, 1, GConv2, 256, false, 3, 4><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G2, P, HW, U);
             });
         }
         if (B <= 64) launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 128><<<dim3(2, 1, *ns1), 256, 0, st>>>(G1); });
@@ -974,6 +977,8 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
     {
         DgradArgs D{d2, c->theta + net::C2W, act1, d1, B};
         long M = (long)B * 100;
+        // (slices as waves: beside the weight gradients of the other stream the wide tile of the one-stream schedule made the
+        // step slower, 1074 against 1029 us at a batch of 1000)
         launch(c, "conv2_dgrad", st, [&] { k_dgrad<DConv2, 64, 32, 4><<<dim3((M + 63) / 64, 1, 4), 512, 0, st>>>(D); });
     }
     // large batch on three streams: the input-gradient chain and conv1's weight gradient on st, the other

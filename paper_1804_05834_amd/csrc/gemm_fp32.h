@@ -309,7 +309,9 @@ template <int BM, int BN, int KS> constexpr int dgrad_lds() { return (KS == 1 ? 
 // The whole reduction is requested before the first stage is staged where it is at most four stages long
 // (every layer at the tile shapes of the small-batch step): the tile is then one round trip to memory, not
 // one per stage; so are the stored activations the epilogue masks with (the ReLU of the layer below).
-template <class D, int BM, int BN, int KS>
+// KA > 1: the KA slices of the reduction as sums of the same waves, in the order KS = KA waves would have them: the same
+// bits from a tile of KA times the rows, for many rows.
+template <class D, int BM, int BN, int KS, int KA = 1>
 __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, int gz, float *smem)
 {
     constexpr int NWT = (BM / 32) * (BN / 32), T = NWT * KS * 64;
@@ -346,6 +348,7 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     const int br = tid / (BN / 4), bc = (tid % (BN / 4)) * 4;
     constexpr int NST = D::K / BKS;             // reduction stages
     constexpr bool ALLPRE = NST <= 4;           // all of them in flight at once
+    static_assert(KA == 1 || (KS == 1 && !ALLPRE && NST % KA == 0), "slices");
     constexpr int NREG = ALLPRE ? NST : 1;
     v4f ra[NREG][NA], rb[NREG][NBL];
     auto gload = [&](int k0, v4f (&qa)[NA], v4f (&qb)[NBL]) {
@@ -379,8 +382,11 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     const int li = lane & 31, h = lane >> 5;
     const float *ap = &As[(wm * 32 + li) * LD + ks * BK + 4 * h];
     const float *bp = &Bs[(ks * BK + 4 * h) * LDB + wn * 32 + li];
-    v16f acc = {0};
-    auto compute = [&](int at = 0) {
+    v16f acc_s[KA];
+#pragma unroll
+    for (int i = 0; i < KA; ++i) acc_s[i] = v16f{0};
+    v16f &acc = acc_s[0];
+    auto compute = [&](v16f &acc, int at = 0) {
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 8) {
             v4f a = ld4(ap + at + kk);
@@ -427,7 +433,7 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
             if (st) __syncthreads();   // every wave has read the stage before
             sstore(ra[st], rb[st]);
             __syncthreads();
-            compute();
+            compute(acc);
         }
     } else if constexpr (KS == 1) {   // two buffers: see wgrad_tile
         constexpr int STAGE = BM * LD + BKS * LDB;
@@ -437,15 +443,22 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
         epilogue_loads();
         sync_lds();
         int at = 0;
-        for (int k0 = 0; k0 < D::K; k0 += BKS) {
-            if (k0 + BKS < D::K) {
-                sstore(ra[0], rb[0], STAGE - at);
-                if (k0 + 2 * BKS < D::K) gload(k0 + 2 * BKS, ra[0], rb[0]);
+        for (int ka = 0; ka < D::K; ka += KA * BKS)
+#pragma unroll
+            for (int i = 0; i < KA; ++i) {   // stage i of KA: slice i
+                const int k0 = ka + i * BKS;
+                if (k0 + BKS < D::K) {
+                    sstore(ra[0], rb[0], STAGE - at);
+                    if (k0 + 2 * BKS < D::K) gload(k0 + 2 * BKS, ra[0], rb[0]);
+                }
+                compute(acc_s[i], at);
+                sync_lds();
+                at = STAGE - at;
             }
-            compute(at);
-            sync_lds();
-            at = STAGE - at;
-        }
+#pragma unroll
+        for (int i = 1; i < KA; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += acc_s[i][r];
     } else {
         gload(0, ra[0], rb[0]);
         epilogue_loads();
@@ -454,7 +467,7 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
         for (int k0 = 0; k0 < D::K; k0 += BKS) {
             const bool more = k0 + BKS < D::K;
             if (more) gload(k0 + BKS, ra[0], rb[0]);
-            compute();
+            compute(acc);
             __syncthreads();
             if (more) {
                 sstore(ra[0], rb[0]);
@@ -469,11 +482,11 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     for (int r = 0; r < 16; ++r)
         if (off[r] >= 0) A.dx[off[r]] = xm[r] > 0.f ? acc[r] : 0.f;
 }
-template <class D, int BM, int BN, int KS = 1>
+template <class D, int BM, int BN, int KS = 1, int KA = 1>
 __global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_dgrad(DgradArgs A)
 {
     __shared__ __attribute__((aligned(16))) float smem[dgrad_lds<BM, BN, KS>()];
-    dgrad_tile<D, BM, BN, KS>(A, net::tile_of_workgroup(), gridDim.x, gridDim.z, smem);
+    dgrad_tile<D, BM, BN, KS, KA>(A, net::tile_of_workgroup(), gridDim.x, gridDim.z, smem);
 }
 
 // ---------------------------------------------------------------------------
