@@ -69,42 +69,44 @@ __device__ __forceinline__ v4f ld4(const uint8_t *p)
 
 // ---------------------------------------------------------------------------
 // Forward geometries: row m = (sample, out_y, out_x); k = position inside the
-// receptive field in the order the weights are stored.
+// receptive field in the order the weights are stored.  row_off: elements from the input's start, at most
+// 8192 rows of 3136 floats or 1024 samples of 35280 bytes, so 32 bits: a weight-gradient tile forms four of them
+// per thread and stage, and signed divisions and 64-bit products cost as much as its matrix instructions.
 // ---------------------------------------------------------------------------
 struct GConv1 {  // 8x8 stride 4, uint8 CHW input, k = (c, p, q)
     using in_t = uint8_t;
     static constexpr int K = 256, N = 32, P = 400;
-    static __device__ __forceinline__ long row_off(int m, long xs)
+    static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        int n = m / 400, r = m % 400, i = r / 20, j = r % 20;
-        return (long)n * xs + (i * 4) * 84 + j * 4;
+        const uint32_t n = m / 400, r = m % 400, i = r / 20, j = r % 20;
+        return n * xs + (i * 4) * 84 + j * 4;
     }
     static __device__ __forceinline__ int k_off(int k) { return (k >> 6) * 7056 + ((k >> 3) & 7) * 84 + (k & 7); }
 };
 struct GConv2 {  // 4x4 stride 2 over 20x20x32, k = (p, q, c)
     using in_t = float;
     static constexpr int K = 512, N = 64, P = 81;
-    static __device__ __forceinline__ long row_off(int m, long xs)
+    static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        int n = m / 81, r = m % 81, i = r / 9, j = r % 9;
-        return (long)n * xs + ((i * 2) * 20 + j * 2) * 32;
+        const uint32_t n = m / 81, r = m % 81, i = r / 9, j = r % 9;
+        return n * xs + ((i * 2) * 20 + j * 2) * 32;
     }
     static __device__ __forceinline__ int k_off(int k) { return (k >> 7) * 640 + (k & 127); }
 };
 struct GConv3 {  // 3x3 stride 1 over 9x9x64, k = (p, q, c)
     using in_t = float;
     static constexpr int K = 576, N = 64, P = 49;
-    static __device__ __forceinline__ long row_off(int m, long xs)
+    static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        int n = m / 49, r = m % 49, i = r / 7, j = r % 7;
-        return (long)n * xs + (i * 9 + j) * 64;
+        const uint32_t n = m / 49, r = m % 49, i = r / 7, j = r % 7;
+        return n * xs + (i * 9 + j) * 64;
     }
     static __device__ __forceinline__ int k_off(int k) { return (k / 192) * 576 + (k % 192); }
 };
 struct GFc1 {  // dense 3136 -> 512 on the flattened conv3 output
     using in_t = float;
     static constexpr int K = 3136, N = 512, P = 1;
-    static __device__ __forceinline__ long row_off(int m, long xs) { return (long)m * xs; }
+    static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs) { return m * xs; }
     static __device__ __forceinline__ int k_off(int k) { return k; }
 };
 
@@ -540,9 +542,9 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int bx, int by, i
     auto gload = [&](int mb) {
         left = mend - mb;
 #pragma unroll
-        for (int i = 0; i < NY; ++i) ry[i] = ld4(A.dy + (long)min(mb + yr + i * YR, mend - 1) * G::N + o0 + yc);
+        for (int i = 0; i < NY; ++i) ry[i] = ld4(A.dy + (uint32_t)min(mb + yr + i * YR, mend - 1) * (uint32_t)G::N + (uint32_t)(o0 + yc));
 #pragma unroll
-        for (int i = 0; i < NX; ++i) rx[i] = ld4raw(x + G::row_off(min(mb + xr + i * XR, mend - 1), A.xs) + xko);
+        for (int i = 0; i < NX; ++i) rx[i] = ld4raw(x + (G::row_off((uint32_t)min(mb + xr + i * XR, mend - 1), (uint32_t)A.xs) + (uint32_t)xko));
     };
     // (rows past the end: dY as zeros is enough, the input there is that of the last row)
     auto sstore = [&](int at) {
