@@ -1245,6 +1245,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
             c->num_cu = cus;
+        // DQN_COMPUTE_UNITS in the environment has the launches planned for fewer compute units than the device has
+        const char *m = std::getenv("DQN_COMPUTE_UNITS");
+        if (m && m[0]) c->num_cu = std::max(1, std::min(c->num_cu, std::atoi(m)));
     }
     // DQN_CONV12_MIN_SAMPLES in the environment moves the batch size from which the fused conv1 + conv2
     // forward launch is used (samples of all passes of a launch; a huge value switches it off)

@@ -316,7 +316,9 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
         const bf16_t *const wts = SP_SEG(si).w;
         const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
-        // (the biases are read behind the next barrier, and the unit before has left its last phase that reads them)
+        // a wave may still be in the last phase of the unit before, which reads that unit's biases: with units of two
+        // networks in one workgroup they are others
+        if (G::MANY && k > 0) sync_lds();
         if (tid < 160) bias[tid] = tid < 32 ? SP_SEG(si).b1[tid] : tid < 96 ? SP_SEG(si).b2[tid - 32] : SP_SEG(si).b3[tid - 96];
         // pixels -> LDS
 #pragma unroll

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_1804_05834_amd import synth
-from test_gpu_parity import (CONFIGS, TOL, TOL_BF16, _check_indices, _replay_step_case, check_argmax, dev, dq, relerr)  # noqa: F401
+from test_gpu_parity import (CONFIGS, TOL, TOL_BF16, _check_indices, _fill_replay, _replay_step_case, check_argmax, dev, dq, relerr)  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +114,32 @@ def test_preprocess_shapes(dq, orc, n, H, W):
         diff = out.astype(np.int32) - ref.astype(np.int32)
         near = np.abs(val - np.floor(val) - 0.5) <= 1e-3   # (as in test_preprocess_parity)
         assert np.all(diff[~near] == 0) and np.all(np.abs(diff) <= 1)
+
+
+@pytest.mark.parametrize("replay,units", [(False, 64), (True, 64), (False, 199), (True, 37)])
+def test_fp32_workgroups_that_take_samples_of_both_networks(dq, monkeypatch, replay, units):
+    """The passes over s' of a batch of 100 are 200 whole samples, the first half through the online network, the second
+    through the target network.  Planned for fewer compute units than that, a workgroup takes several and passes from one
+    network to the other (with biases of its own): the same sums in the same order as with a workgroup per sample."""
+    print("case both networks in a workgroup", replay, units, flush=True)
+    B, K, cap = 100, 18, 5000
+    got = []
+    for limit in (None, units):
+        monkeypatch.delenv("DQN_COMPUTE_UNITS", raising=False)
+        if limit:
+            monkeypatch.setenv("DQN_COMPUTE_UNITS", str(limit))
+        m = dq.Dqn(dq.make_config(max_batch=B, replay_capacity=cap if replay else 0, seed=7, **CONFIGS["dueling_ddqn"]))
+        for net in (0, 1):
+            m.set_params(net, torch.from_numpy(synth.he_uniform_params(5 + net, K, 1, bias_scale=0.5)))
+        if replay:
+            _fill_replay(m, cap, K=K)
+            m.per_fill(synth.exp_priorities(9, cap, "cuda"))
+            outs = [m.train_step(B, None, draw_seed=3)]
+        else:
+            batch = tuple(dev(t) for t in synth.batch(11, B, K))
+            outs = [m.train_step(B, batch)]
+        got.append(outs)
+        m.close()
+    for x, y in zip(*got):
+        for name in ("q_next_online", "q_next_target", "a_star", "y") + (("idx", "is_w") if replay else ()):
+            assert torch.equal(x[name], y[name]), name
