@@ -26,9 +26,9 @@
  *   plain head  : out.W[K][512] out.b[K]
  *   dueling head: V.W[1][512] V.b[1] A.W[K][512] A.b[K]          (Eq.13)
  * The library keeps its parameter buffers in an internal (channel-last)
- * permutation of this blob, and further copies of the weights (bf16, or split
- * into bf16 parts) in the shadow and workspace buffers; only get/set translate
- * and keep the copies, so parameters are written with dqn_set_params.
+ * permutation of this blob; only get/set translate.  With precision 1 it also
+ * keeps copies of the weights in the shadow and workspace buffers, which only
+ * its own calls bring up to date.
  */
 #ifndef DQN_H_
 #define DQN_H_

@@ -59,7 +59,7 @@ struct Workspace {
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
     gbf::bf16_t *w2t;  // bf16 only: the online conv2 weights as [tap][channel in][channel out] (see misc::k_w2_transposed)
-    uint16_t *packed;  // the conv weights of both networks in the forward launches' order (packed.h)
+    uint16_t *packed;  // bf16 only: the conv weights of both networks in the forward launch's order (packed.h)
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -106,7 +106,7 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
     w.w2t = (gbf::bf16_t *)take(c.precision == 1 ? net::L2N * 2 : 0);
-    w.packed = (uint16_t *)take(2 * (size_t)(c.precision == 0 ? sp::W_TOTAL : sp::B_TOTAL) * 2);
+    w.packed = (uint16_t *)take(c.precision == 1 ? 2 * (size_t)sp::B_TOTAL * 2 : 0);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
     w.act1 = take(rows * net::A1 * es);
@@ -314,16 +314,12 @@ void he_uniform_host(std::vector<float> &blob, int K, int dueling, uint64_t seed
     }
 }
 
-// the copy of a network's conv weights that the fused forward launches read
-long packed_count(const dqn_ctx *c) { return c->cfg.precision == 0 ? sp::W_TOTAL : sp::B_TOTAL; }
-uint16_t *packed_of(dqn_ctx *c, int net_i) { return c->ws.packed + (net_i ? packed_count(c) : 0); }
+// bf16: the copy of a network's conv weights that the fused forward launch reads
+uint16_t *packed_of(dqn_ctx *c, int net_i) { return c->ws.packed + (net_i ? sp::B_TOTAL : 0); }
 void pack_conv(dqn_ctx *c, int net_i, hipStream_t st)
 {
     const float *theta = net_i ? c->theta_t : c->theta;
-    launch(c, "pack_conv", st, [&] {
-        if (c->cfg.precision == 0) sp::k_pack_conv<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i));
-        else sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i));
-    });
+    launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i)); });
 }
 
 void permute(dqn_ctx *c, const float *src, float *dst, int dir, hipStream_t st)
@@ -496,12 +492,10 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         sp::Args A{};
         A.nseg = npass - p0;
         for (int i = p0; i < npass; ++i) {
-            const float *theta = theta_of(c, pass[i].net);
             // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
             const bool keep = npass == 3 && i == 0;
             A.seg[i - p0] = sp::Seg{gbf::c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
-                                    packed_of(c, pass[i].net), theta + net::C1B, theta + net::C2B, theta + net::C3B,
-                                    keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
+                                    theta_of(c, pass[i].net), keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
                                     pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts};
         }
         for (int i = A.nseg; i < 3; ++i) A.seg[i] = A.seg[0];
@@ -943,7 +937,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
             const int rps = (int)((std::max<long>((rows + splits - 1) / splits, 64) + 31) / 32 * 32);
             *ns2 = (int)((rows + rps - 1) / rps);
             *ns1 = nps;
-            const sp::BackArgs PA{d2, w.packed, act1,
+            const sp::BackArgs PA{d2, c->theta + net::C2W, act1,
                                   gbf::c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, B};
             const WgradArgs G{d2, act1, w.gp2, B, rps, net::A1, net::L2N, 1.0f};
             launch(c, "conv21_bwd", st, [&] { k_conv21_bwd_sp<<<nps + 2 * *ns2 + U.on, 512, CONV21_LDS, st>>>(PA, G, nps, U); });
@@ -1219,9 +1213,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         for (int i = 0; i < 2; ++i)
             misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta_of(c, i), (__hip_bfloat16 *)shadow_of(c, i), c->n);
         misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
+        pack_conv(c, 0, st);
+        pack_conv(c, 1, st);
     }
-    pack_conv(c, 0, st);
-    pack_conv(c, 1, st);
     if (cfg->precision == 0) {
         // the launches of the conv layers hold images in LDS
         if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
@@ -1382,8 +1376,8 @@ int32_t dqn_set_params(dqn_ctx *c, int32_t which, const float *src, void *stream
     if (c->cfg.precision == 1 && which <= 1) {
         misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, (__hip_bfloat16 *)shadow_of(c, which), c->n);
         if (which == 0) misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
+        pack_conv(c, which, st);
     }
-    if (which <= 1) pack_conv(c, which, st);
     return hip_status(c, "dqn_set_params");
 }
 
@@ -1414,11 +1408,10 @@ int32_t dqn_sync_target(dqn_ctx *c, void *stream)
     if (hipMemcpyAsync(c->theta_t, c->theta, (size_t)c->n * 4, hipMemcpyDeviceToDevice, st) != hipSuccess)
         return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     if (c->cfg.precision == 1) {
-        if (hipMemcpyAsync(shadow_of(c, 1), shadow_of(c, 0), (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
+        if (hipMemcpyAsync(shadow_of(c, 1), shadow_of(c, 0), (size_t)c->n * 2, hipMemcpyDeviceToDevice, st) != hipSuccess ||
+            hipMemcpyAsync(packed_of(c, 1), packed_of(c, 0), (size_t)sp::B_TOTAL * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
             return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     }
-    if (hipMemcpyAsync(packed_of(c, 1), packed_of(c, 0), (size_t)packed_count(c) * 2, hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return fail(c, DQN_ERR_HIP, "dqn_sync_target: copy failed");
     return DQN_OK;
 }
 

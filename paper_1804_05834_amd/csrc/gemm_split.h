@@ -45,13 +45,21 @@ __device__ __forceinline__ v4f unpack4(uint2 u)
 }
 __device__ __forceinline__ Split4 split4(v4f v)
 {
+    // (opaque: otherwise the compiler rounds the low value of each pair once more by itself to unpack it)
+    auto opaque = [](uint2 u) { asm("" : "+v"(u.x), "+v"(u.y)); return u; };
     Split4 s;
-    s.p[0] = pack4(v.x, v.y, v.z, v.w);
+    s.p[0] = opaque(pack4(v.x, v.y, v.z, v.w));
     v4f r = v - unpack4(s.p[0]);
-    s.p[1] = pack4(r.x, r.y, r.z, r.w);
+    s.p[1] = opaque(pack4(r.x, r.y, r.z, r.w));
     r = r - unpack4(s.p[1]);
     s.p[2] = pack4(r.x, r.y, r.z, r.w);
     return s;
+}
+__device__ __forceinline__ void split8(v8bf (&f)[3], v4f a, v4f b)
+{
+    const Split4 s = split4(a), t = split4(b);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[q] = __builtin_bit_cast(v8bf, u32x4{s.p[q].x, s.p[q].y, t.p[q].x, t.p[q].y});
 }
 // The six products of a 32 x 32 x 16 step, smallest first
 __device__ __forceinline__ v16f mfma6(const v8bf (&a)[3], const v8bf (&b)[3], v16f c)
@@ -110,12 +118,17 @@ struct RowSum {
 // and conv3's output in LDS; only the rows the backward pass reads also go to memory.
 //   pixels    read from the ring (or the states) and staged as bf16 (exact)
 //   conv1     16x16x32: wave = (channel half, every fourth tile of 16 pixels), the wave's weights in registers
-//   conv2/3   32x32x16: wave = (channel half, quarter of the reduction), every weight fragment
+//   conv2/3   32x32x16: wave = (channel half, quarter of the reduction), every weight
 //             is read once per unit by one wave; the four partial tiles meet in LDS, each wave
 //             finishing a quarter of the channels (bias, ReLU, split)
-// The weights (456 KB of parts per network) do not fit a CU beside the images, so they stream from the
-// L2s: conv2's are requested before conv1 starts, conv3's take the registers conv2's leave step by step,
-// and conv1's of the next unit those of conv3's; so do the next unit's pixels.
+// The weights are the caller's fp32 parameters and are split here.  310 KB per network do not fit a CU beside the images,
+// so they stream from the L2s: conv2's are requested before conv1 starts, conv3's take the registers conv2's leave step by
+// step, and conv1's of the next unit those of conv3's; so do the next unit's pixels.  Four lanes load 64 bytes of a row
+// together; conv1's weights are split on their way into LDS, where four waves read them, a step of conv2's and conv3's
+// passes through 2 KB of LDS of its wave's own to the lanes that multiply it.  Its parts are formed between the matrix
+// instructions of the step before.  Acting on one observation takes 21.5 us; with loads by the lanes that multiply
+// (16 bytes of 64 rows per instruction) 24.7, with the parts formed in front of the matrix instructions 22.8, with parts
+// kept in memory beside the parameters 20.1, but then a write to the parameters went unseen.
 // R3 = 7 is the least work (no row twice); with few samples smaller parts spread a sample over
 // several CUs, recomputing the rows that neighbouring parts share: R3 = 4 costs 1.3 times the conv1 and 1.2 times
 // the conv2 work, R3 = 1 2.8 and 2.3 times.
@@ -127,8 +140,7 @@ struct RowSum {
 // ---------------------------------------------------------------------------
 struct Seg {
     gbf::c1::Src src;
-    const bf16_t *w;             // packed conv weights
-    const float *b1, *b2, *b3;
+    const float *theta;          // the network's parameters
     float *y1, *y2;              // conv1 / conv2 output for the backward pass, or nullptr
     float *y3;
     int n;
@@ -142,7 +154,7 @@ struct Args {
     misc::SampleArgs samp;
 };
 constexpr int MAX_UNITS = 96;    // units of one workgroup at most
-constexpr int W2_PRE = 6;        // steps of conv2's weights that are requested before conv1 (all eight do not fit beside it)
+constexpr int TURN = 2048;       // bytes of LDS in which a wave hands a step's weights to the lanes that multiply them
 
 template <int R3> struct Geo {
     static constexpr int PARTS = (7 + R3 - 1) / R3;
@@ -153,11 +165,11 @@ template <int R3> struct Geo {
     static constexpr int CH = PR * 84 / 16, NPX = (4 * CH + 511) / 512;   // 16-byte pieces per frame, per thread
     static constexpr int PXB = 4 * PR * 84 * 2;   // pixels; later conv2's image
     static constexpr int P1 = 208, P2 = 400;      // pixel pitch of the images in bytes
-    static constexpr int W1B = W1_FR * FRAG * 2;  // conv1's weights, in the image's place until conv1 begins (one unit only)
-    static constexpr int I1B = MANY || M1 * P1 > W1B ? M1 * P1 : W1B;   // conv1's image; later the partial tiles
+    static constexpr int W1B = 2 * 8 * 3 * 1024;  // conv1's weights, in the image's place until conv1 begins
+    static constexpr int I1B = M1 * P1 > W1B ? M1 * P1 : W1B;   // conv1's image; later the partial tiles
     static constexpr int TAB = (2 * MAX_UNITS + 4 + 160) * 4;   // slots, leaf values, total; biases
-    static constexpr int LDS = PXB + I1B + TAB;
-    static_assert(PR * 84 % 16 == 0 && M2 * P2 <= PXB && 24 * T2 * 1024 <= I1B && 24 * T3 * 1024 <= I1B, "LDS layout");
+    static constexpr int LDS = PXB + I1B + TAB + 8 * TURN;
+    static_assert(PR * 84 % 16 == 0 && TAB % 16 == 0 && M2 * P2 <= PXB && 24 * T2 * 1024 <= I1B && 24 * T3 * 1024 <= I1B, "LDS layout");
 };
 
 // The partial tiles of the four waves of a channel half: wave kq ends up with rows 8 kq + 4 h + 0..3 of the half
@@ -208,10 +220,29 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
 
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
     v8bf w1[8][3];
-    auto load_w1 = [&](const bf16_t *w, int s) {
-        const v8bf *p = reinterpret_cast<const v8bf *>(w + (nt * 8 + s) * 3 * FRAG) + lane;
+    // this wave's eighth of conv1's weights (channel half wave / 4, steps 2 (wave % 4) ..), on their way to LDS
+    v4f w1s[4];
+    auto load_w1 = [&](const float *theta) {
+        const float *p = theta + net::C1W + (16 * (wave >> 2) + (lane >> 2)) * 256 + 64 * (wave & 3) + 4 * (lane & 3);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) w1[s][q] = p[q * 64];
+        for (int q = 0; q < 4; ++q) w1s[q] = *reinterpret_cast<const v4f *>(p + 16 * q);
+    };
+    // four waves want the same half of them: through LDS they are fetched, and split, once per workgroup
+    auto store_w1 = [&] {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {   // 16 of a row's 64 elements: half of step q / 2, lane group 2 (q % 2) + piece / 2
+            uint8_t *d = img1 + ((2 * wave + (q >> 1)) * 3) * 1024 + ((lane >> 2) + 16 * (2 * (q & 1) + ((lane >> 1) & 1))) * 16 + 8 * (lane & 1);
+            const Split4 f = split4(w1s[q]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 1024) = f.p[pl];
+        }
+    };
+    auto read_w1 = [&] {
+        const v8bf *p = reinterpret_cast<const v8bf *>(img1) + nt * 24 * 64 + lane;
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) w1[s][q] = p[(s * 3 + q) * 64];
     };
     u32x4 raw[G::NPX];
     auto load_px = [&](const uint8_t *x, long xs, int shift, int first, int u, int slot) {
@@ -237,38 +268,12 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
     const bool ring = A.seg[0].src.idx != nullptr;   // of every segment, or of none
     // (scalar loads: a select over the three segments' arguments became a table in scratch memory)
     const uint8_t *x0 = SP_SEG(si).src.x;
-    const bf16_t *wf = SP_SEG(si).w;
     const long xs0 = SP_SEG(si).src.xs;
     const int shift0 = SP_SEG(si).src.shift, first0 = SP_SEG(si).first;
     // The first pixels before the weights, which are twenty times as many bytes, where their slot is known; drawing
     // comes first otherwise, with the weights on their way
     if (!ring) load_px(x0, xs0, shift0, first0, u, 0);
-    v8bf w1s[G::MANY ? 1 : 6];   // one unit only: this wave's eighth of conv1's weights, on their way to LDS
-    if constexpr (G::MANY) {
-#pragma unroll
-        for (int s = 0; s < 8; ++s) load_w1(wf, s);
-    } else {
-        const v8bf *p = reinterpret_cast<const v8bf *>(wf + wave * 6 * FRAG) + lane;
-#pragma unroll
-        for (int q = 0; q < 6; ++q) w1s[q] = p[q * 64];
-    }
-    // four waves want the same half of conv1's weights: through LDS they are fetched once per workgroup
-    auto store_w1 = [&] {
-        if constexpr (!G::MANY) {
-            v8bf *d = reinterpret_cast<v8bf *>(img1) + wave * 6 * 64 + lane;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) d[q * 64] = w1s[q];
-        }
-    };
-    auto read_w1 = [&] {
-        if constexpr (!G::MANY) {
-            const v8bf *p = reinterpret_cast<const v8bf *>(img1) + nt * 24 * 64 + lane;
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) w1[s][q] = p[(s * 3 + q) * 64];
-        }
-    };
+    load_w1(SP_SEG(si).theta);
     if (ring) {
         if (A.draw) {
 #pragma unroll 1
@@ -294,10 +299,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 slots[k] = A.seg[0].src.idx[(u + k * G0) / G::PARTS % A.seg[0].n];
             }
         }
-        store_w1();
-        sync_lds();   // the slot table is complete, and the weights
+        sync_lds();   // the slot table is complete
         load_px(x0, xs0, shift0, first0, u, slots[0]);
-        read_w1();
     }
     if (A.draw && wave == 7)   // index, raw importance weight and transition data of the segment-0 draws
         for (int k = lane; k < nu; k += 64) {
@@ -314,12 +317,12 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         const int n16 = lane & 15, kg = lane >> 4, i32 = lane & 31, h = lane >> 5;
         const int ul = u - SP_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
         const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
-        const bf16_t *const wts = SP_SEG(si).w;
+        const float *const theta = SP_SEG(si).theta;
         const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
         // a wave may still be in the last phase of the unit before, which reads that unit's biases: with units of two
         // networks in one workgroup they are others
         if (G::MANY && k > 0) sync_lds();
-        if (tid < 160) bias[tid] = tid < 32 ? SP_SEG(si).b1[tid] : tid < 96 ? SP_SEG(si).b2[tid - 32] : SP_SEG(si).b3[tid - 96];
+        if (tid < 160) bias[tid] = theta[tid < 32 ? net::C1B + tid : tid < 96 ? net::C2B + tid - 32 : net::C3B + tid - 96];
         // pixels -> LDS
 #pragma unroll
         for (int i = 0; i < G::NPX; ++i) {
@@ -330,17 +333,29 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 d[1] = gbf::cvt8_u8(raw[i].z, raw[i].w);
             }
         }
-        if (G::MANY || ring) {
-            sync_lds();
-        } else {
-            store_w1();
-            sync_lds();
-            read_w1();
-            sync_lds();
-        }
-        v8bf w2[8][3], w3[9][3];
-        const v8bf *p2 = reinterpret_cast<const v8bf *>(wts + W2_AT + (((kq * 2 + ch) * 8) * 3) * FRAG) + lane;
-        const v8bf *p3 = reinterpret_cast<const v8bf *>(wts + W3_AT + (((kq * 2 + ch) * 9) * 3) * FRAG) + lane;
+        store_w1();
+        sync_lds();
+        read_w1();
+        sync_lds();   // the weights' place is conv1's image from here on
+        v4f w2[8][2], w3[9][2];
+        const float *p2 = theta + net::C2W + (32 * ch + (lane >> 2)) * 512 + 128 * kq + 4 * (lane & 3);
+        const float *p3 = theta + net::C3W + (32 * ch + (lane >> 2)) * 576 + 144 * kq + 4 * (lane & 3);
+        auto load_w3 = [&](int s) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) w3[s][q] = *reinterpret_cast<const v4f *>(p3 + 16 * s + 16 * 576 * q);
+        };
+        // the weights of a step as they were loaded (row 16 q + lane / 4, piece lane % 4 of four) -> eight of row i32, from
+        // 8 h on; the pieces of a row lie permuted by row / 4, so that the lanes that read together meet all banks
+        uint8_t *const tw = lds + G::PXB + G::I1B + G::TAB + wave * TURN;
+        v4f wr[2];
+        auto turn = [&](const v4f (&w)[2]) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<v4f *>(tw + (16 * q + (lane >> 2)) * 64 + (((lane & 3) ^ (lane >> 4)) * 16)) = w[q];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (LDS operations of a wave complete in order)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) wr[q] = *reinterpret_cast<const v4f *>(tw + i32 * 64 + (((2 * h + q) ^ ((lane >> 2) & 3)) * 16));
+        };
         const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2 and conv3
         float *const y1 = SP_SEG(si).y1, *const y2 = SP_SEG(si).y2;
         __builtin_amdgcn_sched_barrier(0);
@@ -384,9 +399,18 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         };
         auto load_w2 = [&] {
 #pragma unroll
-            for (int s = 0; s < W2_PRE; ++s)
+            for (int s = 0; s < 8; ++s)
 #pragma unroll
-                for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
+                for (int q = 0; q < 2; ++q) w2[s][q] = *reinterpret_cast<const v4f *>(p2 + 16 * s + 16 * 512 * q);
+        };
+        // the parts of the next step's weights, formed between the six matrix instructions in front of them
+        auto split_next = [&](v8bf (&f)[3]) {
+            split8(f, wr[0], wr[1]);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+            }
         };
         // conv2's first weights: behind the first tile where in front of it they would hold up conv1's own
         if constexpr (G::MANY) load_w2();
@@ -415,33 +439,31 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             for (int a = 0; a < NA; ++a)
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
-#pragma unroll
-            for (int s = W2_PRE; s < 8; ++s)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) w2[s][q] = p2[(s * 3 + q) * 64];
-            v8bf b[3], nb[3];
+            v8bf b[3], nb[3], wp[2][3];
             auto load_b = [&](int i) {
                 const int s = i / T, t = i % T, off = (((s >> 1) & 1) * 10 + (s >> 2)) * G::P1 + (s & 1) * 32;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 64);
             };
+            turn(w2[0]);
             load_b(0);
+            split8(wp[0], wr[0], wr[1]);
+            turn(w2[1]);
 #pragma unroll
             for (int i = 0; i < 8 * T; ++i) {   // the operands of a product are requested before the one before it
                 const int s = i / T, t = i % T;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) b[pl] = nb[pl];
                 if (i + 1 < 8 * T) load_b(i + 1);
-                if (t == 0 && s > 0) {          // conv3's weights into the registers of step s - 1
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) w3[s - 1][q] = p3[((s - 1) * 3 + q) * 64];
-                }
+                if (t == 0 && s > 0) load_w3(s - 1);  // conv3's weights into the registers of step s - 1
                 __builtin_amdgcn_sched_barrier(0);
-                acc[s % NA][t] = mfma6(w2[s], b, acc[s % NA][t]);
+                acc[s % NA][t] = mfma6(wp[s & 1], b, acc[s % NA][t]);
+                if (t == T - 1 && s < 7) split_next(wp[(s + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
+                if (t == T - 1 && s < 6) turn(w2[s + 2]);
             }
-#pragma unroll
-            for (int q = 0; q < 6; ++q) w3[7 + q / 3][q % 3] = p3[(7 * 3 + q) * 64];
+            load_w3(7);
+            load_w3(8);
             if constexpr (NA == 2) acc[0][0] += acc[1][0];
             sync_lds();   // every wave has read conv1's image
             v4f own[T];
@@ -467,7 +489,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         // (behind the last unit: its own once more, so that the registers are written on every path and do not
         // have to keep their old contents until here)
         const int kn = k + 1 < nu ? k + 1 : k, un = bid + kn * G0, sn = seg_of(un);
-        const bf16_t *const wn = SP_SEG(sn).w;
+        if constexpr (G::MANY) load_w1(SP_SEG(sn).theta);
         if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, ring ? slots[kn] : 0);
         sync_lds();
 
@@ -487,24 +509,28 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             for (int a = 0; a < NA; ++a)
 #pragma unroll
                 for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
-            v8bf b[3], nb[3];
+            v8bf b[3], nb[3], wp[2][3];
             auto load_b = [&](int i) {
                 const int s = i / T, t = i % T, sg = 9 * kq + s, tap = sg >> 2;
                 const int off = ((tap / 3) * 9 + tap % 3) * G::P2 + (sg & 3) * 32;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 128);
             };
+            turn(w3[0]);
             load_b(0);
+            split8(wp[0], wr[0], wr[1]);
+            turn(w3[1]);
 #pragma unroll
             for (int i = 0; i < 9 * T; ++i) {
                 const int s = i / T, t = i % T;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) b[pl] = nb[pl];
                 if (i + 1 < 9 * T) load_b(i + 1);
-                if (G::MANY && t == 0 && s > 0) load_w1(wn, s - 1);   // conv1's weights of the next unit
                 __builtin_amdgcn_sched_barrier(0);
-                acc[s % NA][t] = mfma6(w3[s], b, acc[s % NA][t]);
+                acc[s % NA][t] = mfma6(wp[s & 1], b, acc[s % NA][t]);
+                if (t == T - 1 && s < 8) split_next(wp[(s + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
+                if (t == T - 1 && s < 7) turn(w3[s + 2]);
             }
             if constexpr (NA == 2) acc[0][0] += acc[1][0];
             v4f own[T];
@@ -983,7 +1009,7 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
 // ---------------------------------------------------------------------------
 struct BackArgs {
     const float *dy;      // [B][81][64]: gradient w.r.t. conv2's pre-activation
-    const uint16_t *w;    // packed conv weights
+    const float *w;       // conv2's weights
     const float *xact;    // [B][400][32]: conv1's output
     gbf::c1::Src src;     // where the frames of sample n come from
     float *part1;         // [nblocks][32*256 + 32]
@@ -1042,10 +1068,11 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
     v8bf wa[8][3];   // step s: kernel column px + 2 (s / 4), output channels 16 (s % 4) ..
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-        const int tap = (py + 2 * kh) * 4 + px + 2 * (s >> 2);
-        const v8bf *p = reinterpret_cast<const v8bf *>(A.w + W2B_AT + ((tap * 4 + (s & 3)) * 3) * FRAG) + lane;
+        const float *p = A.w + (16 * (s & 3) + 8 * h) * 512 + ((py + 2 * kh) * 4 + px + 2 * (s >> 2)) * 32 + i32;
+        v4f lo, hi;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) wa[s][q] = p[q * 64];
+        for (int e = 0; e < 4; ++e) { lo[e] = p[e * 512]; hi[e] = p[(e + 4) * 512]; }
+        split8(wa[s], lo, hi);
     }
     load_unit(bid, slot0);
     int slot_next = bid + nblocks < units ? gbf::c1::sample_slot(A.src, (bid + nblocks) / P) : 0;

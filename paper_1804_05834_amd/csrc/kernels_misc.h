@@ -588,7 +588,7 @@ struct RmsArgs {
     RmsSeg seg[5];
     float *theta, *v, *m, *g;
     __hip_bfloat16 *shadow;  // bf16 copy of theta (same order) or nullptr
-    uint16_t *packed;        // the conv weights in the forward launch's order (packed.h)
+    uint16_t *packed;        // with the bf16 copy: the conv weights in the forward launch's order (packed.h)
     __hip_bfloat16 *w2t;     // with the bf16 copy: conv2's weights once more, as [tap][channel in][channel out] (or nullptr)
     float lr, rho, eps;
 };
@@ -612,10 +612,9 @@ __device__ __forceinline__ void rms_apply(const RmsArgs &A, long i, float g, con
     A.v[i] = v;
     A.theta[i] = th;
     if (store_g) A.g[i] = g;
-    if (A.shadow) A.shadow[i] = __float2bfloat16(th);
-    if (i < net::F1W) {
-        if (A.shadow) sp::store_packed_bf16(A.packed, i, th);
-        else sp::store_packed(A.packed, i, th);
+    if (A.shadow) {
+        A.shadow[i] = __float2bfloat16(th);
+        if (i < net::F1W) sp::store_packed_bf16(A.packed, i, th);
     }
     if (A.w2t && i >= net::C2W && i < net::C2W + 64 * 512) {
         const int t = (int)(i - net::C2W);   // [channel out][tap][channel in]

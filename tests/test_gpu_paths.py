@@ -143,3 +143,34 @@ def test_fp32_workgroups_that_take_samples_of_both_networks(dq, monkeypatch, rep
     for x, y in zip(*got):
         for name in ("q_next_online", "q_next_target", "a_star", "y") + (("idx", "is_w") if replay else ()):
             assert torch.equal(x[name], y[name]), name
+
+
+@pytest.mark.parametrize("E,B", [(3, 8), (60, 32), (300, 64), (1, 160)])
+def test_fp32_parameters_written_in_place(dq, E, B):
+    """fp32 has no copies of the weights: what a caller writes into its own parameter buffers (another context's contents, a
+    target moved towards the online network) is what the next call uses, in every launch, and nothing in the workspace has
+    to survive from one call to the next."""
+    print("case parameters in place", E, B, flush=True)
+    K = 18
+    cfg = dict(max_batch=B, max_act_batch=E, **CONFIGS["dueling_ddqn"])
+    obs, batch = dev(synth.states(31, E)), tuple(dev(t) for t in synth.batch(11, B, K))
+    m, n = dq.Dqn(dq.make_config(seed=7, **cfg)), dq.Dqn(dq.make_config(seed=8, target_seed=9, **cfg))
+    for name in ("online", "target", "opt_state"):
+        n._bufs[name].copy_(m._bufs[name])
+    on, tg = m.get_params(0), m.get_params(1)
+    m.set_params(1, 0.5 * on + 0.5 * tg)   # the same in the canonical order
+    for buf in (n._bufs["target"].view(torch.float32),):
+        buf.copy_(0.5 * n._bufs["online"].view(torch.float32) + 0.5 * buf)
+    for step in range(2):
+        n._bufs["workspace"].fill_(255)
+        a, q = m.act(obs, 0.0, 5, want_q=True)
+        b, p = n.act(obs, 0.0, 5, want_q=True)
+        assert torch.equal(q, p) and torch.equal(a, b), step
+        n._bufs["workspace"].fill_(255)
+        x, y = m.train_step(B, batch), n.train_step(B, batch)
+        for name in x:
+            assert torch.equal(x[name], y[name]), (step, name)
+        for which in (0, 1, 2, 3):
+            assert torch.equal(m.get_params(which), n.get_params(which)), (step, which)
+    m.close()
+    n.close()
