@@ -3,14 +3,21 @@
 // A float is the sum of three bf16 numbers: x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1).
 // Round-to-nearest leaves 8 significant bits to each, 24 in all, so the sum is x itself: nothing of an
 // operand is dropped.  A product x*w is then nine products of bf16 numbers, each exact in the fp32
-// accumulator of the matrix instruction; the three smallest (x1*w2, x2*w1, x2*w2: below 2^-26 of
-// |x*w|, a quarter of what rounding one fp32 product may cost) are left out, six remain.  Pixels are
-// bytes and exact in ONE bf16 number, so conv1 needs three products and drops none.
-// Measured on this chip against fp64 sums of 64 / 512 / 3136 products (32 x 32 results, error over
-// sum |a*b|, three distributions): rms 2.1 / 2.5 / 2.5e-8 with six products, 2.8 / 2.8 / 2.8e-8 with
-// v_mfma_f32_32x32x2_f32 for normal operands; 2.8 / 3.0 / 3.6e-8 against 2.6 / 2.6 / 2.8e-8 for
-// ReLU-like ones, 8.2e-8 / 2.4e-7 / 5.2e-7 against 1.2e-7 / 3.2e-7 / 7.9e-7 for positive ones; with all
-// nine products the same figures to three digits.
+// accumulator of the matrix instruction.  The three smallest, x1*w2, x2*w1 and x2*w2, are left out: x1 is at most 2^-8
+// of x and w2 at most 2^-17 of w, so together they reach 2^-24 of |x*w|, what rounding one product to fp32 may cost;
+// over random operands their rms is 2^-27.5.  Pixels are bytes and exact in ONE bf16 number, so conv1 needs three
+// products and drops none.
+// The leading products x0*w0 are summed apart from the others, which are below 2^-7 of them (Acc2): the matrix
+// instruction's additions do not round to nearest but leave errors of one sign, up to a unit in the last place of the
+// sum, and an instruction of small products into a large sum costs as many of them as one of large products.
+// Measured against fp64, conv2 and conv3 alone through the library's calls, for 3, 60, 200 and 600 observations (the
+// geometries below): inputs after a ReLU, random 24-bit values, error over sum |x*w|, rms over the outputs in 1e-8
+//   weights                              uniform    normal     a fifth nonzero   positive
+//   this form                            0.4-0.5    0.4-0.6    0.8-1.1           4.2-5.4
+//   the six products in one sum          0.8-1.3    0.8-1.4    1.5-2.4           5.2-8.2
+//   v_mfma_f32 in the layers' launches   1.3-2.4    1.2-2.8    1.5-3.1           7.7-30
+// In one sum the errors have a mean of -0.05 to -0.4 (positive weights: down to -1.1), in the other two none that stands
+// out from the noise.
 // Cost per 32 reduction elements of a 16 x 16 tile: six bf16 instructions of 16 cycles against eight
 // fp32 ones of 32: 96 against 256 cycles of the matrix pipe.
 #pragma once
@@ -61,21 +68,10 @@ __device__ __forceinline__ void split8(v8bf (&f)[3], v4f a, v4f b)
 #pragma unroll
     for (int q = 0; q < 3; ++q) f[q] = __builtin_bit_cast(v8bf, u32x4{s.p[q].x, s.p[q].y, t.p[q].x, t.p[q].y});
 }
-// The six products of a 32 x 32 x 16 step, smallest first
-__device__ __forceinline__ v16f mfma6(const v8bf (&a)[3], const v8bf (&b)[3], v16f c)
-{
-    c = mfma(a[2], b[0], c);
-    c = mfma(a[0], b[2], c);
-    c = mfma(a[1], b[1], c);
-    c = mfma(a[1], b[0], c);
-    c = mfma(a[0], b[1], c);
-    return mfma(a[0], b[0], c);
-}
-// The same with the leading products in a sum of their own, to which the caller adds the rest once at the end.  The
-// matrix instruction's additions do not round to nearest: each leaves an error of the same sign, up to a unit in the
-// last place of the sum.  In a gradient, which is a sum of tens of thousands of such results that cancel, these errors
-// would add up (conv1's weight gradient at a batch of 42 with everything in one sum: 8.2e-7 of its norm off fp64, in the
-// plain fp32 chain 3.8e-7).  The other five products are below 2^-8 of the leading one, and so are their sum's errors.
+// The six products of a 32 x 32 x 16 step, the leading ones in a sum of their own, to which the caller adds the rest once
+// at the end.  In a gradient, which is a sum of tens of thousands of such results that cancel, the one-sided errors of a
+// single sum would add up (conv1's weight gradient at a batch of 42 with everything in one sum: 8.2e-7 of its norm off
+// fp64, in the plain fp32 chain 3.8e-7).
 struct Acc2 { v16f hi, lo; };
 __device__ __forceinline__ void mfma6(const v8bf (&a)[3], const v8bf (&b)[3], Acc2 &c)
 {
@@ -171,6 +167,17 @@ template <int R3> struct Geo {
     static constexpr int LDS = PXB + I1B + TAB + 8 * TURN;
     static_assert(PR * 84 % 16 == 0 && TAB % 16 == 0 && M2 * P2 <= PXB && 24 * T2 * 1024 <= I1B && 24 * T3 * 1024 <= I1B, "LDS layout");
 };
+
+// The sums of a wave: leading products and the others, of its NA turns
+template <int NA, int T> __device__ __forceinline__ void close_sums(const Acc2 (&acc)[NA][T], v16f (&sum)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        v16f hi = acc[0][t].hi, lo = acc[0][t].lo;
+        if constexpr (NA == 2) { hi += acc[1][t].hi; lo += acc[1][t].lo; }
+        sum[t] = hi + lo;
+    }
+}
 
 // The partial tiles of the four waves of a channel half: wave kq ends up with rows 8 kq + 4 h + 0..3 of the half
 // (accumulator registers 4 kq .. 4 kq + 3), summed in the order own, then the others ascending.
@@ -368,26 +375,26 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             auto pixels = [&](int s) {   // frame s / 2, kernel rows 4 (s % 2) + kg
                 return __builtin_bit_cast(v8bf, *reinterpret_cast<const u32x4_a8 *>(p + (s >> 1) * (G::PR * 84) + (s & 1) * (4 * 84)));
             };
-            v4f a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
+            v4f hi = {0, 0, 0, 0}, lo0 = {0, 0, 0, 0}, lo1 = {0, 0, 0, 0};
             v8bf b0 = pixels(0), b1 = pixels(1);
 #pragma unroll
             for (int s = 0; s < 8; s += 2) {
                 const v8bf c0 = b0, c1 = b1;
                 if (s < 6) { b0 = pixels(s + 2); b1 = pixels(s + 3); }
                 __builtin_amdgcn_sched_barrier(0);
-                a0 = mfma16(w1[s][2], c0, a0);
-                a1 = mfma16(w1[s + 1][2], c1, a1);
-                a0 = mfma16(w1[s][1], c0, a0);
-                a1 = mfma16(w1[s + 1][1], c1, a1);
-                a0 = mfma16(w1[s][0], c0, a0);
-                a1 = mfma16(w1[s + 1][0], c1, a1);
+                lo0 = mfma16(w1[s][2], c0, lo0);
+                lo1 = mfma16(w1[s + 1][2], c1, lo1);
+                hi = mfma16(w1[s][0], c0, hi);
+                lo0 = mfma16(w1[s][1], c0, lo0);
+                lo1 = mfma16(w1[s + 1][1], c1, lo1);
+                hi = mfma16(w1[s + 1][0], c1, hi);
                 __builtin_amdgcn_sched_barrier(0);
             }
             constexpr float sc = 1.0f / 255.0f;
             const v4f bias1 = *reinterpret_cast<const v4f *>(bias + 16 * nt + 4 * kg);
             v4f v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = fmaxf((a0[r] + a1[r]) * sc + bias1[r], 0.f);
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf((hi[r] + (lo0[r] + lo1[r])) * sc + bias1[r], 0.f);
             if (m < G::M1) {
                 const Split4 q = split4(v);
                 uint8_t *d = img1 + (y * 20 + (x & 1) * 10 + (x >> 1)) * G::P1 + (16 * nt + 4 * kg) * 2;
@@ -434,11 +441,11 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 const int y = m / 9, x = m - 9 * y;
                 pa[t] = img1 + ((2 * y + kq) * 20 + x) * G::P1 + h * 16;
             }
-            v16f acc[NA][T];
+            Acc2 acc[NA][T];
 #pragma unroll
             for (int a = 0; a < NA; ++a)
 #pragma unroll
-                for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
+                for (int t = 0; t < T; ++t) acc[a][t] = Acc2{v16f{0}, v16f{0}};
             v8bf b[3], nb[3], wp[2][3];
             auto load_b = [&](int i) {
                 const int s = i / T, t = i % T, off = (((s >> 1) & 1) * 10 + (s >> 2)) * G::P1 + (s & 1) * 32;
@@ -457,17 +464,18 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 if (i + 1 < 8 * T) load_b(i + 1);
                 if (t == 0 && s > 0) load_w3(s - 1);  // conv3's weights into the registers of step s - 1
                 __builtin_amdgcn_sched_barrier(0);
-                acc[s % NA][t] = mfma6(wp[s & 1], b, acc[s % NA][t]);
+                mfma6(wp[s & 1], b, acc[s % NA][t]);
                 if (t == T - 1 && s < 7) split_next(wp[(s + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (t == T - 1 && s < 6) turn(w2[s + 2]);
             }
             load_w3(7);
             load_w3(8);
-            if constexpr (NA == 2) acc[0][0] += acc[1][0];
+            v16f sum[T];
+            close_sums(acc, sum);
             sync_lds();   // every wave has read conv1's image
             v4f own[T];
-            reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+            reduce_quarters<T>(sum, own, scratch, kq, ch, lane);
             const v4f bias2 = *reinterpret_cast<const v4f *>(bias + 32 + co);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -504,11 +512,11 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 const int y = m / 7, x = m - 7 * y;
                 pa[t] = img2 + (y * 9 + x) * G::P2 + h * 16;
             }
-            v16f acc[NA][T];
+            Acc2 acc[NA][T];
 #pragma unroll
             for (int a = 0; a < NA; ++a)
 #pragma unroll
-                for (int t = 0; t < T; ++t) acc[a][t] = v16f{0};
+                for (int t = 0; t < T; ++t) acc[a][t] = Acc2{v16f{0}, v16f{0}};
             v8bf b[3], nb[3], wp[2][3];
             auto load_b = [&](int i) {
                 const int s = i / T, t = i % T, sg = 9 * kq + s, tap = sg >> 2;
@@ -527,14 +535,15 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 for (int pl = 0; pl < 3; ++pl) b[pl] = nb[pl];
                 if (i + 1 < 9 * T) load_b(i + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                acc[s % NA][t] = mfma6(wp[s & 1], b, acc[s % NA][t]);
+                mfma6(wp[s & 1], b, acc[s % NA][t]);
                 if (t == T - 1 && s < 8) split_next(wp[(s + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (t == T - 1 && s < 7) turn(w3[s + 2]);
             }
-            if constexpr (NA == 2) acc[0][0] += acc[1][0];
+            v16f sum[T];
+            close_sums(acc, sum);
             v4f own[T];
-            reduce_quarters<T>(acc[0], own, scratch, kq, ch, lane);
+            reduce_quarters<T>(sum, own, scratch, kq, ch, lane);
             const v4f bias3 = *reinterpret_cast<const v4f *>(bias + 96 + co);
 #pragma unroll
             for (int t = 0; t < T; ++t) {

@@ -174,3 +174,55 @@ def test_fp32_parameters_written_in_place(dq, E, B):
             assert torch.equal(m.get_params(which), n.get_params(which)), (step, which)
     m.close()
     n.close()
+
+
+@pytest.mark.parametrize("B", [14, 30, 64, 100])
+@pytest.mark.parametrize("layer", [2, 3])
+def test_fp32_split_products_are_no_less_exact_than_the_fp32_chain(dq, layer, B):
+    """conv2 and conv3 in the split form (the passes over s') against the plain fp32 chain (the pass on s) on the same states:
+    the error against fp64, rms over the outputs.  Inputs and outputs of the layer are read off exactly: conv1 is one
+    pixel times a 16-bit weight per channel, the other conv layer and the head pass single values on."""
+    print("case split exactness", layer, B, flush=True)
+    K = 64
+    rng = np.random.default_rng(100 * layer + B)
+    T = {name: np.zeros(shape) for name, shape, _ in synth.param_spec(K, 0)}
+    taps = [(rng.integers(4), rng.integers(8), rng.integers(8)) for _ in range(32)]
+    w1 = rng.integers(32768, 65536, 32) / 65536.0 * np.where(rng.random(32) < 0.3, -1, 1)   # a third: nothing after the ReLU
+    for o in range(32):
+        T["conv1.W"][(o,) + taps[o]] = w1[o]
+    for o in range(64):
+        T["conv2.W"][o, o % 32, 1 + o // 32, 2] = 1.0
+        T["conv3.W"][o, o, 1, 1] = 1.0
+    name, fan = ("conv2.W", 512) if layer == 2 else ("conv3.W", 576)
+    T[name] = np.where(rng.random(T[name].shape) < 0.2, rng.normal(0, (6.0 / fan) ** 0.5, T[name].shape), 0)
+    pick = rng.permutation(3136)[:K]
+    T["fc1.W"][np.arange(K), pick] = T["A.W"][np.arange(K), np.arange(K)] = 1.0
+    blob = torch.from_numpy(np.concatenate([T[n].astype(np.float32).ravel() for n, _, _ in synth.param_spec(K, 0)]))
+    s, _, a, r, d = synth.batch(11, B, K)
+    m = dq.Dqn(dq.make_config(num_actions=K, dueling=0, max_batch=B))
+    m.set_params(0, blob)
+    m.set_params(1, blob)
+    out = m.train_step(B, tuple(dev(t) for t in (s, s, a, r, d)))
+    # the layer's inputs in fp32: integer sums, exact, times fp32(1 / 255)
+    h = np.zeros((B, 32, 20, 20), np.float32)
+    for o, (c, y, x) in enumerate(taps):
+        v = (s[:, c, y:y + 77:4, x:x + 77:4].numpy().astype(np.float64) * w1[o]).astype(np.float32)
+        h[:, o] = np.maximum(v * np.float32(1.0 / 255.0), 0)
+
+    def conv(v, name, stride):
+        W = torch.from_numpy(T[name].astype(np.float32)).double()
+        n = (v.shape[2] - W.shape[-1]) // stride + 1
+        u, W = torch.nn.functional.unfold(v, W.shape[-1], stride=stride), W.reshape(64, -1)
+        return torch.matmul(W, u).reshape(B, 64, n, n), torch.matmul(W.abs(), u.abs()).reshape(B, 64, n, n)
+
+    y, mag = conv(torch.from_numpy(h).double(), "conv2.W", 2)
+    if layer == 3:
+        y, mag = conv(y, "conv3.W", 1)
+    else:
+        y, mag = y[:, :, 1:8, 1:8], mag[:, :, 1:8, 1:8]
+    y, mag = y.flatten(1)[:, pick], mag.flatten(1)[:, pick]
+    on = y > 0
+    rms = {k: float((((out[k].cpu().double() - y) / mag)[on] ** 2).mean().sqrt()) for k in ("q_s", "q_next_online", "q_next_target")}
+    assert rms["q_s"] < 1e-7   # what was read off is the layer
+    assert max(rms["q_next_online"], rms["q_next_target"]) <= rms["q_s"], rms
+    m.close()
