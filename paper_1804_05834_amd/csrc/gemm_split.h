@@ -73,6 +73,17 @@ __device__ __forceinline__ void split8(v8bf (&f)[3], v4f a, v4f b)
 // single sum would add up (conv1's weight gradient at a batch of 42 with everything in one sum: 8.2e-7 of its norm off
 // fp64, in the plain fp32 chain 3.8e-7).
 struct Acc2 { v16f hi, lo; };
+// ... added.  An infinity splits into itself and NaNs: its sum of leading products is what the fp32 chain gives (infinite, or
+// NaN where infinities cancel or meet a zero), the sum of the others NaN, which the median turns into a finite number.
+// (Finite values above 3.39e38, which round to an infinite bf16, count as infinities.)
+__device__ __forceinline__ float joined(float hi, float lo) { return hi + __builtin_amdgcn_fmed3f(lo, -__FLT_MAX__, __FLT_MAX__); }
+__device__ __forceinline__ v16f joined(v16f hi, v16f lo)
+{
+    v16f s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = joined(hi[r], lo[r]);
+    return s;
+}
 __device__ __forceinline__ void mfma6(const v8bf (&a)[3], const v8bf (&b)[3], Acc2 &c)
 {
     c.lo = mfma(a[2], b[0], c.lo);
@@ -89,22 +100,17 @@ __device__ __forceinline__ void mfma3(const v8bf (&a)[3], v8bf b, v16f &hi, v16f
     hi = mfma(a[0], b, hi);
     lo = mfma(a[1], b, lo);
 }
-// Sums of a's rows (bias gradients): the leading parts in column 0 of one accumulator, the others in column 1
+// Sums of a's rows (bias gradients), in every column
 struct RowSum {
-    v8bf e0, e1;
-    v16f acc;
-    __device__ __forceinline__ explicit RowSum(int col) : acc{0}
+    v8bf ones;
+    Acc2 acc;
+    __device__ __forceinline__ RowSum() : acc{v16f{0}, v16f{0}}
     {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { e0[e] = (__bf16)(col == 0 ? 1.0f : 0.0f); e1[e] = (__bf16)(col == 1 ? 1.0f : 0.0f); }
+        for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
     }
-    __device__ __forceinline__ void add(const v8bf (&a)[3])
-    {
-        acc = mfma(a[2], e1, acc);
-        acc = mfma(a[1], e1, acc);
-        acc = mfma(a[0], e0, acc);
-    }
-    __device__ __forceinline__ float row(int r) const { return acc[r] + __shfl_xor(acc[r], 1); }   // in columns 0 and 1, by all lanes
+    __device__ __forceinline__ void add(const v8bf (&a)[3]) { mfma3(a, ones, acc.hi, acc.lo); }
+    __device__ __forceinline__ float row(int r) const { return joined(acc.hi[r], acc.lo[r]); }
 };
 
 // ---------------------------------------------------------------------------
@@ -175,7 +181,7 @@ template <int NA, int T> __device__ __forceinline__ void close_sums(const Acc2 (
     for (int t = 0; t < T; ++t) {
         v16f hi = acc[0][t].hi, lo = acc[0][t].lo;
         if constexpr (NA == 2) { hi += acc[1][t].hi; lo += acc[1][t].lo; }
-        sum[t] = hi + lo;
+        sum[t] = joined(hi, lo);
     }
 }
 
@@ -394,7 +400,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             const v4f bias1 = *reinterpret_cast<const v4f *>(bias + 16 * nt + 4 * kg);
             v4f v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = fmaxf((hi[r] + (lo0[r] + lo1[r])) * sc + bias1[r], 0.f);
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(joined(hi[r], lo0[r] + lo1[r]) * sc + bias1[r], 0.f);
             if (m < G::M1) {
                 const Split4 q = split4(v);
                 uint8_t *d = img1 + (y * 20 + (x & 1) * 10 + (x >> 1)) * G::P1 + (16 * nt + 4 * kg) * 2;
@@ -961,8 +967,7 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
     const bf16_t *yp = Ys + trow * LDY + wo * 32 * WM + tcol, *xp = Xs + trow * LDX + wk * 32 * WN + tcol;
     const bool do_bias = bx == 0 && wk == 0;
     Acc2 acc[WM][WN];
-    RowSum accb[WM] = {RowSum(li), RowSum(li)};
-    static_assert(WM == 2, "accb");
+    RowSum accb[WM];
 #pragma unroll
     for (int a = 0; a < WM; ++a) {
 #pragma unroll
@@ -996,7 +1001,7 @@ __device__ __forceinline__ void wgrad_tile(const g32::WgradArgs &A, int bx, int 
         for (int r = 0; r < 16; ++r) {
             const int o = o0 + (wo * WM + a) * 32 + 8 * (r / 4) + 4 * h + (r % 4);
 #pragma unroll
-            for (int b = 0; b < WN; ++b) part[(long)o * G::K + kc0 + (wk * WN + b) * 32 + li] = acc[a][b].hi[r] + acc[a][b].lo[r];
+            for (int b = 0; b < WN; ++b) part[(long)o * G::K + kc0 + (wk * WN + b) * 32 + li] = joined(acc[a][b].hi[r], acc[a][b].lo[r]);
             if (do_bias) {   // uniform for the wave
                 const float v = accb[a].row(r);
                 if (li == 0) part[(long)G::N * G::K + o] = v;
@@ -1093,7 +1098,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
     }
 
     v16f wacc[2] = {v16f{0}, v16f{0}};
-    RowSum accb(i32);
+    RowSum accb;
     const int cp = wave & 3;   // weight gradient: columns 64 cp .. (frame cp)
     const bool do_bias = cp == 0;
 
@@ -1168,7 +1173,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
         for (int t = 0; t < G::T; ++t)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const v16f s = acc[t].hi + acc[t].lo;
+                const v16f s = joined(acc[t].hi, acc[t].lo);
                 const v4f lo = {s[4 * j], s[4 * j + 1], s[4 * j + 2], s[4 * j + 3]};
                 const v4f hi = {s[4 * j + 8], s[4 * j + 9], s[4 * j + 10], s[4 * j + 11]};
                 own[t][j] = kh ? hi : lo;
@@ -1217,8 +1222,8 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
             mfma3(fa, fb[1], wacc[1], lo2[1]);
             if (do_bias) accb.add(fa);
         }
-        wacc[0] += lo2[0];
-        wacc[1] += lo2[1];
+        wacc[0] = joined(wacc[0], lo2[0]);
+        wacc[1] = joined(wacc[1], lo2[1]);
     }
     float bsum[16];
     if (do_bias)   // uniform for the wave
@@ -1233,7 +1238,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const BackArgs &A, 
 #pragma unroll
             for (int r = 0; r < 16; ++r) sf[((cp * 2 + b) * 16 + r) * 64 + lane] = wacc[b][r];
         if (do_bias && i32 == 0) {
-            // (column 0 of the product with ones; conv1's dY is no longer read)
+            // (every column holds the sums; conv1's dY is no longer read)
 #pragma unroll
             for (int r = 0; r < 16; ++r) reinterpret_cast<float *>(img)[16 * h + r] = bsum[r];
         }

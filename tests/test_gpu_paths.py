@@ -226,3 +226,65 @@ def test_fp32_split_products_are_no_less_exact_than_the_fp32_chain(dq, layer, B)
     assert rms["q_s"] < 1e-7   # what was read off is the layer
     assert max(rms["q_next_online"], rms["q_next_target"]) <= rms["q_s"], rms
     m.close()
+
+
+def _positive_network(K):
+    """All weights and biases positive: an infinity anywhere reaches the Q-values as one."""
+    T = {name: np.abs(synth.u24(50 + i, torch.arange(int(np.prod(shape)))).numpy() - 0.5).reshape(shape) + 0.01
+         for i, (name, shape, _) in enumerate(synth.param_spec(K, 0))}
+    return T, lambda: torch.from_numpy(np.concatenate([T[n].astype(np.float32).ravel() for n, _, _ in synth.param_spec(K, 0)]))
+
+
+@pytest.mark.parametrize("where,value", [("conv1.b", np.inf), ("conv1.W", np.inf), ("conv2.W", np.inf), ("conv2.b", np.inf), ("conv3.W", np.inf),
+                                         ("conv2.W", -np.inf), ("conv3.b", np.nan), ("conv1.W", 1e36), (None, 0)])
+def test_infinities_pass_through_the_fp32_conv_layers(dq, where, value):
+    """An infinite weight or activation, or a sum that overflows, is in the split form (acting, the passes over s') what it is
+    in the plain fp32 chain (the pass on s)."""
+    print("case infinities", where, value, flush=True)
+    K = 5
+    T, blob = _positive_network(K)
+    if where:
+        T[where].reshape(-1)[T[where].size // 2 + 3] = value
+    for B in (14, 30, 64):
+        s, _, a, r, d = synth.batch(11, B, K)
+        s = s.clamp(min=1)   # no zero for an infinite weight to meet
+        m = dq.Dqn(dq.make_config(num_actions=K, dueling=0, max_batch=B, max_act_batch=300))
+        for net in (0, 1):
+            m.set_params(net, blob())
+        acted = [m.act(dev(s)[:E].contiguous(), 0.0, 1, want_q=True)[1] for E in (3, B)]
+        acted.append(m.act(dev(s).repeat(300 // B + 1, 1, 1, 1)[:300].contiguous(), 0.0, 1, want_q=True)[1][:B])
+        out = m.train_step(B, tuple(dev(t) for t in (s, s, a, r, d)))
+        ref = out["q_s"]
+        assert bool(torch.isfinite(ref).all()) == (where is None or value < 0 or np.isnan(value))
+        for q in (out["q_next_online"], out["q_next_target"], acted[0], acted[1], acted[2]):
+            x = ref[:q.shape[0]]
+            assert torch.equal(torch.isinf(q), torch.isinf(x)) and torch.equal(torch.isnan(q), torch.isnan(x))
+            fin = torch.isfinite(x)
+            assert bool(((q - x).abs()[fin] <= TOL * x.abs()[fin]).all())
+        m.close()
+
+
+def test_infinite_gradients_of_small_fp32_steps(dq, monkeypatch):
+    """An infinite TD error: the gradients of conv2 and conv1 in the one-launch split form (a batch of 32) and by the layers'
+    own launches (the same planned for fewer compute units) are infinite, and NaN, in the same places."""
+    print("case infinite gradients", flush=True)
+    B, K = 32, 5
+    _, blob = _positive_network(K)
+    s, sn, a, r, d = synth.batch(11, B, K)
+    s = s.clamp(min=1)
+    r[3] = float("inf")
+    got = []
+    for limit in (None, 100):
+        if limit:
+            monkeypatch.setenv("DQN_COMPUTE_UNITS", str(limit))
+        m = dq.Dqn(dq.make_config(num_actions=K, dueling=0, double_q=0, loss_kind=0, max_batch=B))
+        for net in (0, 1):
+            m.set_params(net, blob())
+        m.train_step(B, tuple(dev(t) for t in (s, sn, a, r, d)))
+        got.append(m.get_params(2))
+        m.close()
+    x, y = got
+    assert torch.isinf(y).any()
+    n = 77984   # conv1 to conv3
+    for k, f in (("inf", torch.isinf), ("nan", torch.isnan)):
+        assert torch.equal(f(x[:n]), f(y[:n])), (k, int(f(x[:n]).sum()), int(f(y[:n]).sum()))
