@@ -26,9 +26,10 @@
  *   plain head  : out.W[K][512] out.b[K]
  *   dueling head: V.W[1][512] V.b[1] A.W[K][512] A.b[K]          (Eq.13)
  * The library keeps its parameter buffers in an internal (channel-last)
- * permutation of this blob; only get/set translate.  With precision 1 it also
- * keeps copies of the weights in the shadow and workspace buffers, which only
- * its own calls bring up to date.
+ * permutation of this blob; only get/set translate.  With precision 1 the
+ * shadow buffer holds copies of both networks' weights that the library's own
+ * calls keep up to date: a program that writes the parameter buffers itself (a
+ * copy of all of a context's buffers, say) writes that one along with them.
  */
 #ifndef DQN_H_
 #define DQN_H_
@@ -80,12 +81,14 @@ typedef struct {
 typedef struct {
     size_t params;        /* ONE network's fp32 parameters (online, target: each)  */
     size_t opt_state;     /* RMSProp accumulators                                  */
-    size_t shadow_bf16;   /* bf16 copies of both networks (precision 1)            */
+    size_t shadow_bf16;   /* bf16 copies of both networks' weights (precision 1)   */
     size_t grads;         /* fp32 gradient of the last step                        */
     size_t replay_frames; /* uint8 [capacity][84][84]                              */
     size_t replay_meta;   /* action / reward / terminal flag per slot              */
     size_t tree;          /* sum-tree: float [2L] heap + 64 floats of state        */
-    size_t workspace;     /* activations, partial sums, minibatch staging          */
+    size_t workspace;     /* activations, partial sums, minibatch staging: nothing
+                             in it has to survive between calls, except for
+                             dqn_get_activations                                   */
     int64_t param_count;  /* number of fp32 parameters of one network              */
     int64_t tree_leaves;  /* L = capacity rounded up to a power of two             */
 } dqn_sizes;

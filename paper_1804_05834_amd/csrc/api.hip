@@ -58,8 +58,6 @@ struct Workspace {
     int32_t *b_idx, *b_a;
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
-    gbf::bf16_t *w2t;  // bf16 only: the online conv2 weights as [tap][channel in][channel out] (see misc::k_w2_transposed)
-    uint16_t *packed;  // bf16 only: the conv weights of both networks in the forward launch's order (packed.h)
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -105,8 +103,6 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.qmax_j = (float *)take(MB * 4);
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
-    w.w2t = (gbf::bf16_t *)take(c.precision == 1 ? net::L2N * 2 : 0);
-    w.packed = (uint16_t *)take(c.precision == 1 ? 2 * (size_t)sp::B_TOTAL * 2 : 0);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
     w.act1 = take(rows * net::A1 * es);
@@ -314,14 +310,6 @@ void he_uniform_host(std::vector<float> &blob, int K, int dueling, uint64_t seed
     }
 }
 
-// bf16: the copy of a network's conv weights that the fused forward launch reads
-uint16_t *packed_of(dqn_ctx *c, int net_i) { return c->ws.packed + (net_i ? sp::B_TOTAL : 0); }
-void pack_conv(dqn_ctx *c, int net_i, hipStream_t st)
-{
-    const float *theta = net_i ? c->theta_t : c->theta;
-    launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i)); });
-}
-
 void permute(dqn_ctx *c, const float *src, float *dst, int dir, hipStream_t st)
 {
     launch(c, "permute", st, [&] { misc::k_permute<<<grid1(c->n, 256), 256, 0, st>>>(src, dst, c->n, dir); });
@@ -357,6 +345,22 @@ constexpr size_t SHADOW_AT = 32;   // elements
 size_t shadow_bytes(int64_t n) { return align_up((size_t)n * 2 + SHADOW_AT * 2, 256); }
 static_assert((net::F1W + SHADOW_AT) % 64 == 0 && (net::C2W + SHADOW_AT) % 64 == 0 && (net::C3W + SHADOW_AT) % 64 == 0, "line-aligned weights");
 gbf::bf16_t *shadow_of(dqn_ctx *c, int net) { return (gbf::bf16_t *)c->buf.shadow_bf16 + (net ? shadow_bytes(c->n) / 2 : 0) + SHADOW_AT; }
+// Behind the two copies lie the further forms of the conv weights, so that the buffer holds all that has to agree with the
+// parameters (the workspace nothing that outlives a call): both networks' in the order of the fused forward launch
+// (packed.h), and the online network's conv2 for the input gradient (misc::k_w2_transposed).
+size_t shadow_total_bytes(int64_t n) { return 2 * shadow_bytes(n) + align_up((2 * (size_t)sp::B_TOTAL + 64 * 512) * 2, 256); }
+uint16_t *packed_of(dqn_ctx *c, int net_i) { return (uint16_t *)c->buf.shadow_bf16 + shadow_bytes(c->n) + (net_i ? sp::B_TOTAL : 0); }
+gbf::bf16_t *w2t_of(dqn_ctx *c) { return (gbf::bf16_t *)packed_of(c, 1) + sp::B_TOTAL; }
+static_assert(sp::B_TOTAL % 128 == 0, "256-byte aligned copies");
+// Every copy of a network's parameters, from the parameters
+void refresh_shadow(dqn_ctx *c, int net_i, hipStream_t st)
+{
+    const float *theta = theta_of(c, net_i);
+    launch(c, "to_bf16", st, [&] { misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta, (__hip_bfloat16 *)shadow_of(c, net_i), c->n); });
+    launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i)); });
+    if (net_i == 0)
+        launch(c, "pack_conv", st, [&] { misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(theta + net::C2W, (__hip_bfloat16 *)w2t_of(c)); });
+}
 
 // Launch shapes of the conv1 forward kernel for `samples` samples (all passes), and whether a wave's
 // share of strips spans few enough samples for it to draw them itself.
@@ -805,8 +809,8 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     for (; k < 5; ++k) RA.seg[k].block_begin = 0x7fffffff;  // never selected
     RA.theta = c->theta; RA.v = c->rms_v; RA.m = c->rms_m; RA.g = c->grads;
     RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)shadow_of(c, 0) : nullptr;
-    RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w.w2t : nullptr;
-    RA.packed = w.packed;
+    RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w2t_of(c) : nullptr;
+    RA.packed = cfg.precision == 1 ? packed_of(c, 0) : nullptr;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
     if (last_part && last_part->on) launch(c, "rmsprop", st, [&] { k_rmsprop_pu<<<blk + 1, 256, 0, st>>>(RA, *last_part); });
     else launch(c, "rmsprop", st, [&] { misc::k_rmsprop<<<blk, 256, 0, st>>>(RA); });
@@ -1092,7 +1096,7 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
             // tiles fewer, and the launch runs in one round of workgroups at B = 512
             const int nps = std::min({B, c->num_cu, MAX_WSPLIT1});
             const int nw2 = 4 * gz;
-            dps::FusedArgs F{P, c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, w.w2t};
+            dps::FusedArgs F{P, c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, w2t_of(c)};
             launch(c, "conv21_bwd", st, [&] {
                 k_conv21_bwd_pu<<<nps + nw2 + U.on, 256, dps::FUSED_LDS, st>>>(F, G, nps, nw2, 4, 1, gz, U);
             });
@@ -1125,7 +1129,7 @@ int32_t dqn_query_sizes(const dqn_config *cfg, dqn_sizes *out)
     s.param_count = n;
     s.params = align_up((size_t)n * 4, 256);
     s.opt_state = s.params * (cfg->rms_centered ? 2 : 1);
-    s.shadow_bf16 = cfg->precision == 1 ? 2 * shadow_bytes(n) : 0;
+    s.shadow_bf16 = cfg->precision == 1 ? shadow_total_bytes(n) : 0;
     s.grads = s.params;
     const int64_t cap = cfg->replay_capacity;
     s.replay_frames = (size_t)cap * net::FRAME;
@@ -1209,13 +1213,8 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         misc::k_fill<<<grid1(nt, 256), 256, 0, st>>>(c->tree, 0.f, nt);
         misc::k_fill<<<1, 64, 0, st>>>(c->tree + 2 * c->L, 1.0f, 1);  // maximal priority starts at 1
     }
-    if (cfg->precision == 1) {
-        for (int i = 0; i < 2; ++i)
-            misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta_of(c, i), (__hip_bfloat16 *)shadow_of(c, i), c->n);
-        misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
-        pack_conv(c, 0, st);
-        pack_conv(c, 1, st);
-    }
+    if (cfg->precision == 1)
+        for (int i = 0; i < 2; ++i) refresh_shadow(c, i, st);
     if (cfg->precision == 0) {
         // the launches of the conv layers hold images in LDS
         if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
@@ -1373,11 +1372,7 @@ int32_t dqn_set_params(dqn_ctx *c, int32_t which, const float *src, void *stream
     if (!src || !aligned(src, 16)) return fail(c, DQN_ERR_INVALID_ARG, "dqn_set_params: src is NULL or misaligned");
     hipStream_t st = (hipStream_t)stream;
     permute(c, src, dst, 0, st);
-    if (c->cfg.precision == 1 && which <= 1) {
-        misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(dst, (__hip_bfloat16 *)shadow_of(c, which), c->n);
-        if (which == 0) misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(c->theta + net::C2W, (__hip_bfloat16 *)c->ws.w2t);
-        pack_conv(c, which, st);
-    }
+    if (c->cfg.precision == 1 && which <= 1) refresh_shadow(c, which, st);
     return hip_status(c, "dqn_set_params");
 }
 

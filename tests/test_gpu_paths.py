@@ -288,3 +288,33 @@ def test_infinite_gradients_of_small_fp32_steps(dq, monkeypatch):
     n = 77984   # conv1 to conv3
     for k, f in (("inf", torch.isinf), ("nan", torch.isnan)):
         assert torch.equal(f(x[:n]), f(y[:n])), (k, int(f(x[:n]).sum()), int(f(y[:n]).sum()))
+
+
+@pytest.mark.parametrize("E,B", [(3, 8), (300, 77), (600, 200)])
+def test_bf16_context_from_copied_buffers(dq, E, B):
+    """bf16: the parameter, optimizer and shadow buffers of one context, copied into another's, make it the same network in
+    every launch; nothing in the workspace has to survive from one call to the next."""
+    print("case copied buffers", E, B, flush=True)
+    K = 18
+    cfg = dict(max_batch=B, max_act_batch=E, precision=1, **CONFIGS["dueling_ddqn"])
+    obs, batch = dev(synth.states(31, E)), tuple(dev(t) for t in synth.batch(11, B, K))
+    m, n = dq.Dqn(dq.make_config(seed=7, **cfg)), dq.Dqn(dq.make_config(seed=8, target_seed=9, **cfg))
+    m.train_step(B, batch)
+    for name in ("online", "target", "opt_state", "shadow_bf16"):
+        n._bufs[name].copy_(m._bufs[name])
+    for step in range(3):
+        if step == 2:
+            m.sync_target()
+            n.sync_target()
+        n._bufs["workspace"].fill_(255)
+        a, q = m.act(obs, 0.0, 5, want_q=True)
+        b, p = n.act(obs, 0.0, 5, want_q=True)
+        assert torch.equal(q, p) and torch.equal(a, b), step
+        n._bufs["workspace"].fill_(255)
+        x, y = m.train_step(B, batch), n.train_step(B, batch)
+        for name in x:
+            assert torch.equal(x[name], y[name]), (step, name)
+        for which in (0, 1, 2, 3):
+            assert torch.equal(m.get_params(which), n.get_params(which)), (step, which)
+    m.close()
+    n.close()
