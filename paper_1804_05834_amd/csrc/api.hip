@@ -161,10 +161,12 @@ struct dqn_ctx {
     // INT_MAX: never (the launch needs 140 KB of LDS per workgroup, granted at initialisation)
     int conv12_min = INT32_MAX;
     bool conv123 = false;   // bf16: conv1 to conv3 as one launch for few samples (gbf::c123)
-    // bf16: fc1 forward as 128 x 128 tiles (gbf::f1) from this many rows per launch on; needs 72 KB of LDS
     float *gp4 = nullptr, *gp5 = nullptr;   // where fc1's and the head's weight gradients are written: inside `grads`
     bool fused_bwd = false;   // conv2's input gradient and conv1's weight gradient in one workgroup per sample
-    bool fc1_big = false;
+    // fp32: the conv layers as one launch (sp::k_conv123_fwd, sp::k_conv123_step), conv2's and conv1's gradients too
+    bool split = false;
+    // bf16: fc1 forward as 128 x 128 tiles (gbf::f1) from this many rows per launch on, with four stages in LDS or two
+    bool fc1_four = false;
     int fc1_big_rows = 512, fc1_big_splits = 0;
     hipStream_t side = nullptr;
     hipStream_t side2 = nullptr;  // the single-workgroup priority update gets a lane of its own
@@ -432,12 +434,12 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 // chain; the passes over s', whose activations are only values, take the split form.  At larger ones the last bits of
 // those values reach a decision, or a draw, through the updated parameters and priorities too (one of 30 seeds at 256,
 // two of 20 at 1000): there every pass keeps it.
-int native_passes(const dqn_ctx *c, int B) { return B <= 128 ? 1 : 3; }
+int native_passes(const dqn_ctx *c, int B) { return B <= 128 && c->split ? 1 : 3; }
 // Small batches: the first pass's layers and the split form of the others as units of one launch
 // (sp::k_conv123_step), one workgroup per CU and one round: the others take at least two workgroups per sample, the first
 // pass four (27 us at a batch of 32, the step 85.2), or two where four no longer fit beside them (33 us at 42).  With the
 // first pass as three launches of its own the step took 107.8 us at 32.
-bool step_launch(const dqn_ctx *c, int B) { return 2 * 3 * B <= c->num_cu; }
+bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->num_cu; }
 int step_native_rows(const dqn_ctx *c, int B) { return 8 * B <= c->num_cu ? 2 : 4; }   // rows of conv3 per unit
 int step_native_blocks(const dqn_ctx *c, int B) { return B * (step_native_rows(c, B) == 2 ? 4 : 2); }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not
@@ -485,7 +487,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
     };
 
     // conv1, conv2 and conv3: one launch for the passes [p0, npass)
-    const int p0 = npass == 3 ? native_passes(c, pass[0].n) : 0;
+    const int p0 = npass == 3 ? native_passes(c, pass[0].n) : c->split ? 0 : npass;
     const bool step = npass == 3 && step_launch(c, pass[0].n);   // the first pass in the same launch
     if (p0 < npass) {
         const int samples = (int)(rows - row0[p0]);
@@ -683,7 +685,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
     }
     const bool few_fit = (size_t)rows * FC1_SPLITS <= w.f1rows;
-    if (c->fc1_big && (rows >= c->fc1_big_rows || !few_fit)) {
+    if (rows >= c->fc1_big_rows || !few_fit) {
         // many rows: 128 x 128 tiles, four stages in LDS, few reduction splits
         f1::Args A{};
         A.nseg = npass;
@@ -702,11 +704,13 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         ns = std::max<long>(1, std::min<long>({(long)ns, 7L, (long)(w.f1rows / (size_t)rows)}));
         A.nsplit = ns;
         A.split_stride = rows * net::HID;
-        launch(c, "fc1_fwd", st, [&] { f1::k_fc1_fwd<<<dim3(4 * tile * ns), 256, f1::LDS_BYTES, st>>>(A); });
+        launch(c, "fc1_fwd", st, [&] {
+            if (c->fc1_four) f1::k_fc1_fwd<4><<<dim3(4 * tile * ns), 256, f1::lds_bytes<4>(), st>>>(A);
+            else f1::k_fc1_fwd<2><<<dim3(4 * tile * ns), 256, f1::lds_bytes<2>(), st>>>(A);
+        });
         *nsplit_out = ns;
         *split_stride_out = rows * net::HID;
     } else {
-        if (!few_fit) return fail(c, DQN_ERR_STATE, "forward: no fc1 kernel for this many rows");
         FwdArgs A{};
         int tile = 0;
         A.nseg = npass;
@@ -1215,19 +1219,6 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
     }
     if (cfg->precision == 1)
         for (int i = 0; i < 2; ++i) refresh_shadow(c, i, st);
-    if (cfg->precision == 0) {
-        // the launches of the conv layers hold images in LDS
-        if (hipFuncSetAttribute((const void *)k_conv21_bwd_sp, hipFuncAttributeMaxDynamicSharedMemorySize, CONV21_LDS) != hipSuccess ||
-            hipFuncSetAttribute((const void *)sp::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<4>::LDS) != hipSuccess ||
-            hipFuncSetAttribute((const void *)sp::k_conv123_step<1, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<1, 2>()) != hipSuccess ||
-            hipFuncSetAttribute((const void *)sp::k_conv123_step<4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<4, 2>()) != hipSuccess ||
-            hipFuncSetAttribute((const void *)sp::k_conv123_step<4, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::step_lds<4, 4>()) != hipSuccess ||
-            hipFuncSetAttribute((const void *)sp::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, sp::Geo<7>::LDS) != hipSuccess) {
-            (void)hipGetLastError();
-            delete c;
-            return fail(nullptr, DQN_ERR_HIP, "dqn_init: the device does not grant the forward kernel its LDS");
-        }
-    }
     if (hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) {
         delete c;
         return fail(nullptr, DQN_ERR_HIP, "dqn_init: device initialisation failed");
@@ -1242,42 +1233,33 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         const char *m = std::getenv("DQN_COMPUTE_UNITS");
         if (m && m[0]) c->num_cu = std::max(1, std::min(c->num_cu, std::atoi(m)));
     }
-    // DQN_CONV12_MIN_SAMPLES in the environment moves the batch size from which the fused conv1 + conv2
-    // forward launch is used (samples of all passes of a launch; a huge value switches it off)
-    if (cfg->precision == 1 &&
-        hipFuncSetAttribute((const void *)gbf::c12::k_conv12_fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            gbf::c12::LDS_BYTES) == hipSuccess) {
+    // The launches that hold images or several stages in LDS.  Each has another form for where its LDS is not granted (or
+    // DQN_SMALL_LDS=1 in the environment refuses it): the layers' own launches, or fewer stages.
+    const char *small_lds = std::getenv("DQN_SMALL_LDS");
+    auto granted = [&](auto *kernel, int bytes) {
+        if (small_lds && small_lds[0] == '1') return false;
+        if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
+    };
+    if (cfg->precision == 0) {
+        c->split = granted(sp::k_conv123_fwd<1>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<4>, sp::Geo<4>::LDS) &&
+                   granted(sp::k_conv123_fwd<7>, sp::Geo<7>::LDS) && granted(sp::k_conv123_step<1, 2>, sp::step_lds<1, 2>()) &&
+                   granted(sp::k_conv123_step<4, 2>, sp::step_lds<4, 2>()) && granted(sp::k_conv123_step<4, 4>, sp::step_lds<4, 4>()) &&
+                   granted(k_conv21_bwd_sp, CONV21_LDS);
+    } else {
+        // DQN_CONV12_MIN_SAMPLES in the environment moves the number of samples (of all passes of a launch) from which
+        // conv1 + conv2 are one launch, in the form without the three-layer launch; a huge value: never
         const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");
-        c->conv12_min = m && m[0] ? std::atoi(m) : 8;
-    } else {
-        (void)hipGetLastError();
-    }
-    if (cfg->precision == 1 &&
-        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<1>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<1>::LDS) == hipSuccess &&
-        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<4>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<4>::LDS) == hipSuccess &&
-        hipFuncSetAttribute((const void *)gbf::c123::k_conv123_fwd<7>, hipFuncAttributeMaxDynamicSharedMemorySize, gbf::c123::Geo<7>::LDS) == hipSuccess) {
-        const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");   // asks for the two-launch form at every size
-        c->conv123 = !(m && m[0]);
-    } else {
-        (void)hipGetLastError();
-    }
-    // DQN_FUSED_BWD=0 in the environment keeps conv1's weight gradient a launch of its own
-    if (cfg->precision == 1 &&
-        hipFuncSetAttribute((const void *)k_conv21_bwd_pu, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            gbf::dps::FUSED_LDS) == hipSuccess) {
-        const char *m = std::getenv("DQN_FUSED_BWD");
-        c->fused_bwd = !(m && m[0] == '0');
-    } else {
-        (void)hipGetLastError();
-    }
-    if (cfg->precision == 1 &&
-        hipFuncSetAttribute((const void *)gbf::f1::k_fc1_fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            gbf::f1::LDS_BYTES) == hipSuccess) {
-        c->fc1_big = true;
-        if (const char *m = std::getenv("DQN_FC1_BIG_ROWS")) if (m[0]) c->fc1_big_rows = std::atoi(m);
-        if (const char *m = std::getenv("DQN_FC1_SPLITS")) if (m[0]) c->fc1_big_splits = std::atoi(m);
-    } else {
-        (void)hipGetLastError();
+        if (granted(gbf::c12::k_conv12_fwd, gbf::c12::LDS_BYTES)) c->conv12_min = m && m[0] ? std::atoi(m) : 8;
+        c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1>, gbf::c123::Geo<1>::LDS) &&
+                     granted(gbf::c123::k_conv123_fwd<4>, gbf::c123::Geo<4>::LDS) && granted(gbf::c123::k_conv123_fwd<7>, gbf::c123::Geo<7>::LDS);
+        // DQN_FUSED_BWD=0 in the environment keeps conv1's weight gradient a launch of its own
+        m = std::getenv("DQN_FUSED_BWD");
+        c->fused_bwd = !(m && m[0] == '0') && granted(k_conv21_bwd_pu, gbf::dps::FUSED_LDS);
+        c->fc1_four = granted(gbf::f1::k_fc1_fwd<4>, gbf::f1::lds_bytes<4>());
+        if (const char *e = std::getenv("DQN_FC1_BIG_ROWS")) if (e[0]) c->fc1_big_rows = std::atoi(e);
+        if (const char *e = std::getenv("DQN_FC1_SPLITS")) if (e[0]) c->fc1_big_splits = std::atoi(e);
     }
     // side stream at the default priority; if anything fails the step simply runs on one stream
     // (DQN_SINGLE_STREAM=1 in the environment keeps everything on the caller's stream)

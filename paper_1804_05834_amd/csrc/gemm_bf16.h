@@ -242,9 +242,9 @@ __device__ __forceinline__ int tile_of(int u, int total)
 // ---------------------------------------------------------------------------
 namespace f1 {
 constexpr int BM = 128, BN = 128;
-constexpr int NBUF = 4;                          // stages in LDS
 constexpr int TILE = BM * BK;                    // elements of one operand tile in LDS
-constexpr int LDS_BYTES = 2 * NBUF * TILE * 2;   // 131,072 bytes: one workgroup per CU
+// NBUF: stages in LDS.  Four are 131,072 bytes: one workgroup per CU; two are what a workgroup gets without asking.
+template <int NBUF> constexpr int lds_bytes() { return 2 * NBUF * TILE * 2; }
 constexpr int STAGES = GFc1::K / BK;             // 49
 
 struct Args {
@@ -271,8 +271,10 @@ __device__ __forceinline__ void to_lds(const bf16_t *g, bf16_t *p)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory");
 }
 
+template <int NBUF>
 __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
 {
+    static_assert(NBUF % 2 == 0 && NBUF <= 4, "register sets alternate by buffer; ready() counts");
     extern __shared__ __attribute__((aligned(16))) bf16_t lds[];   // [operand][buffer][row][BK], pieces in permuted places
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int t = tile_of(blockIdx.x, gridDim.x);
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
 #pragma unroll
     for (int s = 0; s < 4; ++s) F[0][s] = rd(0, s);
     ready((n < NBUF ? n : NBUF) - 2);                              // stage 1, and buffer 0 is free
-    // Stage i, whose operands are in registers: stage i + 1 goes from LDS to registers meanwhile and stage i + 4 is
+    // Stage i, whose operands are in registers: stage i + 1 goes from LDS to registers meanwhile and stage i + NBUF is
     // requested into the buffer that stage i was read from.
     auto stage = [&](int i, int buf) {
         Frag (&C)[4] = F[buf & 1], (&X)[4] = F[(buf & 1) ^ 1];
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
             acc[1][1] = mfma(C[s].b[1], C[s].a[1], acc[1][1]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        ready(n - 3 - i < 2 ? n - 3 - i : 2);
+        ready(n - 3 - i < NBUF - 2 ? n - 3 - i : NBUF - 2);
     };
     for (int i = 0; i < n; i += NBUF)
 #pragma unroll
@@ -369,8 +371,8 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
     // acc[a][b][4g + j] = Y[row block a, lane li][column block b, 8g + 4h + j].  The tile leaves through LDS
     // (the operand buffers are no longer read: the loop ends on a barrier), so that it is written as whole
     // 512-byte rows, two per wave and instruction, instead of 32-byte pieces of 32 different rows.
-    constexpr int LDO = BN + 4;                   // fp32 row stride of the staged output tile
-    static_assert(BM * LDO * 4 <= LDS_BYTES, "the output tile is staged in the operand buffers");
+    constexpr int LDO = NBUF == 4 ? BN + 4 : BN;  // fp32 row stride of the staged output tile
+    static_assert(BM * LDO * 4 <= lds_bytes<NBUF>(), "the output tile is staged in the operand buffers");
     float *ot = reinterpret_cast<float *>(lds);
 #pragma unroll
     for (int a = 0; a < 2; ++a)

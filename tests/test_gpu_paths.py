@@ -318,3 +318,39 @@ def test_bf16_context_from_copied_buffers(dq, E, B):
             assert torch.equal(m.get_params(which), n.get_params(which)), (step, which)
     m.close()
     n.close()
+
+
+@pytest.mark.parametrize("prec,E,B", [(0, 1, 5), (0, 130, 32), (0, 40, 100), (1, 3, 33), (1, 2100, 77)])
+def test_launches_with_no_more_lds_than_every_workgroup_gets(dq, orc, monkeypatch, prec, E, B):
+    print("case small lds", prec, E, B, flush=True)
+    monkeypatch.setenv("DQN_SMALL_LDS", "1")
+    K, tol = 18, TOL_BF16 if prec else TOL
+    m = dq.Dqn(dq.make_config(num_actions=K, dueling=1, max_act_batch=E, precision=prec))
+    p = synth.he_uniform_params(3 + K, K, 1, bias_scale=0.05)
+    m.set_params(0, torch.from_numpy(p))
+    obs = synth.states(31, E)
+    q = m.act(dev(obs), 0.0, 99, want_q=True)[1].cpu().numpy()
+    rows = np.unique(np.linspace(0, E - 1, 200).astype(int))
+    ref = orc.forward(p, K, 1, obs.numpy()[rows], quant=prec)
+    assert relerr(q[rows], ref) <= tol
+    if E <= 32:
+        assert np.array_equal(m.act(dev(obs), 0.0, 99, want_q=True, static=True)[1].cpu().numpy(), q)
+    m.close()
+    _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41, tol=tol, prec=prec)
+
+
+def test_fc1_with_two_and_four_stages_in_lds(dq, monkeypatch):
+    """bf16, 750 samples in each of three passes: the same sums whatever the number of stages, behind the same conv launches."""
+    print("case fc1 stages", flush=True)
+    B, K, got = 750, 18, []
+    batch = tuple(dev(t) for t in synth.batch(11, B, K))
+    monkeypatch.setenv("DQN_CONV12_MIN_SAMPLES", "1000000")
+    monkeypatch.setenv("DQN_FUSED_BWD", "0")
+    for small in ("0", "1"):
+        monkeypatch.setenv("DQN_SMALL_LDS", small)
+        m = dq.Dqn(dq.make_config(max_batch=B, precision=1, seed=7, **CONFIGS["dueling_ddqn"]))
+        out = m.train_step(B, batch)
+        got.append([out[k] for k in ("q_s", "q_next_online", "q_next_target", "td")] + [m.get_params(2)])
+        m.close()
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
