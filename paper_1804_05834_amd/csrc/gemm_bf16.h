@@ -268,7 +268,9 @@ __device__ __forceinline__ void lds_barrier()
 __device__ __forceinline__ void to_lds(const bf16_t *g, bf16_t *p)
 {
     const uint32_t at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)p);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(g) : "memory");
+    uint32_t m0;   // left as it was: the compiler may hold something in it, and it is no register to declare as clobbered
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(at), "v"(g) : "memory");
 }
 
 template <int NBUF>
