@@ -92,15 +92,7 @@ __device__ __forceinline__ uint4 ld8(const uint8_t *p)  // 8 pixels -> 8 bf16 (e
     return r;
 }
 
-// Barrier that orders LDS traffic only: global loads and stores issued earlier stay in flight
-// across it (__syncthreads() would wait for all of them first).
-__device__ __forceinline__ void sync_lds()
-{
-    // written with the builtins so that the compiler's own wait counting knows that every LDS operation
-    // of the wave has completed here (behind an inline-asm barrier it waits for all of them again)
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-}
+using g32::sync_lds;
 
 __device__ __forceinline__ v8bf frag_k(const bf16_t *p)  // 8 consecutive k of one row
 {
@@ -255,14 +247,6 @@ struct Args {
     long split_stride;  // elements between the partial sums of consecutive splits
 };
 
-// Barrier that orders LDS traffic only, written with the builtins so that the compiler's own wait
-// counting knows that every LDS operation of the wave has completed at this point.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-}
-
 // 16 bytes per lane from memory to LDS, lane l's to p + 8 l, past the registers.  In assembly, because the compiler
 // would let every LDS read behind it wait for its arrival; `ready` waits for what a stage needs.
 __device__ __forceinline__ void to_lds(const bf16_t *g, bf16_t *p)
@@ -329,7 +313,7 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
         else if (later == 2) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         else if (later == 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        lds_barrier();
+        sync_lds();
     };
 
 #pragma unroll
@@ -384,7 +368,7 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
             for (int g = 0; g < 4; ++g)
                 *reinterpret_cast<v4f *>(&ot[((wm * 2 + a) * 32 + li) * LDO + (wn * 2 + b) * 32 + 8 * g + 4 * h]) =
                     v4f{acc[a][b][4 * g], acc[a][b][4 * g + 1], acc[a][b][4 * g + 2], acc[a][b][4 * g + 3]};
-    lds_barrier();
+    sync_lds();
     float *y = static_cast<float *>(S.y) + (long)bz * A.split_stride;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {

@@ -34,11 +34,16 @@ __device__ __forceinline__ v16f mfma(float a, float b, v16f c)
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// A barrier that waits for the wave's LDS operations only: the loads of the stages ahead stay in flight
+// A barrier that orders LDS accesses only: global loads and stores issued before it stay in flight across it
+// (__syncthreads() would wait for all of them first).  The wait is written with the builtin so that the compiler's own
+// counting knows that every LDS operation of the wave has completed here (behind an inline-asm barrier it waits for all of
+// them again); the fences keep it from moving LDS accesses across, which the two builtins alone do not forbid.
 __device__ __forceinline__ void sync_lds()
 {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ v4f ld4(const float *p) { return *reinterpret_cast<const v4f *>(p); }
