@@ -498,11 +498,8 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         sp::Args A{};
         A.nseg = npass - p0;
         for (int i = p0; i < npass; ++i) {
-            // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
-            const bool keep = npass == 3 && i == 0;
             A.seg[i - p0] = sp::Seg{gbf::c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub},
-                                    theta_of(c, pass[i].net), keep ? (float *)w.act1 : nullptr, keep ? (float *)w.act2 : nullptr, act3 + row0[i] * net::A3,
-                                    pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts};
+                                    theta_of(c, pass[i].net), act3 + row0[i] * net::A3, pass[i].n, (int)(row0[i] - row0[p0]) * plan.parts};
         }
         for (int i = A.nseg; i < 3; ++i) A.seg[i] = A.seg[0];
         A.units = samples * plan.parts;

@@ -117,7 +117,7 @@ struct RowSum {
 // conv1, conv2 and conv3 forward in ONE launch.  A unit is the part of a sample that yields R3 of the seven
 // output rows of conv3 (R3 = 7: the whole sample): it needs R3 + 2 rows of conv2 and 2 R3 + 6 rows of conv1.
 // One workgroup of eight waves works on a unit at a time and keeps everything between the pixels
-// and conv3's output in LDS; only the rows the backward pass reads also go to memory.
+// and conv3's output in LDS.
 //   pixels    read from the ring (or the states) and staged as bf16 (exact)
 //   conv1     16x16x32: wave = (channel half, every fourth tile of 16 pixels), the wave's weights in registers
 //   conv2/3   32x32x16: wave = (channel half, quarter of the reduction), every weight
@@ -143,7 +143,6 @@ struct RowSum {
 struct Seg {
     gbf::c1::Src src;
     const float *theta;          // the network's parameters
-    float *y1, *y2;              // conv1 / conv2 output for the backward pass, or nullptr
     float *y3;
     int n;
     int first;                   // first unit of the segment
@@ -152,7 +151,7 @@ struct Args {
     Seg seg[3];
     int nseg;
     int units;                   // of all segments
-    int draw;                    // segment samples are drawn here (every segment has the same n)
+    int draw;                    // the samples are drawn from the ring here (every segment has the same n), or are states
     misc::SampleArgs samp;
 };
 constexpr int MAX_UNITS = 96;    // units of one workgroup at most
@@ -278,38 +277,30 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
 
     int u = bid;
     int si = seg_of(u);
-    const bool ring = A.seg[0].src.idx != nullptr;   // of every segment, or of none
     // (scalar loads: a select over the three segments' arguments became a table in scratch memory)
     const uint8_t *x0 = SP_SEG(si).src.x;
     const long xs0 = SP_SEG(si).src.xs;
     const int shift0 = SP_SEG(si).src.shift, first0 = SP_SEG(si).first;
-    // The first pixels before the weights, which are twenty times as many bytes, where their slot is known; drawing
+    // The first pixels before the weights, which are twenty times as many bytes, where they are known; drawing
     // comes first otherwise, with the weights on their way
-    if (!ring) load_px(x0, xs0, shift0, first0, u, 0);
+    if (!A.draw) load_px(x0, xs0, shift0, first0, u, 0);
     load_w1(SP_SEG(si).theta);
-    if (ring) {
-        if (A.draw) {
+    if (A.draw) {
 #pragma unroll 1
-            for (int k = 2 * wave; k < nu; k += 16) {
-                const int kb = k + 1 < nu ? k + 1 : k;
-                // (draw j of a segment is its sample j)
-                const int ga = (u + k * G0) / G::PARTS, gb = (u + kb * G0) / G::PARTS, n = A.seg[0].n;
-                const int jj[2] = {ga % n, gb % n};
-                long sl[2];
-                float leaf[2];
-                const float total = misc::per_sample_walk<2>(A.samp, jj, lane, sl, leaf);
-                if (lane == 0) {
-                    slots[k] = (int)sl[0];
-                    slots[kb] = (int)sl[1];
-                    leafv[k] = leaf[0];
-                    leafv[kb] = leaf[1];
-                    if (k == 0) leafv[MAX_UNITS] = total;
-                }
-            }
-        } else {
-            for (int k = tid; k < nu; k += 512) {
-                // (the segments' index lists are one and the same)
-                slots[k] = A.seg[0].src.idx[(u + k * G0) / G::PARTS % A.seg[0].n];
+        for (int k = 2 * wave; k < nu; k += 16) {
+            const int kb = k + 1 < nu ? k + 1 : k;
+            // (draw j of a segment is its sample j)
+            const int ga = (u + k * G0) / G::PARTS, gb = (u + kb * G0) / G::PARTS, n = A.seg[0].n;
+            const int jj[2] = {ga % n, gb % n};
+            long sl[2];
+            float leaf[2];
+            const float total = misc::per_sample_walk<2>(A.samp, jj, lane, sl, leaf);
+            if (lane == 0) {
+                slots[k] = (int)sl[0];
+                slots[kb] = (int)sl[1];
+                leafv[k] = leaf[0];
+                leafv[kb] = leaf[1];
+                if (k == 0) leafv[MAX_UNITS] = total;
             }
         }
         sync_lds();   // the slot table is complete
@@ -370,7 +361,6 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             for (int q = 0; q < 2; ++q) wr[q] = *reinterpret_cast<const v4f *>(tw + i32 * 64 + (((2 * h + q) ^ ((lane >> 2) & 3)) * 16));
         };
         const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2 and conv3
-        float *const y1 = SP_SEG(si).y1, *const y2 = SP_SEG(si).y2;
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- conv1
@@ -406,8 +396,6 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 uint8_t *d = img1 + (y * 20 + (x & 1) * 10 + (x >> 1)) * G::P1 + (16 * nt + 4 * kg) * 2;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 64) = q.p[pl];
-                if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
-                    *reinterpret_cast<v4f *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 16 * nt + 4 * kg) = v;
             }
         };
         auto load_w2 = [&] {
@@ -485,7 +473,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             const v4f bias2 = *reinterpret_cast<const v4f *>(bias + 32 + co);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int m = 32 * t + i32, y = m / 9;
+                const int m = 32 * t + i32;
                 v4f v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = fmaxf(own[t][r] + bias2[r], 0.f);
@@ -494,8 +482,6 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                     uint8_t *d = img2 + m * G::P2 + co * 2;
 #pragma unroll
                     for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2 *>(d + pl * 128) = q.p[pl];
-                    if (y2 && row0 + y >= rowp + G::R2)
-                        *reinterpret_cast<v4f *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + co) = v;
                 }
             }
         }
@@ -504,7 +490,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         // have to keep their old contents until here)
         const int kn = k + 1 < nu ? k + 1 : k, un = bid + kn * G0, sn = seg_of(un);
         if constexpr (G::MANY) load_w1(SP_SEG(sn).theta);
-        if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, ring ? slots[kn] : 0);
+        if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, A.draw ? slots[kn] : 0);
         sync_lds();
 
         // ---- conv3: steps 9 kq .. 9 kq + 8 of 36
@@ -662,8 +648,7 @@ __device__ __forceinline__ void conv123_native_body(const NatArgs &A, const bool
             raw[i] = *reinterpret_cast<const u32x4 *>(fp + (t - k * G::CH) * 16);
         }
     };
-    const bool ring = A.src.idx != nullptr;
-    if (!ring) load_px(0);
+    if (!draw) load_px(0);
     const int nt = wave & 1, tg = wave >> 1;
     // conv1's weights, an eighth per wave: fragment f = channel half f / 16; frame and kernel rows of pair f % 16 / 2,
     // columns 4 (f % 2) ..; through LDS to the four waves that want them
@@ -676,20 +661,16 @@ __device__ __forceinline__ void conv123_native_body(const NatArgs &A, const bool
     const v4f bias1 = *reinterpret_cast<const v4f *>(A.b1 + 16 * nt + 4 * kg);
     const v4f bias2 = *reinterpret_cast<const v4f *>(A.b2 + 16 * (wave & 3) + 4 * kg);
     const v4f bias3 = *reinterpret_cast<const v4f *>(A.b3 + 16 * (wave & 3) + 4 * kg);
-    if (ring) {
-        if (draw) {
-            if (wave == 0) {
-                const int jj[2] = {g, g};
-                long sl[2];
-                float leaf[2];
-                misc::per_sample_walk<2>(samp, jj, lane, sl, leaf);
-                if (lane == 0) slot_tab[0] = (int)sl[0];
-            }
-            sync_lds();
-            load_px(slot_tab[0]);
-        } else {
-            load_px(A.src.idx[g]);
+    if (draw) {
+        if (wave == 0) {
+            const int jj[2] = {g, g};
+            long sl[2];
+            float leaf[2];
+            misc::per_sample_walk<2>(samp, jj, lane, sl, leaf);
+            if (lane == 0) slot_tab[0] = (int)sl[0];
         }
+        sync_lds();
+        load_px(slot_tab[0]);
     }
     const int ch = wave & 1, kq = wave >> 1;
     v4f *wl = reinterpret_cast<v4f *>(img1);

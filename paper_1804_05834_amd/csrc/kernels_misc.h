@@ -550,11 +550,16 @@ __global__ __launch_bounds__(256, ROWS == 1 ? 1 : 3) void k_head_act(HeadActArgs
 }
 // Four rows per workgroup from four observations per CU on, where a workgroup each no longer fits the chip at once
 // (1024 in six splits: 4.5 against 5.0 us, 600 in seven: 5.1 against 4.5), and for heads of at most 32 rows, whose
-// weights fit in registers.  Three workgroups fit a CU.
+// weights fit in registers (beside the partial sums of up to six splits; that many rows have seven only where they are
+// asked for).  Three workgroups fit a CU.
 template <int NS> void launch_head_act_ns(const HeadActArgs &H, int num_cu, hipStream_t st)
 {
-    if (H.E >= 4 * num_cu && H.K + (H.dueling ? 1 : 0) <= 32) k_head_act<NS, 4><<<min((H.E + 3) / 4, 3 * num_cu), 256, 0, st>>>(H);
-    else k_head_act<NS, 1><<<H.E, 256, 0, st>>>(H);
+    if constexpr (NS <= 6)
+        if (H.E >= 4 * num_cu && H.K + (H.dueling ? 1 : 0) <= 32) {
+            k_head_act<NS, 4><<<min((H.E + 3) / 4, 3 * num_cu), 256, 0, st>>>(H);
+            return;
+        }
+    k_head_act<NS, 1><<<H.E, 256, 0, st>>>(H);
 }
 // the launch for a run-time number of splits
 inline void launch_head_act(const HeadActArgs &H, int num_cu, hipStream_t st)
