@@ -431,14 +431,17 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 // way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
 // one such decision moves a gradient by 1e-4 to 7e-2 of its norm (first steps with the split form in every pass: 9 of 300
 // at 32 and 6 of 150 at 42 beyond 1e-4; with the first pass in this order 0 of them, and 2 after three steps).  Every batch therefore keeps it for the first pass, so that its results stay those of the plain fp32
-// chain; the passes over s', whose activations are only values, take the split form.  At larger ones the last bits of
-// those values reach a decision, or a draw, through the updated parameters and priorities too (one of 30 seeds at 256,
-// two of 20 at 1000): there every pass keeps it.
+// chain; the passes over s', whose activations are only values, take the split form up to a batch of 128.  Their last bits
+// reach a decision only through the updated parameters: of 540 first steps at 43 to 128 none differs by 1e-4 between the two
+// forms of s', of second steps 0 of 150 at 43, 2 of 150 at 64, 2 and 3 of 120 at 100 and 128; at 256 2 of 60, and at 1000,
+// with a draw through the updated priorities, 2 of 20.  Above 128 every pass keeps the fp32 chain.  A step with the split
+// form takes 125.5 us at 43, 134 at 64, 154 at 80, 191 at 128 and would take 248 at 200; with the chain in every pass
+// 121, 134.5, 168, 207 and 259.
 int native_passes(const dqn_ctx *c, int B) { return B <= 128 && c->split ? 1 : 3; }
 // Small batches: the first pass's layers and the split form of the others as units of one launch
 // (sp::k_conv123_step), one workgroup per CU and one round: the others take at least two workgroups per sample, the first
-// pass four (27 us at a batch of 32, the step 85.2), or two where four no longer fit beside them (33 us at 42).  With the
-// first pass as three launches of its own the step took 107.8 us at 32.
+// pass four (27 us at a batch of 32, the step 85), or two where four no longer fit beside them (33 us at 42).  With the
+// first pass as three launches of its own the step took 108 us at 32.
 bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->num_cu; }
 int step_native_rows(const dqn_ctx *c, int B) { return 8 * B <= c->num_cu ? 2 : 4; }   // rows of conv3 per unit
 int step_native_blocks(const dqn_ctx *c, int B) { return B * (step_native_rows(c, B) == 2 ? 4 : 2); }
@@ -935,7 +938,10 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
         }
         if (step_launch(c, B)) {
             // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample
-            // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient
+            // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient.  5/8 is a
+            // fifth of 32 samples each; for 33 to 42 more workgroups would still fit one round beside fewer tiles: capped
+            // at 210 instead of 160 a step takes 92.1 instead of 96.6 us at 33, 93.1 / 98.6 at 36, 96.5 / 100.6 at 40 and
+            // 98.9 / 100.4 at 42; with 128 the same as with 160, at 32 82.1 with any
             const int nps = std::min({BACK_PARTS * B, std::max(1, c->num_cu * 5 / 8), MAX_WSPLIT1});
             const int splits = std::max(1, std::min<int>(MAX_WSPLIT, (c->num_cu - nps - U.on) / 2));
             const long rows = (long)B * 81;
@@ -1757,7 +1763,8 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     // weight gradient and the priority update to another; they join again before the optimizer.
     // Their kernels are long enough (50-120 us) to repay the events; everything else stays on st
     // with one backward launch per layer.
-    // measured: 645 against 665 us/step at B = 512 with the streams, 547 against 536 at 384, 277 against 245 at 128
+    // measured, one stream against three: 436 / 454 us per step at 384, 497 / 502 at 448, 527 / 531 at 480, 562 / 545 at 512,
+    // 672 / 650 at 640, 823 / 795 at 768, 993 / 961 at 1000
     const bool multi = c->side && cfg.precision == 0 && B > 448;
     hipStream_t sd = multi ? c->side : st;
     hipStream_t sp = multi ? (c->side2 ? c->side2 : c->side) : st;

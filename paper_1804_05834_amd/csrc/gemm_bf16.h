@@ -1877,8 +1877,10 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
 //
 // A unit is the part of a sample that yields R3 of conv3's seven output rows (see sp::k_conv123_fwd, the fp32
 // form of this kernel: same units, same phases).  One workgroup of eight waves takes a unit through all
-// three layers in LDS, phase by phase, every wave in the same phase; all weights stay in registers (200),
-// taken once per workgroup from the packed copy.  16x16x32 instructions, transposed tiles:
+// three layers in LDS, phase by phase, every wave in the same phase; the weights stay in registers (200),
+// taken once per workgroup from the packed copy.  With R3 = 7 they do not all fit beside the next unit's pixels: 42 registers
+// are spilled, and a workgroup with a single unit still loads "its next" one's pixels, its own once more (conv launch of a
+// step at 77: 15 of 65 us; R3 = 1 and 4 take one unit and spill nothing).  16x16x32 instructions, transposed tiles:
 //   conv1   wave = every eighth tile of 16 pixels, all 32 channels: a pixel fragment serves two products
 //   conv2/3 wave = 16 channels, half of the tiles: the sum over the taps stays in one wave
 // k_conv12_fwd overlaps conv1 of one sample with conv2 of another and is as fast per sample once it runs, but it

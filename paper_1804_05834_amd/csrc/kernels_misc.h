@@ -424,7 +424,7 @@ struct HeadActArgs {
 // time, built like the training head: every global operand (the partial sums of the thread's two
 // hidden units per row, the biases, the head weights of the first 32 dot products, spread over groups of 16 lanes)
 // is requested before anything is waited for, the dueling combine (Eq.13) and the argmax run on one wave per row
-// with lane a holding action a, and the arithmetic is that of k_head_train, so Q(s, .) has the same bits
+// with lane a holding action a, and the arithmetic is that of k_head_train: the same partial sums give the same Q(s, .)
 // here and there.  NS: reduction splits of fc1 (A.nsplit), a template argument so that the loads are
 // unconditional.
 // With a workgroup per observation, 8192 of them fetched the head's weights, 39 KB at 18 actions, 8192 times and took
