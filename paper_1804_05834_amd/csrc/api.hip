@@ -424,25 +424,25 @@ bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
     }
     return true;
 }
+// Small batches: the first pass's layers and the split form of the others as units of one launch
+// (sp::k_conv123_step), one workgroup per CU and one round: the others take at least two workgroups per sample, the first
+// pass four (27 us at a batch of 32, the step 85), or two where four no longer fit beside them (33 us at 42).  With the
+// first pass as three launches of its own the step took 108 us at 32.
+bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->num_cu; }
 // fp32 training: how many of the step's passes keep the order of summation of the fp32 matrix instruction instead
 // of the split form (gemm_split.h)?
 // The stored activations of the first pass (on s) are what the ReLU decisions of the backward pass are taken on.
 // About one pre-activation in ten million is zero to within the rounding of its sum, and falls the other
 // way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
 // one such decision moves a gradient by 1e-4 to 7e-2 of its norm (first steps with the split form in every pass: 9 of 300
-// at 32 and 6 of 150 at 42 beyond 1e-4; with the first pass in this order 0 of them, and 2 after three steps).  Every batch therefore keeps it for the first pass, so that its results stay those of the plain fp32
-// chain; the passes over s', whose activations are only values, take the split form up to a batch of 128.  Their last bits
+// at 32 and 6 of 150 at 42 beyond 1e-4; with the first pass in this order 0 of them, and 2 after three steps).  Every batch
+// therefore keeps it for the first pass, so that its results stay those of the plain fp32 chain; the passes over s', whose activations are only values, take the split form up to a batch of 128.  Their last bits
 // reach a decision only through the updated parameters: of 540 first steps at 43 to 128 none differs by 1e-4 between the two
 // forms of s', of second steps 0 of 150 at 43, 2 of 150 at 64, 2 and 3 of 120 at 100 and 128; at 256 2 of 60, and at 1000,
-// with a draw through the updated priorities, 2 of 20.  Above 128 every pass keeps the fp32 chain.  A step with the split
-// form takes 125.5 us at 43, 134 at 64, 154 at 80, 191 at 128 and would take 248 at 200; with the chain in every pass
-// 121, 134.5, 168, 207 and 259.
-int native_passes(const dqn_ctx *c, int B) { return B <= 128 && c->split ? 1 : 3; }
-// Small batches: the first pass's layers and the split form of the others as units of one launch
-// (sp::k_conv123_step), one workgroup per CU and one round: the others take at least two workgroups per sample, the first
-// pass four (27 us at a batch of 32, the step 85), or two where four no longer fit beside them (33 us at 42).  With the
-// first pass as three launches of its own the step took 108 us at 32.
-bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->num_cu; }
+// with a draw through the updated priorities, 2 of 20.  Above 128 every pass keeps the fp32 chain.  So it does below 60
+// where the split form would be a launch of its own: a step with it takes 124.5 us at 43, 125 at 48, 131.5 at 54, 133.3 at
+// 60, 154 at 80, 191 at 128 (and would take 248 at 200); with the chain in every pass 120, 120.5, 128, 133.4, 168, 207 (259).
+int native_passes(const dqn_ctx *c, int B) { return c->split && (step_launch(c, B) || (B >= 60 && B <= 128)) ? 1 : 3; }
 int step_native_rows(const dqn_ctx *c, int B) { return 8 * B <= c->num_cu ? 2 : 4; }   // rows of conv3 per unit
 int step_native_blocks(const dqn_ctx *c, int B) { return B * (step_native_rows(c, B) == 2 ? 4 : 2); }
 // Can the first forward kernel of a replay-mode step of batch B draw the transitions itself?  If not

@@ -36,8 +36,9 @@ def test_act_where_the_launches_change(dq, orc, E, K, prec):
 
 
 # fp32 steps: parts of the samples of s' are 1 row up to 14, 4 rows above; those of s are 2 rows up to 32, 4 rows above;
-# conv1 sums its frames in two halves up to 34; one launch for the conv layers up to 42, layers of s apart up to 128
-@pytest.mark.parametrize("B", [14, 15, 34, 35, 42, 43, 128, 129])
+# conv1 sums its frames in two halves up to 34; one launch for the conv layers up to 42; from 60 up to 128 one for s' and
+# layers for s
+@pytest.mark.parametrize("B", [14, 15, 34, 35, 42, 43, 59, 60, 128, 129])
 def test_fp32_step_where_the_launches_change(dq, orc, B):
     print("case fp32 step", B, flush=True)
     _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41)
