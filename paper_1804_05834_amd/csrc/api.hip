@@ -436,9 +436,9 @@ bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->n
 // way under another order of summation: at a batch of 32 that is once in a dozen steps, at 1000 in every step, and
 // one such decision moves a gradient by 1e-4 to 7e-2 of its norm (first steps with the split form in every pass: 9 of 300
 // at 32 and 6 of 150 at 42 beyond 1e-4; with the first pass in this order 0 of them, and 2 after three steps).  Every batch
-// therefore keeps it for the first pass, so that its results stay those of the plain fp32 chain; the passes over s', whose activations are only values, take the split form up to a batch of 128.  Their last bits
-// reach a decision only through the updated parameters: of 540 first steps at 43 to 128 none differs by 1e-4 between the two
-// forms of s', of second steps 0 of 150 at 43, 2 of 150 at 64, 2 and 3 of 120 at 100 and 128; at 256 2 of 60, and at 1000,
+// therefore keeps it for the first pass, so that its results stay those of the plain fp32 chain; the passes over s', whose
+// activations are only values, take the split form up to a batch of 128.  Their last bits reach a decision only through
+// the updated parameters: of 540 first steps at 43 to 128 none differs by 1e-4 between the two forms of s', of second steps 0 of 150 at 43, 2 of 150 at 64, 2 and 3 of 120 at 100 and 128; at 256 2 of 60, and at 1000,
 // with a draw through the updated priorities, 2 of 20.  Above 128 every pass keeps the fp32 chain.  So it does below 60
 // where the split form would be a launch of its own: a step with it takes 124.5 us at 43, 125 at 48, 131.5 at 54, 133.3 at
 // 60, 154 at 80, 191 at 128 (and would take 248 at 200); with the chain in every pass 120, 120.5, 128, 133.4, 168, 207 (259).
@@ -937,12 +937,11 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
             }
         }
         if (step_launch(c, B)) {
-            // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample
-            // (beyond 5/8 of the CUs they take several fifths), 64 rows or more per tile of conv2's weight gradient.  5/8 is a
-            // fifth of 32 samples each; for 33 to 42 more workgroups would still fit one round beside fewer tiles: capped
-            // at 210 instead of 160 a step takes 92.1 instead of 96.6 us at 33, 93.1 / 98.6 at 36, 96.5 / 100.6 at 40 and
-            // 98.9 / 100.4 at 42; with 128 the same as with 160, at 32 82.1 with any
-            const int nps = std::min({BACK_PARTS * B, std::max(1, c->num_cu * 5 / 8), MAX_WSPLIT1});
+            // conv2 and conv1 in one launch and one round of workgroups, one per CU: five workgroups per sample, which is
+            // 5/6 of the CUs at most (step_launch), and tiles of conv2's weight gradient of 64 rows or more on the others.
+            // With the first at 5/8 of the CUs, some of them taking two fifths, and more tiles a step took 96.9 us at 33
+            // (93.8 now), 97.8 at 36 (93.3), 100.4 at 40 (96.7), 100.8 at 42 (99.0); up to 32 nothing differs.
+            const int nps = std::min(BACK_PARTS * B, MAX_WSPLIT1);
             const int splits = std::max(1, std::min<int>(MAX_WSPLIT, (c->num_cu - nps - U.on) / 2));
             const long rows = (long)B * 81;
             const int rps = (int)((std::max<long>((rows + splits - 1) / splits, 64) + 31) / 32 * 32);
