@@ -58,6 +58,7 @@ struct Workspace {
     int32_t *b_idx, *b_a;
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
+    unsigned *arrivals;   // counter of the acting launch of few observations, cleared by the conv launch in front of it
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -103,6 +104,7 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.qmax_j = (float *)take(MB * 4);
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
+    w.arrivals = (unsigned *)take(256);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
     w.act1 = take(rows * net::A1 * es);
@@ -458,8 +460,9 @@ bool in_kernel_draw_fits(const dqn_ctx *c, int B)
     return fused123(c, 3l * B, 3) || fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
 
+// few_rows: acting on few observations; the conv launch clears their counter, and fc1 is left to the launch behind it
 int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *nsplit_out,
-                          long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw)
+                          long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw, bool few_rows)
 {
     using namespace g32;
     float *act3 = (float *)w.act3;
@@ -508,6 +511,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         A.units = samples * plan.parts;
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
+        A.clear = few_rows ? w.arrivals : nullptr;
         if (step) {
             const float *theta = theta_of(c, pass[0].net);
             sp::StepArgs S{};
@@ -561,6 +565,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3(t3, 2, 1), 192, 0, st>>>(A3); });
         else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3(t3, 1, 1), 256, 0, st>>>(A3); });
     }
+    if (few_rows) return hip_status(c, "forward");
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
         FwdArgs A{};
         const int ns = fc1_splits(rows);
@@ -580,7 +585,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
 
 // draw != nullptr: the conv1 kernel draws the transitions itself (replay mode; no sampling kernel ran)
 int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *nsplit_out,
-                           long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw)
+                           long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw, bool few_rows)
 {
     using namespace gbf;
     bf16_t *act1 = (bf16_t *)w.act1, *act2 = (bf16_t *)w.act2, *act3 = (bf16_t *)w.act3;
@@ -606,6 +611,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.units = (int)rows * plan.parts;
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
+        A.clear = few_rows ? w.arrivals : nullptr;
         launch(c, "conv123_fwd", st, [&] {
             if (plan.r3 == 1) c123::k_conv123_fwd<1><<<dim3(plan.grid), 512, c123::Geo<1>::LDS, st>>>(A);
             else if (plan.r3 == 4) c123::k_conv123_fwd<4><<<dim3(plan.grid), 512, c123::Geo<4>::LDS, st>>>(A);
@@ -684,6 +690,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         const int grid = per_sample(A, act2, net::A2, net::C3W, net::C3B, act3, net::A3);
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
     }
+    if (few_rows) return hip_status(c, "forward");
     const bool few_fit = (size_t)rows * FC1_SPLITS <= w.f1rows;
     if (rows >= c->fc1_big_rows || !few_fit) {
         // many rows: 128 x 128 tiles, four stages in LDS, few reduction splits
@@ -733,10 +740,35 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
 // w: where the activations and the fc1 partial sums go (the context's workspace, or a view of the
 // library's static scratch array)
 int32_t forward_trunk(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *ns, long *ss, hipStream_t st,
-                      const misc::SampleArgs *draw = nullptr)
+                      const misc::SampleArgs *draw = nullptr, bool few_rows = false)
 {
-    return c->cfg.precision == 1 ? forward_trunk_bf16(c, w, pass, npass, ns, ss, st, draw)
-                                 : forward_trunk_f32(c, w, pass, npass, ns, ss, st, draw);
+    return c->cfg.precision == 1 ? forward_trunk_bf16(c, w, pass, npass, ns, ss, st, draw, few_rows)
+                                 : forward_trunk_f32(c, w, pass, npass, ns, ss, st, draw, few_rows);
+}
+
+// Acting on E observations (arguments checked): Q(obs, .) and the actions.  w: see forward_trunk
+int32_t act_on(dqn_ctx *c, const Workspace &w, const char *where, const uint8_t *obs, int32_t E, float epsilon,
+               uint64_t draw_seed, int32_t *actions, float *q_opt, hipStream_t st)
+{
+    Pass p{obs, net::STATE, 0, E, nullptr, 0};
+    int ns = 0;
+    long ss = 0;
+    const bool bf16 = c->cfg.precision == 1;
+    // fc1 and the head in one launch, where the conv layers are one that clears the counter
+    const bool few = E <= misc::FEW_ROWS && (bf16 ? fused123(c, E, 1) : c->split);
+    int32_t rc = forward_trunk(c, w, &p, 1, &ns, &ss, st, nullptr, few);
+    if (rc) return rc;
+    misc::HeadActArgs H{w.f1part, ns, ss, E, c->cfg.num_actions, c->cfg.dueling, c->theta + net::F1B,
+                        c->theta + net::HEAD, epsilon, draw_seed, actions, q_opt};
+    if (few) {
+        const misc::Fc1HeadArgs A{H, w.act3, bf16 ? (const void *)(shadow_of(c, 0) + net::F1W) : (const void *)(c->theta + net::F1W),
+                                  w.f1part, w.arrivals};
+        launch(c, "fc1_head_act", st, [&] { misc::launch_fc1_head_act(A, bf16, st); });
+        return hip_status(c, where);
+    }
+    if (ns < 1 || ns > misc::HEAD_MAX_SPLITS) return fail(c, DQN_ERR_STATE, std::string(where) + ": unexpected number of fc1 reduction splits");
+    launch(c, "head_act", st, [&] { misc::launch_head_act(H, c->num_cu, st); });
+    return hip_status(c, where);
 }
 
 // reduction rows per split (a multiple of `unit`) and the resulting number of splits
@@ -1604,16 +1636,7 @@ int32_t dqn_act(dqn_ctx *c, const uint8_t *obs, int32_t E, float epsilon, uint64
     if (!obs || !actions || !aligned(obs, 16)) return fail(c, DQN_ERR_INVALID_ARG, "dqn_act: NULL or misaligned argument");
     if (!(epsilon >= 0.f && epsilon <= 1.f)) return fail(c, DQN_ERR_INVALID_ARG, "dqn_act: epsilon must be in [0,1]");
     hipStream_t st = (hipStream_t)stream;
-    Pass p{obs, net::STATE, 0, E, nullptr, 0};
-    int ns;
-    long ss;
-    int32_t rc = forward_trunk(c, c->ws, &p, 1, &ns, &ss, st);
-    if (rc) return rc;
-    misc::HeadActArgs H{c->ws.f1part, ns, ss, E, c->cfg.num_actions, c->cfg.dueling, c->theta + net::F1B,
-                        c->theta + net::HEAD, epsilon, draw_seed, actions, q_opt};
-    if (ns < 1 || ns > misc::HEAD_MAX_SPLITS) return fail(c, DQN_ERR_STATE, "dqn_act: unexpected number of fc1 reduction splits");
-    launch(c, "head_act", st, [&] { misc::launch_head_act(H, c->num_cu, st); });
-    return hip_status(c, "dqn_act");
+    return act_on(c, c->ws, "dqn_act", obs, E, epsilon, draw_seed, actions, q_opt, st);
 }
 
 int32_t dqn_act_static(dqn_ctx *c, const uint8_t *obs, int32_t E, float epsilon, uint64_t draw_seed,
@@ -1637,25 +1660,13 @@ int32_t dqn_act_static(dqn_ctx *c, const uint8_t *obs, int32_t E, float epsilon,
     w.act3 = take(n * net::A3 * es);
     w.f1part = (float *)take(n * 14 * net::HID * 4);
     w.f1rows = n * 14;
-    static_assert(DQN_ACT_STATIC_MAX * (size_t)(net::A1 + net::A2 + net::A3) * 4 + DQN_ACT_STATIC_MAX * 14 * (size_t)net::HID * 4 + 4 * 256
+    w.arrivals = (unsigned *)take(256);
+    static_assert(DQN_ACT_STATIC_MAX * (size_t)(net::A1 + net::A2 + net::A3) * 4 + DQN_ACT_STATIC_MAX * 14 * (size_t)net::HID * 4 + 5 * 256
                       <= SCRATCH_BYTES, "scratch array too small");
     hipStream_t st = (hipStream_t)stream;
-    Pass p{obs, net::STATE, 0, E, nullptr, 0};
-    int ns;
-    long ss;
     const bool prof = c->prof;   // per-kernel timing creates events: not on this path
     c->prof = false;
-    int32_t rc = forward_trunk(c, w, &p, 1, &ns, &ss, st);
-    if (rc == DQN_OK) {
-        misc::HeadActArgs H{w.f1part, ns, ss, E, c->cfg.num_actions, c->cfg.dueling, c->theta + net::F1B,
-                            c->theta + net::HEAD, epsilon, draw_seed, actions, q_opt};
-        if (ns < 1 || ns > misc::HEAD_MAX_SPLITS) {
-            c->prof = prof;
-            return fail(c, DQN_ERR_STATE, "dqn_act_static: unexpected number of fc1 reduction splits");
-        }
-        misc::launch_head_act(H, c->num_cu, st);
-        rc = hip_status(c, "dqn_act_static");
-    }
+    const int32_t rc = act_on(c, w, "dqn_act_static", obs, E, epsilon, draw_seed, actions, q_opt, st);
     c->prof = prof;
     return rc;
 }

@@ -408,6 +408,30 @@ __global__ __launch_bounds__(512) void k_head_wgrad(HeadWgradArgs A)
     head_wgrad_body<16>(A, blockIdx.x, blockIdx.y, lds);
 }
 
+// ---- work that the last workgroup of a launch to arrive does for all of them
+// A workgroup hands over its few words with device-scope stores, waits until they are acknowledged and draws
+// a number; the one that draws the last reads all words with device-scope loads.  Only those words are made
+// visible beyond the die's L2: a device-wide fence here would write the whole L2 back, a thousand times a
+// launch.  No workgroup waits for another.  The counter is 0 before the launch and the last one puts it back.
+__device__ __forceinline__ void publish_word(float *p, float v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float read_word(const float *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// called by one thread, after the barrier behind which all of the workgroup's words have been stored and
+// acknowledged (words_acknowledged() by the threads that stored them)
+__device__ __forceinline__ void words_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ bool arrived_last(unsigned *count, unsigned of)
+{
+    const unsigned k = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (k != of - 1) return false;
+    __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
 struct HeadActArgs {
     const float *part;
     int nsplit;
@@ -443,6 +467,61 @@ __device__ __forceinline__ void head_rows1_load(HeadRound &H, int round, const f
     for (int k = 0; k < net::HID / 16; ++k) H.w[k] = w[l + 16 * k];
     H.b = head[head_b_off(r, K, dueling)];
 }
+// (head_dot for the rows side by side: a row's sum is one chain of 32 additions, in that order)
+template <int ROWS>
+__device__ __forceinline__ void act_dots(const HeadRound &H, const float (*hid)[HID_LDS], float (*raw)[MAXR], int l)
+{
+    float acc[ROWS] = {};
+    float4 x[ROWS], nx[ROWS];
+    auto read = [&](int k) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) nx[r] = *reinterpret_cast<const float4 *>(&hid[r][l * 36 + k]);
+    };
+    read(0);
+#pragma unroll
+    for (int k = 0; k < net::HID / 16; k += 4) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) x[r] = nx[r];
+        if (k + 4 < net::HID / 16) read(k + 4);
+        if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);   // all reads at once would take the registers of three workgroups
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k] * x[r].x;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 1] * x[r].y;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 2] * x[r].z;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 3] * x[r].w;
+        if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum<8>(acc[r]);
+    if (l == 0 && H.d >= 0)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) raw[r][H.d] = acc[r] + H.b;
+}
+// The dueling combine, the argmax and the draw of observation e, by one wave, out of its raw dot products
+__device__ __forceinline__ void act_choose(const HeadActArgs &A, const float *rw, int e, int a)
+{
+    const int K = A.K;
+    const float v = a < K ? rw[A.dueling ? 1 + a : a] : 0.f;
+    float qa = v;
+    if (A.dueling) qa = rw[0] + (v - wave_sum(v) / (float)K);
+    // argmax with the lowest index winning ties; lanes past K never win
+    float bv = a < K ? qa : -3.4028234663852886e38f;
+    int bi = a < K ? a : 64;
+    wave_argmax(bv, bi);
+    if (a == 0) {
+        int act = bi;
+        const float u = draw_u24(A.seed, 2ull * (uint64_t)e);
+        if (u < A.epsilon) {
+            const float u2 = draw_u24(A.seed, 2ull * (uint64_t)e + 1ull);
+            act = min((int)floorf(u2 * (float)K), K - 1);
+        }
+        A.actions[e] = act;
+    }
+    if (A.q_out && a < K) A.q_out[(long)e * K + a] = qa;
+}
 template <int NS, int ROWS>
 __global__ __launch_bounds__(256, ROWS == 1 ? 1 : 3) void k_head_act(HeadActArgs A)
 {
@@ -468,37 +547,6 @@ __global__ __launch_bounds__(256, ROWS == 1 ? 1 : 3) void k_head_act(HeadActArgs
     head_rows1_load(H0, 0, A.head, K, A.dueling, tid);
     head_rows1_load(H1, 1, A.head, K, A.dueling, tid);
     __builtin_amdgcn_sched_barrier(0);
-    // (head_dot for the rows side by side: a row's sum is one chain of 32 additions, in that order)
-    auto dots = [&](const HeadRound &H) {
-        float acc[ROWS] = {};
-        float4 x[ROWS], nx[ROWS];
-        auto read = [&](int k) {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) nx[r] = *reinterpret_cast<const float4 *>(&hid[r][l * 36 + k]);
-        };
-        read(0);
-#pragma unroll
-        for (int k = 0; k < net::HID / 16; k += 4) {
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) x[r] = nx[r];
-            if (k + 4 < net::HID / 16) read(k + 4);
-            if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);   // all reads at once would take the registers of three workgroups
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k] * x[r].x;
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 1] * x[r].y;
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 2] * x[r].z;
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) acc[r] += H.w[k + 3] * x[r].w;
-            if (ROWS > 1) __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) acc[r] = wave_sum<8>(acc[r]);
-        if (l == 0 && H.d >= 0)
-#pragma unroll
-            for (int r = 0; r < ROWS; ++r) raw[r][H.d] = acc[r] + H.b;
-    };
     for (;;) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
@@ -513,36 +561,16 @@ __global__ __launch_bounds__(256, ROWS == 1 ? 1 : 3) void k_head_act(HeadActArgs
         const int next = e0 + (int)gridDim.x * ROWS;
         if (ROWS > 1 && next < A.E) load_sums(next);
         sync_lds();
-        dots(H0);
-        if (16 + 4 * wave < R) dots(H1);
+        act_dots<ROWS>(H0, hid, raw, l);
+        if (16 + 4 * wave < R) act_dots<ROWS>(H1, hid, raw, l);
         if constexpr (ROWS == 1)
             for (int round = 2; 16 * round < R; ++round) {   // more than 32 dot products: K > 31
                 head_rows1_load(H0, round, A.head, K, A.dueling, tid);
-                dots(H0);
+                act_dots<ROWS>(H0, hid, raw, l);
             }
         sync_lds();
         const int e = e0 + wave;
-        if (wave < ROWS && e < A.E) {
-            const int a = tid & 63;
-            const float *rw = raw[ROWS == 1 ? 0 : wave];
-            const float v = a < K ? rw[A.dueling ? 1 + a : a] : 0.f;
-            float qa = v;
-            if (A.dueling) qa = rw[0] + (v - wave_sum(v) / (float)K);
-            // argmax with the lowest index winning ties; lanes past K never win
-            float bv = a < K ? qa : -3.4028234663852886e38f;
-            int bi = a < K ? a : 64;
-            wave_argmax(bv, bi);
-            if (a == 0) {
-                int act = bi;
-                const float u = draw_u24(A.seed, 2ull * (uint64_t)e);
-                if (u < A.epsilon) {
-                    const float u2 = draw_u24(A.seed, 2ull * (uint64_t)e + 1ull);
-                    act = min((int)floorf(u2 * (float)K), K - 1);
-                }
-                A.actions[e] = act;
-            }
-            if (A.q_out && a < K) A.q_out[(long)e * K + a] = qa;
-        }
+        if (wave < ROWS && e < A.E) act_choose(A, raw[ROWS == 1 ? 0 : wave], e, tid & 63);
         if (ROWS == 1 || next >= A.E) break;
         // (the next round writes hid, which every wave has read, before the barrier behind which raw is written again)
         e0 = next;
@@ -573,6 +601,125 @@ inline void launch_head_act(const HeadActArgs &H, int num_cu, hipStream_t st)
     case 6: launch_head_act_ns<6>(H, num_cu, st); break;
     default: launch_head_act_ns<7>(H, num_cu, st); break;
     }
+}
+
+// Acting on up to FEW_ROWS observations: fc1 and the head in one launch.  Workgroup b forms hidden units 2b and 2b + 1 of
+// every row, wave w unit w % 2 over half w / 2 of the inputs, 25 KB of weights (fp32) per CU, all requested at once;
+// the workgroup that arrives last (above) has the whole hidden layer and finishes every row as k_head_act does.  The
+// tiled fc1 launches multiply 32 rows whatever there are, leave 7 partial sums per unit, and the head is a launch behind
+// them.  One observation: 21.5 -> 19.0 us per call in fp32, 15.1 -> 14.2 in bf16; two: 21.5 -> 19.6, 15.0 -> 14.8.  With four
+// rows here the gain is gone (21.0 against 21.5, 15.9 against 15.2), and with the head's weights requested by every
+// workgroup in advance there is none over this (18.9, 14.4).
+// The counter is cleared by the conv launch in front, so that nothing of one call is left for the next.
+constexpr int FEW_ROWS = 2, FEW_BLOCKS = net::HID / 2;
+struct Fc1HeadArgs {
+    HeadActArgs head;      // (part, nsplit, split_stride: not used)
+    const void *x;         // [E][3136] conv3's output, fp32 or bf16
+    const void *w;         // [512][3136] in the same type
+    float *h;              // [E][512]
+    unsigned *arrivals;
+};
+// four (eight) elements of 16 bytes as floats
+__device__ __forceinline__ void elements(uint4 u, float (&f)[4])
+{
+    f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y); f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
+}
+__device__ __forceinline__ void elements(uint4 u, float (&f)[8])
+{
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f[2 * i] = __uint_as_float(w[i] << 16);
+        f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+    }
+}
+template <int BYTES, int ROWS>   // bytes per element
+__global__ __launch_bounds__(256, 1) void k_fc1_head_act(Fc1HeadArgs A)
+{
+    constexpr int V = 16 / BYTES, C = net::A3 / V / 2, NI = (C + 63) / 64;   // elements per piece; pieces per half, per lane
+    static_assert(ROWS <= FEW_ROWS && net::A3 % (2 * V) == 0, "halves of whole pieces");
+    __shared__ __attribute__((aligned(16))) float hid[ROWS][HID_LDS];
+    __shared__ float raw[ROWS][MAXR];
+    __shared__ float half[ROWS][4];
+    __shared__ int last;
+    const HeadActArgs &H = A.head;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = tid & 15;
+    const int unit = 2 * blockIdx.x + (wave & 1);
+    const uint4 *w = static_cast<const uint4 *>(A.w) + (long)unit * (2 * C) + (wave >> 1) * C;
+    uint4 wq[NI], xq[ROWS][NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) wq[i] = w[min(lane + 64 * i, C - 1)];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const uint4 *x = static_cast<const uint4 *>(A.x) + (long)min(r, H.E - 1) * (2 * C) + (wave >> 1) * C;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) xq[r][i] = x[min(lane + 64 * i, C - 1)];
+    }
+    const float b = H.f1b[2 * blockIdx.x + (tid & 1)];
+    float acc[ROWS][V] = {};
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        float wf[V], xf[V];
+        elements(wq[i], wf);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            elements(xq[r][i], xf);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const float p = fmaf(wf[e], xf[e], acc[r][e]);
+                acc[r][e] = 64 * (i + 1) <= C || lane + 64 * i < C ? p : acc[r][e];
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < V; e += 4) s += (acc[r][e] + acc[r][e + 1]) + (acc[r][e + 2] + acc[r][e + 3]);
+        s = wave_sum(s);
+        if (lane == 0) half[r][wave] = s;
+    }
+    sync_lds();
+    if (wave == 0) {
+        const int r = lane >> 1, u = lane & 1;
+        if (r < ROWS && r < H.E) publish_word(A.h + (long)r * net::HID + 2 * blockIdx.x + u, fmaxf(half[r][u] + half[r][u + 2] + b, 0.f));
+        words_acknowledged();
+        if (lane == 0) last = arrived_last(A.arrivals, FEW_BLOCKS);
+    }
+    sync_lds();
+    if (!last) return;
+    const int K = H.K, R = K + (H.dueling ? 1 : 0);
+    HeadRound H0, H1;
+    float hv[ROWS][2];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) hv[r][u] = read_word(A.h + (long)min(r, H.E - 1) * net::HID + tid + 256 * u);
+    head_rows1_load(H0, 0, H.head, K, H.dueling, tid);
+    head_rows1_load(H1, 1, H.head, K, H.dueling, tid);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) hid[r][hid_at(tid + 256 * u)] = hv[r][u];
+    sync_lds();
+    act_dots<ROWS>(H0, hid, raw, l);
+    if (16 + 4 * wave < R) act_dots<ROWS>(H1, hid, raw, l);
+    for (int round = 2; 16 * round < R; ++round) {   // more than 32 dot products: K > 31
+        head_rows1_load(H0, round, H.head, K, H.dueling, tid);
+        act_dots<ROWS>(H0, hid, raw, l);
+    }
+    sync_lds();
+    if (wave < ROWS && wave < H.E) act_choose(H, raw[wave], wave, lane);
+}
+template <int BYTES> void launch_fc1_head_act_of(const Fc1HeadArgs &A, hipStream_t st)
+{
+    if (A.head.E == 1) k_fc1_head_act<BYTES, 1><<<FEW_BLOCKS, 256, 0, st>>>(A);
+    else k_fc1_head_act<BYTES, FEW_ROWS><<<FEW_BLOCKS, 256, 0, st>>>(A);
+}
+inline void launch_fc1_head_act(const Fc1HeadArgs &A, bool bf16, hipStream_t st)
+{
+    if (bf16) launch_fc1_head_act_of<2>(A, st);
+    else launch_fc1_head_act_of<4>(A, st);
 }
 
 // --------------------------------------------------------------- RMSProp
@@ -811,30 +958,6 @@ __global__ __launch_bounds__(256) void k_tree_rebuild(float *tree, long Lcur, in
     float v[16];
     tree_load16(tree, Lcur, BL, blockIdx.x, v);
     (void)tree_block16(tree, Lcur, BL, blockIdx.x, v, sh);
-}
-
-// ---- work that the last workgroup of a launch to arrive does for all of them
-// A workgroup hands over its few words with device-scope stores, waits until they are acknowledged and draws
-// a number; the one that draws the last reads all words with device-scope loads.  Only those words are made
-// visible beyond the die's L2: a device-wide fence here would write the whole L2 back, a thousand times a
-// launch.  No workgroup waits for another.  The counter is 0 before the launch and the last one puts it back.
-__device__ __forceinline__ void publish_word(float *p, float v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float read_word(const float *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// called by one thread, after the barrier behind which all of the workgroup's words have been stored and
-// acknowledged (words_acknowledged() by the threads that stored them)
-__device__ __forceinline__ void words_acknowledged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ bool arrived_last(unsigned *count, unsigned of)
-{
-    const unsigned k = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (k != of - 1) return false;
-    __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
 }
 
 // Whole tree in one launch: every workgroup builds the block of leaves it holds in registers, and the one that

@@ -35,6 +35,28 @@ def test_act_where_the_launches_change(dq, orc, E, K, prec):
     m.close()
 
 
+# up to two observations fc1 and the head are one launch, with the counter of its workgroups cleared by the conv launch:
+# several calls in a row, the counts of observations mixed, Q and actions of each
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("K,dueling", [(1, 0), (18, 1), (31, 1), (64, 1)])
+def test_act_on_few_observations(dq, orc, K, dueling, prec):
+    print("case act on few", K, dueling, prec, flush=True)
+    tol = TOL_BF16 if prec else TOL
+    m = dq.Dqn(dq.make_config(num_actions=K, dueling=dueling, max_act_batch=3, precision=prec))
+    p = synth.he_uniform_params(3 + K, K, dueling, bias_scale=0.05)
+    m.set_params(0, torch.from_numpy(p))
+    obs = synth.states(31, 3)
+    ref = orc.forward(p, K, dueling, obs.numpy(), quant=prec)
+    on = dev(obs)
+    got = [(E, m.act(on[3 - E:], 0.0, 99, want_q=True)) for E in (1, 2, 1, 3, 2, 1)]
+    for E, (a, q) in got:
+        r = ref[3 - E:]
+        scale = np.maximum(np.abs(r).max(axis=1), np.sqrt(np.mean(ref ** 2)))
+        assert np.all(np.abs(q.cpu().numpy() - r).max(axis=1) <= tol * scale), E
+        check_argmax(a.cpu().numpy(), r, tol)
+    m.close()
+
+
 # fp32 steps: parts of the samples of s' are 1 row up to 14, 4 rows above; those of s are 2 rows up to 32, 4 rows above;
 # conv1 sums its frames in two halves up to 34; one launch for the conv layers up to 42; from 60 up to 128 one for s' and
 # layers for s
