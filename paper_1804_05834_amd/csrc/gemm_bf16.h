@@ -1396,21 +1396,43 @@ struct G3 { static constexpr int IN_PIX = 81, IN_CH = 64, IN_W = 9, OUT = 7, TAP
 
 template <class G> struct Shape {
     static constexpr int PB = G::IN_CH * 2;                        // bytes per pixel
-    static constexpr int GROUP = 128 / PB;                         // pixels per 128-byte group: 2 / 1
-    static constexpr int GB = 144;                                 // LDS bytes per group (128 + 16)
-    static constexpr int SAMPLE = (G::IN_PIX / GROUP + (G::IN_PIX % GROUP ? 1 : 0)) * GB;
+    // LDS layout of a sample.  64 channels: 144 bytes per pixel.  32 channels (stride 2): the even columns of a pixel row,
+    // then the odd ones, 64 bytes each, and 16 bytes more per row.  A 16-byte read is served sixteen lanes at a time,
+    // lanes 0-3, 12-15 and 20-27 of a half wave, then the others (measured): positions 0-3 and 12-15 of a tile with
+    // piece kg, 4-11 with piece kg + 1.  Over two rows of eight positions these sixteen lie in the sixteen different
+    // 16-byte columns of LDS this way; with positions in order and 144 bytes for two pixels every second read of conv2's
+    // took twice as long.
+    static constexpr bool SPLIT = G::IN_CH == 32;
+    static constexpr int GB = 144;
+    static constexpr int RB = (G::IN_W * 4 + 1) * 16;
+    static constexpr int SAMPLE = SPLIT ? (G::IN_PIX / G::IN_W) * RB : G::IN_PIX * GB;
     static constexpr int K = G::TAPS * G::TAPS * G::IN_CH;
     static constexpr int STEPS = K / 32;                           // reduction steps: 16 / 18
     static constexpr int SPT = G::IN_CH / 32;                      // steps per tap: 1 / 2
     static constexpr int WROW = K * 2 + 16;                        // LDS bytes per weight row in transit
     static constexpr int NPOS = G::OUT * G::OUT;                   // 81 / 49
-    static constexpr int NBLK = (NPOS + 31) / 32;                  // position blocks per wave: 3 / 2
+    static constexpr int NBLK = (NPOS + 31) / 32;                  // tiles of positions per wave: 3 / 2
     static constexpr int CHUNKS = G::IN_PIX * PB / 16;             // 16-byte pieces of a sample: 1600 / 648
     static constexpr int NLD = (CHUNKS + 255) / 256;               // pieces per thread: 7 / 3
     static constexpr int WCH = 32 * K * 2 / 16 / 256;              // weight pieces per thread and half: 8 / 9
     static constexpr int LDS = 32 * WROW > 2 * SAMPLE ? 32 * WROW : 2 * SAMPLE;
     // LDS byte offset of 16-byte piece c of pixel q
-    static __device__ __forceinline__ uint32_t at(int q, int c) { return (q / GROUP) * GB + (q % GROUP) * PB + c * 16; }
+    static __device__ __forceinline__ uint32_t at(int q, int c)
+    {
+        if constexpr (SPLIT) {
+            const int y = q / G::IN_W, x = q % G::IN_W;
+            return y * RB + ((x & 1) * (2 * G::IN_W) + (x >> 1) * 4 + c) * 16;
+        } else return q * GB + c * 16;
+    }
+    // Position n of tile t; where there is none, one that another lane has as well.  9 x 9: four tiles of two rows of eight,
+    // then the last row and the last column of eight, then the corner.
+    static __device__ __forceinline__ int position(int t, int n)
+    {
+        if constexpr (SPLIT) {
+            const int r = n >> 3, x = n & 7;
+            return t < 4 ? (2 * t + r) * G::OUT + x : t > 4 ? NPOS - 1 : r ? x * G::OUT + 8 : 8 * G::OUT + x;
+        } else return min(16 * t + n, NPOS - 1);
+    }
 };
 
 template <class G> struct Raw { u32x4 r[Shape<G>::NLD]; };
@@ -1467,15 +1489,12 @@ __device__ __forceinline__ void run(const Seg &S, int g0, int g1, uint8_t *lds, 
     }
     const v4f b0 = *reinterpret_cast<const v4f *>(S.bias + 32 * hh + 8 * kg);
     const v4f b1 = *reinterpret_cast<const v4f *>(S.bias + 32 * hh + 8 * kg + 4);
-    // this lane's positions and the LDS offset of their first tap; positions past the end read a
-    // valid pixel and are not stored
+    // this lane's positions and the LDS offset of their first tap
     uint32_t base[H::NBLK];
     int pos[H::NBLK];
 #pragma unroll
     for (int b = 0; b < H::NBLK; ++b) {
-        int p = 16 * (H::NBLK * ph + b) + n;
-        pos[b] = p;
-        if (p > H::NPOS - 1) p = H::NPOS - 1;
+        const int p = pos[b] = H::position(H::NBLK * ph + b, n);
         base[b] = H::at(G::STRIDE * (G::IN_W * (p / G::OUT) + (p % G::OUT)), kg);
     }
     sync_lds();   // the weight rows have been read
@@ -1520,14 +1539,14 @@ __device__ __forceinline__ void run(const Seg &S, int g0, int g1, uint8_t *lds, 
         bf16_t *y = S.y + (long)g * (H::NPOS * 64) + 32 * hh + 8 * kg;
 #pragma unroll
         for (int b = 0; b < H::NBLK; ++b) {
-            // unconditional: a lane past the last position has computed the last position once more (its
-            // operand address was clamped to that pixel) and stores the same bits there.  Without a branch
+            // unconditional: a lane without a position of its own has computed another lane's once more (from the same
+            // operands) and stores the same bits there.  Without a branch
             // the compiler can count these stores, and the wait for the next sample's pixels, requested
             // before them, does not wait for their acknowledgement as well.
             const v4f a0 = acc[b][0], a1 = acc[b][1];
             const uint2 lo = pack4(fmaxf(a0.x + b0.x, 0.f), fmaxf(a0.y + b0.y, 0.f), fmaxf(a0.z + b0.z, 0.f), fmaxf(a0.w + b0.w, 0.f));
             const uint2 hi = pack4(fmaxf(a1.x + b1.x, 0.f), fmaxf(a1.y + b1.y, 0.f), fmaxf(a1.z + b1.z, 0.f), fmaxf(a1.w + b1.w, 0.f));
-            *reinterpret_cast<uint4 *>(y + (pos[b] < H::NPOS ? pos[b] : H::NPOS - 1) * 64) = uint4{lo.x, lo.y, hi.x, hi.y};
+            *reinterpret_cast<uint4 *>(y + pos[b] * 64) = uint4{lo.x, lo.y, hi.x, hi.y};
         }
     }
 }
@@ -1554,15 +1573,18 @@ __global__ __launch_bounds__(256, 2) void k_conv_fwd_ps(Args A)
 // the CU unless a later kernel reads it (the backward pass reads it for the training rows only).
 //
 // A workgroup of eight waves owns a run of samples of one segment.  Waves 0-3 are PRODUCERS: each
-// computes one conv1 strip per interval exactly as c1::k_conv1_fwd does (strip staged in LDS of its
-// own, weights in registers, next strip's pixels in flight) and writes the 80 x 32 result into the
-// sample's place in a ring of three LDS images, in the layout ps::run reads.  Waves 4-7 are
-// CONSUMERS: they hold conv2's weights in registers as ps::k_conv_fwd_ps does and, in every interval
-// in which a sample has become complete, compute its conv2 output out of the ring.  One barrier per
-// interval.  Strips are dealt out in order, four per interval, five per sample: sample k is complete
-// after interval floor((5k+4)/4) and is consumed in the first interval i with 4i >= 5k+5, which is a
-// different interval for every k; the producers are then at most two samples ahead of the sample
-// being read, so three images suffice.
+// computes every fourth conv1 strip as c1::k_conv1_fwd does (the strip's pixels in LDS of its own, as
+// bytes, and widened between the matrix instructions of the frame before; weights in registers, next
+// strip's pixels in flight) and writes the 80 x 32 result into the sample's place in a ring of four LDS
+// images, in the layout ps::run reads.  Waves 4-7 are CONSUMERS: they hold conv2's weights in registers
+// as ps::k_conv_fwd_ps does and compute the conv2 output of each sample out of the ring.  The waves hand
+// over by counts in LDS: a consumer waits for the five strips of its sample, a producer, before it writes,
+// for the four consumers of the sample that had the image before, four samples back.
+// What bounds it is the issue of the SIMDs: 196 matrix instructions of 16 cycles and about 560 vector instructions
+// of 4 per SIMD and sample make 5,400 of the 6,700 cycles it takes, and hardly overlap.  With a barrier
+// between intervals of four strips instead of the counts, pixels as bf16 in LDS (twice the bytes) and positions
+// in order (conflicts: Shape) the launch of a step at 512 took 37.8 us, now 36.4, of 2048 observations 36.2
+// and 34.6, of 8192 125 and 124; the counts alone with pixels as bf16 37.6 at 512.
 //
 // Replay mode: the workgroup draws its samples first (Eq.10 walk, two draws per wave and walk, all
 // eight waves), while the consumers' weight loads are in flight; the workgroups of segment 0 publish
@@ -1571,8 +1593,6 @@ __global__ __launch_bounds__(256, 2) void k_conv_fwd_ps(Args A)
 // ===========================================================================
 namespace c12 {
 using c1::Src;
-using c1::StripOff;
-using c1::StripRaw;
 using c1::STRIP;
 using c1::UNITS;
 using S2 = ps::Shape<ps::G2>;
@@ -1595,122 +1615,194 @@ struct Args {
     misc::SampleArgs samp;
 };
 
-constexpr int NRING = 3;                                    // conv1 images in LDS
+constexpr int NRING = 4;                                    // conv1 images in LDS
 constexpr int MAX_PER_WG = 32;                              // samples one workgroup may own (slot table)
-constexpr int STRIPS_B = 4 * STRIP * 2;                     // 53,760 bytes: one strip per producer wave
-constexpr int RING_B = NRING * S2::SAMPLE;                  // 86,400 bytes
-constexpr int LDS_BYTES = STRIPS_B + RING_B + MAX_PER_WG * 8 + 16;   // + slot table, leaf values, total
-// The hand-over schedule, as functions the kernel's loops and the host-side check
-// (schedule_is_safe, behind dqn_selftest_fused_conv_schedule) both call.
-constexpr int PRODUCERS = 4;                                // producer waves: strips per interval
-__host__ __device__ constexpr int intervals(int ns) { return (UNITS * ns + PRODUCERS - 1) / PRODUCERS + 1; }
-// sample that strip u of a run belongs to, and the image of the ring that holds a sample
+constexpr int PRODUCERS = 4, CONSUMERS = 4;                 // waves
+constexpr int STRIPS_B = PRODUCERS * STRIP;                 // 26,880 bytes: one strip per producer wave, pixels as bytes
+constexpr int RING_B = NRING * S2::SAMPLE;                  // 103,680 bytes
+constexpr int LDS_BYTES = STRIPS_B + RING_B + MAX_PER_WG * 8 + 16 + MAX_PER_WG * 8;   // + slot table, leaf values, total, counts
+static_assert(STRIP % 16 == 0, "LDS layout");
+// The hand-over, as functions that the kernel and the host-side check (schedule_is_safe, behind
+// dqn_selftest_fused_conv_schedule) both call.  Strip u of a run is produced by wave u % PRODUCERS, in order; a producer
+// counts its strips in per sample, a consumer the samples it has read.
 __host__ __device__ constexpr int sample_of_strip(int u) { return u / UNITS; }
 __host__ __device__ constexpr int image_of_sample(int k) { return k % NRING; }
-// is sample kc consumed in interval i?  (its last strip was produced in an earlier interval)
-__host__ __device__ constexpr bool consumed_in(int kc, int i) { return UNITS * kc + UNITS <= PRODUCERS * i; }
+// may sample k be read, with `strips` of its strips counted in?
+__host__ __device__ constexpr bool complete(int strips) { return strips == UNITS; }
+// may sample k's image be written, with `reads` consumers done with the sample that had it before?
+__host__ __device__ constexpr bool image_free(int k, int reads) { return k < NRING || reads == CONSUMERS; }
 
-// Replays the schedule on the host for a run of ns samples: a sample is complete before it is read, it
-// is read exactly once, and no strip is written into an image that still holds a sample which has
-// not been read or is being read in the same interval.  Returns 0 if safe, else a code naming the failure.
+// Replays a run of ns samples on the host, in the orders that lead furthest: any one wave ahead of all others, and in turn.  A
+// sample is complete when it is read, every consumer reads it once, no strip is written into an image that still holds a
+// sample which some consumer has not read, and no wave waits for ever.  Returns 0 if safe, else a code naming the failure.
 inline int schedule_is_safe(int ns)
 {
     if (ns < 1 || ns > MAX_PER_WG) return 1;
-    int holds[NRING], written[MAX_PER_WG], consumed[MAX_PER_WG];
-    for (int r = 0; r < NRING; ++r) holds[r] = -1;
-    for (int k = 0; k < ns; ++k) written[k] = consumed[k] = 0;
-    int kc = 0;
-    for (int i = 0; i < intervals(ns); ++i) {
-        int reading = -1;
-        if (kc < ns && consumed_in(kc, i)) {
-            if (written[kc] != UNITS || holds[image_of_sample(kc)] != kc) return 2;   // read before complete
-            reading = kc;
-        }
-        for (int u = PRODUCERS * i; u < PRODUCERS * i + PRODUCERS && u < UNITS * ns; ++u) {
-            const int k = sample_of_strip(u), img = image_of_sample(k);
-            if (holds[img] != k) {
-                if (holds[img] >= 0 && !consumed[holds[img]]) return 3;               // overwrites an unread sample
-                if (reading >= 0 && image_of_sample(reading) == img) return 4;        // overwrites the sample being read
-                holds[img] = k;
+    constexpr int WAVES = PRODUCERS + CONSUMERS;
+    for (int first = 0; first <= WAVES; ++first) {   // `first` runs whenever it can (WAVES: nobody in particular)
+        int holds[NRING], strips[MAX_PER_WG], reads[MAX_PER_WG], at[WAVES];
+        for (int r = 0; r < NRING; ++r) holds[r] = -1;
+        for (int k = 0; k < ns; ++k) strips[k] = reads[k] = 0;
+        for (int w = 0; w < WAVES; ++w) at[w] = w < PRODUCERS ? w : 0;   // next strip; next sample
+        int err = 0;
+        auto step = [&](int w) {   // one strip or one sample of wave w, if it need not wait
+            if (w < PRODUCERS) {
+                if (at[w] >= UNITS * ns) return false;
+                const int k = sample_of_strip(at[w]), img = image_of_sample(k);
+                if (!image_free(k, k < NRING ? 0 : reads[k - NRING])) return false;
+                if (holds[img] != k) {
+                    if (holds[img] > k || (holds[img] >= 0 && reads[holds[img]] != CONSUMERS)) err = 3;
+                    holds[img] = k;
+                }
+                ++strips[k];
+                at[w] += PRODUCERS;
+            } else {
+                const int k = at[w];
+                if (k >= ns || !complete(strips[k])) return false;
+                if (holds[image_of_sample(k)] != k) err = 2;
+                ++reads[k];
+                ++at[w];
             }
-            ++written[k];
+            return true;
+        };
+        for (bool any = true; any;) {
+            any = false;
+            for (int w = 0; w < WAVES; ++w) {
+                while (first < WAVES && step(first)) any = true;
+                any |= step(w);
+            }
         }
-        if (reading >= 0) { consumed[reading] = 1; ++kc; }
+        if (err) return err;
+        for (int k = 0; k < ns; ++k)
+            if (strips[k] != UNITS || reads[k] != CONSUMERS) return 5;   // something left over
     }
-    for (int k = 0; k < ns; ++k)
-        if (!consumed[k] || written[k] != UNITS) return 5;                             // something left over
     return 0;
+}
+
+// The counts of a sample, in LDS: every operation of a wave is carried out there in the order in which it was issued, so
+// a count that has been seen stands behind the stores (or reads) of the wave that raised it.
+__device__ __forceinline__ int count_of(int *p)
+{
+    return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+}
+__device__ __forceinline__ void count_in(int *p, int lane)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    if (lane == 0) __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void await_complete(int *strips)
+{
+    while (!complete(count_of(strips))) __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ __forceinline__ void await_image(int *reads, int k)
+{
+    while (!image_free(k, k < NRING ? 0 : count_of(reads + k - NRING))) __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A strip's pixels as they lie in memory, a frame's 105 pieces of 16 bytes in two loads, the second one's last 23 lanes
+// with the frame's last piece: one scalar address per frame, wherever the frames of a sample are
+struct Pixels { u32x4 r[8]; };
+constexpr int PIECES = c1::SROWS * 84 / 16;
+__device__ __forceinline__ void load_strip(Pixels &R, const Src &S, int g, int slot, int strip, int lane)
+{
+    const uint32_t o0 = lane * 16, o1 = min(lane + 64, PIECES - 1) * 16;
+    const uint8_t *x = S.x + strip * (16 * 84);
+    int i = 0, rb = 0;   // the slot, its sub-ring (slots are below 2^30)
+    if (S.idx) {
+        i = __builtin_amdgcn_readfirstlane(slot);
+        i = i < 0 ? 0 : i >= (int)S.cap ? (int)S.cap - 1 : i;
+        rb = (int)c1::sub_ring_base(S, i);
+        i += S.shift - 3 - rb;
+    } else x += (long)g * S.xs;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        int fr = i + f;   // one wrap at most (see c1::frame_ptr)
+        if (S.idx) {
+            if (fr < 0) fr += S.sub;
+            if (fr >= S.sub) fr -= S.sub;
+            fr += rb;
+        }
+        const uint8_t *p = x + (long)(uint32_t)fr * c1::FR;
+        R.r[2 * f] = *reinterpret_cast<const u32x4 *>(p + o0);
+        R.r[2 * f + 1] = *reinterpret_cast<const u32x4 *>(p + o1);
+    }
+}
+__device__ __forceinline__ void store_strip(uint8_t *xs, const Pixels &R, int lane)
+{
+    const uint32_t o0 = lane * 16, o1 = min(lane + 64, PIECES - 1) * 16;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        *reinterpret_cast<u32x4 *>(xs + f * (PIECES * 16) + o0) = R.r[2 * f];
+        *reinterpret_cast<u32x4 *>(xs + f * (PIECES * 16) + o1) = R.r[2 * f + 1];
+    }
 }
 
 // samples [lo, hi) of segment S, consumer wave (ph, hh) = (position half, channel half)
 __device__ __forceinline__ void run_consumer(const Seg &S, int lo, int hi, const uint8_t *ring, const v8bf (&wa)[16][2],
-                                             int lane, int ph, int hh)
+                                             int *strips, int *reads, int lane, int ph, int hh)
 {
     const int n = lane & 15, kg = lane >> 4;
-    const int ns = hi - lo, nint = intervals(ns);
+    const int ns = hi - lo;
     const v4f b0 = *reinterpret_cast<const v4f *>(S.b2 + 32 * hh + 8 * kg);
     const v4f b1 = *reinterpret_cast<const v4f *>(S.b2 + 32 * hh + 8 * kg + 4);
     uint32_t base[3];
     int pos[3];
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-        int p = 16 * (3 * ph + b) + n;
-        pos[b] = p;
-        if (p > 80) p = 80;   // positions past the end read a valid pixel and are not stored
+        const int p = pos[b] = S2::position(3 * ph + b, n);
         base[b] = S2::at(2 * (20 * (p / 9) + (p % 9)), kg);
     }
-    int kc = 0;   // next sample to consume
-    for (int i = 0; i < nint; ++i) {
-        if (kc < ns && consumed_in(kc, i)) {
-            const uint8_t *buf = ring + image_of_sample(kc) * S2::SAMPLE;
-            v4f acc[3][2];
+    for (int k = 0; k < ns; ++k) {
+        await_complete(strips + k);
+        const uint8_t *buf = ring + image_of_sample(k) * S2::SAMPLE;
+        v4f acc[3][2];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0};
-            // the operands of step st+1 are requested before the matrix instructions of step st
-            uint4 cur[3], nxt[3];
+        for (int b = 0; b < 3; ++b) acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0};
+        // the operands are requested two steps ahead of their matrix instructions
+        auto operand = [&](int st, int b) { return *reinterpret_cast<const uint4 *>(buf + base[b] + S2::at(20 * (st >> 2) + (st & 3), 0)); };
+        uint4 q[3][3];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) cur[b] = *reinterpret_cast<const uint4 *>(buf + base[b]);
+        for (int st = 0; st < 2; ++st)
 #pragma unroll
-            for (int st = 0; st < 16; ++st) {
-                if (st < 15) {
-                    const int off = (int)S2::at(20 * ((st + 1) >> 2) + ((st + 1) & 3), 0);
+            for (int b = 0; b < 3; ++b) q[st][b] = operand(st, b);
 #pragma unroll
-                    for (int b = 0; b < 3; ++b) nxt[b] = *reinterpret_cast<const uint4 *>(buf + base[b] + off);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+        for (int st = 0; st < 16; ++st) {
+            if (st < 14)
 #pragma unroll
-                for (int b = 0; b < 3; ++b) {
-                    const v8bf bb = __builtin_bit_cast(v8bf, cur[b]);
-                    acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
-                    acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int b = 0; b < 3; ++b) cur[b] = nxt[b];
-            }
-            bf16_t *y = S.y2 + (long)(lo + kc) * (81 * 64) + 32 * hh + 8 * kg;
+                for (int b = 0; b < 3; ++b) q[(st + 2) % 3][b] = operand(st + 2, b);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                if (pos[b] < 81) {
-                    const v4f a0 = acc[b][0], a1 = acc[b][1];
-                    const uint2 l2 = pack4(fmaxf(a0.x + b0.x, 0.f), fmaxf(a0.y + b0.y, 0.f), fmaxf(a0.z + b0.z, 0.f), fmaxf(a0.w + b0.w, 0.f));
-                    const uint2 h2 = pack4(fmaxf(a1.x + b1.x, 0.f), fmaxf(a1.y + b1.y, 0.f), fmaxf(a1.z + b1.z, 0.f), fmaxf(a1.w + b1.w, 0.f));
-                    *reinterpret_cast<uint4 *>(y + pos[b] * 64) = uint4{l2.x, l2.y, h2.x, h2.y};
-                }
+                const v8bf bb = __builtin_bit_cast(v8bf, q[st % 3][b]);
+                acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
+                acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
             }
-            ++kc;
+            __builtin_amdgcn_sched_barrier(0);
         }
-        sync_lds();
+        count_in(reads + k, lane);
+        bf16_t *y = S.y2 + (long)(lo + k) * (81 * 64) + 32 * hh + 8 * kg;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {   // (lanes that share a position store the same bits)
+            const v4f a0 = acc[b][0], a1 = acc[b][1];
+            const uint2 l2 = pack4(fmaxf(a0.x + b0.x, 0.f), fmaxf(a0.y + b0.y, 0.f), fmaxf(a0.z + b0.z, 0.f), fmaxf(a0.w + b0.w, 0.f));
+            const uint2 h2 = pack4(fmaxf(a1.x + b1.x, 0.f), fmaxf(a1.y + b1.y, 0.f), fmaxf(a1.z + b1.z, 0.f), fmaxf(a1.w + b1.w, 0.f));
+            *reinterpret_cast<uint4 *>(y + pos[b] * 64) = uint4{l2.x, l2.y, h2.x, h2.y};
+        }
     }
 }
 
 // samples [lo, hi) of segment S, producer wave w: strips w, w + 4, ... of the run's strip list.
 // R holds the pixels of strip w (requested by the caller); slots: the run's ring slots (ring mode).
-__device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, bf16_t *xs, uint8_t *ring, const int *slots,
-                                             StripRaw &R, const StripOff &O, int lane, int w)
+__device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8_t *xs, uint8_t *ring, const int *slots,
+                                             int *strips, int *reads, Pixels &R, int lane, int w)
 {
     const int n = lane & 15, kg = lane >> 4, oyl = n >> 2, q = n & 3;
-    const int ns = hi - lo, nstrips = UNITS * ns, nint = intervals(ns);
+    const int nstrips = UNITS * (hi - lo);
+    // where this lane's pixels 5 q + j of a strip's image row go, two columns apart for every second j
+    const int even = S2::at(20 * oyl + 5 * q, kg), odd = S2::at(20 * oyl + 5 * q + 1, kg);
+    const uint32_t yoff = ((20 * oyl + 5 * q) * 32 + 8 * kg) * 2;   // ... and in memory
     v8bf wa[8][2];   // [2c + xh][channel half], as in c1::conv1_fwd_units
 #pragma unroll
     for (int st = 0; st < 8; ++st)
@@ -1723,64 +1815,87 @@ __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, bf16_
         }
     const v4f b0 = *reinterpret_cast<const v4f *>(S.b1 + 8 * kg), b1 = *reinterpret_cast<const v4f *>(S.b1 + 8 * kg + 4);
     const uint32_t px = (uint32_t)(uintptr_t)(xs + (4 * oyl + 2 * kg) * 84 + 20 * q);
-    int u = w;
-    for (int i = 0; i < nint; ++i) {
-        if (u < nstrips) {
-            const int k = sample_of_strip(u), strip = u % UNITS;
-            c1::strip_store(xs, R, lane);   // LDS operations of one wave complete in order
-            const int un = u + PRODUCERS;
-            if (un < nstrips) c1::strip_load(R, S.src, lo + un / UNITS, S.src.idx ? slots[un / UNITS] : 0, un % UNITS, lane, O);
-            struct Quads { uint4 q[6]; };
-            auto quads = [&](int c) {   // see c1::conv1_fwd_units
-                typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-                const uint32_t addr = px + c * (c1::SROWS * 84 * 2);
-                Quads Q;
-#define C12_RD2(JJ) { v4u t; asm volatile("ds_read2_b64 %0, %1 offset0:%2 offset1:%3" : "=v"(t) : "v"(addr), "n"(JJ), "n"(JJ + 21)); Q.q[JJ] = uint4{t.x, t.y, t.z, t.w}; }
-                C12_RD2(0) C12_RD2(1) C12_RD2(2) C12_RD2(3) C12_RD2(4) C12_RD2(5)
+    auto slot_of = [&](int u) { return S.src.idx && u < nstrips ? slots[sample_of_strip(u)] : 0; };
+    int slot = slot_of(w + PRODUCERS);
+    for (int u = w; u < nstrips; u += PRODUCERS) {
+        const int k = sample_of_strip(u), strip = u % UNITS;
+        store_strip(xs, R, lane);            // (LDS operations of one wave complete in order)
+        asm volatile("" ::: "memory");       // ... and the reads below are not ordered behind stores by the compiler
+        const int un = u + PRODUCERS;
+        if (un < nstrips) load_strip(R, S.src, lo + un / UNITS, slot, un % UNITS, lane);
+        slot = slot_of(un + PRODUCERS);
+        // a frame's six quads of pixels (see c1::conv1_fwd_units), two rows each, requested two frames ahead
+        typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+        struct Bytes { v2u q[6]; };
+        struct Quads { uint4 q[6]; };
+        auto request = [&](int c) {
+            const uint32_t addr = px + c * (c1::SROWS * 84);
+            Bytes Q;
+#define C12_RD2(JJ) asm volatile("ds_read2_b32 %0, %1 offset0:%2 offset1:%3" : "=v"(Q.q[JJ]) : "v"(addr), "n"(JJ), "n"(JJ + 21));
+            C12_RD2(0) C12_RD2(1) C12_RD2(2) C12_RD2(3) C12_RD2(4) C12_RD2(5)
 #undef C12_RD2
-                return Q;
-            };
-            v4f acc[5][2];
+            return Q;
+        };
+        auto arrived = [&](Bytes &Q, bool more) {   // more: the six reads of another frame behind these
+            if (more) asm volatile("s_waitcnt lgkmcnt(6)" : "+v"(Q.q[0]), "+v"(Q.q[1]), "+v"(Q.q[2]), "+v"(Q.q[3]), "+v"(Q.q[4]), "+v"(Q.q[5])::"memory");
+            else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(Q.q[0]), "+v"(Q.q[1]), "+v"(Q.q[2]), "+v"(Q.q[3]), "+v"(Q.q[4]), "+v"(Q.q[5])::"memory");
+        };
+        auto widened = [&](const Bytes &Q) {
+            Quads W;
 #pragma unroll
-            for (int j = 0; j < 5; ++j) acc[j][0] = acc[j][1] = v4f{0, 0, 0, 0};
-            Quads cur = quads(0);
+            for (int j = 0; j < 6; ++j) W.q[j] = cvt8_u8(Q.q[j].x, Q.q[j].y);
+            return W;
+        };
+        v4f acc[5][2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                Quads nxt = cur;
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // `cur` has arrived
-                if (c < 3) nxt = quads(c + 1);
-                __builtin_amdgcn_sched_barrier(0);
+        for (int j = 0; j < 5; ++j) acc[j][0] = acc[j][1] = v4f{0, 0, 0, 0};
+        Bytes r0 = request(0), r1 = request(1);
+        arrived(r0, true);
+        Quads cur = widened(r0), nxt;
 #pragma unroll
-                for (int xh = 0; xh < 2; ++xh)
+        for (int c = 0; c < 4; ++c) {
+            Bytes &rn = c & 1 ? r0 : r1;   // frame c + 1
+            if (c < 2) (c & 1 ? r1 : r0) = request(c + 2);
+            if (c < 3) arrived(rn, c < 2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (c < 3) nxt = widened(rn);   // between the matrix instructions
 #pragma unroll
-                    for (int j = 0; j < 5; ++j) {
-                        const v8bf b = __builtin_bit_cast(v8bf, cur.q[j + xh]);
-                        acc[j][0] = mfma16(wa[2 * c + xh][0], b, acc[j][0]);
-                        acc[j][1] = mfma16(wa[2 * c + xh][1], b, acc[j][1]);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-                cur = nxt;
+            for (int xh = 0; xh < 2; ++xh)
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    const v8bf b = __builtin_bit_cast(v8bf, cur.q[j + xh]);
+                    acc[j][0] = mfma16(wa[2 * c + xh][0], b, acc[j][0]);
+                    acc[j][1] = mfma16(wa[2 * c + xh][1], b, acc[j][1]);
+                }
+            if (c < 3) {
+#pragma unroll
+                for (int g = 0; g < 20; ++g) {
+                    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
+                }
             }
-            // bias, 1/255, ReLU, bf16: into the sample's image in the ring and, where kept, to memory
-            uint8_t *img = ring + image_of_sample(k) * S2::SAMPLE;
-            uint8_t *yb = S.y1 ? reinterpret_cast<uint8_t *>(S.y1) + ((long)(lo + k) * 400 + 80 * strip) * 64 +
-                                     ((20 * oyl + 5 * q) * 32 + 8 * kg) * 2
-                               : nullptr;
-            constexpr float sc = 1.0f / 255.0f;
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                const v4f a0 = acc[j][0], a1 = acc[j][1];
-                const uint2 l2 = pack4(fmaxf(a0.x * sc + b0.x, 0.f), fmaxf(a0.y * sc + b0.y, 0.f),
-                                       fmaxf(a0.z * sc + b0.z, 0.f), fmaxf(a0.w * sc + b0.w, 0.f));
-                const uint2 h2 = pack4(fmaxf(a1.x * sc + b1.x, 0.f), fmaxf(a1.y * sc + b1.y, 0.f),
-                                       fmaxf(a1.z * sc + b1.z, 0.f), fmaxf(a1.w * sc + b1.w, 0.f));
-                const uint4 v = uint4{l2.x, l2.y, h2.x, h2.y};
-                *reinterpret_cast<uint4 *>(img + S2::at(80 * strip + 20 * oyl + 5 * q + j, kg)) = v;
-                if (yb) *reinterpret_cast<uint4 *>(yb + j * 64) = v;
-            }
-            u = un;
+            __builtin_amdgcn_sched_barrier(0);
+            cur = nxt;
         }
-        sync_lds();
+#pragma unroll
+        for (int j = 0; j < 5; ++j) asm volatile("" : "+v"(acc[j][0]), "+v"(acc[j][1]));   // (half of the products would sink below the wait)
+        await_image(reads, k);
+        // bias, 1/255, ReLU, bf16: into the sample's image in the ring and, where kept, to memory
+        uint8_t *img = ring + image_of_sample(k) * S2::SAMPLE + strip * (4 * S2::RB);
+        uint8_t *yb = S.y1 ? reinterpret_cast<uint8_t *>(S.y1) + ((long)(lo + k) * 400 + 80 * strip) * 64 : nullptr;   // uniform
+        constexpr float sc = 1.0f / 255.0f;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            const v4f a0 = acc[j][0], a1 = acc[j][1];
+            const uint2 l2 = pack4(fmaxf(a0.x * sc + b0.x, 0.f), fmaxf(a0.y * sc + b0.y, 0.f),
+                                   fmaxf(a0.z * sc + b0.z, 0.f), fmaxf(a0.w * sc + b0.w, 0.f));
+            const uint2 h2 = pack4(fmaxf(a1.x * sc + b1.x, 0.f), fmaxf(a1.y * sc + b1.y, 0.f),
+                                   fmaxf(a1.z * sc + b1.z, 0.f), fmaxf(a1.w * sc + b1.w, 0.f));
+            const uint4 v = uint4{l2.x, l2.y, h2.x, h2.y};
+            *reinterpret_cast<uint4 *>(img + (j & 1 ? odd : even) + (j >> 1) * 64) = v;
+            if (yb) *reinterpret_cast<uint4 *>(yb + yoff + j * 64) = v;
+        }
+        count_in(strips + k, lane);
     }
 }
 
@@ -1807,6 +1922,8 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     float *leafv = reinterpret_cast<float *>(slots + MAX_PER_WG);   // [MAX_PER_WG] leaf values, then the total
+    int *strips = reinterpret_cast<int *>(leafv + MAX_PER_WG + 4), *reads = strips + MAX_PER_WG;
+    if (tid < 2 * MAX_PER_WG) strips[tid] = 0;   // (both)
 
     // The slots of the run: drawn here, two per wave and walk, or copied from the index list.  Nothing but
     // the slot stands between a draw and the first pixel request, so the walk leaves the leaf's value and
@@ -1853,21 +1970,15 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
                 wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(S.w2 + (32 * hh + chl) * 512 + st * 32 + kg * 8));
             }
         fill_slots();
-        sync_lds();   // the slot table is complete
+        sync_lds();   // the slot table is complete, the counts are zero
         if (wave == 4) publish_draws();   // the consumers wait for the first image anyway
-        run_consumer(S, lo, hi, ring, wa, lane, ph, hh);
+        run_consumer(S, lo, hi, ring, wa, strips, reads, lane, ph, hh);
     } else {
-        StripOff O;
-#pragma unroll
-        for (int i = 0; i < 7; ++i) {
-            const int t = lane + 64 * i;
-            O.off[i] = t < c1::CHUNKS ? (t / (c1::CHUNKS / 4)) * c1::FR + (t % (c1::CHUNKS / 4)) * 16 : 0;
-        }
         fill_slots();
-        sync_lds();   // the slot table is complete
-        StripRaw R;
-        if (wave < UNITS * ns) c1::strip_load(R, S.src, lo + wave / UNITS, S.src.idx ? slots[wave / UNITS] : 0, wave % UNITS, lane, O);
-        run_producer(S, lo, hi, reinterpret_cast<bf16_t *>(lds) + wave * STRIP, ring, slots, R, O, lane, wave);
+        sync_lds();   // the slot table is complete, the counts are zero
+        Pixels R;
+        if (wave < UNITS * ns) load_strip(R, S.src, lo + wave / UNITS, S.src.idx ? slots[wave / UNITS] : 0, wave % UNITS, lane);
+        run_producer(S, lo, hi, lds + wave * STRIP, ring, slots, strips, reads, R, lane, wave);
     }
 }
 }  // namespace c12
