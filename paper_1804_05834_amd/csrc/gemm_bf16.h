@@ -110,6 +110,16 @@ __device__ __forceinline__ v8bf frag_tr(const bf16_t *p, int ld)
     return __builtin_bit_cast(v8bf, r);
 }
 
+// A [reduction][COLS] tile for frag_tr, without padding.  The hardware serves such a read half a wave at a time (measured):
+// four consecutive rows of one block of 32 columns, 64 bytes each.  The blocks of a row are permuted by the row's number so
+// that those four lie in all 64 banks side by side.  (Rows padded by 16 bytes instead: 1.6 times the cycles per read
+// with 64 columns, 3 times with 128.)  Rows four apart are permuted alike.
+template <int COLS> struct TrTile {
+    static_assert(COLS == 64 || COLS == 128, "two or four blocks");
+    static __device__ __forceinline__ int block(int row, int blk) { return blk ^ (COLS == 64 ? (row >> 1) & 1 : row & 3); }
+    static __device__ __forceinline__ int at(int row, int col) { return row * COLS + block(row, col >> 5) * 32 + (col & 31); }
+};
+
 using g32::GConv1;
 using g32::GConv2;
 using g32::GConv3;
@@ -396,7 +406,7 @@ struct DgradArgs {
 // single output block alternates between two accumulators so that consecutive MFMAs do not wait
 // for each other's result.
 // LDS elements of an input-gradient tile
-template <int BM, int BN, bool DB> constexpr int dgrad_lds() { return (DB ? 2 : 1) * (BM * LDK + BK * (BN + 8)); }
+template <int BM, int BN, bool DB> constexpr int dgrad_lds() { return (DB ? 2 : 1) * (BM * LDK + BK * BN); }
 
 // Tile number t of a (gx, gy, gz) grid of tiles; tile order: the parity classes of one row tile
 // together, then the row tiles of one column tile.
@@ -405,11 +415,11 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
 {
     constexpr int WAVES_M = BM / (32 * WM), WAVES_N = BN / (32 * WN), T = WAVES_M * WAVES_N * 64;
     constexpr int NA = BM * 8 / T;
-    constexpr int LDB = BN + 8;          // row stride of the [k][c] weight tile
+    constexpr int LDB = BN;              // row stride of the [k][c] weight tile
     constexpr int BCH = BN / 8;          // 16-byte chunks per weight-tile row
     constexpr int BROWS = T / BCH;       // rows filled per pass
     constexpr int NBL = (BK + BROWS - 1) / BROWS;
-    static_assert(NA * T == BM * 8 && D::CO % BK == 0, "tile/threads mismatch");
+    static_assert(NA * T == BM * 8 && D::CO % BK == 0 && BROWS % 4 == 0, "tile/threads mismatch");
     constexpr int NBUF = DB ? 2 : 1;
     constexpr bool ACC2 = DB && WM * WN == 1;
     bf16_t(*As2)[BM * LDK] = reinterpret_cast<bf16_t(*)[BM * LDK]>(lds);
@@ -435,7 +445,7 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
             rn[i] = -1; rh[i] = 0; rw[i] = 0;
         }
     }
-    const int br = tid / BCH, bc = (tid % BCH) * 8;
+    const int br = tid / BCH, bc = (tid % BCH) * 8, bst = TrTile<BN>::at(br, bc);
     uint4 ra[NA], rb[NBL];
     auto gload = [&](int k0) {
         const int tap = k0 / D::CO, o0 = k0 % D::CO;
@@ -461,7 +471,7 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
 #pragma unroll
         for (int i = 0; i < NBL; ++i) {
             int r = br + i * BROWS;
-            if (r < BK) *reinterpret_cast<uint4 *>(&Bs[r * LDB + bc]) = rb[i];
+            if (r < BK) *reinterpret_cast<uint4 *>(&Bs[i * BROWS * LDB + bst]) = rb[i];
         }
     };
 
@@ -469,7 +479,9 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     const int li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
     const int apo = (wm * 32 * WM + li) * LDK + 8 * h;
     // transpose-read base: row 8h + s/4, column (wave block) + 16*half + 4*(s%4)
-    const int bpo = (8 * h + (s16 >> 2)) * LDB + wn * 32 * WN + 16 * half + 4 * (s16 & 3);
+    int bpo[WN];
+#pragma unroll
+    for (int b = 0; b < WN; ++b) bpo[b] = TrTile<BN>::at(8 * h + (s16 >> 2), (wn * WN + b) * 32 + 16 * half + 4 * (s16 & 3));
     v16f acc[WM][WN];
 #pragma unroll
     for (int a = 0; a < WM; ++a)
@@ -500,13 +512,13 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
 
     v16f acc2 = {0};   // second accumulator (ACC2 only)
     auto compute = [&](int buf) {
-        const bf16_t *ap = As2[buf] + apo, *bp = Bs2[buf] + bpo;
+        const bf16_t *ap = As2[buf] + apo, *bp = Bs2[buf];
         // the fragments of a 16-deep step are requested before the matrix instructions of the step before it
         auto frags = [&](int kk, v8bf (&fa)[WM], v8bf (&fb)[WN]) {
 #pragma unroll
             for (int a = 0; a < WM; ++a) fa[a] = frag_k(ap + a * 32 * LDK + kk);
 #pragma unroll
-            for (int b = 0; b < WN; ++b) fb[b] = frag_tr(bp + kk * LDB + b * 32, LDB);
+            for (int b = 0; b < WN; ++b) fb[b] = frag_tr(bp + kk * LDB + bpo[b], LDB);
         };
         v8bf fa[WM], fb[WN], fan[WM], fbn[WN];
         frags(0, fa, fb);
@@ -589,7 +601,7 @@ struct WgradArgs {
 };
 
 // LDS elements of a weight-gradient tile
-template <int BMO, int BNK, bool DB> constexpr int wgrad_lds() { return (DB ? 2 : 1) * BK * (BMO + 8 + BNK + 8); }
+template <int BMO, int BNK, bool DB> constexpr int wgrad_lds() { return (DB ? 2 : 1) * BK * (BMO + BNK); }
 
 // Tile number t of a (gx, gy, gz) grid of tiles; tile order: with row splits (conv layers) all
 // tiles of one split together; without (fc1) all output tiles of one input-column tile together.
@@ -599,10 +611,11 @@ template <class G, int BMO, int BNK, int WM, int WN, bool DB>
 __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, int gy, int gz, bf16_t *lds)
 {
     constexpr int WAVES_M = BMO / (32 * WM), WAVES_N = BNK / (32 * WN), T = WAVES_M * WAVES_N * 64;
-    constexpr int LDY = BMO + 8, LDX = BNK + 8;
+    constexpr int LDY = BMO, LDX = BNK;
     constexpr int YCH = BMO / 8, XCH = BNK / 8;          // 16-byte chunks per tile row
     constexpr int YR = T / YCH, XR = T / XCH;            // rows filled per pass
     constexpr int NY = (BK + YR - 1) / YR, NX = (BK + XR - 1) / XR;
+    static_assert(YR % 4 == 0 && XR % 4 == 0, "rows permuted alike");
     using in_t = typename in_type<G>::t;
     constexpr int NBUF = DB ? 2 : 1;
     constexpr bool ACC2 = DB && WM * WN <= 2;   // two alternating accumulators per output block
@@ -624,6 +637,7 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
     const int yr = tid / YCH, yc = (tid % YCH) * 8;
     const int xr = tid / XCH, xc = (tid % XCH) * 8;
     const int xko = G::k_off(kc0 + xc);
+    const int yst = TrTile<BMO>::at(yr, yc), xst = TrTile<BNK>::at(xr, xc);
     uint4 ry[NY], rx[NX];
     auto gload = [&](int mb) {
 #pragma unroll
@@ -642,19 +656,23 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
 #pragma unroll
         for (int i = 0; i < NY; ++i) {
             int r = yr + i * YR;
-            if (r < BK) *reinterpret_cast<uint4 *>(&Ys[r * LDY + yc]) = ry[i];
+            if (r < BK) *reinterpret_cast<uint4 *>(&Ys[i * YR * LDY + yst]) = ry[i];
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
             int r = xr + i * XR;
-            if (r < BK) *reinterpret_cast<uint4 *>(&Xs[r * LDX + xc]) = rx[i];
+            if (r < BK) *reinterpret_cast<uint4 *>(&Xs[i * XR * LDX + xst]) = rx[i];
         }
     };
 
     const int wo = wave % WAVES_M, wk = wave / WAVES_M;
     const int li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
     const int trow = 8 * h + (s16 >> 2), tcol = 16 * half + 4 * (s16 & 3);
-    const int ypo = trow * LDY + wo * 32 * WM + tcol, xpo = trow * LDX + wk * 32 * WN + tcol;
+    int ypo[WM], xpo[WN];
+#pragma unroll
+    for (int a = 0; a < WM; ++a) ypo[a] = TrTile<BMO>::at(trow, (wo * WM + a) * 32 + tcol);
+#pragma unroll
+    for (int b = 0; b < WN; ++b) xpo[b] = TrTile<BNK>::at(trow, (wk * WN + b) * 32 + tcol);
     const bool do_bias = bx == 0 && wk == 0;
     v16f acc[WM][WN], accb[WM];
 #pragma unroll
@@ -673,13 +691,13 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
 #pragma unroll
         for (int b = 0; b < WN; ++b) acc2[a][b] = v16f{0};
     auto compute = [&](int buf) {
-        const bf16_t *yp = Ys2[buf] + ypo, *xp = Xs2[buf] + xpo;
+        const bf16_t *yp = Ys2[buf], *xp = Xs2[buf];
         // the fragments of a 16-deep step are requested before the matrix instructions of the step before it
         auto frags = [&](int kk, v8bf (&fa)[WM], v8bf (&fb)[WN]) {
 #pragma unroll
-            for (int a = 0; a < WM; ++a) fa[a] = frag_tr(yp + kk * LDY + a * 32, LDY);
+            for (int a = 0; a < WM; ++a) fa[a] = frag_tr(yp + kk * LDY + ypo[a], LDY);
 #pragma unroll
-            for (int b = 0; b < WN; ++b) fb[b] = frag_tr(xp + kk * LDX + b * 32, LDX);
+            for (int b = 0; b < WN; ++b) fb[b] = frag_tr(xp + kk * LDX + xpo[b], LDX);
         };
         v8bf fa[WM], fb[WN], fan[WM], fbn[WN];
         frags(0, fa, fb);
@@ -1252,7 +1270,9 @@ struct WgradArgs {
     int nsplit;        // = gridDim.x; workgroup z sums samples z, z+nsplit, ...
 };
 
-constexpr int LDY1 = 40;  // row stride (elements) of the staged dY tile
+// Row stride (elements) of the staged dY tile.  No padding: an 8-byte transpose read is served half a wave at a time, here
+// four rows of 64 bytes, which lie in all 64 banks side by side (with 40 the fourth row met the first).
+constexpr int LDY1 = 32;
 
 // grid (nsplit, 2): a workgroup takes one channel pair y (frames 2y, 2y+1 = im2col columns
 // 128y .. 128y+127), so a workgroup stages half a state and two workgroups fit one CU.
@@ -2310,8 +2330,20 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 // ===========================================================================
 namespace dps {
 using ps::u32x4;
-constexpr int PIX = 144;             // LDS bytes per dY pixel (128 + 16)
-constexpr int IMG = 11 * 11 * PIX;   // the 9x9 image inside a border of one zero pixel
+// The 9x9 image inside a border of one zero pixel: LDS bytes per pixel (128 + 32) and per row, and the ten by ten pixels of a
+// parity class in tiles of sixteen.  As in ps::Shape: over two rows of eight pixels the sixteen lanes that are served
+// together read from the sixteen different 16-byte columns of LDS (pixels in order at a pitch of 144: nearly every
+// read took twice as long).
+constexpr int PIX = 160, ROW = 11 * PIX + 32;
+constexpr int IMG = 11 * ROW;
+static_assert(ROW % 256 == 0, "rows of whole LDS lines");
+struct Place { int y, x; };
+// pixel n of tile b: five tiles of two rows of eight, then the last two columns; pixels that do not exist repeat another
+__device__ __forceinline__ Place place_of(int b, int n)
+{
+    if (b < 5) return Place{2 * b + (n >> 3), n & 7};
+    return Place{b == 5 ? n >> 1 : 8 + ((n >> 1) & 1), 8 + (n & 1)};
+}
 
 struct Args {
     const bf16_t *dy;    // [B][positions out][64]
@@ -2387,17 +2419,16 @@ __device__ __forceinline__ void conv2_dgrad_ps_body(const Args &A, int bid, int 
     // pixel (2a + py, 2b + px) takes dY positions (a - ty, b - tx); image pixel (a - ty + 1, b - tx + 1) holds them.
     // base = the (ty, tx) = (1, 1) corner, i.e. image pixel (a, b)
     uint32_t base[7];
-    int pos[7];
+    int pix[7];   // its pixel
 #pragma unroll
     for (int b = 0; b < 7; ++b) {
-        int p = 16 * b + n;
-        pos[b] = p;
-        if (p > 99) p = 99;
-        base[b] = ((p / 10) * 11 + (p % 10)) * PIX + kg * 16;
+        const Place P = place_of(b, n);
+        base[b] = P.y * ROW + P.x * PIX + kg * 16;
+        pix[b] = (2 * P.y + py) * 20 + 2 * P.x + px;
     }
     for (int g = g0; g < g1; ++g) {
         sync_lds();   // the previous sample's image (and, the first time, the weights in transit) has been read
-#define DPS_ST(I, V) { const int t = tid + 256 * I; const int q = t >> 3; *reinterpret_cast<u32x4 *>(img + ((q / 9 + 1) * 11 + q % 9 + 1) * PIX + (t & 7) * 16) = V; }
+#define DPS_ST(I, V) { const int t = tid + 256 * I; const int q = t >> 3; *reinterpret_cast<u32x4 *>(img + (q / 9 + 1) * ROW + (q % 9 + 1) * PIX + (t & 7) * 16) = V; }
         DPS_ST(0, r0) DPS_ST(1, r1)
         if (tid < 136) DPS_ST(2, r2)
 #undef DPS_ST
@@ -2405,11 +2436,7 @@ __device__ __forceinline__ void conv2_dgrad_ps_body(const Args &A, int bid, int 
         const long obase = (long)g * (400 * 32) + 8 * kg;
         uint4 mk[7];
 #pragma unroll
-        for (int b = 0; b < 7; ++b) {
-            const int p = pos[b] > 99 ? 99 : pos[b];
-            const int y = 2 * (p / 10) + py, x = 2 * (p % 10) + px;
-            mk[b] = *reinterpret_cast<const uint4 *>(A.xact + obase + (y * 20 + x) * 32);
-        }
+        for (int b = 0; b < 7; ++b) mk[b] = *reinterpret_cast<const uint4 *>(A.xact + obase + pix[b] * 32);
         sync_lds();
 #pragma unroll
         for (int b = 0; b < 7; ++b) {
@@ -2417,16 +2444,13 @@ __device__ __forceinline__ void conv2_dgrad_ps_body(const Args &A, int bid, int 
 #pragma unroll
             for (int st = 0; st < 8; ++st) {
                 const int tap = st >> 1, ty = tap >> 1, tx = tap & 1;
-                const int off = ((1 - ty) * 11 + (1 - tx)) * PIX + (st & 1) * 64;
+                const int off = (1 - ty) * ROW + (1 - tx) * PIX + (st & 1) * 64;
                 const v8bf bb = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(img + base[b] + off));
                 acc0 = mfma16(wa[st][0], bb, acc0);
                 acc1 = mfma16(wa[st][1], bb, acc1);
             }
-            if (pos[b] < 100) {
-                const int p = pos[b];
-                const int y = 2 * (p / 10) + py, x = 2 * (p % 10) + px;
-                *reinterpret_cast<uint4 *>(A.dx + obase + (y * 20 + x) * 32) = masked8(mk[b], acc0, acc1);
-            }
+            // (lanes that share a pixel store the same bits)
+            *reinterpret_cast<uint4 *>(A.dx + obase + pix[b] * 32) = masked8(mk[b], acc0, acc1);
         }
     }
 }
@@ -2447,9 +2471,9 @@ struct FusedArgs {
     float *part1;     // [nblocks][32*256 + 32]
     const bf16_t *w2t;  // conv2's weights as [tap][channel in][channel out]
 };
-constexpr int FUSED_DYS = 400 * c1::LDY1 * 2;             // 32,000 bytes: conv1's dY as the weight gradient reads it
+constexpr int FUSED_DYS = 400 * c1::LDY1 * 2;             // 25,600 bytes: conv1's dY as the weight gradient reads it
 constexpr int FUSED_XIN = 2 * c1::FR * 2;                 // 28,224 bytes: two frames as bf16
-constexpr int FUSED_LDS = FUSED_DYS + FUSED_XIN + IMG;    // 77,648 bytes
+constexpr int FUSED_LDS = FUSED_DYS + FUSED_XIN + IMG;    // 73,536 bytes
 
 __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F, int bid, int nblocks, uint8_t *lds)
 {
@@ -2483,10 +2507,9 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
                 wa[2 * tap + half][cb] = __builtin_bit_cast(
                     v8bf, *reinterpret_cast<const uint4 *>(F.w2t + (((ky * 4 + kx) * 32 + ci) * 64 + 32 * half + 8 * kg)));
             }
-    // position 16b + n of the wave's parity class (block b), clamped; its dY corner in the image; its pixel
-    auto pos_of = [&](int b) { const int p = 16 * b + n; return p > 99 ? 99 : p; };
-    auto base_of = [&](int p) { return (uint32_t)(((p / 10) * 11 + (p % 10)) * PIX + kg * 16); };
-    auto pixel_of = [&](int p) { return (2 * (p / 10) + py) * 20 + 2 * (p % 10) + px; };
+    // this lane's place of tile b in the wave's parity class: its dY corner in the image; its pixel
+    auto base_of = [&](int b) { const Place P = place_of(b, n); return (uint32_t)(P.y * ROW + P.x * PIX + kg * 16); };
+    auto pixel_of = [&](int b) { const Place P = place_of(b, n); return (2 * P.y + py) * 20 + 2 * P.x + px; };
     // conv1's weight gradient: this lane's share as in c1::conv1_wgrad_block (wave = block of 32 im2col columns)
     typedef __attribute__((address_space(3))) v4s *lds_v4s;
     const int li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
@@ -2503,7 +2526,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
 
     for (int g = bid; g < A.B; g += nblocks) {
         sync_lds();   // the previous sample's image, dY tile and frames have been read (the first time: the image is cleared)
-#define DPS_ST(I, V) { const int t = tid + 256 * I; const int q = t >> 3; *reinterpret_cast<u32x4 *>(img + ((q / 9 + 1) * 11 + q % 9 + 1) * PIX + (t & 7) * 16) = V; }
+#define DPS_ST(I, V) { const int t = tid + 256 * I; const int q = t >> 3; *reinterpret_cast<u32x4 *>(img + (q / 9 + 1) * ROW + (q % 9 + 1) * PIX + (t & 7) * 16) = V; }
         DPS_ST(0, r0) DPS_ST(1, r1)
         if (tid < 136) DPS_ST(2, r2)
 #undef DPS_ST
@@ -2511,41 +2534,41 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
         if (gn < A.B) load_dy(gn);
         const bf16_t *xg = A.xact + (long)g * (400 * 32) + 8 * kg;
         // ReLU masks two blocks ahead of their use (all seven at once would cost 28 registers)
-        uint4 mk0 = *reinterpret_cast<const uint4 *>(xg + pixel_of(pos_of(0)) * 32);
-        uint4 mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(pos_of(1)) * 32);
+        uint4 mk0 = *reinterpret_cast<const uint4 *>(xg + pixel_of(0) * 32);
+        uint4 mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(1) * 32);
         // the sample's four frames are on their way while the input gradient is computed
         c1::stage_load<256, 2>(R, F.src, g, slot_g, 0, tid);
         c1::stage_load<256, 2>(R2, F.src, g, slot_g, 2, tid);
         const int slot_n = gn < A.B ? c1::sample_slot(F.src, gn) : 0;
         sync_lds();
-        // the operand of reduction step st + 1 (of the next block after a block's last step) is requested before
-        // the matrix instructions of step st
-        auto operand = [&](int b, int st) {
-            const int tap = st >> 1, ty = tap >> 1, tx = tap & 1;
-            const int off = ((1 - ty) * 11 + (1 - tx)) * PIX + (st & 1) * 64;
-            return *reinterpret_cast<const uint4 *>(img + base_of(pos_of(b)) + off);
+        // the operands are requested three reduction steps ahead (into the next blocks): a step's two matrix instructions
+        // are a quarter of what a read takes
+        constexpr int AHEAD = 3;
+        auto operand = [&](int i) {   // step i % 8 of block i / 8
+            const int b = i >> 3, st = i & 7, tap = st >> 1, ty = tap >> 1, tx = tap & 1;
+            const int off = (1 - ty) * ROW + (1 - tx) * PIX + (st & 1) * 64;
+            return *reinterpret_cast<const uint4 *>(img + base_of(b) + off);
         };
-        uint4 cur = operand(0, 0);
+        uint4 q[AHEAD + 1];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) q[i] = operand(i);
 #pragma unroll
         for (int b = 0; b < 7; ++b) {
-            const int p = pos_of(b);
             const uint4 mk = mk0;
             mk0 = mk1;
-            if (b + 2 < 7) mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(pos_of(b + 2)) * 32);
+            if (b + 2 < 7) mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(b + 2) * 32);
             v4f acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
 #pragma unroll
             for (int st = 0; st < 8; ++st) {
-                uint4 nxt = cur;
-                if (st < 7) nxt = operand(b, st + 1);
-                else if (b < 6) nxt = operand(b + 1, 0);
+                const int i = 8 * b + st;
+                if (i + AHEAD < 56) q[(i + AHEAD) % (AHEAD + 1)] = operand(i + AHEAD);
                 __builtin_amdgcn_sched_barrier(0);
-                const v8bf bb = __builtin_bit_cast(v8bf, cur);
+                const v8bf bb = __builtin_bit_cast(v8bf, q[i % (AHEAD + 1)]);
                 acc0 = mfma16(wa[st][0], bb, acc0);
                 acc1 = mfma16(wa[st][1], bb, acc1);
                 __builtin_amdgcn_sched_barrier(0);
-                cur = nxt;
             }
-            if (16 * b + n < 100) *reinterpret_cast<uint4 *>(dys + pixel_of(p) * LDY1 + 8 * kg) = masked8(mk, acc0, acc1);
+            *reinterpret_cast<uint4 *>(dys + pixel_of(b) * LDY1 + 8 * kg) = masked8(mk, acc0, acc1);
         }
 #pragma unroll
         for (int cp = 0; cp < 2; ++cp) {
@@ -2553,7 +2576,8 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
             c1::stage_store<256, 2>(xin, cp == 0 ? R : R2, tid);
             sync_lds();   // the dY tile and the pair's frames are complete
             const bool do_bias = cp == 0 && wave == 0;
-            // the operands of step t + 1 are requested before the matrix instruction of step t
+            // the operands are requested two steps ahead
+            constexpr int AHEAD = 2;
             auto operands = [&](int t, v8bf &fa, v8bf &fb) {   // 16 output pixels per step
                 fa = frag_tr(yp + 16 * t * LDY1, LDY1);
                 // see c1::conv1_wgrad_block: no division
@@ -2566,17 +2590,17 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
                 v8s xb = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
                 fb = __builtin_bit_cast(v8bf, xb);
             };
-            v8bf fa, fb, fan, fbn;
-            operands(0, fa, fb);
+            v8bf fa[AHEAD + 1], fb[AHEAD + 1];
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) operands(t, fa[t], fb[t]);
 #pragma unroll
             for (int t = 0; t < 25; ++t) {
-                fan = fa; fbn = fb;
-                if (t + 1 < 25) operands(t + 1, fan, fbn);
+                constexpr int N = AHEAD + 1;
+                if (t + AHEAD < 25) operands(t + AHEAD, fa[(t + AHEAD) % N], fb[(t + AHEAD) % N]);
                 __builtin_amdgcn_sched_barrier(0);
-                acc[cp] = mfma(fa, fb, acc[cp]);
-                if (do_bias) accb = mfma(fa, ones, accb);
+                acc[cp] = mfma(fa[t % N], fb[t % N], acc[cp]);
+                if (do_bias) accb = mfma(fa[t % N], ones, accb);
                 __builtin_amdgcn_sched_barrier(0);
-                fa = fan; fb = fbn;
             }
         }
         slot_g = slot_n;
