@@ -527,9 +527,10 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
                 else sp::k_conv123_step<4, 4><<<dim3(nat + plan.grid), 512, sp::step_lds<4, 4>(), st>>>(S);
             });
         } else launch(c, "conv123_fwd", st, [&] {
-            if (plan.r3 == 1) sp::k_conv123_fwd<1><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
-            else if (plan.r3 == 4) sp::k_conv123_fwd<4><<<dim3(plan.grid), 512, sp::Geo<4>::LDS, st>>>(A);
-            else sp::k_conv123_fwd<7><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
+            if (plan.r3 == 1) sp::k_conv123_fwd<1, false><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 4) sp::k_conv123_fwd<4, false><<<dim3(plan.grid), 512, sp::Geo<4>::LDS, st>>>(A);
+            else if (A.units <= plan.grid) sp::k_conv123_fwd<7, false><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
+            else sp::k_conv123_fwd<7, true><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
         });
     }
     if (p0 > 0 && !step) {   // the passes [0, p0), layer by layer
@@ -613,9 +614,10 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         if (draw) A.samp = *draw;
         A.clear = few_rows ? w.arrivals : nullptr;
         launch(c, "conv123_fwd", st, [&] {
-            if (plan.r3 == 1) c123::k_conv123_fwd<1><<<dim3(plan.grid), 512, c123::Geo<1>::LDS, st>>>(A);
-            else if (plan.r3 == 4) c123::k_conv123_fwd<4><<<dim3(plan.grid), 512, c123::Geo<4>::LDS, st>>>(A);
-            else c123::k_conv123_fwd<7><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
+            if (plan.r3 == 1) c123::k_conv123_fwd<1, false><<<dim3(plan.grid), 512, c123::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 4) c123::k_conv123_fwd<4, false><<<dim3(plan.grid), 512, c123::Geo<4>::LDS, st>>>(A);
+            else if (A.units <= plan.grid) c123::k_conv123_fwd<7, false><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
+            else c123::k_conv123_fwd<7, true><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
         });
     }
     // conv1 + conv2 as one launch, one workgroup per CU (faster from a handful of samples on)
@@ -1277,8 +1279,8 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         return false;
     };
     if (cfg->precision == 0) {
-        c->split = granted(sp::k_conv123_fwd<1>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<4>, sp::Geo<4>::LDS) &&
-                   granted(sp::k_conv123_fwd<7>, sp::Geo<7>::LDS) && granted(sp::k_conv123_step<1, 2>, sp::step_lds<1, 2>()) &&
+        c->split = granted(sp::k_conv123_fwd<1, false>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<4, false>, sp::Geo<4>::LDS) &&
+                   granted(sp::k_conv123_fwd<7, false>, sp::Geo<7>::LDS) && granted(sp::k_conv123_fwd<7, true>, sp::Geo<7>::LDS) && granted(sp::k_conv123_step<1, 2>, sp::step_lds<1, 2>()) &&
                    granted(sp::k_conv123_step<4, 2>, sp::step_lds<4, 2>()) && granted(sp::k_conv123_step<4, 4>, sp::step_lds<4, 4>()) &&
                    granted(k_conv21_bwd_sp, CONV21_LDS);
     } else {
@@ -1286,8 +1288,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         // conv1 + conv2 are one launch, in the form without the three-layer launch; a huge value: never
         const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");
         if (granted(gbf::c12::k_conv12_fwd, gbf::c12::LDS_BYTES)) c->conv12_min = m && m[0] ? std::atoi(m) : 8;
-        c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1>, gbf::c123::Geo<1>::LDS) &&
-                     granted(gbf::c123::k_conv123_fwd<4>, gbf::c123::Geo<4>::LDS) && granted(gbf::c123::k_conv123_fwd<7>, gbf::c123::Geo<7>::LDS);
+        c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1, false>, gbf::c123::Geo<1>::LDS) &&
+                     granted(gbf::c123::k_conv123_fwd<4, false>, gbf::c123::Geo<4>::LDS) &&
+                     granted(gbf::c123::k_conv123_fwd<7, false>, gbf::c123::Geo<7>::LDS) && granted(gbf::c123::k_conv123_fwd<7, true>, gbf::c123::Geo<7>::LDS);
         // DQN_FUSED_BWD=0 in the environment keeps conv1's weight gradient a launch of its own
         m = std::getenv("DQN_FUSED_BWD");
         c->fused_bwd = !(m && m[0] == '0') && granted(k_conv21_bwd_pu, gbf::dps::FUSED_LDS);

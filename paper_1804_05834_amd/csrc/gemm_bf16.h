@@ -2009,9 +2009,10 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
 // A unit is the part of a sample that yields R3 of conv3's seven output rows (see sp::k_conv123_fwd, the fp32
 // form of this kernel: same units, same phases).  One workgroup of eight waves takes a unit through all
 // three layers in LDS, phase by phase, every wave in the same phase; the weights stay in registers (200),
-// taken once per workgroup from the packed copy.  With R3 = 7 they do not all fit beside the next unit's pixels: 42 registers
-// are spilled, and a workgroup with a single unit still loads "its next" one's pixels, its own once more (conv launch of a
-// step at 77: 15 of 65 us; R3 = 1 and 4 take one unit and spill nothing).  16x16x32 instructions, transposed tiles:
+// taken once per workgroup from the packed copy.  A workgroup that takes several whole samples (R3 = 7, MANY) spills 37 registers
+// beside the next one's pixels; with a unit each, the form without the next one spills none and does not fetch its own pixels
+// twice (conv launch of a step at 77: 14.9 -> 12.9 us, of 256 observations 15.6 -> 14.2).  The images are laid out for the lanes
+// that LDS serves together (Geo; at 77 12.9 -> 11.8).  16x16x32 instructions, transposed tiles:
 //   conv1   wave = every eighth tile of 16 pixels, all 32 channels: a pixel fragment serves two products
 //   conv2/3 wave = 16 channels, half of the tiles: the sum over the taps stays in one wave
 // k_conv12_fwd overlaps conv1 of one sample with conv2 of another and is as fast per sample once it runs, but it
@@ -2038,19 +2039,32 @@ struct Args {
 constexpr int MAX_UNITS = 96;
 template <int R3> struct Geo {
     static constexpr int PARTS = (7 + R3 - 1) / R3;
-    static constexpr bool MANY = R3 == 7;   // a workgroup takes one unit after the other; otherwise just one
     static constexpr int R2 = R3 + 2, R1 = 2 * R3 + 6, PR = 4 * R1 + 4;
     static constexpr int M1 = R1 * 20, M2 = R2 * 9, M3 = R3 * 7;
     static constexpr int T1 = (M1 + 15) / 16, T2 = (M2 + 31) / 32, T3 = (M3 + 31) / 32;   // tiles of conv1; of conv2 / conv3 per wave
     static constexpr int CH = PR * 84 / 16, NPX = (4 * CH + 511) / 512;
-    static constexpr int PXB = 4 * PR * 84 * 2, P1 = 80, P2 = 144;
-    static constexpr int I1B = M1 * P1, I2B = M2 * P2;
+    // conv1's and conv2's images, laid out and read as the samples of ps::Shape are: sixteen lanes, sixteen columns of LDS.
+    // Bytes per pixel and row
+    static constexpr int PXB = 4 * PR * 84 * 2, P1 = 64, B1 = (20 * 4 + 1) * 16, P2 = 144, B2 = 96 * 16;
+    static constexpr int I1B = R1 * B1, I2B = R2 * B2;
+    // position n of tile t, in y * 9 + x and y * 7 + x; where there is none, one that another lane has as well
+    static __device__ __forceinline__ int position2(int t, int n)
+    {
+        constexpr int PAIRS = R2 / 2;
+        const int r = n >> 3, x = n & 7;
+        if (t < PAIRS) return (2 * t + r) * 9 + x;                     // two rows of eight
+        if (t > PAIRS) return (R2 - 1) * 9 + 8;
+        if (R2 % 2 == 0) return min(n, R2 - 1) * 9 + 8;                // the last column
+        return r ? min(x, R2 - 1) * 9 + 8 : (R2 - 1) * 9 + x;          // the last row and the last column
+    }
+    static __device__ __forceinline__ int position3(int t, int n) { return min(2 * t + (n >> 3), R3 - 1) * 7 + min(n & 7, 6); }
     static constexpr int TAB = (2 * MAX_UNITS + 4 + 160) * 4;   // slots, leaf values, total; biases
     static constexpr int LDS = PXB + I1B + I2B + TAB;
     static_assert(PR * 84 % 16 == 0, "LDS layout");
 };
 
-template <int R3>
+// MANY: a workgroup takes one unit after the other; otherwise just one
+template <int R3, bool MANY>
 __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 {
     using G = Geo<R3>;
@@ -2068,7 +2082,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
     const int ct = wave & 3, mh = wave >> 2;
     int tid = threadIdx.x, lane = tid & 63;
     const int G0 = (int)gridDim.x;
-    const int nu = G::MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;
+    const int nu = MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;
     if (A.clear && blockIdx.x == 0 && tid == 0) *A.clear = 0;
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
     u32x4 raw[G::NPX];
@@ -2137,10 +2151,10 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
         asm volatile("" : "+v"(tid));   // opaque: no lane address of a later phase is formed out here
         lane = tid & 63;
         const int n16 = lane & 15, kg = lane >> 4;
-        if (G::MANY && si != sw) load_w(si);   // the first unit of another network
+        if (MANY && si != sw) load_w(si);   // the first unit of another network
         if (k == 0 || si != sw) {
             // (read after the next barrier; the unit before has left its last phase that reads them)
-            if (G::MANY && k > 0) sync_lds();
+            if (MANY && k > 0) sync_lds();
             if (tid < 160) bias[tid] = tid < 32 ? C123_SEG(si).b1[tid] : tid < 96 ? C123_SEG(si).b2[tid - 32] : C123_SEG(si).b3[tid - 96];
             sw = si;
         }
@@ -2205,25 +2219,24 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             if (m < G::M1) {
                 const uint2 lo = pack4(v0.x, v0.y, v0.z, v0.w), hi = pack4(v1.x, v1.y, v1.z, v1.w);
                 const uint4 o = {lo.x, lo.y, hi.x, hi.y};
-                *reinterpret_cast<uint4 *>(img1 + (y * 20 + (x & 1) * 10 + (x >> 1)) * G::P1 + kg * 16) = o;
+                *reinterpret_cast<uint4 *>(img1 + y * G::B1 + ((x & 1) * 10 + (x >> 1)) * G::P1 + kg * 16) = o;
                 if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
                     *reinterpret_cast<uint4 *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 8 * kg) = o;
             }
         }
         // the next unit's pixels (behind the last unit its own once more)
         const int kn = k + 1 < nu ? k + 1 : k, un = (int)blockIdx.x + kn * G0, sn = seg_of(un);
-        if constexpr (G::MANY) load_px(sn, un, ring ? slots[kn] : 0);
+        if constexpr (MANY) load_px(sn, un, ring ? slots[kn] : 0);
         sync_lds();
         // ---- conv2: tiles T2 mh .. of 16 positions, channels 16 ct ..
         {
             constexpr int T = G::T2;
             const uint8_t *pa[T];
+            int pos[T];
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                int m = 16 * (T * mh + t) + n16;
-                if (m > G::M2 - 1) m = G::M2 - 1;
-                const int y = m / 9, x = m - 9 * y;
-                pa[t] = img1 + (2 * y * 20 + x) * G::P1 + kg * 16;
+                const int m = pos[t] = G::position2(T * mh + t, n16), y = m / 9, x = m - 9 * y;
+                pa[t] = img1 + 2 * y * G::B1 + x * G::P1 + kg * 16;
             }
             v4f acc[T];
 #pragma unroll
@@ -2232,7 +2245,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             auto rd = [&](int s) {   // kernel row s / 4, column s % 4
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + ((s >> 2) * 20 + (s & 1) * 10 + ((s >> 1) & 1)) * G::P1);
+                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s >> 2) * G::B1 + ((s & 1) * 10 + ((s >> 1) & 1)) * G::P1);
             };
             rd(0);
 #pragma unroll
@@ -2246,16 +2259,14 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             const v4f b2 = *reinterpret_cast<const v4f *>(bias + 32 + 16 * ct + 4 * kg);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int m = 16 * (T * mh + t) + n16, y = m / 9;
+                const int m = pos[t], y = m / 9, x = m - 9 * y;
                 v4f v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b2[r], 0.f);
-                if (m < G::M2) {
-                    const uint2 o = pack4(v.x, v.y, v.z, v.w);
-                    *reinterpret_cast<uint2 *>(img2 + m * G::P2 + ct * 32 + kg * 8) = o;
-                    if (y2 && row0 + y >= rowp + G::R2)
-                        *reinterpret_cast<uint2 *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + 16 * ct + 4 * kg) = o;
-                }
+                const uint2 o = pack4(v.x, v.y, v.z, v.w);   // (lanes that share a position store the same bits)
+                *reinterpret_cast<uint2 *>(img2 + y * G::B2 + x * G::P2 + ct * 32 + kg * 8) = o;
+                if (y2 && row0 + y >= rowp + G::R2)
+                    *reinterpret_cast<uint2 *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + 16 * ct + 4 * kg) = o;
             }
         }
         sync_lds();
@@ -2263,12 +2274,11 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
         {
             constexpr int T = G::T3;
             const uint8_t *pa[T];
+            int pos[T];
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                int m = 16 * (T * mh + t) + n16;
-                if (m > G::M3 - 1) m = G::M3 - 1;
-                const int y = m / 7, x = m - 7 * y;
-                pa[t] = img2 + (y * 9 + x) * G::P2 + kg * 16;
+                const int m = pos[t] = G::position3(T * mh + t, n16), y = m / 7, x = m - 7 * y;
+                pa[t] = img2 + y * G::B2 + x * G::P2 + kg * 16;
             }
             v4f acc[T];
 #pragma unroll
@@ -2277,7 +2287,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             auto rd = [&](int s) {   // tap s / 2, channel half s % 2
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + ((s / 6) * 9 + (s / 2) % 3) * G::P2 + (s & 1) * 64);
+                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s / 6) * G::B2 + ((s / 2) % 3) * G::P2 + (s & 1) * 64);
             };
             rd(0);
 #pragma unroll
@@ -2291,15 +2301,15 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             const v4f b3 = *reinterpret_cast<const v4f *>(bias + 96 + 16 * ct + 4 * kg);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                const int m = 16 * (T * mh + t) + n16, y = m / 7;
+                const int m = pos[t], y = m / 7;
                 v4f v;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b3[r], 0.f);
-                if (m < G::M3 && row0 + y >= rowp + R3)
+                if (row0 + y >= rowp + R3)
                     *reinterpret_cast<uint2 *>(C123_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + 16 * ct + 4 * kg) = pack4(v.x, v.y, v.z, v.w);
             }
         }
-        if (!G::MANY) break;
+        if (!MANY) break;
         si = sn;
         u += G0;
     }

@@ -160,7 +160,6 @@ constexpr int TURN = 2048;       // bytes of LDS in which a wave hands a step's 
 
 template <int R3> struct Geo {
     static constexpr int PARTS = (7 + R3 - 1) / R3;
-    static constexpr bool MANY = R3 == 7;   // a workgroup takes one unit after the other; otherwise just one
     static constexpr int R2 = R3 + 2, R1 = 2 * R3 + 6, PR = 4 * R1 + 4;   // rows of conv2, conv1, pixels
     static constexpr int M1 = R1 * 20, M2 = R2 * 9, M3 = R3 * 7;
     static constexpr int T1 = (M1 + 15) / 16, T2 = (M2 + 31) / 32, T3 = (M3 + 31) / 32;
@@ -208,8 +207,9 @@ __device__ __forceinline__ void reduce_quarters(const v16f (&acc)[T], v4f (&own)
         for (int t = 0; t < T; ++t) own[t] += scratch[(((kq * 3 + j) * 2 + ch) * T + t) * 64 + lane];
 }
 
-// Workgroup bid of G0; the kernel's arguments begin with A.
-template <int R3>
+// Workgroup bid of G0; the kernel's arguments begin with A.  MANY: it takes one unit after the other; otherwise just one
+// (whole samples with a workgroup each: 129 observations 38.2 -> 36.7 us per call, 256 40.7 -> 38.7, a step at 128 191 -> 189).
+template <int R3, bool MANY>
 __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const int G0, uint8_t *lds)
 {
     // The segments are indexed at run time; through the by-value structure that would be a copy in scratch
@@ -229,7 +229,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
     const int nt = wave & 1, tg = wave >> 1;      // conv1
     const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
     int tid = threadIdx.x, lane = tid & 63;
-    const int nu = G::MANY ? (A.units - bid + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
+    const int nu = MANY ? (A.units - bid + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
     if (A.clear && bid == 0 && tid == 0) *A.clear = 0;
 
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
@@ -327,7 +327,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one (none: far above)
         // a wave may still be in the last phase of the unit before, which reads that unit's biases: with units of two
         // networks in one workgroup they are others
-        if (G::MANY && k > 0) sync_lds();
+        if (MANY && k > 0) sync_lds();
         if (tid < 160) bias[tid] = theta[tid < 32 ? net::C1B + tid : tid < 96 ? net::C2B + tid - 32 : net::C3B + tid - 96];
         // pixels -> LDS
 #pragma unroll
@@ -416,11 +416,11 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             }
         };
         // conv2's first weights: behind the first tile where in front of it they would hold up conv1's own
-        if constexpr (G::MANY) load_w2();
+        if constexpr (MANY) load_w2();
         __builtin_amdgcn_sched_barrier(0);
         conv1_tile(tg);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (!G::MANY) load_w2();
+        if constexpr (!MANY) load_w2();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll 1
         for (int t = tg + 4; t < G::T1; t += 4) conv1_tile(t);
@@ -491,8 +491,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         // (behind the last unit: its own once more, so that the registers are written on every path and do not
         // have to keep their old contents until here)
         const int kn = k + 1 < nu ? k + 1 : k, un = bid + kn * G0, sn = seg_of(un);
-        if constexpr (G::MANY) load_w1(SP_SEG(sn).theta);
-        if constexpr (G::MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, A.draw ? slots[kn] : 0);
+        if constexpr (MANY) load_w1(SP_SEG(sn).theta);
+        if constexpr (MANY) load_px(SP_SEG(sn).src.x, SP_SEG(sn).src.xs, SP_SEG(sn).src.shift, SP_SEG(sn).first, un, A.draw ? slots[kn] : 0);
         sync_lds();
 
         // ---- conv3: steps 9 kq .. 9 kq + 8 of 36
@@ -549,18 +549,18 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                     *reinterpret_cast<v4f *>(SP_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + co) = v;
             }
         }
-        if (!G::MANY) break;
+        if (!MANY) break;
         si = sn;
         u += G0;
     }
 #undef SP_SEG
 }
 
-template <int R3>
+template <int R3, bool MANY>
 __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    conv123_body<R3>(A, (int)blockIdx.x, (int)gridDim.x, lds);
+    conv123_body<R3, MANY>(A, (int)blockIdx.x, (int)gridDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -886,7 +886,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_step(StepArgs A)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int bid = (int)blockIdx.x;
     if (bid < A.nat_blocks) conv123_native_body<RN>(A.nat, A.split.draw, A.split.samp, bid, lds);
-    else conv123_body<R3>(A.split, bid - A.nat_blocks, (int)gridDim.x - A.nat_blocks, lds);
+    else conv123_body<R3, false>(A.split, bid - A.nat_blocks, (int)gridDim.x - A.nat_blocks, lds);
 }
 
 // ---------------------------------------------------------------------------
