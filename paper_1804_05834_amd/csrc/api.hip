@@ -14,6 +14,7 @@
 #include "../../include/dqn.h"
 #include "gemm_bf16.h"
 #include "gemm_fp32.h"
+#include "gemm_rows.h"
 #include "gemm_split.h"
 #include "kernels_misc.h"
 #include "net.h"
@@ -162,6 +163,7 @@ struct dqn_ctx {
     // bf16: conv1 + conv2 forward run as one launch (gbf::c12) from this many samples per launch on;
     // INT_MAX: never (the launch needs 140 KB of LDS per workgroup, granted at initialisation)
     int conv12_min = INT32_MAX;
+    bool rows_fit = false;   // fp32: the conv layers of many rows with a layer's weights in LDS (rows)
     bool conv123 = false;   // bf16: conv1 to conv3 as one launch for few samples (gbf::c123)
     float *gp4 = nullptr, *gp5 = nullptr;   // where fc1's and the head's weight gradients are written: inside `grads`
     bool fused_bwd = false;   // conv2's input gradient and conv1's weight gradient in one workgroup per sample
@@ -460,6 +462,19 @@ bool in_kernel_draw_fits(const dqn_ctx *c, int B)
     return fused123(c, 3l * B, 3) || fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
 
+// A tiled launch's segments for the launch by rows: the same share of the workgroups each (their rows are the same number)
+rows::Args by_rows(const g32::FwdArgs &A, int num_cu)
+{
+    rows::Args R{};
+    R.nseg = A.nseg;
+    for (int i = 0; i < 3; ++i) {
+        const int j = i < A.nseg ? i : 0, begin = num_cu * j / A.nseg;
+        const g32::FwdSeg &S = A.seg[j];
+        R.seg[i] = rows::Seg{(const float *)S.x, S.w, S.bias, S.y, S.M, begin, num_cu * (j + 1) / A.nseg - begin, (uint32_t)S.xs};
+    }
+    return R;
+}
+
 // few_rows: acting on few observations; the conv launch clears their counter, and fc1 is left to the launch behind it
 int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *nsplit_out,
                           long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw, bool few_rows)
@@ -553,6 +568,7 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         // (few rows: the reduction slab of every stage is sliced over extra waves, KS > 1, which shortens the
         // dependent chain of stages per tile)
         const bool small = rows * 81 < 64 * 512;
+        const bool by_row = c->rows_fit && c->num_cu >= p0;   // a segment has a workgroup at least
         const int BM = small ? 32 : 64;
         FwdArgs A2{}, A3{};
         const int t2 = build(A2, p0, BM, 81, [&](int i) { return (const void *)(act1 + row0[i] * net::A1); }, net::A1, net::C2W,
@@ -562,9 +578,15 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         A2.klen = GConv2::K;
         A3.klen = GConv3::K;
         if (small) launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 32, 32, 4><<<dim3(t2, 2, 1), 256, 0, st>>>(A2); });
-        else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3(t2, 1, 1), 256, 0, st>>>(A2); });
+        else if (by_row) {
+            const rows::Args R = by_rows(A2, c->num_cu);
+            launch(c, "conv2_fwd", st, [&] { rows::k_fwd<GConv2><<<c->num_cu, rows::THREADS, rows::lds_bytes<GConv2>(), st>>>(R); });
+        } else launch(c, "conv2_fwd", st, [&] { k_fwd<GConv2, 64, 64><<<dim3(t2, 1, 1), 256, 0, st>>>(A2); });
         if (small) launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 32, 32, 3><<<dim3(t3, 2, 1), 192, 0, st>>>(A3); });
-        else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3(t3, 1, 1), 256, 0, st>>>(A3); });
+        else if (by_row) {
+            const rows::Args R = by_rows(A3, c->num_cu);
+            launch(c, "conv3_fwd", st, [&] { rows::k_fwd<GConv3><<<c->num_cu, rows::THREADS, rows::lds_bytes<GConv3>(), st>>>(R); });
+        } else launch(c, "conv3_fwd", st, [&] { k_fwd<GConv3, 64, 64><<<dim3(t3, 1, 1), 256, 0, st>>>(A3); });
     }
     if (few_rows) return hip_status(c, "forward");
     {  // fc1: raw partial sums per reduction split; the head kernels finish it
@@ -1283,6 +1305,7 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
                    granted(sp::k_conv123_fwd<7, false>, sp::Geo<7>::LDS) && granted(sp::k_conv123_fwd<7, true>, sp::Geo<7>::LDS) && granted(sp::k_conv123_step<1, 2>, sp::step_lds<1, 2>()) &&
                    granted(sp::k_conv123_step<4, 2>, sp::step_lds<4, 2>()) && granted(sp::k_conv123_step<4, 4>, sp::step_lds<4, 4>()) &&
                    granted(k_conv21_bwd_sp, CONV21_LDS);
+        c->rows_fit = granted(rows::k_fwd<g32::GConv2>, rows::lds_bytes<g32::GConv2>()) && granted(rows::k_fwd<g32::GConv3>, rows::lds_bytes<g32::GConv3>());
     } else {
         // DQN_CONV12_MIN_SAMPLES in the environment moves the number of samples (of all passes of a launch) from which
         // conv1 + conv2 are one launch, in the form without the three-layer launch; a huge value: never

@@ -362,6 +362,24 @@ def test_launches_with_no_more_lds_than_every_workgroup_gets(dq, orc, monkeypatc
     _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41, tol=tol, prec=prec)
 
 
+@pytest.mark.parametrize("B,cus", [(135, None), (136, 7), (211, 3), (449, None), (600, 31)])
+def test_conv_layers_of_many_rows_with_weights_in_lds(dq, monkeypatch, B, cus):
+    """fp32: the same bits as the tiled launches, which run where a workgroup gets no more LDS than every one does."""
+    print("case rows", B, cus, flush=True)
+    got = []
+    batch = tuple(dev(t) for t in synth.batch(17, B, 18))
+    if cus:
+        monkeypatch.setenv("DQN_COMPUTE_UNITS", str(cus))
+    for small in ("0", "1"):
+        monkeypatch.setenv("DQN_SMALL_LDS", small)
+        m = dq.Dqn(dq.make_config(max_batch=B, seed=7, **CONFIGS["dueling_ddqn"]))
+        out = m.train_step(B, batch)
+        got.append([out[k] for k in ("q_s", "q_next_online", "q_next_target", "td")] + [m.get_params(2)])
+        m.close()
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 def test_fc1_with_two_and_four_stages_in_lds(dq, monkeypatch):
     """bf16, 750 samples in each of three passes: the same sums whatever the number of stages, behind the same conv launches."""
     print("case fc1 stages", flush=True)
