@@ -13,6 +13,7 @@
 
 #include "../../include/dqn.h"
 #include "gemm_bf16.h"
+#include "gemm_fc1.h"
 #include "gemm_fp32.h"
 #include "gemm_rows.h"
 #include "gemm_split.h"
@@ -475,6 +476,22 @@ rows::Args by_rows(const g32::FwdArgs &A, int num_cu)
     return R;
 }
 
+// Blocks of 16 rows in a tile of fc1's forward launch: the least rows on the compute unit with most of them, and where that is
+// the same the lower tile (two of 48 rows side by side 76.7 us, one of 96 79.4; 4096 observations in 64 rows 408.5, in 128 410.2).
+// Over batches of 65 to 1000 and 193 to 8192 observations no other height was more than 1 % faster, the worst up to 14 % slower.
+int fc1_blocks(const Pass *pass, int npass, int ns, int num_cu)
+{
+    int best = 0;
+    long least = 0;
+    for (int mb = fc1::MIN_MB; mb <= fc1::MAX_MB; ++mb) {
+        long tiles = 0;
+        for (int i = 0; i < npass; ++i) tiles += (pass[i].n + 16 * mb - 1) / (16 * mb);
+        const long r = (tiles * (net::HID / fc1::BN) * ns + num_cu - 1) / num_cu * mb;
+        if (!best || r < least) { best = mb; least = r; }
+    }
+    return best;
+}
+
 // few_rows: acting on few observations; the conv launch clears their counter, and fc1 is left to the launch behind it
 int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int npass, int *nsplit_out,
                           long *split_stride_out, hipStream_t st, const misc::SampleArgs *draw, bool few_rows)
@@ -593,13 +610,34 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
         FwdArgs A{};
         const int ns = fc1_splits(rows);
         const bool few = rows <= 192;
-        int tiles = build(A, npass, few ? 32 : 64, 1, [&](int i) { return (const void *)(act3 + row0[i] * net::A3); }, net::A3, net::F1W,
-                          net::F1B, w.f1part, net::HID, false);
+        // (passes that follow one another with the same parameters are one range of rows)
+        Pass range[3];
+        int nr = 0;
+        for (int i = 0; i < npass; ++i) {
+            if (nr && range[nr - 1].net == pass[i].net) range[nr - 1].n += pass[i].n;
+            else range[nr++] = pass[i];
+        }
+        const int mb = few ? 0 : fc1_blocks(range, nr, ns, c->num_cu);
+        int tiles = 0;
+        A.nseg = nr;
+        for (int i = 0, r0 = 0; i < nr; r0 += range[i++].n) {
+            A.seg[i] = FwdSeg{act3 + (long)r0 * net::A3, theta_of(c, range[i].net) + net::F1W, nullptr, w.f1part + (long)r0 * net::HID, range[i].n, tiles, net::A3};
+            tiles += (range[i].n + (few ? 32 : 16 * mb) - 1) / (few ? 32 : 16 * mb);
+        }
         A.klen = GFc1::K / ns; A.split_stride = rows * net::HID; A.scale = 1.0f;
-        // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well.  Many: 64 x 64
-        // (against 32 x 64, two waves: 36.7 / 57.6 us at 768 rows, 71 / 113 at 2048, 118 / 123 at 3000, 15.7 / 21.5 at 200)
-        if (few) launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); });
-        else launch(c, "fc1_fwd", st, [&] { k_fwd<GFc1, 64, 64><<<dim3(tiles, 8, ns), 256, 0, st>>>(A); });
+        // few rows: the reduction of a split is sliced over seven wave groups of the workgroup as well
+        launch(c, "fc1_fwd", st, [&] {
+            const dim3 grid(tiles, 8, ns);
+            switch (mb) {
+            case 0: k_fwd<GFc1, 32, 32, 7><<<dim3(tiles, 16, ns), 448, 0, st>>>(A); break;
+            case 3: fc1::k_fwd<3><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            case 4: fc1::k_fwd<4><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            case 5: fc1::k_fwd<5><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            case 6: fc1::k_fwd<6><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            case 7: fc1::k_fwd<7><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            default: fc1::k_fwd<8><<<grid, fc1::THREADS, 0, st>>>(A); break;
+            }
+        });
         *nsplit_out = ns;
         *split_stride_out = rows * net::HID;
     }

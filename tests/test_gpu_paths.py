@@ -380,6 +380,32 @@ def test_conv_layers_of_many_rows_with_weights_in_lds(dq, monkeypatch, B, cus):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("B", [131, 170, 171, 347, 513, 700])
+def test_fc1_in_tiles_of_any_height(dq, monkeypatch, B):
+    """fp32, 7, 2 and 1 splits: the number of compute units moves the tiles' height (48 to 128 rows), never a bit; and the
+    hidden layer lies within the error of a sum of 3136 products, K 2^-24 sum |x w|, of float64."""
+    print("case fc1 tiles", B, flush=True)
+    batch = tuple(dev(t) for t in synth.batch(23, B, 18))
+    first = None
+    for cus in (256, 230, 200, 160, 130, 100, 80, 60):
+        monkeypatch.setenv("DQN_COMPUTE_UNITS", str(cus))
+        m = dq.Dqn(dq.make_config(max_batch=B, seed=7, **CONFIGS["dueling_ddqn"]))
+        p = m.get_params(0).cpu().double()
+        out = m.train_step(B, batch)
+        got = [m.get_activations(4, B)] + [out[k] for k in ("q_s", "q_next_online", "q_next_target")]
+        x = m.get_activations(3, B)
+        m.close()
+        if first is None:
+            first = got
+            o = 32 * 256 + 32 + 64 * 512 + 64 + 64 * 576 + 64
+            w, b = p[o:o + 512 * 3136].view(512, 3136), p[o + 512 * 3136:o + 512 * 3136 + 512]
+            x = x.cpu().double().view(B, 3136)
+            err = (got[0].cpu().double() - (x @ w.T + b).clamp(min=0)).abs()
+            assert (err <= 3136 * 2.0 ** -24 * (x.abs() @ w.abs().T + b.abs())).all()
+        for a, c in zip(first, got):
+            assert torch.equal(a, c)
+
+
 def test_fc1_with_two_and_four_stages_in_lds(dq, monkeypatch):
     """bf16, 750 samples in each of three passes: the same sums whatever the number of stages, behind the same conv launches."""
     print("case fc1 stages", flush=True)
