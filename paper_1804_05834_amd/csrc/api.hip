@@ -1057,8 +1057,9 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 k_layer_bwd_f32<DConv2, 128, 32, 1, GConv2, 256, false, 3, 4><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G2, P, HW, U);
             });
         }
-        if (B <= 64) launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 128><<<dim3(2, 1, *ns1), 256, 0, st>>>(G1); });
-        else launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 256><<<dim3(1, 1, *ns1), 512, 0, st>>>(G1); });
+        if (B <= 64) launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 128, false><<<dim3(2, 1, *ns1), 256, 0, st>>>(G1); });
+        else if (B <= 100) launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 256, false><<<dim3(1, 1, *ns1), 512, 0, st>>>(G1); });
+        else launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 256, true><<<dim3(1, 1, *ns1), 512, 0, st>>>(G1); });
         return;
     }
     {
@@ -1081,12 +1082,12 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
     }
     // large batch on three streams: the input-gradient chain and conv1's weight gradient on st, the other
     // weight gradients on sd behind the events of their input gradients
-    launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 256><<<dim3(1, 1, *ns1), 512, 0, st>>>(G1); });
-    launch(c, "fc1_wgrad", sd, [&] { k_wgrad<GFc1, 64, 64><<<dim3(49, 8, 1), 256, 0, sd>>>(G4); });
+    launch(c, "conv1_wgrad", st, [&] { k_wgrad<GConv1, 32, 256, true><<<dim3(1, 1, *ns1), 512, 0, st>>>(G1); });
+    launch(c, "fc1_wgrad", sd, [&] { k_wgrad<GFc1, 64, 64, true><<<dim3(49, 8, 1), 256, 0, sd>>>(G4); });
     ev_wait(sd, c->ev_a, st);
-    launch(c, "conv3_wgrad", sd, [&] { k_wgrad<GConv3, 64, 64><<<dim3(9, 1, *ns3), 256, 0, sd>>>(G3); });
+    launch(c, "conv3_wgrad", sd, [&] { k_wgrad<GConv3, 64, 64, true><<<dim3(9, 1, *ns3), 256, 0, sd>>>(G3); });
     ev_wait(sd, c->ev_b, st);
-    launch(c, "conv2_wgrad", sd, [&] { k_wgrad<GConv2, 64, 64><<<dim3(8, 1, *ns2), 256, 0, sd>>>(G2); });
+    launch(c, "conv2_wgrad", sd, [&] { k_wgrad<GConv2, 64, 64, true><<<dim3(8, 1, *ns2), 256, 0, sd>>>(G2); });
 }
 
 // fc1's backward pair (see gbf::k_bwd_pair) with the head's weight gradient as a third group of

@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "net.h"
 
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -83,9 +85,9 @@ struct GConv1 {  // 8x8 stride 4, uint8 CHW input, k = (c, p, q)
     static constexpr int K = 256, N = 32, P = 400;
     static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        const uint32_t n = m / 400, r = m % 400, i = r / 20, j = r % 20;
-        return n * xs + (i * 4) * 84 + j * 4;
+        return m / 400 * xs + pos_off(m % 400);
     }
+    static __device__ __forceinline__ uint32_t pos_off(uint32_t r) { return __umul24(__umul24(r, 205) >> 12, 4 * 84 - 20 * 4) + r * 4; }   // r / 20, r < 400
     static __device__ __forceinline__ int k_off(int k) { return (k >> 6) * 7056 + ((k >> 3) & 7) * 84 + (k & 7); }
 };
 struct GConv2 {  // 4x4 stride 2 over 20x20x32, k = (p, q, c)
@@ -93,9 +95,9 @@ struct GConv2 {  // 4x4 stride 2 over 20x20x32, k = (p, q, c)
     static constexpr int K = 512, N = 64, P = 81;
     static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        const uint32_t n = m / 81, r = m % 81, i = r / 9, j = r % 9;
-        return n * xs + ((i * 2) * 20 + j * 2) * 32;
+        return m / 81 * xs + pos_off(m % 81);
     }
+    static __device__ __forceinline__ uint32_t pos_off(uint32_t r) { return __umul24(__umul24(r, 57) >> 9, (2 * 20 - 9 * 2) * 32) + r * 64; }   // r / 9, r < 81
     static __device__ __forceinline__ int k_off(int k) { return (k >> 7) * 640 + (k & 127); }
 };
 struct GConv3 {  // 3x3 stride 1 over 9x9x64, k = (p, q, c)
@@ -103,15 +105,16 @@ struct GConv3 {  // 3x3 stride 1 over 9x9x64, k = (p, q, c)
     static constexpr int K = 576, N = 64, P = 49;
     static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs)
     {
-        const uint32_t n = m / 49, r = m % 49, i = r / 7, j = r % 7;
-        return n * xs + (i * 9 + j) * 64;
+        return m / 49 * xs + pos_off(m % 49);
     }
+    static __device__ __forceinline__ uint32_t pos_off(uint32_t r) { return __umul24(__umul24(r, 37) >> 8, (9 - 7) * 64) + r * 64; }   // r / 7, r < 49
     static __device__ __forceinline__ int k_off(int k) { return (k / 192) * 576 + (k % 192); }
 };
 struct GFc1 {  // dense 3136 -> 512 on the flattened conv3 output
     using in_t = float;
     static constexpr int K = 3136, N = 512, P = 1;
     static __device__ __forceinline__ uint32_t row_off(uint32_t m, uint32_t xs) { return m * xs; }
+    static __device__ __forceinline__ uint32_t pos_off(uint32_t) { return 0; }
     static __device__ __forceinline__ int k_off(int k) { return k; }
 };
 
@@ -622,6 +625,171 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int bx, int by, i
     if (do_bias && h == 0) part[(long)G::N * G::K + o0 + wo * 32 + li] = bsum;
 }
 
+// The same tile for launches of their own with many stages per tile.  wgrad_tile's waves wait where a stage's operands are read
+// in front of its matrix instructions, and a sixth of a SIMD's time are vector instructions, beside which it runs no fp32 matrix
+// instructions: mostly the divisions in the rows' addresses, which are carried along here.  At a batch of 1000, alone, conv1's
+// 87 -> 73 us, conv2's 74 -> 56, conv3's 52 -> 41, fc1's 52 -> 42, the step 898 -> 884; conv1's at 256 23.7 -> 22.0, at 100 equal, at 65
+// 9.9 -> 10.2.  In the small-batch launches beside an input gradient its longer code and the registers cost 1 to 3 us per launch.
+template <class G, int BMO, int BNK>
+__device__ __forceinline__ void wgrad_deep(const WgradArgs &A, int bx, int by, int bz, float *lds)
+{
+    constexpr int T = (BMO / 32) * (BNK / 32) * 64;
+    constexpr int LDY = BMO + 4, LDX = BNK + 4;
+    constexpr int YR = T / (BMO / 4), XR = T / (BNK / 4);  // tile rows filled per pass
+    constexpr int NY = (BK + YR - 1) / YR, NX = (BK + XR - 1) / XR;
+    using in_t = typename G::in_t;
+    if ((int)threadIdx.x >= T) return;   // a wider workgroup: the waves beyond the tile's leave at once
+    constexpr int STAGE = BK * (LDY + LDX);   // floats of a buffer
+    float *Ys = lds, *Xs = lds + BK * LDY;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kc0 = bx * BNK, o0 = by * BMO;
+    const int mbeg = bz * A.rps;
+    const int mend = min(mbeg + A.rps, A.B * G::P);
+    const in_t *x = static_cast<const in_t *>(A.x);
+
+    const int yr = tid / (BMO / 4), yc = (tid % (BMO / 4)) * 4;
+    const int xr = tid / (BNK / 4), xc = (tid % (BNK / 4)) * 4;
+    using raw_t = decltype(ld4raw(x));
+    // where this thread's pieces of the next stage to be requested lie (further rows lie at higher offsets); a stage is 32 rows,
+    // at most one sample further
+    const uint32_t ymax = (uint32_t)(mend - 1) * G::N + o0 + yc, xlast = G::row_off(mend - 1, (uint32_t)A.xs) + G::k_off(kc0 + xc);
+    uint32_t yo[NY], xs0[NX];
+    int xp[NX];
+#pragma unroll
+    for (int i = 0; i < NY; ++i) yo[i] = (uint32_t)(mbeg + yr + i * YR) * G::N + o0 + yc;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int m = mbeg + xr + i * XR;
+        xp[i] = m % G::P;
+        xs0[i] = m / G::P * (uint32_t)A.xs + G::k_off(kc0 + xc);
+    }
+    const int n = mbeg < mend ? (mend - mbeg + BK - 1) / BK : 0;
+    struct Regs { v4f y[NY]; raw_t x[NX]; } R[2];
+    auto request = [&](Regs &q, int j) {   // piece j; rows past the end: the last one
+        if (j < NY) {
+            q.y[j < NY ? j : 0] = ld4(A.dy + min(yo[j < NY ? j : 0], ymax));
+            yo[j < NY ? j : 0] += BK * G::N;
+        } else {
+            const int i = j - NY;
+            q.x[i] = ld4raw(x + min(xs0[i] + G::pos_off(xp[i]), xlast));
+            if constexpr (G::P == 1) xs0[i] += BK * (uint32_t)A.xs;
+            else {
+                const bool over = (xp[i] += BK) >= G::P;
+                xp[i] -= over ? G::P : 0;
+                xs0[i] += over ? (uint32_t)A.xs : 0u;
+            }
+        }
+    };
+    // (rows past the end: dY as zeros is enough)
+    auto put = [&](const Regs &q, int at, int left, int j) {
+        if (j < NY) {
+            const int r = yr + j * YR;
+            v4f v = q.y[j < NY ? j : 0];
+            if (left < BK) v = r < left ? v : v4f{0, 0, 0, 0};
+            if (YR * NY == BK || r < BK) *reinterpret_cast<v4f *>(&Ys[at + r * LDY + yc]) = v;
+        } else {
+            const int r = xr + (j - NY) * XR;
+            if (XR * NX == BK || r < BK) *reinterpret_cast<v4f *>(&Xs[at + r * LDX + xc]) = cvt4(q.x[j - NY]);
+        }
+    };
+
+    const int wo = wave % (BMO / 32), wk = wave / (BMO / 32);
+    const int li = lane & 31, h = lane >> 5;
+    const float *yp = &Ys[(4 * h) * LDY + wo * 32 + li];
+    const float *xp0 = &Xs[(4 * h) * LDX + wk * 32 + li];
+    const bool do_bias = bx == 0 && wk == 0;
+    v16f acc = {0};
+    const float *yb = &Ys[wo * 32 + li];   // the bias gradient: see wgrad_tile
+    float bsum = 0.f;
+
+    // Two buffers, one barrier per stage.  A stage is requested three stages ahead and lies in registers until its buffer is
+    // free; the operands of sixteen rows are read ahead of their matrix instructions, and the barrier stands between the
+    // stage's halves, so that those behind it are read beside the second.  A load or LDS access in front of a matrix
+    // instruction of the same wave holds it up, so they stand one or two at a time behind the matrix instructions.
+    struct Ops { float a[8], b[8]; } O[2];
+    auto get = [&](Ops &o, int at, int half, int j) {   // row 8 (j / 4) + j % 4 of the half, and the one four further
+        const int k = 16 * half + 8 * (j / 4) + j % 4;
+        o.a[j] = yp[at + k * LDY];
+        o.b[j] = xp0[at + k * LDX];
+    };
+    constexpr int NP = NY + NX;
+    auto multiply = [&](const Ops &o, auto item) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            acc = mfma(o.a[j], o.b[j], acc);
+            item(j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // stage s, in the buffer `at`; q: stage s + 1, then on its way s + 3
+    // (inner: neither the last stages nor what they need)
+    auto stage = [&](auto inner, int s, int at, Regs &q) {
+        constexpr bool I = decltype(inner)::value;
+        const int left = mend - mbeg - (s + 1) * BK;
+        multiply(O[0], [&](int j) {
+            get(O[1], at, 1, j);
+            if (I || s + 1 < n) {
+#pragma unroll
+                for (int i = 0; i < NP; ++i)
+                    if (i * 4 / NP == j) put(q, STAGE - at, I ? BK : left, i);
+            }
+            if (I || s + 3 < n) {
+#pragma unroll
+                for (int i = 0; i < NP; ++i)
+                    if (4 + i * 4 / NP == j) request(q, i);
+            }
+        });
+        if (do_bias) {   // uniform for the wave
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += 8)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    bsum += yb[at + (kk + t) * LDY];
+                    bsum += yb[at + (kk + 4 + t) * LDY];
+                }
+        }
+        sync_lds();
+        if (I || s + 1 < n) multiply(O[1], [&](int j) { get(O[0], STAGE - at, 0, j); });
+        else multiply(O[1], [](int) {});
+    };
+    if (n > 0) {
+        auto all = [&](auto item) {   // (in this order: ahead of the loop another one would make its waits longer)
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                item(i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        all([&](int i) { request(R[0], i); });
+        if (n > 1) all([&](int i) { request(R[1], i); });
+        all([&](int i) { put(R[0], 0, mend - mbeg, i); });
+        if (n > 2) all([&](int i) { request(R[0], i); });
+        sync_lds();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) get(O[0], 0, 0, j);
+        int s = 0;
+        for (; s + 5 <= n; s += 2) {
+            stage(std::true_type{}, s, 0, R[1]);
+            stage(std::true_type{}, s + 1, STAGE, R[0]);
+        }
+        for (; s < n; s += 2) {
+            stage(std::false_type{}, s, 0, R[1]);
+            if (s + 1 < n) stage(std::false_type{}, s + 1, STAGE, R[0]);
+        }
+    }
+
+    float *part = A.part + (long)bz * A.part_stride;
+    const int col = kc0 + wk * 32 + li;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        int o = o0 + wo * 32 + 8 * (r / 4) + 4 * h + (r % 4);
+        part[(long)o * G::K + col] = acc[r] * A.scale;
+    }
+    if (do_bias && h == 0) part[(long)G::N * G::K + o0 + wo * 32 + li] = bsum;
+}
+
 // tile number -> (bx, by, bz) of a grid (gx, gy, gz): with row splits (conv layers) all tiles of one
 // split together; without (fc1) all output tiles of one input-column tile together
 __device__ __forceinline__ void wgrad_tile_of(int t, int gx, int gy, int gz, int &bx, int &by, int &bz)
@@ -633,13 +801,15 @@ __device__ __forceinline__ void wgrad_tile_of(int t, int gx, int gy, int gz, int
     }
 }
 
-template <class G, int BMO, int BNK>
+// DEEP: with many stages per tile (wgrad_deep)
+template <class G, int BMO, int BNK, bool DEEP>
 __global__ __launch_bounds__((BMO / 32) * (BNK / 32) * 64) void k_wgrad(WgradArgs A)
 {
     __shared__ __attribute__((aligned(16))) float lds[wgrad_lds<BMO, BNK>()];
     int bx, by, bz;
     wgrad_tile_of(net::tile_of_workgroup(), gridDim.x, gridDim.y, gridDim.z, bx, by, bz);
-    wgrad_tile<G, BMO, BNK>(A, bx, by, bz, lds);
+    if constexpr (DEEP) wgrad_deep<G, BMO, BNK>(A, bx, by, bz, lds);
+    else wgrad_tile<G, BMO, BNK>(A, bx, by, bz, lds);
 }
 
 }  // namespace g32

@@ -406,6 +406,23 @@ def test_fc1_in_tiles_of_any_height(dq, monkeypatch, B):
             assert torch.equal(a, c)
 
 
+@pytest.mark.parametrize("B", [449, 463, 778, 1000])
+def test_backward_on_one_stream_and_on_three(dq, monkeypatch, B):
+    """fp32: the layers' own backward launches of the largest batches and the launches with both gradients of a layer, which one
+    stream takes at every batch, add in the same order: the same bits (the head's weight gradient is split another way)."""
+    print("case streams", B, flush=True)
+    batch = tuple(dev(t) for t in synth.batch(29, B, 18))
+    got = []
+    for single in ("0", "1"):
+        monkeypatch.setenv("DQN_SINGLE_STREAM", single)
+        m = dq.Dqn(dq.make_config(max_batch=B, seed=7, **CONFIGS["dueling_ddqn"]))
+        m.train_step(B, batch)
+        got.append([m.get_params(k)[:1684128] for k in (0, 2)])
+        m.close()
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 def test_fc1_with_two_and_four_stages_in_lds(dq, monkeypatch):
     """bf16, 750 samples in each of three passes: the same sums whatever the number of stages, behind the same conv launches."""
     print("case fc1 stages", flush=True)
