@@ -1078,7 +1078,12 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
         long M = (long)B * 100;
         // (slices as waves: beside the weight gradients of the other stream the wide tile of the one-stream schedule made the
         // step slower, 1074 against 1029 us at a batch of 1000)
-        launch(c, "conv2_dgrad", st, [&] { k_dgrad<DConv2, 64, 32, 4><<<dim3((M + 63) / 64, 1, 4), 512, 0, st>>>(D); });
+        const int tiles = (int)((M + DG2_BM - 1) / DG2_BM);
+        // In one round three workgroups per compute unit, in several two (by 8 KB of LDS more), which leaves room for one of the
+        // other streams' beside them: a step of 449 takes 446 us and 469 with two, of 491 473 and 494; of 512 515 and 503, of 700
+        // 666 and 646, of 1000 877 and 848
+        const int pad = tiles <= 3 * c->num_cu ? 0 : 8192;
+        launch(c, "conv2_dgrad", st, [&] { k_conv2_dgrad<<<tiles, 256, pad, st>>>(D); });
     }
     // large batch on three streams: the input-gradient chain and conv1's weight gradient on st, the other
     // weight gradients on sd behind the events of their input gradients
@@ -1838,9 +1843,9 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     // weight gradient and the priority update to another; they join again before the optimizer.
     // Their kernels are long enough (50-120 us) to repay the events; everything else stays on st
     // with one backward launch per layer.
-    // measured, one stream against three: 436 / 454 us per step at 384, 497 / 502 at 448, 527 / 531 at 480, 562 / 545 at 512,
-    // 672 / 650 at 640, 823 / 795 at 768, 993 / 961 at 1000
-    const bool multi = c->side && cfg.precision == 0 && B > 448;
+    // measured, one stream against three: 300 / 326 us per step at 256, 395 / 407 at 384, 404 / 414 at 400, 419 / 431 at 411, 438.6 / 431.8 at 420,
+    // 461 / 445 at 448
+    const bool multi = c->side && cfg.precision == 0 && B >= 420;
     hipStream_t sd = multi ? c->side : st;
     hipStream_t sp = multi ? (c->side2 ? c->side2 : c->side) : st;
     if (sd != st || sp != st) (void)hipEventRecord(c->ev_fork, st);

@@ -499,6 +499,131 @@ __global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_dgrad(Dgrad
     dgrad_tile<D, BM, BN, KS, KA>(A, net::tile_of_workgroup(), gridDim.x, gridDim.z, smem);
 }
 
+// conv2's input gradient for many rows: the four parity classes read the same dY (class (a, b) at pixel (2h' + a, 2w' + b) the
+// positions h' - u, w' - v), so a tile is 64 of the 10 x 10 grids' rows by all classes' 32 channels, a wave per class, and dY is
+// staged once for the four.
+// Bound by the fp32 matrix pipe and by the vector instructions beside which it stands still (less than half of dgrad_tile's per
+// product).  Two buffers and items behind matrix instructions as in wgrad_deep, the next stage but one in registers (one more
+// took 187 of them, two workgroups per compute unit).  The reduction is in the order of dgrad_tile's four slices, 32 each of two
+// taps, then the sums: the same bits.
+// At a batch of 1000, alone, 111 us in dgrad_tile's 64 x 32 with the slices as waves, now 76; the step 880 -> 850, at 600 579 -> 568,
+// at 449 465 -> 447.
+constexpr int DG2_BM = 64, DG2_LDB = 128 + 4, DG2_STAGE = DG2_BM * LDK + BK * DG2_LDB;
+__device__ const float dg2_zeros[64] = {};   // dY outside the image
+__global__ __launch_bounds__(256, 3) void k_conv2_dgrad(DgradArgs A)
+{
+    using D = DConv2;
+    typedef __attribute__((address_space(1))) const float *Global;   // (a choice between two arrays would become a flat pointer)
+    __shared__ __attribute__((aligned(16))) float smem[2 * DG2_STAGE];
+    float *As = smem, *Bs = smem + DG2_BM * LDK;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, h = lane >> 5;
+    const int m0 = net::tile_of_workgroup() * DG2_BM, M = A.B * D::PP;
+    // this thread's pieces of a stage: rows ar and ar + 32 of dY, 16 bytes of each; rows br, br + 8, .. of the weights, 16 bytes of a class
+    const int ar = tid >> 3, ap = (tid & 7) * 4, br = tid >> 5, bc = tid & 31;
+    const int bcls = bc >> 3;
+    int arow[2];
+    uint32_t taps[2];   // bit tap: inside the image
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = min(m0 + ar + 32 * i, M - 1), n = m / D::PP, r = m % D::PP, ph = r / D::WP, pw = r % D::WP;
+        taps[i] = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) taps[i] |= (uint32_t)((uint32_t)(ph - t / 2) < (uint32_t)D::OH && (uint32_t)(pw - t % 2) < (uint32_t)D::OW) << t;
+        arow[i] = ((n * D::OH + ph) * D::OW + pw) * D::CO + ap;
+    }
+    const float *wp = A.w + ((br * D::KH + bcls / 2) * D::KW + bcls % 2) * D::CI + (bc & 7) * 4;
+    struct Regs { v4f a[2], b[4]; } R;
+    // stage i of eight: 32 of slice i / 2, from tap i / 4 (i even) or 2 + i / 4 (i odd)
+    auto tap_of = [](int i) { return 2 * (i & 1) + i / 4; };
+    auto o_of = [](int i) { return 32 * (i / 2 % 2); };
+    constexpr int NP = 6;
+    auto request = [&](Regs &q, int i, int j) {
+        const int tap = tap_of(i), o = o_of(i), u = tap / 2, v = tap % 2;
+        if (j < 2) {
+            const Global p = (Global)A.dy + (arow[j & 1] - (u * D::OW + v) * D::CO + o), z = (Global)dg2_zeros + ap;
+            q.a[j & 1] = *reinterpret_cast<__attribute__((address_space(1))) const v4f *>(taps[j & 1] >> tap & 1 ? p : z);
+        } else q.b[(j - 2) & 3] = ld4(wp + ((o + 8 * (j - 2)) * D::KH * D::KW + 2 * u * D::KW + 2 * v) * D::CI);
+    };
+    auto put = [&](const Regs &q, int at, int j) {
+        if (j < 2) *reinterpret_cast<v4f *>(&As[at + (ar + 32 * j) * LDK + ap]) = q.a[j & 1];
+        else *reinterpret_cast<v4f *>(&Bs[at + (br + 8 * (j - 2)) * DG2_LDB + bc * 4]) = q.b[(j - 2) & 3];
+    };
+    // operands of half a stage: eight of the reduction twice
+    struct Ops { v4f a[2][2]; float b[8]; } O[2];
+    const float *ap0 = As + li * LDK + 4 * h, *bp0 = Bs + 4 * h * DG2_LDB + 32 * wave + li;
+    auto get = [&](Ops &o, int at, int half, int j) {   // j: 0-3 dY, 4-11 weights
+        if (j < 4) o.a[j >> 1 & 1][j & 1] = ld4(ap0 + at + 32 * (j >> 1) * LDK + 16 * half + 8 * (j & 1));
+        else o.b[(j - 4) & 7] = bp0[at + (16 * half + 8 * ((j - 4) >> 2) + (j & 3)) * DG2_LDB];
+    };
+    v16f acc[2], sum[2];
+    auto multiply = [&](const Ops &o, auto item) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                acc[r] = mfma(o.a[r][t >> 2][t & 3], o.b[t], acc[r]);
+                item(2 * t + r);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    auto all = [&](auto item) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            item(j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    all([&](int j) { request(R, 0, j); });
+    all([&](int j) { put(R, 0, j); });
+    all([&](int j) { request(R, 1, j); });
+    sync_lds();
+#pragma unroll
+    for (int j = 0; j < 12; ++j) get(O[0], 0, 0, j);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int at = i & 1 ? DG2_STAGE : 0;
+        if (i % 2 == 0) acc[0] = acc[1] = v16f{0};
+        multiply(O[0], [&](int k) {
+            if (k < 12) get(O[1], at, 1, k);
+            if (i + 1 < 8 && k < NP) put(R, DG2_STAGE - at, k);
+            if (i + 2 < 8 && k >= NP && k < 2 * NP) request(R, i + 2, k - NP);
+        });
+        if (i + 1 < 8) sync_lds();
+        multiply(O[1], [&](int k) {
+            if (i + 1 < 8 && k < 12) get(O[0], DG2_STAGE - at, 0, k);
+        });
+        if (i % 2 == 1)
+#pragma unroll
+            for (int r = 0; r < 2; ++r) sum[r] = i == 1 ? acc[r] : sum[r] + acc[r];
+    }
+    const int ca = wave >> 1, cb = wave & 1;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        int off[16];
+        float xm[16];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int mg = m0 + 32 * r + 8 * g + 4 * h;
+            int n = mg / D::PP, rr = mg % D::PP, ph = rr / D::WP, pw = rr % D::WP;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int o = ((n * D::H + 2 * ph + ca) * D::W + 2 * pw + cb) * D::CI + li;
+                const bool valid = mg + j < M;
+                off[4 * g + j] = valid ? o : -1;
+                xm[4 * g + j] = A.xact[valid ? o : 0];
+                if (++pw == D::WP) {
+                    pw = 0;
+                    if (++ph == D::HP) { ph = 0; ++n; }
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (off[k] >= 0) A.dx[off[k]] = xm[k] > 0.f ? sum[r][k] : 0.f;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Weight gradient: dW[o][k] = sum_m dY[m][o] * A(m,k), db[o] = sum_m dY[m][o].
 // The reduction runs over all output positions of all samples; it is cut into

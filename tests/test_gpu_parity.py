@@ -837,7 +837,7 @@ def test_replay_train_step_full_size_bf16(dq, orc):
 
 @pytest.mark.parametrize("B", [100, 320, 448, 480])
 def test_replay_train_step_fp32_schedules(dq, orc, B):
-    """fp32 replay step at batch sizes on both sides of the library's schedule switch: up to 448 the
+    """fp32 replay step at batch sizes on both sides of the library's schedule switch: up to 419 the
     step stays on one stream (one backward launch per layer; the priority update, one workgroup of
     256 threads, takes two entries per thread from 257 entries on), above it the weight gradients
     run on side streams.  Every output and the repaired tree are held against the oracle.  At these
