@@ -1070,7 +1070,11 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
     {
         DgradArgs D{d3, c->theta + net::C3W, act2, d2, B};
         long M = (long)B * 81;
-        launch(c, "conv3_dgrad", st, [&] { k_dgrad<DConv3, 64, 64><<<dim3((M + 63) / 64, 1, 1), 256, 0, st>>>(D); });
+        // up to three tiles per compute unit two workgroups at a time (by 20,000 bytes of LDS more, which leaves room for the other
+        // streams'), beyond that four: a step of 449 takes 440 us (449 with four), of 480 472 (484), of 600 569 (574); of 700 654 with two and 650, of
+        // 1000 858 and 843
+        const int tiles = (int)((M + 63) / 64), pad = tiles <= 3 * c->num_cu ? 20000 : 0;
+        launch(c, "conv3_dgrad", st, [&] { k_conv3_dgrad<<<tiles, 256, pad, st>>>(D); });
         ev_record(c->ev_b, st, sd);
     }
     {

@@ -624,6 +624,98 @@ __global__ __launch_bounds__(256, 3) void k_conv2_dgrad(DgradArgs A)
     }
 }
 
+// conv3's input gradient for many rows: dgrad_tile<DConv3, 64, 64>'s tile, sums and bits in the manner of k_conv2_dgrad, a tap
+// (two stages) per turn of the loop.  At a batch of 1000, alone, 69 -> 56 us; the step 852 -> 843, at 480 480 -> 472, at 930 807 -> 793
+// (650: 597 -> 603).
+constexpr int DG3_LDB = 64 + 4, DG3_STAGE = 64 * LDK + BK * DG3_LDB;
+__global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
+{
+    using D = DConv3;
+    typedef __attribute__((address_space(1))) const float *Global;
+    __shared__ __attribute__((aligned(16))) float smem[2 * DG3_STAGE];
+    float *As = smem, *Bs = smem + 64 * LDK;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, h = lane >> 5;
+    const int wm = wave & 1, wn = wave >> 1, m0 = net::tile_of_workgroup() * 64, M = A.B * D::PP;
+    // this thread's pieces of a stage: rows ar and ar + 32 of dY, 16 bytes of each; rows br and br + 16 of the weights, 16 bytes
+    const int ar = tid >> 3, ap = (tid & 7) * 4, br = tid >> 4, bc = (tid & 15) * 4;
+    int arow[2];
+    uint32_t taps[2];   // bit tap: inside the image
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = min(m0 + ar + 32 * i, M - 1), n = m / D::PP, r = m % D::PP, ph = r / D::WP, pw = r % D::WP;
+        taps[i] = 0;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) taps[i] |= (uint32_t)((uint32_t)(ph - t / 3) < (uint32_t)D::OH && (uint32_t)(pw - t % 3) < (uint32_t)D::OW) << t;
+        arow[i] = ((n * D::OH + ph) * D::OW + pw) * D::CO + ap;
+    }
+    const float *wp = A.w + br * 9 * D::CI + bc;
+    struct Regs { v4f a[2], b[2]; } R;
+    constexpr int NP = 4;
+    auto request = [&](int tap, int o, int j) {
+        if (j < 2) {
+            const Global p = (Global)A.dy + (arow[j & 1] + (o - (tap / 3 * D::OW + tap % 3) * D::CO)), z = (Global)dg2_zeros + ap;
+            R.a[j & 1] = *reinterpret_cast<__attribute__((address_space(1))) const v4f *>(taps[j & 1] >> tap & 1 ? p : z);
+        } else R.b[j & 1] = ld4(wp + ((o + 16 * (j & 1)) * 9 + tap) * D::CI);
+    };
+    auto put = [&](int at, int j) {
+        if (j < 2) *reinterpret_cast<v4f *>(&As[at + (ar + 32 * j) * LDK + ap]) = R.a[j & 1];
+        else *reinterpret_cast<v4f *>(&Bs[at + (br + 16 * (j & 1)) * DG3_LDB + bc]) = R.b[j & 1];
+    };
+    struct Ops { v4f a[2]; float b[8]; } O[2];   // of half a stage
+    const float *ap0 = As + (32 * wm + li) * LDK + 4 * h, *bp0 = Bs + 4 * h * DG3_LDB + 32 * wn + li;
+    auto get = [&](Ops &o, int at, int half, int j) {   // j: 0-7 weights, and with 0 and 4 dY
+        if (j % 4 == 0) o.a[j / 4] = ld4(ap0 + at + 16 * half + 2 * j);
+        o.b[j] = bp0[at + (16 * half + 8 * (j / 4) + j % 4) * DG3_LDB];
+    };
+    v16f acc = {0};
+    auto multiply = [&](const Ops &o, auto item) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            acc = mfma(o.a[t / 4][t % 4], o.b[t], acc);
+            item(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto stage = [&](int at, int tap, int o) {   // (tap, o): of the stage after the next
+        multiply(O[0], [&](int k) {
+            get(O[1], at, 1, k);
+            if (k < NP) put(DG3_STAGE - at, k);
+            else request(tap, o, k - NP);
+        });
+        sync_lds();
+        multiply(O[1], [&](int k) { get(O[0], DG3_STAGE - at, 0, k); });
+    };
+#pragma unroll
+    for (int j = 0; j < NP; ++j) request(0, 0, j);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) put(0, j);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) request(0, 32, j);
+    sync_lds();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) get(O[0], 0, 0, j);
+    for (int tap = 0; tap < 9; ++tap) {   // (behind the last tap: its own again, which nobody multiplies)
+        const int next = min(tap + 1, 8);
+        stage(0, next, 0);
+        stage(DG3_STAGE, next, 32);
+    }
+    int off[16];
+    float xm[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = m0 + 32 * wm + 8 * g + 4 * h + j;   // (a row of the result is a pixel of the input)
+            off[4 * g + j] = m < M ? m * D::CI + 32 * wn + li : -1;
+            xm[4 * g + j] = A.xact[m < M ? m * D::CI + 32 * wn + li : 0];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        if (off[k] >= 0) A.dx[off[k]] = xm[k] > 0.f ? acc[k] : 0.f;
+}
+
 // ---------------------------------------------------------------------------
 // Weight gradient: dW[o][k] = sum_m dY[m][o] * A(m,k), db[o] = sum_m dY[m][o].
 // The reduction runs over all output positions of all samples; it is cut into

@@ -406,7 +406,7 @@ def test_fc1_in_tiles_of_any_height(dq, monkeypatch, B):
             assert torch.equal(a, c)
 
 
-@pytest.mark.parametrize("B", [420, 463, 492, 778, 1000])
+@pytest.mark.parametrize("B", [420, 463, 492, 607, 778, 1000])
 def test_backward_on_one_stream_and_on_three(dq, monkeypatch, B):
     """fp32: the layers' own backward launches of the largest batches and the launches with both gradients of a layer, which one
     stream takes at every batch, add in the same order: the same bits (the head's weight gradient is split another way)."""
