@@ -411,9 +411,10 @@ Conv123Plan conv123_plan(int samples, int num_cu)
     return P;
 }
 // bf16: all three conv layers as one launch (gbf::c123), or conv1 + conv2 and conv3 (gbf::c12, gbf::ps)?
-// One unit per workgroup and a launch less: ahead while the samples of a training launch have a CU each (batch 77: 81.4
-// against 84.2 us per step, 32: 70.3 against 78.9, 128: 94.2 against 90.5), acting, which draws nothing, up to two
-// (512 observations: 34.8 against 38.6 us, 1024: 49.3 against 47.8, 1: 19.1 against 27.6).
+// One unit per workgroup and a launch less: ahead while the samples of a training launch have a CU each (batch 32: 57.5
+// against 68.7 us per step, 77: 62.5 against 73.2, 85: 62.7 against 73.4; at 86 to 170, several units per workgroup, equal), acting,
+// which draws nothing, up to two (one observation: 14.4 against 23.0 us, 256: 20.7 against 28.8, 512: 31.4 against 36.3; at 1024,
+// four units per workgroup, 1.5 us behind).
 bool fused123(const dqn_ctx *c, long samples, int npass) { return c->conv123 && samples <= (npass == 1 ? 2 : 1) * c->num_cu; }
 // bf16: conv1 + conv2 as one launch, one workgroup per CU, for passes of n[0..npass) samples?
 bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
@@ -447,6 +448,7 @@ bool step_launch(const dqn_ctx *c, int B) { return c->split && 2 * 3 * B <= c->n
 // with a draw through the updated priorities, 2 of 20.  Above 128 every pass keeps the fp32 chain.  So it does below 60
 // where the split form would be a launch of its own: a step with it takes 124.5 us at 43, 125 at 48, 131.5 at 54, 133.3 at
 // 60, 154 at 80, 191 at 128 (and would take 248 at 200); with the chain in every pass 120, 120.5, 128, 133.4, 168, 207 (259).
+// (Both sides with fc1 in 64-row tiles; fc1_blocks took 7 to 11 us from each above 64.)
 int native_passes(const dqn_ctx *c, int B) { return c->split && (step_launch(c, B) || (B >= 60 && B <= 128)) ? 1 : 3; }
 int step_native_rows(const dqn_ctx *c, int B) { return 8 * B <= c->num_cu ? 2 : 4; }   // rows of conv3 per unit
 int step_native_blocks(const dqn_ctx *c, int B) { return B * (step_native_rows(c, B) == 2 ? 4 : 2); }
