@@ -1066,7 +1066,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
     }
     {
         DgradArgs D{dh, c->theta + net::F1W, act3, d3, B};
-        launch(c, "fc1_dgrad", st, [&] { k_dgrad<DFc1, 32, 64><<<dim3((B + 31) / 32, 49, 1), 128, 0, st>>>(D); });
+        launch(c, "fc1_dgrad", st, [&] { k_dgrad_deep<DFc1><<<dim3((B + 63) / 64, 49, 1), 256, 0, st>>>(D); });
         ev_record(c->ev_a, st, sd);
     }
     {
@@ -1076,7 +1076,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
         // streams'), beyond that four: a step of 449 takes 440 us (449 with four), of 480 472 (484), of 600 569 (574); of 700 654 with two and 650, of
         // 1000 858 and 843
         const int tiles = (int)((M + 63) / 64), pad = tiles <= 3 * c->num_cu ? 20000 : 0;
-        launch(c, "conv3_dgrad", st, [&] { k_conv3_dgrad<<<tiles, 256, pad, st>>>(D); });
+        launch(c, "conv3_dgrad", st, [&] { k_dgrad_deep<DConv3><<<tiles, 256, pad, st>>>(D); });
         ev_record(c->ev_b, st, sd);
     }
     {

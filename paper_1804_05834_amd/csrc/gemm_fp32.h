@@ -4,7 +4,7 @@
 // backward / calculateGradient split of the paper's Layer class is kept as
 // three kernel families):
 //   k_fwd   : Y[m][n]  = sum_k  A(m,k) * W[n][k]            (conv1-3, fc1 forward)
-//   k_dgrad : dX[m][c] = sum_(tap,o) dY(m,tap,o) * W[o][tap][c]   (input gradients)
+//   dgrad   : dX[m][c] = sum_(tap,o) dY(m,tap,o) * W[o][tap][c]   (input gradients)
 //   k_wgrad : dW[o][k] = sum_m  dY[m][o] * A(m,k)           (weight gradients)
 // A(m,k) is the im2col view of a channel-last activation tensor, formed on the
 // fly while staging tiles in LDS; it never exists in memory.
@@ -492,13 +492,6 @@ __device__ __forceinline__ void dgrad_tile(const DgradArgs &A, int t, int gx, in
     for (int r = 0; r < 16; ++r)
         if (off[r] >= 0) A.dx[off[r]] = xm[r] > 0.f ? acc[r] : 0.f;
 }
-template <class D, int BM, int BN, int KS = 1, int KA = 1>
-__global__ __launch_bounds__((BM / 32) * (BN / 32) * KS * 64) void k_dgrad(DgradArgs A)
-{
-    __shared__ __attribute__((aligned(16))) float smem[dgrad_lds<BM, BN, KS>()];
-    dgrad_tile<D, BM, BN, KS, KA>(A, net::tile_of_workgroup(), gridDim.x, gridDim.z, smem);
-}
-
 // conv2's input gradient for many rows: the four parity classes read the same dY (class (a, b) at pixel (2h' + a, 2w' + b) the
 // positions h' - u, w' - v), so a tile is 64 of the 10 x 10 grids' rows by all classes' 32 channels, a wave per class, and dY is
 // staged once for the four.
@@ -624,18 +617,21 @@ __global__ __launch_bounds__(256, 3) void k_conv2_dgrad(DgradArgs A)
     }
 }
 
-// conv3's input gradient for many rows: dgrad_tile<DConv3, 64, 64>'s tile, sums and bits in the manner of k_conv2_dgrad, a tap
-// (two stages) per turn of the loop.  At a batch of 1000, alone, 69 -> 56 us; the step 852 -> 843, at 480 480 -> 472, at 930 807 -> 793
-// (650: 597 -> 603).
+// conv3's and fc1's input gradients for many rows: the sums and bits of dgrad_tile in tiles of 64 x 64, in the manner of
+// k_conv2_dgrad, two stages (conv3: a tap) per turn of the loop.  At a batch of 1000, alone, conv3's
+// 69 -> 56 us (the step 852 -> 843, at 480 480 -> 472, at 930 807 -> 793, at 650 597 -> 603), then fc1's 49 -> 39 from tiles of 32 x 64
+// (844 -> 835, at 480 471 -> 462, at 650 605 -> 596, at 700 652 either way).
 constexpr int DG3_LDB = 64 + 4, DG3_STAGE = 64 * LDK + BK * DG3_LDB;
-__global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
+template <class D>   // grid: row tiles x column tiles
+__global__ __launch_bounds__(256, 4) void k_dgrad_deep(DgradArgs A)
 {
-    using D = DConv3;
+    constexpr int TAPS = D::TH * D::TW, TURNS = D::K / 64, WROW = D::KH * D::KW * D::CI;
+    static_assert(D::S == 1 && D::H == D::HP && D::W == D::WP && D::CO % 64 == 0 && D::CI % 64 == 0, "shape");
     typedef __attribute__((address_space(1))) const float *Global;
     __shared__ __attribute__((aligned(16))) float smem[2 * DG3_STAGE];
     float *As = smem, *Bs = smem + 64 * LDK;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, h = lane >> 5;
-    const int wm = wave & 1, wn = wave >> 1, m0 = net::tile_of_workgroup() * 64, M = A.B * D::PP;
+    const int tile = net::tile_of_workgroup(), wm = wave & 1, wn = wave >> 1, m0 = tile % (int)gridDim.x * 64, n0 = tile / (int)gridDim.x * 64, M = A.B * D::PP;
     // this thread's pieces of a stage: rows ar and ar + 32 of dY, 16 bytes of each; rows br and br + 16 of the weights, 16 bytes
     const int ar = tid >> 3, ap = (tid & 7) * 4, br = tid >> 4, bc = (tid & 15) * 4;
     int arow[2];
@@ -645,17 +641,18 @@ __global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
         const int m = min(m0 + ar + 32 * i, M - 1), n = m / D::PP, r = m % D::PP, ph = r / D::WP, pw = r % D::WP;
         taps[i] = 0;
 #pragma unroll
-        for (int t = 0; t < 9; ++t) taps[i] |= (uint32_t)((uint32_t)(ph - t / 3) < (uint32_t)D::OH && (uint32_t)(pw - t % 3) < (uint32_t)D::OW) << t;
+        for (int t = 0; t < TAPS; ++t) taps[i] |= (uint32_t)((uint32_t)(ph - t / D::TW) < (uint32_t)D::OH && (uint32_t)(pw - t % D::TW) < (uint32_t)D::OW) << t;
         arow[i] = ((n * D::OH + ph) * D::OW + pw) * D::CO + ap;
     }
-    const float *wp = A.w + br * 9 * D::CI + bc;
+    const float *wp = A.w + br * WROW + n0 + bc;
     struct Regs { v4f a[2], b[2]; } R;
     constexpr int NP = 4;
-    auto request = [&](int tap, int o, int j) {
+    auto request = [&](int turn, int half, int j) {
+        const int tap = turn * 64 / D::CO, o = turn * 64 % D::CO + half;
         if (j < 2) {
-            const Global p = (Global)A.dy + (arow[j & 1] + (o - (tap / 3 * D::OW + tap % 3) * D::CO)), z = (Global)dg2_zeros + ap;
-            R.a[j & 1] = *reinterpret_cast<__attribute__((address_space(1))) const v4f *>(taps[j & 1] >> tap & 1 ? p : z);
-        } else R.b[j & 1] = ld4(wp + ((o + 16 * (j & 1)) * 9 + tap) * D::CI);
+            const Global p = (Global)A.dy + (arow[j & 1] + (o - (tap / D::TW * D::OW + tap % D::TW) * D::CO)), z = (Global)dg2_zeros + ap;
+            R.a[j & 1] = *reinterpret_cast<__attribute__((address_space(1))) const v4f *>(TAPS == 1 || taps[j & 1] >> tap & 1 ? p : z);
+        } else R.b[j & 1] = ld4(wp + ((o + 16 * (j & 1)) * WROW + tap * D::CI));
     };
     auto put = [&](int at, int j) {
         if (j < 2) *reinterpret_cast<v4f *>(&As[at + (ar + 32 * j) * LDK + ap]) = R.a[j & 1];
@@ -677,11 +674,11 @@ __global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto stage = [&](int at, int tap, int o) {   // (tap, o): of the stage after the next
+    auto stage = [&](int at, int turn, int o) {   // (turn, o): of the stage after the next
         multiply(O[0], [&](int k) {
             get(O[1], at, 1, k);
             if (k < NP) put(DG3_STAGE - at, k);
-            else request(tap, o, k - NP);
+            else request(turn, o, k - NP);
         });
         sync_lds();
         multiply(O[1], [&](int k) { get(O[0], DG3_STAGE - at, 0, k); });
@@ -695,8 +692,8 @@ __global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
     sync_lds();
 #pragma unroll
     for (int j = 0; j < 8; ++j) get(O[0], 0, 0, j);
-    for (int tap = 0; tap < 9; ++tap) {   // (behind the last tap: its own again, which nobody multiplies)
-        const int next = min(tap + 1, 8);
+    for (int turn = 0; turn < TURNS; ++turn) {   // (behind the last turn: its own again, which nobody multiplies)
+        const int next = min(turn + 1, TURNS - 1);
         stage(0, next, 0);
         stage(DG3_STAGE, next, 32);
     }
@@ -707,8 +704,8 @@ __global__ __launch_bounds__(256, 4) void k_conv3_dgrad(DgradArgs A)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int m = m0 + 32 * wm + 8 * g + 4 * h + j;   // (a row of the result is a pixel of the input)
-            off[4 * g + j] = m < M ? m * D::CI + 32 * wn + li : -1;
-            xm[4 * g + j] = A.xact[m < M ? m * D::CI + 32 * wn + li : 0];
+            off[4 * g + j] = m < M ? m * D::CI + n0 + 32 * wn + li : -1;
+            xm[4 * g + j] = A.xact[m < M ? m * D::CI + n0 + 32 * wn + li : 0];
         }
     }
 #pragma unroll
