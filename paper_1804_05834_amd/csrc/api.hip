@@ -948,7 +948,9 @@ __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::Wg
     if (id < P.nd) {
         // dispatch order -> tile number, die-aware within the group
         const int die = id & 7, slot = id >> 3, q = P.nd >> 3, r = P.nd & 7;
-        dgrad_tile<D, BM, BN, KS, KA>(DA, die * q + (die < r ? die : r) + slot, P.dgx, P.dgz, lds);
+        const int t = die * q + (die < r ? die : r) + slot;
+        if constexpr (KA == 0) dgrad_deep<D>(DA, t, P.dgx, lds);
+        else dgrad_tile<D, BM, BN, KS, KA>(DA, t, P.dgx, P.dgz, lds);
     } else if (id < P.nd + P.nw) {
         int bx, by, bz;
         wgrad_tile_of(id - P.nd, P.wgx, P.wgy, P.wgz, bx, by, bz);
@@ -1010,9 +1012,10 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                     k_layer_bwd_f32<DFc1, 32, 32, 4, GFc1, 256, true, 0><<<P.nd + P.nw + nh, 256, 0, st>>>(D, G4, P, HW, U);
                 });
             } else {
-                PairF32 P{gx * 49, gx, 1, 49 * 8, 49, 8, 1};
+                const int gd = (B + 63) / 64;
+                PairF32 P{gd * 49, gd, 1, 49 * 8, 49, 8, 1};
                 launch(c, "fc1_bwd", st, [&] {
-                    k_layer_bwd_f32<DFc1, 32, 64, 1, GFc1, 256, true, 0><<<P.nd + P.nw + nh, 256, 0, st>>>(D, G4, P, HW, U);
+                    k_layer_bwd_f32<DFc1, 64, 64, 1, GFc1, 256, true, 0, 0><<<P.nd + P.nw + nh, 256, 0, st>>>(D, G4, P, HW, U);
                 });
             }
         }
@@ -1028,7 +1031,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 const int gx = (int)(((long)B * 81 + 63) / 64);
                 PairF32 P{gx, gx, 1, 9 * *ns3, 9, 1, *ns3};
                 launch(c, "conv3_bwd", st, [&] {
-                    k_layer_bwd_f32<DConv3, 64, 64, 1, GConv3, 256, false, 1><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G3, P, HW, U);
+                    k_layer_bwd_f32<DConv3, 64, 64, 1, GConv3, 256, false, 1, 0><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G3, P, HW, U);
                 });
             }
         }
@@ -1849,8 +1852,8 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     // weight gradient and the priority update to another; they join again before the optimizer.
     // Their kernels are long enough (50-120 us) to repay the events; everything else stays on st
     // with one backward launch per layer.
-    // measured, one stream against three: 300 / 326 us per step at 256, 395 / 407 at 384, 404 / 414 at 400, 419 / 431 at 411, 438.6 / 431.8 at 420,
-    // 461 / 445 at 448
+    // measured, one stream against three: 300 / 326 us per step at 256, 395 / 407 at 384, 404 / 414 at 400, 419 / 431 at 411,
+    // 461 / 445 at 448; with the input gradients' deeper tiles in both 421 / 424 at 420, 429 / 423 at 430, 443 / 435 at 448
     const bool multi = c->side && cfg.precision == 0 && B >= 420;
     hipStream_t sd = multi ? c->side : st;
     hipStream_t sp = multi ? (c->side2 ? c->side2 : c->side) : st;

@@ -620,18 +620,19 @@ __global__ __launch_bounds__(256, 3) void k_conv2_dgrad(DgradArgs A)
 // conv3's and fc1's input gradients for many rows: the sums and bits of dgrad_tile in tiles of 64 x 64, in the manner of
 // k_conv2_dgrad, two stages (conv3: a tap) per turn of the loop.  At a batch of 1000, alone, conv3's
 // 69 -> 56 us (the step 852 -> 843, at 480 480 -> 472, at 930 807 -> 793, at 650 597 -> 603), then fc1's 49 -> 39 from tiles of 32 x 64
-// (844 -> 835, at 480 471 -> 462, at 650 605 -> 596, at 700 652 either way).
+// (844 -> 835, at 480 471 -> 462, at 650 605 -> 596, at 700 652 either way).  In the launches with the weight gradients too, a step
+// of 129 200 -> 193, of 200 243 -> 234, of 256 300 -> 289, of 419 435 -> 416.
 constexpr int DG3_LDB = 64 + 4, DG3_STAGE = 64 * LDK + BK * DG3_LDB;
-template <class D>   // grid: row tiles x column tiles
-__global__ __launch_bounds__(256, 4) void k_dgrad_deep(DgradArgs A)
+static_assert(dgrad_lds<64, 64, 1>() == 2 * DG3_STAGE, "LDS");
+template <class D>   // tile of gx row tiles by the column tiles, 256 threads
+__device__ __forceinline__ void dgrad_deep(const DgradArgs &A, int tile, int gx, float *smem)
 {
     constexpr int TAPS = D::TH * D::TW, TURNS = D::K / 64, WROW = D::KH * D::KW * D::CI;
     static_assert(D::S == 1 && D::H == D::HP && D::W == D::WP && D::CO % 64 == 0 && D::CI % 64 == 0, "shape");
     typedef __attribute__((address_space(1))) const float *Global;
-    __shared__ __attribute__((aligned(16))) float smem[2 * DG3_STAGE];
     float *As = smem, *Bs = smem + 64 * LDK;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 31, h = lane >> 5;
-    const int tile = net::tile_of_workgroup(), wm = wave & 1, wn = wave >> 1, m0 = tile % (int)gridDim.x * 64, n0 = tile / (int)gridDim.x * 64, M = A.B * D::PP;
+    const int wm = wave & 1, wn = wave >> 1, m0 = tile % gx * 64, n0 = tile / gx * 64, M = A.B * D::PP;
     // this thread's pieces of a stage: rows ar and ar + 32 of dY, 16 bytes of each; rows br and br + 16 of the weights, 16 bytes
     const int ar = tid >> 3, ap = (tid & 7) * 4, br = tid >> 4, bc = (tid & 15) * 4;
     int arow[2];
@@ -711,6 +712,12 @@ __global__ __launch_bounds__(256, 4) void k_dgrad_deep(DgradArgs A)
 #pragma unroll
     for (int k = 0; k < 16; ++k)
         if (off[k] >= 0) A.dx[off[k]] = xm[k] > 0.f ? acc[k] : 0.f;
+}
+
+template <class D> __global__ __launch_bounds__(256, 4) void k_dgrad_deep(DgradArgs A)   // grid: row tiles x column tiles
+{
+    __shared__ __attribute__((aligned(16))) float smem[2 * DG3_STAGE];
+    dgrad_deep<D>(A, net::tile_of_workgroup(), gridDim.x, smem);
 }
 
 // ---------------------------------------------------------------------------

@@ -423,6 +423,13 @@ def test_backward_on_one_stream_and_on_three(dq, monkeypatch, B):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("B", [129, 191, 193, 419, 421])
+def test_input_gradient_tiles_at_their_edges(dq, orc, B):
+    """fp32: tiles of 64 rows of fc1's, conv3's and conv2's input gradients, in both schedules, against the oracle."""
+    print("case input gradient tiles", B, flush=True)
+    _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41)
+
+
 def test_fc1_with_two_and_four_stages_in_lds(dq, monkeypatch):
     """bf16, 750 samples in each of three passes: the same sums whatever the number of stages, behind the same conv launches."""
     print("case fc1 stages", flush=True)
