@@ -827,7 +827,7 @@ int32_t act_on(dqn_ctx *c, const Workspace &w, const char *where, const uint8_t 
     if (few) {
         const misc::Fc1HeadArgs A{H, w.act3, bf16 ? (const void *)(shadow_of(c, 0) + net::F1W) : (const void *)(c->theta + net::F1W),
                                   w.f1part, w.arrivals};
-        launch(c, "fc1_head_act", st, [&] { misc::launch_fc1_head_act(A, bf16, st); });
+        launch(c, "fc1_head_act", st, [&] { bf16 ? gbf::launch_fc1_head_act(A, st) : misc::launch_fc1_head_act(A, st); });
         return hip_status(c, where);
     }
     if (ns < 1 || ns > misc::HEAD_MAX_SPLITS) return fail(c, DQN_ERR_STATE, std::string(where) + ": unexpected number of fc1 reduction splits");

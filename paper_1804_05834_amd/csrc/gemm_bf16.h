@@ -27,6 +27,7 @@
 #include <stdint.h>
 
 #include "gemm_fp32.h"
+#include "kernels_misc.h"
 #include "packed.h"
 #include "sumtree.h"
 
@@ -150,20 +151,15 @@ struct FwdArgs {
 // requested at once (140 registers) and the launch is one round trip, then seven short stages out of two LDS
 // buffers.  With one stage in flight ahead of the one in work it was a chain of seven trips: 11.4 us at 231 rows.
 constexpr int FC1_SPLITS = 7;
-template <int BN>
-__global__ __launch_bounds__(2 * BN) void k_fc1_fwd_few(FwdArgs A)
+// The tile of rows m0 .. + 31 (S.M in all), columns n0 .. + BN - 1 and split bz by T threads, of which the first BN / 32 waves
+// multiply; put(m, n, v): the sums of row m, columns n .. n + 3.  Dynamic or static LDS `lds`: fc1_few_lds<BN> elements.
+template <int BN> constexpr int fc1_few_lds() { return 2 * (32 + BN) * LDK; }
+template <int BN, int T, class Put>
+__device__ __forceinline__ void fc1_few_tile(const FwdSeg &S, int m0, int n0, int bz, bf16_t *lds, Put put)
 {
-    constexpr int BM = 32, T = 2 * BN, NST = GFc1::K / FC1_SPLITS / BK, NA = BM * 8 / T, NB = BN * 8 / T;
+    constexpr int BM = 32, NST = GFc1::K / FC1_SPLITS / BK, NA = BM * 8 / T, NB = BN * 8 / T;
     static_assert(NST * FC1_SPLITS * BK == GFc1::K && NA * T == BM * 8 && NB * T == BN * 8, "tile/threads mismatch");
-    __shared__ __attribute__((aligned(16))) bf16_t As[2][BM * LDK], Bs[2][BN * LDK];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // tile order: column tiles of one row tile together, reduction splits apart
-    const int t = net::tile_of_workgroup();
-    const int by = t % (int)gridDim.y, bx = (t / (int)gridDim.y) % (int)gridDim.x, bz = t / (int)(gridDim.y * gridDim.x);
-    FwdSeg S = A.seg[0];
-    if (A.nseg > 1 && bx >= A.seg[1].tile_begin) S = A.seg[1];
-    if (A.nseg > 2 && bx >= A.seg[2].tile_begin) S = A.seg[2];
-    const int m0 = (bx - S.tile_begin) * BM, n0 = by * BN, k0 = bz * (NST * BK);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k0 = bz * (NST * BK);
     const bf16_t *x = static_cast<const bf16_t *>(S.x);
     const int lr = tid >> 3, kq = (tid & 7) * 8;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a native vector: stays in registers
@@ -189,12 +185,13 @@ __global__ __launch_bounds__(2 * BN) void k_fc1_fwd_few(FwdArgs A)
     v16f acc = {0};
 #pragma unroll
     for (int st = 0; st < NST; ++st) {
-        bf16_t *as = As[st & 1], *bs = Bs[st & 1];
+        bf16_t *as = lds + (st & 1) * (BM * LDK), *bs = lds + 2 * BM * LDK + (st & 1) * (BN * LDK);
 #pragma unroll
         for (int i = 0; i < NA; ++i) *reinterpret_cast<u32x4 *>(&as[(lr + i * (T / 8)) * LDK + kq]) = ra[st][i];
 #pragma unroll
         for (int i = 0; i < NB; ++i) *reinterpret_cast<u32x4 *>(&bs[(lr + i * (T / 8)) * LDK + kq]) = rb[st][i];
         sync_lds();   // the buffer is complete; every wave is past the stage before, which read the other one
+        if (T > 2 * BN && wave >= BN / 32) continue;
         v8bf fa[4], fb[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -206,10 +203,48 @@ __global__ __launch_bounds__(2 * BN) void k_fc1_fwd_few(FwdArgs A)
     }
     // acc[4g + j] = Y[row m = lane li][channel = 8g + 4h + j]
     const int m = m0 + li;
-    if (m >= S.M) return;
-    float *y = static_cast<float *>(S.y) + (long)bz * A.split_stride + (long)m * GFc1::N + n0 + wave * 32 + 4 * h;
+    if (m >= S.M || (T > 2 * BN && wave >= BN / 32)) return;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) *reinterpret_cast<v4f *>(y + 8 * g) = v4f{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+    for (int g = 0; g < 4; ++g) put(m, n0 + wave * 32 + 4 * h + 8 * g, v4f{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]});
+}
+template <int BN>
+__global__ __launch_bounds__(2 * BN) void k_fc1_fwd_few(FwdArgs A)
+{
+    __shared__ __attribute__((aligned(16))) bf16_t lds[fc1_few_lds<BN>()];
+    // tile order: column tiles of one row tile together, reduction splits apart
+    const int t = net::tile_of_workgroup();
+    const int by = t % (int)gridDim.y, bx = (t / (int)gridDim.y) % (int)gridDim.x, bz = t / (int)(gridDim.y * gridDim.x);
+    FwdSeg S = A.seg[0];
+    if (A.nseg > 1 && bx >= A.seg[1].tile_begin) S = A.seg[1];
+    if (A.nseg > 2 && bx >= A.seg[2].tile_begin) S = A.seg[2];
+    float *y = static_cast<float *>(S.y) + (long)bz * A.split_stride;
+    fc1_few_tile<BN, 2 * BN>(S, (bx - S.tile_begin) * 32, by * BN, bz, lds,
+                             [&](int m, int n, v4f v) { *reinterpret_cast<v4f *>(y + (long)m * GFc1::N + n) = v; });
+}
+
+// bf16 acting on up to misc::FEW_ROWS observations: fc1 and the head in one launch (see misc::k_fc1_head_act for fp32).  The
+// tiles of k_fc1_fwd_few, 32 columns wide so that 112 CUs share the weights, their sums published instead of stored, and
+// the head by the workgroup that arrives last.  Every thread stages; one wave multiplies.
+template <int ROWS>
+__global__ __launch_bounds__(256, 1) void k_fc1_head_act(misc::Fc1HeadArgs A)
+{
+    __shared__ __attribute__((aligned(16))) bf16_t lds[fc1_few_lds<32>()];
+    __shared__ misc::FewLds L;
+    const int by = blockIdx.x % (GFc1::N / 32), bz = blockIdx.x / (GFc1::N / 32);
+    const FwdSeg S{A.x, static_cast<const bf16_t *>(A.w), nullptr, nullptr, ROWS, 0, (long)net::A3};
+    fc1_few_tile<32, 256>(S, 0, by * 32, bz, lds, [&](int m, int n, v4f v) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) misc::publish_word(A.h + (bz * ROWS + m) * net::HID + n + j, v[j]);
+    });
+    misc::words_acknowledged();
+    if (!misc::few_last(A, L, GFc1::N / 32 * FC1_SPLITS)) return;
+    misc::few_head<ROWS, FC1_SPLITS>(A, L);
+}
+inline void launch_fc1_head_act(const misc::Fc1HeadArgs &A, hipStream_t st)
+{
+    constexpr int TILES = GFc1::N / 32 * FC1_SPLITS;
+    if (A.head.E == 1) k_fc1_head_act<1><<<TILES, 256, 0, st>>>(A);
+    else k_fc1_head_act<misc::FEW_ROWS><<<TILES, 256, 0, st>>>(A);
 }
 
 // Dispatch-order number u of `total` workgroups -> tile number, die-aware as net::tile_of_workgroup

@@ -40,6 +40,12 @@ template <int O> __device__ __forceinline__ int lane_xor(int v)
 }
 template <int O> __device__ __forceinline__ float lane_xor(float v) { return __int_as_float(lane_xor<O>(__float_as_int(v))); }
 
+// the value of lane + N, of the same sixteen lanes (0 past them)
+template <int N> __device__ __forceinline__ float row_shl(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x100 + N, 0xF, 0xF, true));
+}
+
 template <int O = 32> __device__ __forceinline__ float wave_sum(float v)   // over groups of 2 O lanes
 {
     v += lane_xor<O>(v);
@@ -603,123 +609,134 @@ inline void launch_head_act(const HeadActArgs &H, int num_cu, hipStream_t st)
     }
 }
 
-// Acting on up to FEW_ROWS observations: fc1 and the head in one launch.  Workgroup b forms hidden units 2b and 2b + 1 of
-// every row, wave w unit w % 2 over half w / 2 of the inputs, 25 KB of weights (fp32) per CU, all requested at once;
-// the workgroup that arrives last (above) has the whole hidden layer and finishes every row as k_head_act does.  The
-// tiled fc1 launches multiply 32 rows whatever there are, leave 7 partial sums per unit, and the head is a launch behind
-// them.  One observation: 21.5 -> 19.0 us per call in fp32, 15.1 -> 14.2 in bf16; two: 21.5 -> 19.6, 15.0 -> 14.8.  With four
-// rows here the gain is gone (21.0 against 21.5, 15.9 against 15.2), and with the head's weights requested by every
-// workgroup in advance there is none over this (18.9, 14.4).
+// Acting on up to FEW_ROWS observations: fc1 and the head in one launch, whose workgroups leave their share of fc1 as
+// words in device memory; the one that arrives last (above) has the whole hidden layer and finishes every row as
+// k_head_act does.  Every sum is formed in the order of the launches for more observations (up to 192 in fp32, 511 in
+// bf16), so that the same inputs give the same bits alone and among others.  One observation, against the two launches:
+// 21.7 -> 19.3 us per call in fp32, 16.1 -> 14.0 in bf16; two: 21.8 -> 20.3, 16.4 -> 14.6.  (A form whose lanes and waves added in an order of their own took
+// 19.2 and 19.7 in fp32, 14.4 and 15.0 in bf16; with four rows that form had no gain left, 21.0 and 15.9.)
 // The counter is cleared by the conv launch in front, so that nothing of one call is left for the next.
-constexpr int FEW_ROWS = 2, FEW_BLOCKS = net::HID / 2;
+constexpr int FEW_ROWS = 2;
 struct Fc1HeadArgs {
     HeadActArgs head;      // (part, nsplit, split_stride: not used)
     const void *x;         // [E][3136] conv3's output, fp32 or bf16
     const void *w;         // [512][3136] in the same type
-    float *h;              // [E][512]
+    float *h;              // the words that are handed over: fp32 [E][512] hidden units; bf16 [split][E][512] partial sums
     unsigned *arrivals;
 };
-// four (eight) elements of 16 bytes as floats
-__device__ __forceinline__ void elements(uint4 u, float (&f)[4])
+struct FewLds {
+    __attribute__((aligned(16))) float hid[FEW_ROWS][HID_LDS];
+    float raw[FEW_ROWS][MAXR];
+    int last;
+};
+// Called by all 256 threads, each wave's published words acknowledged: is this workgroup the last of `of`?
+__device__ __forceinline__ bool few_last(const Fc1HeadArgs &A, FewLds &L, int of)
 {
-    f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y); f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
+    sync_lds();
+    if (threadIdx.x == 0) L.last = arrived_last(A.arrivals, of);
+    sync_lds();
+    return L.last;
 }
-__device__ __forceinline__ void elements(uint4 u, float (&f)[8])
+// The head of the last workgroup.  SUMS == 1: the words are the hidden units; else that many partial sums of each
+template <int ROWS, int SUMS> __device__ __forceinline__ void few_head(const Fc1HeadArgs &A, FewLds &L)
 {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = __uint_as_float(w[i] << 16);
-        f[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
-    }
-}
-template <int BYTES, int ROWS>   // bytes per element
-__global__ __launch_bounds__(256, 1) void k_fc1_head_act(Fc1HeadArgs A)
-{
-    constexpr int V = 16 / BYTES, C = net::A3 / V / 2, NI = (C + 63) / 64;   // elements per piece; pieces per half, per lane
-    static_assert(ROWS <= FEW_ROWS && net::A3 % (2 * V) == 0, "halves of whole pieces");
-    __shared__ __attribute__((aligned(16))) float hid[ROWS][HID_LDS];
-    __shared__ float raw[ROWS][MAXR];
-    __shared__ float half[ROWS][4];
-    __shared__ int last;
     const HeadActArgs &H = A.head;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = tid & 15;
-    const int unit = 2 * blockIdx.x + (wave & 1);
-    const uint4 *w = static_cast<const uint4 *>(A.w) + (long)unit * (2 * C) + (wave >> 1) * C;
-    uint4 wq[NI], xq[ROWS][NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) wq[i] = w[min(lane + 64 * i, C - 1)];
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const uint4 *x = static_cast<const uint4 *>(A.x) + (long)min(r, H.E - 1) * (2 * C) + (wave >> 1) * C;
-#pragma unroll
-        for (int i = 0; i < NI; ++i) xq[r][i] = x[min(lane + 64 * i, C - 1)];
-    }
-    const float b = H.f1b[2 * blockIdx.x + (tid & 1)];
-    float acc[ROWS][V] = {};
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        float wf[V], xf[V];
-        elements(wq[i], wf);
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            elements(xq[r][i], xf);
-#pragma unroll
-            for (int e = 0; e < V; ++e) {
-                const float p = fmaf(wf[e], xf[e], acc[r][e]);
-                acc[r][e] = 64 * (i + 1) <= C || lane + 64 * i < C ? p : acc[r][e];
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < V; e += 4) s += (acc[r][e] + acc[r][e + 1]) + (acc[r][e + 2] + acc[r][e + 3]);
-        s = wave_sum(s);
-        if (lane == 0) half[r][wave] = s;
-    }
-    sync_lds();
-    if (wave == 0) {
-        const int r = lane >> 1, u = lane & 1;
-        if (r < ROWS && r < H.E) publish_word(A.h + (long)r * net::HID + 2 * blockIdx.x + u, fmaxf(half[r][u] + half[r][u + 2] + b, 0.f));
-        words_acknowledged();
-        if (lane == 0) last = arrived_last(A.arrivals, FEW_BLOCKS);
-    }
-    sync_lds();
-    if (!last) return;
     const int K = H.K, R = K + (H.dueling ? 1 : 0);
     HeadRound H0, H1;
-    float hv[ROWS][2];
+    float p[ROWS][2][SUMS];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) hv[r][u] = read_word(A.h + (long)min(r, H.E - 1) * net::HID + tid + 256 * u);
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int sp = 0; sp < SUMS; ++sp) p[r][u][sp] = read_word(A.h + (sp * ROWS + r) * net::HID + tid + 256 * u);
+    const float b0 = H.f1b[tid], b1 = H.f1b[tid + 256];
     head_rows1_load(H0, 0, H.head, K, H.dueling, tid);
     head_rows1_load(H1, 1, H.head, K, H.dueling, tid);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-        for (int u = 0; u < 2; ++u) hid[r][hid_at(tid + 256 * u)] = hv[r][u];
+        for (int u = 0; u < 2; ++u) {
+            float acc = 0.f;
+#pragma unroll
+            for (int sp = 0; sp < SUMS; ++sp) acc += p[r][u][sp];
+            L.hid[r][hid_at(tid + 256 * u)] = SUMS == 1 ? p[r][u][0] : fmaxf(acc + (u ? b1 : b0), 0.f);
+        }
     sync_lds();
-    act_dots<ROWS>(H0, hid, raw, l);
-    if (16 + 4 * wave < R) act_dots<ROWS>(H1, hid, raw, l);
+    act_dots<ROWS>(H0, L.hid, L.raw, l);
+    if (16 + 4 * wave < R) act_dots<ROWS>(H1, L.hid, L.raw, l);
     for (int round = 2; 16 * round < R; ++round) {   // more than 32 dot products: K > 31
         head_rows1_load(H0, round, H.head, K, H.dueling, tid);
-        act_dots<ROWS>(H0, hid, raw, l);
+        act_dots<ROWS>(H0, L.hid, L.raw, l);
     }
     sync_lds();
-    if (wave < ROWS && wave < H.E) act_choose(H, raw[wave], wave, lane);
+    if (wave < ROWS) act_choose(H, L.raw[wave], wave, lane);
 }
-template <int BYTES> void launch_fc1_head_act_of(const Fc1HeadArgs &A, hipStream_t st)
+
+// fp32: workgroup b forms hidden units 2b and 2b + 1 of every row, 25 KB of weights per CU, all requested at once, and each
+// wave one unit of one row.  The sums of g32::k_fwd<GFc1, 32, 32, 7> in seven splits: a split's 448 inputs are two stages of
+// seven slices of 32; a slice is one chain of 64 products over both stages, which takes inputs 4..7 of every eight between
+// 0..3 (the matrix instruction's pairs); the seven slices are added in order, then the seven splits.  Those 49 chains are a
+// lane each, out of LDS, where 32 elements lie 36 apart: lanes that read the same element of neighbouring slices then start
+// in different banks.
+template <int ROWS>
+__global__ __launch_bounds__(256, 1) void k_fc1_head_act(Fc1HeadArgs A)
 {
-    if (A.head.E == 1) k_fc1_head_act<BYTES, 1><<<FEW_BLOCKS, 256, 0, st>>>(A);
-    else k_fc1_head_act<BYTES, FEW_ROWS><<<FEW_BLOCKS, 256, 0, st>>>(A);
+    constexpr int SPLITS = 7, SLICES = 7, SLICE = 32, PITCH = SLICE + 4;
+    constexpr int GROUPS = net::A3 / SLICE;                       // slices of a vector: 98
+    static_assert(GROUPS == SPLITS * 2 * SLICES && 8 * SPLITS <= 64 && SLICES == 7 && 2 * ROWS <= 4, "two stages per split; a wave per unit and row");
+    constexpr int NW = 2 * net::A3 / 4, NX = ROWS * net::A3 / 4;  // pieces of 16 bytes
+    constexpr int LW = (NW + 255) / 256, LX = (NX + 255) / 256;
+    __shared__ __attribute__((aligned(16))) float v[(2 + ROWS) * GROUPS * PITCH];   // the two units' weights, the rows
+    __shared__ FewLds L;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float4 *w = static_cast<const float4 *>(A.w) + (long)blockIdx.x * NW, *x = static_cast<const float4 *>(A.x);
+    float4 wq[LW], xq[LX];
+#pragma unroll
+    for (int i = 0; i < LW; ++i) wq[i] = w[min(tid + 256 * i, NW - 1)];
+#pragma unroll
+    for (int i = 0; i < LX; ++i) xq[i] = x[min(tid + 256 * i, NX - 1)];
+    const float b = A.head.f1b[2 * blockIdx.x + (wave & 1)];
+    auto store = [&](int piece, float4 q) { *reinterpret_cast<float4 *>(&v[(piece >> 3) * PITCH + (piece & 7) * 4]) = q; };
+#pragma unroll
+    for (int i = 0; i < LW; ++i) store(min(tid + 256 * i, NW - 1), wq[i]);   // (past the end: the last one's bits again)
+#pragma unroll
+    for (int i = 0; i < LX; ++i) store(NW + min(tid + 256 * i, NX - 1), xq[i]);
+    sync_lds();
+    if (wave < 2 * ROWS) {
+        // lane 8 p + j: slice j of split p (the eighth of every eight, and the last eight, repeat one)
+        const int p = min(lane >> 3, SPLITS - 1), first = 2 * SLICES * p + min(lane & 7, SLICES - 1);
+        const float *wp = v + ((wave & 1) * GROUPS + first) * PITCH, *xp = v + ((2 + (wave >> 1)) * GROUPS + first) * PITCH;
+        float s = 0.f;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int k = 0; k < SLICE; k += 8) {
+                const int at = st * SLICES * PITCH + k;
+                const float4 w0 = *reinterpret_cast<const float4 *>(wp + at), w1 = *reinterpret_cast<const float4 *>(wp + at + 4);
+                const float4 x0 = *reinterpret_cast<const float4 *>(xp + at), x1 = *reinterpret_cast<const float4 *>(xp + at + 4);
+                s = fmaf(x0.x, w0.x, s); s = fmaf(x1.x, w1.x, s);
+                s = fmaf(x0.y, w0.y, s); s = fmaf(x1.y, w1.y, s);
+                s = fmaf(x0.z, w0.z, s); s = fmaf(x1.z, w1.z, s);
+                s = fmaf(x0.w, w0.w, s); s = fmaf(x1.w, w1.w, s);
+            }
+        float split = s, sum = 0.f;   // complete in lanes 8 p
+        split += row_shl<1>(s); split += row_shl<2>(s); split += row_shl<3>(s);
+        split += row_shl<4>(s); split += row_shl<5>(s); split += row_shl<6>(s);
+#pragma unroll
+        for (int j = 0; j < SPLITS; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(split), 8 * j));
+        if (lane == 0) publish_word(A.h + (wave >> 1) * net::HID + 2 * blockIdx.x + (wave & 1), fmaxf(sum + b, 0.f));
+        words_acknowledged();
+    }
+    if (!few_last(A, L, net::HID / 2)) return;
+    few_head<ROWS, 1>(A, L);
 }
-inline void launch_fc1_head_act(const Fc1HeadArgs &A, bool bf16, hipStream_t st)
+inline void launch_fc1_head_act(const Fc1HeadArgs &A, hipStream_t st)
 {
-    if (bf16) launch_fc1_head_act_of<2>(A, st);
-    else launch_fc1_head_act_of<4>(A, st);
+    if (A.head.E == 1) k_fc1_head_act<1><<<net::HID / 2, 256, 0, st>>>(A);
+    else k_fc1_head_act<FEW_ROWS><<<net::HID / 2, 256, 0, st>>>(A);
 }
 
 // --------------------------------------------------------------- RMSProp

@@ -57,6 +57,35 @@ def test_act_on_few_observations(dq, orc, K, dueling, prec):
     m.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("K,dueling,small", [(18, 1, 0), (4, 0, 0), (64, 1, 0), (18, 1, 1)])
+def test_an_observation_has_the_same_bits_alone_and_among_others(dq, K, dueling, small, prec):
+    """One and two observations take launches of their own behind the conv layers; every sum is that of the launches for
+    more: up to 36 in fp32 (the conv layers of more are summed in other parts) and 511 in bf16.  small: fc1's weights are subnormal, the head's bring its sums back."""
+    print("case bits of few", K, dueling, small, prec, flush=True)
+    T = {name: synth.u24(70 + i, torch.arange(int(np.prod(shape)))).numpy().reshape(shape) - 0.5 if name.endswith(".W") else
+         np.zeros(shape) for i, (name, shape, _) in enumerate(synth.param_spec(K, dueling))}
+    if small:
+        T["fc1.W"] *= 1e-39
+        T["A.W"] *= 1e30
+        T["V.W"] *= 1e30
+    else:
+        T["fc1.b"] += 0.01
+    blob = np.concatenate([T[n].astype(np.float32).ravel() for n, _, _ in synth.param_spec(K, dueling)])
+    n = 511 if prec else 36
+    m = dq.Dqn(dq.make_config(num_actions=K, dueling=dueling, max_act_batch=n, precision=prec))
+    m.set_params(0, torch.from_numpy(blob))
+    obs = dev(synth.states(31, n))
+    a, q = m.act(obs, 0.0, 99, want_q=True)
+    assert torch.isfinite(q).all() and q.unique().numel() > n
+    for E in (1, 2, 3):
+        for i in range(0, n - E + 1, 5):
+            for static in (False, True):
+                x, y = m.act(obs[i:i + E].contiguous(), 0.0, 99, want_q=True, static=static)
+                assert torch.equal(y, q[i:i + E]) and torch.equal(x, a[i:i + E]), (E, i, static)
+    m.close()
+
+
 # fp32 steps: parts of the samples of s' are 1 row up to 14, 4 rows above; those of s are 2 rows up to 32, 4 rows above;
 # conv1 sums its frames in two halves up to 34; one launch for the conv layers up to 42; from 60 up to 128 one for s' and
 # layers for s
