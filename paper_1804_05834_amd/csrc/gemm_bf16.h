@@ -26,6 +26,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <iterator>
+#include <vector>
+
 #include "gemm_fp32.h"
 #include "kernels_misc.h"
 #include "packed.h"
@@ -1687,49 +1691,79 @@ __host__ __device__ constexpr bool complete(int strips) { return strips == UNITS
 // may sample k's image be written, with `reads` consumers done with the sample that had it before?
 __host__ __device__ constexpr bool image_free(int k, int reads) { return k < NRING || reads == CONSUMERS; }
 
-// Replays a run of ns samples on the host, in the orders that lead furthest: any one wave ahead of all others, and in turn.  A
-// sample is complete when it is read, every consumer reads it once, no strip is written into an image that still holds a
-// sample which some consumer has not read, and no wave waits for ever.  Returns 0 if safe, else a code naming the failure.
+// The host-side check of a run of ns samples: a search of all states that the waves can reach, in whatever order they take
+// their steps.  A state is how far each wave has come, twice the steps it is through with and one more while it is in one: a
+// producer that stores a strip has passed its wait and has not counted it in yet, and so a consumer that reads a sample.
+// What a wait lets through is held against the positions themselves: a sample is complete when it is read, no strip is
+// stored where a sample lies that some consumer has still to read, none of a later sample lies where one is read; and no
+// state but the last leaves every wave waiting.  Returns 0 if safe, else a code naming the failure.  (Consumers are alike:
+// their positions stay sorted, the last of equals moves.  A run of 32 samples has 4.2 million such states, 0.4 s.)
 inline int schedule_is_safe(int ns)
 {
     if (ns < 1 || ns > MAX_PER_WG) return 1;
-    constexpr int WAVES = PRODUCERS + CONSUMERS;
-    for (int first = 0; first <= WAVES; ++first) {   // `first` runs whenever it can (WAVES: nobody in particular)
-        int holds[NRING], strips[MAX_PER_WG], reads[MAX_PER_WG], at[WAVES];
-        for (int r = 0; r < NRING; ++r) holds[r] = -1;
-        for (int k = 0; k < ns; ++k) strips[k] = reads[k] = 0;
-        for (int w = 0; w < WAVES; ++w) at[w] = w < PRODUCERS ? w : 0;   // next strip; next sample
-        int err = 0;
-        auto step = [&](int w) {   // one strip or one sample of wave w, if it need not wait
-            if (w < PRODUCERS) {
-                if (at[w] >= UNITS * ns) return false;
-                const int k = sample_of_strip(at[w]), img = image_of_sample(k);
-                if (!image_free(k, k < NRING ? 0 : reads[k - NRING])) return false;
-                if (holds[img] != k) {
-                    if (holds[img] > k || (holds[img] >= 0 && reads[holds[img]] != CONSUMERS)) err = 3;
-                    holds[img] = k;
-                }
-                ++strips[k];
-                at[w] += PRODUCERS;
-            } else {
-                const int k = at[w];
-                if (k >= ns || !complete(strips[k])) return false;
-                if (holds[image_of_sample(k)] != k) err = 2;
-                ++reads[k];
-                ++at[w];
-            }
-            return true;
-        };
-        for (bool any = true; any;) {
-            any = false;
-            for (int w = 0; w < WAVES; ++w) {
-                while (first < WAVES && step(first)) any = true;
-                any |= step(w);
-            }
+    constexpr int WAVES = PRODUCERS + CONSUMERS, BITS = 8;
+    static_assert(WAVES * BITS <= 64 && 2 * MAX_PER_WG * UNITS / PRODUCERS + 2 < 1 << BITS, "a state in a word");
+    struct State { int at[WAVES]; };
+    int steps[WAVES];
+    std::vector<uint8_t> through[PRODUCERS];   // [n][k]: strips of sample k among a producer's first n
+    for (int w = 0; w < WAVES; ++w) {
+        steps[w] = w < PRODUCERS ? (UNITS * ns - w + PRODUCERS - 1) / PRODUCERS : ns;
+        if (w >= PRODUCERS) continue;
+        through[w].assign((steps[w] + 1) * ns, 0);
+        for (int n = 1; n <= steps[w]; ++n) {
+            for (int k = 0; k < ns; ++k) through[w][n * ns + k] = through[w][(n - 1) * ns + k];
+            ++through[w][n * ns + sample_of_strip(w + (n - 1) * PRODUCERS)];
         }
-        if (err) return err;
-        for (int k = 0; k < ns; ++k)
-            if (strips[k] != UNITS || reads[k] != CONSUMERS) return 5;   // something left over
+    }
+    auto strips = [&](const State &s, int k) {   // counted in
+        int n = 0;
+        for (int w = 0; w < PRODUCERS; ++w) n += through[w][s.at[w] / 2 * ns + k];
+        return n;
+    };
+    auto reads = [&](const State &s, int k) {
+        int n = 0;
+        for (int w = PRODUCERS; w < WAVES; ++w) n += s.at[w] / 2 > k;
+        return n;
+    };
+    std::vector<uint64_t> now{0}, next, sum, by[WAVES];   // each in ascending order
+    while (!now.empty()) {
+        for (auto &b : by) b.clear();
+        for (const uint64_t v : now) {
+            State s;
+            bool moved = false, done = true;
+            int begun = -1;   // the latest sample of which a strip has been stored or is being stored
+            for (int w = 0; w < WAVES; ++w) {
+                s.at[w] = (int)(v >> (BITS * w)) & ((1 << BITS) - 1);
+                done &= s.at[w] == 2 * steps[w];
+                if (w < PRODUCERS && s.at[w]) begun = std::max(begun, sample_of_strip(w + ((s.at[w] + 1) / 2 - 1) * PRODUCERS));
+            }
+            for (int w = 0; w < WAVES; ++w) {
+                if (s.at[w] == 2 * steps[w]) continue;
+                const int i = s.at[w] / 2, k = w < PRODUCERS ? sample_of_strip(w + i * PRODUCERS) : i;
+                if (!(s.at[w] & 1)) {   // its wait
+                    if (w < PRODUCERS) {
+                        if (!image_free(k, k < NRING ? 0 : reads(s, k - NRING))) continue;
+                        for (int j = s.at[PRODUCERS] / 2; j < k; ++j)   // samples that the last consumer is not through with
+                            if (image_of_sample(j) == image_of_sample(k)) return 3;
+                    } else {
+                        if (!complete(strips(s, k))) continue;
+                        if (strips(s, k) != UNITS) return 2;
+                        for (int j = k + 1; j <= begun; ++j)
+                            if (image_of_sample(j) == image_of_sample(k)) return 2;
+                    }
+                }
+                if (w < PRODUCERS || w == WAVES - 1 || s.at[w + 1] > s.at[w]) by[w].push_back(v + (1ull << (BITS * w)));
+                moved = true;
+            }
+            if (!moved && !done) return 5;
+        }
+        next.clear();
+        for (const auto &b : by) {
+            sum.clear();
+            std::set_union(next.begin(), next.end(), b.begin(), b.end(), std::back_inserter(sum));
+            next.swap(sum);
+        }
+        now.swap(next);
     }
     return 0;
 }

@@ -86,12 +86,12 @@ def test_product_does_not_touch_the_oracle():
 
 def test_fused_conv_ring_schedule_never_overwrites_an_unread_image(lib):
     """The fused conv1 + conv2 forward launch (bf16) hands conv1's output to the conv2 waves through
-    a ring of LDS images, by counts of the strips of a sample and of its reads.  The library replays
-    that hand-over on the host with the same functions its kernel loops call (which strip belongs to
-    which sample, which image holds a sample, when a sample may be read and an image written), for
-    every run length a workgroup can get and with every single wave running ahead of the others: a
-    sample is complete before it is read, it is read exactly once, no strip is written into an image
-    that still holds an unread sample, and no wave waits for ever."""
+    a ring of LDS images, by counts of the strips of a sample and of its reads.  The library searches
+    on the host, with the same functions its kernel loops call (which strip belongs to which sample,
+    which image holds a sample, when a sample may be read and an image written), all states that any
+    order of the waves' steps can reach, for every run length a workgroup can get: a sample is
+    complete before it is read, it is read exactly once, no strip is written into an image that
+    still holds an unread sample, and no wave waits for ever."""
     for ns in range(1, 33):
         assert lib.dqn_selftest_fused_conv_schedule(ns) == 0, ns
     assert lib.dqn_selftest_fused_conv_schedule(0) != 0 and lib.dqn_selftest_fused_conv_schedule(33) != 0
