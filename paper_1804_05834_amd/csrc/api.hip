@@ -930,6 +930,9 @@ struct SmallTail {
 // gradient rides in what the launch leaves free.  fc1's launch also takes the head's weight
 // gradient; workgroup 0 of each launch is part PART of the priority update.  A launch has the width of its widest tile
 // (256 / 384 / 512 threads); in a narrower tile the waves beyond leave at once.
+// The input gradient is formed in dgrad_tile's tiles, KA slices of the reduction in the same waves, or, with DEEP in the place
+// of KA, in dgrad_deep's, which have one size.
+constexpr int DEEP = 0;
 struct PairF32 {
     int nd, dgx, dgz;        // input gradient: tiles, grid x and z
     int nw, wgx, wgy, wgz;   // weight gradient: tiles, grid
@@ -939,6 +942,7 @@ __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::Wg
                                                       misc::HeadWgradArgs H, SplitUpdate U)
 {
     using namespace g32;
+    static_assert(KA != DEEP || (BM == 64 && BN == 64 && KS == 1 && TH == 256), "dgrad_deep: 64 x 64, four waves");
     constexpr int LD = dgrad_lds<BM, BN, KS>(), LW = wgrad_lds<64, 64>();
     constexpr int L0 = LD > LW ? LD : LW;
     constexpr int L = PART == 0 && misc::PU_LDS_WORDS > L0 ? misc::PU_LDS_WORDS : L0;
@@ -949,7 +953,7 @@ __global__ __launch_bounds__(TH) void k_layer_bwd_f32(g32::DgradArgs DA, g32::Wg
         // dispatch order -> tile number, die-aware within the group
         const int die = id & 7, slot = id >> 3, q = P.nd >> 3, r = P.nd & 7;
         const int t = die * q + (die < r ? die : r) + slot;
-        if constexpr (KA == 0) dgrad_deep<D>(DA, t, P.dgx, lds);
+        if constexpr (KA == DEEP) dgrad_deep<D>(DA, t, P.dgx, lds);
         else dgrad_tile<D, BM, BN, KS, KA>(DA, t, P.dgx, P.dgz, lds);
     } else if (id < P.nd + P.nw) {
         int bx, by, bz;
@@ -1015,7 +1019,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 const int gd = (B + 63) / 64;
                 PairF32 P{gd * 49, gd, 1, 49 * 8, 49, 8, 1};
                 launch(c, "fc1_bwd", st, [&] {
-                    k_layer_bwd_f32<DFc1, 64, 64, 1, GFc1, 256, true, 0, 0><<<P.nd + P.nw + nh, 256, 0, st>>>(D, G4, P, HW, U);
+                    k_layer_bwd_f32<DFc1, 64, 64, 1, GFc1, 256, true, 0, DEEP><<<P.nd + P.nw + nh, 256, 0, st>>>(D, G4, P, HW, U);
                 });
             }
         }
@@ -1031,7 +1035,7 @@ void backward_f32(dqn_ctx *c, int B, const Pass &ps, const uint8_t *s, long xs, 
                 const int gx = (int)(((long)B * 81 + 63) / 64);
                 PairF32 P{gx, gx, 1, 9 * *ns3, 9, 1, *ns3};
                 launch(c, "conv3_bwd", st, [&] {
-                    k_layer_bwd_f32<DConv3, 64, 64, 1, GConv3, 256, false, 1, 0><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G3, P, HW, U);
+                    k_layer_bwd_f32<DConv3, 64, 64, 1, GConv3, 256, false, 1, DEEP><<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G3, P, HW, U);
                 });
             }
         }
