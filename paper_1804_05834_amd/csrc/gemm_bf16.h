@@ -1427,9 +1427,9 @@ __global__ __launch_bounds__(256) void k_conv1_wgrad(WgradArgs A)
 // Wave (ph, hh) owns half of the position blocks and half of the channels; the result of lane
 // (n, g = lane/16) is channels 32hh + 8g .. +7 of its positions: 16 bytes per store.
 //
-// LDS layout of a sample: pixels in raster order, padded so that the pixels which the 16 lanes of
-// one lane group read (two apart for the stride-2 layer, neighbours for the stride-1 layer) start
-// 144 bytes apart, i.e. one 16-byte bank group further each: conflict-free.
+// LDS layout of a sample: see Shape.  conv2's reads meet no bank conflicts; conv3's, pixels in raster order 144 bytes
+// apart, meet some (1.6 M conflict cycles in a launch of 1536 samples), and a layout without them changed
+// nothing (42 us at 8192 samples either way: the launch is bound by its bytes).
 // ===========================================================================
 namespace ps {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // a native vector: stays in registers across barriers
@@ -1643,7 +1643,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_fwd_ps(Args A)
 // of 4 per SIMD and sample make 5,400 of the 6,700 cycles it takes, and hardly overlap.  With a barrier
 // between intervals of four strips instead of the counts, pixels as bf16 in LDS (twice the bytes) and positions
 // in order (conflicts: Shape) the launch of a step at 512 took 37.8 us, now 36.4, of 2048 observations 36.2
-// and 34.6, of 8192 125 and 124; the counts alone with pixels as bf16 37.6 at 512.
+// and 34.6, of 8192 125 and 124; the counts alone with pixels as bf16 37.6 at 512.  (Timed with events, which add
+// 2 us; rocprofv3 reads 33.9 at 512.)
 //
 // Replay mode: the workgroup draws its samples first (Eq.10 walk, two draws per wave and walk, all
 // eight waves), while the consumers' weight loads are in flight; the workgroups of segment 0 publish
@@ -2394,7 +2395,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 // passed through LDS in two halves of 32 output channels, and read back with the transposing LDS
 // load (ds_read_tr16_b64) straight into a-operand registers, where they stay for all samples.
 //
-// A sample's dY image sits in LDS at a 144-byte pixel pitch inside a border of zeros (written
+// A sample's dY image sits in LDS (160 bytes per pixel, PIX and ROW below) inside a border of zeros (written
 // once), so taps that fall outside the image read zeros: no bounds test, and every b-operand is a
 // single 16-byte read at a per-lane base + immediate offset.  The next sample's dY is in flight
 // while the current one is multiplied.  The ReLU mask is the stored activation at the result's
