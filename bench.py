@@ -33,7 +33,7 @@ def flops_per_launch(B, R):
     head = 2 * 512 * R
     return {
         "conv1_fwd": 3 * B * F_CONV1, "conv2_fwd": 3 * B * F_CONV2, "conv3_fwd": 3 * B * F_CONV3,
-        "conv12_fwd": 3 * B * (F_CONV1 + F_CONV2),   # bf16, larger batches: conv1 + conv2 in one launch
+        "conv123_fwd": 3 * B * (F_CONV1 + F_CONV2 + F_CONV3),   # the three layers in one launch
         "fc1_fwd": 3 * B * F_FC1, "head_train": 4 * B * head, "head_wgrad": B * head,
         "fc1_dgrad": B * F_FC1, "fc1_wgrad": B * F_FC1, "conv3_dgrad": B * F_CONV3,
         "conv3_wgrad": B * F_CONV3, "conv2_dgrad": B * F_CONV2, "conv2_wgrad": B * F_CONV2,
@@ -66,8 +66,8 @@ def gemm_bytes_per_launch(B, R, bf16):
     return {
         "conv1_fwd": frames + w1 + 3 * B * a1,
         "conv2_fwd": 3 * B * (a1 + a2) + w2,
-        # the fused launch keeps conv1's output on the CU; only the training rows' copy goes to memory
-        "conv12_fwd": frames + w1 + w2 + B * a1 + 3 * B * a2,
+        # the fused launch keeps conv1's and conv2's output on the CU; only the training rows' copies go to memory
+        "conv123_fwd": frames + w1 + w2 + w3 + B * (a1 + a2) + 3 * B * a3,
         "conv3_fwd": 3 * B * (a2 + a3) + w3,
         "fc1_fwd": 3 * B * (a3 + hid) + wf,
         "fc1_dgrad": B * (512 * e + 2 * a3) + wf,           # dH, ReLU mask, dX
@@ -92,8 +92,6 @@ def gemm_bytes_per_launch(B, R, bf16):
 # run (fetch x1.949, write x0.9875).  Keyed by (kernel, batch, precision); the figures and the
 # commands are in profiles/train_step_b512_bf16_hbm_traffic.md.
 MEASURED_TRAFFIC = {
-    ("conv12_fwd", 512, "bf16"): 46.2e6 + 28.7e6,
-    ("conv3_fwd", 512, "bf16"): 16.8e6 + 9.5e6,
     ("fc1_fwd", 512, "bf16"): 19.6e6 + 12.4e6,
     ("head_train", 512, "bf16"): 13.2e6 + 1.7e6,
     ("fc1_bwd", 512, "bf16"): 13.5e6 + 9.6e6,

@@ -294,13 +294,13 @@ int32_t dqn_replay_gather(dqn_ctx *ctx, const int32_t *idx, int32_t n, uint8_t *
 int32_t dqn_get_activations(dqn_ctx *ctx, int32_t layer, int32_t n, float *dst, void *stream);
 
 /* Host-only self-check, no device work: searches, for a run of ns samples per
- * workgroup (1..32), every state that the waves of the fused conv1 + conv2
+ * workgroup (1..32), every state that the waves of the fused conv1 to conv3
  * forward launch of the bf16 path can reach in any order of their steps, where
- * producer waves hand conv1's output of a sample (Section 3, first and second
- * layer) to consumer waves through a ring of images in LDS, by counts, using the
- * very functions the kernel's loops call.  A step is to begin or to end the
- * storing of a strip or the reading of a sample.  Returns 0 if every sample is
- * complete before it is read, read exactly once, and never overwritten while
+ * waves hand conv1's and conv2's output of a sample (Section 3, first and second
+ * layer) to the next layer's waves through rings of images in LDS, by counts, using
+ * the very functions the kernel's loops call.  A step is to begin or to end the
+ * storing of a share of a sample or the reading of a sample.  Returns 0 if every
+ * sample is complete before it is read, read exactly once, and never overwritten while
  * unread, and in no state but the last every wave waits; a positive code otherwise. */
 int32_t dqn_selftest_fused_conv_schedule(int32_t ns);
 

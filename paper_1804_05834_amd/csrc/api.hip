@@ -161,8 +161,8 @@ struct dqn_ctx {
     // side stream: kernels off the critical chain (weight gradients, priority update) overlap
     // the input-gradient chain of the backward pass
     int num_cu = 256;  // compute units of the device
-    // bf16: conv1 + conv2 forward run as one launch (gbf::c12) from this many samples per launch on;
-    // INT_MAX: never (the launch needs 140 KB of LDS per workgroup, granted at initialisation)
+    // bf16: the conv layers run as one launch of pipelined waves (gbf::pipe) from this many samples per launch on;
+    // INT_MAX: never (the launch needs 155 KB of LDS per workgroup, granted at initialisation)
     int conv12_min = INT32_MAX;
     bool rows_fit = false;   // fp32: the conv layers of many rows with a layer's weights in LDS (rows)
     bool conv123 = false;   // bf16: conv1 to conv3 as one launch for few samples (gbf::c123)
@@ -410,22 +410,22 @@ Conv123Plan conv123_plan(int samples, int num_cu)
     P.draw_fits = (units + P.grid - 1) / P.grid <= sp::MAX_UNITS;
     return P;
 }
-// bf16: all three conv layers as one launch (gbf::c123), or conv1 + conv2 and conv3 (gbf::c12, gbf::ps)?
+// bf16: the three conv layers' launch for few samples (gbf::c123), or for many (gbf::pipe)?
 // One unit per workgroup and a launch less: ahead while the samples of a training launch have a CU each (batch 32: 57.5
 // against 68.7 us per step, 77: 62.5 against 73.2, 85: 62.7 against 73.4; at 86 to 170, several units per workgroup, equal), acting,
 // which draws nothing, up to two (one observation: 14.4 against 23.0 us, 256: 20.7 against 28.8, 512: 31.4 against 36.3; at 1024,
 // four units per workgroup, 1.5 us behind).
-bool fused123(const dqn_ctx *c, long samples, int npass) { return c->conv123 && samples <= (npass == 1 ? 2 : 1) * c->num_cu; }
-// bf16: conv1 + conv2 as one launch, one workgroup per CU, for passes of n[0..npass) samples?
-bool fused12_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
+bool piped3(const dqn_ctx *c, long samples, int npass) { return c->conv123 && samples <= (npass == 1 ? 2 : 1) * c->num_cu; }
+// bf16: the conv layers as one launch of pipelined waves, one workgroup per CU, for passes of n[0..npass) samples?
+bool pipe_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 {
     long rows = 0;
     for (int i = 0; i < npass; ++i) rows += n[i];
     if (rows < c->conv12_min || npass > c->num_cu) return false;
-    const int grid12 = (int)std::min<long>(rows, c->num_cu);
+    const int grid_pipe = (int)std::min<long>(rows, c->num_cu);
     for (int i = 0; i < npass; ++i) {
-        const int wgs = (int)((long)grid12 * (i + 1) / npass - (long)grid12 * i / npass);
-        if (wgs < 1 || (n[i] + wgs - 1) / wgs > gbf::c12::MAX_PER_WG) return false;
+        const int wgs = (int)((long)grid_pipe * (i + 1) / npass - (long)grid_pipe * i / npass);
+        if (wgs < 1 || (n[i] + wgs - 1) / wgs > gbf::pipe::MAX_PER_WG) return false;
         if (draw && n[i] != n[0]) return false;
     }
     return true;
@@ -462,7 +462,7 @@ bool in_kernel_draw_fits(const dqn_ctx *c, int B)
         return np == 3 ? conv1_plan_f32(3 * B, c->num_cu).draw_fits : conv123_plan((3 - np) * B, c->num_cu).draw_fits;
     }
     const int n[3] = {B, B, B};
-    return fused123(c, 3l * B, 3) || fused12_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
+    return piped3(c, 3l * B, 3) || pipe_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
 
 // A tiled launch's segments for the launch by rows: the same share of the workgroups each (their rows are the same number)
@@ -656,7 +656,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
     long rows = 0;
     for (int i = 0; i < npass; ++i) { row0[i] = rows; rows += pass[i].n; }
 
-    const bool fused3 = fused123(c, rows, npass);
+    const bool fused3 = piped3(c, rows, npass);
     if (fused3) {
         const Conv123Plan plan = conv123_plan((int)rows, c->num_cu);
         c123::Args A{};
@@ -682,29 +682,29 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
             else c123::k_conv123_fwd<7, true><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
         });
     }
-    // conv1 + conv2 as one launch, one workgroup per CU (faster from a handful of samples on)
+    // ... or as a pipeline of waves, one workgroup per CU
     const int pass_n[3] = {pass[0].n, npass > 1 ? pass[1].n : 0, npass > 2 ? pass[2].n : 0};
-    const bool fused12 = !fused3 && fused12_fits(c, pass_n, npass, draw != nullptr);
-    const int grid12 = (int)std::min<long>(rows, c->num_cu);
-    if (fused12) {
-        c12::Args A{};
+    const bool piped = !fused3 && pipe_fits(c, pass_n, npass, draw != nullptr);
+    const int grid_pipe = (int)std::min<long>(rows, c->num_cu);
+    if (piped) {
+        pipe::Args A{};
         A.nseg = npass;
         for (int i = 0; i < npass; ++i) {
-            c12::Seg &S = A.seg[i];
+            pipe::Seg &S = A.seg[i];
+            const float *theta = theta_of(c, pass[i].net);
+            const bf16_t *sh = shadow_of(c, pass[i].net);
             S.src = c1::Src{pass[i].x, pass[i].xs, pass[i].idx, (long)c->cfg.replay_capacity, pass[i].shift, (int)c->sub};
-            S.w1 = shadow_of(c, pass[i].net) + net::C1W;
-            S.b1 = theta_of(c, pass[i].net) + net::C1B;
-            // only the backward pass reads conv1's output, and only the rows of the first pass of a training step
-            S.y1 = npass == 3 && i == 0 ? act1 + row0[i] * net::A1 : nullptr;
-            S.w2 = shadow_of(c, pass[i].net) + net::C2W;
-            S.b2 = theta_of(c, pass[i].net) + net::C2B;
-            S.y2 = act2 + row0[i] * net::A2;
+            // only the backward pass reads conv1's and conv2's output, and only the rows of a training step's first pass
+            const bool keep = npass == 3 && i == 0;
+            S.w1 = sh + net::C1W; S.b1 = theta + net::C1B; S.y1 = keep ? act1 + row0[i] * net::A1 : nullptr;
+            S.w2 = sh + net::C2W; S.b2 = theta + net::C2B; S.y2 = keep ? act2 + row0[i] * net::A2 : nullptr;
+            S.w3 = sh + net::C3W; S.b3 = theta + net::C3B; S.y3 = act3 + row0[i] * net::A3;
             S.n = pass[i].n;
         }
         for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
-        launch(c, "conv12_fwd", st, [&] { c12::k_conv12_fwd<<<dim3(grid12), 512, c12::LDS_BYTES, st>>>(A); });
+        launch(c, "conv123_fwd", st, [&] { pipe::k_conv_fwd_pipe<<<dim3(grid_pipe), 512, pipe::LDS_BYTES, st>>>(A); });
     } else if (!fused3)
     {  // conv1: persistent waves, strips of the frames staged in LDS (read from the ring in ring mode)
         c1::FwdArgs A{};
@@ -744,12 +744,12 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.total = first;
         return std::min(first, 2 * c->num_cu);
     };
-    if (!fused12 && !fused3) {
+    if (!piped && !fused3) {
         ps::Args A{};
         const int grid = per_sample(A, act1, net::A1, net::C2W, net::C2B, act2, net::A2);
         launch(c, "conv2_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G2><<<dim3(grid), 256, 0, st>>>(A); });
     }
-    if (!fused3) {
+    if (!piped && !fused3) {
         ps::Args A{};
         const int grid = per_sample(A, act2, net::A2, net::C3W, net::C3B, act3, net::A3);
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
@@ -819,7 +819,7 @@ int32_t act_on(dqn_ctx *c, const Workspace &w, const char *where, const uint8_t 
     long ss = 0;
     const bool bf16 = c->cfg.precision == 1;
     // fc1 and the head in one launch, where the conv layers are one that clears the counter
-    const bool few = E <= misc::FEW_ROWS && (bf16 ? fused123(c, E, 1) : c->split);
+    const bool few = E <= misc::FEW_ROWS && (bf16 ? piped3(c, E, 1) : c->split);
     int32_t rc = forward_trunk(c, w, &p, 1, &ns, &ss, st, nullptr, few);
     if (rc) return rc;
     misc::HeadActArgs H{w.f1part, ns, ss, E, c->cfg.num_actions, c->cfg.dueling, c->theta + net::F1B,
@@ -1365,9 +1365,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         c->rows_fit = granted(rows::k_fwd<g32::GConv2>, rows::lds_bytes<g32::GConv2>()) && granted(rows::k_fwd<g32::GConv3>, rows::lds_bytes<g32::GConv3>());
     } else {
         // DQN_CONV12_MIN_SAMPLES in the environment moves the number of samples (of all passes of a launch) from which
-        // conv1 + conv2 are one launch, in the form without the three-layer launch; a huge value: never
+        // the conv layers are one launch of pipelined waves, without the launch for few samples; a huge value: never
         const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");
-        if (granted(gbf::c12::k_conv12_fwd, gbf::c12::LDS_BYTES)) c->conv12_min = m && m[0] ? std::atoi(m) : 8;
+        if (granted(gbf::pipe::k_conv_fwd_pipe, gbf::pipe::LDS_BYTES)) c->conv12_min = m && m[0] ? std::atoi(m) : 8;
         c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1, false>, gbf::c123::Geo<1>::LDS) &&
                      granted(gbf::c123::k_conv123_fwd<4, false>, gbf::c123::Geo<4>::LDS) &&
                      granted(gbf::c123::k_conv123_fwd<7, false>, gbf::c123::Geo<7>::LDS) && granted(gbf::c123::k_conv123_fwd<7, true>, gbf::c123::Geo<7>::LDS);
@@ -1493,7 +1493,7 @@ int32_t dqn_get_activations(dqn_ctx *c, int32_t layer, int32_t n, float *dst, vo
 int32_t dqn_selftest_fused_conv_schedule(int32_t ns)
 {
     try {
-        return gbf::c12::schedule_is_safe(ns);
+        return gbf::pipe::schedule_is_safe(ns);
     } catch (const std::bad_alloc &) {
         return 4;   // not checked
     }

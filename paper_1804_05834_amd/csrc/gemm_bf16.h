@@ -1628,34 +1628,36 @@ __global__ __launch_bounds__(256, 2) void k_conv_fwd_ps(Args A)
 }  // namespace ps
 
 // ===========================================================================
-// conv1 + conv2 forward in ONE launch (Section 2.1 network): conv1's output of a sample never leaves
-// the CU unless a later kernel reads it (the backward pass reads it for the training rows only).
+// conv1, conv2 and conv3 forward in ONE launch for many samples: of what lies between the pixels and conv3's output,
+// only what a later kernel reads leaves the CU (the backward pass reads conv1's and conv2's of the training rows).
 //
-// A workgroup of eight waves owns a run of samples of one segment.  Waves 0-3 are PRODUCERS: each
-// computes every fourth conv1 strip as c1::k_conv1_fwd does (the strip's pixels in LDS of its own, as
+// A workgroup of eight waves owns a run of samples of one segment, and the layers are a pipeline of waves.  Waves 0-3 are
+// PRODUCERS: each computes conv1 strips as c1::k_conv1_fwd does (the strip's pixels in LDS of its own, as
 // bytes, and widened between the matrix instructions of the frame before; weights in registers, next
 // strip's pixels in flight) and writes the 80 x 32 result into the sample's place in a ring of four LDS
-// images, in the layout ps::run reads.  Waves 4-7 are CONSUMERS: they hold conv2's weights in registers
-// as ps::k_conv_fwd_ps does and compute the conv2 output of each sample out of the ring.  The waves hand
-// over by counts in LDS: a consumer waits for the five strips of its sample, a producer, before it writes,
-// for the four consumers of the sample that had the image before, four samples back.
-// What bounds it is the issue of the SIMDs: 196 matrix instructions of 16 cycles and about 560 vector instructions
-// of 4 per SIMD and sample make 5,400 of the 6,700 cycles it takes, and hardly overlap.  With a barrier
-// between intervals of four strips instead of the counts, pixels as bf16 in LDS (twice the bytes) and positions
-// in order (conflicts: Shape) the launch of a step at 512 took 37.8 us, now 36.4, of 2048 observations 36.2
-// and 34.6, of 8192 125 and 124; the counts alone with pixels as bf16 37.6 at 512.  (Timed with events, which add
-// 2 us; rocprofv3 reads 33.9 at 512.)
+// images, in the layout ps::run reads.  Waves 4 and 5 hold conv2's weights in registers, a channel half each,
+// and compute the conv2 output of each sample out of the ring into a ring of two images; waves 6 and 7 hold conv3's
+// and finish the sample out of those.  The waves hand over by counts in LDS: a consumer waits for the five strips (the two
+// halves) of its sample, whoever writes for the two consumers of the sample that had the image before.
+// What bounds it is the issue of the SIMDs: 268 matrix instructions of 16 cycles and about 600 vector instructions of 4
+// per SIMD and sample, which hardly overlap.  conv2's waves have a third more matrix instructions per sample than conv3's
+// (192, 144), so the producers beside them (a wave sits on SIMD number % 4) take fewer strips: first_strip, next_strip (three of
+// fourteen; one of six 177 us for 8192 observations, two of ten or four of eighteen the same 173, seven of thirty 175).
+// Against conv1 + conv2 in a launch of four producers and four conv2 waves and conv3 in one of its own, which wrote conv2's output and
+// read it back: 8192 observations 189.1 -> 170.1 us per call, a step of 512 136.1 -> 130.3, the fleet's iteration (acting on
+// 2048, a step of 256) 188.8 -> 174.4; the same bits.  Consumers at a higher wave priority: 182 us for 8192.
 //
 // Replay mode: the workgroup draws its samples first (Eq.10 walk, two draws per wave and walk, all
 // eight waves), while the consumers' weight loads are in flight; the workgroups of segment 0 publish
 // the draws.  Otherwise the slots (ring mode) are copied into LDS from where a sampling kernel left them.
 // Workgroups are dealt out per segment, so none pays the start-up twice.
 // ===========================================================================
-namespace c12 {
+namespace pipe {
 using c1::Src;
 using c1::STRIP;
 using c1::UNITS;
 using S2 = ps::Shape<ps::G2>;
+using S3 = ps::Shape<ps::G3>;
 using ps::u32x4;
 
 struct Seg {
@@ -1665,7 +1667,10 @@ struct Seg {
     bf16_t *y1;         // [n][400][32], or nullptr: conv1's output is not kept
     const bf16_t *w2;   // [64][512]
     const float *b2;    // [64]
-    bf16_t *y2;         // [n][81][64]
+    bf16_t *y2;         // [n][81][64], or nullptr
+    const bf16_t *w3;   // [64][576]
+    const float *b3;    // [64]
+    bf16_t *y3;         // [n][49][64]
     int n;              // samples
 };
 struct Args {
@@ -1675,85 +1680,100 @@ struct Args {
     misc::SampleArgs samp;
 };
 
-constexpr int NRING = 4;                                    // conv1 images in LDS
+constexpr int NRING = 4, NRING2 = 2;                        // conv1's and conv2's images in LDS
 constexpr int MAX_PER_WG = 32;                              // samples one workgroup may own (slot table)
-constexpr int PRODUCERS = 4, CONSUMERS = 4;                 // waves
+constexpr int PRODUCERS = 4, CONSUMERS = 2;                 // waves of conv1; of conv2, and of conv3
 constexpr int STRIPS_B = PRODUCERS * STRIP;                 // 26,880 bytes: one strip per producer wave, pixels as bytes
 constexpr int RING_B = NRING * S2::SAMPLE;                  // 103,680 bytes
-constexpr int LDS_BYTES = STRIPS_B + RING_B + MAX_PER_WG * 8 + 16 + MAX_PER_WG * 8;   // + slot table, leaf values, total, counts
-static_assert(STRIP % 16 == 0, "LDS layout");
+constexpr int RING2_B = NRING2 * S3::SAMPLE;                // 23,328 bytes
+constexpr int COUNTS = 4;                                   // per sample: strips, reads, halves, reads of conv2's image
+constexpr int LDS_BYTES = STRIPS_B + RING_B + RING2_B + MAX_PER_WG * 8 + 16 + COUNTS * MAX_PER_WG * 4;   // + slot table, leaf values, total, counts
+static_assert(STRIP % 16 == 0 && S3::SAMPLE % 16 == 0 && LDS_BYTES <= 160 * 1024, "LDS layout");
 // The hand-over, as functions that the kernel and the host-side check (schedule_is_safe, behind
-// dqn_selftest_fused_conv_schedule) both call.  Strip u of a run is produced by wave u % PRODUCERS, in order; a producer
-// counts its strips in per sample, a consumer the samples it has read.
+// dqn_selftest_fused_conv_schedule) both call.  The strips of a run are dealt out in order, PERIOD at a time: waves 2, 3, 0, 1,
+// 2, 3 and so on, so that 2 and 3 get four of fourteen and 0 and 1 three.  A producer counts its strips in per sample, a
+// consumer the samples it has read, a conv2 wave also those it has stored.
+constexpr int PERIOD = 14;
+static_assert(PERIOD % PRODUCERS == 2, "waves 2 and 3 first and last");
+__host__ __device__ constexpr int first_strip(int w) { return (w + 2) % PRODUCERS; }
+__host__ __device__ constexpr int next_strip(int u)
+{
+    const int at = u % PERIOD;
+    return u + (at + PRODUCERS < PERIOD ? PRODUCERS : at < PERIOD - 2 ? PRODUCERS + 2 : 2);
+}
 __host__ __device__ constexpr int sample_of_strip(int u) { return u / UNITS; }
 __host__ __device__ constexpr int image_of_sample(int k) { return k % NRING; }
-// may sample k be read, with `strips` of its strips counted in?
+__host__ __device__ constexpr int image2_of_sample(int k) { return k % NRING2; }
+// may sample k be read, with `strips` of its strips (`halves` of its channel halves) counted in?
 __host__ __device__ constexpr bool complete(int strips) { return strips == UNITS; }
+__host__ __device__ constexpr bool complete2(int halves) { return halves == CONSUMERS; }
 // may sample k's image be written, with `reads` consumers done with the sample that had it before?
 __host__ __device__ constexpr bool image_free(int k, int reads) { return k < NRING || reads == CONSUMERS; }
+__host__ __device__ constexpr bool image2_free(int k, int reads) { return k < NRING2 || reads == CONSUMERS; }
 
-// The host-side check of a run of ns samples: a search of all states that the waves can reach, in whatever order they take
+// The host-side check of one hand-over: a search of all states that its waves can reach, in whatever order they take
 // their steps.  A state is how far each wave has come, twice the steps it is through with and one more while it is in one: a
-// producer that stores a strip has passed its wait and has not counted it in yet, and so a consumer that reads a sample.
-// What a wait lets through is held against the positions themselves: a sample is complete when it is read, no strip is
-// stored where a sample lies that some consumer has still to read, none of a later sample lies where one is read; and no
-// state but the last leaves every wave waiting.  Returns 0 if safe, else a code naming the failure.  (Consumers are alike:
-// their positions stay sorted, the last of equals moves.  A run of 32 samples has 4.2 million such states, 0.4 s.)
-inline int schedule_is_safe(int ns)
+// writer that stores has passed its wait and has not counted its share in yet, and so a reader of a sample.
+// What a wait lets through is held against the positions themselves: a sample is complete when it is read, nothing is
+// stored where a sample lies that some reader has still to read, none of a later sample lies where one is read; and no
+// state but the last leaves every wave waiting.  of[w]: the samples of writer w's steps, in order; a sample is `parts` steps.
+// Returns 0 if safe, else a code naming the failure.  (Readers are alike: their positions stay sorted, the last of equals moves.)
+template <class Complete, class Image, class Free>
+int handover_is_safe(int ns, int parts, const std::vector<std::vector<int>> &of, int ring, Complete is_complete, Image image, Free is_free)
 {
-    if (ns < 1 || ns > MAX_PER_WG) return 1;
-    constexpr int WAVES = PRODUCERS + CONSUMERS, BITS = 8;
-    static_assert(WAVES * BITS <= 64 && 2 * MAX_PER_WG * UNITS / PRODUCERS + 2 < 1 << BITS, "a state in a word");
-    struct State { int at[WAVES]; };
-    int steps[WAVES];
-    std::vector<uint8_t> through[PRODUCERS];   // [n][k]: strips of sample k among a producer's first n
-    for (int w = 0; w < WAVES; ++w) {
-        steps[w] = w < PRODUCERS ? (UNITS * ns - w + PRODUCERS - 1) / PRODUCERS : ns;
-        if (w >= PRODUCERS) continue;
+    constexpr int BITS = 8;
+    const int W = (int)of.size(), WAVES = W + CONSUMERS;
+    int at[64 / BITS];
+    std::vector<std::vector<uint8_t>> through(W);   // [n][k]: steps for sample k among a writer's first n
+    std::vector<int> steps(WAVES, ns);
+    for (int w = 0; w < W; ++w) {
+        steps[w] = (int)of[w].size();
         through[w].assign((steps[w] + 1) * ns, 0);
         for (int n = 1; n <= steps[w]; ++n) {
             for (int k = 0; k < ns; ++k) through[w][n * ns + k] = through[w][(n - 1) * ns + k];
-            ++through[w][n * ns + sample_of_strip(w + (n - 1) * PRODUCERS)];
+            ++through[w][n * ns + of[w][n - 1]];
         }
     }
-    auto strips = [&](const State &s, int k) {   // counted in
+    for (int w = 0; w < WAVES; ++w)
+        if (2 * steps[w] >= 1 << BITS || WAVES * BITS > 64) return 4;
+    auto stored = [&](int k) {   // counted in
         int n = 0;
-        for (int w = 0; w < PRODUCERS; ++w) n += through[w][s.at[w] / 2 * ns + k];
+        for (int w = 0; w < W; ++w) n += through[w][at[w] / 2 * ns + k];
         return n;
     };
-    auto reads = [&](const State &s, int k) {
+    auto reads = [&](int k) {
         int n = 0;
-        for (int w = PRODUCERS; w < WAVES; ++w) n += s.at[w] / 2 > k;
+        for (int w = W; w < WAVES; ++w) n += at[w] / 2 > k;
         return n;
     };
-    std::vector<uint64_t> now{0}, next, sum, by[WAVES];   // each in ascending order
+    std::vector<uint64_t> now{0}, next, sum;   // each in ascending order
+    std::vector<std::vector<uint64_t>> by(WAVES);
     while (!now.empty()) {
         for (auto &b : by) b.clear();
         for (const uint64_t v : now) {
-            State s;
             bool moved = false, done = true;
-            int begun = -1;   // the latest sample of which a strip has been stored or is being stored
+            int begun = -1;   // the latest sample of which something has been stored or is being stored
             for (int w = 0; w < WAVES; ++w) {
-                s.at[w] = (int)(v >> (BITS * w)) & ((1 << BITS) - 1);
-                done &= s.at[w] == 2 * steps[w];
-                if (w < PRODUCERS && s.at[w]) begun = std::max(begun, sample_of_strip(w + ((s.at[w] + 1) / 2 - 1) * PRODUCERS));
+                at[w] = (int)(v >> (BITS * w)) & ((1 << BITS) - 1);
+                done &= at[w] == 2 * steps[w];
+                if (w < W && at[w]) begun = std::max(begun, of[w][(at[w] + 1) / 2 - 1]);
             }
             for (int w = 0; w < WAVES; ++w) {
-                if (s.at[w] == 2 * steps[w]) continue;
-                const int i = s.at[w] / 2, k = w < PRODUCERS ? sample_of_strip(w + i * PRODUCERS) : i;
-                if (!(s.at[w] & 1)) {   // its wait
-                    if (w < PRODUCERS) {
-                        if (!image_free(k, k < NRING ? 0 : reads(s, k - NRING))) continue;
-                        for (int j = s.at[PRODUCERS] / 2; j < k; ++j)   // samples that the last consumer is not through with
-                            if (image_of_sample(j) == image_of_sample(k)) return 3;
+                if (at[w] == 2 * steps[w]) continue;
+                const int i = at[w] / 2, k = w < W ? of[w][i] : i;
+                if (!(at[w] & 1)) {   // its wait
+                    if (w < W) {
+                        if (!is_free(k, k < ring ? 0 : reads(k - ring))) continue;
+                        for (int j = at[W] / 2; j < k; ++j)   // samples that the last reader is not through with
+                            if (image(j) == image(k)) return 3;
                     } else {
-                        if (!complete(strips(s, k))) continue;
-                        if (strips(s, k) != UNITS) return 2;
+                        if (!is_complete(stored(k))) continue;
+                        if (stored(k) != parts) return 2;
                         for (int j = k + 1; j <= begun; ++j)
-                            if (image_of_sample(j) == image_of_sample(k)) return 2;
+                            if (image(j) == image(k)) return 2;
                     }
                 }
-                if (w < PRODUCERS || w == WAVES - 1 || s.at[w + 1] > s.at[w]) by[w].push_back(v + (1ull << (BITS * w)));
+                if (w < W || w == WAVES - 1 || at[w + 1] > at[w]) by[w].push_back(v + (1ull << (BITS * w)));
                 moved = true;
             }
             if (!moved && !done) return 5;
@@ -1768,9 +1788,31 @@ inline int schedule_is_safe(int ns)
     }
     return 0;
 }
+// A run of ns samples: the two hand-overs one by one.  A conv2 wave is a reader in the first and a writer in the second; either
+// search covers its steps at any pace, so also its waits in the other; and its wait for an image of the second ends without
+// any step of the first (conv3's waves wait for nothing but halves that conv2's have begun).  Every strip has one owner.
+inline int schedule_is_safe(int ns)
+{
+    if (ns < 1 || ns > MAX_PER_WG) return 1;
+    std::vector<std::vector<int>> strips(PRODUCERS), halves(CONSUMERS);
+    std::vector<int> owners(UNITS * ns, 0);
+    for (int w = 0; w < PRODUCERS; ++w)
+        for (int u = first_strip(w); u < UNITS * ns; u = next_strip(u)) {
+            strips[w].push_back(sample_of_strip(u));
+            ++owners[u];
+        }
+    for (const int n : owners)
+        if (n != 1) return 6;
+    for (auto &h : halves)
+        for (int k = 0; k < ns; ++k) h.push_back(k);
+    if (const int e = handover_is_safe(ns, UNITS, strips, NRING, complete, image_of_sample, image_free)) return e;
+    const int e = handover_is_safe(ns, CONSUMERS, halves, NRING2, complete2, image2_of_sample, image2_free);
+    return e ? 10 + e : 0;
+}
 
 // The counts of a sample, in LDS: every operation of a wave is carried out there in the order in which it was issued, so
 // a count that has been seen stands behind the stores (or reads) of the wave that raised it.
+struct Counts { int *strips, *reads, *halves, *reads2; };
 __device__ __forceinline__ int count_of(int *p)
 {
     return __builtin_amdgcn_readfirstlane(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
@@ -1780,14 +1822,9 @@ __device__ __forceinline__ void count_in(int *p, int lane)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     if (lane == 0) __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-__device__ __forceinline__ void await_complete(int *strips)
+template <class Ready> __device__ __forceinline__ void await(Ready ready)
 {
-    while (!complete(count_of(strips))) __builtin_amdgcn_s_sleep(1);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-__device__ __forceinline__ void await_image(int *reads, int k)
-{
-    while (!image_free(k, k < NRING ? 0 : count_of(reads + k - NRING))) __builtin_amdgcn_s_sleep(1);
+    while (!ready()) __builtin_amdgcn_s_sleep(1);
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
@@ -1829,64 +1866,129 @@ __device__ __forceinline__ void store_strip(uint8_t *xs, const Pixels &R, int la
     }
 }
 
-// samples [lo, hi) of segment S, consumer wave (ph, hh) = (position half, channel half)
-__device__ __forceinline__ void run_consumer(const Seg &S, int lo, int hi, const uint8_t *ring, const v8bf (&wa)[16][2],
-                                             int *strips, int *reads, int lane, int ph, int hh)
+// bias, ReLU, bf16 of a position's eight channels
+__device__ __forceinline__ uint4 finished(v4f a0, v4f a1, v4f b0, v4f b1)
+{
+    const uint2 lo = pack4(fmaxf(a0.x + b0.x, 0.f), fmaxf(a0.y + b0.y, 0.f), fmaxf(a0.z + b0.z, 0.f), fmaxf(a0.w + b0.w, 0.f));
+    const uint2 hi = pack4(fmaxf(a1.x + b1.x, 0.f), fmaxf(a1.y + b1.y, 0.f), fmaxf(a1.z + b1.z, 0.f), fmaxf(a1.w + b1.w, 0.f));
+    return uint4{lo.x, lo.y, hi.x, hi.y};
+}
+// A consumer wave's weights of channel half hh, straight into a-operand registers: row 8(n/4) + 4cb + n%4 of the half,
+// reduction elements 32st + 8kg .. +7
+template <class S> __device__ __forceinline__ void load_weights(v8bf (&wa)[S::STEPS][2], const bf16_t *w, int lane, int hh)
+{
+    const int n = lane & 15, kg = lane >> 4;
+#pragma unroll
+    for (int st = 0; st < S::STEPS; ++st)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const int chl = 8 * (n >> 2) + 4 * cb + (n & 3);
+            wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(w + (32 * hh + chl) * S::K + st * 32 + kg * 8));
+        }
+}
+// The sums of NB tiles of 16 positions, this lane's operand of tile b and step st at at(b, st); the operands are requested two
+// steps ahead of their matrix instructions
+template <class S, int NB, class At>
+__device__ __forceinline__ void multiply(v4f (&acc)[NB][2], const v8bf (&wa)[S::STEPS][2], At at)
+{
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0};
+    uint4 q[3][NB];
+    auto request = [&](int st) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) q[st % 3][b] = *reinterpret_cast<const uint4 *>(at(b, st));
+    };
+    request(0);
+    request(1);
+#pragma unroll
+    for (int st = 0; st < S::STEPS; ++st) {
+        if (st + 2 < S::STEPS) request(st + 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const v8bf bb = __builtin_bit_cast(v8bf, q[st % 3][b]);
+            acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
+            acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) asm volatile("" : "+v"(acc[b][0]), "+v"(acc[b][1]));   // (half of the products would sink below the caller's wait)
+}
+
+// samples [lo, hi) of segment S: conv2, channel half hh, three tiles of positions and then the other three (all six at once
+// would take the registers of the weights)
+__device__ __forceinline__ void run_conv2(const Seg &S, int lo, int hi, const uint8_t *ring, uint8_t *ring2, const v8bf (&wa)[16][2],
+                                          const Counts &C, int lane, int hh)
 {
     const int n = lane & 15, kg = lane >> 4;
     const int ns = hi - lo;
     const v4f b0 = *reinterpret_cast<const v4f *>(S.b2 + 32 * hh + 8 * kg);
     const v4f b1 = *reinterpret_cast<const v4f *>(S.b2 + 32 * hh + 8 * kg + 4);
-    uint32_t base[3];
-    int pos[3];
+    // the first four tiles lie two rows of positions apart, the others anywhere (Shape::position)
+    uint32_t base[6];
+    int pos[6];
 #pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        const int p = pos[b] = S2::position(3 * ph + b, n);
-        base[b] = S2::at(2 * (20 * (p / 9) + (p % 9)), kg);
+    for (int t = 0; t < 6; ++t) {
+        pos[t] = t > 0 && t < 4 ? pos[0] + 18 * t : S2::position(t, n);
+        base[t] = t > 0 && t < 4 ? base[0] + t * 4 * S2::RB : S2::at(2 * (20 * (pos[t] / 9) + pos[t] % 9), kg);
     }
     for (int k = 0; k < ns; ++k) {
-        await_complete(strips + k);
+        await([&] { return complete(count_of(C.strips + k)); });
         const uint8_t *buf = ring + image_of_sample(k) * S2::SAMPLE;
-        v4f acc[3][2];
+        uint8_t *img = ring2 + image2_of_sample(k) * S3::SAMPLE + 64 * hh + 16 * kg;
+        bf16_t *y = S.y2 ? S.y2 + (long)(lo + k) * (81 * 64) + 32 * hh + 8 * kg : nullptr;   // uniform
 #pragma unroll
-        for (int b = 0; b < 3; ++b) acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0};
-        // the operands are requested two steps ahead of their matrix instructions
-        auto operand = [&](int st, int b) { return *reinterpret_cast<const uint4 *>(buf + base[b] + S2::at(20 * (st >> 2) + (st & 3), 0)); };
-        uint4 q[3][3];
+        for (int t0 = 0; t0 < 6; t0 += 3) {
+            v4f acc[3][2];
+            multiply<S2, 3>(acc, wa, [&](int b, int st) { return buf + base[t0 + b] + S2::at(20 * (st >> 2) + (st & 3), 0); });
+            if (t0 == 0) await([&] { return image2_free(k, k < NRING2 ? 0 : count_of(C.reads2 + k - NRING2)); });
+            else count_in(C.reads + k, lane);
 #pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) q[st][b] = operand(st, b);
-#pragma unroll
-        for (int st = 0; st < 16; ++st) {
-            if (st < 14)
-#pragma unroll
-                for (int b = 0; b < 3; ++b) q[(st + 2) % 3][b] = operand(st + 2, b);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const v8bf bb = __builtin_bit_cast(v8bf, q[st % 3][b]);
-                acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
-                acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
+            for (int b = 0; b < 3; ++b) {   // (lanes that share a position store the same bits)
+                const uint4 v = finished(acc[b][0], acc[b][1], b0, b1);
+                *reinterpret_cast<uint4 *>(img + S3::at(pos[t0 + b], 0)) = v;
+                if (y) *reinterpret_cast<uint4 *>(y + pos[t0 + b] * 64) = v;
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
-        count_in(reads + k, lane);
-        bf16_t *y = S.y2 + (long)(lo + k) * (81 * 64) + 32 * hh + 8 * kg;
+        count_in(C.halves + k, lane);
+    }
+}
+
+// ... conv3, two tiles and two tiles
+__device__ __forceinline__ void run_conv3(const Seg &S, int lo, int hi, const uint8_t *ring2, const v8bf (&wa)[18][2],
+                                          const Counts &C, int lane, int hh)
+{
+    const int n = lane & 15, kg = lane >> 4;
+    const int ns = hi - lo;
+    const v4f b0 = *reinterpret_cast<const v4f *>(S.b3 + 32 * hh + 8 * kg);
+    const v4f b1 = *reinterpret_cast<const v4f *>(S.b3 + 32 * hh + 8 * kg + 4);
+    uint32_t base[4];
+    int pos[4];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {   // (lanes that share a position store the same bits)
-            const v4f a0 = acc[b][0], a1 = acc[b][1];
-            const uint2 l2 = pack4(fmaxf(a0.x + b0.x, 0.f), fmaxf(a0.y + b0.y, 0.f), fmaxf(a0.z + b0.z, 0.f), fmaxf(a0.w + b0.w, 0.f));
-            const uint2 h2 = pack4(fmaxf(a1.x + b1.x, 0.f), fmaxf(a1.y + b1.y, 0.f), fmaxf(a1.z + b1.z, 0.f), fmaxf(a1.w + b1.w, 0.f));
-            *reinterpret_cast<uint4 *>(y + pos[b] * 64) = uint4{l2.x, l2.y, h2.x, h2.y};
+    for (int b = 0; b < 4; ++b) {
+        const int p = pos[b] = S3::position(b, n);
+        base[b] = S3::at(9 * (p / 7) + (p % 7), kg);
+    }
+    for (int k = 0; k < ns; ++k) {
+        await([&] { return complete2(count_of(C.halves + k)); });
+        const uint8_t *buf = ring2 + image2_of_sample(k) * S3::SAMPLE;
+        bf16_t *y = S.y3 + (long)(lo + k) * (49 * 64) + 32 * hh + 8 * kg;
+#pragma unroll
+        for (int t = 0; t < 4; t += 2) {
+            v4f acc[2][2];
+            multiply<S3, 2>(acc, wa, [&](int b, int st) { return buf + base[t + b] + S3::at(9 * (st / 6) + (st >> 1) % 3, 0) + (st & 1) * 64; });
+            if (t) count_in(C.reads2 + k, lane);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) *reinterpret_cast<uint4 *>(y + pos[t + b] * 64) = finished(acc[b][0], acc[b][1], b0, b1);
         }
     }
 }
 
-// samples [lo, hi) of segment S, producer wave w: strips w, w + 4, ... of the run's strip list.
-// R holds the pixels of strip w (requested by the caller); slots: the run's ring slots (ring mode).
+// samples [lo, hi) of segment S, producer wave w: its strips of the run's list.
+// R holds the pixels of the first (requested by the caller); slots: the run's ring slots (ring mode).
 __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8_t *xs, uint8_t *ring, const int *slots,
-                                             int *strips, int *reads, Pixels &R, int lane, int w)
+                                             const Counts &C, Pixels &R, int lane, int w)
 {
     const int n = lane & 15, kg = lane >> 4, oyl = n >> 2, q = n & 3;
     const int nstrips = UNITS * (hi - lo);
@@ -1906,14 +2008,14 @@ __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8
     const v4f b0 = *reinterpret_cast<const v4f *>(S.b1 + 8 * kg), b1 = *reinterpret_cast<const v4f *>(S.b1 + 8 * kg + 4);
     const uint32_t px = (uint32_t)(uintptr_t)(xs + (4 * oyl + 2 * kg) * 84 + 20 * q);
     auto slot_of = [&](int u) { return S.src.idx && u < nstrips ? slots[sample_of_strip(u)] : 0; };
-    int slot = slot_of(w + PRODUCERS);
-    for (int u = w; u < nstrips; u += PRODUCERS) {
+    int slot = slot_of(next_strip(first_strip(w)));
+    for (int u = first_strip(w), un; u < nstrips; u = un) {
         const int k = sample_of_strip(u), strip = u % UNITS;
         store_strip(xs, R, lane);            // (LDS operations of one wave complete in order)
         asm volatile("" ::: "memory");       // ... and the reads below are not ordered behind stores by the compiler
-        const int un = u + PRODUCERS;
+        un = next_strip(u);
         if (un < nstrips) load_strip(R, S.src, lo + un / UNITS, slot, un % UNITS, lane);
-        slot = slot_of(un + PRODUCERS);
+        slot = slot_of(next_strip(un));
         // a frame's six quads of pixels (see c1::conv1_fwd_units), two rows each, requested two frames ahead
         typedef uint32_t v2u __attribute__((ext_vector_type(2)));
         struct Bytes { v2u q[6]; };
@@ -1921,9 +2023,9 @@ __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8
         auto request = [&](int c) {
             const uint32_t addr = px + c * (c1::SROWS * 84);
             Bytes Q;
-#define C12_RD2(JJ) asm volatile("ds_read2_b32 %0, %1 offset0:%2 offset1:%3" : "=v"(Q.q[JJ]) : "v"(addr), "n"(JJ), "n"(JJ + 21));
-            C12_RD2(0) C12_RD2(1) C12_RD2(2) C12_RD2(3) C12_RD2(4) C12_RD2(5)
-#undef C12_RD2
+#define PIPE_RD2(JJ) asm volatile("ds_read2_b32 %0, %1 offset0:%2 offset1:%3" : "=v"(Q.q[JJ]) : "v"(addr), "n"(JJ), "n"(JJ + 21));
+            PIPE_RD2(0) PIPE_RD2(1) PIPE_RD2(2) PIPE_RD2(3) PIPE_RD2(4) PIPE_RD2(5)
+#undef PIPE_RD2
             return Q;
         };
         auto arrived = [&](Bytes &Q, bool more) {   // more: the six reads of another frame behind these
@@ -1969,7 +2071,7 @@ __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8
         }
 #pragma unroll
         for (int j = 0; j < 5; ++j) asm volatile("" : "+v"(acc[j][0]), "+v"(acc[j][1]));   // (half of the products would sink below the wait)
-        await_image(reads, k);
+        await([&] { return image_free(k, k < NRING ? 0 : count_of(C.reads + k - NRING)); });
         // bias, 1/255, ReLU, bf16: into the sample's image in the ring and, where kept, to memory
         uint8_t *img = ring + image_of_sample(k) * S2::SAMPLE + strip * (4 * S2::RB);
         uint8_t *yb = S.y1 ? reinterpret_cast<uint8_t *>(S.y1) + ((long)(lo + k) * 400 + 80 * strip) * 64 : nullptr;   // uniform
@@ -1985,13 +2087,13 @@ __device__ __forceinline__ void run_producer(const Seg &S, int lo, int hi, uint8
             *reinterpret_cast<uint4 *>(img + (j & 1 ? odd : even) + (j >> 1) * 64) = v;
             if (yb) *reinterpret_cast<uint4 *>(yb + yoff + j * 64) = v;
         }
-        count_in(strips + k, lane);
+        count_in(C.strips + k, lane);
     }
 }
 
 // Segment t owns workgroups [G t / nseg, G (t+1) / nseg); each of them an even share of its samples.
 // The host sizes the grid so that no share exceeds MAX_PER_WG.  Dynamic LDS: LDS_BYTES.
-__global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
+__global__ __launch_bounds__(512) void k_conv_fwd_pipe(Args A)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     int s = 0, w0 = 0, w1 = 1;
@@ -2006,14 +2108,15 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
     const int hi = (int)((long)((int)blockIdx.x - w0 + 1) * S.n / (w1 - w0));
     if (lo >= hi) return;   // the whole workgroup
     const int ns = hi - lo;
-    uint8_t *ring = lds + STRIPS_B;
-    int *slots = reinterpret_cast<int *>(lds + STRIPS_B + RING_B);
+    uint8_t *ring = lds + STRIPS_B, *ring2 = ring + RING_B;
+    int *slots = reinterpret_cast<int *>(ring2 + RING2_B);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     float *leafv = reinterpret_cast<float *>(slots + MAX_PER_WG);   // [MAX_PER_WG] leaf values, then the total
-    int *strips = reinterpret_cast<int *>(leafv + MAX_PER_WG + 4), *reads = strips + MAX_PER_WG;
-    if (tid < 2 * MAX_PER_WG) strips[tid] = 0;   // (both)
+    int *const counts = reinterpret_cast<int *>(leafv + MAX_PER_WG + 4);
+    const Counts C{counts, counts + MAX_PER_WG, counts + 2 * MAX_PER_WG, counts + 3 * MAX_PER_WG};
+    if (tid < COUNTS * MAX_PER_WG) counts[tid] = 0;
 
     // The slots of the run: drawn here, two per wave and walk, or copied from the index list.  Nothing but
     // the slot stands between a draw and the first pixel request, so the walk leaves the leaf's value and
@@ -2047,31 +2150,25 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
             misc::per_sample_emit(A.samp, lo + lane, slots[lane], leafv[MAX_PER_WG], leafv[lane]);
     };
 
-    if (wave >= 4) {
-        const int n = lane & 15, kg = lane >> 4, ph = wave & 1, hh = (wave >> 1) & 1;
-        // this wave's share of conv2's weights, straight into a-operand registers (row 8(n/4) + 4cb + n%4 of
-        // channel half hh, reduction elements 32st + 8kg .. +7); on its way while the slots are found
-        v8bf wa[16][2];
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const int chl = 8 * (n >> 2) + 4 * cb + (n & 3);
-                wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(S.w2 + (32 * hh + chl) * 512 + st * 32 + kg * 8));
-            }
-        fill_slots();
-        sync_lds();   // the slot table is complete, the counts are zero
-        if (wave == 4) publish_draws();   // the consumers wait for the first image anyway
-        run_consumer(S, lo, hi, ring, wa, strips, reads, lane, ph, hh);
+    fill_slots();
+    sync_lds();   // the slot table is complete, the counts are zero
+    if (wave >= PRODUCERS + CONSUMERS) {
+        v8bf wa[S3::STEPS][2];
+        load_weights<S3>(wa, S.w3, lane, wave & 1);
+        if (wave == PRODUCERS + CONSUMERS) publish_draws();   // (the first image is long in coming)
+        run_conv3(S, lo, hi, ring2, wa, C, lane, wave & 1);
+    } else if (wave >= PRODUCERS) {
+        v8bf wa[S2::STEPS][2];
+        load_weights<S2>(wa, S.w2, lane, wave & 1);
+        run_conv2(S, lo, hi, ring, ring2, wa, C, lane, wave & 1);
     } else {
-        fill_slots();
-        sync_lds();   // the slot table is complete, the counts are zero
         Pixels R;
-        if (wave < UNITS * ns) load_strip(R, S.src, lo + wave / UNITS, S.src.idx ? slots[wave / UNITS] : 0, wave % UNITS, lane);
-        run_producer(S, lo, hi, lds + wave * STRIP, ring, slots, strips, reads, R, lane, wave);
+        const int u = first_strip(wave);
+        if (u < UNITS * ns) load_strip(R, S.src, lo + sample_of_strip(u), S.src.idx ? slots[sample_of_strip(u)] : 0, u % UNITS, lane);
+        run_producer(S, lo, hi, lds + wave * STRIP, ring, slots, C, R, lane, wave);
     }
 }
-}  // namespace c12
+}  // namespace pipe
 
 // ===========================================================================
 // conv1, conv2 and conv3 forward in one launch (bf16), for as many samples as the launch-bound sizes have.
@@ -2085,7 +2182,7 @@ __global__ __launch_bounds__(512) void k_conv12_fwd(Args A)
 // that LDS serves together (Geo; at 77 12.9 -> 11.8).  16x16x32 instructions, transposed tiles:
 //   conv1   wave = every eighth tile of 16 pixels, all 32 channels: a pixel fragment serves two products
 //   conv2/3 wave = 16 channels, half of the tiles: the sum over the taps stays in one wave
-// k_conv12_fwd overlaps conv1 of one sample with conv2 of another and is as fast per sample once it runs, but it
+// pipe::k_conv_fwd_pipe overlaps conv1 of one sample with conv2 of another and is as fast per sample once it runs, but it
 // takes a second launch for conv3 and a longer start.
 // ===========================================================================
 namespace c123 {
@@ -2248,7 +2345,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
         for (int t = wave; t < G::T1; t += 8) {
             const int m = 16 * t + n16, mc = m < G::M1 ? m : G::M1 - 1;
             const int y = mc / 20, x = mc - 20 * y;
-            // A step takes four columns (4 xh ..) of the kernel rows 2 kg, 2 kg + 1 of a frame, as in k_conv12_fwd: the same
+            // A step takes four columns (4 xh ..) of the kernel rows 2 kg, 2 kg + 1 of a frame, as in pipe::run_producer: the same
             // sums in the same order, so both launches leave the same bits.  Two-address reads put such a pair into
             // four consecutive registers; they are invisible to the compiler's wait counting.
             typedef uint32_t v4u __attribute__((ext_vector_type(4)));

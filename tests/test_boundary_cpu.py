@@ -85,8 +85,8 @@ def test_product_does_not_touch_the_oracle():
 
 
 def test_fused_conv_ring_schedule_never_overwrites_an_unread_image(lib):
-    """The fused conv1 + conv2 forward launch (bf16) hands conv1's output to the conv2 waves through
-    a ring of LDS images, by counts of the strips of a sample and of its reads.  The library searches
+    """The fused conv forward launch (bf16) hands conv1's output to the conv2 waves, and conv2's to conv3's, through
+    rings of LDS images, by counts of the strips of a sample and of its reads.  The library searches
     on the host, with the same functions its kernel loops call (which strip belongs to which sample,
     which image holds a sample, when a sample may be read and an image written), all states that any
     order of the waves' steps can reach, for every run length a workgroup can get: a sample is

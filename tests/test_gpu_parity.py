@@ -673,10 +673,31 @@ def test_tree_without_mass_trains_on_nothing(dq):
         m.close()
 
 
+@pytest.mark.parametrize("E", [8, 257, 513, 8191])
+def test_pipelined_and_separate_conv_launches_agree_when_acting(dq, E):
+    """bf16: the conv layers of a forward pass as one launch of pipelined waves, against a launch per layer: the same bits.
+    8: a workgroup per sample, 257 and 513: one to three samples per workgroup, so that no ring of images comes round or each
+    only just; 8191: the longest runs, 31 and 32 samples."""
+    import os
+    print("case pipelined conv layers", E, flush=True)
+    obs = synth.frames(3, torch.arange(4 * E, device="cuda"), device="cuda").view(E, 4, 84, 84)
+    got = []
+    for least in ("1", "1000000000"):
+        os.environ["DQN_CONV12_MIN_SAMPLES"] = least
+        try:
+            m = dq.Dqn(dq.make_config(**dict(CONFIGS["dueling_ddqn"], max_batch=1, max_act_batch=E, precision=1)))
+        finally:
+            os.environ.pop("DQN_CONV12_MIN_SAMPLES", None)
+        got.append(m.act(obs, 0.0, 3, want_q=True))
+        torch.cuda.synchronize()
+        m.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("B", [5, 33, 512])
 def test_fused_and_separate_conv_launches_agree(dq, B):
-    """bf16: conv1 and conv2 of the forward pass run as one launch (conv1's output handed over in
-    LDS) from a handful of samples on, and as two launches below that or when
+    """bf16: the conv layers of the forward pass run as one launch (their output handed over in
+    LDS) from a handful of samples on, and as three launches below that or when
     DQN_CONV12_MIN_SAMPLES says so.  Both do the same arithmetic in the same order: two contexts over
     identical state, one on each path, must agree bit for bit -- in replay mode (the first forward
     kernel draws the transitions), on an explicit batch, and when acting.  B = 5: workgroups with a
