@@ -354,10 +354,11 @@ static_assert((net::F1W + SHADOW_AT) % 64 == 0 && (net::C2W + SHADOW_AT) % 64 ==
 gbf::bf16_t *shadow_of(dqn_ctx *c, int net) { return (gbf::bf16_t *)c->buf.shadow_bf16 + (net ? shadow_bytes(c->n) / 2 : 0) + SHADOW_AT; }
 // Behind the two copies lie the further forms of the conv weights, so that the buffer holds all that has to agree with the
 // parameters (the workspace nothing that outlives a call): both networks' in the order of the fused forward launch
-// (packed.h), and the online network's conv2 for the input gradient (misc::k_w2_transposed).
-size_t shadow_total_bytes(int64_t n) { return 2 * shadow_bytes(n) + align_up((2 * (size_t)sp::B_TOTAL + 64 * 512) * 2, 256); }
+// (packed.h), and the online network's conv2 and conv3 for the input gradients (misc::k_w2_transposed, packed.h).
+size_t shadow_total_bytes(int64_t n) { return 2 * shadow_bytes(n) + align_up((2 * (size_t)sp::B_TOTAL + 64 * 512 + sp::C3BACK_TOTAL) * 2, 256); }
 uint16_t *packed_of(dqn_ctx *c, int net_i) { return (uint16_t *)c->buf.shadow_bf16 + shadow_bytes(c->n) + (net_i ? sp::B_TOTAL : 0); }
 gbf::bf16_t *w2t_of(dqn_ctx *c) { return (gbf::bf16_t *)packed_of(c, 1) + sp::B_TOTAL; }
+uint16_t *w3back_of(dqn_ctx *c) { return packed_of(c, 1) + sp::B_TOTAL + 64 * 512; }
 static_assert(sp::B_TOTAL % 128 == 0, "256-byte aligned copies");
 // Every copy of a network's parameters, from the parameters
 void refresh_shadow(dqn_ctx *c, int net_i, hipStream_t st)
@@ -365,8 +366,9 @@ void refresh_shadow(dqn_ctx *c, int net_i, hipStream_t st)
     const float *theta = theta_of(c, net_i);
     launch(c, "to_bf16", st, [&] { misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta, (__hip_bfloat16 *)shadow_of(c, net_i), c->n); });
     launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i)); });
-    if (net_i == 0)
-        launch(c, "pack_conv", st, [&] { misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(theta + net::C2W, (__hip_bfloat16 *)w2t_of(c)); });
+    if (net_i != 0) return;
+    launch(c, "pack_conv", st, [&] { misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(theta + net::C2W, (__hip_bfloat16 *)w2t_of(c)); });
+    launch(c, "pack_conv", st, [&] { misc::k_pack_conv3_back<<<grid1(64 * 576, 256), 256, 0, st>>>(theta + net::C3W, w3back_of(c)); });
 }
 
 // Launch shapes of the conv1 forward kernel for `samples` samples (all passes), and whether a wave's
@@ -911,6 +913,7 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)shadow_of(c, 0) : nullptr;
     RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w2t_of(c) : nullptr;
     RA.packed = cfg.precision == 1 ? packed_of(c, 0) : nullptr;
+    RA.w3back = cfg.precision == 1 ? w3back_of(c) : nullptr;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
     if (last_part && last_part->on) launch(c, "rmsprop", st, [&] { k_rmsprop_pu<<<blk + 1, 256, 0, st>>>(RA, *last_part); });
     else launch(c, "rmsprop", st, [&] { misc::k_rmsprop<<<blk, 256, 0, st>>>(RA); });
@@ -1129,16 +1132,16 @@ __global__ __launch_bounds__(256) void k_fc1_head_bwd(gbf::DgradArgs DA, gbf::Wg
     }
 }
 
-// conv3's backward pair after workgroup 0
-__global__ __launch_bounds__(256) void k_conv3_bwd_pu(gbf::DgradArgs DA, gbf::WgradArgs WA, gbf::PairGrid P, SplitUpdate U)
+// conv3's backward pair after workgroup 0: nd workgroups of the input gradient, three per range of samples of the weight gradient
+__global__ __launch_bounds__(256, 2) void k_conv3_bwd_pu(gbf::c3b::Args A, SplitUpdate U)
 {
     using namespace gbf;
-    constexpr int LD = dgrad_lds<64, 64, true>(), LW = wgrad_lds<64, 64, true>();
-    __shared__ __attribute__((aligned(16))) bf16_t lds[LD > LW ? LD : LW];
+    static_assert(c3b::LDS >= misc::PU_LDS_WORDS * 4, "LDS");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[c3b::LDS];
     if (U.on && blockIdx.x == 0) return update_part(U, 1, reinterpret_cast<int *>(lds));
     const int id = (int)blockIdx.x - U.on;
-    if (id < P.nd) dgrad_tile<DConv3, 64, 64, 1, 1, true>(DA, tile_of(id, P.nd), P.dgx, P.dgz, lds);
-    else wgrad_tile<GConv3, 64, 64, 1, 1, true>(WA, tile_of(id - P.nd, P.nw), P.wgx, P.wgy, P.wgz, lds);
+    if (id < A.nd) c3b::dgrad_body(A, id, lds);
+    else c3b::wgrad_body(A, tile_of(id - A.nd, 3 * A.nsplit), reinterpret_cast<bf16_t *>(lds));
 }
 
 // conv2's backward pair after workgroup 0: the per-sample input gradient (nps workgroups) and the
@@ -1193,16 +1196,13 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
         launch(c, "fc1_bwd", st, [&] { k_fc1_head_bwd<<<P.nd + P.nw + nh + U.on, 256, 0, st>>>(D, G, P, head, U); });
     }
     {
-        DgradArgs D{d3, sh + net::C3W, act2, d2, B};
-        const int nd = (int)(((long)B * 81 + 63) / 64);
-        // four workgroups of this launch fit one CU: where fewer splits let the whole launch run in one
-        // round of workgroups, take fewer (B = 512: 41 instead of 56; 153.2 against 154.6 us/step)
-        int cap3 = (4 * c->num_cu - 1 - nd) / 9;
-        if (cap3 < 32 || cap3 > MAX_WSPLIT) cap3 = MAX_WSPLIT;
-        split_rows((long)B * 49, 9, cap3, 64, &rps, ns3);
-        WgradArgs G{d3, act2, w.gp3, B, rps, net::A2, net::L3N, 1.0f};
-        PairGrid P{nd, nd, 1, 9 * *ns3, 9, 1, *ns3};
-        launch(c, "conv3_bwd", st, [&] { k_conv3_bwd_pu<<<P.nd + P.nw + U.on, 256, 0, st>>>(D, G, P, U); });
+        // One workgroup per CU, half of them at most for the input gradient (a step of 512: 119.7 us; 170 and 48 ranges, or 256 and
+        // 64, two on some CUs, 121.7; 85 and 42 124.9; of 1000 180.2, 183.5, 185), and two samples or more to a range (of 77: 39
+        // ranges 58.5, 64 60.1: RMSProp reads a partial sum per range)
+        const int nd = std::max(1, std::min(B, c->num_cu / 2));
+        *ns3 = std::max(1, std::min({(B + 1) / 2, MAX_WSPLIT, (c->num_cu - U.on - nd) / 3}));
+        const c3b::Args A{d3, act2, w3back_of(c), d2, w.gp3, B, nd, *ns3};
+        launch(c, "conv3_bwd", st, [&] { k_conv3_bwd_pu<<<A.nd + 3 * A.nsplit + U.on, 256, 0, st>>>(A, U); });
     }
     {   // conv2: the per-sample input gradient, at most one workgroup per CU, beside the tiled weight gradient
         dps::Args P{d2, sh + net::C2W, act1, d1, B};

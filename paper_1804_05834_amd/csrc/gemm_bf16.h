@@ -2794,4 +2794,205 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
         }
 }
 }  // namespace dps
+
+// ===========================================================================
+// conv3 backward (3x3 stride 1, 9x9x64 -> 7x7x64), both gradients in one launch out of whole samples in LDS.
+//
+// What bounds it is latency, not work: at a batch of 512 both gradients are 2 us of matrix instructions if spread over all
+// CUs.  As 64x64 im2col tiles, nine or ten stages of 0.8 to 1.2 us each, every pixel was fetched once per tap
+// (58 MB out of the L2s for the weight gradient) and the launch took 15.3 us at a batch of 512.  Here a sample is staged once
+// and every tap reads it at another offset (a step of 512 129.7 -> 126.2 us, of 77 61.4 -> 58.3):
+//   input gradient : a workgroup per CU at most, its samples one after the other; the weights in registers (from a copy in the
+//                    order of the operands, packed.h), dY inside a border of two zero pixels, in two images.
+//   weight gradient: a workgroup takes one kernel row (64 x 192 outputs) over a range of samples; dY and the seven
+//                    pixel rows under it in LDS, two samples further on their way.
+// ===========================================================================
+namespace c3b {
+using ps::u32x4;
+using dps::IMG;
+using dps::PIX;
+using dps::ROW;
+constexpr int OUT = 49 * 64, IN = 81 * 64;                   // elements of a sample: dY; X and dX
+constexpr int YPIECES = OUT / 8, XPIECES = 63 * 8;           // 16-byte pieces: dY 392, seven pixel rows 504
+constexpr int ZERO_ROW = 63;                                 // of the weight gradient's X: what positions past the 49th read
+constexpr int STAGE = 2 * 64 * 64;                           // elements of a sample there: 64 rows of dY, 64 of X
+constexpr int LDS = std::max(2 * IMG, 2 * STAGE * 2);        // 39,424 bytes
+
+struct Args {
+    const bf16_t *dy;    // [B][7][7][64]
+    const bf16_t *x;     // [B][9][9][64], conv2's output after ReLU
+    const uint16_t *w;   // the weights in the order of sp::packed_conv3_back_at
+    bf16_t *dx;          // [B][9][9][64]
+    float *part;         // [nsplit][64 * 576 + 64]
+    int B;
+    int nd;              // workgroups of the input gradient
+    int nsplit;          // ranges of samples of the weight gradient, B at most
+};
+
+// Samples [bid * B / nd, (bid + 1) * B / nd).  Wave (ph, hh): tiles 3 ph .. + 2 of sixteen pixels, channels 32 hh .. + 31.
+__device__ __forceinline__ void dgrad_body(const Args &A, int bid, uint8_t *lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ph = wave & 1, hh = wave >> 1;
+    const int g0 = (int)((long)bid * A.B / A.nd), g1 = (int)((long)(bid + 1) * A.B / A.nd);
+    if (g0 >= g1) return;
+    u32x4 r0, r1;
+    auto load_dy = [&](int g) {
+        const u32x4 *p = reinterpret_cast<const u32x4 *>(A.dy + (long)g * OUT);
+        r0 = p[tid]; r1 = p[tid < YPIECES - 256 ? tid + 256 : YPIECES - 1];
+    };
+    load_dy(g0);
+    v8bf wa[18][2];   // step 2 tap + half of dY's channels; rows 8 (i / 4) + 4 cb + i % 4 of the wave's channels
+#pragma unroll
+    for (int st = 0; st < 18; ++st)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+            wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(A.w + ((2 * hh + cb) * 18 + st) * sp::FRAG + lane * 8));
+    for (int i = tid; i < 2 * IMG / 16; i += 256) *reinterpret_cast<u32x4 *>(lds + i * 16) = u32x4{0, 0, 0, 0};
+    // pixel (y, x) takes dY position (y - p, x - q) for tap (p, q): image pixel (y - p + 2, x - q + 2)
+    uint32_t base[3];
+    int pos[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        pos[b] = ps::Shape<ps::G2>::position(3 * ph + b, n);   // 9 x 9 pixels in six tiles
+        base[b] = pos[b] / 9 * ROW + pos[b] % 9 * PIX + kg * 16;
+    }
+    sync_lds();   // the images are cleared
+    for (int g = g0, s = 0; g < g1; ++g, s ^= 1) {
+        uint8_t *img = lds + s * IMG;   // (last read two samples ago; every wave has passed a barrier since)
+        auto put = [&](int t, u32x4 v) {
+            const int q = t >> 3;
+            *reinterpret_cast<u32x4 *>(img + (q / 7 + 2) * ROW + (q % 7 + 2) * PIX + (t & 7) * 16) = v;
+        };
+        put(tid, r0);
+        if (tid < YPIECES - 256) put(tid + 256, r1);
+        load_dy(min(g + 1, g1 - 1));   // the last one repeats the last sample
+        const long o = (long)g * IN + 32 * hh + 8 * kg;
+        uint4 mk[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) mk[b] = *reinterpret_cast<const uint4 *>(A.x + o + pos[b] * 64);
+        sync_lds();
+        auto operand = [&](int b, int st) {
+            const int tap = st >> 1;
+            return *reinterpret_cast<const uint4 *>(img + base[b] + (2 - tap / 3) * ROW + (2 - tap % 3) * PIX + (st & 1) * 64);
+        };
+        v4f acc[3][2];
+        uint4 cur[3], nxt[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) { acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0}; cur[b] = operand(b, 0); }
+#pragma unroll
+        for (int st = 0; st < 18; ++st) {
+            if (st + 1 < 18) {
+#pragma unroll
+                for (int b = 0; b < 3; ++b) nxt[b] = operand(b, st + 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const v8bf bb = __builtin_bit_cast(v8bf, cur[b]);
+                acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
+                acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) cur[b] = nxt[b];
+        }
+        // (lanes that share a pixel store the same bits)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) *reinterpret_cast<uint4 *>(A.dx + o + pos[b] * 64) = dps::masked8(mk[b], acc[b][0], acc[b][1]);
+    }
+}
+
+// Tile t: kernel row t % 3 over range t / 3 of the samples.  Wave (oh, kh): output channels 32 oh .. + 31, three of the kernel
+// row's six blocks of 32 columns.  A sample's 49 positions are four reduction steps of 16; the last fifteen are rows of zeros on
+// both sides.
+__device__ __forceinline__ void wgrad_body(const Args &A, int t, bf16_t *lds)
+{
+    typedef __attribute__((address_space(3))) v4s *lds_v4s;
+    using Tr = TrTile<64>;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), oh = wave & 1, kh = wave >> 1;
+    const int range = t / 3, ty = t % 3;
+    const int n0 = (int)((long)range * A.B / A.nsplit), n1 = (int)((long)(range + 1) * A.B / A.nsplit);
+    struct Raw { u32x4 y0, y1, x0, x1; };
+    auto load = [&](Raw &R, int g) {   // the last loads repeat the last sample
+        g = min(g, n1 - 1);
+        const u32x4 *y = reinterpret_cast<const u32x4 *>(A.dy + (long)g * OUT);
+        const u32x4 *x = reinterpret_cast<const u32x4 *>(A.x + (long)g * IN + ty * (9 * 64));
+        R.y0 = y[tid]; R.y1 = y[tid < YPIECES - 256 ? tid + 256 : YPIECES - 1];
+        R.x0 = x[tid]; R.x1 = x[tid < XPIECES - 256 ? tid + 256 : XPIECES - 1];
+    };
+    constexpr int AHEAD = 2;   // (four, and dY of the input gradient two ahead: 87.8 -> 89.4 us for a step of 256, equal at 512)
+    Raw R[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) load(R[k], n0 + k);
+    for (int i = tid; i < 2 * 16 * 8; i += 256) {   // rows 49 .. 63 of dY, row 63 of X, in both buffers
+        const int r = (i >> 3) & 15;
+        bf16_t *b = lds + (i >> 7) * STAGE + (r ? (48 + r) * 64 : 64 * 64 + ZERO_ROW * 64);
+        *reinterpret_cast<u32x4 *>(b + (i & 7) * 8) = u32x4{0, 0, 0, 0};
+    }
+    const int trow = 8 * h + (s16 >> 2), tcol = 16 * half + 4 * (s16 & 3);
+    const int yo = Tr::at(trow, oh * 32 + tcol);
+    int xo[4][2][3];   // step, four rows further, block
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int p = 16 * k + trow + 4 * f, blk = 3 * kh + i;
+                xo[k][f][i] = 64 * 64 + Tr::at(p < 49 ? p + 2 * (p / 7) + (blk >> 1) : ZERO_ROW, (blk & 1) * 32 + tcol);
+            }
+    const bool do_bias = ty == 0 && kh == 0;
+    v16f acc[3] = {v16f{0}, v16f{0}, v16f{0}}, accb = {0};
+    v8bf ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    const int yr = tid >> 3, yc = (tid & 7) * 8, at = Tr::at(yr, yc);   // (rows 32 apart are permuted alike)
+
+    auto sample = [&](Raw &R, bf16_t *b, int g) {
+        *reinterpret_cast<u32x4 *>(b + at) = R.y0;
+        if (tid < YPIECES - 256) *reinterpret_cast<u32x4 *>(b + 32 * 64 + at) = R.y1;
+        *reinterpret_cast<u32x4 *>(b + 64 * 64 + at) = R.x0;
+        if (tid < XPIECES - 256) *reinterpret_cast<u32x4 *>(b + 96 * 64 + at) = R.x1;
+        load(R, g + AHEAD);
+        sync_lds();   // the buffer is complete; every wave is past the previous sample, which read the other one
+        auto operands = [&](int k, v8bf &fa, v8bf (&fb)[3]) {
+            fa = frag_tr(b + yo + 16 * k * 64, 64);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(b + xo[k][0][i]));
+                const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(b + xo[k][1][i]));
+                typedef short v8s __attribute__((ext_vector_type(8)));
+                const v8s r = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                fb[i] = __builtin_bit_cast(v8bf, r);
+            }
+        };
+        v8bf fa[2], fb[2][3];
+        operands(0, fa[0], fb[0]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (k + 1 < 4) operands(k + 1, fa[(k + 1) & 1], fb[(k + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) acc[i] = mfma(fa[k & 1], fb[k & 1][i], acc[i]);
+            if (do_bias) accb = mfma(fa[k & 1], ones, accb);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    for (int g = n0; g < n1; g += AHEAD)
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k)
+            if (g + k < n1) sample(R[k], lds + (k & 1) * STAGE, g + k);
+
+    float *part = A.part + (long)range * (64 * 576 + 64);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int o = 32 * oh + 8 * (r / 4) + 4 * h + (r % 4);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) part[(long)o * 576 + ty * 192 + (3 * kh + i) * 32 + li] = acc[i][r];
+        if (do_bias && li == 0) part[64 * 576 + o] = accb[r];
+    }
+}
+}  // namespace c3b
 }  // namespace gbf

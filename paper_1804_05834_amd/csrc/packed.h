@@ -39,6 +39,15 @@ __host__ __device__ __forceinline__ int packed_bf16_at(long i)
     }
     return -1;
 }
+// conv3's weights for its input gradient (gbf::c3b): fragments of the same instruction, [16 input channels][step], a step being
+// half the output channels of a tap.  Row i of fragment group 2 h + c is input channel 32 h + 8 (i / 4) + 4 c + i % 4, so that a
+// lane that holds rows 4g .. 4g+3 of both groups holds eight consecutive channels.
+constexpr int C3BACK_TOTAL = 4 * 18 * FRAG;
+__host__ __device__ __forceinline__ int packed_conv3_back_at(int t)   // element t of conv3.W
+{
+    const int o = t / 576, tap = t % 576 >> 6, c = t & 63;
+    return ((2 * (c >> 5) + ((c >> 2) & 1)) * 18 + 2 * tap + (o >> 5)) * FRAG + (4 * ((c >> 3) & 3) + (c & 3) + 16 * ((o >> 3) & 3)) * 8 + (o & 7);
+}
 __device__ __forceinline__ void store_packed_bf16(uint16_t *packed, long i, float x)
 {
     const int at = packed_bf16_at(i);

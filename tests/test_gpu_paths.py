@@ -102,6 +102,27 @@ def test_bf16_step_where_the_launches_change(dq, orc, prec, B):
     _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41, tol=TOL_BF16, prec=1)
 
 
+@pytest.mark.parametrize("B,cus", [(1, 2), (2, 9), (5, 7), (75, 9), (127, 40), (129, 100)])
+def test_conv3_backward_over_ranges_of_samples(dq, monkeypatch, B, cus):
+    """bf16: conv3's gradients with one to 37 samples in a workgroup (input gradient) or a range (weight gradient) against one or
+    two: the same activations, and sums of the same products in another order, to the fp32 path's tolerance."""
+    print("case conv3 backward", B, cus, flush=True)
+    batch = tuple(dev(t) for t in synth.batch(29, B, 18))
+    got = []
+    for n in (None, cus):
+        if n:
+            monkeypatch.setenv("DQN_COMPUTE_UNITS", str(n))
+        m = dq.Dqn(dq.make_config(max_batch=B, precision=1, seed=7, **CONFIGS["dueling_ddqn"]))
+        m.train_step(B, batch)
+        got.append((m.get_activations(3, B), m.get_params(2).cpu().numpy()))
+        m.close()
+    assert torch.equal(got[0][0], got[1][0])
+    lo = 0
+    for name, n in (("conv1", 8224), ("conv2", 32832), ("conv3", 36928)):
+        assert relerr(got[1][1][lo:lo + n], got[0][1][lo:lo + n]) <= TOL, name
+        lo += n
+
+
 @pytest.mark.parametrize("n", [35, 42])
 def test_fp32_step_activations_are_those_of_the_separate_launches(dq, n):
     """A batch of 43 runs the layers of s as launches of their own, its first n rows alone as units of one launch: the
