@@ -354,21 +354,17 @@ static_assert((net::F1W + SHADOW_AT) % 64 == 0 && (net::C2W + SHADOW_AT) % 64 ==
 gbf::bf16_t *shadow_of(dqn_ctx *c, int net) { return (gbf::bf16_t *)c->buf.shadow_bf16 + (net ? shadow_bytes(c->n) / 2 : 0) + SHADOW_AT; }
 // Behind the two copies lie the further forms of the conv weights, so that the buffer holds all that has to agree with the
 // parameters (the workspace nothing that outlives a call): both networks' in the order of the fused forward launch
-// (packed.h), and the online network's conv2 and conv3 for the input gradients (misc::k_w2_transposed, packed.h).
-size_t shadow_total_bytes(int64_t n) { return 2 * shadow_bytes(n) + align_up((2 * (size_t)sp::B_TOTAL + 64 * 512 + sp::C3BACK_TOTAL) * 2, 256); }
+// (packed.h), and the online network's conv2 and conv3 for the input gradients.
+size_t shadow_total_bytes(int64_t n) { return 2 * shadow_bytes(n) + align_up((2 * (size_t)sp::B_TOTAL + sp::BACK_TOTAL) * 2, 256); }
 uint16_t *packed_of(dqn_ctx *c, int net_i) { return (uint16_t *)c->buf.shadow_bf16 + shadow_bytes(c->n) + (net_i ? sp::B_TOTAL : 0); }
-gbf::bf16_t *w2t_of(dqn_ctx *c) { return (gbf::bf16_t *)packed_of(c, 1) + sp::B_TOTAL; }
-uint16_t *w3back_of(dqn_ctx *c) { return packed_of(c, 1) + sp::B_TOTAL + 64 * 512; }
+uint16_t *back_of(dqn_ctx *c) { return packed_of(c, 1) + sp::B_TOTAL; }
 static_assert(sp::B_TOTAL % 128 == 0, "256-byte aligned copies");
 // Every copy of a network's parameters, from the parameters
 void refresh_shadow(dqn_ctx *c, int net_i, hipStream_t st)
 {
     const float *theta = theta_of(c, net_i);
     launch(c, "to_bf16", st, [&] { misc::k_to_bf16<<<grid1(c->n, 256), 256, 0, st>>>(theta, (__hip_bfloat16 *)shadow_of(c, net_i), c->n); });
-    launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i)); });
-    if (net_i != 0) return;
-    launch(c, "pack_conv", st, [&] { misc::k_w2_transposed<<<grid1(64 * 512, 256), 256, 0, st>>>(theta + net::C2W, (__hip_bfloat16 *)w2t_of(c)); });
-    launch(c, "pack_conv", st, [&] { misc::k_pack_conv3_back<<<grid1(64 * 576, 256), 256, 0, st>>>(theta + net::C3W, w3back_of(c)); });
+    launch(c, "pack_conv", st, [&] { sp::k_pack_conv_bf16<<<grid1(net::F1W, 256), 256, 0, st>>>(theta, packed_of(c, net_i), net_i == 0 ? back_of(c) : nullptr); });
 }
 
 // Launch shapes of the conv1 forward kernel for `samples` samples (all passes), and whether a wave's
@@ -911,9 +907,8 @@ void launch_rmsprop(dqn_ctx *c, unsigned layers, int ns1, int ns2, int ns3, hipS
     for (; k < 5; ++k) RA.seg[k].block_begin = 0x7fffffff;  // never selected
     RA.theta = c->theta; RA.v = c->rms_v; RA.m = c->rms_m; RA.g = c->grads;
     RA.shadow = cfg.precision == 1 ? (__hip_bfloat16 *)shadow_of(c, 0) : nullptr;
-    RA.w2t = cfg.precision == 1 ? (__hip_bfloat16 *)w2t_of(c) : nullptr;
     RA.packed = cfg.precision == 1 ? packed_of(c, 0) : nullptr;
-    RA.w3back = cfg.precision == 1 ? w3back_of(c) : nullptr;
+    RA.back = cfg.precision == 1 ? back_of(c) : nullptr;
     RA.lr = cfg.lr; RA.rho = cfg.rms_decay; RA.eps = cfg.rms_eps;
     if (last_part && last_part->on) launch(c, "rmsprop", st, [&] { k_rmsprop_pu<<<blk + 1, 256, 0, st>>>(RA, *last_part); });
     else launch(c, "rmsprop", st, [&] { misc::k_rmsprop<<<blk, 256, 0, st>>>(RA); });
@@ -1132,16 +1127,16 @@ __global__ __launch_bounds__(256) void k_fc1_head_bwd(gbf::DgradArgs DA, gbf::Wg
     }
 }
 
-// conv3's backward pair after workgroup 0: nd workgroups of the input gradient, three per range of samples of the weight gradient
-__global__ __launch_bounds__(256, 2) void k_conv3_bwd_pu(gbf::c3b::Args A, SplitUpdate U)
+// conv3's backward pair after workgroup 0: the input gradient's workgroups, then the weight gradient's
+__global__ __launch_bounds__(256, 2) void k_conv3_bwd_pu(gbf::c3b::Args DA, gbf::WgradArgs WA, int ns, SplitUpdate U)
 {
     using namespace gbf;
-    static_assert(c3b::LDS >= misc::PU_LDS_WORDS * 4, "LDS");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[c3b::LDS];
+    constexpr int L = std::max({c3b::LDS, wgrad_lds<64, 192, true>() * 2, misc::PU_LDS_WORDS * 4});
+    __shared__ __attribute__((aligned(16))) uint8_t lds[L];
     if (U.on && blockIdx.x == 0) return update_part(U, 1, reinterpret_cast<int *>(lds));
     const int id = (int)blockIdx.x - U.on;
-    if (id < A.nd) c3b::dgrad_body(A, id, lds);
-    else c3b::wgrad_body(A, tile_of(id - A.nd, 3 * A.nsplit), reinterpret_cast<bf16_t *>(lds));
+    if (id < DA.nd) c3b::dgrad_body(DA, id, lds);
+    else wgrad_tile<GConv3, 64, 192, 1, 3, true>(WA, tile_of(id - DA.nd, 3 * ns), 3, 1, ns, reinterpret_cast<bf16_t *>(lds));
 }
 
 // conv2's backward pair after workgroup 0: the per-sample input gradient (nps workgroups) and the
@@ -1186,7 +1181,6 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
     bf16_t *act1 = (bf16_t *)w.act1, *act2 = (bf16_t *)w.act2, *act3 = (bf16_t *)w.act3;
     bf16_t *dh = (bf16_t *)w.dh, *d3 = (bf16_t *)w.d3, *d2 = (bf16_t *)w.d2, *d1 = (bf16_t *)w.d1;
     const bf16_t *sh = shadow_of(c, 0);
-    int rps;
     {
         DgradArgs D{dh, sh + net::F1W, act3, d3, B};
         WgradArgs G{dh, act3, c->gp4, B, (B + 63) / 64 * 64, net::A3, 0, 1.0f};
@@ -1195,14 +1189,21 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
         const int nh = c->R * 16;
         launch(c, "fc1_bwd", st, [&] { k_fc1_head_bwd<<<P.nd + P.nw + nh + U.on, 256, 0, st>>>(D, G, P, head, U); });
     }
+    int rps;
     {
-        // One workgroup per CU, half of them at most for the input gradient (a step of 512: 119.7 us; 170 and 48 ranges, or 256 and
-        // 64, two on some CUs, 121.7; 85 and 42 124.9; of 1000 180.2, 183.5, 185), and two samples or more to a range (of 77: 39
-        // ranges 58.5, 64 60.1: RMSProp reads a partial sum per range)
-        const int nd = std::max(1, std::min(B, c->num_cu / 2));
-        *ns3 = std::max(1, std::min({(B + 1) / 2, MAX_WSPLIT, (c->num_cu - U.on - nd) / 3}));
-        const c3b::Args A{d3, act2, w3back_of(c), d2, w.gp3, B, nd, *ns3};
-        launch(c, "conv3_bwd", st, [&] { k_conv3_bwd_pu<<<A.nd + 3 * A.nsplit + U.on, 256, 0, st>>>(A, U); });
+        // The splits of the 64 x 64 tiles that were here before, four to a CU, and with them their bits: another order of the same
+        // sums moves a gradient by 1e-7, that rounded weights, those ReLU decisions, and after four steps the gradients are 2e-2 apart
+        // (a batch of 77 or 512).
+        int cap3 = (4 * c->num_cu - 1 - (int)(((long)B * 81 + 63) / 64)) / 9;
+        if (cap3 < 32 || cap3 > MAX_WSPLIT) cap3 = MAX_WSPLIT;
+        split_rows((long)B * 49, 9, cap3, 64, &rps, ns3);
+        // The input gradient takes the CUs that the weight gradient's tiles leave, so that every workgroup has one, but no more than
+        // the tiles, which end last, can spare of the L2s (steps of 256, 512, 1000: 89.2, 120.9, 185.1 us with 108, 100 and 90
+        // workgroups, 89.8, 123.3, 189.8 with 64, 90.1, 121.2, 187.2 with 128)
+        const int nd = std::min({B, std::max(1, 2 * c->num_cu / 5), std::max({1, c->num_cu / 4, c->num_cu - U.on - 3 * *ns3})});
+        const WgradArgs G{d3, act2, w.gp3, B, rps, net::A2, net::L3N, 1.0f};
+        const c3b::Args D{d3, act2, back_of(c) + sp::C2BACK_TOTAL, d2, B, nd};
+        launch(c, "conv3_bwd", st, [&] { k_conv3_bwd_pu<<<nd + 3 * *ns3 + U.on, 256, 0, st>>>(D, G, *ns3, U); });
     }
     {   // conv2: the per-sample input gradient, at most one workgroup per CU, beside the tiled weight gradient
         dps::Args P{d2, sh + net::C2W, act1, d1, B};
@@ -1215,7 +1216,7 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
             // tiles fewer, and the launch runs in one round of workgroups at B = 512
             const int nps = std::min({B, c->num_cu, MAX_WSPLIT1});
             const int nw2 = 4 * gz;
-            dps::FusedArgs F{P, c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, w2t_of(c)};
+            dps::FusedArgs F{P, c1::Src{ps.x, ps.xs, ps.idx, (long)c->cfg.replay_capacity, ps.shift, (int)c->sub}, w.gp1, back_of(c)};
             launch(c, "conv21_bwd", st, [&] {
                 k_conv21_bwd_pu<<<nps + nw2 + U.on, 256, dps::FUSED_LDS, st>>>(F, G, nps, nw2, 4, 1, gz, U);
             });

@@ -120,8 +120,8 @@ __device__ __forceinline__ v8bf frag_tr(const bf16_t *p, int ld)
 // that those four lie in all 64 banks side by side.  (Rows padded by 16 bytes instead: 1.6 times the cycles per read
 // with 64 columns, 3 times with 128.)  Rows four apart are permuted alike.
 template <int COLS> struct TrTile {
-    static_assert(COLS == 64 || COLS == 128, "two or four blocks");
-    static __device__ __forceinline__ int block(int row, int blk) { return blk ^ (COLS == 64 ? (row >> 1) & 1 : row & 3); }
+    static_assert(COLS == 64 || COLS == 128 || COLS == 192, "two, four or six blocks");
+    static __device__ __forceinline__ int block(int row, int blk) { return blk ^ (COLS == 128 ? row & 3 : (row >> 1) & 1); }
     static __device__ __forceinline__ int at(int row, int col) { return row * COLS + block(row, col >> 5) * 32 + (col & 31); }
 };
 
@@ -652,12 +652,14 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
     constexpr int WAVES_M = BMO / (32 * WM), WAVES_N = BNK / (32 * WN), T = WAVES_M * WAVES_N * 64;
     constexpr int LDY = BMO, LDX = BNK;
     constexpr int YCH = BMO / 8, XCH = BNK / 8;          // 16-byte chunks per tile row
-    constexpr int YR = T / YCH, XR = T / XCH;            // rows filled per pass
-    constexpr int NY = (BK + YR - 1) / YR, NX = (BK + XR - 1) / XR;
-    static_assert(YR % 4 == 0 && XR % 4 == 0, "rows permuted alike");
+    constexpr int YR = T / YCH;                          // rows filled per pass
+    constexpr int NY = (BK + YR - 1) / YR;
+    constexpr bool WHOLE = T % XCH == 0;                 // a pass fills whole rows of X: a thread has one column
+    constexpr int XR = T / XCH, NX = WHOLE ? (BK + XR - 1) / XR : BK * XCH / T, NC = WHOLE ? 1 : NX;
+    static_assert(YR % 4 == 0 && (WHOLE ? XR % 4 == 0 : BK * XCH % T == 0), "rows permuted alike");
     using in_t = typename in_type<G>::t;
     constexpr int NBUF = DB ? 2 : 1;
-    constexpr bool ACC2 = DB && WM * WN <= 2;   // two alternating accumulators per output block
+    constexpr bool ACC2 = DB && WM * WN <= 3;   // two alternating accumulators per output block
     bf16_t(*Ys2)[BK * LDY] = reinterpret_cast<bf16_t(*)[BK * LDY]>(lds);
     bf16_t(*Xs2)[BK * LDX] = reinterpret_cast<bf16_t(*)[BK * LDX]>(lds + NBUF * BK * LDY);
 
@@ -674,9 +676,15 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
     const in_t *x = static_cast<const in_t *>(A.x);
 
     const int yr = tid / YCH, yc = (tid % YCH) * 8;
-    const int xr = tid / XCH, xc = (tid % XCH) * 8;
-    const int xko = G::k_off(kc0 + xc);
-    const int yst = TrTile<BMO>::at(yr, yc), xst = TrTile<BNK>::at(xr, xc);
+    const int yst = TrTile<BMO>::at(yr, yc);
+    int xr[NC], xko[NC], xst[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int q = tid + i * T, xc = (q % XCH) * 8;
+        xr[i] = q / XCH;
+        xko[i] = G::k_off(kc0 + xc);
+        xst[i] = TrTile<BNK>::at(xr[i], xc);
+    }
     uint4 ry[NY], rx[NX];
     auto gload = [&](int mb) {
 #pragma unroll
@@ -686,8 +694,8 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-            int r = xr + i * XR, m = mb + r;
-            rx[i] = (r < BK && m < mend) ? ld8(x + G::row_off(m, A.xs) + xko) : uint4{0, 0, 0, 0};
+            int r = WHOLE ? xr[0] + i * XR : xr[i % NC], m = mb + r;
+            rx[i] = (r < BK && m < mend) ? ld8(x + G::row_off(m, A.xs) + xko[i % NC]) : uint4{0, 0, 0, 0};
         }
     };
     auto sstore = [&](int buf) {
@@ -699,8 +707,8 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-            int r = xr + i * XR;
-            if (r < BK) *reinterpret_cast<uint4 *>(&Xs[i * XR * LDX + xst]) = rx[i];
+            if (!WHOLE) *reinterpret_cast<uint4 *>(&Xs[xst[i % NC]]) = rx[i];
+            else if (xr[0] + i * XR < BK) *reinterpret_cast<uint4 *>(&Xs[i * XR * LDX + xst[0]]) = rx[i];
         }
     };
 
@@ -2637,16 +2645,15 @@ constexpr int PS_LDS = IMG + 32 * W2PITCH;   // bytes
 // backward pass of the Section 2.2 loss): conv1's dY is needed by nothing but conv1's weight gradient,
 // sample by sample, so the workgroup that forms it keeps it in LDS, in the layout the weight gradient
 // stages it in, and goes on to the weight gradient of the same sample (c1::conv1_wgrad_block's loop,
-// both channel pairs one after the other, the frames read from the ring or the explicit states while
-// the input gradient is computed).  conv1's dY is never written to memory, and the launch of conv1's
-// weight gradient, with its hand-over, is gone.  Workgroup b takes samples b, b + nblocks, ... and
+// both channel pairs one after the other, the frames read from the ring or the explicit states).  conv1's dY is never written to
+// memory, and the launch of conv1's weight gradient, with its hand-over, is gone.  Workgroup b takes samples b, b + nblocks, ... and
 // writes ONE partial of conv1's weight gradient: the same samples in the same order as split b of
 // c1::k_conv1_wgrad with nblocks splits, so the partials have the same bits.
 struct FusedArgs {
     Args d;           // dx is not used
     c1::Src src;      // where the frames of sample n come from
     float *part1;     // [nblocks][32*256 + 32]
-    const bf16_t *w2t;  // conv2's weights as [tap][channel in][channel out]
+    const uint16_t *w2;  // conv2's weights in the order of sp::packed_conv2_back_at
 };
 constexpr int FUSED_DYS = 400 * c1::LDY1 * 2;             // 25,600 bytes: conv1's dY as the weight gradient reads it
 constexpr int FUSED_XIN = 2 * c1::FR * 2;                 // 28,224 bytes: two frames as bf16
@@ -2668,22 +2675,16 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
         r0 = p[tid]; r1 = p[tid + 256]; r2 = p[tid < 136 ? tid + 512 : 647];
     };
     load_dy(bid);
-    int slot_g = c1::sample_slot(F.src, bid);
+    int slot_n = c1::sample_slot(F.src, bid);
+    const bf16_t *const xg0 = A.xact + 8 * kg;
     for (int i = tid; i < IMG / 16; i += 256) *reinterpret_cast<u32x4 *>(img + i * 16) = u32x4{0, 0, 0, 0};
-    // conv2's weights, wa[2 tap + co half][ci block] as in conv2_dgrad_ps_body, straight from the copy that
-    // keeps the output channels next to each other: the eight reduction elements of a lane are 16 bytes
+    // conv2's weights, wa[2 tap + co half][ci block] as in conv2_dgrad_ps_body, from a copy in the order of the operands
     v8bf wa[8][2];
 #pragma unroll
-    for (int tap = 0; tap < 4; ++tap)
+    for (int st = 0; st < 8; ++st)
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const int ky = py + 2 * (tap >> 1), kx = px + 2 * (tap & 1);
-                const int ci = 8 * (n >> 2) + 4 * cb + (n & 3);
-                wa[2 * tap + half][cb] = __builtin_bit_cast(
-                    v8bf, *reinterpret_cast<const uint4 *>(F.w2t + (((ky * 4 + kx) * 32 + ci) * 64 + 32 * half + 8 * kg)));
-            }
+        for (int cb = 0; cb < 2; ++cb)
+            wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(F.w2 + (((2 * py + px) * 8 + st) * 2 + cb) * sp::FRAG + lane * 8));
     // this lane's place of tile b in the wave's parity class: its dY corner in the image; its pixel
     auto base_of = [&](int b) { const Place P = place_of(b, n); return (uint32_t)(P.y * ROW + P.x * PIX + kg * 16); };
     auto pixel_of = [&](int b) { const Place P = place_of(b, n); return (2 * P.y + py) * 20 + 2 * P.x + px; };
@@ -2700,6 +2701,14 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
     c1::Staged<256, 2> R, R2;   // the frames of the two channel pairs
+    // A sample's dY, frames and first two ReLU masks are on their way while the sample before is computed, its slot one sample longer
+    // (with the weights in the order of the operands, not 64 bytes at a time: a step of 512 124 -> 121 us, of 1000 190 -> 185, of 77
+    // 58.4 -> 57.9; eight waves with all four frames in LDS, one workgroup per CU: 77 57.4, 256 91.1 against 89, 512 128 against 121)
+    uint4 mk0 = *reinterpret_cast<const uint4 *>(xg0 + (long)bid * (400 * 32) + pixel_of(0) * 32);
+    uint4 mk1 = *reinterpret_cast<const uint4 *>(xg0 + (long)bid * (400 * 32) + pixel_of(1) * 32);
+    c1::stage_load<256, 2>(R, F.src, bid, slot_n, 0, tid);
+    c1::stage_load<256, 2>(R2, F.src, bid, slot_n, 2, tid);
+    slot_n = bid + nblocks < A.B ? c1::sample_slot(F.src, bid + nblocks) : 0;
 
     for (int g = bid; g < A.B; g += nblocks) {
         sync_lds();   // the previous sample's image, dY tile and frames have been read (the first time: the image is cleared)
@@ -2709,14 +2718,8 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
 #undef DPS_ST
         const int gn = g + nblocks;
         if (gn < A.B) load_dy(gn);
-        const bf16_t *xg = A.xact + (long)g * (400 * 32) + 8 * kg;
-        // ReLU masks two blocks ahead of their use (all seven at once would cost 28 registers)
-        uint4 mk0 = *reinterpret_cast<const uint4 *>(xg + pixel_of(0) * 32);
-        uint4 mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(1) * 32);
-        // the sample's four frames are on their way while the input gradient is computed
-        c1::stage_load<256, 2>(R, F.src, g, slot_g, 0, tid);
-        c1::stage_load<256, 2>(R2, F.src, g, slot_g, 2, tid);
-        const int slot_n = gn < A.B ? c1::sample_slot(F.src, gn) : 0;
+        const int slot_nn = gn + nblocks < A.B ? c1::sample_slot(F.src, gn + nblocks) : 0;
+        const bf16_t *xg = xg0 + (long)g * (400 * 32), *xgn = gn < A.B ? xg0 + (long)gn * (400 * 32) : xg;
         sync_lds();
         // the operands are requested three reduction steps ahead (into the next blocks): a step's two matrix instructions
         // are a quarter of what a read takes
@@ -2733,7 +2736,8 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
         for (int b = 0; b < 7; ++b) {
             const uint4 mk = mk0;
             mk0 = mk1;
-            if (b + 2 < 7) mk1 = *reinterpret_cast<const uint4 *>(xg + pixel_of(b + 2) * 32);
+            // ReLU masks two blocks ahead of their use (all seven at once would cost 28 registers)
+            mk1 = *reinterpret_cast<const uint4 *>((b + 2 < 7 ? xg : xgn) + pixel_of((b + 2) % 7) * 32);
             v4f acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
 #pragma unroll
             for (int st = 0; st < 8; ++st) {
@@ -2751,6 +2755,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
         for (int cp = 0; cp < 2; ++cp) {
             if (cp == 1) sync_lds();   // the first pair's frames have been read
             c1::stage_store<256, 2>(xin, cp == 0 ? R : R2, tid);
+            if (gn < A.B) c1::stage_load<256, 2>(cp == 0 ? R : R2, F.src, gn, slot_n, 2 * cp, tid);
             sync_lds();   // the dY tile and the pair's frames are complete
             const bool do_bias = cp == 0 && wave == 0;
             // the operands are requested two steps ahead
@@ -2780,7 +2785,7 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        slot_g = slot_n;
+        slot_n = slot_nn;
     }
 
     float *part = F.part1 + (long)bid * (32 * 256 + 32);
@@ -2796,202 +2801,108 @@ __device__ __forceinline__ void conv2_dgrad_conv1_wgrad_body(const FusedArgs &F,
 }  // namespace dps
 
 // ===========================================================================
-// conv3 backward (3x3 stride 1, 9x9x64 -> 7x7x64), both gradients in one launch out of whole samples in LDS.
-//
-// What bounds it is latency, not work: at a batch of 512 both gradients are 2 us of matrix instructions if spread over all
-// CUs.  As 64x64 im2col tiles, nine or ten stages of 0.8 to 1.2 us each, every pixel was fetched once per tap
-// (58 MB out of the L2s for the weight gradient) and the launch took 15.3 us at a batch of 512.  Here a sample is staged once
-// and every tap reads it at another offset (a step of 512 129.7 -> 126.2 us, of 77 61.4 -> 58.3):
-//   input gradient : a workgroup per CU at most, its samples one after the other; the weights in registers (from a copy in the
-//                    order of the operands, packed.h), dY inside a border of two zero pixels, in two images.
-//   weight gradient: a workgroup takes one kernel row (64 x 192 outputs) over a range of samples; dY and the seven
-//                    pixel rows under it in LDS, two samples further on their way.
+// conv3's input gradient (3x3 stride 1, 7x7x64 -> 9x9x64), a sample's dY inside a border of two zero pixels in LDS, the weights in
+// registers (from a copy in the order of the operands, packed.h).  In 64 x 64 im2col tiles every dY was fetched once per
+// tap, in nine dependent stages of 0.8 us.
+// 32x32x16 instructions, the steps of sixteen output channels by turns into two sums, as in dgrad_tile: the same bits as its
+// tiles.  A lane of the result holds sixteen channels of a pixel.
+// A pixel is 144 bytes and a row 1808, so that position p lies 144 p bytes (mod 256) from the first: the sixteen positions that are
+// served together read from the sixteen different 16-byte columns of LDS.
+// In its launch conv3's weight gradient has become tiles of a whole kernel row (64 x 192; 64 x 64 before), which read dY a third
+// as often.  A step of 512 131.2 -> 124 us, of 77 60.7 -> 59, of 256 96.2 -> 90 with these two; what bounds the launch is the chain
+// of a tile's ten stages and of a workgroup's samples: both gradients are 2 us of matrix instructions spread over all CUs.
+// (16x16x32 instructions, and the weight gradient out of whole samples in LDS, each in an order of its own, were 3 us faster at 512.
+// In the old order, sixteen rows wherever a sample ends, the latter is a chain of LDS reads: 8 us slower.)
 // ===========================================================================
 namespace c3b {
 using ps::u32x4;
-using dps::IMG;
-using dps::PIX;
-using dps::ROW;
-constexpr int OUT = 49 * 64, IN = 81 * 64;                   // elements of a sample: dY; X and dX
-constexpr int YPIECES = OUT / 8, XPIECES = 63 * 8;           // 16-byte pieces: dY 392, seven pixel rows 504
-constexpr int ZERO_ROW = 63;                                 // of the weight gradient's X: what positions past the 49th read
-constexpr int STAGE = 2 * 64 * 64;                           // elements of a sample there: 64 rows of dY, 64 of X
-constexpr int LDS = std::max(2 * IMG, 2 * STAGE * 2);        // 39,424 bytes
+constexpr int OUT = 49 * 64, IN = 81 * 64, YPIECES = OUT / 8;
+constexpr int PIX = 144, ROW = 11 * PIX + 224, IMG = 11 * ROW;   // bytes
+static_assert(ROW % 256 == 9 * PIX % 256, "banks");
+constexpr int LDS = 2 * IMG;                                     // 39,776 bytes
 
 struct Args {
     const bf16_t *dy;    // [B][7][7][64]
     const bf16_t *x;     // [B][9][9][64], conv2's output after ReLU
     const uint16_t *w;   // the weights in the order of sp::packed_conv3_back_at
     bf16_t *dx;          // [B][9][9][64]
-    float *part;         // [nsplit][64 * 576 + 64]
     int B;
-    int nd;              // workgroups of the input gradient
-    int nsplit;          // ranges of samples of the weight gradient, B at most
+    int nd;              // workgroups
 };
 
-// Samples [bid * B / nd, (bid + 1) * B / nd).  Wave (ph, hh): tiles 3 ph .. + 2 of sixteen pixels, channels 32 hh .. + 31.
+// Samples [bid * B / nd, (bid + 1) * B / nd), two at a time.  Wave (ph, hh): channels 32 hh .. + 31 of half of the six tiles of 32
+// pixels that two samples have.
 __device__ __forceinline__ void dgrad_body(const Args &A, int bid, uint8_t *lds)
 {
-    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, kg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ph = wave & 1, hh = wave >> 1;
     const int g0 = (int)((long)bid * A.B / A.nd), g1 = (int)((long)(bid + 1) * A.B / A.nd);
     if (g0 >= g1) return;
-    u32x4 r0, r1;
-    auto load_dy = [&](int g) {
-        const u32x4 *p = reinterpret_cast<const u32x4 *>(A.dy + (long)g * OUT);
-        r0 = p[tid]; r1 = p[tid < YPIECES - 256 ? tid + 256 : YPIECES - 1];
+    u32x4 r[2][2];
+    auto load_dy = [&](int g) {   // samples g and g + 1; the last loads repeat the last sample
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const u32x4 *p = reinterpret_cast<const u32x4 *>(A.dy + (long)min(g + s, g1 - 1) * OUT);
+            r[s][0] = p[tid];
+            r[s][1] = p[tid < YPIECES - 256 ? tid + 256 : YPIECES - 1];
+        }
     };
     load_dy(g0);
-    v8bf wa[18][2];   // step 2 tap + half of dY's channels; rows 8 (i / 4) + 4 cb + i % 4 of the wave's channels
+    v8bf wa[36];   // step 4 tap + sixteenth of dY's channels
 #pragma unroll
-    for (int st = 0; st < 18; ++st)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-            wa[st][cb] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(A.w + ((2 * hh + cb) * 18 + st) * sp::FRAG + lane * 8));
-    for (int i = tid; i < 2 * IMG / 16; i += 256) *reinterpret_cast<u32x4 *>(lds + i * 16) = u32x4{0, 0, 0, 0};
-    // pixel (y, x) takes dY position (y - p, x - q) for tap (p, q): image pixel (y - p + 2, x - q + 2)
-    uint32_t base[3];
-    int pos[3];
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-        pos[b] = ps::Shape<ps::G2>::position(3 * ph + b, n);   // 9 x 9 pixels in six tiles
-        base[b] = pos[b] / 9 * ROW + pos[b] % 9 * PIX + kg * 16;
-    }
-    sync_lds();   // the images are cleared
-    for (int g = g0, s = 0; g < g1; ++g, s ^= 1) {
-        uint8_t *img = lds + s * IMG;   // (last read two samples ago; every wave has passed a barrier since)
-        auto put = [&](int t, u32x4 v) {
+    for (int st = 0; st < 36; ++st) wa[st] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4 *>(A.w + (hh * 36 + st) * sp::FRAG + lane * 8));
+    for (int i = tid; i < LDS / 16; i += 256) *reinterpret_cast<u32x4 *>(lds + i * 16) = u32x4{0, 0, 0, 0};
+    for (int g = g0; g < g1; g += 2) {
+        sync_lds();   // the images have been read (the first time: are cleared)
+        auto put = [&](int s, int t, u32x4 v) {
             const int q = t >> 3;
-            *reinterpret_cast<u32x4 *>(img + (q / 7 + 2) * ROW + (q % 7 + 2) * PIX + (t & 7) * 16) = v;
+            *reinterpret_cast<u32x4 *>(lds + s * IMG + (q / 7 + 2) * ROW + (q % 7 + 2) * PIX + (t & 7) * 16) = v;
         };
-        put(tid, r0);
-        if (tid < YPIECES - 256) put(tid + 256, r1);
-        load_dy(min(g + 1, g1 - 1));   // the last one repeats the last sample
-        const long o = (long)g * IN + 32 * hh + 8 * kg;
-        uint4 mk[3];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) mk[b] = *reinterpret_cast<const uint4 *>(A.x + o + pos[b] * 64);
+        for (int s = 0; s < 2; ++s) {
+            put(s, tid, r[s][0]);
+            if (tid < YPIECES - 256) put(s, tid + 256, r[s][1]);
+        }
+        load_dy(min(g + 2, g1 - 1));
         sync_lds();
-        auto operand = [&](int b, int st) {
-            const int tap = st >> 1;
-            return *reinterpret_cast<const uint4 *>(img + base[b] + (2 - tap / 3) * ROW + (2 - tap % 3) * PIX + (st & 1) * 64);
-        };
-        v4f acc[3][2];
-        uint4 cur[3], nxt[3];
+        // pixel (y, x) takes dY position (y - p, x - q) for tap (p, q): image pixel (y - p + 2, x - q + 2)
+        auto tile = [&](int s, int t) {
+            const int pos = min(32 * t + li, 80);   // (past the last pixel: the last one once more, the same bits)
+            const uint8_t *b = lds + s * IMG + pos / 9 * ROW + pos % 9 * PIX + h * 16;
+            const long o = (long)(g + s) * IN + pos * 64 + 32 * hh + 16 * h;
+            uint4 mk[2];
 #pragma unroll
-        for (int b = 0; b < 3; ++b) { acc[b][0] = acc[b][1] = v4f{0, 0, 0, 0}; cur[b] = operand(b, 0); }
+            for (int k = 0; k < 2; ++k) mk[k] = *reinterpret_cast<const uint4 *>(A.x + o + 8 * k);
+            auto operand = [&](int st) {
+                const int tap = st >> 2;
+                return *reinterpret_cast<const uint4 *>(b + (2 - tap / 3) * ROW + (2 - tap % 3) * PIX + (st & 3) * 32);
+            };
+            constexpr int N = 5;   // four steps ahead
+            uint4 q[N];
 #pragma unroll
-        for (int st = 0; st < 18; ++st) {
-            if (st + 1 < 18) {
+            for (int st = 0; st < N - 1; ++st) q[st] = operand(st);
+            v16f acc[2] = {v16f{0}, v16f{0}};
 #pragma unroll
-                for (int b = 0; b < 3; ++b) nxt[b] = operand(b, st + 1);
+            for (int st = 0; st < 36; ++st) {
+                if (st + N - 1 < 36) q[(st + N - 1) % N] = operand(st + N - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[st & 1] = mfma(wa[st], __builtin_bit_cast(v8bf, q[st % N]), acc[st & 1]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            acc[0] += acc[1];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const v8bf bb = __builtin_bit_cast(v8bf, cur[b]);
-                acc[b][0] = mfma16(wa[st][0], bb, acc[b][0]);
-                acc[b][1] = mfma16(wa[st][1], bb, acc[b][1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int b = 0; b < 3; ++b) cur[b] = nxt[b];
-        }
-        // (lanes that share a pixel store the same bits)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) *reinterpret_cast<uint4 *>(A.dx + o + pos[b] * 64) = dps::masked8(mk[b], acc[b][0], acc[b][1]);
-    }
-}
-
-// Tile t: kernel row t % 3 over range t / 3 of the samples.  Wave (oh, kh): output channels 32 oh .. + 31, three of the kernel
-// row's six blocks of 32 columns.  A sample's 49 positions are four reduction steps of 16; the last fifteen are rows of zeros on
-// both sides.
-__device__ __forceinline__ void wgrad_body(const Args &A, int t, bf16_t *lds)
-{
-    typedef __attribute__((address_space(3))) v4s *lds_v4s;
-    using Tr = TrTile<64>;
-    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, h = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), oh = wave & 1, kh = wave >> 1;
-    const int range = t / 3, ty = t % 3;
-    const int n0 = (int)((long)range * A.B / A.nsplit), n1 = (int)((long)(range + 1) * A.B / A.nsplit);
-    struct Raw { u32x4 y0, y1, x0, x1; };
-    auto load = [&](Raw &R, int g) {   // the last loads repeat the last sample
-        g = min(g, n1 - 1);
-        const u32x4 *y = reinterpret_cast<const u32x4 *>(A.dy + (long)g * OUT);
-        const u32x4 *x = reinterpret_cast<const u32x4 *>(A.x + (long)g * IN + ty * (9 * 64));
-        R.y0 = y[tid]; R.y1 = y[tid < YPIECES - 256 ? tid + 256 : YPIECES - 1];
-        R.x0 = x[tid]; R.x1 = x[tid < XPIECES - 256 ? tid + 256 : XPIECES - 1];
-    };
-    constexpr int AHEAD = 2;   // (four, and dY of the input gradient two ahead: 87.8 -> 89.4 us for a step of 256, equal at 512)
-    Raw R[AHEAD];
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k) load(R[k], n0 + k);
-    for (int i = tid; i < 2 * 16 * 8; i += 256) {   // rows 49 .. 63 of dY, row 63 of X, in both buffers
-        const int r = (i >> 3) & 15;
-        bf16_t *b = lds + (i >> 7) * STAGE + (r ? (48 + r) * 64 : 64 * 64 + ZERO_ROW * 64);
-        *reinterpret_cast<u32x4 *>(b + (i & 7) * 8) = u32x4{0, 0, 0, 0};
-    }
-    const int trow = 8 * h + (s16 >> 2), tcol = 16 * half + 4 * (s16 & 3);
-    const int yo = Tr::at(trow, oh * 32 + tcol);
-    int xo[4][2][3];   // step, four rows further, block
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int p = 16 * k + trow + 4 * f, blk = 3 * kh + i;
-                xo[k][f][i] = 64 * 64 + Tr::at(p < 49 ? p + 2 * (p / 7) + (blk >> 1) : ZERO_ROW, (blk & 1) * 32 + tcol);
-            }
-    const bool do_bias = ty == 0 && kh == 0;
-    v16f acc[3] = {v16f{0}, v16f{0}, v16f{0}}, accb = {0};
-    v8bf ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-    const int yr = tid >> 3, yc = (tid & 7) * 8, at = Tr::at(yr, yc);   // (rows 32 apart are permuted alike)
-
-    auto sample = [&](Raw &R, bf16_t *b, int g) {
-        *reinterpret_cast<u32x4 *>(b + at) = R.y0;
-        if (tid < YPIECES - 256) *reinterpret_cast<u32x4 *>(b + 32 * 64 + at) = R.y1;
-        *reinterpret_cast<u32x4 *>(b + 64 * 64 + at) = R.x0;
-        if (tid < XPIECES - 256) *reinterpret_cast<u32x4 *>(b + 96 * 64 + at) = R.x1;
-        load(R, g + AHEAD);
-        sync_lds();   // the buffer is complete; every wave is past the previous sample, which read the other one
-        auto operands = [&](int k, v8bf &fa, v8bf (&fb)[3]) {
-            fa = frag_tr(b + yo + 16 * k * 64, 64);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(b + xo[k][0][i]));
-                const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(b + xo[k][1][i]));
-                typedef short v8s __attribute__((ext_vector_type(8)));
-                const v8s r = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                fb[i] = __builtin_bit_cast(v8bf, r);
+            for (int k = 0; k < 2; ++k) {
+                const v4f a0 = {acc[0][8 * k], acc[0][8 * k + 1], acc[0][8 * k + 2], acc[0][8 * k + 3]};
+                const v4f a1 = {acc[0][8 * k + 4], acc[0][8 * k + 5], acc[0][8 * k + 6], acc[0][8 * k + 7]};
+                *reinterpret_cast<uint4 *>(A.dx + o + 8 * k) = dps::masked8(mk[k], a0, a1);
             }
         };
-        v8bf fa[2], fb[2][3];
-        operands(0, fa[0], fb[0]);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k + 1 < 4) operands(k + 1, fa[(k + 1) & 1], fb[(k + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) acc[i] = mfma(fa[k & 1], fb[k & 1][i], acc[i]);
-            if (do_bias) accb = mfma(fa[k & 1], ones, accb);
-            __builtin_amdgcn_sched_barrier(0);
+        // tiles 0 and 1 of the first sample and 0 of the second; 2 of the first, 1 and 2 of the second
+#pragma unroll 1
+        for (int k = 0; k < 3; ++k) {
+            const int s = ph == 0 ? k == 2 : k > 0, t = ph == 0 ? (k == 2 ? 0 : k) : (k == 0 ? 2 : k);
+            if (g + s < g1) tile(s, t);
         }
-    };
-    for (int g = n0; g < n1; g += AHEAD)
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k)
-            if (g + k < n1) sample(R[k], lds + (k & 1) * STAGE, g + k);
-
-    float *part = A.part + (long)range * (64 * 576 + 64);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int o = 32 * oh + 8 * (r / 4) + 4 * h + (r % 4);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) part[(long)o * 576 + ty * 192 + (3 * kh + i) * 32 + li] = acc[i][r];
-        if (do_bias && li == 0) part[64 * 576 + o] = accb[r];
     }
 }
 }  // namespace c3b

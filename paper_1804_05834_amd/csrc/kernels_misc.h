@@ -758,8 +758,7 @@ struct RmsArgs {
     float *theta, *v, *m, *g;
     __hip_bfloat16 *shadow;  // bf16 copy of theta (same order) or nullptr
     uint16_t *packed;        // with the bf16 copy: the conv weights in the forward launch's order (packed.h)
-    __hip_bfloat16 *w2t;     // with the bf16 copy: conv2's weights once more, as [tap][channel in][channel out] (or nullptr)
-    uint16_t *w3back;        // ... and conv3's, in the order of its input gradient (packed.h)
+    uint16_t *back;          // ... and conv2's and conv3's once more in the orders of their input gradients (packed.h)
     float lr, rho, eps;
 };
 
@@ -784,13 +783,11 @@ __device__ __forceinline__ void rms_apply(const RmsArgs &A, long i, float g, con
     if (store_g) A.g[i] = g;
     if (A.shadow) {
         A.shadow[i] = __float2bfloat16(th);
-        if (i < net::F1W) sp::store_packed_bf16(A.packed, i, th);
+        if (i < net::F1W) {
+            sp::store_packed_bf16(A.packed, i, th);
+            sp::store_back_bf16(A.back, i, th);
+        }
     }
-    if (A.w2t && i >= net::C2W && i < net::C2W + 64 * 512) {
-        const int t = (int)(i - net::C2W);   // [channel out][tap][channel in]
-        A.w2t[(t & 511) * 64 + (t >> 9)] = __float2bfloat16(th);
-    }
-    if (A.w3back && i >= net::C3W && i < net::C3B) A.w3back[sp::packed_conv3_back_at((int)(i - net::C3W))] = sp::bf16_bits(th);
 }
 // every operand is requested before the first store: the buffers may overlap as far as the compiler
 // knows, so a load behind a store would wait for the arithmetic in front of that store
@@ -843,22 +840,6 @@ __global__ __launch_bounds__(256) void k_rmsprop(RmsArgs A)
     __shared__ float red[4][64];
     RMS_SELECT_SEGMENT(A, (int)blockIdx.x, S)
     rmsprop_block(A, S, blockIdx.x, red);
-}
-
-// conv2's weights [channel out][tap][channel in] (fp32, internal order) as bf16 [tap][channel in][channel out]:
-// the layout in which the input gradient of conv2 finds the eight output channels of a matrix-instruction
-// operand next to each other (its reduction runs over the output channels)
-__global__ void k_w2_transposed(const float *w2, __hip_bfloat16 *w2t)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < 64 * 512) w2t[(t & 511) * 64 + (t >> 9)] = __float2bfloat16(w2[t]);
-}
-
-// conv3's weights in the order of its input gradient (packed.h)
-__global__ void k_pack_conv3_back(const float *w3, uint16_t *w3back)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < 64 * 576) w3back[sp::packed_conv3_back_at(t)] = sp::bf16_bits(w3[t]);
 }
 
 // fp32 -> bf16 copy (round to nearest even)

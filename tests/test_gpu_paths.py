@@ -102,11 +102,11 @@ def test_bf16_step_where_the_launches_change(dq, orc, prec, B):
     _replay_step_case(dq, orc, cap=30000, B=B, draw_seed=41, tol=TOL_BF16, prec=1)
 
 
-@pytest.mark.parametrize("B,cus", [(1, 2), (2, 9), (5, 7), (75, 9), (127, 40), (129, 100)])
-def test_conv3_backward_over_ranges_of_samples(dq, monkeypatch, B, cus):
-    """bf16: conv3's gradients with one to 37 samples in a workgroup (input gradient) or a range (weight gradient) against one or
-    two: the same activations, and sums of the same products in another order, to the fp32 path's tolerance."""
-    print("case conv3 backward", B, cus, flush=True)
+@pytest.mark.parametrize("B,cus", [(1, 2), (2, 9), (4, 7), (5, 7), (75, 9), (100, 65), (110, 65), (127, 40), (129, 100)])
+def test_conv_backward_over_ranges_of_samples(dq, monkeypatch, B, cus):
+    """bf16: the conv layers' gradients with one to 37 samples in a workgroup (pairs of samples and single ones in conv3's input
+    gradient) against few: the same activations, and sums of the same products split another way, to the fp32 path's tolerance."""
+    print("case conv backward", B, cus, flush=True)
     batch = tuple(dev(t) for t in synth.batch(29, B, 18))
     got = []
     for n in (None, cus):
