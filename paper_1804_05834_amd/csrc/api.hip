@@ -60,7 +60,7 @@ struct Workspace {
     int32_t *b_idx, *b_a;
     float *b_w, *b_r, *td_abs, *loss_j, *qmax_j, *loss_slot;
     int *pu_state;   // walkers of a priority update that is split over two launches
-    unsigned *arrivals;   // counter of the acting launch of few observations, cleared by the conv launch in front of it
+    unsigned *arrivals;   // counters of the acting launch of few observations, cleared by the conv launch in front of it
     uint8_t *b_done;
     // activations, channel-last, rows = samples of all passes (fp32 or bf16 by precision)
     void *act1, *act2, *act3;
@@ -106,7 +106,7 @@ Workspace carve(const dqn_config &c, uint8_t *base)
     w.qmax_j = (float *)take(MB * 4);
     w.loss_slot = (float *)take(256);
     w.pu_state = (int *)take(3 * misc::STATE_STRIDE * 4);
-    w.arrivals = (unsigned *)take(256);
+    w.arrivals = (unsigned *)take(misc::FEW_COUNTERS * misc::FEW_LINE * 4);
     w.b_done = take(MB);
     const size_t es = c.precision == 1 ? 2 : 4;  // bytes per activation element
     w.act1 = take(rows * net::A1 * es);
@@ -1748,8 +1748,8 @@ int32_t dqn_act_static(dqn_ctx *c, const uint8_t *obs, int32_t E, float epsilon,
     w.act3 = take(n * net::A3 * es);
     w.f1part = (float *)take(n * 14 * net::HID * 4);
     w.f1rows = n * 14;
-    w.arrivals = (unsigned *)take(256);
-    static_assert(DQN_ACT_STATIC_MAX * (size_t)(net::A1 + net::A2 + net::A3) * 4 + DQN_ACT_STATIC_MAX * 14 * (size_t)net::HID * 4 + 5 * 256
+    w.arrivals = (unsigned *)take(misc::FEW_COUNTERS * misc::FEW_LINE * 4);
+    static_assert(DQN_ACT_STATIC_MAX * (size_t)(net::A1 + net::A2 + net::A3) * 4 + DQN_ACT_STATIC_MAX * 14 * (size_t)net::HID * 4 + (4 + misc::FEW_COUNTERS) * 256
                       <= SCRATCH_BYTES, "scratch array too small");
     hipStream_t st = (hipStream_t)stream;
     const bool prof = c->prof;   // per-kernel timing creates events: not on this path

@@ -2209,7 +2209,7 @@ struct Args {
     int units;
     int draw;
     misc::SampleArgs samp;
-    unsigned *clear;              // a counter of a later launch, set to 0 here, or nullptr
+    unsigned *clear;              // the arrival counters of a later launch, set to 0 here, or nullptr
 };
 constexpr int MAX_UNITS = 96;
 template <int R3> struct Geo {
@@ -2258,7 +2258,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
     int tid = threadIdx.x, lane = tid & 63;
     const int G0 = (int)gridDim.x;
     const int nu = MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;
-    if (A.clear && blockIdx.x == 0 && tid == 0) *A.clear = 0;
+    if (A.clear && blockIdx.x == 0) misc::few_clear(A.clear, tid);
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
     u32x4 raw[G::NPX];
     auto load_px = [&](int si, int u, int slot) {

@@ -153,7 +153,7 @@ struct Args {
     int units;                   // of all segments
     int draw;                    // the samples are drawn from the ring here (every segment has the same n), or are states
     misc::SampleArgs samp;
-    unsigned *clear;             // a counter of a later launch, set to 0 here, or nullptr
+    unsigned *clear;             // the arrival counters of a later launch, set to 0 here, or nullptr
 };
 constexpr int MAX_UNITS = 96;    // units of one workgroup at most
 constexpr int TURN = 2048;       // bytes of LDS in which a wave hands a step's weights to the lanes that multiply them
@@ -230,7 +230,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
     const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
     int tid = threadIdx.x, lane = tid & 63;
     const int nu = MANY ? (A.units - bid + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
-    if (A.clear && bid == 0 && tid == 0) *A.clear = 0;
+    if (A.clear && bid == 0) misc::few_clear(A.clear, tid);
 
     auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
     v8bf w1[8][3];

@@ -613,10 +613,20 @@ inline void launch_head_act(const HeadActArgs &H, int num_cu, hipStream_t st)
 // words in device memory; the one that arrives last (above) has the whole hidden layer and finishes every row as
 // k_head_act does.  Every sum is formed in the order of the launches for more observations (up to 192 in fp32, 511 in
 // bf16), so that the same inputs give the same bits alone and among others.  One observation, against the two launches:
-// 21.7 -> 19.3 us per call in fp32, 16.1 -> 14.0 in bf16; two: 21.8 -> 20.3, 16.4 -> 14.6.  (A form whose lanes and waves added in an order of their own took
+// 21.7 -> 19.3 us per call in fp32, 16.1 -> 14.0 in bf16; two: 21.8 -> 20.3, 16.4 -> 14.6 (with one counter, see below).  (A form whose lanes and waves added in an order of their own took
 // 19.2 and 19.7 in fp32, 14.4 and 15.0 in bf16; with four rows that form had no gain left, 21.0 and 15.9.)
-// The counter is cleared by the conv launch in front, so that nothing of one call is left for the next.
+// Additions to words of one line of memory follow each other, about 10 ns each: at a single counter the 256 workgroups
+// of the fp32 form queued for 2.5 us.  So they arrive in sixteen groups, each at a line of its own, and the last of a group
+// at the counter of the groups: 19.6 -> 17.9 us per call (with the groups' counters in one line 20.3: the queue, and a
+// second trip behind it).
+// The counters are cleared by the conv launch in front, so that nothing of one call is left for the next.
 constexpr int FEW_ROWS = 2;
+constexpr int FEW_GROUPS = 16, FEW_LINE = 64;   // words from one counter to the next
+constexpr int FEW_COUNTERS = FEW_GROUPS + 1;    // the groups', then the counter of the groups
+__device__ __forceinline__ void few_clear(unsigned *arrivals, int tid)
+{
+    if (tid < FEW_COUNTERS) arrivals[tid * FEW_LINE] = 0;
+}
 struct Fc1HeadArgs {
     HeadActArgs head;      // (part, nsplit, split_stride: not used)
     const void *x;         // [E][3136] conv3's output, fp32 or bf16
@@ -630,10 +640,14 @@ struct FewLds {
     int last;
 };
 // Called by all 256 threads, each wave's published words acknowledged: is this workgroup the last of `of`?
-__device__ __forceinline__ bool few_last(const Fc1HeadArgs &A, FewLds &L, int of)
+__device__ __forceinline__ bool few_last(const Fc1HeadArgs &A, FewLds &L, unsigned of /*>= FEW_GROUPS*/)
 {
     sync_lds();
-    if (threadIdx.x == 0) L.last = arrived_last(A.arrivals, of);
+    if (threadIdx.x == 0) {
+        const unsigned g = blockIdx.x % FEW_GROUPS;
+        L.last = arrived_last(A.arrivals + g * FEW_LINE, (of - g + FEW_GROUPS - 1) / FEW_GROUPS) &&
+                 arrived_last(A.arrivals + FEW_GROUPS * FEW_LINE, FEW_GROUPS);
+    }
     sync_lds();
     return L.last;
 }
