@@ -559,7 +559,9 @@ int32_t forward_trunk_f32(dqn_ctx *c, const Workspace &w, const Pass *pass, int 
                 else sp::k_conv123_step<4, 4><<<dim3(nat + plan.grid), 512, sp::step_lds<4, 4>(), st>>>(S);
             });
         } else launch(c, "conv123_fwd", st, [&] {
-            if (plan.r3 == 1) sp::k_conv123_fwd<1, false><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
+            // parts of one output row in two workgroups each while they have a CU each (acting on up to 18 observations)
+            if (plan.r3 == 1 && 2 * plan.grid <= c->num_cu && !draw) sp::k_conv123_fwd<1, false, true><<<dim3(2 * plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 1) sp::k_conv123_fwd<1, false><<<dim3(plan.grid), 512, sp::Geo<1>::LDS, st>>>(A);
             else if (plan.r3 == 4) sp::k_conv123_fwd<4, false><<<dim3(plan.grid), 512, sp::Geo<4>::LDS, st>>>(A);
             else if (A.units <= plan.grid) sp::k_conv123_fwd<7, false><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
             else sp::k_conv123_fwd<7, true><<<dim3(plan.grid), 512, sp::Geo<7>::LDS, st>>>(A);
@@ -1359,7 +1361,7 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         return false;
     };
     if (cfg->precision == 0) {
-        c->split = granted(sp::k_conv123_fwd<1, false>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<4, false>, sp::Geo<4>::LDS) &&
+        c->split = granted(sp::k_conv123_fwd<1, false>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<1, false, true>, sp::Geo<1>::LDS) && granted(sp::k_conv123_fwd<4, false>, sp::Geo<4>::LDS) &&
                    granted(sp::k_conv123_fwd<7, false>, sp::Geo<7>::LDS) && granted(sp::k_conv123_fwd<7, true>, sp::Geo<7>::LDS) && granted(sp::k_conv123_step<1, 2>, sp::step_lds<1, 2>()) &&
                    granted(sp::k_conv123_step<4, 2>, sp::step_lds<4, 2>()) && granted(sp::k_conv123_step<4, 4>, sp::step_lds<4, 4>()) &&
                    granted(k_conv21_bwd_sp, CONV21_LDS);

@@ -209,9 +209,14 @@ __device__ __forceinline__ void reduce_quarters(const v16f (&acc)[T], v4f (&own)
 
 // Workgroup bid of G0; the kernel's arguments begin with A.  MANY: it takes one unit after the other; otherwise just one
 // (whole samples with a workgroup each: 129 observations 38.2 -> 36.7 us per call, 256 40.7 -> 38.7, a step at 128 191 -> 189).
-template <int R3, bool MANY>
+// HALF (one unit): workgroups 2 b and 2 b + 1 share unit b, the second one finishing the upper half of conv3's channels.
+// conv3, bound by its matrix instructions (an output row fills 7 of a tile's 32 columns), is then the work of four waves,
+// one per SIMD, and half of its weights stay away; conv1 and conv2 are computed twice, on compute units that would be
+// idle.  Acting on one observation 17.9 -> 17.2 us per call, on 3 to 18 0.6 us less each; the same bits.
+template <int R3, bool MANY, bool HALF = false>
 __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const int G0, uint8_t *lds)
 {
+    static_assert(!(MANY && HALF), "one unit");
     // The segments are indexed at run time; through the by-value structure that would be a copy in scratch
     // memory, or a select over three times fifteen scalars.  The arguments themselves lie in constant memory.
     typedef const __attribute__((address_space(4))) Args *ArgsPtr;
@@ -228,6 +233,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nt = wave & 1, tg = wave >> 1;      // conv1
     const int ch = wave & 1, kq = wave >> 1;      // conv2, conv3
+    const int ch3 = HALF ? bid & 1 : ch, kq3 = HALF ? wave & 3 : kq;
+    const bool on3 = !HALF || wave < 4;           // has a share of conv3
     int tid = threadIdx.x, lane = tid & 63;
     const int nu = MANY ? (A.units - bid + G0 - 1) / G0 : 1;   // units of this workgroup (>= 1)
     if (A.clear && bid == 0) misc::few_clear(A.clear, tid);
@@ -277,7 +284,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         }
     };
 
-    int u = bid;
+    int u = HALF ? bid >> 1 : bid;
     int si = seg_of(u);
     // (scalar loads: a select over the three segments' arguments became a table in scratch memory)
     const uint8_t *x0 = SP_SEG(si).src.x;
@@ -345,8 +352,9 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         sync_lds();   // the weights' place is conv1's image from here on
         v4f w2[8][2], w3[9][2];
         const float *p2 = theta + net::C2W + (32 * ch + (lane >> 2)) * 512 + 128 * kq + 4 * (lane & 3);
-        const float *p3 = theta + net::C3W + (32 * ch + (lane >> 2)) * 576 + 144 * kq + 4 * (lane & 3);
+        const float *p3 = theta + net::C3W + (32 * ch3 + (lane >> 2)) * 576 + 144 * kq3 + 4 * (lane & 3);
         auto load_w3 = [&](int s) {
+            if (!on3) return;
 #pragma unroll
             for (int q = 0; q < 2; ++q) w3[s][q] = *reinterpret_cast<const v4f *>(p3 + 16 * s + 16 * 576 * q);
         };
@@ -362,7 +370,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
 #pragma unroll
             for (int q = 0; q < 2; ++q) wr[q] = *reinterpret_cast<const v4f *>(tw + i32 * 64 + (((2 * h + q) ^ ((lane >> 2) & 3)) * 16));
         };
-        const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2 and conv3
+        const int co = 32 * ch + 8 * kq + 4 * h;    // the four channels this lane finishes in conv2, in conv3
+        const int co3 = 32 * ch3 + 8 * kq3 + 4 * h;
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- conv1
@@ -496,7 +505,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
         sync_lds();
 
         // ---- conv3: steps 9 kq .. 9 kq + 8 of 36
-        {
+        if (!on3) sync_lds();   // the barrier of reduce_quarters
+        else {
             constexpr int T = G::T3, NA = T == 1 ? 2 : 1;
             const uint8_t *pa[T];
 #pragma unroll
@@ -513,7 +523,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
                 for (int t = 0; t < T; ++t) acc[a][t] = Acc2{v16f{0}, v16f{0}};
             v8bf b[3], nb[3], wp[2][3];
             auto load_b = [&](int i) {
-                const int s = i / T, t = i % T, sg = 9 * kq + s, tap = sg >> 2;
+                const int s = i / T, t = i % T, sg = 9 * kq3 + s, tap = sg >> 2;
                 const int off = ((tap / 3) * 9 + tap % 3) * G::P2 + (sg & 3) * 32;
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) nb[pl] = *reinterpret_cast<const v8bf *>(pa[t] + off + pl * 128);
@@ -537,8 +547,8 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
             v16f sum[T];
             close_sums(acc, sum);
             v4f own[T];
-            reduce_quarters<T>(sum, own, scratch, kq, ch, lane);
-            const v4f bias3 = *reinterpret_cast<const v4f *>(bias + 96 + co);
+            reduce_quarters<T>(sum, own, scratch, kq3, ch3, lane);
+            const v4f bias3 = *reinterpret_cast<const v4f *>(bias + 96 + co3);
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const int m = 32 * t + i32, y = m / 7;
@@ -546,7 +556,7 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = fmaxf(own[t][r] + bias3[r], 0.f);
                 if (m < G::M3 && row0 + y >= rowp + R3)
-                    *reinterpret_cast<v4f *>(SP_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + co) = v;
+                    *reinterpret_cast<v4f *>(SP_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + co3) = v;
             }
         }
         if (!MANY) break;
@@ -556,11 +566,11 @@ __device__ __forceinline__ void conv123_body(const Args &A, const int bid, const
 #undef SP_SEG
 }
 
-template <int R3, bool MANY>
+template <int R3, bool MANY, bool HALF = false>
 __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    conv123_body<R3, MANY>(A, (int)blockIdx.x, (int)gridDim.x, lds);
+    conv123_body<R3, MANY, HALF>(A, (int)blockIdx.x, (int)gridDim.x, lds);
 }
 
 // ---------------------------------------------------------------------------

@@ -56,6 +56,21 @@ def test_act_on_few_observations(dq, orc, K, dueling, prec):
         check_argmax(a.cpu().numpy(), r, tol)
     m.close()
 
+# up to 18 observations (7 parts each, two workgroups per part on 256 compute units) conv3's channels are split over two
+# workgroups in fp32; 19 and 36 are one workgroup per part.  The sums are the same, so the bits are
+@pytest.mark.parametrize("prec", [0, 1])
+def test_act_same_bits_however_many(dq, prec):
+    m = dq.Dqn(dq.make_config(num_actions=6, dueling=1, max_act_batch=36, precision=prec))
+    m.set_params(0, torch.from_numpy(synth.he_uniform_params(8, 6, 1, bias_scale=0.05)))
+    on = dev(synth.states(33, 36))
+    a36, q36 = (t.clone() for t in m.act(on, 0.0, 99, want_q=True))
+    for E in (1, 2, 3, 17, 18, 19):
+        print("case act same bits", prec, E, flush=True)
+        a, q = m.act(on[36 - E:], 0.0, 99, want_q=True)
+        assert torch.equal(q, q36[36 - E:]) and torch.equal(a, a36[36 - E:]), E
+    m.close()
+
+
 
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("K,dueling,small", [(18, 1, 0), (4, 0, 0), (64, 1, 0), (18, 1, 1)])
