@@ -269,7 +269,7 @@ void launch(dqn_ctx *c, const char *name, hipStream_t st, F &&f)
 
 // Launch shape of a kernel that builds the whole sum-tree from its leaves: blocks of BL leaves.  The state area
 // behind the heap holds the maximal priority (word 0) and the arrival counters of the launches whose last
-// workgroup finishes the work (words 1 and 2; 0 between launches).
+// workgroup finishes the work (words 1 to 3; 0 between launches).
 int tree_block_leaves(const dqn_ctx *c) { return (int)std::min<long>(c->L, 4096); }
 unsigned *tree_counter(dqn_ctx *c, int k) { return reinterpret_cast<unsigned *>(c->tree + 2 * c->L + k); }
 // What such a launch leaves to do: the levels above the blocks' roots of a tree of more than 4096 x 4096 leaves
@@ -1564,8 +1564,9 @@ int32_t per_update(dqn_ctx *c, const int32_t *idx, const float *td_abs, int32_t 
     if (!idx || !td_abs) return fail(c, DQN_ERR_INVALID_ARG, "per_update: NULL argument");
     hipStream_t st = (hipStream_t)stream;
     launch(c, "per_update", st, [&] {
-        misc::k_per_update<<<1, (n + 63) / 64 * 64, 0, st>>>(
-            misc::PerUpdateArgs{c->tree, c->L, c->levels, c->slot_limit, idx, td_abs, n, c->cfg.per_alpha, c->cfg.per_eps, 0});
+        misc::launch_per_update(
+            misc::PerUpdateArgs{c->tree, c->L, c->levels, c->slot_limit, idx, td_abs, n, c->cfg.per_alpha, c->cfg.per_eps, 0},
+            tree_counter(c, 3), st);
     });
     return hip_status(c, "per_update");
 }
@@ -1881,7 +1882,7 @@ static int32_t enqueue_step(dqn_ctx *c, int32_t B, const dqn_batch *batch, const
     const bool fuse_tail = sd == st;
     if (!fuse_tail) {
         launch(c, "head_wgrad", sp, [&] { misc::k_head_wgrad<<<dim3(c->R, 16), 512, 0, sp>>>(HW); });
-        if (!batch) launch(c, "per_update", sp, [&] { misc::k_per_update<<<1, (B + 63) / 64 * 64, 0, sp>>>(PU); });
+        if (!batch) launch(c, "per_update", sp, [&] { misc::launch_per_update(PU, tree_counter(c, 3), sp); });
     }
     if (sp != sd) (void)hipEventRecord(c->ev_join2, sp);
 

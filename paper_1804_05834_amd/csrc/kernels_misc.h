@@ -1230,19 +1230,18 @@ struct PerUpdateArgs {
 constexpr int PU_LDS_WORDS = 2 * PU_SLOTS + 16;  // LDS of per_update_body, in 4-byte words
 
 // The whole workgroup must call this; it handles W entries per thread (W * blockDim.x >= n).
-// lds: PU_LDS_WORDS words.  With `state` the walk stops after `first_levels` levels and leaves
-// every walker (node, value, active) there, for per_update_resume to take to the root later:
+// lds: PU_LDS_WORDS words.  The walk stops after `first_levels` levels and leaves every walker (node, value,
+// active) in `state`, for per_update_resume to take to the root later:
 // entry j at state[j], state[STATE_STRIDE + j], state[2 * STATE_STRIDE + j].
 constexpr int STATE_STRIDE = 1024;
-template <int W = 1>
-__device__ __forceinline__ void per_update_body(const PerUpdateArgs &A, int *lds, int first_levels = -1,
-                                                int *state = nullptr)
+template <int W>
+__device__ __forceinline__ void per_update_body(const PerUpdateArgs &A, int *lds, int first_levels, int *state)
 {
     int *keys = lds, *ivals = lds + PU_SLOTS;  // ivals: largest entry number naming the slot's leaf
     float *sh = reinterpret_cast<float *>(lds + 2 * PU_SLOTS);
     float *tree = A.tree;
     const long L = A.L, size = A.size;
-    const int levels = A.levels, n = A.n;
+    const int n = A.n;
     const int32_t *idx = A.idx;
     const float *td_abs = A.td_abs;
     const float alpha = A.alpha, eps = A.eps;
@@ -1292,16 +1291,14 @@ __device__ __forceinline__ void per_update_body(const PerUpdateArgs &A, int *lds
         walk[w] = my[w] >= 0 && ivals[slot[w]] == tid + w * nt;
         v[w] = (float)pow((double)p[w], (double)alpha);
     }
-    tree_walk<W>(tree, node, v, walk, state ? first_levels : levels);
-    if (state) {
+    tree_walk<W>(tree, node, v, walk, first_levels);
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int j = tid + w * nt;
-            if (j < STATE_STRIDE) {
-                state[j] = node[w];
-                state[STATE_STRIDE + j] = __float_as_int(v[w]);
-                state[2 * STATE_STRIDE + j] = walk[w] ? 1 : 0;
-            }
+    for (int w = 0; w < W; ++w) {
+        const int j = tid + w * nt;
+        if (j < STATE_STRIDE) {
+            state[j] = node[w];
+            state[STATE_STRIDE + j] = __float_as_int(v[w]);
+            state[2 * STATE_STRIDE + j] = walk[w] ? 1 : 0;
         }
     }
 }
@@ -1339,10 +1336,105 @@ __device__ __forceinline__ void per_update_resume(const PerUpdateArgs &A, int do
     }
 }
 
-__global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A)
+// The update as a launch of its own.  What bounds it is one compute unit's rate of scattered words, a store and a load per
+// entry and level: 6.4 us for 128 entries over a million slots, 11.7 for 512, 19.8 for 1024 (back to back).
+// PARTS: the part of the tree that holds the slots is cut into PU_PARTS subtrees, a workgroup each, which picks its entries
+// out of the list, repairs its subtree and publishes the subtree's root; the one that arrives last forms the few nodes above:
+// 7.2 and 7.6 us for 512 and 1024.  (With the entries sorted, all siblings requested at once and values handed over in LDS the
+// same split took 9.2 and 9.7, 8.1 where one workgroup takes 6; in one workgroup 15 for 512.)
+// It pays from 384 entries on: 7.3 against about 9 us over a million slots, 6.5 against 6 over 10,000, where 512 and 1024
+// take 6.5 and 7 against 7 and 10; 256 entries 7.2 against 7.5 and 6.5 against 5.4.  Over 4096 slots or fewer it gains
+// nothing below 1024.  Entries that all lie in one subtree pay about 1 us for the split.
+constexpr int PU_PART_BITS = 5, PU_PARTS = 1 << PU_PART_BITS;
+constexpr int PU_PARTS_FROM = 384, PU_PARTS_BITS = 13;   // entries; bits of the slots' numbers
+template <bool PARTS>
+__global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A, int levels /*of a workgroup's subtree*/, unsigned *count)
 {
-    __shared__ int lds[PU_LDS_WORDS];
-    per_update_body<1>(A, lds);
+    __shared__ int keys[PU_SLOTS], ivals[PU_SLOTS];   // see per_update_body
+    __shared__ float sh[16];
+    float *const tree = A.tree;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6, part = blockIdx.x;
+    int my = -1;
+    float p = 0.f;
+    if (tid < A.n) {
+        const int v = A.idx[tid];
+        p = (float)((double)fabsf(A.td_abs[tid]) + (double)A.eps);
+        if (v >= 0 && v < A.size && p <= 3.4028234663852886e38f) my = v;   // others are skipped (see per_update_body)
+    }
+    for (int t = tid; t < PU_SLOTS; t += blockDim.x) { keys[t] = -1; ivals[t] = -1; }
+    if (part == 0) {   // uniform for the workgroup
+        const float pmax = block_max_1024(my >= 0 ? p : 0.f, sh);   // contains barriers
+        if (tid == 0) tree[2 * A.L] = fmaxf(tree[2 * A.L], pmax);
+    }
+    if (A.leaves_fixed) return;   // uniform for the launch
+    if constexpr (PARTS) {
+        // this part's entries, in the list's order, to the first threads; the waves that are left without one leave, and
+        // barriers no longer count them
+        __shared__ int found[16], own[1024];
+        __shared__ float own_p[1024];
+        const bool mine = my >= 0 && my >> levels == part;
+        const uint64_t here = __ballot(mine);
+        if (lane == 0) found[wave] = __popcll(here);
+        sync_lds();
+        int m = 0, at = __popcll(here & ((1ull << lane) - 1));
+        for (int w = 0; w < nw; ++w) {
+            if (w == wave) at += m;
+            m += found[w];
+        }
+        if (mine) {
+            own[at] = my;
+            own_p[at] = p;
+        }
+        sync_lds();
+        if (wave > 0 && 64 * wave >= m) return;
+        my = tid < m ? own[tid] : -1;
+        p = tid < m ? own_p[tid] : 0.f;
+    } else sync_lds();
+    int node[1] = {(int)A.L + (my >= 0 ? my : 0)}, slot = 0;
+    if (my >= 0) {
+        bool first;
+        slot = pu_insert(keys, node[0], &first);
+        atomicMax(&ivals[slot], tid);
+    }
+    sync_lds();
+    const bool walk[1] = {my >= 0 && ivals[slot] == tid};   // one walker per leaf: the last entry naming it
+    float v[1] = {(float)pow((double)p, (double)A.alpha)};
+    tree_walk<1>(tree, node, v, walk, levels);
+    if constexpr (PARTS) {
+        // every walker has the subtree's root
+        if (walk[0]) publish_word(tree + node[0], v[0]);
+        words_acknowledged();
+        sync_lds();
+        if (wave > 0) return;
+        int last = 0;
+        if (lane == 0) last = arrived_last(count, PU_PARTS);
+        if (!__builtin_amdgcn_readfirstlane(last)) return;
+        // a lane per part; above their common root the path is the leftmost one, whose siblings no entry lies under
+        const int roots = (int)(A.L >> levels), top = roots >> PU_PART_BITS;
+        float s = read_word(tree + roots + (lane & (PU_PARTS - 1)));
+        const float right = lane < 31 && top >> lane > 1 ? tree[(top >> lane) + 1] : 0.f;
+        auto level = [&](int k, float other) {
+            s += other;
+            if (lane < PU_PARTS && (lane & ((1 << k) - 1)) == 0) tree[(roots + lane) >> k] = s;
+        };
+        level(1, lane_xor<1>(s));
+        level(2, lane_xor<2>(s));
+        level(3, lane_xor<4>(s));
+        level(4, lane_xor<8>(s));
+        level(5, lane_xor<16>(s));
+        for (int k = 0; top >> k > 1; ++k) {
+            s += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(right), k));
+            if (lane == 0) tree[top >> (k + 1)] = s;
+        }
+    }
+}
+inline void launch_per_update(const PerUpdateArgs &A, unsigned *count, hipStream_t st)
+{
+    const int threads = (A.n + 63) / 64 * 64;
+    int bits = 0;   // of a slot's number: at most A.levels
+    while ((1l << bits) < A.size) ++bits;
+    if (A.n >= PU_PARTS_FROM && bits >= PU_PARTS_BITS) k_per_update<true><<<PU_PARTS, threads, 0, st>>>(A, bits - PU_PART_BITS, count);
+    else k_per_update<false><<<1, threads, 0, st>>>(A, A.levels, count);
 }
 
 // Repair of the tree above `cnt` CONSECUTIVE leaves first .. first + cnt - 1 (heap indexes), whose new values

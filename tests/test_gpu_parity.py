@@ -432,6 +432,54 @@ def test_tree_fill_sample_update(dq, orc, cap, n, B, strat):
     m.close()
 
 
+# one workgroup, or from 384 entries and more than 4096 slots on one per subtree: both sides of the rule, entries spread over
+# all subtrees, over a few slots or over one, a slot range that is no power of two, repeated and skipped entries
+@pytest.mark.parametrize("cap,n,spread", [(5, 1, 5), (37, 64, 37), (1000, 129, 1000), (4096, 384, 4096), (4097, 383, 4097), (4097, 384, 4097),
+                                          (70000, 512, 600), (300000, 513, 300000), (1 << 20, 1000, 1 << 20), (1 << 20, 1024, 1),
+                                          (1 << 20, 1024, 1400)])
+def test_per_update_parts(dq, orc, cap, n, spread):
+    print("case update", cap, n, spread, flush=True)
+    m = dq.Dqn(dq.make_config(replay_capacity=cap, max_batch=32))
+    pri = synth.exp_priorities(9, cap)
+    m.per_fill(dev(pri))
+    tree_ref = orc.tree_build(pri.numpy(), m.L, float(np.float32(0.6)))
+    mp = 1.0
+    rng = np.random.default_rng(cap + n)
+    for k in range(3):   # slots in any order, ascending, descending
+        idx = (cap - spread + rng.integers(0, spread, n)).astype(np.int32)
+        if k:
+            idx = np.sort(idx)[::1 if k == 1 else -1].copy()
+        if n > 4:
+            idx[2], idx[n - 2] = -1, cap
+        td = rng.standard_exponential(n).astype(np.float32)
+        m.per_update(dev(idx), dev(td))
+        ok = (idx >= 0) & (idx < cap)   # (the oracle takes no others)
+        mp = orc.per_update(tree_ref, cap, idx[ok], td[ok], float(np.float32(0.6)), float(np.float32(1e-6)), mp)
+        assert np.array_equal(m.tree.cpu().numpy()[1:], tree_ref[1:])
+        assert float(m.max_priority) == np.float32(mp)
+    m.close()
+
+
+def test_per_update_parts_of_a_partly_filled_ring(dq, orc):
+    """The subtrees are those of the slots that are filled; the levels above them are one path."""
+    cap, filled, n = 1 << 18, 20000, 700
+    m = dq.Dqn(dq.make_config(replay_capacity=cap, max_batch=32))
+    pri = synth.exp_priorities(9, filled)
+    m.per_fill(dev(pri))
+    tree_ref = orc.tree_build(pri.numpy(), m.L, float(np.float32(0.6)))
+    rng = np.random.default_rng(3)
+    mp = 1.0
+    for k in range(2):   # the second call finds the arrival counter as the first left it
+        print("case partly filled", k, flush=True)
+        idx = rng.integers(0, filled, n).astype(np.int32)
+        td = rng.standard_exponential(n).astype(np.float32)
+        m.per_update(dev(idx), dev(td))
+        mp = orc.per_update(tree_ref, filled, idx, td, float(np.float32(0.6)), float(np.float32(1e-6)), mp)
+        assert np.array_equal(m.tree.cpu().numpy()[1:], tree_ref[1:])
+        assert float(m.max_priority) == np.float32(mp)
+    m.close()
+
+
 def test_per_update_skips_non_finite_errors(dq, orc):
     """A NaN or infinite TD error must not reach the tree: the entry is skipped on both sides."""
     print("case per_update non-finite", flush=True)
