@@ -92,10 +92,11 @@ def gemm_bytes_per_launch(B, R, bf16):
 # run (fetch x1.949, write x0.9875).  Keyed by (kernel, batch, precision); the figures and the
 # commands are in profiles/train_step_b512_bf16_hbm_traffic.md.
 MEASURED_TRAFFIC = {
+    ("conv123_fwd", 512, "bf16"): 47.4e6 + 27.7e6,
     ("fc1_fwd", 512, "bf16"): 19.6e6 + 12.4e6,
     ("head_train", 512, "bf16"): 13.2e6 + 1.7e6,
     ("fc1_bwd", 512, "bf16"): 13.5e6 + 9.6e6,
-    ("conv3_bwd", 512, "bf16"): 10.0e6 + 11.2e6,
+    ("conv3_bwd", 512, "bf16"): 16.7e6 + 11.2e6,
     ("conv21_bwd", 512, "bf16"): 50.3e6 + 16.0e6,
     ("rmsprop", 512, "bf16"): 41.1e6 + 17.1e6,
 }

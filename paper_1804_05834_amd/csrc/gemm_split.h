@@ -128,7 +128,7 @@ struct RowSum {
 // step, and conv1's of the next unit those of conv3's; so do the next unit's pixels.  Four lanes load 64 bytes of a row
 // together; conv1's weights are split on their way into LDS, where four waves read them, a step of conv2's and conv3's
 // passes through 2 KB of LDS of its wave's own to the lanes that multiply it.  Its parts are formed between the matrix
-// instructions of the step before.  Acting on one observation takes 21.5 us; with loads by the lanes that multiply
+// instructions of the step before.  Acting on one observation took 21.5 us (17.2 since, HALF below and k_fc1_head_act); with loads by the lanes that multiply
 // (16 bytes of 64 rows per instruction) 24.7, with the parts formed in front of the matrix instructions 22.8, with parts
 // kept in memory beside the parameters 20.1, but then a write to the parameters went unseen.
 // R3 = 7 is the least work (no row twice); with few samples smaller parts spread a sample over
