@@ -3,7 +3,7 @@
 This module holds input generators only (no arithmetic of the method): frames,
 actions, rewards, terminal flags, raw priorities and initial weights, all pure
 functions of (seed, counter) through one 64-bit counter mixer, so any subset can
-be regenerated anywhere (CPU for the oracle, GPU for filling the replay ring)
+be regenerated anywhere (CPU for comparisons, GPU for filling the replay ring)
 without storing the rest.  It imports nothing else from this package.
 
 Mixer: z = seed + (ctr+1)*0x9E3779B97F4A7C15; z = (z ^ z>>30)*0xBF58476D1CE4E5B9;
