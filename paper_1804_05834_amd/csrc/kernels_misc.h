@@ -46,7 +46,7 @@ template <int N> __device__ __forceinline__ float row_shl(float v)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x100 + N, 0xF, 0xF, true));
 }
 
-template <int O = 32> __device__ __forceinline__ float wave_sum(float v)   // over groups of 2 O lanes
+template <int O = 32, class T> __device__ __forceinline__ T wave_sum(T v)   // over groups of 2 O lanes
 {
     v += lane_xor<O>(v);
     if constexpr (O > 1) return wave_sum<O / 2>(v);
@@ -1341,14 +1341,16 @@ __device__ __forceinline__ void per_update_resume(const PerUpdateArgs &A, int do
 }
 
 // The update as a launch of its own.  What bounds it is one compute unit's rate of scattered words, a store and a load per
-// entry and level: 6.4 us for 128 entries over a million slots, 11.7 for 512, 19.8 for 1024 (back to back).
+// entry and level: 6.4 us for 128 entries over a million slots, 10.3 for 512, 19.3 for 1024 (back to back).
 // PARTS: the part of the tree that holds the slots is cut into PU_PARTS subtrees, a workgroup each, which picks its entries
 // out of the list, repairs its subtree and publishes the subtree's root; the one that arrives last forms the few nodes above:
-// 7.2 and 7.6 us for 512 and 1024.  (With the entries sorted, all siblings requested at once and values handed over in LDS the
-// same split took 9.2 and 9.7, 8.1 where one workgroup takes 6; in one workgroup 15 for 512.)
-// It pays from 384 entries on: 7.3 against about 9 us over a million slots, 6.5 against 6 over 10,000, where 512 and 1024
-// take 6.5 and 7 against 7 and 10; 256 entries 7.2 against 7.5 and 6.5 against 5.4.  Over 4096 slots or fewer it gains
-// nothing below 1024.  Entries that all lie in one subtree pay about 1 us for the split.
+// 7.2 and 7.5 us for 512 and 1024.  (With the entries sorted, all siblings requested at once and values handed over in LDS the
+// same split took 2 us more, 8.1 where one workgroup takes 6; in one workgroup 15 for 512.)
+// Entries that all lie in one part are the work of its workgroup, up to the tree's root, and no other arrives: 8.4 and 12.3 us
+// for 512 and 1024 of a million slots, where one workgroup takes 8.1 and 12.0 and a walk to the part's root, the arrivals and the
+// nodes above 9.6 and 14.1.
+// It pays from 384 entries on: 7.2 against 8.9 us over a million slots, 6.4 against 6.1 over 10,000, where 512 and 1024
+// take 6.3 and 6.7 against 6.6 and 9.6.  Over 4096 slots or fewer it gains nothing below 1024.
 constexpr int PU_PART_BITS = 5, PU_PARTS = 1 << PU_PART_BITS;
 constexpr int PU_PARTS_FROM = 384, PU_PARTS_BITS = 13;   // entries; bits of the slots' numbers
 template <bool PARTS>
@@ -1358,8 +1360,10 @@ __global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A, int levels
     __shared__ float sh[16];
     float *const tree = A.tree;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6, part = blockIdx.x;
-    int my = -1;
+    int my = -1, of_first = 0;
     float p = 0.f;
+    // (an atomic load, so that it stays here: the compiler would move it behind the others, another trip to memory)
+    if constexpr (PARTS) of_first = __hip_atomic_load(A.idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (tid < A.n) {
         const int v = A.idx[tid];
         p = (float)((double)fabsf(A.td_abs[tid]) + (double)A.eps);
@@ -1371,28 +1375,39 @@ __global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A, int levels
         pmax = block_max_1024(pmax, sh);   // contains barriers
         if (tid == 0) tree[2 * A.L] = fmaxf(tree[2 * A.L], pmax);
     };
+    bool alone = false;
     if constexpr (PARTS) {
-        if (part == 0) raise_max();   // uniform for the workgroup
-        if (A.leaves_fixed) return;   // uniform for the launch
         // this part's entries, in the list's order, to the first threads; the waves that are left without one leave, and
-        // barriers no longer count them
+        // barriers no longer count them.  Every workgroup learns whether all entries lie in the part of the list's first one
+        constexpr int ELSEWHERE = 1 << 16;
         __shared__ int found[16], own[1024];
         __shared__ float own_p[1024];
-        const bool mine = my >= 0 && my >> levels == part;
-        const uint64_t here = __ballot(mine);
-        if (lane == 0) found[wave] = __popcll(here);
+        const int its = my >= 0 ? my >> levels : -1, first_part = of_first >= 0 ? of_first >> levels : -1;
+        const bool mine = its == part;
+        const uint64_t here = __ballot(mine), elsewhere = __ballot(its >= 0 && its != first_part);
+        if (lane == 0) found[wave] = __popcll(here) + (elsewhere ? ELSEWHERE : 0);
+        if (part == 0) {   // uniform for the workgroup
+            pmax = wave_max(pmax);
+            if (lane == 0) sh[wave] = pmax;
+        }
         sync_lds();
-        int m = 0, at = __popcll(here & ((1ull << lane) - 1));
-        for (int w = 0; w < nw; ++w) {
-            if (w == wave) at += m;
-            m += found[w];
+        // (a lane per wave: short code, which these few us fetch as they go)
+        const int of_wave = (lane & 15) < nw ? found[lane & 15] : 0;
+        const int sum = __builtin_amdgcn_readfirstlane(wave_sum<8>(of_wave));
+        const int before = wave_sum<8>((lane & 15) < wave ? of_wave : 0);
+        const int m = sum & (ELSEWHERE - 1), at = (before & (ELSEWHERE - 1)) + __popcll(here & ((1ull << lane) - 1));
+        alone = sum < ELSEWHERE;
+        if (part == 0 && wave == 0) {
+            pmax = wave_max(lane < nw ? sh[lane] : 0.f);
+            if (lane == 0) tree[2 * A.L] = fmaxf(tree[2 * A.L], pmax);
         }
         if (mine) {
             own[at] = my;
             own_p[at] = p;
         }
         sync_lds();
-        if (wave > 0 && 64 * wave >= m) return;
+        if ((alone || wave > 0) && 64 * wave >= m) return;
+        if (alone) levels = A.levels;   // nobody to wait for
         my = tid < m ? own[tid] : -1;
         p = tid < m ? own_p[tid] : 0.f;
     } else sync_lds();
@@ -1411,6 +1426,7 @@ __global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A, int levels
     float v[1] = {(float)pow((double)p, (double)A.alpha)};
     tree_walk<1>(tree, node, v, walk, levels);
     if constexpr (PARTS) {
+        if (alone) return;
         // every walker has the subtree's root
         if (walk[0]) publish_word(tree + node[0], v[0]);
         words_acknowledged();
@@ -1443,7 +1459,7 @@ inline void launch_per_update(const PerUpdateArgs &A, unsigned *count, hipStream
     const int threads = (A.n + 63) / 64 * 64;
     int bits = 0;   // of a slot's number: at most A.levels
     while ((1l << bits) < A.size) ++bits;
-    if (A.n >= PU_PARTS_FROM && bits >= PU_PARTS_BITS) k_per_update<true><<<PU_PARTS, threads, 0, st>>>(A, bits - PU_PART_BITS, count);
+    if (!A.leaves_fixed && A.n >= PU_PARTS_FROM && bits >= PU_PARTS_BITS) k_per_update<true><<<PU_PARTS, threads, 0, st>>>(A, bits - PU_PART_BITS, count);
     else k_per_update<false><<<1, threads, 0, st>>>(A, A.levels, count);
 }
 

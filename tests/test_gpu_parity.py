@@ -460,6 +460,36 @@ def test_per_update_parts(dq, orc, cap, n, spread):
     m.close()
 
 
+# entries of one subtree (its workgroup walks to the root alone), of two (the nodes above are the last arrival's), of none, by turns,
+# so that each kind finds the arrival counter as the others left it; the list's first entry valid or not
+def test_per_update_entries_of_few_parts(dq, orc):
+    cap, n = 1 << 18, 1024
+    part = cap // 32
+    m = dq.Dqn(dq.make_config(replay_capacity=cap, max_batch=32))
+    pri = synth.exp_priorities(9, cap)
+    m.per_fill(dev(pri))
+    tree_ref = orc.tree_build(pri.numpy(), m.L, float(np.float32(0.6)))
+    rng = np.random.default_rng(11)
+    mp = 1.0
+    for parts in ((0,), (31,), (5, 6), (17,), (0, 31), (), (16,), tuple(range(32))):
+        for first in (0, -1, cap):   # 0: the list as it is; otherwise an entry to be skipped comes first
+            print("case few parts", parts, first, flush=True)
+            idx = np.full(n, -1, np.int32)
+            if parts:
+                idx = (part * rng.choice(parts, n) + rng.integers(0, part, n)).astype(np.int32)
+            if first:
+                idx[0] = first
+            td = rng.standard_exponential(n).astype(np.float32)
+            td[7] = np.nan
+            m.per_update(dev(idx), dev(td))
+            ok = (idx >= 0) & (idx < cap) & np.isfinite(td)
+            if ok.any():
+                mp = orc.per_update(tree_ref, cap, idx[ok], td[ok], float(np.float32(0.6)), float(np.float32(1e-6)), mp)
+            assert np.array_equal(m.tree.cpu().numpy()[1:], tree_ref[1:])
+            assert float(m.max_priority) == np.float32(mp)
+    m.close()
+
+
 def test_per_update_parts_of_a_partly_filled_ring(dq, orc):
     """The subtrees are those of the slots that are filled; the levels above them are one path."""
     cap, filled, n = 1 << 18, 20000, 700
@@ -601,7 +631,7 @@ def test_replay_step_settings(dq, orc, name, B, prec, alpha, strat):
         raise AssertionError("three draw seeds in a row hit a bucket boundary")
 
 
-@pytest.mark.parametrize("prec,B,n", [(0, 32, 20000), (1, 512, 20000), (0, 7, 777)])
+@pytest.mark.parametrize("prec,B,n", [(0, 32, 20000), (1, 512, 20000), (0, 7, 777), (0, 640, 20000)])
 def test_uniform_replay_without_the_tree(dq, orc, prec, B, n):
     """Priority exponent 0 (the settings without prioritized replay of the paper's performance
     figure) over a bulk-filled tree: sampling reads no tree node and the priority update writes none.
