@@ -1349,10 +1349,12 @@ __device__ __forceinline__ void per_update_resume(const PerUpdateArgs &A, int do
 // Entries that all lie in one part are the work of its workgroup, up to the tree's root, and no other arrives: 8.4 and 12.3 us
 // for 512 and 1024 of a million slots, where one workgroup takes 8.1 and 12.0 and a walk to the part's root, the arrivals and the
 // nodes above 9.6 and 14.1.
-// It pays from 384 entries on: 7.2 against 8.9 us over a million slots, 6.4 against 6.1 over 10,000, where 512 and 1024
-// take 6.3 and 6.7 against 6.6 and 9.6.  Over 4096 slots or fewer it gains nothing below 1024.
+// It pays from 384 entries on over more than 2^14 slots (7.2 against 8.9 us over a million, 6.4 against 6.5 over 20,000), from 512
+// over 2^13 to 2^14 (6.3 against 6.6 over 10,000; 384: 6.2 against 6.1) and from 640 over 2^12 to 2^13 (6.4 against 6.5 over 4097,
+// 6.3 against 6.9 over 8192; 512: 6.36 against 6.10, 6.20 against 6.32).
 constexpr int PU_PART_BITS = 5, PU_PARTS = 1 << PU_PART_BITS;
-constexpr int PU_PARTS_FROM = 384, PU_PARTS_BITS = 13;   // entries; bits of the slots' numbers
+constexpr int PU_PARTS_BITS = 13;   // of the slots' numbers, at least
+constexpr int pu_parts_from(int bits) { return bits >= 15 ? 384 : bits == 14 ? 512 : 640; }   // entries
 template <bool PARTS>
 __global__ __launch_bounds__(1024) void k_per_update(PerUpdateArgs A, int levels /*of a workgroup's subtree*/, unsigned *count)
 {
@@ -1459,7 +1461,7 @@ inline void launch_per_update(const PerUpdateArgs &A, unsigned *count, hipStream
     const int threads = (A.n + 63) / 64 * 64;
     int bits = 0;   // of a slot's number: at most A.levels
     while ((1l << bits) < A.size) ++bits;
-    if (!A.leaves_fixed && A.n >= PU_PARTS_FROM && bits >= PU_PARTS_BITS) k_per_update<true><<<PU_PARTS, threads, 0, st>>>(A, bits - PU_PART_BITS, count);
+    if (!A.leaves_fixed && bits >= PU_PARTS_BITS && A.n >= pu_parts_from(bits)) k_per_update<true><<<PU_PARTS, threads, 0, st>>>(A, bits - PU_PART_BITS, count);
     else k_per_update<false><<<1, threads, 0, st>>>(A, A.levels, count);
 }
 

@@ -432,11 +432,13 @@ def test_tree_fill_sample_update(dq, orc, cap, n, B, strat):
     m.close()
 
 
-# one workgroup, or from 384 entries and more than 4096 slots on one per subtree: both sides of the rule, entries spread over
-# all subtrees, over a few slots or over one, a slot range that is no power of two, repeated and skipped entries
+# one workgroup, or one per subtree (from 384 entries over more than 16,384 slots, from 512 over more than 8192, from 640 over more
+# than 4096): both sides of the rule, entries spread over all subtrees, over a few slots or over one, a slot range that is no power
+# of two, repeated and skipped entries
 @pytest.mark.parametrize("cap,n,spread", [(5, 1, 5), (37, 64, 37), (1000, 129, 1000), (4096, 384, 4096), (4097, 383, 4097), (4097, 384, 4097),
                                           (70000, 512, 600), (300000, 513, 300000), (1 << 20, 1000, 1 << 20), (1 << 20, 1024, 1),
-                                          (1 << 20, 1024, 1400)])
+                                          (1 << 20, 1024, 1400), (4096, 640, 4096), (4097, 639, 4097), (4097, 640, 4097), (8192, 1024, 8192),
+                                          (8193, 511, 8193), (8193, 512, 8193), (16384, 512, 16384), (16385, 383, 16385), (16385, 384, 16385)])
 def test_per_update_parts(dq, orc, cap, n, spread):
     print("case update", cap, n, spread, flush=True)
     m = dq.Dqn(dq.make_config(replay_capacity=cap, max_batch=32))
