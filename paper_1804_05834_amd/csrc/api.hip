@@ -163,7 +163,7 @@ struct dqn_ctx {
     int num_cu = 256;  // compute units of the device
     // bf16: the conv layers run as one launch of pipelined waves (gbf::pipe) from this many samples per launch on;
     // INT_MAX: never (the launch needs 155 KB of LDS per workgroup, granted at initialisation)
-    int conv12_min = INT32_MAX;
+    int pipe_min = INT32_MAX;
     bool rows_fit = false;   // fp32: the conv layers of many rows with a layer's weights in LDS (rows)
     bool conv123 = false;   // bf16: conv1 to conv3 as one launch for few samples (gbf::c123)
     float *gp4 = nullptr, *gp5 = nullptr;   // where fc1's and the head's weight gradients are written: inside `grads`
@@ -409,17 +409,17 @@ Conv123Plan conv123_plan(int samples, int num_cu)
     return P;
 }
 // bf16: the three conv layers' launch for few samples (gbf::c123), or for many (gbf::pipe)?
-// One unit per workgroup and a launch less: ahead while the samples of a training launch have a CU each (batch 32: 57.5
-// against 68.7 us per step, 77: 62.5 against 73.2, 85: 62.7 against 73.4; at 86 to 170, several units per workgroup, equal), acting,
-// which draws nothing, up to two (one observation: 14.4 against 23.0 us, 256: 20.7 against 28.8, 512: 31.4 against 36.3; at 1024,
-// four units per workgroup, 1.5 us behind).
-bool piped3(const dqn_ctx *c, long samples, int npass) { return c->conv123 && samples <= (npass == 1 ? 2 : 1) * c->num_cu; }
+// One unit per workgroup: ahead while the samples of a launch have a CU each (a step of 32: 56.5 against 65.1 us, of 77 61.1
+// against 69.5, of 85 61.6 against 69.9; acting on one observation 12.9 against 24.0, on 64 15.8 against 23.0, on 256 19.8 against
+// 25.6).  A form with several units per workgroup was behind at once: a step of 86 78.9 against 71.2, of 170 85.3 against 77.9,
+// acting on 257 27.8 against 26.8, on 400 30.4 against 29.9, on 1024 45.0 against 39.4.
+bool fused_few(const dqn_ctx *c, long samples) { return c->conv123 && samples <= c->num_cu; }
 // bf16: the conv layers as one launch of pipelined waves, one workgroup per CU, for passes of n[0..npass) samples?
 bool pipe_fits(const dqn_ctx *c, const int *n, int npass, bool draw)
 {
     long rows = 0;
     for (int i = 0; i < npass; ++i) rows += n[i];
-    if (rows < c->conv12_min || npass > c->num_cu) return false;
+    if (rows < c->pipe_min || npass > c->num_cu) return false;
     const int grid_pipe = (int)std::min<long>(rows, c->num_cu);
     for (int i = 0; i < npass; ++i) {
         const int wgs = (int)((long)grid_pipe * (i + 1) / npass - (long)grid_pipe * i / npass);
@@ -460,7 +460,7 @@ bool in_kernel_draw_fits(const dqn_ctx *c, int B)
         return np == 3 ? conv1_plan_f32(3 * B, c->num_cu).draw_fits : conv123_plan((3 - np) * B, c->num_cu).draw_fits;
     }
     const int n[3] = {B, B, B};
-    return piped3(c, 3l * B, 3) || pipe_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
+    return fused_few(c, 3l * B) || pipe_fits(c, n, 3, true) || conv1_plan_bf16(3 * B, c->num_cu).draw_fits;
 }
 
 // A tiled launch's segments for the launch by rows: the same share of the workgroups each (their rows are the same number)
@@ -656,8 +656,8 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
     long rows = 0;
     for (int i = 0; i < npass; ++i) { row0[i] = rows; rows += pass[i].n; }
 
-    const bool fused3 = piped3(c, rows, npass);
-    if (fused3) {
+    const bool few = fused_few(c, rows);
+    if (few) {
         const Conv123Plan plan = conv123_plan((int)rows, c->num_cu);
         c123::Args A{};
         A.nseg = npass;
@@ -671,20 +671,19 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
                                  (int)row0[i] * plan.parts};
         }
         for (int i = npass; i < 3; ++i) A.seg[i] = A.seg[0];
-        A.units = (int)rows * plan.parts;
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
         A.clear = few_rows ? w.arrivals : nullptr;
+        const dim3 grid((int)rows * plan.parts);   // a unit each: no more than there are compute units
         launch(c, "conv123_fwd", st, [&] {
-            if (plan.r3 == 1) c123::k_conv123_fwd<1, false><<<dim3(plan.grid), 512, c123::Geo<1>::LDS, st>>>(A);
-            else if (plan.r3 == 4) c123::k_conv123_fwd<4, false><<<dim3(plan.grid), 512, c123::Geo<4>::LDS, st>>>(A);
-            else if (A.units <= plan.grid) c123::k_conv123_fwd<7, false><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
-            else c123::k_conv123_fwd<7, true><<<dim3(plan.grid), 512, c123::Geo<7>::LDS, st>>>(A);
+            if (plan.r3 == 1) c123::k_conv123_fwd<1><<<grid, 512, c123::Geo<1>::LDS, st>>>(A);
+            else if (plan.r3 == 4) c123::k_conv123_fwd<4><<<grid, 512, c123::Geo<4>::LDS, st>>>(A);
+            else c123::k_conv123_fwd<7><<<grid, 512, c123::Geo<7>::LDS, st>>>(A);
         });
     }
     // ... or as a pipeline of waves, one workgroup per CU
     const int pass_n[3] = {pass[0].n, npass > 1 ? pass[1].n : 0, npass > 2 ? pass[2].n : 0};
-    const bool piped = !fused3 && pipe_fits(c, pass_n, npass, draw != nullptr);
+    const bool piped = !few && pipe_fits(c, pass_n, npass, draw != nullptr);
     const int grid_pipe = (int)std::min<long>(rows, c->num_cu);
     if (piped) {
         pipe::Args A{};
@@ -705,7 +704,7 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.draw = draw != nullptr;
         if (draw) A.samp = *draw;
         launch(c, "conv123_fwd", st, [&] { pipe::k_conv_fwd_pipe<<<dim3(grid_pipe), 512, pipe::LDS_BYTES, st>>>(A); });
-    } else if (!fused3)
+    } else if (!few)
     {  // conv1: persistent waves, strips of the frames staged in LDS (read from the ring in ring mode)
         c1::FwdArgs A{};
         A.nseg = npass;
@@ -744,12 +743,12 @@ int32_t forward_trunk_bf16(dqn_ctx *c, const Workspace &w, const Pass *pass, int
         A.total = first;
         return std::min(first, 2 * c->num_cu);
     };
-    if (!piped && !fused3) {
+    if (!piped && !few) {
         ps::Args A{};
         const int grid = per_sample(A, act1, net::A1, net::C2W, net::C2B, act2, net::A2);
         launch(c, "conv2_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G2><<<dim3(grid), 256, 0, st>>>(A); });
     }
-    if (!piped && !fused3) {
+    if (!piped && !few) {
         ps::Args A{};
         const int grid = per_sample(A, act2, net::A2, net::C3W, net::C3B, act3, net::A3);
         launch(c, "conv3_fwd", st, [&] { ps::k_conv_fwd_ps<ps::G3><<<dim3(grid), 256, 0, st>>>(A); });
@@ -819,7 +818,7 @@ int32_t act_on(dqn_ctx *c, const Workspace &w, const char *where, const uint8_t 
     long ss = 0;
     const bool bf16 = c->cfg.precision == 1;
     // fc1 and the head in one launch, where the conv layers are one that clears the counter
-    const bool few = E <= misc::FEW_ROWS && (bf16 ? piped3(c, E, 1) : c->split);
+    const bool few = E <= misc::FEW_ROWS && (bf16 ? fused_few(c, E) : c->split);
     int32_t rc = forward_trunk(c, w, &p, 1, &ns, &ss, st, nullptr, few);
     if (rc) return rc;
     misc::HeadActArgs H{w.f1part, ns, ss, E, c->cfg.num_actions, c->cfg.dueling, c->theta + net::F1B,
@@ -1370,10 +1369,9 @@ int32_t dqn_init(dqn_ctx **out, const dqn_config *cfg, const dqn_buffers *b, voi
         // DQN_CONV12_MIN_SAMPLES in the environment moves the number of samples (of all passes of a launch) from which
         // the conv layers are one launch of pipelined waves, without the launch for few samples; a huge value: never
         const char *m = std::getenv("DQN_CONV12_MIN_SAMPLES");
-        if (granted(gbf::pipe::k_conv_fwd_pipe, gbf::pipe::LDS_BYTES)) c->conv12_min = m && m[0] ? std::atoi(m) : 8;
-        c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1, false>, gbf::c123::Geo<1>::LDS) &&
-                     granted(gbf::c123::k_conv123_fwd<4, false>, gbf::c123::Geo<4>::LDS) &&
-                     granted(gbf::c123::k_conv123_fwd<7, false>, gbf::c123::Geo<7>::LDS) && granted(gbf::c123::k_conv123_fwd<7, true>, gbf::c123::Geo<7>::LDS);
+        if (granted(gbf::pipe::k_conv_fwd_pipe, gbf::pipe::LDS_BYTES)) c->pipe_min = m && m[0] ? std::atoi(m) : 8;
+        c->conv123 = !(m && m[0]) && granted(gbf::c123::k_conv123_fwd<1>, gbf::c123::Geo<1>::LDS) &&
+                     granted(gbf::c123::k_conv123_fwd<4>, gbf::c123::Geo<4>::LDS) && granted(gbf::c123::k_conv123_fwd<7>, gbf::c123::Geo<7>::LDS);
         // DQN_FUSED_BWD=0 in the environment keeps conv1's weight gradient a launch of its own
         m = std::getenv("DQN_FUSED_BWD");
         c->fused_bwd = !(m && m[0] == '0') && granted(k_conv21_bwd_pu, gbf::dps::FUSED_LDS);

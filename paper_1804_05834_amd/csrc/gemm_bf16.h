@@ -2184,14 +2184,13 @@ __global__ __launch_bounds__(512) void k_conv_fwd_pipe(Args A)
 // A unit is the part of a sample that yields R3 of conv3's seven output rows (see sp::k_conv123_fwd, the fp32
 // form of this kernel: same units, same phases).  One workgroup of eight waves takes a unit through all
 // three layers in LDS, phase by phase, every wave in the same phase; the weights stay in registers (200),
-// taken once per workgroup from the packed copy.  A workgroup that takes several whole samples (R3 = 7, MANY) spills 37 registers
-// beside the next one's pixels; with a unit each, the form without the next one spills none and does not fetch its own pixels
-// twice (conv launch of a step at 77: 14.9 -> 12.9 us, of 256 observations 15.6 -> 14.2).  The images are laid out for the lanes
+// from the packed copy.  A workgroup has one unit (one that took several whole samples spilled 37 registers beside the next
+// one's pixels: conv launch of a step at 77 14.9 us against 12.9).  The images are laid out for the lanes
 // that LDS serves together (Geo; at 77 12.9 -> 11.8).  16x16x32 instructions, transposed tiles:
 //   conv1   wave = every eighth tile of 16 pixels, all 32 channels: a pixel fragment serves two products
 //   conv2/3 wave = 16 channels, half of the tiles: the sum over the taps stays in one wave
-// pipe::k_conv_fwd_pipe overlaps conv1 of one sample with conv2 of another and is as fast per sample once it runs, but it
-// takes a second launch for conv3 and a longer start.
+// pipe::k_conv_fwd_pipe overlaps the layers of different samples and is faster per sample once it runs, but its first
+// sample takes longer: a layer is the work of two or four waves there (fused_few in api.hip has both sides).
 // ===========================================================================
 namespace c123 {
 struct Seg {
@@ -2206,12 +2205,10 @@ struct Seg {
 struct Args {
     Seg seg[3];
     int nseg;
-    int units;
     int draw;
     misc::SampleArgs samp;
     unsigned *clear;              // the arrival counters of a later launch, set to 0 here, or nullptr
 };
-constexpr int MAX_UNITS = 96;
 template <int R3> struct Geo {
     static constexpr int PARTS = (7 + R3 - 1) / R3;
     static constexpr int R2 = R3 + 2, R1 = 2 * R3 + 6, PR = 4 * R1 + 4;
@@ -2233,13 +2230,13 @@ template <int R3> struct Geo {
         return r ? min(x, R2 - 1) * 9 + 8 : (R2 - 1) * 9 + x;          // the last row and the last column
     }
     static __device__ __forceinline__ int position3(int t, int n) { return min(2 * t + (n >> 3), R3 - 1) * 7 + min(n & 7, 6); }
-    static constexpr int TAB = (2 * MAX_UNITS + 4 + 160) * 4;   // slots, leaf values, total; biases
+    static constexpr int TAB = (4 + 160) * 4;   // slot, leaf value, total; biases
     static constexpr int LDS = PXB + I1B + I2B + TAB;
     static_assert(PR * 84 % 16 == 0, "LDS layout");
 };
 
-// MANY: a workgroup takes one unit after the other; otherwise just one
-template <int R3, bool MANY>
+// Workgroup u takes unit u of the grid's
+template <int R3>
 __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 {
     using G = Geo<R3>;
@@ -2250,24 +2247,27 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     bf16_t *px = reinterpret_cast<bf16_t *>(lds);
     uint8_t *img1 = lds + G::PXB, *img2 = img1 + G::I1B;
-    int *slots = reinterpret_cast<int *>(img2 + G::I2B);
-    float *leafv = reinterpret_cast<float *>(slots + MAX_UNITS);   // [MAX_UNITS], then the total
-    float *bias = leafv + MAX_UNITS + 4;                           // conv1 [32], conv2 [64], conv3 [64]
+    int *slot_at = reinterpret_cast<int *>(img2 + G::I2B);
+    float *leafv = reinterpret_cast<float *>(slot_at + 1);   // the leaf's value, then the total
+    float *bias = leafv + 3;                                 // conv1 [32], conv2 [64], conv3 [64]
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ct = wave & 3, mh = wave >> 2;
     int tid = threadIdx.x, lane = tid & 63;
-    const int G0 = (int)gridDim.x;
-    const int nu = MANY ? (A.units - (int)blockIdx.x + G0 - 1) / G0 : 1;
     if (A.clear && blockIdx.x == 0) misc::few_clear(A.clear, tid);
-    auto seg_of = [&](int u) { return (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first); };
+    const int u = (int)blockIdx.x, si = (A.nseg > 1 && u >= A.seg[1].first) + (A.nseg > 2 && u >= A.seg[2].first);
     u32x4 raw[G::NPX];
-    auto load_px = [&](int si, int u, int slot) {
+    auto load_px = [&](int slot) {
         const int ul = u - C123_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
         const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
         const uint8_t *f[4];
         const c1::Src src{C123_SEG(si).src.x, C123_SEG(si).src.xs, C123_SEG(si).src.idx, C123_SEG(si).src.cap, C123_SEG(si).src.shift, C123_SEG(si).src.sub};
+        if (src.idx) {   // (tested once: with a test per frame acting on one took 0.2 us longer)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) f[k] = c1::frame_ptr(src, g, slot, k) + row0 * (8 * 84);
+            for (int k = 0; k < 4; ++k) f[k] = c1::frame_ptr(src, g, slot, k) + row0 * (8 * 84);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = src.x + (long)g * src.xs + (long)(k * c1::FR + row0 * (8 * 84));
+        }
 #pragma unroll
         for (int i = 0; i < G::NPX; ++i) {
             int t = tid + 512 * i;
@@ -2277,11 +2277,10 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
             raw[i] = *reinterpret_cast<const u32x4 *>(fp + (t - k * G::CH) * 16);
         }
     };
-    int u = (int)blockIdx.x, si = seg_of(u), sw = si;
     const bool ring = A.seg[0].src.idx != nullptr;
     v8bf w1[8][2], w2[16], w3[18];
-    auto load_w = [&](int s) {
-        const v8bf *p = reinterpret_cast<const v8bf *>(C123_SEG(s).w) + lane;
+    {
+        const v8bf *p = reinterpret_cast<const v8bf *>(C123_SEG(si).w) + lane;
 #pragma unroll
         for (int k = 0; k < 8; ++k) { w1[k][0] = p[k * 64]; w1[k][1] = p[(8 + k) * 64]; }
         const v8bf *p2 = p + sp::B_W2 / 8 + ct * 16 * 64, *p3 = p + sp::B_W3 / 8 + ct * 18 * 64;
@@ -2289,204 +2288,179 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
         for (int k = 0; k < 16; ++k) w2[k] = p2[k * 64];
 #pragma unroll
         for (int k = 0; k < 18; ++k) w3[k] = p3[k * 64];
-    };
-    load_w(si);
+    }
     if (ring) {
-        if (A.draw) {
-#pragma unroll 1
-            for (int k = 2 * wave; k < nu; k += 16) {
-                const int kb = k + 1 < nu ? k + 1 : k;
-                const int ga = (u + k * G0) / G::PARTS, gb = (u + kb * G0) / G::PARTS, n = A.seg[0].n;
-                const int jj[2] = {ga % n, gb % n};
-                long sl[2];
-                float leaf[2];
-                const float total = misc::per_sample_walk<2>(A.samp, jj, lane, sl, leaf);
+        if (wave == 0) {
+            const int j[1] = {u / G::PARTS % A.seg[0].n};
+            if (A.draw) {
+                long sl[1];
+                float leaf[1];
+                const float total = misc::per_sample_walk<1>(A.samp, j, lane, sl, leaf);
                 if (lane == 0) {
-                    slots[k] = (int)sl[0];
-                    slots[kb] = (int)sl[1];
-                    leafv[k] = leaf[0];
-                    leafv[kb] = leaf[1];
-                    if (k == 0) leafv[MAX_UNITS] = total;
+                    *slot_at = (int)sl[0];
+                    leafv[0] = leaf[0];
+                    leafv[1] = total;
                 }
-            }
-        } else {
-            for (int k = tid; k < nu; k += 512) slots[k] = A.seg[0].src.idx[(u + k * G0) / G::PARTS % A.seg[0].n];
+            } else if (lane == 0) *slot_at = A.seg[0].src.idx[j[0]];
         }
         sync_lds();
     }
-    load_px(si, u, ring ? slots[0] : 0);
-    if (A.draw && wave == 7)
-        for (int k = lane; k < nu; k += 64) {
-            const int uk = u + k * G0;
-            if (uk < A.seg[0].n * G::PARTS && uk % G::PARTS == 0)
-                misc::per_sample_emit(A.samp, uk / G::PARTS, slots[k], leafv[MAX_UNITS], leafv[k]);
-        }
+    load_px(ring ? *slot_at : 0);
+    if (A.draw && wave == 7 && lane == 0 && u < A.seg[0].n * G::PARTS && u % G::PARTS == 0)
+        misc::per_sample_emit(A.samp, u / G::PARTS, *slot_at, leafv[1], leafv[0]);
 
-    for (int k = 0; k < nu; ++k) {
-        asm volatile("" : "+v"(tid));   // opaque: no lane address of a later phase is formed out here
-        lane = tid & 63;
-        const int n16 = lane & 15, kg = lane >> 4;
-        if (MANY && si != sw) load_w(si);   // the first unit of another network
-        if (k == 0 || si != sw) {
-            // (read after the next barrier; the unit before has left its last phase that reads them)
-            if (MANY && k > 0) sync_lds();
-            if (tid < 160) bias[tid] = tid < 32 ? C123_SEG(si).b1[tid] : tid < 96 ? C123_SEG(si).b2[tid - 32] : C123_SEG(si).b3[tid - 96];
-            sw = si;
-        }
-        const int ul = u - C123_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
-        const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
-        const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one
+    asm volatile("" : "+v"(tid));   // opaque: no lane address of a later phase is formed further up
+    lane = tid & 63;
+    const int n16 = lane & 15, kg = lane >> 4;
+    if (tid < 160) bias[tid] = tid < 32 ? C123_SEG(si).b1[tid] : tid < 96 ? C123_SEG(si).b2[tid - 32] : C123_SEG(si).b3[tid - 96];
+    // (load_px's once more; formed ahead of the weights' requests they delay those, acting on one 0.2 us)
+    const int ul = u - C123_SEG(si).first, g = ul / G::PARTS, part = ul % G::PARTS;
+    const int row0 = part * R3 < 7 - R3 ? part * R3 : 7 - R3;
+    const int rowp = part == 0 ? -32 : (part - 1) * R3;   // first conv3 row of the part before this one
 #pragma unroll
-        for (int i = 0; i < G::NPX; ++i) {
-            const int t = tid + 512 * i;
-            if (t < 4 * G::CH) {
-                uint4 *d = reinterpret_cast<uint4 *>(px + t * 16);
-                d[0] = cvt8_u8(raw[i].x, raw[i].y);
-                d[1] = cvt8_u8(raw[i].z, raw[i].w);
-            }
+    for (int i = 0; i < G::NPX; ++i) {
+        const int t = tid + 512 * i;
+        if (t < 4 * G::CH) {
+            uint4 *d = reinterpret_cast<uint4 *>(px + t * 16);
+            d[0] = cvt8_u8(raw[i].x, raw[i].y);
+            d[1] = cvt8_u8(raw[i].z, raw[i].w);
         }
-        bf16_t *const y1 = C123_SEG(si).y1, *const y2 = C123_SEG(si).y2;
-        sync_lds();
+    }
+    bf16_t *const y1 = C123_SEG(si).y1, *const y2 = C123_SEG(si).y2;
+    sync_lds();
 
-        // ---- conv1
+    // ---- conv1
 #pragma unroll 1
-        for (int t = wave; t < G::T1; t += 8) {
-            const int m = 16 * t + n16, mc = m < G::M1 ? m : G::M1 - 1;
-            const int y = mc / 20, x = mc - 20 * y;
-            // A step takes four columns (4 xh ..) of the kernel rows 2 kg, 2 kg + 1 of a frame, as in pipe::run_producer: the same
-            // sums in the same order, so both launches leave the same bits.  Two-address reads put such a pair into
-            // four consecutive registers; they are invisible to the compiler's wait counting.
-            typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-            const uint32_t addr = (uint32_t)(uintptr_t)(px + (4 * y + 2 * kg) * 84 + 4 * x);
-            auto pixels = [&](int f, v4u &q0, v4u &q1) {
-                const uint32_t af = addr + f * (G::PR * 84 * 2);
-                asm volatile("ds_read2_b64 %0, %1 offset0:0 offset1:21" : "=v"(q0) : "v"(af));
-                asm volatile("ds_read2_b64 %0, %1 offset0:1 offset1:22" : "=v"(q1) : "v"(af));
-            };
-            v4f a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
-            v4u q[2][2];
-            pixels(0, q[0][0], q[0][1]);
+    for (int t = wave; t < G::T1; t += 8) {
+        const int m = 16 * t + n16, mc = m < G::M1 ? m : G::M1 - 1;
+        const int y = mc / 20, x = mc - 20 * y;
+        // A step takes four columns (4 xh ..) of the kernel rows 2 kg, 2 kg + 1 of a frame, as in pipe::run_producer: the same
+        // sums in the same order, so both launches leave the same bits.  Two-address reads put such a pair into
+        // four consecutive registers; they are invisible to the compiler's wait counting.
+        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+        const uint32_t addr = (uint32_t)(uintptr_t)(px + (4 * y + 2 * kg) * 84 + 4 * x);
+        auto pixels = [&](int f, v4u &q0, v4u &q1) {
+            const uint32_t af = addr + f * (G::PR * 84 * 2);
+            asm volatile("ds_read2_b64 %0, %1 offset0:0 offset1:21" : "=v"(q0) : "v"(af));
+            asm volatile("ds_read2_b64 %0, %1 offset0:1 offset1:22" : "=v"(q1) : "v"(af));
+        };
+        v4f a0 = {0, 0, 0, 0}, a1 = {0, 0, 0, 0};
+        v4u q[2][2];
+        pixels(0, q[0][0], q[0][1]);
 #pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                v4u(&c)[2] = q[f & 1], (&nx)[2] = q[(f & 1) ^ 1];
-                if (f < 3) {
-                    pixels(f + 1, nx[0], nx[1]);
-                    asm volatile("s_waitcnt lgkmcnt(2)" : "+v"(c[0]), "+v"(c[1]));
-                } else {
-                    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(c[0]), "+v"(c[1]));
-                }
-                __builtin_amdgcn_sched_barrier(0);
+        for (int f = 0; f < 4; ++f) {
+            v4u(&c)[2] = q[f & 1], (&nx)[2] = q[(f & 1) ^ 1];
+            if (f < 3) {
+                pixels(f + 1, nx[0], nx[1]);
+                asm volatile("s_waitcnt lgkmcnt(2)" : "+v"(c[0]), "+v"(c[1]));
+            } else {
+                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(c[0]), "+v"(c[1]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int xh = 0; xh < 2; ++xh) {
-                    a0 = mfma16(w1[2 * f + xh][0], __builtin_bit_cast(v8bf, c[xh]), a0);
-                    a1 = mfma16(w1[2 * f + xh][1], __builtin_bit_cast(v8bf, c[xh]), a1);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+            for (int xh = 0; xh < 2; ++xh) {
+                a0 = mfma16(w1[2 * f + xh][0], __builtin_bit_cast(v8bf, c[xh]), a0);
+                a1 = mfma16(w1[2 * f + xh][1], __builtin_bit_cast(v8bf, c[xh]), a1);
             }
-            const v4f b1a = *reinterpret_cast<const v4f *>(bias + 8 * kg), b1b = *reinterpret_cast<const v4f *>(bias + 8 * kg + 4);
-            constexpr float sc = 1.0f / 255.0f;
-            v4f v0, v1;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                v0[r] = fmaxf(a0[r] * sc + b1a[r], 0.f);
-                v1[r] = fmaxf(a1[r] * sc + b1b[r], 0.f);
-            }
-            if (m < G::M1) {
-                const uint2 lo = pack4(v0.x, v0.y, v0.z, v0.w), hi = pack4(v1.x, v1.y, v1.z, v1.w);
-                const uint4 o = {lo.x, lo.y, hi.x, hi.y};
-                *reinterpret_cast<uint4 *>(img1 + y * G::B1 + ((x & 1) * 10 + (x >> 1)) * G::P1 + kg * 16) = o;
-                if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
-                    *reinterpret_cast<uint4 *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 8 * kg) = o;
-            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // the next unit's pixels (behind the last unit its own once more)
-        const int kn = k + 1 < nu ? k + 1 : k, un = (int)blockIdx.x + kn * G0, sn = seg_of(un);
-        if constexpr (MANY) load_px(sn, un, ring ? slots[kn] : 0);
-        sync_lds();
-        // ---- conv2: tiles T2 mh .. of 16 positions, channels 16 ct ..
-        {
-            constexpr int T = G::T2;
-            const uint8_t *pa[T];
-            int pos[T];
+        const v4f b1a = *reinterpret_cast<const v4f *>(bias + 8 * kg), b1b = *reinterpret_cast<const v4f *>(bias + 8 * kg + 4);
+        constexpr float sc = 1.0f / 255.0f;
+        v4f v0, v1;
 #pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int m = pos[t] = G::position2(T * mh + t, n16), y = m / 9, x = m - 9 * y;
-                pa[t] = img1 + 2 * y * G::B1 + x * G::P1 + kg * 16;
-            }
-            v4f acc[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) acc[t] = v4f{0, 0, 0, 0};
-            v8bf f[2][T];
-            auto rd = [&](int s) {   // kernel row s / 4, column s % 4
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s >> 2) * G::B1 + ((s & 1) * 10 + ((s >> 1) & 1)) * G::P1);
-            };
-            rd(0);
-#pragma unroll
-            for (int s = 0; s < 16; ++s) {
-                if (s < 15) rd(s + 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < T; ++t) acc[t] = mfma16(w2[s], f[s & 1][t], acc[t]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const v4f b2 = *reinterpret_cast<const v4f *>(bias + 32 + 16 * ct + 4 * kg);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int m = pos[t], y = m / 9, x = m - 9 * y;
-                v4f v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b2[r], 0.f);
-                const uint2 o = pack4(v.x, v.y, v.z, v.w);   // (lanes that share a position store the same bits)
-                *reinterpret_cast<uint2 *>(img2 + y * G::B2 + x * G::P2 + ct * 32 + kg * 8) = o;
-                if (y2 && row0 + y >= rowp + G::R2)
-                    *reinterpret_cast<uint2 *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + 16 * ct + 4 * kg) = o;
-            }
+        for (int r = 0; r < 4; ++r) {
+            v0[r] = fmaxf(a0[r] * sc + b1a[r], 0.f);
+            v1[r] = fmaxf(a1[r] * sc + b1b[r], 0.f);
         }
-        sync_lds();
-        // ---- conv3
-        {
-            constexpr int T = G::T3;
-            const uint8_t *pa[T];
-            int pos[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int m = pos[t] = G::position3(T * mh + t, n16), y = m / 7, x = m - 7 * y;
-                pa[t] = img2 + y * G::B2 + x * G::P2 + kg * 16;
-            }
-            v4f acc[T];
-#pragma unroll
-            for (int t = 0; t < T; ++t) acc[t] = v4f{0, 0, 0, 0};
-            v8bf f[2][T];
-            auto rd = [&](int s) {   // tap s / 2, channel half s % 2
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s / 6) * G::B2 + ((s / 2) % 3) * G::P2 + (s & 1) * 64);
-            };
-            rd(0);
-#pragma unroll
-            for (int s = 0; s < 18; ++s) {
-                if (s < 17) rd(s + 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < T; ++t) acc[t] = mfma16(w3[s], f[s & 1][t], acc[t]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const v4f b3 = *reinterpret_cast<const v4f *>(bias + 96 + 16 * ct + 4 * kg);
-#pragma unroll
-            for (int t = 0; t < T; ++t) {
-                const int m = pos[t], y = m / 7;
-                v4f v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b3[r], 0.f);
-                if (row0 + y >= rowp + R3)
-                    *reinterpret_cast<uint2 *>(C123_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + 16 * ct + 4 * kg) = pack4(v.x, v.y, v.z, v.w);
-            }
+        if (m < G::M1) {
+            const uint2 lo = pack4(v0.x, v0.y, v0.z, v0.w), hi = pack4(v1.x, v1.y, v1.z, v1.w);
+            const uint4 o = {lo.x, lo.y, hi.x, hi.y};
+            *reinterpret_cast<uint4 *>(img1 + y * G::B1 + ((x & 1) * 10 + (x >> 1)) * G::P1 + kg * 16) = o;
+            if (y1 && 2 * row0 + y >= 2 * rowp + G::R1)
+                *reinterpret_cast<uint4 *>(y1 + (long)g * net::A1 + ((2 * row0 + y) * 20 + x) * 32 + 8 * kg) = o;
         }
-        if (!MANY) break;
-        si = sn;
-        u += G0;
+    }
+    sync_lds();
+    // ---- conv2: tiles T2 mh .. of 16 positions, channels 16 ct ..
+    {
+        constexpr int T = G::T2;
+        const uint8_t *pa[T];
+        int pos[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int m = pos[t] = G::position2(T * mh + t, n16), y = m / 9, x = m - 9 * y;
+            pa[t] = img1 + 2 * y * G::B1 + x * G::P1 + kg * 16;
+        }
+        v4f acc[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = v4f{0, 0, 0, 0};
+        v8bf f[2][T];
+        auto rd = [&](int s) {   // kernel row s / 4, column s % 4
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s >> 2) * G::B1 + ((s & 1) * 10 + ((s >> 1) & 1)) * G::P1);
+        };
+        rd(0);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            if (s < 15) rd(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = mfma16(w2[s], f[s & 1][t], acc[t]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const v4f b2 = *reinterpret_cast<const v4f *>(bias + 32 + 16 * ct + 4 * kg);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int m = pos[t], y = m / 9, x = m - 9 * y;
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b2[r], 0.f);
+            const uint2 o = pack4(v.x, v.y, v.z, v.w);   // (lanes that share a position store the same bits)
+            *reinterpret_cast<uint2 *>(img2 + y * G::B2 + x * G::P2 + ct * 32 + kg * 8) = o;
+            if (y2 && row0 + y >= rowp + G::R2)
+                *reinterpret_cast<uint2 *>(y2 + (long)g * net::A2 + (row0 * 9 + m) * 64 + 16 * ct + 4 * kg) = o;
+        }
+    }
+    sync_lds();
+    // ---- conv3
+    {
+        constexpr int T = G::T3;
+        const uint8_t *pa[T];
+        int pos[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int m = pos[t] = G::position3(T * mh + t, n16), y = m / 7, x = m - 7 * y;
+            pa[t] = img2 + y * G::B2 + x * G::P2 + kg * 16;
+        }
+        v4f acc[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[t] = v4f{0, 0, 0, 0};
+        v8bf f[2][T];
+        auto rd = [&](int s) {   // tap s / 2, channel half s % 2
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                f[s & 1][t] = *reinterpret_cast<const v8bf *>(pa[t] + (s / 6) * G::B2 + ((s / 2) % 3) * G::P2 + (s & 1) * 64);
+        };
+        rd(0);
+#pragma unroll
+        for (int s = 0; s < 18; ++s) {
+            if (s < 17) rd(s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < T; ++t) acc[t] = mfma16(w3[s], f[s & 1][t], acc[t]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const v4f b3 = *reinterpret_cast<const v4f *>(bias + 96 + 16 * ct + 4 * kg);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int m = pos[t], y = m / 7;
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(acc[t][r] + b3[r], 0.f);
+            if (row0 + y >= rowp + R3)
+                *reinterpret_cast<uint2 *>(C123_SEG(si).y3 + (long)g * net::A3 + (row0 * 7 + m) * 64 + 16 * ct + 4 * kg) = pack4(v.x, v.y, v.z, v.w);
+        }
     }
 #undef C123_SEG
 }

@@ -71,6 +71,19 @@ def test_act_same_bits_however_many(dq, prec):
     m.close()
 
 
+# bf16: up to an observation per compute unit the conv layers are units of one workgroup each, above it the pipeline of waves;
+# fc1's tiles are the same up to 511 rows
+def test_act_same_bits_where_the_conv_launch_changes(dq):
+    m = dq.Dqn(dq.make_config(num_actions=6, dueling=1, max_act_batch=511, precision=1))
+    m.set_params(0, torch.from_numpy(synth.he_uniform_params(8, 6, 1, bias_scale=0.05)))
+    on = synth.frames(3, torch.arange(4 * 511, device="cuda"), device="cuda").view(511, 4, 84, 84)
+    a511, q511 = (t.clone() for t in m.act(on, 0.0, 99, want_q=True))
+    for E in (37, 128, 255, 256, 257, 510):
+        print("case act same bits, conv launches", E, flush=True)
+        a, q = m.act(on[511 - E:], 0.0, 99, want_q=True)
+        assert torch.equal(q, q511[511 - E:]) and torch.equal(a, a511[511 - E:]), E
+    m.close()
+
 
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("K,dueling,small", [(18, 1, 0), (4, 0, 0), (64, 1, 0), (18, 1, 1)])
