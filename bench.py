@@ -28,12 +28,19 @@ PEAK = {"fp32": 157.3e12, "bf16": 2.5e15}
 HBM_PEAK = 8.0e12
 
 
-def flops_per_launch(B, R):
+def conv_passes(kernels):
+    """Of a step's three forward passes, those in the launches of single conv layers and those in the launch of all
+    three layers: where a step has both (fp32, batches of 60 to 128) the passes over s' share the latter."""
+    return (1, 2) if "conv1_fwd" in kernels and "conv123_fwd" in kernels else (3, 3)
+
+
+def flops_per_launch(B, R, passes=(3, 3)):
     """Algorithmic flop (2*MAC) of each GEMM kernel for one training step of batch B."""
     head = 2 * 512 * R
+    single, joint = passes
     return {
-        "conv1_fwd": 3 * B * F_CONV1, "conv2_fwd": 3 * B * F_CONV2, "conv3_fwd": 3 * B * F_CONV3,
-        "conv123_fwd": 3 * B * (F_CONV1 + F_CONV2 + F_CONV3),   # the three layers in one launch
+        "conv1_fwd": single * B * F_CONV1, "conv2_fwd": single * B * F_CONV2, "conv3_fwd": single * B * F_CONV3,
+        "conv123_fwd": joint * B * (F_CONV1 + F_CONV2 + F_CONV3),   # the three layers in one launch
         "fc1_fwd": 3 * B * F_FC1, "head_train": 4 * B * head, "head_wgrad": B * head,
         "fc1_dgrad": B * F_FC1, "fc1_wgrad": B * F_FC1, "conv3_dgrad": B * F_CONV3,
         "conv3_wgrad": B * F_CONV3, "conv2_dgrad": B * F_CONV2, "conv2_wgrad": B * F_CONV2,
@@ -56,19 +63,21 @@ def bytes_per_launch(B, n_params, bf16, levels=20):
     }
 
 
-def gemm_bytes_per_launch(B, R, bf16):
+def gemm_bytes_per_launch(B, R, bf16, passes=(3, 3)):
     """Algorithmic HBM bytes (read + write) of each GEMM kernel: every operand once, no split
     partial sums, the five distinct ring frames of a transition once for the three forward passes."""
+    single, joint = passes
     e = 2 if bf16 else 4                       # activation / shadow-weight element
     a1, a2, a3, hid = 400 * 32 * e, 81 * 64 * e, 49 * 64 * e, 512 * 4
     w1, w2, w3, wf = 32 * 256 * e, 64 * 512 * e, 64 * 576 * e, 512 * 3136 * e
     frames = B * 5 * 7056 * (1 if bf16 else 2)   # fp32 path: conv1 also writes the gathered 5-frame stacks
     return {
-        "conv1_fwd": frames + w1 + 3 * B * a1,
-        "conv2_fwd": 3 * B * (a1 + a2) + w2,
-        # the fused launch keeps conv1's and conv2's output on the CU; only the training rows' copies go to memory
-        "conv123_fwd": frames + w1 + w2 + w3 + B * (a1 + a2) + 3 * B * a3,
-        "conv3_fwd": 3 * B * (a2 + a3) + w3,
+        "conv1_fwd": frames + w1 + single * B * a1,
+        "conv2_fwd": single * B * (a1 + a2) + w2,
+        # the fused launch keeps conv1's and conv2's output on the CU; only the training rows' copies go to memory, and s'
+        # alone (four frames) has none
+        "conv123_fwd": (frames + B * (a1 + a2) if joint == 3 else B * 4 * 7056) + w1 + w2 + w3 + joint * B * a3,
+        "conv3_fwd": single * B * (a2 + a3) + w3,
         "fc1_fwd": 3 * B * (a3 + hid) + wf,
         "fc1_dgrad": B * (512 * e + 2 * a3) + wf,           # dH, ReLU mask, dX
         "conv3_dgrad": B * (a3 + 2 * a2) + w3,
@@ -294,9 +303,10 @@ def kernel_table(prof, B, R, n_params, precision, step_s=None):
     that cost: the kernels of a step run back to back on one stream, so the event-timed durations
     exceed the step by (launches per step) x (cost per pair).  It is subtracted (`avg_us`; the raw
     event time stays in `avg_us_events`), so that the kernel times add up to the step."""
-    fl = flops_per_launch(B, R)
+    passes = conv_passes(prof)
+    fl = flops_per_launch(B, R, passes)
     by = bytes_per_launch(B, n_params, precision == "bf16")
-    gb = gemm_bytes_per_launch(B, R, precision == "bf16")
+    gb = gemm_bytes_per_launch(B, R, precision == "bf16", passes)
     out = {}
     overhead_s = 0.0
     if step_s is not None and prof:
