@@ -1199,8 +1199,8 @@ void backward_bf16(dqn_ctx *c, int B, const Pass &ps, int *ns1, int *ns2, int *n
         if (cap3 < 32 || cap3 > MAX_WSPLIT) cap3 = MAX_WSPLIT;
         split_rows((long)B * 49, 9, cap3, 64, &rps, ns3);
         // The input gradient takes the CUs that the weight gradient's tiles leave, so that every workgroup has one, but no more than
-        // the tiles, which end last, can spare of the L2s (steps of 256, 512, 1000: 89.2, 120.9, 185.1 us with 108, 100 and 90
-        // workgroups, 89.8, 123.3, 189.8 with 64, 90.1, 121.2, 187.2 with 128)
+        // the tiles, which end last, can spare of the L2s (steps of 256, 512, 1000: 90.2, 118.5, 181.5 us with the 102, 102 and 90
+        // workgroups of this rule, 90.8, 120.3, 186.7 with 64, 90.2, 118.7, 184.9 with 108, 91.1, 118.6, 183.7 with 128)
         const int nd = std::min({B, std::max(1, 2 * c->num_cu / 5), std::max({1, c->num_cu / 4, c->num_cu - U.on - 3 * *ns3})});
         const WgradArgs G{d3, act2, w.gp3, B, rps, net::A2, net::L3N, 1.0f};
         const c3b::Args D{d3, act2, back_of(c) + sp::C2BACK_TOTAL, d2, B, nd};

@@ -429,7 +429,6 @@ __global__ __launch_bounds__(256, 1) void k_fc1_fwd(Args A)
 
 // ---------------------------------------------------------------------------
 using g32::DConv2;
-using g32::DConv3;
 using g32::DFc1;
 
 struct DgradArgs {
@@ -819,9 +818,9 @@ __device__ __forceinline__ void wgrad_tile(const WgradArgs &A, int t, int gx, in
     }
 }
 
-// The input gradient and the weight gradient of one layer go into ONE launch of 64x64 tiles (both
+// The input gradient and the weight gradient of fc1 go into ONE launch of 64x64 tiles (both
 // read the layer's dY and depend on nothing else that is computed in the backward pass): nd
-// input-gradient tiles, then nw weight-gradient tiles.
+// input-gradient tiles, then nw weight-gradient tiles.  (The conv layers' pairs: c3b and dps.)
 struct PairGrid {
     int nd, dgx, dgz;        // input gradient: tiles, grid x and z
     int nw, wgx, wgy, wgz;   // weight gradient: tiles, grid
@@ -1656,8 +1655,10 @@ __global__ __launch_bounds__(256, 2) void k_conv_fwd_ps(Args A)
 // 2048, a step of 256) 188.8 -> 174.4; the same bits.  Consumers at a higher wave priority: 182 us for 8192.
 //
 // Replay mode: the workgroup draws its samples first (Eq.10 walk, two draws per wave and walk, all
-// eight waves), while the consumers' weight loads are in flight; the workgroups of segment 0 publish
-// the draws.  Otherwise the slots (ring mode) are copied into LDS from where a sampling kernel left them.
+// eight waves); the workgroups of segment 0 publish the draws.  The consumers request their weights behind the slot table,
+// while the producers compute the first strips: ahead of it those 136 KB per workgroup queue in front of the walk and of the
+// first pixels (a given batch of 128 69.5 -> 70.9 us, acting on 1024 38.9 -> 40.5, steps that draw 118.3 against 119.3 at 512,
+// 76.4 against 75.5 at 128, 181.0 against 180.1 at 1000).  Otherwise the slots (ring mode) are copied into LDS from where a sampling kernel left them.
 // Workgroups are dealt out per segment, so none pays the start-up twice.
 // ===========================================================================
 namespace pipe {
@@ -2484,8 +2485,7 @@ __global__ __launch_bounds__(512, 1) void k_conv123_fwd(Args A)
 // The kernel is 4x4 with stride 2, so the 20x20 input pixels fall into four stride-parity classes
 // (y%2, x%2); a pixel of class (py, px) is reached by the four taps (py + 2ty, px + 2tx) only.
 // Wave = class: 100 pixels = 7 position blocks, 4 taps x 64 co = 8 reduction steps, 64 weight
-// registers.  (The same scheme for the 3x3 stride-1 layer needs 144 weight registers per wave; it
-// is faster alone but leaves no room for the kernels that run beside it, and is not used.)
+// registers.  (c3b is this scheme for the 3x3 stride-1 layer, in 144 weight registers.)
 // ===========================================================================
 namespace dps {
 using ps::u32x4;

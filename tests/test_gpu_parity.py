@@ -101,7 +101,7 @@ def test_act_forward_parity(dq, orc, K, dueling, E, prec):
 @pytest.mark.parametrize("E,prec", [(2048, 1), (8192, 1), (2048, 0)])
 def test_act_large_batches(dq, orc, E, prec):
     """Acting at the fifth configuration's size (2048 environments) and at the library's limit (8192
-    observations: 32 samples per workgroup of the fused conv1 + conv2 launch, the most its slot table
+    observations: 32 samples per workgroup of the fused conv launch, the most its slot table
     holds).  Every row's Q-values against the oracle, the draws bit for bit."""
     print("case act large", E, prec, flush=True)
     K, dueling = 18, 1
